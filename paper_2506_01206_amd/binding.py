@@ -1,8 +1,10 @@
-"""ctypes binding of libmamba_hip.so (the C ABI in include/mamba_hip.h).
+"""Binding of libmamba_hip.so (the C ABI in include/mamba_hip.h).
 
 Argument marshalling only: shapes and dtypes are read off the tensors, output
 tensors are allocated with torch when the caller passes none, pointers and the
 current HIP stream are handed to the C function, and a non-zero status raises.
+The functions a model calls once per layer and token are marshalled natively
+(``csrc/marshal.cpp``, built as ``_marshal``), the others through ctypes.
 Every step of the computation runs in the library's kernels.  There is no
 fallback: if the library has not been built, importing this module raises.
 """
@@ -26,6 +28,8 @@ if not os.path.exists(LIB_PATH):
     raise ImportError(
         "libmamba_hip.so is missing: build it with `python -m paper_2506_01206_amd.build` "
         "(there is no CPU or PyTorch fallback for the kernels)")
+
+from . import _marshal  # noqa: E402  (built next to the library)
 
 _vp, _i64, _int, _sz = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_size_t
 
@@ -123,6 +127,14 @@ class MambaError(RuntimeError):
         super().__init__("%s failed with status %d: %s" % (fn, status, mamba_status_string(status)))
 
 
+# the natively marshalled functions call the same copy of the library
+_marshal.bind(MambaError, torch.OutOfMemoryError, *[ctypes.cast(getattr(lib, name), _vp).value for name in (
+    "mamba_conv1d_fwd", "mamba_scan_workspace_bytes", "mamba_scan_fwd", "mamba_state_step", "mamba_conv_state_step",
+    "mamba_state_fork", "mamba_linear_fwd", "mamba_rmsnorm_fwd", "mamba_block_workspace_bytes", "mamba_block_fwd",
+    "mamba_block_step", "mamba_embedding_fwd", "mamba_topk_fwd", "mamba2_ssd_workspace_bytes", "mamba2_ssd_fwd",
+    "mamba2_state_step")])
+
+
 def mamba_status_string(status: int) -> str:
     return lib.mamba_status_string(int(status)).decode()
 
@@ -172,20 +184,8 @@ def _scratch(nbytes, device, stream):
 def mamba_conv1d_fwd(x, w, bias=None, conv_state_in=None, y=None, conv_state_out=None,
                      apply_silu=True, want_state=True, stream=None):
     """x (B,L,D) f32|bf16, w (D,K) f32 -> y (B,L,D), conv_state_out (B,D,K-1)."""
-    B, L, D = x.shape
-    K = w.shape[1]
-    io = _io_code(x)
-    if y is None:
-        y = torch.empty_like(x)
-    if conv_state_out is None and want_state:
-        conv_state_out = torch.empty((B, D, K - 1), dtype=x.dtype, device=x.device)
-    st = lib.mamba_conv1d_fwd(
-        _ptr(x, name="x"), _ptr(w, torch.float32, (D, K), "w"), _ptr(bias, torch.float32, (D,), "bias"),
-        _ptr(conv_state_in, x.dtype, (B, D, K - 1), "conv_state_in"), _ptr(y, x.dtype, (B, L, D), "y"),
-        _ptr(conv_state_out, x.dtype, (B, D, K - 1), "conv_state_out"),
-        B, L, D, K, int(bool(apply_silu)), io, _stream(stream))
-    _check("mamba_conv1d_fwd", st)
-    return y, conv_state_out
+    return _marshal.conv1d_fwd(x, w, bias, conv_state_in, y, conv_state_out, apply_silu, want_state,
+                               stream and stream.cuda_stream)
 
 
 def mamba_scan_workspace_bytes(batch, L, D, N, chunk_len=0) -> int:
@@ -201,27 +201,10 @@ def mamba_scan_fwd(x, dt, A, Bm, Cm, Dskip=None, z=None, dt_bias=None, h0=None, 
                    h_final=None, workspace=None, chunk_len=0, dt_softplus=True, want_state=True,
                    stream=None):
     """x, dt, z (B,L,D); Bm, Cm (B,L,N); A (D,N) f32 -> out (B,L,D), h_final (B,D,N) f32."""
-    B, L, D = x.shape
-    N = A.shape[1]
-    io = _io_code(x)
-    if out is None:
-        out = torch.empty_like(x)
-    if h_final is None and want_state:
-        h_final = torch.empty((B, D, N), dtype=torch.float32, device=x.device)
-    need = mamba_scan_workspace_bytes(B, L, D, N, chunk_len)
-    if workspace is None and need > 0:
-        workspace = _scratch(need, x.device, stream)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib.mamba_scan_fwd(
-        _ptr(x, name="x"), _ptr(dt, x.dtype, (B, L, D), "dt"), _ptr(A, torch.float32, (D, N), "A"),
-        _ptr(Bm, x.dtype, (B, L, N), "Bm"), _ptr(Cm, x.dtype, (B, L, N), "Cm"),
-        _ptr(Dskip, torch.float32, (D,), "Dskip"), _ptr(z, x.dtype, (B, L, D), "z"),
-        _ptr(dt_bias, torch.float32, (D,), "dt_bias"), _ptr(h0, torch.float32, (B, D, N), "h0"),
-        _ptr(out, x.dtype, (B, L, D), "out"), _ptr(h_final, torch.float32, (B, D, N), "h_final"),
-        _ptr(workspace, name="workspace"), ws_bytes, B, L, D, N, int(chunk_len),
-        int(bool(dt_softplus)), io, _stream(stream))
-    _check("mamba_scan_fwd", st)
-    return out, h_final
+    if stream is not None and workspace is None:
+        workspace = _scratch(mamba_scan_workspace_bytes(*x.shape, A.shape[1], chunk_len), x.device, stream)
+    return _marshal.scan_fwd(x, dt, A, Bm, Cm, Dskip, z, dt_bias, h0, out, h_final, workspace, chunk_len, dt_softplus,
+                             want_state, stream and stream.cuda_stream)
 
 
 MAMBA_SCAN_STATIC_BYTES = 32 << 20
@@ -310,23 +293,8 @@ def mamba_state_step(h_in, x, dt, A, Bm, Cm, Dskip=None, z=None, dt_bias=None, p
                      h_out=None, out=None, dt_softplus=True, stream=None):
     """h_in (n_in,D,N) f32; x, dt, z (n_out,D); Bm, Cm (n_out,N); parent_idx int32[n_out]
     -> h_out (n_out,D,N), out (n_out,D).  Pass h_out=h_in for the in-place sequential step."""
-    n_in, D, N = h_in.shape
-    n_out = x.shape[0]
-    io = _io_code(x)
-    if h_out is None:
-        h_out = torch.empty((n_out, D, N), dtype=torch.float32, device=x.device)
-    if out is None:
-        out = torch.empty_like(x)
-    st = lib.mamba_state_step(
-        _ptr(h_out, torch.float32, (n_out, D, N), "h_out"), _ptr(h_in, torch.float32, name="h_in"),
-        _ptr(parent_idx, torch.int32, (n_out,), "parent_idx"), _ptr(x, name="x"),
-        _ptr(dt, x.dtype, (n_out, D), "dt"), _ptr(A, torch.float32, (D, N), "A"),
-        _ptr(Bm, x.dtype, (n_out, N), "Bm"), _ptr(Cm, x.dtype, (n_out, N), "Cm"),
-        _ptr(Dskip, torch.float32, (D,), "Dskip"), _ptr(z, x.dtype, (n_out, D), "z"),
-        _ptr(dt_bias, torch.float32, (D,), "dt_bias"), _ptr(out, x.dtype, (n_out, D), "out"),
-        n_out, n_in, D, N, int(bool(dt_softplus)), io, _stream(stream))
-    _check("mamba_state_step", st)
-    return h_out, out
+    return _marshal.state_step(h_in, x, dt, A, Bm, Cm, Dskip, z, dt_bias, parent_idx, h_out, out, dt_softplus,
+                               stream and stream.cuda_stream)
 
 
 def mamba_conv_state_step(h_in, conv_state_in, x, conv_w, conv_bias, dt, A, Bm, Cm, Dskip=None, z=None,
@@ -335,57 +303,15 @@ def mamba_conv_state_step(h_in, conv_state_in, x, conv_w, conv_bias, dt, A, Bm, 
     """Fork + conv step + state update of one layer in one launch.  h_in (n_in,D,N) f32, conv_state_in
     (n_in,D,K-1), x (n_out,D) the input before the conv, conv_w (D,K) f32; the rest as mamba_state_step.
     -> h_out, conv_state_out (n_out,D,K-1), out (n_out,D), x_c (n_out,D) or None."""
-    n_in, D, N = h_in.shape
-    n_out = x.shape[0]
-    K = conv_w.shape[1]
-    io = _io_code(x)
-    if h_out is None:
-        h_out = torch.empty((n_out, D, N), dtype=torch.float32, device=x.device)
-    if conv_state_out is None:
-        conv_state_out = torch.empty((n_out, D, K - 1), dtype=x.dtype, device=x.device)
-    if out is None:
-        out = torch.empty_like(x)
-    if xc_out is None and want_xc:
-        xc_out = torch.empty_like(x)
-    st = lib.mamba_conv_state_step(
-        _ptr(h_out, torch.float32, (n_out, D, N), "h_out"), _ptr(h_in, torch.float32, name="h_in"),
-        _ptr(conv_state_out, x.dtype, (n_out, D, K - 1), "conv_state_out"),
-        _ptr(conv_state_in, x.dtype, (n_in, D, K - 1), "conv_state_in"),
-        _ptr(parent_idx, torch.int32, (n_out,), "parent_idx"), _ptr(x, name="x"),
-        _ptr(conv_w, torch.float32, (D, K), "conv_w"), _ptr(conv_bias, torch.float32, (D,), "conv_bias"),
-        _ptr(dt, x.dtype, (n_out, D), "dt"), _ptr(A, torch.float32, (D, N), "A"),
-        _ptr(Bm, x.dtype, (n_out, N), "Bm"), _ptr(Cm, x.dtype, (n_out, N), "Cm"),
-        _ptr(Dskip, torch.float32, (D,), "Dskip"), _ptr(z, x.dtype, (n_out, D), "z"),
-        _ptr(dt_bias, torch.float32, (D,), "dt_bias"), _ptr(out, x.dtype, (n_out, D), "out"),
-        _ptr(xc_out, x.dtype, (n_out, D), "xc_out"),
-        n_out, n_in, D, N, K, int(bool(apply_silu)), int(bool(dt_softplus)), io, _stream(stream))
-    _check("mamba_conv_state_step", st)
-    return h_out, conv_state_out, out, xc_out
+    return _marshal.conv_state_step(h_in, conv_state_in, x, conv_w, conv_bias, dt, A, Bm, Cm, Dskip, z, dt_bias, parent_idx,
+                                    h_out, conv_state_out, out, xc_out, want_xc, apply_silu, dt_softplus,
+                                    stream and stream.cuda_stream)
 
 
 def mamba_state_fork(conv_src, ssm_src, parent_idx, conv_dst=None, ssm_dst=None, stream=None):
     """conv_src (n_layers,n_in,D,K-1) f32|bf16 or None, ssm_src (n_layers,n_in,D,N) f32 or None,
     parent_idx int32[n_out] -> gathered copies (n_layers,n_out,...)."""
-    ref = conv_src if conv_src is not None else ssm_src
-    n_layers, n_in, D = ref.shape[0], ref.shape[1], ref.shape[2]
-    n_out = parent_idx.shape[0]
-    K, N, cd = 1, 0, MAMBA_F32
-    if conv_src is not None:
-        K = conv_src.shape[3] + 1
-        cd = _io_code(conv_src)
-        if conv_dst is None:
-            conv_dst = torch.empty((n_layers, n_out, D, K - 1), dtype=conv_src.dtype, device=ref.device)
-    if ssm_src is not None:
-        N = ssm_src.shape[3]
-        if ssm_dst is None:
-            ssm_dst = torch.empty((n_layers, n_out, D, N), dtype=torch.float32, device=ref.device)
-    st = lib.mamba_state_fork(
-        _ptr(conv_dst, name="conv_dst"), _ptr(conv_src, name="conv_src"),
-        _ptr(ssm_dst, torch.float32, name="ssm_dst"), _ptr(ssm_src, torch.float32, name="ssm_src"),
-        _ptr(parent_idx, torch.int32, name="parent_idx"), n_layers, n_out, n_in, D, N, K, cd,
-        _stream(stream))
-    _check("mamba_state_fork", st)
-    return conv_dst, ssm_dst
+    return _marshal.state_fork(conv_src, ssm_src, parent_idx, conv_dst, ssm_dst, stream and stream.cuda_stream)
 
 
 def _tree_array(tree):
@@ -411,33 +337,17 @@ def mamba_tree_parents(slab, plan: TreePlan, tree, stream=None):
 def mamba_linear_fwd(x, w, bias=None, residual=None, splits=None, outs=None, stream=None):
     """x (M,K) bf16, w (N,K) bf16 -> x @ w.T (+ bias) (+ residual).  ``splits`` = widths of up to three
     output tensors that share the N columns (default: one tensor of width N); returns a tuple."""
-    M, K = x.shape
-    N = w.shape[0]
-    widths = [N] if splits is None else list(splits)
-    assert sum(widths) == N and 1 <= len(widths) <= 3
-    if outs is None:
-        outs = [torch.empty((M, n), dtype=x.dtype, device=x.device) for n in widths]
-    widths += [0] * (3 - len(widths))
-    outs = list(outs) + [None] * (3 - len(outs))
-    st = lib.mamba_linear_fwd(
-        _ptr(x, name="x"), _ptr(w, x.dtype, (N, K), "w"), _ptr(bias, torch.float32, (N,), "bias"),
-        _ptr(residual, x.dtype, (M, N), "residual"),
-        _ptr(outs[0], x.dtype, (M, widths[0]), "out0"), widths[0],
-        _ptr(outs[1], x.dtype, (M, widths[1]), "out1"), widths[1],
-        _ptr(outs[2], x.dtype, (M, widths[2]), "out2"), widths[2], M, K, _io_code(x), _stream(stream))
-    _check("mamba_linear_fwd", st)
-    return tuple(o for o in outs if o is not None)
+    widths = [w.shape[0]] if splits is None else list(splits)
+    assert sum(widths) == w.shape[0] and 1 <= len(widths) <= 3
+    widths += [-1] * (3 - len(widths))
+    o = [None] * 3 if outs is None else list(outs) + [None] * (3 - len(outs))
+    return _marshal.linear_fwd(x, w, bias, residual, o[0], widths[0], o[1], widths[1], o[2], widths[2], outs is None,
+                               stream and stream.cuda_stream)
 
 
 def mamba_rmsnorm_fwd(x, w, eps=1e-5, y=None, stream=None):
     """x (M,C) bf16, w (C) f32 -> x * rsqrt(mean(x^2) + eps) * w."""
-    M, C = x.shape
-    if y is None:
-        y = torch.empty_like(x)
-    st = lib.mamba_rmsnorm_fwd(_ptr(x, name="x"), _ptr(w, torch.float32, (C,), "w"), _ptr(y, x.dtype, (M, C), "y"),
-                               M, C, float(eps), _io_code(x), _stream(stream))
-    _check("mamba_rmsnorm_fwd", st)
-    return y
+    return _marshal.rmsnorm_fwd(x, w, eps, y, stream and stream.cuda_stream)
 
 
 class Block:
@@ -462,6 +372,7 @@ class Block:
             _ptr(w["dt_proj_w"], bf, (d_inner, dt_rank), "dt_proj_w"), _ptr(w["dt_bias"], f32, (d_inner,), "dt_bias"),
             _ptr(w["A"], f32, (d_inner, d_state), "A"), _ptr(w["Dskip"], f32, (d_inner,), "Dskip"),
             _ptr(w["out_proj_w"], bf, (d_model, d_inner), "out_proj_w"))
+        self.address = ctypes.addressof(self.c)
         self.d_model, self.d_inner, self.d_state, self.dt_rank, self.d_conv = d_model, d_inner, d_state, dt_rank, d_conv
 
 
@@ -484,81 +395,30 @@ def mamba_block_workspace_layout(block: Block, batch, L, workspace):
 def mamba_block_fwd(block: Block, hidden, hidden_out=None, conv_state_in=None, h0=None, conv_state_out=None,
                     h_final=None, workspace=None, want_state=True, stream=None):
     """hidden (B,L,d_model) bf16 -> hidden + mixer(rmsnorm(hidden)); also the conv and SSM states."""
-    B, L, dm = hidden.shape
-    D, N, K = block.d_inner, block.d_state, block.d_conv
-    if hidden_out is None:
-        hidden_out = torch.empty_like(hidden)
-    if want_state and conv_state_out is None:
-        conv_state_out = torch.empty((B, D, K - 1), dtype=hidden.dtype, device=hidden.device)
-    if want_state and h_final is None:
-        h_final = torch.empty((B, D, N), dtype=torch.float32, device=hidden.device)
-    need = mamba_block_workspace_bytes(block, B, L)
-    if workspace is None:
-        workspace = _scratch(need, hidden.device, stream)
-    st = lib.mamba_block_fwd(
-        ctypes.byref(block.c), _ptr(hidden, torch.bfloat16, name="hidden"),
-        _ptr(hidden_out, torch.bfloat16, (B, L, dm), "hidden_out"),
-        _ptr(conv_state_in, torch.bfloat16, (B, D, K - 1), "conv_state_in"),
-        _ptr(conv_state_out, torch.bfloat16, (B, D, K - 1), "conv_state_out"),
-        _ptr(h0, torch.float32, (B, D, N), "h0"), _ptr(h_final, torch.float32, (B, D, N), "h_final"),
-        _ptr(workspace, name="workspace"), workspace.numel() * workspace.element_size(), B, L, _stream(stream))
-    _check("mamba_block_fwd", st)
-    return hidden_out, conv_state_out, h_final
+    if stream is not None and workspace is None:
+        workspace = _scratch(mamba_block_workspace_bytes(block, *hidden.shape[:2]), hidden.device, stream)
+    return _marshal.block_fwd(block.address, hidden, hidden_out, conv_state_in, h0, conv_state_out, h_final, workspace,
+                              want_state, stream and stream.cuda_stream)
 
 
 def mamba_block_step(block: Block, hidden, conv_src, ssm_src, parent_idx=None, conv_dst=None, ssm_dst=None,
                      hidden_out=None, workspace=None, stream=None):
     """One token for n_out draft branches: hidden (n_out,d_model); states (n_in,D,K-1) / (n_in,D,N).
     With parent_idx the children's states go to conv_dst / ssm_dst; without, the step is in place."""
-    n_out, dm = hidden.shape
-    n_in = conv_src.shape[0]
-    D, N, K = block.d_inner, block.d_state, block.d_conv
-    if hidden_out is None:
-        hidden_out = torch.empty_like(hidden)
-    if parent_idx is None:
-        conv_dst, ssm_dst = conv_src, ssm_src
-    else:
-        if conv_dst is None:
-            conv_dst = torch.empty((n_out, D, K - 1), dtype=conv_src.dtype, device=hidden.device)
-        if ssm_dst is None:
-            ssm_dst = torch.empty((n_out, D, N), dtype=torch.float32, device=hidden.device)
-    need = mamba_block_workspace_bytes(block, n_out, 1)
-    if workspace is None:
-        workspace = _scratch(need, hidden.device, stream)
-    st = lib.mamba_block_step(
-        ctypes.byref(block.c), _ptr(hidden, torch.bfloat16, name="hidden"),
-        _ptr(hidden_out, torch.bfloat16, (n_out, dm), "hidden_out"),
-        _ptr(conv_src, torch.bfloat16, (n_in, D, K - 1), "conv_src"), _ptr(conv_dst, torch.bfloat16, (n_out, D, K - 1), "conv_dst"),
-        _ptr(ssm_src, torch.float32, (n_in, D, N), "ssm_src"), _ptr(ssm_dst, torch.float32, (n_out, D, N), "ssm_dst"),
-        _ptr(parent_idx, torch.int32, (n_out,), "parent_idx"), _ptr(workspace, name="workspace"),
-        workspace.numel() * workspace.element_size(), n_out, n_in, _stream(stream))
-    _check("mamba_block_step", st)
-    return hidden_out, conv_dst, ssm_dst
+    if stream is not None and workspace is None:
+        workspace = _scratch(mamba_block_workspace_bytes(block, hidden.shape[0], 1), hidden.device, stream)
+    return _marshal.block_step(block.address, hidden, conv_src, ssm_src, parent_idx, conv_dst, ssm_dst, hidden_out, workspace,
+                               stream and stream.cuda_stream)
 
 
 def mamba_embedding_fwd(tokens, table, out=None, stream=None):
     """tokens int32[M], table (V,dm) bf16 -> (M,dm) rows."""
-    M = tokens.shape[0]
-    V, dm = table.shape
-    if out is None:
-        out = torch.empty((M, dm), dtype=table.dtype, device=table.device)
-    st = lib.mamba_embedding_fwd(_ptr(tokens, torch.int32, (M,), "tokens"), _ptr(table, name="table"),
-                                 _ptr(out, table.dtype, (M, dm), "out"), M, V, dm, _io_code(table), _stream(stream))
-    _check("mamba_embedding_fwd", st)
-    return out
+    return _marshal.embedding_fwd(tokens, table, out, stream and stream.cuda_stream)
 
 
 def mamba_topk_fwd(logits, k, idx=None, val=None, stream=None):
     """logits (M,V) bf16 -> idx int32 (M,k), val float32 (M,k), largest first, ties to the lower index."""
-    M, V = logits.shape
-    if idx is None:
-        idx = torch.empty((M, k), dtype=torch.int32, device=logits.device)
-    if val is None:
-        val = torch.empty((M, k), dtype=torch.float32, device=logits.device)
-    st = lib.mamba_topk_fwd(_ptr(logits, name="logits"), _ptr(idx, torch.int32, (M, k), "idx"),
-                            _ptr(val, torch.float32, (M, k), "val"), M, V, int(k), _io_code(logits), _stream(stream))
-    _check("mamba_topk_fwd", st)
-    return idx, val
+    return _marshal.topk_fwd(logits, k, idx, val, stream and stream.cuda_stream)
 
 
 def mamba2_ssd_workspace_bytes(batch, L, H, P, N) -> int:
@@ -569,41 +429,14 @@ def mamba2_ssd_fwd(x, dt, A, Bm, Cm, Dskip=None, z=None, dt_bias=None, h0=None, 
                    workspace=None, want_state=True, dt_softplus=True, stream=None):
     """Scalar-decay layer core: x, z (B,L,H,P) bf16; dt (B,L,H); Bm, Cm (B,L,N); A, Dskip, dt_bias (H) f32;
     h0 (B,H,P,N) f32 -> out (B,L,H,P), h_final (B,H,P,N)."""
-    B, L, H, P = x.shape
-    N = Bm.shape[-1]
-    if out is None:
-        out = torch.empty_like(x)
-    if want_state and h_final is None:
-        h_final = torch.empty((B, H, P, N), dtype=torch.float32, device=x.device)
-    need = mamba2_ssd_workspace_bytes(B, L, H, P, N)
-    if workspace is None:
-        workspace = _scratch(need, x.device, stream)
-    st = lib.mamba2_ssd_fwd(
-        _ptr(x, name="x"), _ptr(dt, x.dtype, (B, L, H), "dt"), _ptr(A, torch.float32, (H,), "A"),
-        _ptr(Bm, x.dtype, (B, L, N), "Bm"), _ptr(Cm, x.dtype, (B, L, N), "Cm"), _ptr(Dskip, torch.float32, (H,), "Dskip"),
-        _ptr(z, x.dtype, (B, L, H, P), "z"), _ptr(dt_bias, torch.float32, (H,), "dt_bias"),
-        _ptr(h0, torch.float32, (B, H, P, N), "h0"), _ptr(out, x.dtype, (B, L, H, P), "out"),
-        _ptr(h_final, torch.float32, (B, H, P, N), "h_final"), _ptr(workspace, name="workspace"),
-        workspace.numel() * workspace.element_size(), B, L, H, P, N, int(bool(dt_softplus)), _io_code(x), _stream(stream))
-    _check("mamba2_ssd_fwd", st)
-    return out, h_final
+    if stream is not None and workspace is None:
+        workspace = _scratch(mamba2_ssd_workspace_bytes(*x.shape, Bm.shape[-1]), x.device, stream)
+    return _marshal.ssd_fwd(x, dt, A, Bm, Cm, Dskip, z, dt_bias, h0, out, h_final, workspace, want_state, dt_softplus,
+                            stream and stream.cuda_stream)
 
 
 def mamba2_state_step(h_in, x, dt, A, Bm, Cm, Dskip=None, z=None, dt_bias=None, parent_idx=None, h_out=None, out=None,
                       dt_softplus=True, stream=None):
     """h_in (n_in,H,P,N) f32; x, z (n_out,H,P); dt (n_out,H); Bm, Cm (n_out,N) -> h_out (n_out,H,P,N), out (n_out,H,P)."""
-    n_in, H, P, N = h_in.shape
-    n_out = x.shape[0]
-    if h_out is None:
-        h_out = torch.empty((n_out, H, P, N), dtype=torch.float32, device=x.device)
-    if out is None:
-        out = torch.empty_like(x)
-    st = lib.mamba2_state_step(
-        _ptr(h_out, torch.float32, (n_out, H, P, N), "h_out"), _ptr(h_in, torch.float32, name="h_in"),
-        _ptr(parent_idx, torch.int32, (n_out,), "parent_idx"), _ptr(x, name="x"), _ptr(dt, x.dtype, (n_out, H), "dt"),
-        _ptr(A, torch.float32, (H,), "A"), _ptr(Bm, x.dtype, (n_out, N), "Bm"), _ptr(Cm, x.dtype, (n_out, N), "Cm"),
-        _ptr(Dskip, torch.float32, (H,), "Dskip"), _ptr(z, x.dtype, (n_out, H, P), "z"),
-        _ptr(dt_bias, torch.float32, (H,), "dt_bias"), _ptr(out, x.dtype, (n_out, H, P), "out"),
-        n_out, n_in, H, P, N, int(bool(dt_softplus)), _io_code(x), _stream(stream))
-    _check("mamba2_state_step", st)
-    return h_out, out
+    return _marshal.ssd_step(h_in, x, dt, A, Bm, Cm, Dskip, z, dt_bias, parent_idx, h_out, out, dt_softplus,
+                             stream and stream.cuda_stream)

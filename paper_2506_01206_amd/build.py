@@ -1,15 +1,18 @@
-"""Build libmamba_hip.so (gfx950) in-tree with hipcc.  Usage: python -m paper_2506_01206_amd.build"""
+"""Build libmamba_hip.so (gfx950, hipcc) and the binding's marshalling module (host C++) in-tree.
+Usage: python -m paper_2506_01206_amd.build"""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmamba_hip.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 SOURCES = ["api.cpp", "sd_tree_search.cpp", "conv1d.hip", "scan.hip", "scan_direct.hip", "scan_lanes.hip", "strided.hip", "step.hip", "fork.hip", "linear.hip", "norm.hip", "vocab.hip", "ssd.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-fp32 VALU instructions are switched off for every device function
@@ -31,14 +34,31 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_marshal() -> None:
+    """The native half of binding.py: host code against torch's C++ headers (device memory and streams only)."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = MARSHAL + ".tmp%d" % os.getpid()
+    subprocess.check_call(
+        [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+         "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
+        + ["-isystem" + d for d in (os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                                    sysconfig.get_paths()["include"], os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"))]
+        + [os.path.join(CSRC, "marshal.cpp"), "-o", tmp, "-L" + os.path.join(root, "lib")]
+        + ["-l" + n for n in ("torch_python", "torch_cpu", "torch", "c10", "c10_hip")])
+    os.replace(tmp, MARSHAL)
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every source and link libmamba_hip.so next to this file."""
+    """Compile every source, link libmamba_hip.so next to this file, and build the marshalling module."""
     os.makedirs(OBJDIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+        marshal = ex.submit(_build_marshal)
         objs = list(ex.map(_compile, SOURCES))
     tmp = LIB + ".tmp%d" % os.getpid()
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs)
     os.replace(tmp, LIB)
+    marshal.result()
     if verbose:
         print("built", LIB)
     return LIB
