@@ -42,9 +42,8 @@ __device__ __forceinline__ void lds_barrier_linear()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// tile counts from which each kernel shape takes over (measured crossovers, see launch_linear)
-constexpr int64_t kTilesBig = 512, kTilesMid = 512, kTilesWide = 96, kTilesWideSmall = 192, kTilesWideSmallMax = 512,
-                  kTilesDeep = 513;
+// tile counts from which each register-staged tile shape takes over (measured crossovers, see launch_linear)
+constexpr int64_t kTilesBig = 512, kTilesMid = 512, kTilesDeep = 513;
 
 struct OutSplit {
     bf16_t *ptr[3];
@@ -236,9 +235,9 @@ linear_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, const 
 // ---------------------------------------------------------------------------------------------------
 // Many rows (the projections of a long context).  A 128 x 128 tile asks the L1 for 512 bytes per k and
 // multiplies 8 cycles per k on every SIMD, so the cache, which delivers 64 bytes a cycle, can feed the
-// matrix cores half the time at best.  This kernel takes 256 x 256 (or 256 x 128) tiles, one workgroup
-// per CU and one wavefront per SIMD, each wavefront a 128 x 128 (128 x 64) part held in 256 (128)
-// accumulator registers: per k the same 8 (6) cycles of cache traffic now feed 32 (16) cycles of MFMA.
+// matrix cores half the time at best.  This kernel takes 256 x 256 tiles, one workgroup per CU and one
+// wavefront per SIMD, each wavefront a 128 x 128 part held in 256 accumulator registers: per k the same
+// 8 cycles of cache traffic now feed 32 cycles of MFMA.
 // (With BM = 128 it also runs 128 x 128 tiles, two workgroups to a CU, for products too small to give every CU
 // a 256-row tile: the feeding scheme below, not the tile size, is what those gain from.)
 //
@@ -254,11 +253,13 @@ linear_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, const 
 // right after it into the stage just freed and has a whole slab of multiplications to arrive.
 // The product is formed transposed (w fragments as the row operand), so that a lane's four accumulators
 // of a group are four adjacent output columns of one row and leave as one 8-byte write.
-// Requires M % 256 == 0, N % BN == 0, K % 128 == 0 and output widths that are multiples of 8.
+// Requires M >= BM, N % BN == 0, K % 128 == 0 and output widths that are multiples of 8.  The last row block of an M
+// that is not a multiple of BM is moved back to end at M: it works on a full tile of rows that exist and stores only
+// the rows the block before it does not have.
 // grid: 8 * ceil(tiles / 8) workgroups; consecutive workgroups go to different XCDs, so tile numbers are
 // dealt such that each XCD (each L2) works on a contiguous range of tiles, column tiles of one row block
 // adjacent.
-constexpr int kWideBM = 256, kWideBK = 64, kWideRow = kWideBK * 2;
+constexpr int kWideBK = 64, kWideRow = kWideBK * 2;
 
 // 16 bytes per lane from base + lane_off into LDS at lds_addr + 16 * lane (lds_addr wave-uniform)
 __device__ __forceinline__ void load_to_lds16(const char *base, uint32_t lane_off, uint32_t lds_addr)
@@ -284,7 +285,9 @@ linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
     const int per_xcd = (n_tiles + 7) / 8;
     const int tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
     if (tile >= n_tiles) return;
-    const int64_t m0 = (int64_t)(tile / tiles_n) * BM, n0 = (int64_t)(tile % tiles_n) * BN;
+    const int64_t m_first = (int64_t)(tile / tiles_n) * BM, n0 = (int64_t)(tile % tiles_n) * BN;
+    const int64_t m0 = m_first + BM <= M ? m_first : M - BM;
+    const int dead = (int)(m_first - m0);                         // leading rows that belong to the row block before
 
     // Loads: wavefront v takes the row groups g = 4 j + v (rows 8 g .. 8 g + 7 of the stage; x rows first, then w);
     // lane l lands in row 8 g + l / 8, slot l % 8, and therefore fetches slot (l % 8) ^ ((4 (g & 1) + l / 16) & 7)
@@ -417,7 +420,8 @@ linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
             const int c = tid + i * 256, row = c / kCpr, cc = c % kCpr;
             int64_t col;
             const int sp = locate(out, n0 + cc * 8, &col);
-            res[i] = *reinterpret_cast<const u32x4 *>(residual + (m0 + row) * out.width[sp] + col);
+            // (a dead row is not read: where the residual is the output itself its owner may be writing it)
+            res[i] = *reinterpret_cast<const u32x4 *>(residual + (m0 + (row < dead ? dead : row)) * out.width[sp] + col);
         }
     }
     lds_barrier_linear();                                         // the stages are free for the output tile (the requests stay in flight)
@@ -441,9 +445,7 @@ linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
             __builtin_amdgcn_sched_barrier(0);                    // one group at a time: the accumulators stay where they are until used
         }
     lds_barrier_linear();
-#pragma unroll
-    for (int i = 0; i < kChunks; ++i) {
-        const int c = tid + i * 256, row = c / kCpr, cc = c % kCpr;
+    auto store_chunk = [&](int i, int row, int cc) __attribute__((always_inline)) {
         uint4 v = *reinterpret_cast<const uint4 *>(lds + row * kOutRow + cc * 16);
         int64_t col;
         const int sp = locate(out, n0 + cc * 8, &col);
@@ -456,6 +458,14 @@ linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
             v.w = f32x2_to_bf16x2(bf16_lo(v.w) + bf16_lo(r.w), bf16_hi(v.w) + bf16_hi(r.w));
         }
         *reinterpret_cast<uint4 *>(out.ptr[sp] + off) = v;
+    };
+    if (dead == 0) {
+#pragma unroll
+        for (int i = 0; i < kChunks; ++i) store_chunk(i, (tid + i * 256) / kCpr, (tid + i * 256) % kCpr);
+    } else {
+#pragma unroll
+        for (int i = 0; i < kChunks; ++i)
+            if ((tid + i * 256) / kCpr >= dead) store_chunk(i, (tid + i * 256) / kCpr, (tid + i * 256) % kCpr);
     }
 }
 
@@ -862,27 +872,24 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
         return hipGetLastError();
     }
     auto tiles = [&](int64_t bm, int64_t bn) { return ((N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
-    if (vec && a.M % 128 == 0 && a.K % (2 * kWideBK) == 0 && a.K >= 2 * kWideBK) {
-        // The memory-to-LDS kernel with 128 x 128 tiles (two workgroups to a CU) from 192 tiles on, while 256 x 128
-        // ones would come to fewer than two per CU: in_proj on 2048 tokens 17.6 -> 16.3 us, on 4096 tokens 32 -> 29 us,
-        // out_proj on 4096 tokens 22 -> 16 us.  (With fewer tiles it wins only on operands that are already in cache
-        // -- out_proj on 2048 tokens, 96 tiles: 17.2 -> 12.7 us alone in a loop, but 17.6 -> 19.5 us inside the block,
-        // where two 32 KiB stages per CU are too little in flight for operands that come from memory.)  Beyond that
-        // 256-row tiles (in_proj on 32768 tokens 222 -> 172 us), 256 columns wide unless that leaves a ragged last round.
-        const bool m256 = a.M % kWideBM == 0;
-        const int64_t t256 = m256 && N % 256 == 0 ? (a.M / kWideBM) * (N / 256) : 0;
-        const int64_t t128 = m256 && N % 128 == 0 ? (a.M / kWideBM) * (N / 128) : 0;
-        const int64_t t128s = N % 128 == 0 ? (a.M / 128) * (N / 128) : 0;
-        if (t128s >= kTilesWideSmall && t128 < kTilesWideSmallMax) {
-            linear_wide_kernel<128, 128><<<(unsigned)(8 * ((t128s + 7) / 8)), 256, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, (int)(N / 128), (int)t128s);
-            return hipGetLastError();
-        }
-        if (t256 >= kTilesWide && (t256 % 256 == 0 || t256 >= 4 * 256 || t128 == 0)) {
+    if (vec && N % 128 == 0 && a.M >= 128 && a.K % (2 * kWideBK) == 0) {
+        // The memory-to-LDS kernel, on any number of rows.  Measured inside the 24-block prefill (alone in a loop the
+        // wide tiles look better than they are there: their denser matrix work lowers the clock for what runs between
+        // them).  256 x 256 tiles, one to a CU, where they fill at least nine tenths of the rounds they take (32768 rows
+        // x 3072 columns 184 us against 227 on the register-staged tiles).  Otherwise 128 x 128 tiles, two to a CU: with
+        // a long k loop from half a tile per CU on (8000 rows x 768 columns, K = 1536: 36.7 -> 28.5 us, the whole
+        // prefill 5.70 -> 5.54 ms; 2000 rows, 96 tiles, 19.5 us on the deep register-staged tiles against 25), with a
+        // short one from one tile per CU to two (1500 to 2500 rows x 3072 columns, K = 768: prefill 2 to 3 % faster;
+        // 8000 rows, three rounds: 53.7 us register-staged against 55.5).
+        const int64_t t256 = a.M >= 256 && N % 256 == 0 ? ((a.M + 255) / 256) * (N / 256) : 0;
+        const int64_t t128 = ((a.M + 127) / 128) * (N / 128);
+        const int64_t rounds = (t256 + 255) / 256;
+        if (t256 >= 9 * 256 / 10 && 10 * t256 >= 9 * 256 * rounds) {
             linear_wide_kernel<256, 256><<<(unsigned)(8 * ((t256 + 7) / 8)), 256, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, (int)(N / 256), (int)t256);
             return hipGetLastError();
         }
-        if (t128 >= kTilesWide) {
-            linear_wide_kernel<256, 128><<<(unsigned)(8 * ((t128 + 7) / 8)), 256, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, (int)(N / 128), (int)t128);
+        if (a.K >= 1024 ? t128 >= 128 : t128 >= 256 && t128 <= 512) {
+            linear_wide_kernel<128, 128><<<(unsigned)(8 * ((t128 + 7) / 8)), 256, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, (int)(N / 128), (int)t128);
             return hipGetLastError();
         }
     }

@@ -1140,6 +1140,14 @@ def test_linear_against_oracle(m, M, N, K, splits):
         assert_close(values(to_host(o)), oracle.linear(W(x), W(w), None, W(res)), TOL[synth.BF16], "linear + residual")
 
 
+@pytest.mark.parametrize("M,N,K,splits", [(129, 32768, 128, None), (5003, 3072, 256, (1536, 1536)), (10241, 1536, 128, None),
+                                          (2177, 1152, 1024, None), (4001, 768, 1536, None), (3999, 1280, 128, (1000, 280))])
+def test_linear_wide_tiles_ragged_rows(m, M, N, K, splits):
+    """Row counts that leave the memory-to-LDS kernels a last row block shared with the one before it (from one row of
+    its own to all but one): results against the oracle, and the residual added in place exactly once per row."""
+    test_linear_against_oracle(m, M, N, K, splits)
+
+
 def test_linear_at_block_bench_size_sampled_rows(m):
     """in_proj and out_proj of the whole-block leg of bench.py (32768 tokens, Mamba-130M widths), in the launch
     configuration it times; rows are independent, so the oracle computes a seeded sample of them (every row block
