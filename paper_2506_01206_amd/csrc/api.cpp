@@ -486,7 +486,7 @@ namespace {
 struct BlockBuffers {
     char *a, *b, *c, *d;        // four (rows, d_inner) bf16 buffers: x then dt | z | x_c | normed then y
     char *dtl, *bm, *cm;        // (rows, dt_rank), (rows, d_state), (rows, d_state) bf16
-    char *xpart;                // one token on up to 64 rows: (rows, dt_rank + 2 d_state, d_inner / 32) float32 partial sums
+    char *xpart;                // one token on up to 64 rows: (rows, d_inner / 16, dt_rank + 2 d_state) float32 partial sums
     char *scan_ws;
     size_t scan_ws_bytes, total;
 };
@@ -511,7 +511,7 @@ bool block_layout(const mamba_block_params_t *p, int64_t batch, int64_t L, void 
     bb->a = take(big); bb->b = take(big); bb->c = take(big); bb->d = take(big);
     bb->dtl = take(dtl); bb->bm = take(bc); bb->cm = take(bc);
     int64_t xp = 0;
-    if (L == 1 && rows <= 64 && !size3(p->d_inner / 32 + 1, rows, p->dt_rank + 2 * p->d_state, 4, &xp)) return false;
+    if (L == 1 && rows <= 64 && !size3(p->d_inner / 16 + 1, rows, p->dt_rank + 2 * p->d_state, 4, &xp)) return false;
     bb->xpart = take(xp);
     bb->scan_ws = take((int64_t)sws);
     bb->scan_ws_bytes = sws;
@@ -649,10 +649,10 @@ int mamba_block_step(const mamba_block_params_t *p, const void *hidden, void *hi
         in.conv_parent = parent_idx;
         in.conv_n_in = n_in;
         in.conv_k = p->d_conv;
-        // With a wide enough model the x projection rides along as well: every in_proj workgroup multiplies its 32
-        // finished x_c columns into it and the state step adds the partial sums up, which takes the launch of a
-        // product with three output tiles out of the chain.
-        const bool fuse_xproj = p->d_model > 512 && Di % 128 == 0 && R + 2 * N <= 256;
+        // The x projection rides along as well: every in_proj workgroup multiplies its 16 finished x_c columns into it
+        // and the state step adds the partial sums up, which takes the launch of a product with few output tiles out of
+        // the chain.
+        const bool fuse_xproj = Di % 16 == 0 && R + 2 * N <= 256;
         if (fuse_xproj) {
             in.xproj_w = p->x_proj_w;
             in.xproj_part = reinterpret_cast<float *>(bb.xpart);
@@ -668,7 +668,7 @@ int mamba_block_step(const mamba_block_params_t *p, const void *hidden, void *hi
         sa.dt_rank = R;
         if (fuse_xproj) {
             sa.xpart = reinterpret_cast<const float *>(bb.xpart);
-            sa.n_parts = (int)(Di / 32);
+            sa.n_parts = (int)(Di / 16);
         }
         if (hipError_t e = launch_step(sa, stream)) return (int)e;
         return mamba_linear_fwd(bb.d, p->out_proj_w, nullptr, hidden, hidden_out, p->d_model, nullptr, 0, nullptr, 0, n_out, Di, io, hip_stream);

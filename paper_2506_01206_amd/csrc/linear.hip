@@ -44,6 +44,7 @@ __device__ __forceinline__ void lds_barrier_linear()
 
 // tile counts from which each register-staged tile shape takes over (measured crossovers, see launch_linear)
 constexpr int64_t kTilesBig = 512, kTilesMid = 512, kTilesDeep = 513;
+constexpr int64_t kTilesResident = 256;                           // one workgroup per CU
 
 struct OutSplit {
     bf16_t *ptr[3];
@@ -470,17 +471,15 @@ linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Few rows (M <= 64: the branches of one draft position, Sec. 4.1).  The product is then bound by
-// reading w once and by latency, so the work is cut finely: one workgroup per 32 output columns,
-// its NW wavefronts take the 64-wide k blocks of the row round robin and their partial 32 x 32 tiles
-// are added through LDS.  A wavefront fetches a k block of 32 rows x 128 bytes with four 16-byte
-// loads per lane, eight lanes on one row, so that every load instruction covers whole 128-byte
-// lines; the block then goes through a 4 KiB LDS patch private to the wavefront (16-byte slots
-// xor-swizzled by the row, conflict-free both ways) and comes back as MFMA fragments: lane (r, h)
-// takes the slots 4 h .. 4 h + 3 of row r, one per k16 step.  Both operands use the same slot
-// order, so the sum over k is complete.  (Run over a grid of row blocks for more rows with a long k loop and
-// few output tiles it measured slower than the tiled kernel with 256-deep slabs: x_proj 10.4 vs 10.5 us,
-// out_proj 30 vs 17 us on 2048 tokens.)
+// Few output tiles and a long k loop (the projections of a short context, x_proj of one of a few thousand tokens): walked
+// slab by slab such a product takes a memory latency per slab on a part of the chip, so here a workgroup's whole k range
+// is in flight at once.  One workgroup per 32 output columns and 32 MB rows; its eight wavefronts take the 64-wide k
+// blocks round robin, three of them at a time, and their partial tiles are added through LDS.  A wavefront fetches a k
+// block of 32 rows x 128 bytes with four 16-byte loads per lane, eight lanes on one row, so that every load instruction
+// covers whole 128-byte lines (what the address path takes time for: about 4 cycles a line); the block then goes through
+// a 4 KiB LDS patch private to the wavefront (16-byte slots xor-swizzled by the row, conflict-free both ways) and comes
+// back as MFMA fragments: lane (r, h) takes the slots 4 h .. 4 h + 3 of row r, one per k16 step.  Both operands use the
+// same slot order, so the sum over k is complete.
 // grid: (ceil(N / 32), ceil(M / (32 MB)))
 __device__ __forceinline__ void wave_sync()
 {
@@ -489,339 +488,357 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int NW, int MB>
-__global__ void __launch_bounds__(NW * 64)
-linear_skinny_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, const float *__restrict__ bias,
-                     const bf16_t *residual, OutSplit out, int64_t M, int64_t N, int64_t K,
-                     const float *__restrict__ norm_w, float eps, ConvTail conv, XprojTail xp)
+template <int MB>
+__global__ void __launch_bounds__(512)
+linear_split_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, const float *__restrict__ bias,
+                    const bf16_t *residual, OutSplit out, int64_t M, int64_t N, int64_t K)
 {
-    // LDS: in the main loop two 4 KiB patches per wavefront (w block, x block); afterwards the same
-    // memory holds the partial tiles, the sums of x^2 (with norm_w) and the row factors
-    __shared__ __attribute__((aligned(16))) unsigned char lds[NW * 8192];
-    float (*part)[16][64] = reinterpret_cast<float (*)[16][64]>(lds);
-    float (*ssq)[MB][4][64] = reinterpret_cast<float (*)[MB][4][64]>(lds + NW * 4096);
-    float *row_scale = reinterpret_cast<float *>(lds + NW * 4096 + NW * MB * 1024);
-    static_assert(NW * 4096 + NW * MB * 1024 + 128 <= NW * 8192, "LDS reuse");
-    // with eight wavefronts there is room for the finished columns of the first output (float32), which the
-    // projection tail multiplies on
-    constexpr bool kTailRoom = NW * 4096 + NW * MB * 1024 + 128 + MB * 4096 <= NW * 8192;
-    float (*xc)[32][32] = reinterpret_cast<float (*)[32][32]>(lds + NW * 4096 + NW * MB * 1024 + 128);
+    constexpr int NW = 8, G = 3;
+    constexpr int OPT = MB * 1024 / (NW * 64);                    // outputs per thread
+    // in the main loop 1 + MB patches of 4 KiB per wavefront (w block, x blocks), afterwards the partial tiles
+    __shared__ __attribute__((aligned(16))) unsigned char lds[NW * (1 + MB) * 4096];
+    float (*part)[MB * 16][64] = reinterpret_cast<float (*)[MB * 16][64]>(lds);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r = lane & 31, h = lane >> 5;                       // fragment view: row, k half
     const int lrow = lane >> 3, lch = lane & 7;                   // load view: row (+ 8 i), 16-byte slot
     const int64_t n0 = (int64_t)blockIdx.x * 32, m0 = (int64_t)blockIdx.y * (32 * MB);
     const int64_t kchunks = K / 8, kblocks = (K + 63) / 64;
-    uint4 *patch_w = reinterpret_cast<uint4 *>(lds + wave * 8192), *patch_x = patch_w + 256;
+    uint4 *patch_w = reinterpret_cast<uint4 *>(lds + wave * (1 + MB) * 4096), *patch_x = patch_w + 256;
     const int put = lrow * 8 + (lch ^ lrow);                      // + 64 i: slot of row lrow + 8 i ((lrow + 8 i) & 7 == lrow)
     int get[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) get[s] = r * 8 + ((4 * h + s) ^ (r & 7));
 
-    const uint4 *wptr[4];
-    const uint4 *xptr[MB][4];
-    bool xlive[MB][4];
+    const uint4 *wptr[4], *xptr[MB][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        int64_t wr = n0 + lrow + 8 * i;
-        wr = wr < N ? wr : N - 1;                                 // columns past N repeat the last one, never stored
-        wptr[i] = reinterpret_cast<const uint4 *>(w + wr * K);
+        const int64_t n = n0 + lrow + 8 * i;                      // columns past N and rows past M repeat the last one, never stored
+        wptr[i] = reinterpret_cast<const uint4 *>(w + (n < N ? n : N - 1) * K);
 #pragma unroll
         for (int b = 0; b < MB; ++b) {
             const int64_t m = m0 + b * 32 + lrow + 8 * i;
-            xlive[b][i] = m < M;                                  // rows past M stay zero
-            xptr[b][i] = reinterpret_cast<const uint4 *>(x + (xlive[b][i] ? m : 0) * K);
+            xptr[b][i] = reinterpret_cast<const uint4 *>(x + (m < M ? m : M - 1) * K);
         }
+    }
+    // output o = tid + 512 j: row block o / 1024, accumulator i = o / 64 % 16 of lane o % 64; what it needs besides its
+    // sum is fetched ahead of the main loop
+    int64_t off[OPT];
+    int sp[OPT];
+    float bv[OPT];
+    uint16_t res[OPT];
+#pragma unroll
+    for (int j = 0; j < OPT; ++j) {
+        const int o = tid + j * 512, i = (o >> 6) & 15;
+        const int64_t m = m0 + (o >> 10) * 32 + 8 * (i >> 2) + 4 * h + (i & 3), n = n0 + r;
+        bv[j] = 0.0f;
+        res[j] = 0;
+        sp[j] = -1;
+        off[j] = 0;
+        if (m >= M || n >= N) continue;
+        int64_t col;
+        sp[j] = locate(out, n, &col);
+        off[j] = m * (sp[j] == 0 ? out.width[0] : sp[j] == 1 ? out.width[1] : out.width[2]) + col;
+        if (bias) bv[j] = bias[n];
+        if (residual) res[j] = residual[off[j]];
     }
     f32x16 acc[MB];
 #pragma unroll
     for (int b = 0; b < MB; ++b)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[b][i] = 0.0f;
-    float ss[MB][4];
-#pragma unroll
-    for (int b = 0; b < MB; ++b)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) ss[b][i] = 0.0f;
 
-    // What an output element needs besides the sums: bias, residual, and for the conv tail the carried
-    // window (through the parent index), the taps and the conv bias.  With one row block these loads
-    // are issued ahead of and inside the main loop, so that the epilogue does not wait for them: first what needs no
-    // parent index, and the index itself; then, once the first group of the main loop's loads is on its way, the
-    // window behind the index.  No fetch is used where it is issued (a value converted, selected or compared there
-    // is waited for there, one memory latency each): raw bits are kept, taps and window entries a short conv does not
-    // have re-read the last one and are dropped at use, and the width and pointer of an output tensor are picked
-    // from values held in registers (indexing the argument struct by a per-lane number goes through memory).
-    struct Tail {
-        float bias, cb, wk[4];
-        uint16_t res, carried[3];
-        int32_t parent;
-    };
-    int64_t ow0 = out.width[0], ow1 = out.width[1], ow2 = out.width[2];
-    bf16_t *op0 = out.ptr[0], *op1 = out.ptr[1], *op2 = out.ptr[2];
-    asm volatile("" : "+s"(ow0), "+s"(ow1), "+s"(ow2), "+s"(op0), "+s"(op1), "+s"(op2));
-    auto locate_tail = [&](int64_t n, int64_t *col, int64_t *width, bf16_t **ptr) {
-        int64_t c = n, wd = ow0;
-        bf16_t *pt = op0;
-        int sp = 0;
-        if (c >= ow0) {
-            c -= ow0; sp = 1; wd = ow1; pt = op1;
-            if (c >= ow1) { c -= ow1; sp = 2; wd = ow2; pt = op2; }
-        }
-        *col = c; *width = wd; *ptr = pt;
-        return sp;
-    };
-    constexpr int OPT = 16 * 64 / (NW * 64);                      // outputs per thread and row block
-    auto tail_first = [&](int b, int j, Tail &t) {
-        t.bias = t.cb = 0.0f;
-        t.res = 0;
-        t.parent = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) t.wk[k] = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) t.carried[k] = 0;
-        const int o = tid + j * NW * 64, i = o >> 6, l = o & 63;
-        const int64_t m = m0 + b * 32 + 8 * (i >> 2) + 4 * (l >> 5) + (i & 3), n = n0 + (l & 31);
-        if (m >= M || n >= N) return;
-        if (bias) t.bias = bias[n];
-        int64_t col, width;
-        bf16_t *ptr;
-        const int sp = locate_tail(n, &col, &width, &ptr);
-        if (residual) t.res = residual[m * width + col];
-        if (conv.w && sp == 0 && conv.parent) t.parent = conv.parent[m];
-    };
-    // (all parent indices are turned into addresses before the first window fetch: the wait for an index also
-    // waits for every fetch issued before it)
-    struct WinAddr {
-        int64_t win, col;                                         // window's first element in conv.src; channel
-        bool on;
-    };
-    auto tail_address = [&](int b, int j, const Tail &t) {
-        WinAddr a;
-        const int o = tid + j * NW * 64, i = o >> 6, l = o & 63;
-        const int64_t m = m0 + b * 32 + 8 * (i >> 2) + 4 * (l >> 5) + (i & 3), n = n0 + (l & 31);
-        a.on = !(m >= M || n >= N || !conv.w || n >= ow0);
-        a.col = a.on ? n : 0;
-        const int64_t p = conv.parent ? (int64_t)t.parent : m;
-        const bool p_ok = !conv.parent || (p >= 0 && p < conv.n_in);
-        a.win = (((a.on && p_ok) ? p : 0) * ow0 + a.col) * (conv.k - 1);
-        return a;
-    };
-    auto tail_window = [&](const WinAddr &a, Tail &t) {
-        if (!a.on) return;
-        const int H = conv.k - 1;
-        if (conv.bias) t.cb = conv.bias[a.col];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) t.wk[k] = conv.w[a.col * conv.k + (k <= H ? k : H)];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) t.carried[k] = conv.src[a.win + (k < H ? k : H - 1)];
-    };
-    auto tail_windows = [&](int b, Tail *ts) {
-        if (!conv.w) return;
-        WinAddr wa[OPT];
-#pragma unroll
-        for (int j = 0; j < OPT; ++j) wa[j] = tail_address(b, j, ts[j]);
-#pragma unroll
-        for (int j = 0; j < OPT; ++j) asm volatile("" : "+v"(wa[j].win));  // formed here, not where it is first used
-#pragma unroll
-        for (int j = 0; j < OPT; ++j) tail_window(wa[j], ts[j]);
-    };
-    // projection tail: thread (group g, output j) of NW * 64 / n groups takes rows g, g + groups, ... of the
-    // block; its 32 weights are fetched here, ahead of the main loop
-    uint4 xw4[4] = {make_uint4(0, 0, 0, 0), make_uint4(0, 0, 0, 0), make_uint4(0, 0, 0, 0), make_uint4(0, 0, 0, 0)};
-    const bool tail_on = kTailRoom && xp.w && n0 < out.width[0];  // uniform: a column block lies in one output tensor
-    const int tail_groups = tail_on ? (NW * 64) / xp.n : 0, tail_g = tail_on ? tid / xp.n : 0, tail_j = tail_on ? tid - tail_g * xp.n : 0;
-    if (tail_on && tail_g < tail_groups) {
-        const uint4 *wr = reinterpret_cast<const uint4 *>(xp.w + (int64_t)tail_j * xp.ldw + n0);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) xw4[c] = wr[c];
-    }
-    Tail early[OPT];
-    bool window_pending = MB == 1;
-    if constexpr (MB == 1) {
-#pragma unroll
-        for (int j = 0; j < OPT; ++j) tail_first(0, j, early[j]);
-    }
-
-    // A wavefront's k blocks are taken G at a time: all loads of a group are issued before its first
-    // MFMA, so that a row of up to 64 * NW * G values costs one trip to memory, not one per block.
-    constexpr int G = MB == 1 ? 3 : 2;
-    for (int64_t blk0 = wave; blk0 < kblocks; blk0 += (int64_t)NW * G) {
+    for (int64_t blk0 = wave; blk0 < kblocks; blk0 += NW * G) {
         uint4 wf[G][4], xf[G][MB][4];
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const int64_t c = (blk0 + (int64_t)g * NW) * 8 + lch;
+            const int64_t c = (blk0 + g * NW) * 8 + lch;
             const bool ok = c < kchunks;                          // also false for blocks past the last
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 wf[g][i] = ok ? wptr[i][c] : make_uint4(0, 0, 0, 0);
 #pragma unroll
-                for (int b = 0; b < MB; ++b) xf[g][b][i] = (ok && xlive[b][i]) ? xptr[b][i][c] : make_uint4(0, 0, 0, 0);
-            }
-        }
-        // the norm weights of all groups go out with the group's own loads (fetched group by group where they are
-        // used, each costs a trip of its own); chunks past the end re-read the last one and are not used
-        float4 nw[G][2];
-        if (norm_w) {
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const int64_t c = (blk0 + (int64_t)g * NW) * 8 + lch;
-                const int64_t cc = c < kchunks ? c : kchunks - 1;
-                nw[g][0] = reinterpret_cast<const float4 *>(norm_w)[2 * cc];
-                nw[g][1] = reinterpret_cast<const float4 *>(norm_w)[2 * cc + 1];
-            }
-        }
-        if (MB == 1 && window_pending) {
-            tail_windows(0, early);
-            window_pending = false;
-        }
-        if (norm_w) {
-            // RMSNorm on the way in: the element-wise weight now, the row factor after the sums
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const int64_t c = (blk0 + (int64_t)g * NW) * 8 + lch;
-                if (c >= kchunks) continue;
-                const float4 g0 = nw[g][0], g1 = nw[g][1];
-#pragma unroll
-                for (int b = 0; b < MB; ++b)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        uint4 &q = xf[g][b][i];
-                        const float v0 = bf16_lo(q.x), v1 = bf16_hi(q.x), v2 = bf16_lo(q.y), v3 = bf16_hi(q.y);
-                        const float v4 = bf16_lo(q.z), v5 = bf16_hi(q.z), v6 = bf16_lo(q.w), v7 = bf16_hi(q.w);
-                        ss[b][i] += v0 * v0 + v1 * v1 + v2 * v2 + v3 * v3 + v4 * v4 + v5 * v5 + v6 * v6 + v7 * v7;
-                        q = make_uint4(f32x2_to_bf16x2(v0 * g0.x, v1 * g0.y), f32x2_to_bf16x2(v2 * g0.z, v3 * g0.w),
-                                       f32x2_to_bf16x2(v4 * g1.x, v5 * g1.y), f32x2_to_bf16x2(v6 * g1.z, v7 * g1.w));
-                    }
+                for (int b = 0; b < MB; ++b) xf[g][b][i] = ok ? xptr[b][i][c] : make_uint4(0, 0, 0, 0);
             }
         }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            bf16x8 wv[4], xv[4];
+            bf16x8 wv[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 patch_w[put + 64 * i] = wf[g][i];
-                patch_x[put + 64 * i] = xf[g][0][i];
+#pragma unroll
+                for (int b = 0; b < MB; ++b) patch_x[256 * b + put + 64 * i] = xf[g][b][i];
             }
             wave_sync();
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                wv[s] = __builtin_bit_cast(bf16x8, patch_w[get[s]]);
-                xv[s] = __builtin_bit_cast(bf16x8, patch_x[get[s]]);
-            }
+            for (int s = 0; s < 4; ++s) wv[s] = __builtin_bit_cast(bf16x8, patch_w[get[s]]);
 #pragma unroll
-            for (int s = 0; s < 4; ++s) acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv[s], wv[s], acc[0], 0, 0, 0);
-#pragma unroll
-            for (int b = 1; b < MB; ++b) {
-                wave_sync();                                      // the x patch has been read
-#pragma unroll
-                for (int i = 0; i < 4; ++i) patch_x[put + 64 * i] = xf[g][b][i];
-                wave_sync();
+            for (int b = 0; b < MB; ++b)
 #pragma unroll
                 for (int s = 0; s < 4; ++s)
-                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, patch_x[get[s]]), wv[s], acc[b], 0, 0, 0);
-            }
+                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, patch_x[256 * b + get[s]]), wv[s], acc[b], 0, 0, 0);
             wave_sync();
         }
     }
-    if (MB == 1 && window_pending) tail_windows(0, early);        // a wavefront without a k block of its own
     __syncthreads();                                              // patches are done with: their memory is reused below
-
     // acc[b][i] is C[m = 32 b + 8 (i / 4) + 4 (lane / 32) + i % 4][n = n0 + lane % 32]
 #pragma unroll
-    for (int b = 0; b < MB; ++b) {
-        if (b > 0) __syncthreads();
+    for (int b = 0; b < MB; ++b)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) part[wave][i][lane] = acc[b][i];
-        if (norm_w) {
+        for (int i = 0; i < 16; ++i) part[wave][16 * b + i][lane] = acc[b][i];
+    __syncthreads();
 #pragma unroll
-            for (int i = 0; i < 4; ++i) ssq[wave][b][i][lane] = ss[b][i];
-        }
-        __syncthreads();
-        if (norm_w) {
-            if (tid < 32) {                                       // row tid = (tid & 7) + 8 (tid >> 3): lanes 8 (tid & 7) .. + 7, i = tid >> 3
-                float t = 0.0f;
+    for (int j = 0; j < OPT; ++j) {
+        const int o = tid + j * 512;
+        float v = 0.0f;
 #pragma unroll
-                for (int q = 0; q < NW; ++q)
+        for (int q = 0; q < NW; ++q) v += part[q][o >> 6][lane];
+        if (sp[j] < 0) continue;
+        v = bf16_to_f32(f32_to_bf16(v + bv[j]));                  // same two roundings as the tiled kernel
+        if (residual) v += bf16_to_f32(res[j]);
+        (sp[j] == 0 ? out.ptr[0] : sp[j] == 1 ? out.ptr[1] : out.ptr[2])[off[j]] = (bf16_t)f32_to_bf16(v);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------
+// A draft position (M <= 64 rows, Sec. 4.1): w is read once, nothing is big, and what counts is the number of trips to
+// memory and of barriers between the launch and the last store.  One workgroup per 16 output columns (192 of them for
+// in_proj, twice what 32 columns give) and 16 MT rows, its eight wavefronts share the k range in contiguous pieces of k32 steps.
+// v_mfma_f32_16x16x32_bf16 takes lane l's operand as 16 bytes of row l % 16 at k = 8 (l / 16), so one load instruction
+// covers 64 adjacent bytes of each of 16 rows and its result IS the fragment: no staging through LDS.  (With 32 x 32
+// tiles a row's share of an instruction is 32 bytes, which is why those need the transposing patches above.)
+// The partial tiles of the wavefronts meet in LDS, one output per thread; what else an output needs (bias, residual, the
+// carried conv window behind the parent index) has been on its way since before the main loop.
+// IN (in_proj of a draft position): norm, conv and next projection ride along.
+//   NORM: RMSNorm on the way in.  The weight goes on the x fragments; the sum of squares of a row is reduced over the
+//     lanes that share it by lane swaps and over the wavefronts by whoever applies the row factor (eight LDS words).
+//   CONV: the columns of the first output tensor go through one step of the causal conv + SiLU.
+//   xp.w: the finished 16 columns of the first output tensor (as stored) are multiplied into the next projection right
+//     here, one 16x16x16 MFMA per 16 of its outputs and 16 rows, and leave as partial sums (row, column block, output):
+//     runs of `n` floats per row, so that both sides move whole lines.
+// Measured on the drafter's shapes (12 rows, weights rotating through 24 layers, per launch in a replayed graph), against
+// 32-column tiles that went through LDS patches: in_proj with everything 9.0 -> 5.7 us, out_proj 5.8 -> 4.8 us; with 64
+// rows 18.2 -> 11.0 and 10.3 -> 5.1 us.  (16 wavefronts, or six k steps in flight instead of three, measured the same.)
+typedef short bf16x4_bits __attribute__((ext_vector_type(4)));
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+
+// the sum over the four lanes that share l % 16, in all of them
+__device__ __forceinline__ float sum_over_groups16(float v)
+{
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+    v = __uint_as_float(r.x) + __uint_as_float(r.y);
+    r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+    return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
+
+template <int MT, bool IN>
+__global__ void __launch_bounds__(512)
+linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, const float *__restrict__ bias,
+                  const bf16_t *residual, OutSplit out, int M, int N, int K, const float *__restrict__ norm_w, float eps,
+                  ConvTail conv, XprojTail xp)
+{
+    constexpr int NW = 8, kThr = NW * 64, G = 3;                   // G: k32 steps in flight per wavefront
+    constexpr int OPT = (MT * 256 + kThr - 1) / kThr;              // outputs per thread
+    constexpr bool NORM = IN, CONV = IN;
+    constexpr int kXcRow = 24;                                     // elements between rows of the finished columns in LDS (48 bytes: 8-byte aligned, spread over the banks)
+    __shared__ __attribute__((aligned(16))) float part[NW][MT][4][64];
+    __shared__ __attribute__((aligned(16))) float ssq[MT * 16][NW];
+    __shared__ __attribute__((aligned(16))) uint16_t xc[CONV ? MT * 16 * kXcRow : 8];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, lg = lane >> 4;
+    const int n0 = blockIdx.x * 16, m0 = blockIdx.y * (16 * MT);
+    const int w0 = (int)out.width[0], w1 = (int)out.width[1];
+
+    // ---- what the outputs of this thread need besides their sums, first part (nothing is used where it is fetched)
+    struct Tail {
+        float bias, cb, wk[4];
+        uint16_t res, carried[3];
+        int32_t parent;
+    };
+    Tail tail[OPT];
+    int om[OPT], on[OPT];
+    bool live[OPT];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) t += ssq[q][b][tid >> 3][8 * (tid & 7) + j];
-                row_scale[tid] = __builtin_amdgcn_rsqf(t / (float)K + eps);
+    for (int j = 0; j < OPT; ++j) {
+        const int o = tid + j * kThr, r = o & 255, l = r & 63;     // tile o / 256, accumulator r / 64 of lane l
+        om[j] = m0 + (o >> 8) * 16 + 4 * (l >> 4) + (r >> 6);
+        on[j] = n0 + (l & 15);
+        live[j] = o < MT * 256 && om[j] < M && on[j] < N;
+        tail[j].bias = tail[j].cb = 0.0f;
+        tail[j].res = 0;
+        tail[j].parent = om[j];
+        if (!live[j]) continue;
+        if (bias) tail[j].bias = bias[on[j]];
+        if (residual) tail[j].res = residual[(int64_t)om[j] * N + on[j]];          // single output tensor
+        if (CONV && conv.parent && on[j] < w0) tail[j].parent = conv.parent[om[j]];
+    }
+
+    // ---- the wavefront's share of k: steps [s_first, s_end) of 32
+    const int steps = (K + 31) >> 5, per = (steps + NW - 1) / NW;
+    const int s_first = wave * per, s_end = s_first + per < steps ? s_first + per : steps;
+    const int kchunks = K >> 3;                                    // K % 8 == 0
+    const uint4 *wrow = reinterpret_cast<const uint4 *>(w + (int64_t)(n0 + li < N ? n0 + li : N - 1) * K);
+    const uint4 *xrow[MT];
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+        const int m = m0 + 16 * t + li;
+        xrow[t] = reinterpret_cast<const uint4 *>(x + (int64_t)(m < M ? m : M - 1) * K);   // rows past M repeat the last one, never stored
+    }
+    f32x4v acc[MT];
+    float ss[MT];
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+        acc[t] = f32x4v(0.0f);
+        ss[t] = 0.0f;
+    }
+    const bool xp_on = CONV && xp.w && n0 < w0;                    // uniform: a column block lies in one output tensor (w0 % 16 == 0)
+    const int xp_tiles = xp_on ? (xp.n + 15) >> 4 : 0, xp_tasks = xp_tiles * MT;
+    uint2 xw[3] = {};
+    bool windows_pending = CONV;
+    for (int s0 = s_first; s0 < s_end || windows_pending; s0 += G) {
+        uint4 wf[G], xf[MT][G];
+        float4 nw[NORM ? G : 1][2];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int c = 4 * (s0 + g) + lg;
+            const bool ok = s0 + g < s_end && c < kchunks;
+            const int cc = ok ? c : 0;
+            wf[g] = wrow[cc];
+#pragma unroll
+            for (int t = 0; t < MT; ++t) xf[t][g] = xrow[t][cc];
+            if constexpr (NORM) {
+                nw[g][0] = reinterpret_cast<const float4 *>(norm_w)[2 * cc];
+                nw[g][1] = reinterpret_cast<const float4 *>(norm_w)[2 * cc + 1];
             }
-            __syncthreads();
         }
-        Tail late[OPT];
-        if constexpr (MB != 1) {
+        if (CONV && windows_pending) {
+            // the windows behind the parent index, once the main loop's first requests are on their way
+            windows_pending = false;
+            const int H = conv.k - 1;
 #pragma unroll
-            for (int j = 0; j < OPT; ++j) tail_first(b, j, late[j]);
-            tail_windows(b, late);
-        }
+            for (int j = 0; j < OPT; ++j) {
+                if (!live[j] || on[j] >= w0) continue;
+                const bool p_ok = tail[j].parent >= 0 && (int64_t)tail[j].parent < conv.n_in;
+                const int64_t win = ((int64_t)(p_ok ? tail[j].parent : 0) * w0 + on[j]) * H;
+                if (conv.bias) tail[j].cb = conv.bias[on[j]];
 #pragma unroll
-        for (int j = 0; j < OPT; ++j) {
-            const int o = tid + j * NW * 64, i = o >> 6, l = o & 63;
-            const Tail t = MB == 1 ? early[j] : late[j];
-            float v = 0.0f;
+                for (int k = 0; k < 4; ++k) tail[j].wk[k] = conv.w[(int64_t)on[j] * conv.k + (k <= H ? k : H)];
 #pragma unroll
-            for (int q = 0; q < NW; ++q) v += part[q][i][l];
-            if (norm_w) v *= row_scale[8 * (i >> 2) + 4 * (l >> 5) + (i & 3)];
-            const int64_t m = m0 + b * 32 + 8 * (i >> 2) + 4 * (l >> 5) + (i & 3), n = n0 + (l & 31);
-            if (m >= M || n >= N) continue;
-            v = bf16_to_f32(f32_to_bf16(v + t.bias));             // same two roundings as the tiled kernel
-            int64_t col, width;
-            bf16_t *optr;
-            const int sp = locate_tail(n, &col, &width, &optr);
-            const int64_t off = m * width + col;
-            if (residual) v += bf16_to_f32(t.res);
-            if (conv.w && sp == 0) {
-                // the window of this (row, channel): K - 1 carried values, then v; same order of operations
-                // as the stand-alone conv kernel.  A bad parent index leaves NaN in the carried places.
-                const int H = conv.k - 1;
-                const bool p_ok = !conv.parent || (t.parent >= 0 && (int64_t)t.parent < conv.n_in);
-                uint16_t carried[3];
-#pragma unroll
-                for (int k = 0; k < 3; ++k) carried[k] = p_ok ? t.carried[k] : (uint16_t)0x7fc0;
-                bf16_t *nwin = conv.dst + off * H;
-                float a = t.cb;
-#pragma unroll
-                for (int k = 0; k < 3; ++k)
-                    if (k < H) a = fmaf(t.wk[k], bf16_to_f32(carried[k]), a);
-                float wlast = t.wk[0];
-#pragma unroll
-                for (int k = 1; k < 4; ++k)
-                    if (k == H) wlast = t.wk[k];
-                a = fmaf(wlast, v, a);
-#pragma unroll
-                for (int k = 0; k < 2; ++k)
-                    if (k + 1 < H) nwin[k] = carried[k + 1];
-                if (H > 0) nwin[H - 1] = (bf16_t)f32_to_bf16(v);
-                v = silu_f32(a);
+                for (int k = 0; k < 3; ++k) tail[j].carried[k] = conv.src[win + (k < H ? k : H - 1)];
             }
-            const uint32_t stored = f32_to_bf16(v);
-            optr[off] = (bf16_t)stored;
-            if constexpr (kTailRoom) {
-                if (xp.w && sp == 0) xc[b][8 * (i >> 2) + 4 * (l >> 5) + (i & 3)][l & 31] = bf16_to_f32(stored);
+            // and this wavefront's fragments of the next projection: rows of xp.w are its outputs, 16 of its k are n0 ..
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+                const int task = r * NW + wave;
+                const int row = (task < xp_tasks ? task % (xp_tiles ? xp_tiles : 1) : 0) * 16 + li;
+                if (xp_on) xw[r] = *reinterpret_cast<const uint2 *>(xp.w + (int64_t)(row < xp.n ? row : xp.n - 1) * xp.ldw + n0 + 4 * lg);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);                         // all of it in flight before any of it is used
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const bool ok = s0 + g < s_end && 4 * (s0 + g) + lg < kchunks;   // else zeros: adds nothing
+            const bf16x8 wv = __builtin_bit_cast(bf16x8, ok ? wf[g] : make_uint4(0, 0, 0, 0));
+#pragma unroll
+            for (int t = 0; t < MT; ++t) {
+                uint4 q = ok ? xf[t][g] : make_uint4(0, 0, 0, 0);
+                if constexpr (NORM) {
+                    const float4 g0 = nw[g][0], g1 = nw[g][1];
+                    const float v0 = bf16_lo(q.x), v1 = bf16_hi(q.x), v2 = bf16_lo(q.y), v3 = bf16_hi(q.y);
+                    const float v4 = bf16_lo(q.z), v5 = bf16_hi(q.z), v6 = bf16_lo(q.w), v7 = bf16_hi(q.w);
+                    ss[t] += v0 * v0 + v1 * v1 + v2 * v2 + v3 * v3 + v4 * v4 + v5 * v5 + v6 * v6 + v7 * v7;
+                    q = make_uint4(f32x2_to_bf16x2(v0 * g0.x, v1 * g0.y), f32x2_to_bf16x2(v2 * g0.z, v3 * g0.w),
+                                   f32x2_to_bf16x2(v4 * g1.x, v5 * g1.y), f32x2_to_bf16x2(v6 * g1.z, v7 * g1.w));
+                }
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, q), wv, acc[t], 0, 0, 0);
             }
         }
     }
-    if constexpr (kTailRoom) {
-        if (tail_on) {
-            __syncthreads();
-            const int rows = (int)((M - m0 < 32 * MB) ? M - m0 : 32 * MB);
-            for (int ml = tail_g; ml < rows && tail_g < tail_groups; ml += tail_groups) {
-                const int j = tail_j;
-                const float *xr = xc[ml >> 5][ml & 31];
-                float acc = 0.0f;
+    // acc[t][i] is C[m = 16 t + 4 (lane / 16) + i][n = lane % 16]
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const uint4 q = xw4[c];
-                    acc = fmaf(xr[8 * c + 0], bf16_lo(q.x), acc);
-                    acc = fmaf(xr[8 * c + 1], bf16_hi(q.x), acc);
-                    acc = fmaf(xr[8 * c + 2], bf16_lo(q.y), acc);
-                    acc = fmaf(xr[8 * c + 3], bf16_hi(q.y), acc);
-                    acc = fmaf(xr[8 * c + 4], bf16_lo(q.z), acc);
-                    acc = fmaf(xr[8 * c + 5], bf16_hi(q.z), acc);
-                    acc = fmaf(xr[8 * c + 6], bf16_lo(q.w), acc);
-                    acc = fmaf(xr[8 * c + 7], bf16_hi(q.w), acc);
-                }
-                xp.part[((m0 + ml) * xp.n + j) * (xp.ldw / 32) + blockIdx.x] = acc;
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) part[wave][t][i][lane] = acc[t][i];
+    if constexpr (NORM) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+            const float v = sum_over_groups16(ss[t]);
+            if (lg == 0) ssq[16 * t + li][wave] = v;
+        }
+    }
+    lds_barrier_linear();
+
+#pragma unroll
+    for (int j = 0; j < OPT; ++j) {
+        const int o = tid + j * kThr, t = (o >> 8) < MT ? o >> 8 : 0, i = (o >> 6) & 3, l = o & 63;
+        float v = 0.0f;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) v += part[q][t][i][l];
+        if constexpr (NORM) {
+            float sq = 0.0f;
+#pragma unroll
+            for (int q = 0; q < NW; ++q) sq += ssq[16 * t + 4 * (l >> 4) + i][q];
+            v *= __builtin_amdgcn_rsqf(sq / (float)K + eps);
+        }
+        if (!live[j]) continue;
+        v = bf16_to_f32(f32_to_bf16(v + tail[j].bias));            // same two roundings as the tiled kernel
+        int col = on[j], width = w0, sp = 0;
+        if (col >= w0) {
+            col -= w0; width = w1; sp = 1;
+            if (col >= w1) { col -= w1; width = (int)out.width[2]; sp = 2; }
+        }
+        bf16_t *optr = sp == 0 ? out.ptr[0] : sp == 1 ? out.ptr[1] : out.ptr[2];
+        const int64_t off = (int64_t)om[j] * width + col;
+        if (residual) v += bf16_to_f32(tail[j].res);
+        if (CONV && sp == 0) {
+            // the window of this (row, channel): K - 1 carried values, then v; same order of operations as the stand-alone
+            // conv kernel.  A bad parent index leaves NaN in the carried places.
+            const int H = conv.k - 1;
+            const bool p_ok = tail[j].parent >= 0 && (int64_t)tail[j].parent < conv.n_in;
+            uint16_t carried[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) carried[k] = p_ok ? tail[j].carried[k] : (uint16_t)0x7fc0;
+            bf16_t *nwin = conv.dst + off * H;
+            float a = tail[j].cb;
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                if (k < H) a = fmaf(tail[j].wk[k], bf16_to_f32(carried[k]), a);
+            float wlast = tail[j].wk[0];
+#pragma unroll
+            for (int k = 1; k < 4; ++k)
+                if (k == H) wlast = tail[j].wk[k];
+            a = fmaf(wlast, v, a);
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                if (k + 1 < H) nwin[k] = carried[k + 1];
+            if (H > 0) nwin[H - 1] = (bf16_t)f32_to_bf16(v);
+            v = silu_f32(a);
+        }
+        const uint32_t stored = f32_to_bf16(v);
+        optr[off] = (bf16_t)stored;
+        if (CONV && xp_on) xc[(om[j] - m0) * kXcRow + (l & 15)] = (uint16_t)stored;
+    }
+    if constexpr (CONV) {
+        if (!xp_on) return;
+        // (rows past M hold whatever was in LDS: they only reach outputs that are not stored)
+        lds_barrier_linear();
+        for (int r = 0; r * NW + wave < xp_tasks; ++r) {
+            const int task = r * NW + wave, jt = task % xp_tiles, t = task / xp_tiles;
+            uint2 b2 = r == 0 ? xw[0] : r == 1 ? xw[1] : xw[2];
+            if (r > 2) {
+                const int row = jt * 16 + li;
+                b2 = *reinterpret_cast<const uint2 *>(xp.w + (int64_t)(row < xp.n ? row : xp.n - 1) * xp.ldw + n0 + 4 * lg);
+            }
+            const uint2 a2 = *reinterpret_cast<const uint2 *>(&xc[(16 * t + li) * kXcRow + 4 * lg]);
+            const f32x4v y = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4_bits, a2), __builtin_bit_cast(bf16x4_bits, b2),
+                                                                       f32x4v(0.0f), 0, 0, 0);
+            const int jn = jt * 16 + li;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int m = m0 + 16 * t + 4 * lg + i;
+                if (m < M && jn < xp.n) xp.part[((int64_t)m * (w0 >> 4) + blockIdx.x) * xp.n + jn] = y[i];
             }
         }
     }
@@ -840,38 +857,44 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     const int vec = (a.width[0] % 8 == 0 && a.width[1] % 8 == 0 && a.width[2] % 8 == 0) ? 1 : 0;
     const bf16_t *x = static_cast<const bf16_t *>(a.x), *w = static_cast<const bf16_t *>(a.w);
     const bf16_t *res = static_cast<const bf16_t *>(a.residual);
-    // few rows: the split-k kernel, except for very wide outputs (the LM head), where the tiled kernel's
-    // shared x tile reads less
-    const int64_t col_blocks = (N + 31) / 32;
-    const bool few_rows = a.M <= 64 && (N < 8192 || a.norm_w || a.conv_w);
-    if (few_rows) {
-        const ConvTail ct{a.conv_w, a.conv_b, static_cast<const bf16_t *>(a.conv_src), static_cast<bf16_t *>(a.conv_dst),
-                          a.conv_parent, a.conv_n_in, a.conv_k};
-        const bool deep = a.K > 512;                              // more wavefronts share a long k loop
-        const XprojTail xt{deep ? static_cast<const bf16_t *>(a.xproj_w) : nullptr, a.xproj_part, a.xproj_n, a.width[0]};
-        if (a.M <= 32) {
-            const dim3 grid((unsigned)col_blocks, 1);
-            if (deep) linear_skinny_kernel<8, 1><<<grid, 512, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, a.norm_w, a.eps, ct, xt);
-            else      linear_skinny_kernel<4, 1><<<grid, 256, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, a.norm_w, a.eps, ct, xt);
-        } else {
-            const dim3 grid((unsigned)col_blocks, (unsigned)((a.M + 63) / 64));
-            if (deep) linear_skinny_kernel<8, 2><<<grid, 512, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, a.norm_w, a.eps, ct, xt);
-            else      linear_skinny_kernel<4, 2><<<grid, 256, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, a.norm_w, a.eps, ct, xt);
-        }
-        return hipGetLastError();
-    }
-    // Few output columns and a long k loop (x_proj on a context of a few thousand tokens): the tiled kernel would walk
-    // k slab by slab on a few dozen CUs; the split-k kernel over a grid of 32-row blocks fetches a block's whole k range
-    // in one trip, as long as all of its workgroups are resident at once (2048 tokens: 10.4 -> 6.5 us; with a second
-    // round of workgroups, at 4096 tokens, it is slower than the tiles: 13.6 against 10.7 us).
-    if (N <= 128 && a.K > 512 && col_blocks * ((a.M + 31) / 32) <= 256) {
-        const ConvTail ct{nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0};
-        const XprojTail xt{nullptr, nullptr, 0, 0};
-        const dim3 grid((unsigned)col_blocks, (unsigned)((a.M + 31) / 32));
-        linear_skinny_kernel<8, 1><<<grid, 512, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, nullptr, a.eps, ct, xt);
-        return hipGetLastError();
-    }
     auto tiles = [&](int64_t bm, int64_t bn) { return ((N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
+    const ConvTail ct{a.conv_w, a.conv_b, static_cast<const bf16_t *>(a.conv_src), static_cast<bf16_t *>(a.conv_dst),
+                      a.conv_parent, a.conv_n_in, a.conv_k};
+    const XprojTail xt{static_cast<const bf16_t *>(a.xproj_w), a.xproj_part, a.xproj_n, a.width[0]};
+#define MAMBA_FEW(MT, IN) linear_few_kernel<MT, IN><<<dim3((unsigned)((N + 15) / 16), (unsigned)((a.M + 16 * MT - 1) / (16 * MT))), 512, 0, stream>>>(x, w, a.bias, res, o, (int)a.M, (int)N, (int)a.K, a.norm_w, a.eps, ct, xt)
+    if (a.norm_w) {
+        // the way into a block at a draft position: norm and conv come together, the next projection only with them
+        if (!a.conv_w || !a.conv_src || !a.conv_dst || a.conv_k < 2 || (a.xproj_w && (!a.xproj_part || a.width[0] % 16)))
+            return hipErrorInvalidValue;
+        if (tiles(16, 16) <= kTilesResident) MAMBA_FEW(1, true);
+        else if (tiles(32, 16) <= kTilesResident) MAMBA_FEW(2, true);
+        else MAMBA_FEW(4, true);
+        return hipGetLastError();
+    }
+    // Few output tiles: latency decides, and the tiles are kept so small that they just fill the CUs once (a second
+    // round of workgroups costs as much again: 256 rows x 768 columns, K = 1536, 5.9 us, 264 rows 9.4 us).  16-column
+    // tiles with the fragments straight from memory while 16 or, on a short k, 32 rows each are enough; their half-line
+    // loads take the address path twice the time, so then the 32-column tiles that load whole lines: 32 rows from where
+    // every wavefront has a k block, 64 rows from where it has two (on less the slab kernel, 64 x 64 tiles, is as fast).
+    // In us, 16 / 32 / 64 rows / slabs: 64 x 1024, K = 512 3.5 / 4.8 / - / 5.5;  333 x 80, K = 1536 5.1 / 6.3 / - / 10.4;
+    // 256 x 768, K = 1536 10.3 / 5.9 / 8.1 / 10.9;  512 x 768, K = 1536 18.9 / 10.0 / 8.2 / 11.0;  256 x 2048, K = 1024
+    // 24 / 9.2 / 7.4 / 8.2.
+    if (tiles(16, 16) <= kTilesResident) { MAMBA_FEW(1, false); return hipGetLastError(); }
+    if (a.K <= 768 && tiles(32, 16) <= kTilesResident) { MAMBA_FEW(2, false); return hipGetLastError(); }
+    if (a.K >= 512 && tiles(32, 32) <= kTilesResident) {
+        const dim3 grid((unsigned)((N + 31) / 32), (unsigned)((a.M + 31) / 32));
+        linear_split_kernel<1><<<grid, 512, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K);
+        return hipGetLastError();
+    }
+    if (a.K >= 1024 && tiles(64, 32) <= kTilesResident) {
+        const dim3 grid((unsigned)((N + 31) / 32), (unsigned)((a.M + 63) / 64));
+        linear_split_kernel<2><<<grid, 512, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K);
+        return hipGetLastError();
+    }
+    // what is left of the few rows, except for very wide outputs (the LM head), where the tiled kernel's shared x tile
+    // reads less
+    if (a.M <= 64 && N < 8192) { MAMBA_FEW(4, false); return hipGetLastError(); }
+#undef MAMBA_FEW
     if (vec && N % 128 == 0 && a.M >= 128 && a.K % (2 * kWideBK) == 0) {
         // The memory-to-LDS kernel, on any number of rows.  Measured inside the 24-block prefill (alone in a loop the
         // wide tiles look better than they are there: their denser matrix work lowers the clock for what runs between

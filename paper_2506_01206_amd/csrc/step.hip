@@ -403,7 +403,7 @@ state_step_xproj_kernel(float *h_out, const float *h_in, const int32_t *__restri
     const int64_t j = blockIdx.y;
     const int64_t row4 = D * Q;  // float4s per branch
     const float4 *a4 = reinterpret_cast<const float4 *>(A);
-    __shared__ __attribute__((aligned(16))) float xs[256];
+    __shared__ __attribute__((aligned(16))) float xs[256], xs_side[3][256];
     const bool hold_w = dt_rank / 4 <= CW * Q;
 
     int64_t f[U], d[U];
@@ -441,22 +441,32 @@ state_step_xproj_kernel(float *h_out, const float *h_in, const int32_t *__restri
 #pragma unroll
     for (int i = 0; i < U; ++i) h[i] = ld_stream(hin4 + f[i]);
     // The branch's row of the x projection (dt low rank | B | C) arrives as n_parts partial sums: they are added
-    // up in order and rounded to bf16, as the stored tensors they replace would have been.
+    // up in order and rounded to bf16, as the stored tensors they replace would have been.  A part is one run of
+    // dt_rank + 2 N floats; the workgroup reads as many parts side by side as it has threads for, each a contiguous
+    // range of them, and adds those few sums up from LDS.
     {
         const int xn = (int)dt_rank + 2 * N;
-        for (int k = threadIdx.x; k < xn; k += kBlock) {
-            // the parts of one sum lie side by side (n_parts % 4 == 0): four 16-byte loads in flight at a time
-            const float4 *pr = reinterpret_cast<const float4 *>(xpart + (j * xn + k) * n_parts);
+        const int sides = xn <= kBlock / 3 ? 3 : xn <= kBlock / 2 ? 2 : 1;
+        const int side = (int)threadIdx.x / xn, k = (int)threadIdx.x - side * xn;
+        if (side < sides) {
+            const int per = (n_parts + sides - 1) / sides, first = side * per, last = min(first + per, n_parts);
+            const float *pr = xpart + j * n_parts * xn + k;
             float sum = 0.0f;
-            for (int c = 0; c < n_parts / 4; c += 4) {
-                float4 v[4];
+            for (int c = first; c < last; c += 16) {
+                float v[16];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = pr[min(c + u, n_parts / 4 - 1)];
+                for (int u = 0; u < 16; ++u) v[u] = pr[(int64_t)min(c + u, last - 1) * xn];
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (c + u < n_parts / 4) sum = (((sum + v[u].x) + v[u].y) + v[u].z) + v[u].w;
+                for (int u = 0; u < 16; ++u)
+                    if (c + u < last) sum += v[u];
             }
-            xs[k] = bf16_to_f32(f32_to_bf16(sum));
+            xs_side[side][k] = sum;
+        }
+        __syncthreads();
+        if ((int)threadIdx.x < xn) {
+            float sum = xs_side[0][threadIdx.x];
+            for (int u = 1; u < sides; ++u) sum += xs_side[u][threadIdx.x];
+            xs[threadIdx.x] = bf16_to_f32(f32_to_bf16(sum));
         }
         __syncthreads();
 #pragma unroll

@@ -1148,6 +1148,17 @@ def test_linear_wide_tiles_ragged_rows(m, M, N, K, splits):
     test_linear_against_oracle(m, M, N, K, splits)
 
 
+@pytest.mark.parametrize("M,N,K,splits", [(1, 4096, 8, None), (17, 2050, 40, None), (257, 250, 1544, (48, 102, 100)),   # 16 x 16
+                                          (19, 4090, 768, (2040, 2050)), (100, 800, 520, None),                          # 32 x 16
+                                          (65, 4000, 512, (1500, 2500)), (255, 999, 1288, None), (2700, 80, 1536, (48, 16, 16)),   # 32 x 32
+                                          (330, 761, 1096, (3, 700, 58)), (641, 700, 1024, None), (129, 2600, 4104, None),         # 64 x 32
+                                          (50, 5000, 264, (4000, 1000)), (64, 4500, 776, None)])                         # 64 x 16
+def test_linear_few_tiles(m, M, N, K, splits):
+    """Products with few output tiles, at both sides of the lines between the tile shapes they get and with ragged rows,
+    columns, k and outputs whose borders lie inside a tile."""
+    test_linear_against_oracle(m, M, N, K, splits)
+
+
 def test_linear_at_block_bench_size_sampled_rows(m):
     """in_proj and out_proj of the whole-block leg of bench.py (32768 tokens, Mamba-130M widths), in the launch
     configuration it times; rows are independent, so the oracle computes a seeded sample of them (every row block
@@ -1321,6 +1332,26 @@ def test_block_decode_steps_other_shapes(m, dm, D, N, K, R):
         assert_close(to_host(g_ssm), r_ssm, tol, "block step ssm")
         assert_close(values(to_host(g_conv)), r_conv, tol, "block step conv")
         r_conv = W(synth.to_io(r_conv.astype(np.float32), synth.BF16))
+
+
+@pytest.mark.parametrize("n,dm,D,N,K,R", [(16, 64, 136, 16, 4, 8), (17, 1032, 144, 16, 2, 8), (33, 40, 272, 8, 3, 64),
+                                          (17, 776, 1536, 16, 4, 48), (64, 256, 1600, 16, 4, 48), (63, 128, 2064, 32, 4, 192)])
+def test_block_step_more_branches(m, n, dm, D, N, K, R):
+    """A draft position with up to 64 branches from shared parents: every row tile of the way into the block (16, 32 and
+    64 rows, several of them side by side, a ragged last one), with the x projection inside it and apart from it."""
+    say(n=n, dm=dm, D=D, N=N, K=K, R=R)
+    rng = np.random.default_rng(n + dm + D)
+    w, w64, blk = make_block(m, rng, dm, D, N, K, R)
+    conv = synth.to_io(rng.standard_normal((5, D, K - 1)).astype(np.float32), synth.BF16)
+    ssm = rng.standard_normal((5, D, N)).astype(np.float32)
+    hid = synth.to_io(rng.standard_normal((n, dm)).astype(np.float32), synth.BF16)
+    par = rng.integers(0, 5, n).astype(np.int32)
+    out, g_conv, g_ssm = m.mamba_block_step(blk, to_dev(hid), to_dev(conv), to_dev(ssm), parent_idx=to_dev(par))
+    ro, r_conv, r_ssm = oracle.block_fwd(w64, W(hid)[:, None, :], conv_state_in=W(conv)[par], h0=ssm.astype(np.float64)[par])
+    tol = TOL[synth.BF16]
+    assert_close(values(to_host(out)), ro[:, 0], tol, "block step out")
+    assert_close(to_host(g_ssm), r_ssm, tol, "block step ssm")
+    assert_close(values(to_host(g_conv)), r_conv, tol, "block step conv")
 
 
 def test_block_step_bad_parent_poisons_only_that_branch(m):
