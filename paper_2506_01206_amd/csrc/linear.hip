@@ -604,9 +604,10 @@ linear_split_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, 
 // A draft position (M <= 64 rows, Sec. 4.1): w is read once, nothing is big, and what counts is the number of trips to
 // memory and of barriers between the launch and the last store.  One workgroup per 16 output columns (192 of them for
 // in_proj, twice what 32 columns give) and 16 MT rows, its eight wavefronts share the k range in contiguous pieces of k32 steps.
-// v_mfma_f32_16x16x32_bf16 takes lane l's operand as 16 bytes of row l % 16 at k = 8 (l / 16), so one load instruction
-// covers 64 adjacent bytes of each of 16 rows and its result IS the fragment: no staging through LDS.  (With 32 x 32
-// tiles a row's share of an instruction is 32 bytes, which is why those need the transposing patches above.)
+// A fragment of v_mfma_f32_16x16x32_bf16 wants row l % 16 in lane l; loaded like that, no two lanes of a quad share a
+// 64-byte piece of a line and the address path takes a cycle per lane (60 for the 1 KiB, measured over 192 loads a CU).
+// With a row's 64 bytes on the four lanes of a quad it takes 34, so that is how rows are loaded; a 1 KiB patch of LDS
+// private to the wavefront turns them into fragments.
 // The partial tiles of the wavefronts meet in LDS, one output per thread; what else an output needs (bias, residual, the
 // carried conv window behind the parent index) has been on its way since before the main loop.
 // IN (in_proj of a draft position): norm, conv and next projection ride along.
@@ -617,19 +618,17 @@ linear_split_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, 
 //     here, one 16x16x16 MFMA per 16 of its outputs and 16 rows, and leave as partial sums (row, column block, output):
 //     runs of `n` floats per row, so that both sides move whole lines.
 // Measured on the drafter's shapes (12 rows, weights rotating through 24 layers, per launch in a replayed graph), against
-// 32-column tiles that went through LDS patches: in_proj with everything 9.0 -> 5.7 us, out_proj 5.8 -> 4.8 us; with 64
-// rows 18.2 -> 11.0 and 10.3 -> 5.1 us.  (16 wavefronts, or six k steps in flight instead of three, measured the same.)
+// 32-column tiles that went through LDS patches: in_proj with everything 9.0 -> 5.4 us, out_proj 5.8 -> 3.9 us; with 64
+// rows 18.2 -> 10.0 and 10.3 -> 4.0 us.  (Fragments straight from memory: 5.7, 4.8, 11.0 and 5.1 us.  16 wavefronts, or
+// six k steps in flight instead of three, measured the same.)
 typedef short bf16x4_bits __attribute__((ext_vector_type(4)));
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
-// the sum over the four lanes that share l % 16, in all of them
-__device__ __forceinline__ float sum_over_groups16(float v)
+// the sum over the four lanes of a quad, in all of them
+__device__ __forceinline__ float sum_over_quad(float v)
 {
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false));
-    v = __uint_as_float(r.x) + __uint_as_float(r.y);
-    r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false));
-    return __uint_as_float(r.x) + __uint_as_float(r.y);
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xb1, 0xf, 0xf, false));   // quad_perm [1,0,3,2]
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4e, 0xf, 0xf, false));   // quad_perm [2,3,0,1]
 }
 
 template <int MT, bool IN>
@@ -642,12 +641,15 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
     constexpr int OPT = (MT * 256 + kThr - 1) / kThr;              // outputs per thread
     constexpr bool NORM = IN, CONV = IN;
     constexpr int kXcRow = 24;                                     // elements between rows of the finished columns in LDS (48 bytes: 8-byte aligned, spread over the banks)
+    __shared__ __attribute__((aligned(16))) uint4 patch[NW][1 + MT][G][64];
     __shared__ __attribute__((aligned(16))) float part[NW][MT][4][64];
     __shared__ __attribute__((aligned(16))) float ssq[MT * 16][NW];
     __shared__ __attribute__((aligned(16))) uint16_t xc[CONV ? MT * 16 * kXcRow : 8];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int li = lane & 15, lg = lane >> 4;
+    const int li = lane & 15, lg = lane >> 4;                      // fragment view: row, 16-byte chunk of the step
+    const int lrow = lane >> 2, lch = lane & 3;                    // load view
+    const int put = lrow * 4 + (lch ^ (lrow >> 2)), get = li * 4 + (lg ^ (li >> 2));   // xor: no bank conflicts either way
     const int n0 = blockIdx.x * 16, m0 = blockIdx.y * (16 * MT);
     const int w0 = (int)out.width[0], w1 = (int)out.width[1];
 
@@ -679,11 +681,11 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
     const int steps = (K + 31) >> 5, per = (steps + NW - 1) / NW;
     const int s_first = wave * per, s_end = s_first + per < steps ? s_first + per : steps;
     const int kchunks = K >> 3;                                    // K % 8 == 0
-    const uint4 *wrow = reinterpret_cast<const uint4 *>(w + (int64_t)(n0 + li < N ? n0 + li : N - 1) * K);
+    const uint4 *wrow = reinterpret_cast<const uint4 *>(w + (int64_t)(n0 + lrow < N ? n0 + lrow : N - 1) * K);
     const uint4 *xrow[MT];
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
-        const int m = m0 + 16 * t + li;
+        const int m = m0 + 16 * t + lrow;
         xrow[t] = reinterpret_cast<const uint4 *>(x + (int64_t)(m < M ? m : M - 1) * K);   // rows past M repeat the last one, never stored
     }
     f32x4v acc[MT];
@@ -702,7 +704,7 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
         float4 nw[NORM ? G : 1][2];
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const int c = 4 * (s0 + g) + lg;
+            const int c = 4 * (s0 + g) + lch;
             const bool ok = s0 + g < s_end && c < kchunks;
             const int cc = ok ? c : 0;
             wf[g] = wrow[cc];
@@ -739,8 +741,8 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
         __builtin_amdgcn_sched_barrier(0);                         // all of it in flight before any of it is used
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const bool ok = s0 + g < s_end && 4 * (s0 + g) + lg < kchunks;   // else zeros: adds nothing
-            const bf16x8 wv = __builtin_bit_cast(bf16x8, ok ? wf[g] : make_uint4(0, 0, 0, 0));
+            const bool ok = s0 + g < s_end && 4 * (s0 + g) + lch < kchunks;   // else zeros: adds nothing
+            patch[wave][0][g][put] = ok ? wf[g] : make_uint4(0, 0, 0, 0);
 #pragma unroll
             for (int t = 0; t < MT; ++t) {
                 uint4 q = ok ? xf[t][g] : make_uint4(0, 0, 0, 0);
@@ -752,9 +754,18 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
                     q = make_uint4(f32x2_to_bf16x2(v0 * g0.x, v1 * g0.y), f32x2_to_bf16x2(v2 * g0.z, v3 * g0.w),
                                    f32x2_to_bf16x2(v4 * g1.x, v5 * g1.y), f32x2_to_bf16x2(v6 * g1.z, v7 * g1.w));
                 }
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, q), wv, acc[t], 0, 0, 0);
+                patch[wave][1 + t][g][put] = q;
             }
         }
+        wave_sync();
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const bf16x8 wv = __builtin_bit_cast(bf16x8, patch[wave][0][g][get]);
+#pragma unroll
+            for (int t = 0; t < MT; ++t)
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, patch[wave][1 + t][g][get]), wv, acc[t], 0, 0, 0);
+        }
+        wave_sync();
     }
     // acc[t][i] is C[m = 16 t + 4 (lane / 16) + i][n = lane % 16]
 #pragma unroll
@@ -764,8 +775,8 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
     if constexpr (NORM) {
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
-            const float v = sum_over_groups16(ss[t]);
-            if (lg == 0) ssq[16 * t + li][wave] = v;
+            const float v = sum_over_quad(ss[t]);
+            if (lch == 0) ssq[16 * t + lrow][wave] = v;
         }
     }
     lds_barrier_linear();
@@ -872,15 +883,17 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
         return hipGetLastError();
     }
     // Few output tiles: latency decides, and the tiles are kept so small that they just fill the CUs once (a second
-    // round of workgroups costs as much again: 256 rows x 768 columns, K = 1536, 5.9 us, 264 rows 9.4 us).  16-column
-    // tiles with the fragments straight from memory while 16 or, on a short k, 32 rows each are enough; their half-line
-    // loads take the address path twice the time, so then the 32-column tiles that load whole lines: 32 rows from where
-    // every wavefront has a k block, 64 rows from where it has two (on less the slab kernel, 64 x 64 tiles, is as fast).
-    // In us, 16 / 32 / 64 rows / slabs: 64 x 1024, K = 512 3.5 / 4.8 / - / 5.5;  333 x 80, K = 1536 5.1 / 6.3 / - / 10.4;
-    // 256 x 768, K = 1536 10.3 / 5.9 / 8.1 / 10.9;  512 x 768, K = 1536 18.9 / 10.0 / 8.2 / 11.0;  256 x 2048, K = 1024
-    // 24 / 9.2 / 7.4 / 8.2.
-    if (tiles(16, 16) <= kTilesResident) { MAMBA_FEW(1, false); return hipGetLastError(); }
-    if (a.K <= 768 && tiles(32, 16) <= kTilesResident) { MAMBA_FEW(2, false); return hipGetLastError(); }
+    // round of workgroups costs nearly as much again: 256 rows x 768 columns, K = 1536, on 32 x 32 tiles 5.9 us, 264 rows
+    // 9.4 us; a fifth of a round does not).  Tiles 16 columns wide while 16 or 32 rows each are enough, or 64 on a short k;
+    // they fetch x for every 16 columns anew, so beyond that the 32-column tiles: 32 rows from where every wavefront has
+    // a k block, 64 rows from where it has two (on less the slab kernel, 64 x 64 tiles, is as fast).
+    // us on      16x16 32x16 64x16 32x32 64x32 slabs  (x: more than one round)
+    //   64 x 1024, K = 512    2.9   3.3   4.0   4.8   6.5   5.6        333 x 80, K = 1536    3.9   5.3   6.5   5.7   7.6  10.4
+    //  128 x  768, K = 1536   5.2x  5.3   6.6   5.9   8.2  10.9        333 x 640, K = 768    5.1x  5.7x  4.7   5.3   7.1   7.0
+    //  256 x  768, K = 1536   7.1x  8.3x  6.8   5.9   8.0  10.9        512 x 768, K = 1536  11.3x 12.1x 11.6x  9.8x  8.1  10.9
+    if (tiles(16, 16) <= kTilesResident * 5 / 4) { MAMBA_FEW(1, false); return hipGetLastError(); }
+    if (tiles(32, 16) <= kTilesResident) { MAMBA_FEW(2, false); return hipGetLastError(); }
+    if (a.K <= 768 && tiles(64, 16) <= kTilesResident) { MAMBA_FEW(4, false); return hipGetLastError(); }
     if (a.K >= 512 && tiles(32, 32) <= kTilesResident) {
         const dim3 grid((unsigned)((N + 31) / 32), (unsigned)((a.M + 31) / 32));
         linear_split_kernel<1><<<grid, 512, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K);
