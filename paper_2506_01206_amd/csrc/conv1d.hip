@@ -8,7 +8,10 @@
 // HBM-bound: 2 elements moved per output.  A lane owns VEC adjacent channels (16 bytes of a token
 // row), walks a tile of consecutive tokens and keeps the K-1 previous rows in registers, so every
 // input element is read once (plus K-1 halo rows per tile) and every wavefront access is a
-// contiguous run.  Loads of the next group of rows are issued before the current group is used.
+// contiguous run.  Loads of the next group of rows are issued before the current group is used.  Groups are short:
+// what is in flight is bounded by wavefronts, and those by registers.  Against tiles of 8 to 32 rows per single wavefront
+// with taps of its own: 64 x 1536 4.3 -> 3.4 us, 2048 x 1536 6.7 -> 5.8, 8000 x 1536 14.9 -> 12.0, 32768 x 1536 46.7 ->
+// 42 us (201 MB, 4.8 TB/s), 15 x 5525 x 544 60 -> 50 us.
 // In tree drafting (Sec. 4.1) a branch starts from the window of its parent: the carried rows can be
 // read through a parent index, which replaces a separate copy of the window.
 #include "device_math.h"
@@ -17,8 +20,18 @@
 namespace mamba {
 namespace {
 
-constexpr int kBlock = 64;
-constexpr int kRows = 8;       // rows loaded together, one group ahead
+constexpr int kWave = 64;
+constexpr int kTilesPerBlock = 4;   // wavefronts of a workgroup: consecutive time tiles of the same channels
+constexpr int kBlock = kWave * kTilesPerBlock;
+constexpr int kRows = 2;       // rows loaded together, one group ahead
+
+// orders LDS only: the rows requested ahead of it stay in flight
+__device__ __forceinline__ void lds_barrier_c()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 
 template <typename T, int VEC> struct RowVec;
 template <> struct RowVec<float, 4> { typedef float4 type; };
@@ -70,31 +83,50 @@ template <int COUNT> __device__ __forceinline__ void st_block(bf16_t *p, const f
     for (int v = 0; v < COUNT / 8; ++v) pack_row(f + 8 * v, q[v]);
 }
 
-// grid: (channel-vector groups, time tiles, batch)
+// grid: (channel-vector groups, groups of four time tiles, batch)
 template <typename T, int VEC, int K, bool SILU>
 __global__ void __launch_bounds__(kBlock)
 conv1d_kernel(const T *__restrict__ x, const float *__restrict__ w, const float *__restrict__ bias,
               const T *state_in, T *__restrict__ y, T *state_out, int64_t L, int64_t D,
-              int64_t tile_len, const int32_t *__restrict__ parent, int64_t n_in)
+              int64_t tile_len, int lanes, const int32_t *__restrict__ parent, int64_t n_in)
 {
     typedef typename RowVec<T, VEC>::type row_t;
     constexpr int H = K - 1;
     const int64_t b = blockIdx.z;
-    const int64_t dv = (int64_t)blockIdx.x * kBlock + threadIdx.x;  // channel-vector index
-    if (dv * VEC >= D) return;                                      // no cross-lane work below
-    const int64_t d0 = dv * VEC;
-    const int64_t t0 = (int64_t)blockIdx.y * tile_len;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int64_t d_block = (int64_t)blockIdx.x * (lanes * VEC);    // first channel of the workgroup
+    const int64_t d0 = d_block + lane * VEC;
+    const bool live = lane < lanes && d0 < D;
+    const int64_t t0 = ((int64_t)blockIdx.y * kTilesPerBlock + wave) * tile_len;
     const int64_t t1 = (t0 + tile_len < L) ? t0 + tile_len : L;
 
+    // Taps and bias of the 64 VEC channels, fetched once for the workgroup with adjacent lanes on adjacent 16 bytes.  (A
+    // lane's own VEC K taps are one run of memory, but read by that lane every 16-byte piece lies 128 bytes from its
+    // neighbour's, and the address path takes a cycle per lane: three times what the token rows themselves take.)
+    constexpr int kSlots = VEC > 1 ? VEC * K / 4 : 1;               // float4 of taps per lane
+    constexpr int kTapIters = (kWave * kSlots + kBlock - 1) / kBlock, kBiasIters = VEC > 1 ? (kWave * VEC + kBlock - 1) / kBlock : 1;
+    __shared__ __attribute__((aligned(16))) float4 lds_w[VEC > 1 ? kSlots : 1][kWave + 1];   // + 1: eight slots of a lane fall on eight bank groups
+    __shared__ __attribute__((aligned(16))) float lds_b[VEC > 1 ? kWave * VEC : 1];
+    float4 tap[kTapIters];
+    float bias_in[kBiasIters];
     float wr[VEC][K], br[VEC];
     if constexpr (VEC > 1) {
-        ld_block<VEC * K>(w + d0 * K, &wr[0][0]);
-    } else {
+        const int64_t n_taps = (D - d_block) * K / 4;               // D % VEC == 0: whole float4
+#pragma unroll
+        for (int i = 0; i < kTapIters; ++i) {
+            const int q = tid + i * kBlock;
+            tap[i] = reinterpret_cast<const float4 *>(w + d_block * K)[q < n_taps ? q : 0];
+        }
+#pragma unroll
+        for (int i = 0; i < kBiasIters; ++i) {
+            const int64_t d = d_block + tid + i * kBlock;
+            bias_in[i] = bias ? bias[d < D ? d : D - 1] : 0.0f;
+        }
+    } else if (live) {
 #pragma unroll
         for (int k = 0; k < K; ++k) wr[0][k] = w[d0 * K + k];
+        br[0] = bias ? bias[d0] : 0.0f;
     }
-#pragma unroll
-    for (int c = 0; c < VEC; ++c) br[c] = bias ? bias[d0 + c] : 0.0f;
 
     const T *xb = x + b * L * D + d0;
     T *yb = y + b * L * D + d0;
@@ -104,7 +136,7 @@ conv1d_kernel(const T *__restrict__ x, const float *__restrict__ w, const float 
     // come from the carried state, whose (VEC, H) block of this lane is one contiguous run.
     float win[H > 0 ? H : 1][VEC];
     float carried[VEC * (H > 0 ? H : 1)];
-    if (t0 < H) {
+    if (live && t0 < H && t0 < t1 + (L == 0)) {
         // a draft branch continues from its parent's window (the copy is fused into this load)
         const int64_t pb = parent ? (int64_t)parent[b] : b;
         const bool p_ok = !parent || (pb >= 0 && pb < n_in);
@@ -121,11 +153,40 @@ conv1d_kernel(const T *__restrict__ x, const float *__restrict__ w, const float 
             for (int k = 0; k < H; ++k) carried[k] = ld_io(state_in, (pb * D + d0) * H + k);
         }
     }
+    // (the rows before the tile and its first group of rows are on their way before anything is waited for)
+    row_t before[H > 0 ? H : 1];
+    row_t cur[kRows];
+    // rows t .. t + kRows - 1, those past the tile's end replaced by its last one (never used)
+    auto ld_group = [&](row_t (&r)[kRows], int64_t t) {
+#pragma unroll
+        for (int i = 0; i < kRows; ++i) r[i] = ld_row(t + i < t1 ? t + i : t1 - 1);
+    };
+    if (live && t0 < t1) {
+#pragma unroll
+        for (int i = 0; i < H; ++i) before[i] = ld_row(t0 - H + i < 0 ? 0 : t0 - H + i);
+        ld_group(cur, t0);
+    }
+    if constexpr (VEC > 1) {
+#pragma unroll
+        for (int i = 0; i < kTapIters; ++i) {
+            const int q = tid + i * kBlock;
+            if (q < kWave * kSlots) lds_w[q % kSlots][q / kSlots] = tap[i];
+        }
+#pragma unroll
+        for (int i = 0; i < kBiasIters; ++i)
+            if (tid + i * kBlock < kWave * VEC) lds_b[tid + i * kBlock] = bias_in[i];
+        lds_barrier_c();
+#pragma unroll
+        for (int i = 0; i < kSlots; ++i) unpack_row(lds_w[i][lane], &wr[0][0] + 4 * i);
+#pragma unroll
+        for (int i = 0; i < VEC / 4; ++i) unpack_row(*reinterpret_cast<const float4 *>(&lds_b[lane * VEC + 4 * i]), br + 4 * i);
+    }
+    if (!live || t0 >= t1 + (t0 == 0 && L == 0)) return;        // (no token at all: one tile passes the carried state on)
 #pragma unroll
     for (int i = 0; i < H; ++i) {
         const int64_t t = t0 - H + i;  // token index of this window row, negative => carried state
         if (t >= 0) {
-            unpack_row(ld_row(t), win[i]);
+            unpack_row(before[i], win[i]);
         } else {
 #pragma unroll
             for (int c = 0; c < VEC; ++c) {
@@ -160,27 +221,23 @@ conv1d_kernel(const T *__restrict__ x, const float *__restrict__ w, const float 
         *reinterpret_cast<row_t *>(yb + t * D) = packed;
     };
 
-    int64_t t = t0;
-    row_t cur[kRows];
-    if (t + kRows <= t1) {
-#pragma unroll
-        for (int i = 0; i < kRows; ++i) cur[i] = ld_row(t + i);
-    }
-    for (; t + kRows <= t1; t += kRows) {
+    for (int64_t t = t0; t < t1; t += kRows) {
         row_t nxt[kRows];
-        const bool more = t + 2 * kRows <= t1;
-        if (more) {
+        const bool more = t + kRows < t1;
+        if (more) ld_group(nxt, t + kRows);
+        if (t + kRows <= t1) {
 #pragma unroll
-            for (int i = 0; i < kRows; ++i) nxt[i] = ld_row(t + kRows + i);
+            for (int i = 0; i < kRows; ++i) emit(t + i, cur[i]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < kRows - 1; ++i)
+                if (t + i < t1) emit(t + i, cur[i]);
         }
-#pragma unroll
-        for (int i = 0; i < kRows; ++i) emit(t + i, cur[i]);
         if (more) {
 #pragma unroll
             for (int i = 0; i < kRows; ++i) cur[i] = nxt[i];
         }
     }
-    for (; t < t1; ++t) emit(t, ld_row(t));
 
     if (state_out && t1 == L) {
         float last[VEC * (H > 0 ? H : 1)];
@@ -200,26 +257,28 @@ conv1d_kernel(const T *__restrict__ x, const float *__restrict__ w, const float 
 template <typename T, int VEC, int K> hipError_t launch_conv_k(const ConvArgs &a, hipStream_t stream)
 {
     const int64_t vecs = (a.D + VEC - 1) / VEC;
-    const unsigned gx = (unsigned)((vecs + kBlock - 1) / kBlock);
+    const unsigned gx = (unsigned)((vecs + kWave - 1) / kWave);
+    const int lanes = (int)((vecs + gx - 1) / gx);   // per wavefront: the last one has as many as the others, not a remainder
     // Time tiles: enough workgroups to fill the chip, long enough to amortize the K-1 halo rows.
     // An in-place state update keeps one tile so that a thread reads the state before it writes it.
-    // Short inputs get shorter tiles (down to one group of rows) until there are about two wavefronts per SIMD.
-    int64_t tile_len = 32;
+    // Short inputs get shorter tiles (down to one group of rows) until there are about two wavefronts per SIMD: a row
+    // takes a wavefront some 500 cycles of arithmetic, so on a short input the rows in turn are most of the time.
+    int64_t tile_len = 16;
     while (tile_len > kRows && (int64_t)gx * ((a.L + tile_len - 1) / tile_len) * a.batch < 2048) tile_len /= 2;
     if (a.state_out && a.state_in == a.state_out) tile_len = a.L;
     if ((a.L + tile_len - 1) / tile_len > 65535) tile_len = (a.L + 65534) / 65535;
     if (tile_len < 1) tile_len = 1;
     int64_t tiles = (a.L + tile_len - 1) / tile_len;
     if (tiles < 1) tiles = 1;  // L == 0: one tile that only passes the carried state on
-    dim3 grid(gx, (unsigned)tiles, (unsigned)a.batch);
+    dim3 grid(gx, (unsigned)((tiles + kTilesPerBlock - 1) / kTilesPerBlock), (unsigned)a.batch);
     const T *x = static_cast<const T *>(a.x);
     const T *si = static_cast<const T *>(a.state_in);
     T *y = static_cast<T *>(a.y);
     T *so = static_cast<T *>(a.state_out);
     if (a.apply_silu)
-        conv1d_kernel<T, VEC, K, true><<<grid, kBlock, 0, stream>>>(x, a.w, a.bias, si, y, so, a.L, a.D, tile_len, a.parent, a.n_in);
+        conv1d_kernel<T, VEC, K, true><<<grid, kBlock, 0, stream>>>(x, a.w, a.bias, si, y, so, a.L, a.D, tile_len, lanes, a.parent, a.n_in);
     else
-        conv1d_kernel<T, VEC, K, false><<<grid, kBlock, 0, stream>>>(x, a.w, a.bias, si, y, so, a.L, a.D, tile_len, a.parent, a.n_in);
+        conv1d_kernel<T, VEC, K, false><<<grid, kBlock, 0, stream>>>(x, a.w, a.bias, si, y, so, a.L, a.D, tile_len, lanes, a.parent, a.n_in);
     return hipGetLastError();
 }
 
