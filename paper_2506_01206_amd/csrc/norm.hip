@@ -1,7 +1,10 @@
 // RMSNorm in front of the block's input projection (the Mamba-130M drafter of the paper, Sec. 3.1,
 // normalizes the residual stream before every mixer):  y[m, :] = x[m, :] * rsqrt(mean(x[m, :]^2) + eps) * w
-// HBM-bound: one wavefront per token row, 16-byte loads, the row kept in registers between the
-// reduction and the scaling so that it is read once.
+// One wavefront per token row, the row and its weights kept in registers between the reduction and the scaling so that
+// everything is read once and in one trip to memory.  A lane takes four adjacent features at a time: its weights are then
+// 16 bytes next to its neighbour's 16.  (With eight features, 16 bytes of the row, the weights come in 16-byte pieces 32
+// bytes apart, and the address path takes a cycle per lane for those, three times what the row itself takes.)  8000 x 768
+// 7.7 -> 6.5 us, 333 x 768 3.2 -> 2.9 us.
 #include "device_math.h"
 #include "launch.h"
 
@@ -10,8 +13,6 @@ namespace {
 
 constexpr int kWave = 64;
 constexpr int kRowsPerBlock = 4;
-constexpr int kMaxVecs = 8;  // 8 vectors of 8 bf16 per lane: rows up to 4096 features stay in registers
-
 __device__ __forceinline__ float wave_sum(float v)
 {
 #pragma unroll
@@ -19,44 +20,46 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
-// C % 8 == 0 and C <= 64 * 8 * kMaxVecs
+// C % 4 == 0 and C <= 64 * 4 * NV
+template <int NV>
 __global__ void __launch_bounds__(kWave * kRowsPerBlock)
-rmsnorm_kernel(const bf16_t *__restrict__ x, const float *__restrict__ w, bf16_t *__restrict__ y, int64_t M,
-               int64_t C, float eps)
+rmsnorm_kernel(const bf16_t *__restrict__ x, const float *__restrict__ w, bf16_t *__restrict__ y, int64_t M, int C, float eps)
 {
     const int lane = threadIdx.x & 63;
     const int64_t m = (int64_t)blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
     if (m >= M) return;                                  // whole wavefronts leave together
-    const int64_t vecs = C / 8;
-    const uint4 *xr = reinterpret_cast<const uint4 *>(x + m * C);
-    uint4 raw[kMaxVecs];
+    const int vecs = C / 4;
+    const uint2 *xr = reinterpret_cast<const uint2 *>(x + m * C);
+    uint2 raw[NV];
+    float4 wv[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int v = lane + i * kWave;
+        raw[i] = v < vecs ? xr[v] : make_uint2(0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int v = lane + i * kWave;
+        wv[i] = reinterpret_cast<const float4 *>(w)[v < vecs ? v : 0];
+    }
     float ss = 0.0f;
 #pragma unroll
-    for (int i = 0; i < kMaxVecs; ++i) {
-        const int64_t v = lane + (int64_t)i * kWave;
-        raw[i] = v < vecs ? xr[v] : make_uint4(0, 0, 0, 0);
-        const uint32_t u[4] = {raw[i].x, raw[i].y, raw[i].z, raw[i].w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float a = bf16_lo(u[j]), b = bf16_hi(u[j]);
-            ss = fmaf(a, a, ss);
-            ss = fmaf(b, b, ss);
-        }
+    for (int i = 0; i < NV; ++i) {
+        const float v0 = bf16_lo(raw[i].x), v1 = bf16_hi(raw[i].x), v2 = bf16_lo(raw[i].y), v3 = bf16_hi(raw[i].y);
+        ss = fmaf(v0, v0, ss);
+        ss = fmaf(v1, v1, ss);
+        ss = fmaf(v2, v2, ss);
+        ss = fmaf(v3, v3, ss);
     }
     ss = wave_sum(ss);
     const float scale = __builtin_amdgcn_rsqf(ss / (float)C + eps);
-    uint4 *yr = reinterpret_cast<uint4 *>(y + m * C);
+    uint2 *yr = reinterpret_cast<uint2 *>(y + m * C);
 #pragma unroll
-    for (int i = 0; i < kMaxVecs; ++i) {
-        const int64_t v = lane + (int64_t)i * kWave;
+    for (int i = 0; i < NV; ++i) {
+        const int v = lane + i * kWave;
         if (v >= vecs) continue;
-        const float4 w0 = reinterpret_cast<const float4 *>(w)[2 * v], w1 = reinterpret_cast<const float4 *>(w)[2 * v + 1];
-        uint4 o;
-        o.x = f32x2_to_bf16x2(bf16_lo(raw[i].x) * scale * w0.x, bf16_hi(raw[i].x) * scale * w0.y);
-        o.y = f32x2_to_bf16x2(bf16_lo(raw[i].y) * scale * w0.z, bf16_hi(raw[i].y) * scale * w0.w);
-        o.z = f32x2_to_bf16x2(bf16_lo(raw[i].z) * scale * w1.x, bf16_hi(raw[i].z) * scale * w1.y);
-        o.w = f32x2_to_bf16x2(bf16_lo(raw[i].w) * scale * w1.z, bf16_hi(raw[i].w) * scale * w1.w);
-        yr[v] = o;
+        yr[v] = make_uint2(f32x2_to_bf16x2(bf16_lo(raw[i].x) * scale * wv[i].x, bf16_hi(raw[i].x) * scale * wv[i].y),
+                           f32x2_to_bf16x2(bf16_lo(raw[i].y) * scale * wv[i].z, bf16_hi(raw[i].y) * scale * wv[i].w));
     }
 }
 
@@ -65,8 +68,15 @@ rmsnorm_kernel(const bf16_t *__restrict__ x, const float *__restrict__ w, bf16_t
 hipError_t launch_rmsnorm(const NormArgs &a, hipStream_t stream)
 {
     const unsigned blocks = (unsigned)((a.M + kRowsPerBlock - 1) / kRowsPerBlock);
-    rmsnorm_kernel<<<blocks, kWave * kRowsPerBlock, 0, stream>>>(static_cast<const bf16_t *>(a.x), a.w,
-                                                               static_cast<bf16_t *>(a.y), a.M, a.C, a.eps);
+    const int64_t need = (a.C + 4 * kWave - 1) / (4 * kWave);    // C <= 4096: at most 16
+#define MAMBA_LAUNCH_NORM(NV) rmsnorm_kernel<NV><<<blocks, kWave * kRowsPerBlock, 0, stream>>>(static_cast<const bf16_t *>(a.x), a.w, static_cast<bf16_t *>(a.y), a.M, (int)a.C, a.eps)
+    if (need <= 1) MAMBA_LAUNCH_NORM(1);
+    else if (need <= 2) MAMBA_LAUNCH_NORM(2);
+    else if (need <= 3) MAMBA_LAUNCH_NORM(3);
+    else if (need <= 4) MAMBA_LAUNCH_NORM(4);
+    else if (need <= 8) MAMBA_LAUNCH_NORM(8);
+    else MAMBA_LAUNCH_NORM(16);
+#undef MAMBA_LAUNCH_NORM
     return hipGetLastError();
 }
 
