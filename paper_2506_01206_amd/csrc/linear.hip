@@ -618,8 +618,8 @@ linear_split_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, 
 //     here, one 16x16x16 MFMA per 16 of its outputs and 16 rows, and leave as partial sums (row, column block, output):
 //     runs of `n` floats per row, so that both sides move whole lines.
 // Measured on the drafter's shapes (12 rows, weights rotating through 24 layers, per launch in a replayed graph), against
-// 32-column tiles that went through LDS patches: in_proj with everything 9.0 -> 5.4 us, out_proj 5.8 -> 3.9 us; with 64
-// rows 18.2 -> 10.0 and 10.3 -> 4.0 us.  (Fragments straight from memory: 5.7, 4.8, 11.0 and 5.1 us.  16 wavefronts, or
+// 32-column tiles that went through LDS patches: in_proj with everything 9.0 -> 5.0 us, out_proj 5.8 -> 3.9 us; with 64
+// rows 18.2 -> 9.9 and 10.3 -> 4.0 us.  (Fragments straight from memory: 5.7, 4.8, 11.0 and 5.1 us.  16 wavefronts, or
 // six k steps in flight instead of three, measured the same.)
 typedef short bf16x4_bits __attribute__((ext_vector_type(4)));
 typedef float f32x4v __attribute__((ext_vector_type(4)));
@@ -643,6 +643,7 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
     constexpr int kXcRow = 24;                                     // elements between rows of the finished columns in LDS (48 bytes: 8-byte aligned, spread over the banks)
     __shared__ __attribute__((aligned(16))) uint4 patch[NW][1 + MT][G][64];
     __shared__ __attribute__((aligned(16))) float part[NW][MT][4][64];
+    __shared__ __attribute__((aligned(16))) float4 norm_lds[NORM ? NW : 1][G * 8];
     __shared__ __attribute__((aligned(16))) float ssq[MT * 16][NW];
     __shared__ __attribute__((aligned(16))) uint16_t xc[CONV ? MT * 16 * kXcRow : 8];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -701,7 +702,13 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
     bool windows_pending = CONV;
     for (int s0 = s_first; s0 < s_end || windows_pending; s0 += G) {
         uint4 wf[G], xf[MT][G];
-        float4 nw[NORM ? G : 1][2];
+        // the norm weights of the wavefront's 32 G k values: one 16-byte piece per lane, handed out by LDS (fetched by every lane
+        // that needs them they would be 32 bytes apart, two loads per step at a cycle of the address path per lane)
+        float4 nw;
+        if constexpr (NORM) {
+            const int f = 8 * s0 + lane;
+            nw = reinterpret_cast<const float4 *>(norm_w)[lane < 8 * G && f < 2 * kchunks ? f : 0];
+        }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const int c = 4 * (s0 + g) + lch;
@@ -710,10 +717,6 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
             wf[g] = wrow[cc];
 #pragma unroll
             for (int t = 0; t < MT; ++t) xf[t][g] = xrow[t][cc];
-            if constexpr (NORM) {
-                nw[g][0] = reinterpret_cast<const float4 *>(norm_w)[2 * cc];
-                nw[g][1] = reinterpret_cast<const float4 *>(norm_w)[2 * cc + 1];
-            }
         }
         if (CONV && windows_pending) {
             // the windows behind the parent index, once the main loop's first requests are on their way
@@ -734,11 +737,15 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
 #pragma unroll
             for (int r = 0; r < 3; ++r) {
                 const int task = r * NW + wave;
-                const int row = (task < xp_tasks ? task % (xp_tiles ? xp_tiles : 1) : 0) * 16 + li;
-                if (xp_on) xw[r] = *reinterpret_cast<const uint2 *>(xp.w + (int64_t)(row < xp.n ? row : xp.n - 1) * xp.ldw + n0 + 4 * lg);
+                const int row = task % (xp_tiles ? xp_tiles : 1) * 16 + li;
+                if (xp_on && task < xp_tasks) xw[r] = *reinterpret_cast<const uint2 *>(xp.w + (int64_t)(row < xp.n ? row : xp.n - 1) * xp.ldw + n0 + 4 * lg);
             }
         }
         __builtin_amdgcn_sched_barrier(0);                         // all of it in flight before any of it is used
+        if constexpr (NORM) {
+            if (lane < 8 * G) norm_lds[wave][lane] = nw;
+            wave_sync();
+        }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const bool ok = s0 + g < s_end && 4 * (s0 + g) + lch < kchunks;   // else zeros: adds nothing
@@ -747,7 +754,7 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
             for (int t = 0; t < MT; ++t) {
                 uint4 q = ok ? xf[t][g] : make_uint4(0, 0, 0, 0);
                 if constexpr (NORM) {
-                    const float4 g0 = nw[g][0], g1 = nw[g][1];
+                    const float4 g0 = norm_lds[wave][8 * g + 2 * lch], g1 = norm_lds[wave][8 * g + 2 * lch + 1];
                     const float v0 = bf16_lo(q.x), v1 = bf16_hi(q.x), v2 = bf16_lo(q.y), v3 = bf16_hi(q.y);
                     const float v4 = bf16_lo(q.z), v5 = bf16_hi(q.z), v6 = bf16_lo(q.w), v7 = bf16_hi(q.w);
                     ss[t] += v0 * v0 + v1 * v1 + v2 * v2 + v3 * v3 + v4 * v4 + v5 * v5 + v6 * v6 + v7 * v7;

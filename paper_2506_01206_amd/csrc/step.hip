@@ -403,7 +403,7 @@ state_step_xproj_kernel(float *h_out, const float *h_in, const int32_t *__restri
     const int64_t j = blockIdx.y;
     const int64_t row4 = D * Q;  // float4s per branch
     const float4 *a4 = reinterpret_cast<const float4 *>(A);
-    __shared__ __attribute__((aligned(16))) float xs[256], xs_side[3][256];
+    __shared__ __attribute__((aligned(16))) float xs[256], xs_side[kBlock * 4];
     const bool hold_w = dt_rank / 4 <= CW * Q;
 
     int64_t f[U], d[U];
@@ -412,7 +412,25 @@ state_step_xproj_kernel(float *h_out, const float *h_in, const int32_t *__restri
     float4 h[U], a[U], bv[U], cv[U];
     float xv[U], dv[U], zv[U], bias[U], dsk[U];
     uint2 wq[U][CW];
-    // everything that does not depend on the x projection is requested first
+    // The branch's row of the x projection (dt low rank | B | C) arrives as n_parts partial sums: they are added
+    // up in order and rounded to bf16, as the stored tensors they replace would have been.  A part is one run of
+    // dt_rank + 2 N floats (a multiple of four); the workgroup reads as many parts side by side as it has threads for, 16
+    // bytes each and a contiguous range of parts, and adds those few sums up from LDS.  The parts are what the step waits
+    // for first, so the first eight of a range are requested ahead of everything else (behind the state row they would
+    // wait for the parent index): 12 x 1536 channels 4.6 -> 4.2 us, 3 x 1536 4.3 -> 3.8 us.
+    constexpr int kParts = 8;
+    const int xn = (int)dt_rank + 2 * N, xn4 = xn / 4;
+    const int sides = min(kBlock / xn4, n_parts);
+    const int side = (int)threadIdx.x / xn4, k4 = (int)threadIdx.x - side * xn4;
+    const int per = (n_parts + sides - 1) / sides, first = side * per, last = min(first + per, n_parts);
+    const bool adds = side < sides && first < last;
+    const float4 *pr = reinterpret_cast<const float4 *>(xpart) + j * n_parts * xn4 + k4;
+    float4 pv[kParts];
+    if (adds) {
+#pragma unroll
+        for (int u = 0; u < kParts; ++u) pv[u] = pr[(int64_t)min(first + u, last - 1) * xn4];
+    }
+    // then everything else that does not depend on the x projection
 #pragma unroll
     for (int i = 0; i < U; ++i) {
         const int64_t f_raw = ((int64_t)blockIdx.x * U + i) * kBlock + threadIdx.x;
@@ -440,32 +458,22 @@ state_step_xproj_kernel(float *h_out, const float *h_in, const int32_t *__restri
     const float4 *hin4 = reinterpret_cast<const float4 *>(h_in) + (p_ok ? p : 0) * row4;
 #pragma unroll
     for (int i = 0; i < U; ++i) h[i] = ld_stream(hin4 + f[i]);
-    // The branch's row of the x projection (dt low rank | B | C) arrives as n_parts partial sums: they are added
-    // up in order and rounded to bf16, as the stored tensors they replace would have been.  A part is one run of
-    // dt_rank + 2 N floats; the workgroup reads as many parts side by side as it has threads for, each a contiguous
-    // range of them, and adds those few sums up from LDS.
     {
-        const int xn = (int)dt_rank + 2 * N;
-        const int sides = xn <= kBlock / 3 ? 3 : xn <= kBlock / 2 ? 2 : 1;
-        const int side = (int)threadIdx.x / xn, k = (int)threadIdx.x - side * xn;
         if (side < sides) {
-            const int per = (n_parts + sides - 1) / sides, first = side * per, last = min(first + per, n_parts);
-            const float *pr = xpart + j * n_parts * xn + k;
-            float sum = 0.0f;
-            for (int c = first; c < last; c += 16) {
-                float v[16];
+            float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            auto add = [&](float4 v) { sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w; };
+            if (adds) {
 #pragma unroll
-                for (int u = 0; u < 16; ++u) v[u] = pr[(int64_t)min(c + u, last - 1) * xn];
-#pragma unroll
-                for (int u = 0; u < 16; ++u)
-                    if (c + u < last) sum += v[u];
+                for (int u = 0; u < kParts; ++u)
+                    if (first + u < last) add(pv[u]);
+                for (int c = first + kParts; c < last; ++c) add(pr[(int64_t)c * xn4]);
             }
-            xs_side[side][k] = sum;
+            *reinterpret_cast<float4 *>(&xs_side[side * xn + 4 * k4]) = sum;
         }
         __syncthreads();
         if ((int)threadIdx.x < xn) {
-            float sum = xs_side[0][threadIdx.x];
-            for (int u = 1; u < sides; ++u) sum += xs_side[u][threadIdx.x];
+            float sum = 0.0f;
+            for (int u = 0; u < sides; ++u) sum += xs_side[u * xn + threadIdx.x];
             xs[threadIdx.x] = bf16_to_f32(f32_to_bf16(sum));
         }
         __syncthreads();
