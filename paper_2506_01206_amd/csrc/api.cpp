@@ -580,10 +580,18 @@ int mamba_block_fwd(const mamba_block_params_t *p, const void *hidden, void *hid
     if ((rc = mamba_linear_fwd(bb.d, p->in_proj_w, nullptr, nullptr, bb.a, Di, bb.b, Di, nullptr, 0, rows, p->d_model, io, hip_stream))) return rc;
     // x_c = silu(conv1d(x))                                 -> c
     if ((rc = mamba_conv1d_fwd(bb.a, p->conv_w, p->conv_b, conv_state_in, bb.c, conv_state_out, batch, L, Di, p->d_conv, 1, io, hip_stream))) return rc;
-    // [dt_low | B | C] = x_c W_x^T
-    if ((rc = mamba_linear_fwd(bb.c, p->x_proj_w, nullptr, nullptr, bb.dtl, R, bb.bm, N, bb.cm, N, rows, Di, io, hip_stream))) return rc;
-    // dt = dt_low W_dt^T                                    -> a (x is dead)
-    if ((rc = mamba_linear_fwd(bb.dtl, p->dt_proj_w, nullptr, nullptr, bb.a, Di, nullptr, 0, nullptr, 0, rows, R, io, hip_stream))) return rc;
+    // [dt_low | B | C] = x_c W_x^T,  dt = dt_low W_dt^T       -> a (x is dead)
+    if (xdt_applies(rows, Di, R, N)) {
+        const int64_t xw = (R + 2 * N) * Di * 2, low = rows * R * 2, bc = rows * N * 2;   // (sizes that block_layout has checked)
+        if (overlap(bb.dtl, low, p->x_proj_w, xw) || overlap(bb.bm, bc, p->x_proj_w, xw) || overlap(bb.cm, bc, p->x_proj_w, xw) ||
+            overlap(bb.a, rows * Di * 2, p->dt_proj_w, Di * R * 2))
+            return MAMBA_ERR_ALIAS;
+        const XdtArgs xa{bb.c, p->x_proj_w, p->dt_proj_w, bb.dtl, bb.bm, bb.cm, bb.a, rows, Di, R};
+        if (hipError_t e = launch_xdt(xa, static_cast<hipStream_t>(hip_stream))) return (int)e;
+    } else {
+        if ((rc = mamba_linear_fwd(bb.c, p->x_proj_w, nullptr, nullptr, bb.dtl, R, bb.bm, N, bb.cm, N, rows, Di, io, hip_stream))) return rc;
+        if ((rc = mamba_linear_fwd(bb.dtl, p->dt_proj_w, nullptr, nullptr, bb.a, Di, nullptr, 0, nullptr, 0, rows, R, io, hip_stream))) return rc;
+    }
     // y = scan(...) gated by silu(z)                        -> d (u is dead)
     if ((rc = mamba_scan_fwd(bb.c, bb.a, p->A, bb.bm, bb.cm, p->Dskip, bb.b, p->dt_bias, h0, bb.d, h_final,
                              bb.scan_ws_bytes ? bb.scan_ws : nullptr, bb.scan_ws_bytes, batch, L, Di, N, 0, 1, io, hip_stream)))

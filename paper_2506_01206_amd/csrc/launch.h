@@ -181,6 +181,16 @@ struct LinearArgs {
 };
 hipError_t launch_linear(const LinearArgs &a, hipStream_t stream);
 
+// x_proj and dt_proj of a context as one kernel: [dtl | bm | cm] = xc wx^T, dt = dtl wdt^T, all bf16.
+// xc, dt: (M, d_inner); wx: (dt_rank + 2 N, d_inner); wdt: (d_inner, dt_rank); dtl: (M, dt_rank); bm, cm: (M, N).
+struct XdtArgs {
+    const void *xc, *wx, *wdt;
+    void *dtl, *bm, *cm, *dt;
+    int64_t M, d_inner, dt_rank;
+};
+bool xdt_applies(int64_t M, int64_t d_inner, int64_t dt_rank, int64_t N);   // shapes it is built for and faster on than two launches
+hipError_t launch_xdt(const XdtArgs &a, hipStream_t stream);
+
 struct NormArgs {
     const void *x;           // (M, C) bf16
     const float *w;          // (C)

@@ -1282,6 +1282,20 @@ def test_block_prefill_against_oracle(m, B, L, dm, D, N, K, R):
     assert torch.equal(h2, out)
 
 
+@pytest.mark.parametrize("B,L,D,R", [(1, 768, 64, 32), (3, 301, 576, 48), (1, 1361, 1536, 64),      # 16 rows, three column groups
+                                     (2, 683, 320, 48), (1, 4095, 128, 32),                         # two column groups; one
+                                     (1, 4097, 192, 48), (7, 601, 640, 64), (1, 8192, 64, 32),      # 32 rows
+                                     (1, 8193, 192, 48), (2, 4500, 128, 32)])                       # 64 rows
+def test_block_x_and_dt_projection_in_one_pass(m, B, L, D, R):
+    """x_proj and dt_proj as one kernel, at the edges of its row tiles, column groups and k split (fewer k steps than
+    wavefronts, a number that does not divide evenly, widths where some wavefronts have no dt block), stage by stage."""
+    say(B=B, L=L, D=D, R=R)
+    rng = np.random.default_rng(B * 1000 + L + D + R)
+    w, w64, blk = make_block(m, rng, 64, D, 16, 4, R)
+    hid = synth.to_io(rng.standard_normal((B, L, 64)).astype(np.float32), synth.BF16)
+    check_block_stages(m, blk, w64, hid)
+
+
 @pytest.mark.parametrize("tree", [(3, 2, 1), (1, 1), (4,), (33, 2, 1), (66, 2)])
 def test_block_decode_steps_against_oracle(m, tree):
     """Tree drafting through whole blocks: at every draft position each branch continues from its
