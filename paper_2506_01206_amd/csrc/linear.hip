@@ -603,11 +603,15 @@ linear_split_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, 
 // ---------------------------------------------------------------------------------------------------
 // A draft position (M <= 64 rows, Sec. 4.1): w is read once, nothing is big, and what counts is the number of trips to
 // memory and of barriers between the launch and the last store.  One workgroup per 16 output columns (192 of them for
-// in_proj, twice what 32 columns give) and 16 MT rows, its eight wavefronts share the k range in contiguous pieces of k32 steps.
+// in_proj, twice what 32 columns give) and 16 MT rows, its eight wavefronts share the k range in contiguous pieces of steps.
 // A fragment of v_mfma_f32_16x16x32_bf16 wants row l % 16 in lane l; loaded like that, no two lanes of a quad share a
 // 64-byte piece of a line and the address path takes a cycle per lane (60 for the 1 KiB, measured over 192 loads a CU).
-// With a row's 64 bytes on the four lanes of a quad it takes 34, so that is how rows are loaded; a 1 KiB patch of LDS
-// private to the wavefront turns them into fragments.
+// With a row's 64 bytes on the four lanes of a quad it takes 34, with 128 on eight lanes about half of that, so that is
+// how rows are loaded; a patch of LDS private to the wavefront turns them into fragments.  KW: the k of a step, 64 (whole
+// lines) from K = 1024 on, where every wavefront has two steps or more: out_proj of 12 rows 3.9 -> 3.6 us, x_proj of 333
+// rows 3.9 -> 3.7, 128 rows x 768 5.2 -> 4.4.  On a shorter k steps of 64 leave wavefronts with one step or none and asking
+// for rows that do not exist (64 x 1024, K = 512: 2.9 us against 3.4; in_proj of a draft position 5.0 against 6.0), and a
+// branch around those requests costs more than it saves (3.6 -> 3.9 us).
 // The partial tiles of the wavefronts meet in LDS, one output per thread; what else an output needs (bias, residual, the
 // carried conv window behind the parent index) has been on its way since before the main loop.
 // IN (in_proj of a draft position): norm, conv and next projection ride along.
@@ -631,26 +635,34 @@ __device__ __forceinline__ float sum_over_quad(float v)
     return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4e, 0xf, 0xf, false));   // quad_perm [2,3,0,1]
 }
 
-template <int MT, bool IN>
+template <int MT, bool IN, int KW>
 __global__ void __launch_bounds__(512)
 linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, const float *__restrict__ bias,
                   const bf16_t *residual, OutSplit out, int M, int N, int K, const float *__restrict__ norm_w, float eps,
                   ConvTail conv, XprojTail xp)
 {
-    constexpr int NW = 8, kThr = NW * 64, G = 3;                   // G: k32 steps in flight per wavefront
+    constexpr int NW = 8, kThr = NW * 64, G = 3;                   // G: k steps in flight per wavefront
+    constexpr int C = KW / 8;                                      // 16-byte chunks of a row in a step of KW
+    constexpr int LT = C / 4, RL = 16 / LT;                        // loads per 16-row tile, rows per load
+    constexpr int PB = KW == 32 ? G : 2;                           // patches in turn
     constexpr int OPT = (MT * 256 + kThr - 1) / kThr;              // outputs per thread
     constexpr bool NORM = IN, CONV = IN;
+    static_assert(KW == 32 || (KW == 64 && !IN), "the sum of squares is reduced over quads");
     constexpr int kXcRow = 24;                                     // elements between rows of the finished columns in LDS (48 bytes: 8-byte aligned, spread over the banks)
-    __shared__ __attribute__((aligned(16))) uint4 patch[NW][1 + MT][G][64];
+    __shared__ __attribute__((aligned(16))) uint4 patch[NW][PB][1 + MT][64 * LT];
     __shared__ __attribute__((aligned(16))) float part[NW][MT][4][64];
-    __shared__ __attribute__((aligned(16))) float4 norm_lds[NORM ? NW : 1][G * 8];
+    __shared__ __attribute__((aligned(16))) float4 norm_lds[NORM ? NW : 1][G * 2 * C];
     __shared__ __attribute__((aligned(16))) float ssq[MT * 16][NW];
     __shared__ __attribute__((aligned(16))) uint16_t xc[CONV ? MT * 16 * kXcRow : 8];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int li = lane & 15, lg = lane >> 4;                      // fragment view: row, 16-byte chunk of the step
-    const int lrow = lane >> 2, lch = lane & 3;                    // load view
-    const int put = lrow * 4 + (lch ^ (lrow >> 2)), get = li * 4 + (lg ^ (li >> 2));   // xor: no bank conflicts either way
+    const int li = lane & 15, lg = lane >> 4;                      // fragment view: row, 16-byte chunk of a k32 half
+    const int lrow = lane / C, lch = lane % C;                     // load view: row (+ RL), 16-byte chunk of the step
+    auto slot = [](int row, int chunk) { return row * C + (chunk ^ (C == 8 ? row & 7 : row >> 2)); };   // no bank conflicts either way
+    const int put = slot(lrow, lch);                               // + 64: RL rows further
+    int get[LT];
+#pragma unroll
+    for (int h = 0; h < LT; ++h) get[h] = slot(li, lg + 4 * h);
     const int n0 = blockIdx.x * 16, m0 = blockIdx.y * (16 * MT);
     const int w0 = (int)out.width[0], w1 = (int)out.width[1];
 
@@ -678,15 +690,19 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
         if (CONV && conv.parent && on[j] < w0) tail[j].parent = conv.parent[om[j]];
     }
 
-    // ---- the wavefront's share of k: steps [s_first, s_end) of 32
-    const int steps = (K + 31) >> 5, per = (steps + NW - 1) / NW;
+    // ---- the wavefront's share of k: steps [s_first, s_end) of KW
+    const int steps = (K + KW - 1) / KW, per = (steps + NW - 1) / NW;
     const int s_first = wave * per, s_end = s_first + per < steps ? s_first + per : steps;
     const int kchunks = K >> 3;                                    // K % 8 == 0
-    const uint4 *wrow = reinterpret_cast<const uint4 *>(w + (int64_t)(n0 + lrow < N ? n0 + lrow : N - 1) * K);
-    const uint4 *xrow[MT];
+    const uint4 *wrow[LT], *xrow[LT * MT];
 #pragma unroll
-    for (int t = 0; t < MT; ++t) {
-        const int m = m0 + 16 * t + lrow;
+    for (int t = 0; t < LT; ++t) {
+        const int n = n0 + RL * t + lrow;
+        wrow[t] = reinterpret_cast<const uint4 *>(w + (int64_t)(n < N ? n : N - 1) * K);
+    }
+#pragma unroll
+    for (int t = 0; t < LT * MT; ++t) {
+        const int m = m0 + RL * t + lrow;
         xrow[t] = reinterpret_cast<const uint4 *>(x + (int64_t)(m < M ? m : M - 1) * K);   // rows past M repeat the last one, never stored
     }
     f32x4v acc[MT];
@@ -701,22 +717,22 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
     uint2 xw[3] = {};
     bool windows_pending = CONV;
     for (int s0 = s_first; s0 < s_end || windows_pending; s0 += G) {
-        uint4 wf[G], xf[MT][G];
-        // the norm weights of the wavefront's 32 G k values: one 16-byte piece per lane, handed out by LDS (fetched by every lane
-        // that needs them they would be 32 bytes apart, two loads per step at a cycle of the address path per lane)
+        uint4 wf[LT][G], xf[LT * MT][G];
+        // the norm weights of the wavefront's KW G k values: one 16-byte piece per lane, handed out by LDS (fetched by every lane
+        // that needs them they would be 32 bytes apart, loads at a cycle of the address path per lane)
         float4 nw;
         if constexpr (NORM) {
-            const int f = 8 * s0 + lane;
-            nw = reinterpret_cast<const float4 *>(norm_w)[lane < 8 * G && f < 2 * kchunks ? f : 0];
+            const int f = 2 * C * s0 + lane;
+            nw = reinterpret_cast<const float4 *>(norm_w)[lane < 2 * C * G && f < 2 * kchunks ? f : 0];
         }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const int c = 4 * (s0 + g) + lch;
-            const bool ok = s0 + g < s_end && c < kchunks;
-            const int cc = ok ? c : 0;
-            wf[g] = wrow[cc];
+            const int c = C * (s0 + g) + lch;
+            const int cc = s0 + g < s_end && c < kchunks ? c : 0;
 #pragma unroll
-            for (int t = 0; t < MT; ++t) xf[t][g] = xrow[t][cc];
+            for (int t = 0; t < LT; ++t) wf[t][g] = wrow[t][cc];
+#pragma unroll
+            for (int t = 0; t < LT * MT; ++t) xf[t][g] = xrow[t][cc];
         }
         if (CONV && windows_pending) {
             // the windows behind the parent index, once the main loop's first requests are on their way
@@ -743,36 +759,42 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
         }
         __builtin_amdgcn_sched_barrier(0);                         // all of it in flight before any of it is used
         if constexpr (NORM) {
-            if (lane < 8 * G) norm_lds[wave][lane] = nw;
+            if (lane < 2 * C * G) norm_lds[wave][lane] = nw;
             wave_sync();
         }
+        auto fill = [&](int g) __attribute__((always_inline)) {
+            const bool ok = s0 + g < s_end && C * (s0 + g) + lch < kchunks;   // else zeros: adds nothing
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const bool ok = s0 + g < s_end && 4 * (s0 + g) + lch < kchunks;   // else zeros: adds nothing
-            patch[wave][0][g][put] = ok ? wf[g] : make_uint4(0, 0, 0, 0);
+            for (int t = 0; t < LT; ++t) patch[wave][g % PB][0][64 * t + put] = ok ? wf[t][g] : make_uint4(0, 0, 0, 0);
 #pragma unroll
-            for (int t = 0; t < MT; ++t) {
+            for (int t = 0; t < LT * MT; ++t) {
                 uint4 q = ok ? xf[t][g] : make_uint4(0, 0, 0, 0);
                 if constexpr (NORM) {
-                    const float4 g0 = norm_lds[wave][8 * g + 2 * lch], g1 = norm_lds[wave][8 * g + 2 * lch + 1];
+                    const float4 g0 = norm_lds[wave][2 * C * g + 2 * lch], g1 = norm_lds[wave][2 * C * g + 2 * lch + 1];
                     const float v0 = bf16_lo(q.x), v1 = bf16_hi(q.x), v2 = bf16_lo(q.y), v3 = bf16_hi(q.y);
                     const float v4 = bf16_lo(q.z), v5 = bf16_hi(q.z), v6 = bf16_lo(q.w), v7 = bf16_hi(q.w);
-                    ss[t] += v0 * v0 + v1 * v1 + v2 * v2 + v3 * v3 + v4 * v4 + v5 * v5 + v6 * v6 + v7 * v7;
+                    ss[t / LT] += v0 * v0 + v1 * v1 + v2 * v2 + v3 * v3 + v4 * v4 + v5 * v5 + v6 * v6 + v7 * v7;
                     q = make_uint4(f32x2_to_bf16x2(v0 * g0.x, v1 * g0.y), f32x2_to_bf16x2(v2 * g0.z, v3 * g0.w),
                                    f32x2_to_bf16x2(v4 * g1.x, v5 * g1.y), f32x2_to_bf16x2(v6 * g1.z, v7 * g1.w));
                 }
-                patch[wave][1 + t][g][put] = q;
+                patch[wave][g % PB][1 + t / LT][64 * (t % LT) + put] = q;
             }
-        }
-        wave_sync();
+        };
+#pragma unroll
+        for (int g = 0; g < (PB < G ? 1 : G); ++g) fill(g);
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const bf16x8 wv = __builtin_bit_cast(bf16x8, patch[wave][0][g][get]);
+            if (PB < G && g + 1 < G) fill(g + 1);
+            wave_sync();
 #pragma unroll
-            for (int t = 0; t < MT; ++t)
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, patch[wave][1 + t][g][get]), wv, acc[t], 0, 0, 0);
+            for (int h = 0; h < LT; ++h) {
+                const bf16x8 wv = __builtin_bit_cast(bf16x8, patch[wave][g % PB][0][get[h]]);
+#pragma unroll
+                for (int t = 0; t < MT; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, patch[wave][g % PB][1 + t][get[h]]), wv, acc[t], 0, 0, 0);
+            }
+            wave_sync();
         }
-        wave_sync();
     }
     // acc[t][i] is C[m = 16 t + 4 (lane / 16) + i][n = lane % 16]
 #pragma unroll
@@ -782,7 +804,7 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
     if constexpr (NORM) {
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
-            const float v = sum_over_quad(ss[t]);
+            float v = sum_over_quad(ss[t]);
             if (lch == 0) ssq[16 * t + lrow][wave] = v;
         }
     }
@@ -879,14 +901,15 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     const ConvTail ct{a.conv_w, a.conv_b, static_cast<const bf16_t *>(a.conv_src), static_cast<bf16_t *>(a.conv_dst),
                       a.conv_parent, a.conv_n_in, a.conv_k};
     const XprojTail xt{static_cast<const bf16_t *>(a.xproj_w), a.xproj_part, a.xproj_n, a.width[0]};
-#define MAMBA_FEW(MT, IN) linear_few_kernel<MT, IN><<<dim3((unsigned)((N + 15) / 16), (unsigned)((a.M + 16 * MT - 1) / (16 * MT))), 512, 0, stream>>>(x, w, a.bias, res, o, (int)a.M, (int)N, (int)a.K, a.norm_w, a.eps, ct, xt)
+#define MAMBA_FEW_K(MT, IN, KW) linear_few_kernel<MT, IN, KW><<<dim3((unsigned)((N + 15) / 16), (unsigned)((a.M + 16 * MT - 1) / (16 * MT))), 512, 0, stream>>>(x, w, a.bias, res, o, (int)a.M, (int)N, (int)a.K, a.norm_w, a.eps, ct, xt)
+#define MAMBA_FEW(MT) do { if (a.K >= 1024) MAMBA_FEW_K(MT, false, 64); else MAMBA_FEW_K(MT, false, 32); } while (0)
     if (a.norm_w) {
         // the way into a block at a draft position: norm and conv come together, the next projection only with them
         if (!a.conv_w || !a.conv_src || !a.conv_dst || a.conv_k < 2 || (a.xproj_w && (!a.xproj_part || a.width[0] % 16)))
             return hipErrorInvalidValue;
-        if (tiles(16, 16) <= kTilesResident) MAMBA_FEW(1, true);
-        else if (tiles(32, 16) <= kTilesResident) MAMBA_FEW(2, true);
-        else MAMBA_FEW(4, true);
+        if (tiles(16, 16) <= kTilesResident) MAMBA_FEW_K(1, true, 32);
+        else if (tiles(32, 16) <= kTilesResident) MAMBA_FEW_K(2, true, 32);
+        else MAMBA_FEW_K(4, true, 32);
         return hipGetLastError();
     }
     // Few output tiles: latency decides, and the tiles are kept so small that they just fill the CUs once (a second
@@ -895,12 +918,12 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     // they fetch x for every 16 columns anew, so beyond that the 32-column tiles: 32 rows from where every wavefront has
     // a k block, 64 rows from where it has two (on less the slab kernel, 64 x 64 tiles, is as fast).
     // us on      16x16 32x16 64x16 32x32 64x32 slabs  (x: more than one round)
-    //   64 x 1024, K = 512    2.9   3.3   4.0   4.8   6.5   5.6        333 x 80, K = 1536    3.9   5.3   6.5   5.7   7.6  10.4
-    //  128 x  768, K = 1536   5.2x  5.3   6.6   5.9   8.2  10.9        333 x 640, K = 768    5.1x  5.7x  4.7   5.3   7.1   7.0
-    //  256 x  768, K = 1536   7.1x  8.3x  6.8   5.9   8.0  10.9        512 x 768, K = 1536  11.3x 12.1x 11.6x  9.8x  8.1  10.9
-    if (tiles(16, 16) <= kTilesResident * 5 / 4) { MAMBA_FEW(1, false); return hipGetLastError(); }
-    if (tiles(32, 16) <= kTilesResident) { MAMBA_FEW(2, false); return hipGetLastError(); }
-    if (a.K <= 768 && tiles(64, 16) <= kTilesResident) { MAMBA_FEW(4, false); return hipGetLastError(); }
+    //   64 x 1024, K = 512    2.9   3.3   4.0   4.8   6.5   5.6        333 x 80, K = 1536    3.7   4.4   6.2   5.7   7.6  10.4
+    //  128 x  768, K = 1536   4.6x  4.4   6.2   5.6   7.7  10.5        333 x 640, K = 768    5.1x  5.7x  4.7   5.3   7.1   7.0
+    //  256 x  768, K = 1536   6.0x  7.0x  6.3   5.6   7.6  10.5        512 x 768, K = 1536   9.5x  9.9x 10.6x  9.3x  7.7  10.6
+    if (tiles(16, 16) <= kTilesResident * 5 / 4) { MAMBA_FEW(1); return hipGetLastError(); }
+    if (tiles(32, 16) <= kTilesResident) { MAMBA_FEW(2); return hipGetLastError(); }
+    if (a.K <= 768 && tiles(64, 16) <= kTilesResident) { MAMBA_FEW_K(4, false, 32); return hipGetLastError(); }
     if (a.K >= 512 && tiles(32, 32) <= kTilesResident) {
         const dim3 grid((unsigned)((N + 31) / 32), (unsigned)((a.M + 31) / 32));
         linear_split_kernel<1><<<grid, 512, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K);
@@ -913,8 +936,9 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     }
     // what is left of the few rows, except for very wide outputs (the LM head), where the tiled kernel's shared x tile
     // reads less
-    if (a.M <= 64 && N < 8192) { MAMBA_FEW(4, false); return hipGetLastError(); }
+    if (a.M <= 64 && N < 8192) { MAMBA_FEW_K(4, false, 32); return hipGetLastError(); }
 #undef MAMBA_FEW
+#undef MAMBA_FEW_K
     if (vec && N % 128 == 0 && a.M >= 128 && a.K % (2 * kWideBK) == 0) {
         // The memory-to-LDS kernel, on any number of rows.  Measured inside the 24-block prefill (alone in a loop the
         // wide tiles look better than they are there: their denser matrix work lowers the clock for what runs between

@@ -1152,7 +1152,9 @@ def test_linear_wide_tiles_ragged_rows(m, M, N, K, splits):
                                           (19, 4090, 768, (2040, 2050)), (100, 800, 520, None),                          # 32 x 16
                                           (65, 4000, 512, (1500, 2500)), (255, 999, 1288, None), (2700, 80, 1536, (48, 16, 16)),   # 32 x 32
                                           (330, 761, 1096, (3, 700, 58)), (641, 700, 1024, None), (129, 2600, 4104, None),         # 64 x 32
-                                          (50, 5000, 264, (4000, 1000)), (64, 4500, 776, None)])                         # 64 x 16
+                                          (50, 5000, 264, (4000, 1000)), (64, 4500, 776, None),                          # 64 x 16
+                                          # steps of 64 k: 16 x 16, 32 x 16
+                                          (13, 80, 1024, None), (333, 80, 2056, (48, 16, 16)), (100, 790, 1032, (300, 490))])
 def test_linear_few_tiles(m, M, N, K, splits):
     """Products with few output tiles, at both sides of the lines between the tile shapes they get and with ragged rows,
     columns, k and outputs whose borders lie inside a tile."""
