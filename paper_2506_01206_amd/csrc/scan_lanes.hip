@@ -128,36 +128,34 @@ template <> struct Row6<float> {
         f[0] = v[0].x; f[1] = v[0].y; f[2] = v[1].x; f[3] = v[1].y; f[4] = v[2].x; f[5] = v[2].y;
     }
 };
-__device__ __forceinline__ void store_row6(bf16_t *p, const float *f)
-{
-    uint32_t *q = reinterpret_cast<uint32_t *>(p);
-    q[0] = f32x2_to_bf16x2(f[0], f[1]);
-    q[1] = f32x2_to_bf16x2(f[2], f[3]);
-    q[2] = f32x2_to_bf16x2(f[4], f[5]);
-}
-__device__ __forceinline__ void store_row6(float *p, const float *f)
-{
-    float2 *q = reinterpret_cast<float2 *>(p);
-    q[0] = make_float2(f[0], f[1]);
-    q[1] = make_float2(f[2], f[3]);
-    q[2] = make_float2(f[4], f[5]);
-}
-
-// the channel pairs from `first` on only (first even)
-__device__ __forceinline__ void store_pairs(bf16_t *p, const float *f, int first)
-{
-    uint32_t *q = reinterpret_cast<uint32_t *>(p);
+// six adjacent channels of one output row, rounded to the type they are stored as
+template <typename T> struct Out6;
+template <> struct Out6<bf16_t> {
+    typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
+    typedef u32x3 u32x3_at4 __attribute__((aligned(4)));
+    uint32_t v[3];
+    __device__ __forceinline__ void pack(const float *f)
+    {
 #pragma unroll
-    for (int c = 0; c < kG; c += 2)
-        if (c >= first) q[c / 2] = f32x2_to_bf16x2(f[c], f[c + 1]);
-}
-__device__ __forceinline__ void store_pairs(float *p, const float *f, int first)
-{
-    float2 *q = reinterpret_cast<float2 *>(p);
+        for (int c = 0; c < 3; ++c) v[c] = f32x2_to_bf16x2(f[2 * c], f[2 * c + 1]);
+    }
+    __device__ __forceinline__ void store(bf16_t *p) const { *reinterpret_cast<u32x3_at4 *>(p) = u32x3{v[0], v[1], v[2]}; }
+    __device__ __forceinline__ void store_pair(bf16_t *p, int c) const { reinterpret_cast<uint32_t *>(p)[c] = v[c]; }
+};
+template <> struct Out6<float> {
+    float2 v[3];
+    __device__ __forceinline__ void pack(const float *f)
+    {
 #pragma unroll
-    for (int c = 0; c < kG; c += 2)
-        if (c >= first) q[c / 2] = make_float2(f[c], f[c + 1]);
-}
+        for (int c = 0; c < 3; ++c) v[c] = make_float2(f[2 * c], f[2 * c + 1]);
+    }
+    __device__ __forceinline__ void store(float *p) const
+    {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) reinterpret_cast<float2 *>(p)[c] = v[c];
+    }
+    __device__ __forceinline__ void store_pair(float *p, int c) const { reinterpret_cast<float2 *>(p)[c] = v[c]; }
+};
 
 // B_t and C_t of a super-step are fetched by all threads in 16-byte chunks, consecutive threads on consecutive
 // chunks (fully coalesced), and land in LDS as float32 groups of 4 states.
@@ -311,11 +309,13 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
         x_cur = x_nxt;
         if constexpr (HAS_Z && kAhead) z_cur = z_nxt;
     };
-    auto epilogue = [&](int64_t t_base) {
-        const int64_t t = t_base + kTau * ti + tj;
+    auto gate = [&](int64_t t_base, Out6<T> &o6) {   // the outputs of the super-step
         float xv[kG], zv[kG], ov[kG];
         x_cur.unpack(xv);
-        if constexpr (HAS_Z && !kAhead) z_cur.load(z + (row0 + (t < L ? t : L - 1)) * D + c0);
+        if constexpr (HAS_Z && !kAhead) {
+            const int64_t t = t_base + kTau * ti + tj;
+            z_cur.load(z + (row0 + (t < L ? t : L - 1)) * D + c0);
+        }
         if constexpr (HAS_Z) z_cur.unpack(zv);
 #pragma unroll
         for (int c = 0; c < kG; ++c) {
@@ -325,9 +325,18 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
             const float y = fmaf(lds_par[1][c], xv[c], ch);
             ov[c] = HAS_Z ? y * silu_f32(zv[c]) : y;
         }
-        if (t < L) {
-            if (dead == 0) store_row6(out + (row0 + t) * D + c0, ov);
-            else store_pairs(out + (row0 + t) * D + c0, ov, dead);
+        o6.pack(ov);
+    };
+    auto store = [&](int64_t t_base, const Out6<T> &o6) {
+        const int64_t t = t_base + kTau * ti + tj;
+        if (t >= L) return;
+        T *p = out + (row0 + t) * D + c0;
+        if (dead == 0) {
+            o6.store(p);
+        } else {
+#pragma unroll
+            for (int c = 0; c < kG; c += 2)
+                if (c >= dead) o6.store_pair(p, c / 2);
         }
     };
 
@@ -445,8 +454,12 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
         if constexpr (!kAhead) {
             if (more) fetch_bc(t_base + kT, 0);
         }
+        Out6<T> o6;
+        // The outputs are stored last: loads and stores are waited for by one counter, so a wait for the next rows that came
+        // after the stores would also wait for the stores, with everyone else at the barrier.
         if (token_thread) {
-            epilogue(t_base);
+            gate(t_base, o6);
+            if constexpr (!kAhead) store(t_base, o6);   // (float32 has no registers to hold them in)
             if (more) publish(t_base + kT);
         }
         if (more) {
@@ -455,6 +468,9 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
                 fetch_bc(t_base + kT, kBcHeld);
                 publish_bc(kBcHeld);
             }
+        }
+        if constexpr (kAhead) {
+            if (token_thread) store(t_base, o6);
         }
         lds_barrier_l();   // the next super-step is in LDS
     }
