@@ -73,35 +73,60 @@ constexpr int kSchedMemoryOnly = 0x4 | 0x10 | 0x20 | 0x40 | 0x80 | 0x100 | 0x200
 constexpr int kBcTile = 16;
 static_assert(kBcTile % kTile == 0, "B/C tiles must start on a token-tile boundary");
 
+// The values of a lane are adjacent (one load per array) and stay as they were loaded until they go to LDS: converted where
+// they are requested, they would make the wavefront wait there, for them and for the token rows requested before them.
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+template <int BYTES> struct RawVec;
+template <> struct RawVec<2> { typedef uint16_t type; };
+template <> struct RawVec<4> { typedef uint32_t type; };
+template <> struct RawVec<8> { typedef u32x2 type; };
+template <> struct RawVec<16> { typedef u32x4 type; };
+template <> struct RawVec<32> { typedef u32x8 type __attribute__((aligned(16))); };
+template <typename T, typename V> __device__ __forceinline__ float raw_element(const V &v, int i)
+{
+    if constexpr (sizeof(V) == 2) return bf16_to_f32(v);
+    else if constexpr (sizeof(V) == 4 && sizeof(T) == 4) return __uint_as_float(v);
+    else if constexpr (sizeof(V) == 4) return i ? bf16_hi(v) : bf16_lo(v);
+    else if constexpr (sizeof(T) == 4) return __uint_as_float(v[i]);
+    else return (i & 1) ? bf16_hi(v[i >> 1]) : bf16_lo(v[i >> 1]);
+}
+
 template <typename T, int N, int NARR> struct BcStage {
     static constexpr int kPerTile = kBcTile * N;                 // elements per array per tile
-    static constexpr int kPerLane = (kPerTile + kWave - 1) / kWave;
+    static constexpr int kPerLane = kPerTile / kWave;            // 1, 2, 4 or 8
+    static_assert(kPerTile % kWave == 0 && N % kPerLane == 0, "a lane's elements lie in one row");
     static constexpr int kBufFloats = NARR * kPerTile;
+    typedef typename RawVec<kPerLane * sizeof(T)>::type vec_t;
     float *lds;            // [2][NARR][kBcTile][N]
     const T *src[NARR];    // row base of this batch row
     int64_t last;          // index of the last valid element, t1 * N - 1
-    float raw[NARR][kPerLane];
+    vec_t raw[NARR];
 
     __device__ __forceinline__ void issue(int64_t tile_t0)
     {
+        int64_t i = tile_t0 * N + (int)threadIdx.x * kPerLane;
+        i = i < last ? i : last + 1 - kPerLane;                  // steps past the chunk end are never used
 #pragma unroll
-        for (int a = 0; a < NARR; ++a)
-#pragma unroll
-            for (int j = 0; j < kPerLane; ++j) {
-                int64_t i = tile_t0 * N + (int)threadIdx.x + kWave * j;
-                i = i < last ? i : last;   // steps past the chunk end are never used
-                raw[a][j] = ld_io(src[a], i);
-            }
+        for (int a = 0; a < NARR; ++a) raw[a] = *reinterpret_cast<const vec_t *>(src[a] + i);
     }
     __device__ __forceinline__ void commit(int buf)
     {
 #pragma unroll
-        for (int a = 0; a < NARR; ++a)
+        for (int a = 0; a < NARR; ++a) {
+            float *dst = lds + buf * kBufFloats + a * kPerTile + (int)threadIdx.x * kPerLane;
+            float f[kPerLane];
 #pragma unroll
-            for (int j = 0; j < kPerLane; ++j) {
-                const int e = (int)threadIdx.x + kWave * j;
-                if (kPerTile % kWave == 0 || e < kPerTile) lds[buf * kBufFloats + a * kPerTile + e] = raw[a][j];
+            for (int j = 0; j < kPerLane; ++j) f[j] = raw_element<T>(raw[a], j);
+            if constexpr (kPerLane % 4 == 0) {
+#pragma unroll
+                for (int j = 0; j < kPerLane; j += 4) *reinterpret_cast<float4 *>(dst + j) = make_float4(f[j], f[j + 1], f[j + 2], f[j + 3]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < kPerLane; ++j) dst[j] = f[j];
             }
+        }
         __syncthreads();
     }
     // N values of array a for step s of buffer buf
@@ -191,7 +216,7 @@ scan_chunk_out(const T *__restrict__ x, const T *__restrict__ dt, const float *_
     const int chunk = blockIdx.y;
     const int64_t d_lane = ((int64_t)blockIdx.x * kWave + lane) * CPL;
     const bool live = d_lane < D;                 // CPL == 2 only runs with D even
-    const int64_t d0 = live ? d_lane : D - CPL;   // dead lanes shadow the last channels, store nothing
+    const int64_t d0 = live ? d_lane : D - CPL;   // dead lanes shadow the last channels
     const int64_t t0 = (int64_t)chunk * chunk_len;
     const int64_t t1 = (t0 + chunk_len < L) ? t0 + chunk_len : L;
 
@@ -260,7 +285,9 @@ scan_chunk_out(const T *__restrict__ x, const T *__restrict__ dt, const float *_
             }
             ov[c] = HAS_Z ? y * silu_f32(zv[c]) : y;
         }
-        if (live) st_pack<CPL>(out + (row0 + t) * D + d0, ov);
+        // (dead lanes store too, what the lane they shadow stores: a branch here would leave the number of stores in flight
+        // open, and the wait for the next rows would then be a wait for the stores as well)
+        st_pack<CPL>(out + (row0 + t) * D + d0, ov);
     };
 
     raw_t xc[kTile], dc[kTile], zc[kTile];
