@@ -63,24 +63,43 @@ template <> struct Row8<float> {
         f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
     }
 };
-__device__ __forceinline__ void store_row8(bf16_t *p, const float *f)
-{
-    *reinterpret_cast<uint4 *>(p) = make_uint4(f32x2_to_bf16x2(f[0], f[1]), f32x2_to_bf16x2(f[2], f[3]),
-                                               f32x2_to_bf16x2(f[4], f[5]), f32x2_to_bf16x2(f[6], f[7]));
-}
-__device__ __forceinline__ void store_row8(float *p, const float *f)
-{
-    reinterpret_cast<float4 *>(p)[0] = make_float4(f[0], f[1], f[2], f[3]);
-    reinterpret_cast<float4 *>(p)[1] = make_float4(f[4], f[5], f[6], f[7]);
-}
+// eight adjacent channels of an output row, rounded to the type they are stored as
+template <typename T> struct Out8;
+template <> struct Out8<bf16_t> {
+    uint4 v;
+    __device__ __forceinline__ void pack(const float *f)
+    {
+        v = make_uint4(f32x2_to_bf16x2(f[0], f[1]), f32x2_to_bf16x2(f[2], f[3]),
+                       f32x2_to_bf16x2(f[4], f[5]), f32x2_to_bf16x2(f[6], f[7]));
+    }
+    __device__ __forceinline__ void store(bf16_t *p) const { *reinterpret_cast<uint4 *>(p) = v; }
+};
+template <> struct Out8<float> {
+    float4 a, b;
+    __device__ __forceinline__ void pack(const float *f)
+    {
+        a = make_float4(f[0], f[1], f[2], f[3]);
+        b = make_float4(f[4], f[5], f[6], f[7]);
+    }
+    __device__ __forceinline__ void store(float *p) const
+    {
+        reinterpret_cast<float4 *>(p)[0] = a;
+        reinterpret_cast<float4 *>(p)[1] = b;
+    }
+};
 
-// four adjacent elements of a B or C row
-__device__ __forceinline__ float4 load4(const bf16_t *p)
-{
-    const uint2 r = *reinterpret_cast<const uint2 *>(p);
-    return make_float4(bf16_lo(r.x), bf16_hi(r.x), bf16_lo(r.y), bf16_hi(r.y));
-}
-__device__ __forceinline__ float4 load4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+// four adjacent elements of a B or C row, kept as they were loaded until they are used
+template <typename T> struct Raw4;
+template <> struct Raw4<bf16_t> {
+    uint2 r;
+    __device__ __forceinline__ void load(const bf16_t *p) { r = *reinterpret_cast<const uint2 *>(p); }
+    __device__ __forceinline__ float4 widen() const { return make_float4(bf16_lo(r.x), bf16_hi(r.x), bf16_lo(r.y), bf16_hi(r.y)); }
+};
+template <> struct Raw4<float> {
+    float4 r;
+    __device__ __forceinline__ void load(const float *p) { r = *reinterpret_cast<const float4 *>(p); }
+    __device__ __forceinline__ float4 widen() const { return r; }
+};
 
 template <int CTRL> __device__ __forceinline__ float dpp_take(float v)
 {
@@ -154,7 +173,7 @@ scan_direct_kernel(const T *x, const T *dt, const float *__restrict__ A, const T
     // rows of a tile as fetched: kept raw until the tile's turn (x and z again for the gate and skip term)
     struct Rows {
         Row8<T> x[kRows], dt[kRows], z[kRows];
-        float4 bc[kBcIters];
+        Raw4<T> bc[kBcIters];
     };
     Rows nxt;
     Row8<T> x_cur[kRows], z_cur[kRows];
@@ -178,7 +197,7 @@ scan_direct_kernel(const T *x, const T *dt, const float *__restrict__ A, const T
                 const int s = rem / (N / 4), n4 = rem % (N / 4);
                 int64_t ts = t_base + s;
                 ts = ts < L ? ts : L - 1;
-                r.bc[it] = load4((arr ? Cm : Bm) + (row0 + ts) * N + 4 * n4);
+                r.bc[it].load((arr ? Cm : Bm) + (row0 + ts) * N + 4 * n4);
             }
         }
     };
@@ -215,12 +234,12 @@ scan_direct_kernel(const T *x, const T *dt, const float *__restrict__ A, const T
                 const int arr = g / (kTile * N / 4), rem = g % (kTile * N / 4);
                 const int s = rem / (N / 4), n4 = rem % (N / 4);
                 const bool ok = t_base + s < L;
-                *reinterpret_cast<float4 *>(&lds_bc[s][arr * N + 4 * n4]) = ok ? r.bc[it] : make_float4(0.f, 0.f, 0.f, 0.f);
+                *reinterpret_cast<float4 *>(&lds_bc[s][arr * N + 4 * n4]) = ok ? r.bc[it].widen() : make_float4(0.f, 0.f, 0.f, 0.f);
             }
         }
     };
-    // skip term, gate and store of the current tile
-    auto epilogue = [&](int64_t t_base) {
+    // skip term and gate of the current tile
+    auto gate = [&](Out8<T> (&o8)[kRows]) {
 #pragma unroll
         for (int i = 0; i < kRows; ++i) {
             float xv[8], yv[8], ov[8], zv[8];
@@ -234,8 +253,14 @@ scan_direct_kernel(const T *x, const T *dt, const float *__restrict__ A, const T
                 const float y = fmaf(dsk8[e], xv[e], yv[e]);
                 ov[e] = HAS_Z ? y * silu_f32(zv[e]) : y;
             }
+            o8[i].pack(ov);
+        }
+    };
+    auto store = [&](const Out8<T> (&o8)[kRows], int64_t t_base) {
+#pragma unroll
+        for (int i = 0; i < kRows; ++i) {
             const int64_t t = t_base + lr + 32 * i;
-            if (l_live && t < L) store_row8(out + (row0 + t) * D + lc, ov);
+            if (l_live && t < L) o8[i].store(out + (row0 + t) * D + lc);
         }
     };
 
@@ -310,8 +335,11 @@ scan_direct_kernel(const T *x, const T *dt, const float *__restrict__ A, const T
             cur = ahead;
         }
         lds_barrier();   // y of the tile is complete; delta, delta * x, B and C of the tile are used up
-        epilogue(t_base);
+        // (the outputs are stored after the next rows have been taken over: loads and stores are waited for by one counter)
+        Out8<T> o8[kRows];
+        gate(o8);
         if (more) publish(nxt, t_base + kTile);
+        store(o8, t_base);
         lds_barrier();   // the next tile is in LDS; y has been read
     }
 
