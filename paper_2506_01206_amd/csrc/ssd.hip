@@ -90,7 +90,8 @@ __device__ __forceinline__ uint32_t pair_el(const uint4 &a, const uint4 &b, int 
 // living transposed (N x P float32) in MFMA accumulators: per chunk acc <- exp(s_end) acc + S.
 //   PASS2 = false: from a zero state; leaves the segment's end state in slot seg + 1 of ws_state
 //       ((batch, n_slots, H * P, N)) and the segment's sum of deltas in ws_sumdt; the carry kernel
-//       of the selective scan then turns the slots into the states at the segment starts;
+//       of the selective scan then turns the slots into the states at the segment starts, or (fold) pass 2
+//       stitches them itself, with the same operations in the same order;
 //   PASS2 = true: from the true incoming state (slot seg * slot_step: pass 1 may cut the sequence
 //       slot_step times finer than pass 2, its workgroups being small enough to share a CU), with outputs.
 // Two roles.  The four "state" wavefronts hold the accumulators: per chunk they multiply the transposed B and
@@ -107,11 +108,11 @@ __device__ __forceinline__ uint32_t pair_el(const uint4 &a, const uint4 &b, int 
 // register sets used in turn, C and z one chunk ahead; delta and its running sum are formed one chunk ahead
 // into the other half of a double buffer.
 // grid: (n_seg, H, batch); 256 threads in pass 1, 512 in pass 2.
-template <int N, bool PASS2, bool HAS_Z>
+template <int N, bool PASS2, bool HAS_Z, bool FOLD>
 __global__ void __launch_bounds__(PASS2 ? 2 * kThreads : kThreads) __attribute__((amdgpu_waves_per_eu(2)))
 ssd_segment(const bf16_t *x, const bf16_t *dt, const float *__restrict__ A, const bf16_t *Bm, const bf16_t *Cm,
             const float *__restrict__ Dskip, const bf16_t *z, const float *__restrict__ dt_bias, float *ws_state,
-            float *ws_sumdt, float *a_rows, bf16_t *out, float *h_final, int64_t L, int64_t H, int chunks_per_seg,
+            float *ws_sumdt, float *a_rows, bf16_t *out, const float *h0, float *h_final, int64_t L, int64_t H, int chunks_per_seg,
             int n_seg, int n_slots, int slot_step, int n_chunks, int softplus)
 {
     // (x, dt, B, C, z are deliberately not declared restrict: as possibly aliased by the stores to out they
@@ -246,18 +247,20 @@ ssd_segment(const bf16_t *x, const bf16_t *dt, const float *__restrict__ A, cons
     for (int j = 0; j < PPW; ++j)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[j][i] = 0.0f;
-    if (PASS2 && !role_y) {
+    // (fold: the segments before this one are stitched here, from h0, instead of by a kernel of their own: see launch_ssd)
+    const float *acc_in = !FOLD ? slot_in : h0 ? h0 + (b * D + h * kP) * N : nullptr;
+    if (PASS2 && !role_y && acc_in) {
 #pragma unroll
         for (int j = 0; j < PPW; ++j) {
             const int id = sw * PPW + j, pt = id & 1, nt = id >> 1;
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                const float4 v = *reinterpret_cast<const float4 *>(slot_in + (int64_t)(pt * 32 + r) * N + nt * 32 + 8 * g + 4 * up);
+                const float4 v = *reinterpret_cast<const float4 *>(acc_in + (int64_t)(pt * 32 + r) * N + nt * 32 + 8 * g + 4 * up);
                 acc[j][4 * g] = v.x, acc[j][4 * g + 1] = v.y, acc[j][4 * g + 2] = v.z, acc[j][4 * g + 3] = v.w;
             }
         }
     }
-    if (!PASS2 && seg == 0 && b == 0)
+    if (!PASS2 && !FOLD && seg == 0 && b == 0)
         for (int i = tid; i < kP * N; i += kThreads) a_rows[h * kP * N + i] = A_h;   // decay matrix for the carry kernel
 
     bf16_t dt_next = 0, dt_after = 0;                             // dt of the next chunk and of the one after
@@ -275,7 +278,43 @@ ssd_segment(const bf16_t *x, const bf16_t *dt, const float *__restrict__ A, cons
         mask_early(c_first, E2[0]);
         park_state_operands(E2[0], 0);
     }
-    if constexpr (!PASS2) lds_barrier();                          // (pass 2 has a barrier ahead of the first state update anyway)
+    if constexpr (PASS2) {
+        if (FOLD && !role_y) {
+            // acc <- exp(A * sum of deltas) acc + end state, segment after segment; kFold of them in flight
+            constexpr int kFold = 4;
+            const int n_before = seg * slot_step;
+            const float a2 = A_h * kLog2e;
+            const float4 *loc = reinterpret_cast<const float4 *>(ws_state + (((int64_t)b * n_slots + 1) * D + h * kP) * N) + sw * (PPW * 256) + lane;
+            const float *sums = ws_sumdt + (int64_t)b * n_slots * D + h * kP;
+#pragma nounroll
+            for (int c0 = 0; c0 < n_before; c0 += kFold) {
+                float4 v[kFold][PPW * 4];
+                float sum[kFold];
+#pragma unroll
+                for (int i = 0; i < kFold; ++i) {
+                    const int64_t c = c0 + i < n_before ? c0 + i : n_before - 1;
+                    sum[i] = sums[c * D];
+#pragma unroll
+                    for (int k = 0; k < PPW * 4; ++k) v[i][k] = loc[c * (D * N / 4) + k * 64];
+                }
+#pragma unroll
+                for (int i = 0; i < kFold; ++i) {
+                    if (c0 + i >= n_before) break;
+                    const float e = exp2_hw(a2 * sum[i]);
+#pragma unroll
+                    for (int k = 0; k < PPW * 4; ++k) {
+                        const int j = k >> 2, g = k & 3;
+                        acc[j][4 * g] = fmaf(e, acc[j][4 * g], v[i][k].x);
+                        acc[j][4 * g + 1] = fmaf(e, acc[j][4 * g + 1], v[i][k].y);
+                        acc[j][4 * g + 2] = fmaf(e, acc[j][4 * g + 2], v[i][k].z);
+                        acc[j][4 * g + 3] = fmaf(e, acc[j][4 * g + 3], v[i][k].w);
+                    }
+                }
+            }
+        }
+    } else {
+        lds_barrier();                                            // (pass 2 has a barrier ahead of the first state update anyway)
+    }
 
     // Each role runs its own loop over the chunks, with the same three barriers per chunk (two in pass 1):
     //   A  state role: row-major B, transposed x and the state at the chunk start into LDS; fetches.
@@ -467,7 +506,13 @@ ssd_segment(const bf16_t *x, const bf16_t *dt, const float *__restrict__ A, cons
     float *dst = nullptr;
     if (!PASS2) dst = ws_state + (((int64_t)b * n_slots + seg + 1) * D + h * kP) * N;
     else if (h_final && seg == n_seg - 1) dst = h_final + (b * D + h * kP) * N;
-    if (dst && !role_y) {
+    if (!PASS2 && FOLD) {
+        // as it lies in the registers: both sides move whole lines (rows of the state are 512 bytes apart)
+        float4 *p = reinterpret_cast<float4 *>(dst) + sw * (PPW * 256) + lane;
+#pragma unroll
+        for (int k = 0; k < PPW * 4; ++k)
+            p[k * 64] = make_float4(acc[k >> 2][4 * (k & 3)], acc[k >> 2][4 * (k & 3) + 1], acc[k >> 2][4 * (k & 3) + 2], acc[k >> 2][4 * (k & 3) + 3]);
+    } else if (dst && !role_y) {
 #pragma unroll
         for (int j = 0; j < PPW; ++j) {
             const int id = sw * PPW + j, pt = id & 1, nt = id >> 1;
@@ -592,15 +637,24 @@ hipError_t launch_ssd(const SsdArgs &a, hipStream_t stream)
     const bf16_t *Bm = static_cast<const bf16_t *>(a.Bm), *Cm = static_cast<const bf16_t *>(a.Cm);
     const bf16_t *z = static_cast<const bf16_t *>(a.z);
     bf16_t *out = static_cast<bf16_t *>(a.out);
-#define MAMBA_SSD(NN, P2, HZ)                                                                                       \
-    ssd_segment<NN, P2, HZ><<<dim3((unsigned)((P2) ? p.n_seg2 : p.n_seg1), (unsigned)a.H, (unsigned)a.batch),        \
+    // Pass 2 stitches the segments itself where the last one has at most ten before it: it reads their end states, 32 KB
+    // each, through one CU, which beats the carry kernel's launch and its second trip through memory up to there (24 heads
+    // of 128 states: 256 tokens 22.2 -> 16.5 us, 700 tokens (ten) 29.5 -> 25.1, 4 x 1000 54.6 -> 41.4, 2 x 2000 52 -> 47, 4 x
+    // 8000 255 -> 228; 2048 tokens (fourteen) takes 3 us more that way).  Not where the final state replaces h0: other
+    // workgroups still read that.  (Instantiations of their own: as a run-time switch it changed the register allocation of
+    // the other way, 2048 tokens 37 -> 41 us.)
+    const int fold = p.n_seg1 > 1 && (p.n_seg2 - 1) * slot_step <= 10 && (!a.h0 || a.h0 != a.h_final);
+#define MAMBA_SSD(NN, P2, HZ) (fold ? MAMBA_SSD_F(NN, P2, HZ, true) : MAMBA_SSD_F(NN, P2, HZ, false))
+#define MAMBA_SSD_F(NN, P2, HZ, FD)                                                                                       \
+    ssd_segment<NN, P2, HZ, FD><<<dim3((unsigned)((P2) ? p.n_seg2 : FD ? (p.n_seg2 - 1) * slot_step : p.n_seg1), (unsigned)a.H, (unsigned)a.batch),        \
                               (P2) ? 2 * kThreads : kThreads, 0, stream>>>(                                         \
-        x, dt, a.A, Bm, Cm, a.Dskip, z, a.dt_bias, ws_state, ws_sumdt, a_rows, out, a.h_final, a.L, a.H,             \
+        x, dt, a.A, Bm, Cm, a.Dskip, z, a.dt_bias, ws_state, ws_sumdt, a_rows, out, a.h0, a.h_final, a.L, a.H,       \
         (P2) ? p.chunks2 : p.chunks1, (P2) ? p.n_seg2 : p.n_seg1, n_slots, slot_step, nc, a.dt_softplus)
     if (p.n_seg1 > 1) {
         if (a.N == 64) MAMBA_SSD(64, false, false);
         else MAMBA_SSD(128, false, false);
-        if (hipError_t e = launch_chunk_carry(a_rows, a.h0, ws_state, ws_sumdt, a.batch, D, a.N, n_slots, stream)) return e;
+        if (!fold)
+            if (hipError_t e = launch_chunk_carry(a_rows, a.h0, ws_state, ws_sumdt, a.batch, D, a.N, n_slots, stream)) return e;
     } else {
         // a single segment starts from h0 itself: slot 0 <- h0 (or zeros)
         for (int64_t b = 0; b < a.batch; ++b)
@@ -615,6 +669,7 @@ hipError_t launch_ssd(const SsdArgs &a, hipStream_t stream)
         else MAMBA_SSD(128, true, false);
     }
 #undef MAMBA_SSD
+#undef MAMBA_SSD_F
     return hipGetLastError();
 }
 

@@ -1519,6 +1519,22 @@ def test_ssd_scan_against_oracle(m, B, L, H, N):
         assert_close(to_host(h2), rh, tol, "ssd pieces state")
 
 
+@pytest.mark.parametrize("B,L,H,N", [(1, 65, 24, 128), (1, 704, 24, 128), (1, 641, 12, 64), (2, 2000, 24, 64), (4, 1000, 24, 128)])
+def test_ssd_scan_segments_stitched_in_the_second_pass(m, B, L, H, N):
+    """Few segments (two up to eleven) are stitched by the second pass itself.  Not so where the final state replaces h0:
+    both ways do the same operations in the same order, so the results are the same bit for bit."""
+    rng = np.random.default_rng(B + L + H + N)
+    g = {k: to_dev(v) for k, v in ssd_case(rng, B, L, H, 64, N, synth.BF16).items()}
+    call = lambda h0, **kw: m.mamba2_ssd_fwd(g["x"], g["dt"], g["A"], g["Bm"], g["Cm"], g["Dskip"], g["z"], g["dt_bias"], h0, **kw)
+    out, hf = call(g["h0"])
+    state = g["h0"].clone()
+    out2, _ = call(state, h_final=state)
+    assert torch.equal(out, out2) and torch.equal(hf, state)
+    out3, hf3 = call(None)
+    out4, hf4 = call(torch.zeros_like(state))
+    assert torch.equal(out3, out4) and torch.equal(hf3, hf4)
+
+
 def test_ssd_scan_at_bench_size_sampled_heads(m):
     """The scan at the size and launch configuration bench.py times (32768 tokens, 24 heads, 128 states: ten
     segments per head in the output pass, twenty in the state pass).  Heads are independent, so the oracle runs
