@@ -490,10 +490,10 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
 // channel, at least one full workgroup; and among those the ones it is expected to finish before the two-pass
 // kernels of scan.hip.  Its time is rounds x (about 6 us + 11.6 ns per token), a round being 256 workgroups of 6
 // channels (every workgroup walks the whole sequence); the two-pass kernels take about 24 us + 9.8 ns per token
-// and 1536 channels.  Measured in one run, lanes against two-pass, 1536 channels: 2048 tokens 31 against 43 us,
-// 5120 tokens 71 against 78, 8192 tokens 101 against 104, 10240 tokens 121 against 122, 32768 tokens 461 against
-// 353; two sequences of 2048 tokens 56 against 60, of 4096 tokens 102 against 101; 768 channels x 4096 tokens 48
-// against 44; 2048 channels (342 workgroups, two rounds) x 4096 tokens 105 against 76.
+// and 1536 channels.  Measured in one run, lanes against two-pass, 1536 channels: 9000 tokens 113 against 121 us; two sequences of 3000 tokens 72 against 79; 768
+// channels x 2000 tokens 25 against 30, x 600 tokens 15 against 21.  Before either had its waits for stores taken out: 32768
+// tokens 461 against 353, two sequences of 4096 102 against 101, 768 channels x 4096 tokens 48 against 44, 2048 channels (342
+// workgroups, two rounds) x 4096 tokens 105 against 76.
 bool scan_lanes_applies(int64_t batch, int64_t L, int64_t D, int64_t N)
 {
     if (N != kN || D % 2 != 0 || D < kG || L < 64 || batch > 65535) return false;
