@@ -258,7 +258,9 @@ template <typename T, int VEC, int K> hipError_t launch_conv_k(const ConvArgs &a
 {
     const int64_t vecs = (a.D + VEC - 1) / VEC;
     const unsigned gx = (unsigned)((vecs + kWave - 1) / kWave);
-    const int lanes = (int)((vecs + gx - 1) / gx);   // per wavefront: the last one has as many as the others, not a remainder
+    // channel vectors per wavefront: an even split, not a remainder for the last one, in whole 128-byte lines
+    const int even = (int)((vecs + gx - 1) / gx);
+    const int lanes = VEC > 1 ? (even + 7) / 8 * 8 : even;
     // Time tiles: enough workgroups to fill the chip, long enough to amortize the K-1 halo rows.
     // An in-place state update keeps one tile so that a thread reads the state before it writes it.
     // Short inputs get shorter tiles (down to one group of rows) until there are about two wavefronts per SIMD: a row
