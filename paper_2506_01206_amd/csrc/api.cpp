@@ -2,6 +2,7 @@
 // any HIP call, so it can be exercised without a GPU), then dispatch to the kernel launchers.
 #include "../../include/mamba_hip.h"
 #include "launch.h"
+#include "routes.h"
 
 #include <stdint.h>
 
@@ -24,13 +25,6 @@ bool size3(int64_t a, int64_t b, int64_t c, int64_t elem, int64_t *bytes)
     if (t > (int64_t)1 << 62) return false;
     *bytes = t;
     return true;
-}
-
-bool overlap(const void *p, int64_t pn, const void *q, int64_t qn)
-{
-    if (!p || !q || pn <= 0 || qn <= 0) return false;
-    const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
-    return a < b + (uintptr_t)qn && b < a + (uintptr_t)pn;
 }
 
 int io_size(int io) { return io == MAMBA_F32 ? 4 : io == MAMBA_BF16 ? 2 : 0; }

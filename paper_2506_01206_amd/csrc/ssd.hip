@@ -25,6 +25,7 @@
 // not of the result), which the bf16 I/O tolerance does not allow for.
 #include "device_math.h"
 #include "launch.h"
+#include "routes.h"
 
 namespace mamba {
 namespace {
@@ -640,10 +641,10 @@ hipError_t launch_ssd(const SsdArgs &a, hipStream_t stream)
     // Pass 2 stitches the segments itself where the last one has at most ten before it: it reads their end states, 32 KB
     // each, through one CU, which beats the carry kernel's launch and its second trip through memory up to there (24 heads
     // of 128 states: 256 tokens 22.2 -> 16.5 us, 700 tokens (ten) 29.5 -> 25.1, 4 x 1000 54.6 -> 41.4, 2 x 2000 52 -> 47, 4 x
-    // 8000 255 -> 228; 2048 tokens (fourteen) takes 3 us more that way).  Not where the final state replaces h0: other
-    // workgroups still read that.  (Instantiations of their own: as a run-time switch it changed the register allocation of
+    // 8000 255 -> 228; 2048 tokens (fourteen) takes 3 us more that way).  Not where the final state lies over h0, all or
+    // part of it: other workgroups still read that.  (Instantiations of their own: as a run-time switch it changed the register allocation of
     // the other way, 2048 tokens 37 -> 41 us.)
-    const int fold = p.n_seg1 > 1 && (p.n_seg2 - 1) * slot_step <= 10 && (!a.h0 || a.h0 != a.h_final);
+    const bool fold = ssd_folds(p.n_seg1, (p.n_seg2 - 1) * slot_step, a.h0, a.h_final, a.batch * D * a.N * (int64_t)sizeof(float));
 #define MAMBA_SSD(NN, P2, HZ) (fold ? MAMBA_SSD_F(NN, P2, HZ, true) : MAMBA_SSD_F(NN, P2, HZ, false))
 #define MAMBA_SSD_F(NN, P2, HZ, FD)                                                                                       \
     ssd_segment<NN, P2, HZ, FD><<<dim3((unsigned)((P2) ? p.n_seg2 : FD ? (p.n_seg2 - 1) * slot_step : p.n_seg1), (unsigned)a.H, (unsigned)a.batch),        \

@@ -1535,6 +1535,23 @@ def test_ssd_scan_segments_stitched_in_the_second_pass(m, B, L, H, N):
     assert torch.equal(out3, out4) and torch.equal(hf3, hf4)
 
 
+@pytest.mark.parametrize("B,L,H,N", [(2, 65, 24, 128), (3, 300, 12, 64), (4, 1000, 24, 128)])
+def test_ssd_scan_final_state_shifted_over_the_initial_state(m, B, L, H, N):
+    """h0 and h_final in one buffer, shifted by a batch row or a head either way: the same results as in separate buffers."""
+    rng = np.random.default_rng(B + L + H + N)
+    g = {k: to_dev(v) for k, v in ssd_case(rng, B, L, H, 64, N, synth.BF16).items()}
+    call = lambda h0, **kw: m.mamba2_ssd_fwd(g["x"], g["dt"], g["A"], g["Bm"], g["Cm"], g["Dskip"], g["z"], g["dt_bias"], h0, **kw)
+    out, hf = call(g["h0"])
+    n = g["h0"].numel()
+    for shift in (n // B, 64 * N):
+        buf = torch.empty(n + shift, device=g["h0"].device)
+        for at, to in ((0, shift), (shift, 0)):
+            h0, state = buf[at:at + n].view_as(g["h0"]), buf[to:to + n].view_as(g["h0"])
+            h0.copy_(g["h0"])
+            out2, _ = call(h0, h_final=state)
+            assert torch.equal(out, out2) and torch.equal(hf, state), (shift, at)
+
+
 def test_ssd_scan_at_bench_size_sampled_heads(m):
     """The scan at the size and launch configuration bench.py times (32768 tokens, 24 heads, 128 states: ten
     segments per head in the output pass, twenty in the state pass).  Heads are independent, so the oracle runs

@@ -1,0 +1,38 @@
+"""Host-side tests of csrc/routes.h: which calls a launcher keeps away from a kernel that cannot take them.  The header holds
+plain host functions; a small shim of them is compiled with the system's C++ compiler, no GPU and no large tensor involved."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SHIM = """
+#include "routes.h"
+extern "C" int folds(int n_seg1, int before, uintptr_t h0, uintptr_t h_final, int64_t bytes)
+{ return mamba::ssd_folds(n_seg1, before, (const void *)h0, (const void *)h_final, bytes); }
+"""
+
+
+@pytest.fixture(scope="module")
+def routes(tmp_path_factory):
+    d = tmp_path_factory.mktemp("routes")
+    (d / "shim.cpp").write_text(SHIM)
+    subprocess.check_call([os.environ.get("CXX", "g++"), "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-o", str(d / "shim.so"),
+                           "-I" + os.path.join(ROOT, "paper_2506_01206_amd", "csrc"), str(d / "shim.cpp")])
+    lib = ctypes.CDLL(str(d / "shim.so"))
+    i32, i64, ptr = ctypes.c_int, ctypes.c_int64, ctypes.c_size_t
+    lib.folds.argtypes = [i32, i32, ptr, ptr, i64]
+    return lib
+
+
+def test_scalar_decay_segments_are_not_stitched_over_their_own_initial_state(routes):
+    """Workgroups of the second pass read h0 while others write h_final: no fold where the two share a byte."""
+    row = 24 * 64 * 128 * 4
+    base, n = 1 << 40, 3 * row
+    assert routes.folds(2, 1, base, base + n, n) and routes.folds(2, 1, base + n, base, n)     # side by side
+    assert routes.folds(11, 10, base, 0, n) and routes.folds(11, 10, 0, base, n) and routes.folds(11, 10, 0, 0, n)
+    assert not routes.folds(2, 1, base, base, n)                                              # in place
+    for shift in (16, 64 * 128 * 4, row, 2 * row, n - 16):
+        assert not routes.folds(2, 1, base, base + shift, n) and not routes.folds(2, 1, base + shift, base, n)
+    assert not routes.folds(1, 0, base, 0, n) and not routes.folds(12, 11, base, 0, n)         # one segment; too many
