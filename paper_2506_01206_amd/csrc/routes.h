@@ -22,4 +22,8 @@ inline bool ssd_folds(int n_seg1, int before, const void *h0, const void *h_fina
     return n_seg1 > 1 && before <= 10 && !overlap(h0, state_bytes, h_final, state_bytes);
 }
 
+// The few-row product counts k in 32 bits: k rounded up to a step of 64 has to fit an int.  What does not fit takes the kernels
+// that count in 64 bits.
+inline bool linear_few_fits(int64_t K) { return K <= (int64_t)INT32_MAX - 63; }
+
 }  // namespace mamba

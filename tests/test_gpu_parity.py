@@ -1161,6 +1161,21 @@ def test_linear_few_tiles(m, M, N, K, splits):
     test_linear_against_oracle(m, M, N, K, splits)
 
 
+def test_linear_k_beyond_32_bits(m):
+    """k that rounds up past 2^31 and k beyond it, on one output tile: the product of two sparse rows, whole numbers, so exact."""
+    longest = (1 << 31) + 8
+    x = torch.zeros(1, longest, dtype=torch.bfloat16, device=DEV)
+    w = torch.zeros(1, longest, dtype=torch.bfloat16, device=DEV)
+    for K in ((1 << 31) - 8, 1 << 31, longest):
+        say(K=K)
+        at = torch.tensor([0, 65, (1 << 30) + 7, K - 100, K - 9, K - 1], device=DEV)
+        x.zero_(), w.zero_()
+        x[0, at] = torch.tensor([1, 2, 3, 4, 5, 6], device=DEV).bfloat16()
+        w[0, at] = torch.tensor([1, 1, 2, 2, 4, 8], device=DEV).bfloat16()
+        (out,) = m.mamba_linear_fwd(x[:, :K], w[:, :K])
+        assert float(out) == 1 + 2 + 6 + 8 + 20 + 48, K
+
+
 def test_linear_at_block_bench_size_sampled_rows(m):
     """in_proj and out_proj of the whole-block leg of bench.py (32768 tokens, Mamba-130M widths), in the launch
     configuration it times; rows are independent, so the oracle computes a seeded sample of them (every row block
