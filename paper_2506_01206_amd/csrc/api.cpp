@@ -636,7 +636,7 @@ int mamba_block_step(const mamba_block_params_t *p, const void *hidden, void *hi
         if (overlap(hidden, hid_bytes, workspace, (int64_t)bb.total) || overlap(hidden_out, hid_bytes, workspace, (int64_t)bb.total))
             return MAMBA_ERR_ALIAS;
     }
-    if (n_out <= 64) {
+    if (n_out <= 64 && linear_few_fits(2 * Di, p->d_model)) {
         // A draft position has a few rows and lives on launch latency, so the chain is shortened to four
         // launches: RMSNorm rides into in_proj and the conv step (with the copy of the parent's window)
         // out of it, the dt projection rides in the state step.  (Buffers: z -> b, x_c -> c, y -> d.)

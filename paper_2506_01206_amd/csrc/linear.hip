@@ -906,7 +906,7 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
 #define MAMBA_FEW(MT) do { if (a.K >= 1024) MAMBA_FEW_K(MT, false, 64); else MAMBA_FEW_K(MT, false, 32); } while (0)
     if (a.norm_w) {
         // the way into a block at a draft position: norm and conv come together, the next projection only with them
-        if (!linear_few_fits(a.K) || !a.conv_w || !a.conv_src || !a.conv_dst || a.conv_k < 2 || (a.xproj_w && (!a.xproj_part || a.width[0] % 16)))
+        if (!linear_few_fits(N, a.K) || !a.conv_w || !a.conv_src || !a.conv_dst || a.conv_k < 2 || (a.xproj_w && (!a.xproj_part || a.width[0] % 16)))
             return hipErrorInvalidValue;
         if (tiles(16, 16) <= kTilesResident) MAMBA_FEW_K(1, true, 32);
         else if (tiles(32, 16) <= kTilesResident) MAMBA_FEW_K(2, true, 32);
@@ -922,7 +922,7 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     //   64 x 1024, K = 512    2.9   3.3   4.0   4.8   6.5   5.6        333 x 80, K = 1536    3.7   4.4   6.2   5.7   7.6  10.4
     //  128 x  768, K = 1536   4.6x  4.4   6.2   5.6   7.7  10.5        333 x 640, K = 768    5.1x  5.7x  4.7   5.3   7.1   7.0
     //  256 x  768, K = 1536   6.0x  7.0x  6.3   5.6   7.6  10.5        512 x 768, K = 1536   9.5x  9.9x 10.6x  9.3x  7.7  10.6
-    const bool few = linear_few_fits(a.K);
+    const bool few = linear_few_fits(N, a.K);
     if (few && tiles(16, 16) <= kTilesResident * 5 / 4) { MAMBA_FEW(1); return hipGetLastError(); }
     if (few && tiles(32, 16) <= kTilesResident) { MAMBA_FEW(2); return hipGetLastError(); }
     if (a.K <= 768 && tiles(64, 16) <= kTilesResident) { MAMBA_FEW_K(4, false, 32); return hipGetLastError(); }

@@ -22,8 +22,12 @@ inline bool ssd_folds(int n_seg1, int before, const void *h0, const void *h_fina
     return n_seg1 > 1 && before <= 10 && !overlap(h0, state_bytes, h_final, state_bytes);
 }
 
-// The few-row product counts k in 32 bits: k rounded up to a step of 64 has to fit an int.  What does not fit takes the kernels
-// that count in 64 bits.
-inline bool linear_few_fits(int64_t K) { return K <= (int64_t)INT32_MAX - 63; }
+// The few-row product counts k and columns in 32 bits and a workgroup of 512 threads takes 16 columns: k rounded up to a step
+// of 64 has to fit an int, and the grid's threads along x have to stay below 2^32.  What does not fit takes the kernels
+// that count in 64 bits (at a draft position: the chain of separate launches).
+inline bool linear_few_fits(int64_t N, int64_t K)
+{
+    return K <= (int64_t)INT32_MAX - 63 && N <= ((int64_t)1 << 27) - 16;
+}
 
 }  // namespace mamba

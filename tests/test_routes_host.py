@@ -11,7 +11,7 @@ SHIM = """
 #include "routes.h"
 extern "C" int folds(int n_seg1, int before, uintptr_t h0, uintptr_t h_final, int64_t bytes)
 { return mamba::ssd_folds(n_seg1, before, (const void *)h0, (const void *)h_final, bytes); }
-extern "C" int few_fits(int64_t K) { return mamba::linear_few_fits(K); }
+extern "C" int few_fits(int64_t N, int64_t K) { return mamba::linear_few_fits(N, K); }
 """
 
 
@@ -24,7 +24,7 @@ def routes(tmp_path_factory):
     lib = ctypes.CDLL(str(d / "shim.so"))
     i32, i64, ptr = ctypes.c_int, ctypes.c_int64, ctypes.c_size_t
     lib.folds.argtypes = [i32, i32, ptr, ptr, i64]
-    lib.few_fits.argtypes = [i64]
+    lib.few_fits.argtypes = [i64, i64]
     return lib
 
 
@@ -41,7 +41,9 @@ def test_scalar_decay_segments_are_not_stitched_over_their_own_initial_state(rou
 
 
 def test_few_row_product_leaves_what_32_bits_do_not_count_to_others(routes):
-    """It rounds k up to steps of 64, counted in 32 bits."""
-    assert routes.few_fits(8) and routes.few_fits(1 << 30) and routes.few_fits((1 << 31) - 64)
+    """It rounds k up to steps of 64 and launches 512 threads per 16 columns, both counted in 32 bits."""
+    assert routes.few_fits(1, 8) and routes.few_fits(8191, 1 << 30) and routes.few_fits(1, (1 << 31) - 64)
     for K in ((1 << 31) - 56, (1 << 31) - 8, 1 << 31, (1 << 31) + 8, 1 << 32, 1 << 40):
-        assert not routes.few_fits(K), K
+        assert not routes.few_fits(1, K), K
+    assert routes.few_fits(1 << 26, 768) and (((1 << 27) - 16) // 16) * 512 < 1 << 32
+    assert routes.few_fits((1 << 27) - 16, 768) and not routes.few_fits(1 << 27, 768) and not routes.few_fits(1 << 31, 8)
