@@ -83,7 +83,8 @@ template <int COUNT> __device__ __forceinline__ void st_block(bf16_t *p, const f
     for (int v = 0; v < COUNT / 8; ++v) pack_row(f + 8 * v, q[v]);
 }
 
-// grid: (channel-vector groups, groups of four time tiles, batch)
+// grid: (channel-vector groups, groups of four time tiles, batch), blocks of 64 x 4 threads (a grid has fewer than 2^32 threads
+// along x, so the wavefronts of a workgroup count along y)
 template <typename T, int VEC, int K, bool SILU>
 __global__ void __launch_bounds__(kBlock)
 conv1d_kernel(const T *__restrict__ x, const float *__restrict__ w, const float *__restrict__ bias,
@@ -93,7 +94,7 @@ conv1d_kernel(const T *__restrict__ x, const float *__restrict__ w, const float 
     typedef typename RowVec<T, VEC>::type row_t;
     constexpr int H = K - 1;
     const int64_t b = blockIdx.z;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int lane = threadIdx.x, wave = threadIdx.y, tid = wave * kWave + lane;
     const int64_t d_block = (int64_t)blockIdx.x * (lanes * VEC);    // first channel of the workgroup
     const int64_t d0 = d_block + lane * VEC;
     const bool live = lane < lanes && d0 < D;
@@ -272,15 +273,15 @@ template <typename T, int VEC, int K> hipError_t launch_conv_k(const ConvArgs &a
     if (tile_len < 1) tile_len = 1;
     int64_t tiles = (a.L + tile_len - 1) / tile_len;
     if (tiles < 1) tiles = 1;  // L == 0: one tile that only passes the carried state on
-    dim3 grid(gx, (unsigned)((tiles + kTilesPerBlock - 1) / kTilesPerBlock), (unsigned)a.batch);
+    const dim3 grid(gx, (unsigned)((tiles + kTilesPerBlock - 1) / kTilesPerBlock), (unsigned)a.batch), block(kWave, kTilesPerBlock);
     const T *x = static_cast<const T *>(a.x);
     const T *si = static_cast<const T *>(a.state_in);
     T *y = static_cast<T *>(a.y);
     T *so = static_cast<T *>(a.state_out);
     if (a.apply_silu)
-        conv1d_kernel<T, VEC, K, true><<<grid, kBlock, 0, stream>>>(x, a.w, a.bias, si, y, so, a.L, a.D, tile_len, lanes, a.parent, a.n_in);
+        conv1d_kernel<T, VEC, K, true><<<grid, block, 0, stream>>>(x, a.w, a.bias, si, y, so, a.L, a.D, tile_len, lanes, a.parent, a.n_in);
     else
-        conv1d_kernel<T, VEC, K, false><<<grid, kBlock, 0, stream>>>(x, a.w, a.bias, si, y, so, a.L, a.D, tile_len, lanes, a.parent, a.n_in);
+        conv1d_kernel<T, VEC, K, false><<<grid, block, 0, stream>>>(x, a.w, a.bias, si, y, so, a.L, a.D, tile_len, lanes, a.parent, a.n_in);
     return hipGetLastError();
 }
 

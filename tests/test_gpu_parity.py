@@ -944,6 +944,17 @@ def test_softplus_and_silu_accuracy_through_the_step(m):
 
 
 # ------------------------------------------------------------------------------------ size limits
+def test_conv_of_more_channels_than_a_grid_has_threads_in_fours(m):
+    """2^30 + 1 channels, one to a lane: 64 threads a workgroup along x, not all 256, which would pass the grid's 2^32."""
+    D = (1 << 30) + 1
+    x = torch.zeros(1, 1, D, device=DEV)
+    w = torch.ones(D, 2, device=DEV)
+    at = torch.tensor([0, 63, 64, 1 << 29, D - 65, D - 2, D - 1], device=DEV)
+    x[0, 0, at] = torch.arange(1, 8, device=DEV).float()
+    y, state = m.mamba_conv1d_fwd(x, w, apply_silu=False)
+    assert torch.equal(y, x) and torch.equal(state[..., 0], x[:, 0])
+
+
 def test_largest_grids(m):
     """Shapes that sit on the launch-grid limits: 65535 branches / batch rows / layers, and a
     sequence long enough that the conv tiles must grow to stay within 65535 time tiles."""
