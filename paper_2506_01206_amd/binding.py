@@ -339,9 +339,10 @@ def mamba_linear_fwd(x, w, bias=None, residual=None, splits=None, outs=None, str
     output tensors that share the N columns (default: one tensor of width N); returns a tuple."""
     widths = [w.shape[0]] if splits is None else list(splits)
     assert sum(widths) == w.shape[0] and 1 <= len(widths) <= 3
-    widths += [-1] * (3 - len(widths))
+    allocate = len(widths) if outs is None else 0
+    widths += [0] * (3 - len(widths))
     o = [None] * 3 if outs is None else list(outs) + [None] * (3 - len(outs))
-    return _marshal.linear_fwd(x, w, bias, residual, o[0], widths[0], o[1], widths[1], o[2], widths[2], outs is None,
+    return _marshal.linear_fwd(x, w, bias, residual, o[0], widths[0], o[1], widths[1], o[2], widths[2], allocate,
                                stream and stream.cuda_stream)
 
 

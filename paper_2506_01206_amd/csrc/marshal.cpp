@@ -335,7 +335,7 @@ PyObject *state_fork(Args a)
     return result({conv_dst.object, ssm_dst.object});
 }
 
-PyObject *linear_fwd(Args a)   // x, w, bias, residual, (out0, width0, out1, width1, out2, width2), stream
+PyObject *linear_fwd(Args a)   // x, w, bias, residual, out0, width0, out1, width1, out2, width2, outputs to allocate, stream
 {
     PyObject *x = a[0], *w = a[1];
     const at::Tensor &xt = tensor(x, "x");
@@ -343,17 +343,14 @@ PyObject *linear_fwd(Args a)   // x, w, bias, residual, (out0, width0, out1, wid
     const int64_t M = s[0], K = s[1], N = sizes(w, "w", 2)[0];
     const auto type = xt.scalar_type();
     const int io = io_code(xt);
-    const int64_t n0 = integer(a[5]), n1 = integer(a[7]), n2 = integer(a[9]);
+    const int64_t n0 = integer(a[5]), n1 = integer(a[7]), n2 = integer(a[9]), allocate = integer(a[10]);
     Out o0(a[4]), o1(a[6]), o2(a[8]);
-    if (flag(a[10])) {
-        o0.make(xt, {M, n0}, type);
-        if (n1 >= 0) o1.make(xt, {M, n1}, type);
-        if (n2 >= 0) o2.make(xt, {M, n2}, type);
-    }
-    const int64_t w1 = n1 < 0 ? 0 : n1, w2 = n2 < 0 ? 0 : n2;
+    if (allocate > 0) o0.make(xt, {M, n0}, type);                // (a negative width is refused here, or by the C function)
+    if (allocate > 1) o1.make(xt, {M, n1}, type);
+    if (allocate > 2) o2.make(xt, {M, n2}, type);
     invoke("mamba_linear_fwd", api.linear_fwd, ptr(x, "x"), ptr(w, type, {N, K}, "w"), fptr(a[2], {N}, "bias"), ptr(a[3], type, {M, N}, "residual"),
-           ptr(o0.object, type, {M, n0}, "out0"), n0, ptr(o1.object, type, {M, w1}, "out1"), w1,
-           ptr(o2.object, type, {M, w2}, "out2"), w2, M, K, io, stream_of(a[11]));
+           ptr(o0.object, type, {M, n0}, "out0"), n0, ptr(o1.object, type, {M, n1}, "out1"), n1,
+           ptr(o2.object, type, {M, n2}, "out2"), n2, M, K, io, stream_of(a[11]));
     if (o2.object != Py_None && o1.object != Py_None && o0.object != Py_None) return result({o0.object, o1.object, o2.object});
     if (o1.object != Py_None && o0.object != Py_None) return result({o0.object, o1.object});
     return result({o0.object});
