@@ -373,7 +373,6 @@ class Block:
             _ptr(w["dt_proj_w"], bf, (d_inner, dt_rank), "dt_proj_w"), _ptr(w["dt_bias"], f32, (d_inner,), "dt_bias"),
             _ptr(w["A"], f32, (d_inner, d_state), "A"), _ptr(w["Dskip"], f32, (d_inner,), "Dskip"),
             _ptr(w["out_proj_w"], bf, (d_model, d_inner), "out_proj_w"))
-        self.address = ctypes.addressof(self.c)
         self.d_model, self.d_inner, self.d_state, self.dt_rank, self.d_conv = d_model, d_inner, d_state, dt_rank, d_conv
 
 
@@ -398,8 +397,8 @@ def mamba_block_fwd(block: Block, hidden, hidden_out=None, conv_state_in=None, h
     """hidden (B,L,d_model) bf16 -> hidden + mixer(rmsnorm(hidden)); also the conv and SSM states."""
     if stream is not None and workspace is None:
         workspace = _scratch(mamba_block_workspace_bytes(block, *hidden.shape[:2]), hidden.device, stream)
-    return _marshal.block_fwd(block.address, hidden, hidden_out, conv_state_in, h0, conv_state_out, h_final, workspace,
-                              want_state, stream and stream.cuda_stream)
+    return _marshal.block_fwd(ctypes.addressof(block.c), hidden, hidden_out, conv_state_in, h0, conv_state_out, h_final,
+                              workspace, want_state, stream and stream.cuda_stream)
 
 
 def mamba_block_step(block: Block, hidden, conv_src, ssm_src, parent_idx=None, conv_dst=None, ssm_dst=None,
@@ -408,8 +407,8 @@ def mamba_block_step(block: Block, hidden, conv_src, ssm_src, parent_idx=None, c
     With parent_idx the children's states go to conv_dst / ssm_dst; without, the step is in place."""
     if stream is not None and workspace is None:
         workspace = _scratch(mamba_block_workspace_bytes(block, hidden.shape[0], 1), hidden.device, stream)
-    return _marshal.block_step(block.address, hidden, conv_src, ssm_src, parent_idx, conv_dst, ssm_dst, hidden_out, workspace,
-                               stream and stream.cuda_stream)
+    return _marshal.block_step(ctypes.addressof(block.c), hidden, conv_src, ssm_src, parent_idx, conv_dst, ssm_dst, hidden_out,
+                               workspace, stream and stream.cuda_stream)
 
 
 def mamba_embedding_fwd(tokens, table, out=None, stream=None):

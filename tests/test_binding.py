@@ -1,6 +1,8 @@
 """The Python binding: argument checks, and that what is refused is refused before anything is launched.  Without a GPU every
 call ends in a check, and the checks are reached in the order of the arguments; what takes device tensors is marked gpu."""
+import ctypes
 import os
+import types
 
 import pytest
 import torch
@@ -24,3 +26,12 @@ def test_linear_refuses_negative_output_widths(m):
     for splits in ([32, -8], [-8, 32], [40, -8, -8], [24, 8, -8], [32, -1, -7]):
         with pytest.raises(RuntimeError, match="negative dimension"):
             m.mamba_linear_fwd(x, w, splits=splits)
+
+
+def test_block_parameters_are_read_at_each_call(m, monkeypatch):
+    """What goes to the library is the parameter structure a block holds now: nothing keeps the address of an earlier one."""
+    monkeypatch.setattr(m, "_marshal", types.SimpleNamespace(block_fwd=lambda address, *a: address, block_step=lambda address, *a: address))
+    block = m.Block.__new__(m.Block)
+    for d_inner in (64, 128):
+        block.c = m.BlockParams(64, d_inner, 16, 8, 4, 1e-5)
+        assert m.mamba_block_fwd(block, None) == m.mamba_block_step(block, None, None, None) == ctypes.addressof(block.c)
