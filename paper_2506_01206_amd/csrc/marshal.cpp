@@ -194,21 +194,24 @@ struct Workspace {
 };
 
 // Calls a function of the C ABI, the interpreter lock released meanwhile (a launch can block on a full queue), and
-// raises MambaError for a status that is not zero.
-template <typename F, typename... A> void invoke(const char *function, F f, A... args)
-{
-    int status;
-    Py_BEGIN_ALLOW_THREADS
-    status = f(args...);
-    Py_END_ALLOW_THREADS
-    if (status == 0) return;
-    PyObject *e = PyObject_CallFunction(mamba_error, "si", function, status);
-    if (e) {
-        PyErr_SetObject(mamba_error, e);
-        Py_DECREF(e);
+// raises MambaError for a status that is not zero.  A class, to be used with braces: only there are the arguments, which do
+// the checks, formed in the order in which they are written (the current stream last, when all tensors are known to be the GPU's).
+template <typename F, typename... A> struct Call {
+    Call(const char *function, F f, A... args)
+    {
+        int status;
+        Py_BEGIN_ALLOW_THREADS
+        status = f(args...);
+        Py_END_ALLOW_THREADS
+        if (status == 0) return;
+        PyObject *e = PyObject_CallFunction(mamba_error, "si", function, status);
+        if (e) {
+            PyErr_SetObject(mamba_error, e);
+            Py_DECREF(e);
+        }
+        throw PyFailed();
     }
-    throw PyFailed();
-}
+};
 
 PyObject *result(std::initializer_list<PyObject *> items)
 {
@@ -236,9 +239,9 @@ PyObject *conv1d_fwd(Args a)
     const auto type = xt.scalar_type();
     y.unless_given(xt, s, type);
     if (flag(a[7])) state_out.unless_given(xt, {B, D, K - 1}, type);
-    invoke("mamba_conv1d_fwd", api.conv1d_fwd, ptr(x, "x"), fptr(w, {D, K}, "w"), fptr(bias, {D}, "bias"), ptr(state_in, type, {B, D, K - 1}, "conv_state_in"),
-           ptr(y.object, type, {B, L, D}, "y"), ptr(state_out.object, type, {B, D, K - 1}, "conv_state_out"), B, L, D,
-           (int)K, flag(a[6]), io, stream_of(a[8]));
+    Call{"mamba_conv1d_fwd", api.conv1d_fwd, ptr(x, "x"), fptr(w, {D, K}, "w"), fptr(bias, {D}, "bias"), ptr(state_in, type, {B, D, K - 1}, "conv_state_in"),
+         ptr(y.object, type, {B, L, D}, "y"), ptr(state_out.object, type, {B, D, K - 1}, "conv_state_out"), B, L, D,
+         (int)K, flag(a[6]), io, stream_of(a[8])};
     return result({y.object, state_out.object});
 }
 
@@ -254,11 +257,11 @@ PyObject *scan_fwd(Args a)
     out.unless_given(xt, s, type);
     if (flag(a[14])) h_final.unless_given(xt, {B, D, N}, at::kFloat);
     const Workspace ws(a[11], api.scan_workspace_bytes(B, L, D, N, chunk_len), xt);
-    invoke("mamba_scan_fwd", api.scan_fwd, ptr(x, "x"), ptr(a[1], type, {B, L, D}, "dt"), fptr(A, {D, N}, "A"), ptr(a[3], type, {B, L, N}, "Bm"),
-           ptr(a[4], type, {B, L, N}, "Cm"), fptr(a[5], {D}, "Dskip"), ptr(a[6], type, {B, L, D}, "z"),
-           fptr(a[7], {D}, "dt_bias"), fptr(a[8], {B, D, N}, "h0"), ptr(out.object, type, {B, L, D}, "out"),
-           fptr(h_final.object, {B, D, N}, "h_final"), ws.data, ws.bytes, B, L, D, N, chunk_len, flag(a[13]), io,
-           stream_of(a[15]));
+    Call{"mamba_scan_fwd", api.scan_fwd, ptr(x, "x"), ptr(a[1], type, {B, L, D}, "dt"), fptr(A, {D, N}, "A"), ptr(a[3], type, {B, L, N}, "Bm"),
+         ptr(a[4], type, {B, L, N}, "Cm"), fptr(a[5], {D}, "Dskip"), ptr(a[6], type, {B, L, D}, "z"),
+         fptr(a[7], {D}, "dt_bias"), fptr(a[8], {B, D, N}, "h0"), ptr(out.object, type, {B, L, D}, "out"),
+         fptr(h_final.object, {B, D, N}, "h_final"), ws.data, ws.bytes, B, L, D, N, chunk_len, flag(a[13]), io,
+         stream_of(a[15])};
     return result({out.object, h_final.object});
 }
 
@@ -273,12 +276,12 @@ PyObject *state_step(Args a)
     const auto type = xt.scalar_type();
     h_out.unless_given(xt, {n_out, D, N}, at::kFloat);
     out.unless_given(xt, xt.sizes(), type);
-    invoke("mamba_state_step", api.state_step, fptr(h_out.object, {n_out, D, N}, "h_out"), static_cast<const float *>(ptr(h_in, at::kFloat, "h_in")),
-           static_cast<const int32_t *>(ptr(parent, at::kInt, {n_out}, "parent_idx")), ptr(x, "x"),
-           ptr(a[2], type, {n_out, D}, "dt"), fptr(a[3], {D, N}, "A"), ptr(a[4], type, {n_out, N}, "Bm"),
-           ptr(a[5], type, {n_out, N}, "Cm"), fptr(a[6], {D}, "Dskip"), ptr(a[7], type, {n_out, D}, "z"),
-           fptr(a[8], {D}, "dt_bias"), ptr(out.object, type, {n_out, D}, "out"), n_out, n_in, D, N, flag(a[12]), io,
-           stream_of(a[13]));
+    Call{"mamba_state_step", api.state_step, fptr(h_out.object, {n_out, D, N}, "h_out"), static_cast<const float *>(ptr(h_in, at::kFloat, "h_in")),
+         static_cast<const int32_t *>(ptr(parent, at::kInt, {n_out}, "parent_idx")), ptr(x, "x"),
+         ptr(a[2], type, {n_out, D}, "dt"), fptr(a[3], {D, N}, "A"), ptr(a[4], type, {n_out, N}, "Bm"),
+         ptr(a[5], type, {n_out, N}, "Cm"), fptr(a[6], {D}, "Dskip"), ptr(a[7], type, {n_out, D}, "z"),
+         fptr(a[8], {D}, "dt_bias"), ptr(out.object, type, {n_out, D}, "out"), n_out, n_in, D, N, flag(a[12]), io,
+         stream_of(a[13])};
     return result({h_out.object, out.object});
 }
 
@@ -295,15 +298,15 @@ PyObject *conv_state_step(Args a)
     conv_out.unless_given(xt, {n_out, D, K - 1}, type);
     out.unless_given(xt, xt.sizes(), type);
     if (flag(a[17])) xc.unless_given(xt, xt.sizes(), type);
-    invoke("mamba_conv_state_step", api.conv_state_step, fptr(h_out.object, {n_out, D, N}, "h_out"), static_cast<const float *>(ptr(h_in, at::kFloat, "h_in")),
-           ptr(conv_out.object, type, {n_out, D, K - 1}, "conv_state_out"),
-           ptr(conv_in, type, {n_in, D, K - 1}, "conv_state_in"),
-           static_cast<const int32_t *>(ptr(parent, at::kInt, {n_out}, "parent_idx")), ptr(x, "x"),
-           fptr(conv_w, {D, K}, "conv_w"), fptr(a[4], {D}, "conv_bias"), ptr(a[5], type, {n_out, D}, "dt"),
-           fptr(a[6], {D, N}, "A"), ptr(a[7], type, {n_out, N}, "Bm"), ptr(a[8], type, {n_out, N}, "Cm"),
-           fptr(a[9], {D}, "Dskip"), ptr(a[10], type, {n_out, D}, "z"), fptr(a[11], {D}, "dt_bias"),
-           ptr(out.object, type, {n_out, D}, "out"), ptr(xc.object, type, {n_out, D}, "xc_out"), n_out, n_in, D, N,
-           (int)K, flag(a[18]), flag(a[19]), io, stream_of(a[20]));
+    Call{"mamba_conv_state_step", api.conv_state_step, fptr(h_out.object, {n_out, D, N}, "h_out"), static_cast<const float *>(ptr(h_in, at::kFloat, "h_in")),
+         ptr(conv_out.object, type, {n_out, D, K - 1}, "conv_state_out"),
+         ptr(conv_in, type, {n_in, D, K - 1}, "conv_state_in"),
+         static_cast<const int32_t *>(ptr(parent, at::kInt, {n_out}, "parent_idx")), ptr(x, "x"),
+         fptr(conv_w, {D, K}, "conv_w"), fptr(a[4], {D}, "conv_bias"), ptr(a[5], type, {n_out, D}, "dt"),
+         fptr(a[6], {D, N}, "A"), ptr(a[7], type, {n_out, N}, "Bm"), ptr(a[8], type, {n_out, N}, "Cm"),
+         fptr(a[9], {D}, "Dskip"), ptr(a[10], type, {n_out, D}, "z"), fptr(a[11], {D}, "dt_bias"),
+         ptr(out.object, type, {n_out, D}, "out"), ptr(xc.object, type, {n_out, D}, "xc_out"), n_out, n_in, D, N,
+         (int)K, flag(a[18]), flag(a[19]), io, stream_of(a[20])};
     return result({h_out.object, conv_out.object, out.object, xc.object});
 }
 
@@ -327,11 +330,11 @@ PyObject *state_fork(Args a)
         N = sizes(ssm_src, "ssm_src", 4)[3];
         ssm_dst.unless_given(rt, {n_layers, n_out, D, N}, at::kFloat);
     }
-    invoke("mamba_state_fork", api.state_fork, ptr(conv_dst.object, "conv_dst"), ptr(conv_src, "conv_src"),
-           static_cast<float *>(ptr(ssm_dst.object, at::kFloat, "ssm_dst")),
-           static_cast<const float *>(ptr(ssm_src, at::kFloat, "ssm_src")),
-           static_cast<const int32_t *>(ptr(parent, at::kInt, "parent_idx")), n_layers, n_out, n_in, D, N, (int)K, code,
-           stream_of(a[5]));
+    Call{"mamba_state_fork", api.state_fork, ptr(conv_dst.object, "conv_dst"), ptr(conv_src, "conv_src"),
+         static_cast<float *>(ptr(ssm_dst.object, at::kFloat, "ssm_dst")),
+         static_cast<const float *>(ptr(ssm_src, at::kFloat, "ssm_src")),
+         static_cast<const int32_t *>(ptr(parent, at::kInt, "parent_idx")), n_layers, n_out, n_in, D, N, (int)K, code,
+         stream_of(a[5])};
     return result({conv_dst.object, ssm_dst.object});
 }
 
@@ -348,9 +351,9 @@ PyObject *linear_fwd(Args a)   // x, w, bias, residual, out0, width0, out1, widt
     if (allocate > 0) o0.make(xt, {M, n0}, type);                // (a negative width is refused here, or by the C function)
     if (allocate > 1) o1.make(xt, {M, n1}, type);
     if (allocate > 2) o2.make(xt, {M, n2}, type);
-    invoke("mamba_linear_fwd", api.linear_fwd, ptr(x, "x"), ptr(w, type, {N, K}, "w"), fptr(a[2], {N}, "bias"), ptr(a[3], type, {M, N}, "residual"),
-           ptr(o0.object, type, {M, n0}, "out0"), n0, ptr(o1.object, type, {M, n1}, "out1"), n1,
-           ptr(o2.object, type, {M, n2}, "out2"), n2, M, K, io, stream_of(a[11]));
+    Call{"mamba_linear_fwd", api.linear_fwd, ptr(x, "x"), ptr(w, type, {N, K}, "w"), fptr(a[2], {N}, "bias"), ptr(a[3], type, {M, N}, "residual"),
+         ptr(o0.object, type, {M, n0}, "out0"), n0, ptr(o1.object, type, {M, n1}, "out1"), n1,
+         ptr(o2.object, type, {M, n2}, "out2"), n2, M, K, io, stream_of(a[11])};
     if (o2.object != Py_None && o1.object != Py_None && o0.object != Py_None) return result({o0.object, o1.object, o2.object});
     if (o1.object != Py_None && o0.object != Py_None) return result({o0.object, o1.object});
     return result({o0.object});
@@ -366,8 +369,8 @@ PyObject *rmsnorm_fwd(Args a)
     const double eps = PyFloat_AsDouble(a[2]);
     if (eps == -1.0 && PyErr_Occurred()) throw PyFailed();
     y.unless_given(xt, s, xt.scalar_type());
-    invoke("mamba_rmsnorm_fwd", api.rmsnorm_fwd, ptr(x, "x"), fptr(w, {C}, "w"), ptr(y.object, xt.scalar_type(), {M, C}, "y"), M, C,
-           (float)eps, io_code(xt), stream_of(a[4]));
+    Call{"mamba_rmsnorm_fwd", api.rmsnorm_fwd, ptr(x, "x"), fptr(w, {C}, "w"), ptr(y.object, xt.scalar_type(), {M, C}, "y"), M, C,
+         (float)eps, io_code(xt), stream_of(a[4])};
     Py_INCREF(y.object);
     return y.object;
 }
@@ -392,10 +395,10 @@ PyObject *block_fwd(Args a)   // address of the parameters, hidden, hidden_out, 
     }
     size_t need = api.block_workspace_bytes(p, B, L);
     const Workspace ws(a[7], need < 16 ? 16 : need, ht);
-    invoke("mamba_block_fwd", api.block_fwd, p, ptr(hidden, at::kBFloat16, "hidden"), ptr(hidden_out.object, at::kBFloat16, {B, L, dm}, "hidden_out"),
-           ptr(a[3], at::kBFloat16, {B, D, K - 1}, "conv_state_in"),
-           ptr(conv_out.object, at::kBFloat16, {B, D, K - 1}, "conv_state_out"), fptr(a[4], {B, D, N}, "h0"),
-           fptr(h_final.object, {B, D, N}, "h_final"), ws.data, ws.bytes, B, L, stream_of(a[9]));
+    Call{"mamba_block_fwd", api.block_fwd, p, ptr(hidden, at::kBFloat16, "hidden"), ptr(hidden_out.object, at::kBFloat16, {B, L, dm}, "hidden_out"),
+         ptr(a[3], at::kBFloat16, {B, D, K - 1}, "conv_state_in"),
+         ptr(conv_out.object, at::kBFloat16, {B, D, K - 1}, "conv_state_out"), fptr(a[4], {B, D, N}, "h0"),
+         fptr(h_final.object, {B, D, N}, "h_final"), ws.data, ws.bytes, B, L, stream_of(a[9])};
     return result({hidden_out.object, conv_out.object, h_final.object});
 }
 
@@ -418,12 +421,12 @@ PyObject *block_step(Args a)   // address of the parameters, hidden, conv_src, s
     }
     size_t need = api.block_workspace_bytes(p, n_out, 1);
     const Workspace ws(a[8], need < 16 ? 16 : need, ht);
-    invoke("mamba_block_step", api.block_step, p, ptr(hidden, at::kBFloat16, "hidden"), ptr(hidden_out.object, at::kBFloat16, {n_out, dm}, "hidden_out"),
-           ptr(conv_src, at::kBFloat16, {n_in, D, K - 1}, "conv_src"),
-           ptr(conv_dst.object, at::kBFloat16, {n_out, D, K - 1}, "conv_dst"), fptr(ssm_src, {n_in, D, N}, "ssm_src"),
-           fptr(ssm_dst.object, {n_out, D, N}, "ssm_dst"),
-           static_cast<const int32_t *>(ptr(parent, at::kInt, {n_out}, "parent_idx")), ws.data, ws.bytes, n_out, n_in,
-           stream_of(a[9]));
+    Call{"mamba_block_step", api.block_step, p, ptr(hidden, at::kBFloat16, "hidden"), ptr(hidden_out.object, at::kBFloat16, {n_out, dm}, "hidden_out"),
+         ptr(conv_src, at::kBFloat16, {n_in, D, K - 1}, "conv_src"),
+         ptr(conv_dst.object, at::kBFloat16, {n_out, D, K - 1}, "conv_dst"), fptr(ssm_src, {n_in, D, N}, "ssm_src"),
+         fptr(ssm_dst.object, {n_out, D, N}, "ssm_dst"),
+         static_cast<const int32_t *>(ptr(parent, at::kInt, {n_out}, "parent_idx")), ws.data, ws.bytes, n_out, n_in,
+         stream_of(a[9])};
     return result({hidden_out.object, conv_dst.object, ssm_dst.object});
 }
 
@@ -436,8 +439,8 @@ PyObject *embedding_fwd(Args a)
     const at::IntArrayRef ks = tensor(tokens, "tokens").sizes();
     const int64_t M = ks.empty() ? 0 : ks[0], V = ts[0], dm = ts[1];
     out.unless_given(tt, {M, dm}, tt.scalar_type());
-    invoke("mamba_embedding_fwd", api.embedding_fwd, static_cast<const int32_t *>(ptr(tokens, at::kInt, {M}, "tokens")), ptr(table, "table"),
-           ptr(out.object, tt.scalar_type(), {M, dm}, "out"), M, V, dm, io_code(tt), stream_of(a[3]));
+    Call{"mamba_embedding_fwd", api.embedding_fwd, static_cast<const int32_t *>(ptr(tokens, at::kInt, {M}, "tokens")), ptr(table, "table"),
+         ptr(out.object, tt.scalar_type(), {M, dm}, "out"), M, V, dm, io_code(tt), stream_of(a[3])};
     Py_INCREF(out.object);
     return out.object;
 }
@@ -451,8 +454,8 @@ PyObject *topk_fwd(Args a)
     const int64_t M = s[0], V = s[1], k = integer(a[1]);
     idx.unless_given(lt, {M, k}, at::kInt);
     val.unless_given(lt, {M, k}, at::kFloat);
-    invoke("mamba_topk_fwd", api.topk_fwd, ptr(logits, "logits"), static_cast<int32_t *>(ptr(idx.object, at::kInt, {M, k}, "idx")),
-           fptr(val.object, {M, k}, "val"), M, V, (int)k, io_code(lt), stream_of(a[4]));
+    Call{"mamba_topk_fwd", api.topk_fwd, ptr(logits, "logits"), static_cast<int32_t *>(ptr(idx.object, at::kInt, {M, k}, "idx")),
+         fptr(val.object, {M, k}, "val"), M, V, (int)k, io_code(lt), stream_of(a[4])};
     return result({idx.object, val.object});
 }
 
@@ -468,11 +471,11 @@ PyObject *ssd_fwd(Args a)
     if (flag(a[12])) h_final.unless_given(xt, {B, H, P, N}, at::kFloat);
     size_t need = api.ssd_workspace_bytes(B, L, H, P, N);
     const Workspace ws(a[11], need < 16 ? 16 : need, xt);
-    invoke("mamba2_ssd_fwd", api.ssd_fwd, ptr(x, "x"), ptr(a[1], type, {B, L, H}, "dt"), fptr(a[2], {H}, "A"), ptr(Bm, type, {B, L, N}, "Bm"),
-           ptr(a[4], type, {B, L, N}, "Cm"), fptr(a[5], {H}, "Dskip"), ptr(a[6], type, {B, L, H, P}, "z"),
-           fptr(a[7], {H}, "dt_bias"), fptr(a[8], {B, H, P, N}, "h0"), ptr(out.object, type, {B, L, H, P}, "out"),
-           fptr(h_final.object, {B, H, P, N}, "h_final"), ws.data, ws.bytes, B, L, H, P, N, flag(a[13]), io_code(xt),
-           stream_of(a[14]));
+    Call{"mamba2_ssd_fwd", api.ssd_fwd, ptr(x, "x"), ptr(a[1], type, {B, L, H}, "dt"), fptr(a[2], {H}, "A"), ptr(Bm, type, {B, L, N}, "Bm"),
+         ptr(a[4], type, {B, L, N}, "Cm"), fptr(a[5], {H}, "Dskip"), ptr(a[6], type, {B, L, H, P}, "z"),
+         fptr(a[7], {H}, "dt_bias"), fptr(a[8], {B, H, P, N}, "h0"), ptr(out.object, type, {B, L, H, P}, "out"),
+         fptr(h_final.object, {B, H, P, N}, "h_final"), ws.data, ws.bytes, B, L, H, P, N, flag(a[13]), io_code(xt),
+         stream_of(a[14])};
     return result({out.object, h_final.object});
 }
 
@@ -486,12 +489,12 @@ PyObject *ssd_step(Args a)
     const auto type = xt.scalar_type();
     h_out.unless_given(xt, {n_out, H, P, N}, at::kFloat);
     out.unless_given(xt, xt.sizes(), type);
-    invoke("mamba2_state_step", api.ssd_step, fptr(h_out.object, {n_out, H, P, N}, "h_out"), static_cast<const float *>(ptr(h_in, at::kFloat, "h_in")),
-           static_cast<const int32_t *>(ptr(parent, at::kInt, {n_out}, "parent_idx")), ptr(x, "x"),
-           ptr(a[2], type, {n_out, H}, "dt"), fptr(a[3], {H}, "A"), ptr(a[4], type, {n_out, N}, "Bm"),
-           ptr(a[5], type, {n_out, N}, "Cm"), fptr(a[6], {H}, "Dskip"), ptr(a[7], type, {n_out, H, P}, "z"),
-           fptr(a[8], {H}, "dt_bias"), ptr(out.object, type, {n_out, H, P}, "out"), n_out, n_in, H, P, N, flag(a[12]),
-           io_code(xt), stream_of(a[13]));
+    Call{"mamba2_state_step", api.ssd_step, fptr(h_out.object, {n_out, H, P, N}, "h_out"), static_cast<const float *>(ptr(h_in, at::kFloat, "h_in")),
+         static_cast<const int32_t *>(ptr(parent, at::kInt, {n_out}, "parent_idx")), ptr(x, "x"),
+         ptr(a[2], type, {n_out, H}, "dt"), fptr(a[3], {H}, "A"), ptr(a[4], type, {n_out, N}, "Bm"),
+         ptr(a[5], type, {n_out, N}, "Cm"), fptr(a[6], {H}, "Dskip"), ptr(a[7], type, {n_out, H, P}, "z"),
+         fptr(a[8], {H}, "dt_bias"), ptr(out.object, type, {n_out, H, P}, "out"), n_out, n_in, H, P, N, flag(a[12]),
+         io_code(xt), stream_of(a[13])};
     return result({h_out.object, out.object});
 }
 

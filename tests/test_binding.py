@@ -35,3 +35,40 @@ def test_block_parameters_are_read_at_each_call(m, monkeypatch):
     for d_inner in (64, 128):
         block.c = m.BlockParams(64, d_inner, 16, 8, 4, 1e-5)
         assert m.mamba_block_fwd(block, None) == m.mamba_block_step(block, None, None, None) == ctypes.addressof(block.c)
+
+
+def calls(m):
+    """Every natively marshalled function on small CPU tensors, with the name of its first tensor."""
+    z = torch.zeros
+    x, bl, a = z(1, 8, 16), z(1, 8, 4), z(16, 4)
+    xs, bs = z(2, 16), z(2, 4)
+    xm, bm = z(1, 8, 2, 64, dtype=BF16), z(1, 8, 64, dtype=BF16)
+    block = m.Block.__new__(m.Block)
+    block.c = m.BlockParams(64, 64, 16, 8, 4, 1e-5)
+    hid, conv, ssm = z(1, 8, 64, dtype=BF16), z(1, 64, 3, dtype=BF16), z(1, 64, 16)
+    return {
+        "mamba_conv1d_fwd": ("x", lambda: m.mamba_conv1d_fwd(x, z(16, 4))),
+        "mamba_scan_fwd": ("x", lambda: m.mamba_scan_fwd(x, x, a, bl, bl)),
+        "mamba_state_step": ("h_out", lambda: m.mamba_state_step(z(2, 16, 4), xs, xs, a, bs, bs)),
+        "mamba_conv_state_step": ("h_out", lambda: m.mamba_conv_state_step(z(2, 16, 4), z(2, 16, 3), xs, z(16, 4), None, xs, a, bs, bs)),
+        "mamba_state_fork": ("conv_dst", lambda: m.mamba_state_fork(z(1, 2, 16, 3), z(1, 2, 16, 4), z(2, dtype=I32))),
+        "mamba_linear_fwd": ("x", lambda: m.mamba_linear_fwd(z(2, 16, dtype=BF16), z(24, 16, dtype=BF16))),
+        "mamba_rmsnorm_fwd": ("x", lambda: m.mamba_rmsnorm_fwd(z(2, 16, dtype=BF16), z(16))),
+        "mamba_block_fwd": ("hidden", lambda: m.mamba_block_fwd(block, hid)),
+        "mamba_block_step": ("hidden", lambda: m.mamba_block_step(block, hid[0, :1], conv, ssm)),
+        "mamba_embedding_fwd": ("tokens", lambda: m.mamba_embedding_fwd(z(3, dtype=I32), z(5, 8, dtype=BF16))),
+        "mamba_topk_fwd": ("logits", lambda: m.mamba_topk_fwd(z(2, 100, dtype=BF16), 4)),
+        "mamba2_ssd_fwd": ("x", lambda: m.mamba2_ssd_fwd(xm, z(1, 8, 2, dtype=BF16), z(2), bm, bm)),
+        "mamba2_state_step": ("h_out", lambda: m.mamba2_state_step(z(2, 1, 64, 64), z(2, 1, 64), z(2, 1), z(1), z(2, 64), z(2, 64))),
+    }
+
+
+@pytest.mark.parametrize("name", ["mamba_conv1d_fwd", "mamba_scan_fwd", "mamba_state_step", "mamba_conv_state_step", "mamba_state_fork",
+                                  "mamba_linear_fwd", "mamba_rmsnorm_fwd", "mamba_block_fwd", "mamba_block_step", "mamba_embedding_fwd",
+                                  "mamba_topk_fwd", "mamba2_ssd_fwd", "mamba2_state_step"])
+def test_tensors_not_on_the_gpu_are_refused_by_name(m, name):
+    """The first argument of the C function is the first to be named, on a machine without a GPU too: the stream is asked for
+    only when all tensors have been checked."""
+    first, call = calls(m)[name]
+    with pytest.raises(ValueError, match="^%s must live on the GPU$" % first):
+        call()
