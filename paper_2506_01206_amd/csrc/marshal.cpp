@@ -13,9 +13,12 @@
 
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Dtype.h>
+#include <torch/csrc/DynamicTypes.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <initializer_list>
+#include <string>
 
 #include "../../include/mamba_hip.h"
 
@@ -80,20 +83,28 @@ void placed(const at::Tensor &t, const char *name)
     if (!t.is_contiguous()) fail(PyExc_ValueError, "%s must be contiguous", name);
 }
 
+PyObject *dtype_object(at::ScalarType type) { return reinterpret_cast<PyObject *>(torch::getTHPDtype(type)); }   // borrowed
+
 void typed(const at::Tensor &t, at::ScalarType type, const char *name)
 {
     if (t.scalar_type() != type) {
-        PyErr_Format(PyExc_TypeError, "%s must be %s, got %s", name, c10::toString(type), c10::toString(t.scalar_type()));
+        PyErr_Format(PyExc_TypeError, "%s must be %S, got %S", name, dtype_object(type), dtype_object(t.scalar_type()));
         throw PyFailed();
     }
+}
+
+std::string text(at::IntArrayRef shape)   // as Python writes a tuple
+{
+    std::string s = "(";
+    for (size_t i = 0; i < shape.size(); ++i) s += (i ? ", " : "") + std::to_string(shape[i]);
+    return s + (shape.size() == 1 ? ",)" : ")");
 }
 
 void shaped(const at::Tensor &t, Shape shape, const char *name)
 {
     const at::IntArrayRef s = t.sizes();
     if (s == at::IntArrayRef(shape)) return;
-    PyErr_Format(PyExc_ValueError, "%s has the wrong shape (%zu dimensions of %zu expected, or another size)", name, s.size(),
-                 shape.size());
+    PyErr_Format(PyExc_ValueError, "%s must have shape %s, got %s", name, text(shape).c_str(), text(s).c_str());
     throw PyFailed();
 }
 
@@ -128,7 +139,7 @@ int io_code(const at::Tensor &t)
 {
     if (t.scalar_type() == at::kFloat) return MAMBA_F32;
     if (t.scalar_type() == at::kBFloat16) return MAMBA_BF16;
-    PyErr_Format(PyExc_TypeError, "I/O tensors must be float32 or bfloat16, got %s", c10::toString(t.scalar_type()));
+    PyErr_Format(PyExc_TypeError, "I/O tensors must be float32 or bfloat16, got %S", dtype_object(t.scalar_type()));
     throw PyFailed();
 }
 

@@ -72,3 +72,25 @@ def test_tensors_not_on_the_gpu_are_refused_by_name(m, name):
     first, call = calls(m)[name]
     with pytest.raises(ValueError, match="^%s must live on the GPU$" % first):
         call()
+
+
+def test_io_type_is_named_as_torch_names_it(m):
+    with pytest.raises(TypeError, match=r"^I/O tensors must be float32 or bfloat16, got torch\.float64$"):
+        m.mamba_conv1d_fwd(torch.zeros(1, 8, 16, dtype=torch.float64), torch.zeros(16, 4))
+
+
+@pytest.mark.gpu
+def test_wrong_shapes_and_types_are_named_with_what_was_expected(m):
+    z = lambda *s, dt=F32: torch.zeros(*s, dtype=dt, device="cuda:0")
+    x, w = z(1, 8, 16), z(16, 4)
+    for call, error, text in (
+            (lambda: m.mamba_conv1d_fwd(x, w, z(15)), ValueError, r"bias must have shape (16,), got (15,)"),
+            (lambda: m.mamba_conv1d_fwd(x, w, conv_state_in=z(1, 16)), ValueError, r"conv_state_in must have shape (1, 16, 3), got (1, 16)"),
+            (lambda: m.mamba_conv1d_fwd(x, z(16, 4, dt=BF16)), TypeError, r"w must be torch.float32, got torch.bfloat16"),
+            (lambda: m.mamba_scan_fwd(x, x, z(16, 4), z(1, 8, 4), z(1, 7, 4)), ValueError, r"Cm must have shape (1, 8, 4), got (1, 7, 4)"),
+            (lambda: m.mamba_state_step(z(2, 16, 4), z(2, 16), z(2, 16), z(16, 4), z(2, 4), z(2, 4), parent_idx=z(3, dt=I32)), ValueError,
+             r"parent_idx must have shape (2,), got (3,)"),
+            (lambda: m.mamba_conv1d_fwd(x.transpose(1, 2), w), ValueError, r"x must be contiguous")):
+        with pytest.raises(error) as e:
+            call()
+        assert str(e.value) == text
