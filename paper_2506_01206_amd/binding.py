@@ -348,7 +348,7 @@ def mamba_linear_fwd(x, w, bias=None, residual=None, splits=None, outs=None, str
 
 def mamba_rmsnorm_fwd(x, w, eps=1e-5, y=None, stream=None):
     """x (M,C) bf16, w (C) f32 -> x * rsqrt(mean(x^2) + eps) * w."""
-    return _marshal.rmsnorm_fwd(x, w, eps, y, stream and stream.cuda_stream)
+    return _marshal.rmsnorm_fwd(x, w, float(eps), y, stream and stream.cuda_stream)
 
 
 class Block:
@@ -418,6 +418,8 @@ def mamba_embedding_fwd(tokens, table, out=None, stream=None):
 
 def mamba_topk_fwd(logits, k, idx=None, val=None, stream=None):
     """logits (M,V) bf16 -> idx int32 (M,k), val float32 (M,k), largest first, ties to the lower index."""
+    if idx is not None and val is not None and k == int(k):
+        k = int(k)                                       # (where the outputs are given, any number that equals their width)
     return _marshal.topk_fwd(logits, k, idx, val, stream and stream.cuda_stream)
 
 

@@ -4,6 +4,7 @@ import ctypes
 import os
 import types
 
+import numpy as np
 import pytest
 import torch
 
@@ -94,3 +95,23 @@ def test_wrong_shapes_and_types_are_named_with_what_was_expected(m):
         with pytest.raises(error) as e:
             call()
         assert str(e.value) == text
+
+
+def test_numbers_of_other_types_are_taken_as_before(m):
+    """eps is whatever float() takes, k any number that is whole where the outputs are given and an integer where they are not."""
+    x, logits = torch.zeros(2, 16, dtype=BF16), torch.zeros(2, 100, dtype=BF16)
+    idx, val = torch.zeros(2, 8, dtype=I32), torch.zeros(2, 8)
+    on_gpu = pytest.raises(ValueError, match="must live on the GPU")          # all other checks of the arguments passed
+    for eps in (1e-5, "1e-5", 1, np.float32(1e-5), torch.tensor(1e-5)):
+        with on_gpu:
+            m.mamba_rmsnorm_fwd(x, torch.zeros(16), eps=eps)
+    for k in (8, 8.0, np.int64(8), np.float32(8), torch.tensor(8)):
+        with on_gpu:
+            m.mamba_topk_fwd(logits, k, idx, val)
+    for k in (8, np.int64(8), torch.tensor(8)):
+        with on_gpu:
+            m.mamba_topk_fwd(logits, k)
+    with pytest.raises(TypeError):
+        m.mamba_topk_fwd(logits, 8.0)
+    with pytest.raises((TypeError, ValueError)):
+        m.mamba_topk_fwd(logits, 8.5, idx, val)
