@@ -64,12 +64,12 @@ const at::Tensor &tensor(PyObject *o, const char *name)
     return THPVariable_Unpack(o);
 }
 
-// sizes of a tensor that has to have `rank` dimensions
-at::IntArrayRef sizes(PyObject *o, const char *name, size_t rank)
+// sizes of a tensor that has to have `rank` dimensions, or at least as many
+at::IntArrayRef sizes(PyObject *o, const char *name, size_t rank, bool or_more = false)
 {
     const at::IntArrayRef s = tensor(o, name).sizes();
-    if (s.size() != rank) {
-        PyErr_Format(PyExc_ValueError, "%s must have %zu dimensions, got %zu", name, rank, s.size());
+    if (s.size() < rank || (s.size() > rank && !or_more)) {
+        PyErr_Format(PyExc_ValueError, "%s must have %s%zu dimensions, got %zu", name, or_more ? "at least " : "", rank, s.size());
         throw PyFailed();
     }
     return s;
@@ -328,8 +328,8 @@ PyObject *state_fork(Args a)
     const bool has_conv = conv_src != Py_None, has_ssm = ssm_src != Py_None;
     PyObject *ref = has_conv ? conv_src : ssm_src;
     const at::Tensor &rt = tensor(ref, has_conv ? "conv_src" : "ssm_src");
-    const auto s = sizes(ref, has_conv ? "conv_src" : "ssm_src", 4);
-    const int64_t n_layers = s[0], n_in = s[1], D = s[2], n_out = sizes(parent, "parent_idx", 1)[0];
+    const auto s = sizes(ref, has_conv ? "conv_src" : "ssm_src", 4, true);
+    const int64_t n_layers = s[0], n_in = s[1], D = s[2], n_out = sizes(parent, "parent_idx", 1, true)[0];
     int64_t K = 1, N = 0;
     int code = MAMBA_F32;
     if (has_conv) {
@@ -338,7 +338,7 @@ PyObject *state_fork(Args a)
         conv_dst.unless_given(rt, {n_layers, n_out, D, K - 1}, rt.scalar_type());
     }
     if (has_ssm) {
-        N = sizes(ssm_src, "ssm_src", 4)[3];
+        N = sizes(ssm_src, "ssm_src", 4, true)[3];
         ssm_dst.unless_given(rt, {n_layers, n_out, D, N}, at::kFloat);
     }
     Call{"mamba_state_fork", api.state_fork, ptr(conv_dst.object, "conv_dst"), ptr(conv_src, "conv_src"),

@@ -115,3 +115,15 @@ def test_numbers_of_other_types_are_taken_as_before(m):
         m.mamba_topk_fwd(logits, 8.0)
     with pytest.raises((TypeError, ValueError)):
         m.mamba_topk_fwd(logits, 8.5, idx, val)
+
+
+@pytest.mark.gpu
+def test_fork_takes_parents_and_states_with_further_dimensions(m):
+    """Parents as a column (n_out, 1), states with a last dimension of one."""
+    conv = torch.randn(2, 3, 16, 3, device="cuda:0")
+    ssm = torch.randn(2, 3, 16, 4, device="cuda:0")
+    parent = torch.tensor([2, 0, 1, 1, 2], dtype=I32, device="cuda:0")
+    want = conv[:, parent.long()], ssm[:, parent.long()]
+    for got in (m.mamba_state_fork(conv, ssm, parent), m.mamba_state_fork(conv, ssm, parent[:, None]),
+                m.mamba_state_fork(conv[..., None], ssm[..., None], parent)):
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
