@@ -224,17 +224,17 @@ template <typename F, typename... A> struct Call {
     }
 };
 
-PyObject *result(std::initializer_list<PyObject *> items)
+PyObject *result(PyObject *const *first, PyObject *const *last)
 {
-    PyObject *t = PyTuple_New((Py_ssize_t)items.size());
+    PyObject *t = PyTuple_New((Py_ssize_t)(last - first));
     if (!t) throw PyFailed();
-    Py_ssize_t i = 0;
-    for (PyObject *o : items) {
-        Py_INCREF(o);
-        PyTuple_SET_ITEM(t, i++, o);
+    for (Py_ssize_t i = 0; i < last - first; ++i) {
+        Py_INCREF(first[i]);
+        PyTuple_SET_ITEM(t, i, first[i]);
     }
     return t;
 }
+PyObject *result(std::initializer_list<PyObject *> items) { return result(items.begin(), items.end()); }
 
 // The functions below take the arguments of binding.py's functions of the same names, all of them, by position.
 typedef PyObject *const *Args;
@@ -365,9 +365,11 @@ PyObject *linear_fwd(Args a)   // x, w, bias, residual, out0, width0, out1, widt
     Call{"mamba_linear_fwd", api.linear_fwd, ptr(x, "x"), ptr(w, type, {N, K}, "w"), fptr(a[2], {N}, "bias"), ptr(a[3], type, {M, N}, "residual"),
          ptr(o0.object, type, {M, n0}, "out0"), n0, ptr(o1.object, type, {M, n1}, "out1"), n1,
          ptr(o2.object, type, {M, n2}, "out2"), n2, M, K, io, stream_of(a[11])};
-    if (o2.object != Py_None && o1.object != Py_None && o0.object != Py_None) return result({o0.object, o1.object, o2.object});
-    if (o1.object != Py_None && o0.object != Py_None) return result({o0.object, o1.object});
-    return result({o0.object});
+    PyObject *made[3];
+    size_t count = 0;
+    for (PyObject *o : {o0.object, o1.object, o2.object})
+        if (o != Py_None) made[count++] = o;
+    return result(made, made + count);
 }
 
 PyObject *rmsnorm_fwd(Args a)

@@ -127,3 +127,17 @@ def test_fork_takes_parents_and_states_with_further_dimensions(m):
     for got in (m.mamba_state_fork(conv, ssm, parent), m.mamba_state_fork(conv, ssm, parent[:, None]),
                 m.mamba_state_fork(conv[..., None], ssm[..., None], parent)):
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+@pytest.mark.gpu
+def test_linear_returns_every_output_that_is_there(m):
+    """An output of no width may be None among the given ones: the others are returned."""
+    x = torch.randn(5, 16, device="cuda:0").to(BF16)
+    w = torch.randn(24, 16, device="cuda:0").to(BF16)
+    a, c = m.mamba_linear_fwd(x, w, splits=[8, 16])
+    new = lambda n: torch.empty(5, n, dtype=BF16, device="cuda:0")
+    for splits, outs in (([8, 0, 16], [new(8), None, new(16)]), ([0, 8, 16], [None, new(8), new(16)])):
+        got = m.mamba_linear_fwd(x, w, splits=splits, outs=outs)
+        assert len(got) == 2 and torch.equal(got[0], a) and torch.equal(got[1], c)
+    (whole,) = m.mamba_linear_fwd(x, w, splits=[0, 24], outs=[None, new(24)])
+    assert torch.equal(whole, torch.cat([a, c], 1))
