@@ -282,7 +282,7 @@ PyObject *state_step(Args a)
     Out h_out(a[10]), out(a[11]);
     const at::Tensor &xt = tensor(x, "x");
     const auto s = sizes(h_in, "h_in", 3);
-    const int64_t n_in = s[0], D = s[1], N = s[2], n_out = xt.sizes().empty() ? 0 : xt.sizes()[0];
+    const int64_t n_in = s[0], D = s[1], N = s[2], n_out = sizes(x, "x", 1, true)[0];
     const int io = io_code(xt);
     const auto type = xt.scalar_type();
     h_out.unless_given(xt, {n_out, D, N}, at::kFloat);
@@ -302,7 +302,7 @@ PyObject *conv_state_step(Args a)
     Out h_out(a[13]), conv_out(a[14]), out(a[15]), xc(a[16]);
     const at::Tensor &xt = tensor(x, "x");
     const auto s = sizes(h_in, "h_in", 3);
-    const int64_t n_in = s[0], D = s[1], N = s[2], n_out = xt.sizes().empty() ? 0 : xt.sizes()[0], K = sizes(conv_w, "conv_w", 2)[1];
+    const int64_t n_in = s[0], D = s[1], N = s[2], n_out = sizes(x, "x", 1, true)[0], K = sizes(conv_w, "conv_w", 2)[1];
     const int io = io_code(xt);
     const auto type = xt.scalar_type();
     h_out.unless_given(xt, {n_out, D, N}, at::kFloat);
@@ -422,8 +422,7 @@ PyObject *block_step(Args a)   // address of the parameters, hidden, conv_src, s
     Out conv_dst(a[5]), ssm_dst(a[6]), hidden_out(a[7]);
     const at::Tensor &ht = tensor(hidden, "hidden");
     const auto s = sizes(hidden, "hidden", 2);
-    const at::IntArrayRef cs = tensor(conv_src, "conv_src").sizes();
-    const int64_t n_out = s[0], dm = s[1], n_in = cs.empty() ? 0 : cs[0], D = p->d_inner, N = p->d_state, K = p->d_conv;
+    const int64_t n_out = s[0], dm = s[1], n_in = sizes(conv_src, "conv_src", 1, true)[0], D = p->d_inner, N = p->d_state, K = p->d_conv;
     hidden_out.unless_given(ht, s, ht.scalar_type());
     if (parent == Py_None) {
         conv_dst.object = conv_src;
@@ -449,8 +448,7 @@ PyObject *embedding_fwd(Args a)
     Out out(a[2]);
     const at::Tensor &tt = tensor(table, "table");
     const auto ts = sizes(table, "table", 2);
-    const at::IntArrayRef ks = tensor(tokens, "tokens").sizes();
-    const int64_t M = ks.empty() ? 0 : ks[0], V = ts[0], dm = ts[1];
+    const int64_t M = sizes(tokens, "tokens", 1, true)[0], V = ts[0], dm = ts[1];
     out.unless_given(tt, {M, dm}, tt.scalar_type());
     Call{"mamba_embedding_fwd", api.embedding_fwd, static_cast<const int32_t *>(ptr(tokens, at::kInt, {M}, "tokens")), ptr(table, "table"),
          ptr(out.object, tt.scalar_type(), {M, dm}, "out"), M, V, dm, io_code(tt), stream_of(a[3])};
@@ -498,7 +496,7 @@ PyObject *ssd_step(Args a)
     Out h_out(a[10]), out(a[11]);
     const at::Tensor &xt = tensor(x, "x");
     const auto s = sizes(h_in, "h_in", 4);
-    const int64_t n_in = s[0], H = s[1], P = s[2], N = s[3], n_out = xt.sizes().empty() ? 0 : xt.sizes()[0];
+    const int64_t n_in = s[0], H = s[1], P = s[2], N = s[3], n_out = sizes(x, "x", 1, true)[0];
     const auto type = xt.scalar_type();
     h_out.unless_given(xt, {n_out, H, P, N}, at::kFloat);
     out.unless_given(xt, xt.sizes(), type);

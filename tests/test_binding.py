@@ -141,3 +141,15 @@ def test_linear_returns_every_output_that_is_there(m):
         assert len(got) == 2 and torch.equal(got[0], a) and torch.equal(got[1], c)
     (whole,) = m.mamba_linear_fwd(x, w, splits=[0, 24], outs=[None, new(24)])
     assert torch.equal(whole, torch.cat([a, c], 1))
+
+
+def test_a_tensor_without_dimensions_is_no_empty_batch(m):
+    """What gives the number of rows has to have rows: a scalar is refused, not taken for none of them."""
+    z = torch.zeros
+    for call in (lambda: m.mamba_state_step(z(2, 16, 4), z(()), z(0, 16), z(16, 4), z(0, 4), z(0, 4)),
+                 lambda: m.mamba_conv_state_step(z(2, 16, 4), z(2, 16, 3), z(()), z(16, 4), None, z(0, 16), z(16, 4), z(0, 4), z(0, 4)),
+                 lambda: m.mamba2_state_step(z(2, 1, 64, 64), z(()), z(0, 1), z(1), z(0, 64), z(0, 64)),
+                 lambda: m.mamba_embedding_fwd(z((), dtype=I32), z(5, 8, dtype=BF16)),
+                 lambda: m.mamba_state_fork(z(1, 2, 16, 3), None, z((), dtype=I32))):
+        with pytest.raises(ValueError, match="must have at least 1 dimensions, got 0"):
+            call()
