@@ -202,7 +202,9 @@ def mamba_scan_fwd(x, dt, A, Bm, Cm, Dskip=None, z=None, dt_bias=None, h0=None, 
                    stream=None):
     """x, dt, z (B,L,D); Bm, Cm (B,L,N); A (D,N) f32 -> out (B,L,D), h_final (B,D,N) f32."""
     if stream is not None and workspace is None:
-        workspace = _scratch(mamba_scan_workspace_bytes(*x.shape, A.shape[1], chunk_len), x.device, stream)
+        need = mamba_scan_workspace_bytes(*x.shape, A.shape[1], chunk_len)
+        if need > 0:
+            workspace = _scratch(need, x.device, stream)
     return _marshal.scan_fwd(x, dt, A, Bm, Cm, Dskip, z, dt_bias, h0, out, h_final, workspace, chunk_len, dt_softplus,
                              want_state, stream and stream.cuda_stream)
 

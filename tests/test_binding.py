@@ -153,3 +153,16 @@ def test_a_tensor_without_dimensions_is_no_empty_batch(m):
                  lambda: m.mamba_state_fork(z(1, 2, 16, 3), None, z((), dtype=I32))):
         with pytest.raises(ValueError, match="must have at least 1 dimensions, got 0"):
             call()
+
+
+def test_scan_on_another_stream_allocates_a_workspace_only_where_it_needs_one(m, monkeypatch):
+    made = []
+    monkeypatch.setattr(m, "_scratch", lambda nbytes, device, stream: made.append(nbytes))
+    stream = types.SimpleNamespace(cuda_stream=0)
+    for L, D in ((8, 16), (4096, 256)):
+        x, bc = torch.zeros(1, L, D), torch.zeros(1, L, 16)
+        need = m.mamba_scan_workspace_bytes(1, L, D, 16)
+        assert (need > 0) == (L == 4096)
+        with pytest.raises(ValueError, match="x must live on the GPU"):
+            m.mamba_scan_fwd(x, x, torch.zeros(D, 16), bc, bc, stream=stream)
+        assert made == [need] * (need > 0)
