@@ -172,6 +172,11 @@ def _stream(stream):
     return s.cuda_stream
 
 
+def _raw(stream):
+    """A stream as the native half takes it: the handle, or None for the current one."""
+    return None if stream is None else stream.cuda_stream
+
+
 def _scratch(nbytes, device, stream):
     """A workspace the binding allocates for one call and drops on return.  The caching allocator may hand the
     block to later work on the current stream, so when the call runs on another stream the block is tied to it."""
@@ -185,7 +190,7 @@ def mamba_conv1d_fwd(x, w, bias=None, conv_state_in=None, y=None, conv_state_out
                      apply_silu=True, want_state=True, stream=None):
     """x (B,L,D) f32|bf16, w (D,K) f32 -> y (B,L,D), conv_state_out (B,D,K-1)."""
     return _marshal.conv1d_fwd(x, w, bias, conv_state_in, y, conv_state_out, apply_silu, want_state,
-                               stream and stream.cuda_stream)
+                               _raw(stream))
 
 
 def mamba_scan_workspace_bytes(batch, L, D, N, chunk_len=0) -> int:
@@ -206,7 +211,7 @@ def mamba_scan_fwd(x, dt, A, Bm, Cm, Dskip=None, z=None, dt_bias=None, h0=None, 
         if need > 0:
             workspace = _scratch(need, x.device, stream)
     return _marshal.scan_fwd(x, dt, A, Bm, Cm, Dskip, z, dt_bias, h0, out, h_final, workspace, chunk_len, dt_softplus,
-                             want_state, stream and stream.cuda_stream)
+                             want_state, _raw(stream))
 
 
 MAMBA_SCAN_STATIC_BYTES = 32 << 20
@@ -296,7 +301,7 @@ def mamba_state_step(h_in, x, dt, A, Bm, Cm, Dskip=None, z=None, dt_bias=None, p
     """h_in (n_in,D,N) f32; x, dt, z (n_out,D); Bm, Cm (n_out,N); parent_idx int32[n_out]
     -> h_out (n_out,D,N), out (n_out,D).  Pass h_out=h_in for the in-place sequential step."""
     return _marshal.state_step(h_in, x, dt, A, Bm, Cm, Dskip, z, dt_bias, parent_idx, h_out, out, dt_softplus,
-                               stream and stream.cuda_stream)
+                               _raw(stream))
 
 
 def mamba_conv_state_step(h_in, conv_state_in, x, conv_w, conv_bias, dt, A, Bm, Cm, Dskip=None, z=None,
@@ -307,13 +312,13 @@ def mamba_conv_state_step(h_in, conv_state_in, x, conv_w, conv_bias, dt, A, Bm, 
     -> h_out, conv_state_out (n_out,D,K-1), out (n_out,D), x_c (n_out,D) or None."""
     return _marshal.conv_state_step(h_in, conv_state_in, x, conv_w, conv_bias, dt, A, Bm, Cm, Dskip, z, dt_bias, parent_idx,
                                     h_out, conv_state_out, out, xc_out, want_xc, apply_silu, dt_softplus,
-                                    stream and stream.cuda_stream)
+                                    _raw(stream))
 
 
 def mamba_state_fork(conv_src, ssm_src, parent_idx, conv_dst=None, ssm_dst=None, stream=None):
     """conv_src (n_layers,n_in,D,K-1) f32|bf16 or None, ssm_src (n_layers,n_in,D,N) f32 or None,
     parent_idx int32[n_out] -> gathered copies (n_layers,n_out,...)."""
-    return _marshal.state_fork(conv_src, ssm_src, parent_idx, conv_dst, ssm_dst, stream and stream.cuda_stream)
+    return _marshal.state_fork(conv_src, ssm_src, parent_idx, conv_dst, ssm_dst, _raw(stream))
 
 
 def _tree_array(tree):
@@ -345,12 +350,12 @@ def mamba_linear_fwd(x, w, bias=None, residual=None, splits=None, outs=None, str
     widths += [0] * (3 - len(widths))
     o = [None] * 3 if outs is None else list(outs) + [None] * (3 - len(outs))
     return _marshal.linear_fwd(x, w, bias, residual, o[0], widths[0], o[1], widths[1], o[2], widths[2], allocate,
-                               stream and stream.cuda_stream)
+                               _raw(stream))
 
 
 def mamba_rmsnorm_fwd(x, w, eps=1e-5, y=None, stream=None):
     """x (M,C) bf16, w (C) f32 -> x * rsqrt(mean(x^2) + eps) * w."""
-    return _marshal.rmsnorm_fwd(x, w, float(eps), y, stream and stream.cuda_stream)
+    return _marshal.rmsnorm_fwd(x, w, float(eps), y, _raw(stream))
 
 
 class Block:
@@ -400,7 +405,7 @@ def mamba_block_fwd(block: Block, hidden, hidden_out=None, conv_state_in=None, h
     if stream is not None and workspace is None:
         workspace = _scratch(mamba_block_workspace_bytes(block, *hidden.shape[:2]), hidden.device, stream)
     return _marshal.block_fwd(ctypes.addressof(block.c), hidden, hidden_out, conv_state_in, h0, conv_state_out, h_final,
-                              workspace, want_state, stream and stream.cuda_stream)
+                              workspace, want_state, _raw(stream))
 
 
 def mamba_block_step(block: Block, hidden, conv_src, ssm_src, parent_idx=None, conv_dst=None, ssm_dst=None,
@@ -410,19 +415,19 @@ def mamba_block_step(block: Block, hidden, conv_src, ssm_src, parent_idx=None, c
     if stream is not None and workspace is None:
         workspace = _scratch(mamba_block_workspace_bytes(block, hidden.shape[0], 1), hidden.device, stream)
     return _marshal.block_step(ctypes.addressof(block.c), hidden, conv_src, ssm_src, parent_idx, conv_dst, ssm_dst, hidden_out,
-                               workspace, stream and stream.cuda_stream)
+                               workspace, _raw(stream))
 
 
 def mamba_embedding_fwd(tokens, table, out=None, stream=None):
     """tokens int32[M], table (V,dm) bf16 -> (M,dm) rows."""
-    return _marshal.embedding_fwd(tokens, table, out, stream and stream.cuda_stream)
+    return _marshal.embedding_fwd(tokens, table, out, _raw(stream))
 
 
 def mamba_topk_fwd(logits, k, idx=None, val=None, stream=None):
     """logits (M,V) bf16 -> idx int32 (M,k), val float32 (M,k), largest first, ties to the lower index."""
     if idx is not None and val is not None and k == int(k):
         k = int(k)                                       # (where the outputs are given, any number that equals their width)
-    return _marshal.topk_fwd(logits, k, idx, val, stream and stream.cuda_stream)
+    return _marshal.topk_fwd(logits, k, idx, val, _raw(stream))
 
 
 def mamba2_ssd_workspace_bytes(batch, L, H, P, N) -> int:
@@ -436,11 +441,11 @@ def mamba2_ssd_fwd(x, dt, A, Bm, Cm, Dskip=None, z=None, dt_bias=None, h0=None, 
     if stream is not None and workspace is None:
         workspace = _scratch(mamba2_ssd_workspace_bytes(*x.shape, Bm.shape[-1]), x.device, stream)
     return _marshal.ssd_fwd(x, dt, A, Bm, Cm, Dskip, z, dt_bias, h0, out, h_final, workspace, want_state, dt_softplus,
-                            stream and stream.cuda_stream)
+                            _raw(stream))
 
 
 def mamba2_state_step(h_in, x, dt, A, Bm, Cm, Dskip=None, z=None, dt_bias=None, parent_idx=None, h_out=None, out=None,
                       dt_softplus=True, stream=None):
     """h_in (n_in,H,P,N) f32; x, z (n_out,H,P); dt (n_out,H); Bm, Cm (n_out,N) -> h_out (n_out,H,P,N), out (n_out,H,P)."""
     return _marshal.ssd_step(h_in, x, dt, A, Bm, Cm, Dskip, z, dt_bias, parent_idx, h_out, out, dt_softplus,
-                             stream and stream.cuda_stream)
+                             _raw(stream))

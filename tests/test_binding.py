@@ -166,3 +166,15 @@ def test_scan_on_another_stream_allocates_a_workspace_only_where_it_needs_one(m,
         with pytest.raises(ValueError, match="x must live on the GPU"):
             m.mamba_scan_fwd(x, x, torch.zeros(D, 16), bc, bc, stream=stream)
         assert made == [need] * (need > 0)
+
+
+def test_a_stream_is_a_stream_whatever_its_truth(m, monkeypatch):
+    """Only None stands for the current stream; an object that happens to be false is not one."""
+    monkeypatch.setattr(m, "_marshal", types.SimpleNamespace(conv1d_fwd=lambda *a: a[-1]))
+
+    class Empty(types.SimpleNamespace):
+        def __len__(self):
+            return 0
+    assert m.mamba_conv1d_fwd(None, None, stream=Empty(cuda_stream=7)) == 7 and m.mamba_conv1d_fwd(None, None) is None
+    with pytest.raises(AttributeError):
+        m.mamba_conv1d_fwd(None, None, stream=0)
