@@ -29,7 +29,12 @@ if not os.path.exists(LIB_PATH):
         "libmamba_hip.so is missing: build it with `python -m paper_2506_01206_amd.build` "
         "(there is no CPU or PyTorch fallback for the kernels)")
 
-from . import _marshal  # noqa: E402  (built next to the library)
+try:
+    from . import _marshal  # noqa: E402  (built next to the library)
+except ImportError as e:
+    raise ImportError(
+        "the marshalling module beside libmamba_hip.so does not load: build it with `python -m paper_2506_01206_amd.build` "
+        "(%s)" % e) from e
 
 _vp, _i64, _int, _sz = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_size_t
 

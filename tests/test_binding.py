@@ -1,7 +1,9 @@
 """The Python binding: argument checks, and that what is refused is refused before anything is launched.  Without a GPU every
 call ends in a check, and the checks are reached in the order of the arguments; what takes device tensors is marked gpu."""
 import ctypes
+import importlib
 import os
+import shutil
 import types
 
 import numpy as np
@@ -178,3 +180,15 @@ def test_a_stream_is_a_stream_whatever_its_truth(m, monkeypatch):
     assert m.mamba_conv1d_fwd(None, None, stream=Empty(cuda_stream=7)) == 7 and m.mamba_conv1d_fwd(None, None) is None
     with pytest.raises(AttributeError):
         m.mamba_conv1d_fwd(None, None, stream=0)
+
+
+def test_binding_without_the_marshalling_module_says_how_to_build_it(tmp_path, monkeypatch):
+    package = tmp_path / "half_built"
+    package.mkdir()
+    (package / "__init__.py").write_text("")
+    (package / "libmamba_hip.so").write_bytes(b"")
+    shutil.copy(os.path.join(ROOT, "paper_2506_01206_amd", "binding.py"), package / "binding.py")
+    monkeypatch.delenv("MAMBA_HIP_LIB", raising=False)
+    monkeypatch.syspath_prepend(str(tmp_path))
+    with pytest.raises(ImportError, match="python -m paper_2506_01206_amd.build"):
+        importlib.import_module("half_built.binding")
