@@ -11,12 +11,13 @@ fallback: if the library has not been built, importing this module raises.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
-# MAMBA_HIP_LIB names another build of the same library (the host-sanitizer run loads an instrumented one)
+# MAMBA_HIP_LIB and MAMBA_HIP_MARSHAL name other builds of the same library and module (the host-sanitizer run loads instrumented ones)
 LIB_PATH = os.environ.get("MAMBA_HIP_LIB") or os.path.join(_HERE, "libmamba_hip.so")
 
 MAMBA_F32 = 0
@@ -30,7 +31,12 @@ if not os.path.exists(LIB_PATH):
         "(there is no CPU or PyTorch fallback for the kernels)")
 
 try:
-    from . import _marshal  # noqa: E402  (built next to the library)
+    if os.environ.get("MAMBA_HIP_MARSHAL"):
+        _spec = importlib.util.spec_from_file_location(__package__ + "._marshal", os.environ["MAMBA_HIP_MARSHAL"])
+        _marshal = importlib.util.module_from_spec(_spec)
+        _spec.loader.exec_module(_marshal)
+    else:
+        from . import _marshal  # noqa: E402  (built next to the library)
 except ImportError as e:
     raise ImportError(
         "the marshalling module beside libmamba_hip.so does not load: build it with `python -m paper_2506_01206_amd.build` "

@@ -34,18 +34,21 @@ def _compile(src: str) -> str:
     return obj
 
 
-def _build_marshal() -> None:
-    """The native half of binding.py: host code against torch's C++ headers (device memory and streams only)."""
+def marshal_command(out: str, compiler: str, flags=("-O2", "-Wall")) -> list:
+    """How the native half of binding.py is compiled: host code against torch's C++ headers (device memory and streams only)."""
     import torch
     root = os.path.dirname(torch.__file__)
+    return ([compiler, *flags, "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+             "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
+            + ["-isystem" + d for d in (os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                                        sysconfig.get_paths()["include"], os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"))]
+            + [os.path.join(CSRC, "marshal.cpp"), "-o", out, "-L" + os.path.join(root, "lib")]
+            + ["-l" + n for n in ("torch_python", "torch_cpu", "torch", "c10", "c10_hip")])
+
+
+def _build_marshal() -> None:
     tmp = MARSHAL + ".tmp%d" % os.getpid()
-    subprocess.check_call(
-        [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-         "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
-        + ["-isystem" + d for d in (os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
-                                    sysconfig.get_paths()["include"], os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"))]
-        + [os.path.join(CSRC, "marshal.cpp"), "-o", tmp, "-L" + os.path.join(root, "lib")]
-        + ["-l" + n for n in ("torch_python", "torch_cpu", "torch", "c10", "c10_hip")])
+    subprocess.check_call(marshal_command(tmp, os.environ.get("CXX", "g++")))
     os.replace(tmp, MARSHAL)
 
 

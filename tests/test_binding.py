@@ -1,9 +1,11 @@
 """The Python binding: argument checks, and that what is refused is refused before anything is launched.  Without a GPU every
 call ends in a check, and the checks are reached in the order of the arguments; what takes device tensors is marked gpu."""
 import ctypes
+import gc
 import importlib
 import os
 import shutil
+import sys
 import types
 
 import numpy as np
@@ -188,7 +190,65 @@ def test_binding_without_the_marshalling_module_says_how_to_build_it(tmp_path, m
     (package / "__init__.py").write_text("")
     (package / "libmamba_hip.so").write_bytes(b"")
     shutil.copy(os.path.join(ROOT, "paper_2506_01206_amd", "binding.py"), package / "binding.py")
-    monkeypatch.delenv("MAMBA_HIP_LIB", raising=False)
+    for name in ("MAMBA_HIP_LIB", "MAMBA_HIP_MARSHAL"):
+        monkeypatch.delenv(name, raising=False)
     monkeypatch.syspath_prepend(str(tmp_path))
     with pytest.raises(ImportError, match="python -m paper_2506_01206_amd.build"):
         importlib.import_module("half_built.binding")
+
+
+@pytest.mark.parametrize("name", ["mamba_conv1d_fwd", "mamba_scan_fwd", "mamba_linear_fwd", "mamba_rmsnorm_fwd", "mamba_topk_fwd", "mamba2_ssd_fwd"])
+def test_what_is_no_tensor_or_has_another_rank_is_refused(m, name):
+    z, call = torch.zeros, getattr(m, name)
+    args = dict(mamba_conv1d_fwd=(z(16, 4),), mamba_scan_fwd=(z(1, 8, 16), z(16, 4), z(1, 8, 4), z(1, 8, 4)), mamba_linear_fwd=(z(24, 16),),
+                mamba_rmsnorm_fwd=(z(16),), mamba_topk_fwd=(4,), mamba2_ssd_fwd=(z(1, 8, 2), z(2), z(1, 8, 64), z(1, 8, 64)))[name]
+    for no_tensor in (None, 3, "x", [1.0], np.zeros((1, 8, 16), np.float32)):
+        with pytest.raises(TypeError, match="must be a tensor"):
+            call(no_tensor, *args)
+    for shape in ((), (4,), (1, 2, 3, 4, 5)):
+        with pytest.raises(ValueError, match="must have . dimensions, got %d" % len(shape)):
+            call(z(*shape) if shape else z(()), *args)
+    if name == "mamba_scan_fwd":
+        for chunk_len in (4.0, "4", None, 1 << 70):
+            with pytest.raises((TypeError, OverflowError)):
+                call(z(1, 8, 16), *args, chunk_len=chunk_len)
+
+
+def test_native_entries_take_exactly_their_arguments(m):
+    """By position, all of them: one more or one less is an error, and so is a bind without the addresses."""
+    counts = dict(conv1d_fwd=9, scan_fwd=16, state_step=14, conv_state_step=21, state_fork=6, linear_fwd=12, rmsnorm_fwd=5, block_fwd=10,
+                  block_step=10, embedding_fwd=4, topk_fwd=5, ssd_fwd=15, ssd_step=14)
+    assert set(counts) == {n for n in dir(m._marshal) if not n.startswith("_")} - {"bind"}
+    for name, n in counts.items():
+        for args in ((), (None,) * (n - 1), (None,) * (n + 1)):
+            with pytest.raises(TypeError, match="%d arguments expected, got %d" % (n, len(args))):
+                getattr(m._marshal, name)(*args)
+    for args in ((), (m.MambaError, torch.OutOfMemoryError), (m.MambaError, torch.OutOfMemoryError) + ("no address",) * 16):
+        with pytest.raises(TypeError):
+            m._marshal.bind(*args)
+
+
+def test_an_output_that_cannot_be_allocated_raises(m):
+    """Errors of torch's allocation come out as torch's own: negative sizes, more memory than there is."""
+    x = torch.zeros(1, 8, 16)
+    with pytest.raises(RuntimeError):
+        m.mamba_conv1d_fwd(x, torch.zeros(16, 0))
+    with pytest.raises(RuntimeError):
+        m.mamba_topk_fwd(torch.zeros(2, 8, dtype=BF16), 1 << 61)      # (the bytes overflow)
+
+
+def test_no_references_are_lost_or_kept(m):
+    """Outputs that were allocated before a check failed are given back, and the arguments are only borrowed."""
+    x, w, y = torch.zeros(1, 8, 16), torch.zeros(16, 4), torch.zeros(1, 8, 16)
+
+    def counts():
+        gc.collect()                                     # (exceptions hold the frames that they came through)
+        return [sys.getrefcount(o) for o in (x, w, y, None)]
+    before = counts()
+    for _ in range(200):
+        for out, want_state in ((None, True), (y, True), (y, False)):
+            with pytest.raises(ValueError):
+                m.mamba_conv1d_fwd(x, w, y=out, want_state=want_state)
+    del out
+    after = counts()
+    assert before[:3] == after[:3] and abs(after[3] - before[3]) < 100
