@@ -575,7 +575,8 @@ int mamba_block_fwd(const mamba_block_params_t *p, const void *hidden, void *hid
     // x_c = silu(conv1d(x))                                 -> c
     if ((rc = mamba_conv1d_fwd(bb.a, p->conv_w, p->conv_b, conv_state_in, bb.c, conv_state_out, batch, L, Di, p->d_conv, 1, io, hip_stream))) return rc;
     // [dt_low | B | C] = x_c W_x^T,  dt = dt_low W_dt^T       -> a (x is dead)
-    if (xdt_applies(rows, Di, R, N)) {
+    unsigned groups;
+    if (xdt_plan(rows, Di, R, N, &groups) > 0) {
         const int64_t xw = (R + 2 * N) * Di * 2, low = rows * R * 2, bc = rows * N * 2;   // (sizes that block_layout has checked)
         if (overlap(bb.dtl, low, p->x_proj_w, xw) || overlap(bb.bm, bc, p->x_proj_w, xw) || overlap(bb.cm, bc, p->x_proj_w, xw) ||
             overlap(bb.a, rows * Di * 2, p->dt_proj_w, Di * R * 2))

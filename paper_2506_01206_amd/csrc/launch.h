@@ -188,8 +188,7 @@ struct XdtArgs {
     void *dtl, *bm, *cm, *dt;
     int64_t M, d_inner, dt_rank;
 };
-bool xdt_applies(int64_t M, int64_t d_inner, int64_t dt_rank, int64_t N);   // shapes it is built for and faster on than two launches
-hipError_t launch_xdt(const XdtArgs &a, hipStream_t stream);
+hipError_t launch_xdt(const XdtArgs &a, hipStream_t stream);                // for shapes that xdt_plan (routes.h) has rows for
 
 struct NormArgs {
     const void *x;           // (M, C) bf16

@@ -30,4 +30,43 @@ inline bool linear_few_fits(int64_t N, int64_t K)
     return K <= (int64_t)INT32_MAX - 63 && N <= ((int64_t)1 << 27) - 16;
 }
 
+// x_proj and dt_proj in one kernel (xdt.hip): rows per workgroup and column groups for M rows; 0 rows: two launches.
+// Every workgroup reads all weights, so what counts is the number of rounds on 256 CUs times what a workgroup takes (us in
+// xdt.hip, in a full round).  One round of 16 rows: column groups as long as they fit the chip beside each other (24-block
+// prefill of 1024 tokens with 1, 2, 3 groups 1507, 1486, 1466 us; of 2000 tokens, where only two fit, 2016, 2001, 2104).
+// The two launches take 9 us + 2.05 ns a row at 1536 channels, and the gap between them.
+// With few rows there are too few workgroups for the weights to stream through, the fewer the more weights there are.  us of a
+// block (d_inner, dt_rank) in a chain of eight to 24 different ones, two launches / one:
+//   rows    512, 32      1024, 32      1536, 48      2048, 64       3072, 48       4096, 64       5120, 64
+//    768   39.7/38.6    48.9/48.0     57.7/58.5     82.4/82.5      86.2/89.8     132.1/139.6    173.8/182.3
+//   1100   48.5/47.0    59.2/58.1     67.5/67.5    101.3/102.0    103.5/105.6    196.1/198.7    251.8/257.5
+//   1700   56.6/55.3    67.5/66.0     80.8/80.2    112.4/112.6    133.2/134.2    230.9/233.6    329.5/331.9
+//   2500   59.9/58.0    78.5/76.4     94.6/95.3    142.5/142.9    156.7/156.3    294.7/296.9    424.6/426.9
+//   3000   62.0/59.6    86.2/83.9    112.3/109.9   156.8/153.0    187.9/181.1    334.0/332.4    439.3/432.7
+//   8000  115.8/112.6  158.6/151.4   228.7/218.1   322.8/310.9    435.2/416.3    775.6/753.2   1097.7/1068.6
+// So from 768 rows up to 1536 channels (500 rows there: 24-block prefill 1146 against 1140 us), from 2700 beyond (2560: 1792,
+// 48 128.1/128.6, 2048, 64 142.1/142.5, 5120, 64 424.7/426.0; 2700: 132.0/132.3, 146.6/146.5, 446.0/445.4).
+constexpr int kXdtStates = 16;
+inline int xdt_plan(int64_t M, int64_t d_inner, int64_t dt_rank, int64_t N, unsigned *groups)
+{
+    *groups = 1;
+    if (N != kXdtStates || (dt_rank != 32 && dt_rank != 48 && dt_rank != 64)) return 0;
+    if (d_inner < 64 || d_inner % 64 != 0 || d_inner > (int64_t)1 << 20) return 0;
+    if (M < (d_inner <= 1536 ? 768 : 2700)) return 0;
+    const int64_t t16 = (M + 15) / 16;
+    if (t16 <= 256) {
+        *groups = (unsigned)(256 / t16 < 3 ? 256 / t16 : 3);
+        return 16;
+    }
+    const double cost[3] = {11.0, 15.0, 23.0};
+    double best = 10.0 + 2.05e-3 * (double)M;
+    int rows = 0;
+    for (int i = 0; i < 3; ++i) {
+        if (i == 2 && dt_rank > 48) break;                         // 64 rows and 64 dt columns: more LDS than a CU has
+        const double t = cost[i] * (double)((M + ((int64_t)4096 << i) - 1) / ((int64_t)4096 << i));
+        if (t < best) best = t, rows = 16 << i;
+    }
+    return rows;
+}
+
 }  // namespace mamba

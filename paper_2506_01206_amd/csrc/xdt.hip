@@ -16,6 +16,7 @@
 // us, of 2000 2037 -> 2001, of 4096 3218 -> 3165, of 8000 5376 -> 5130, of 12000 7860 -> 7585.
 #include "device_math.h"
 #include "launch.h"
+#include "routes.h"
 
 namespace mamba {
 namespace {
@@ -26,7 +27,7 @@ typedef float f32x4v __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kNW = 8, kThr = 64 * kNW;
-constexpr int kStates = 16;
+constexpr int kStates = kXdtStates;
 
 __device__ __forceinline__ void wave_sync()
 {
@@ -217,43 +218,10 @@ xdt_kernel(const bf16_t *__restrict__ xc, const bf16_t *__restrict__ wx, const b
 
 }  // namespace
 
-// Rows per workgroup and column groups for M rows; 0 rows: two launches are as fast.  Every workgroup reads all weights, so
-// what counts is the number of rounds on 256 CUs times what a workgroup takes (us above, in a full round).  One round of 16
-// rows: column groups as long as they fit the chip beside each other (24-block prefill of 1024 tokens with 1, 2, 3 groups
-// 1507, 1486, 1466 us; of 2000 tokens, where only two fit, 2016, 2001, 2104).  Under 768 rows there are too few workgroups for
-// the weights to stream through (500 tokens 1146 against 1140 us, 900 tokens 1438 against 1463).  The two launches take 9 us + 2.05 ns
-// a row and the gap between them.
-static int xdt_plan(int64_t M, int64_t dt_rank, unsigned *groups)
-{
-    *groups = 1;
-    if (M < 768) return 0;
-    const int64_t t16 = (M + 15) / 16;
-    if (t16 <= 256) {
-        *groups = (unsigned)(256 / t16 < 3 ? 256 / t16 : 3);
-        return 16;
-    }
-    const double cost[3] = {11.0, 15.0, 23.0};
-    double best = 10.0 + 2.05e-3 * (double)M;
-    int rows = 0;
-    for (int i = 0; i < 3; ++i) {
-        if (i == 2 && dt_rank > 48) break;                         // 64 rows and 64 dt columns: more LDS than a CU has
-        const double t = cost[i] * (double)((M + ((int64_t)4096 << i) - 1) / ((int64_t)4096 << i));
-        if (t < best) best = t, rows = 16 << i;
-    }
-    return rows;
-}
-
-bool xdt_applies(int64_t M, int64_t d_inner, int64_t dt_rank, int64_t N)
-{
-    unsigned groups;
-    return N == kStates && (dt_rank == 32 || dt_rank == 48 || dt_rank == 64) && d_inner >= 64 && d_inner % 64 == 0 &&
-           d_inner <= (int64_t)1 << 20 && xdt_plan(M, dt_rank, &groups) > 0;
-}
-
 hipError_t launch_xdt(const XdtArgs &a, hipStream_t stream)
 {
     unsigned groups;
-    const int rows = xdt_plan(a.M, a.dt_rank, &groups);
+    const int rows = xdt_plan(a.M, a.d_inner, a.dt_rank, kStates, &groups);
     const unsigned blocks = rows ? (unsigned)((a.M + rows - 1) / rows) : 0u;
 #define MAMBA_XDT(KS, MT)                                                                                                          \
     xdt_kernel<KS, MT><<<dim3(blocks, groups), kThr, 0, stream>>>(                                                                \

@@ -12,6 +12,8 @@ SHIM = """
 extern "C" int folds(int n_seg1, int before, uintptr_t h0, uintptr_t h_final, int64_t bytes)
 { return mamba::ssd_folds(n_seg1, before, (const void *)h0, (const void *)h_final, bytes); }
 extern "C" int few_fits(int64_t N, int64_t K) { return mamba::linear_few_fits(N, K); }
+extern "C" int xdt(int64_t M, int64_t d_inner, int64_t dt_rank, int64_t N, unsigned *groups)
+{ return mamba::xdt_plan(M, d_inner, dt_rank, N, groups); }
 """
 
 
@@ -25,6 +27,7 @@ def routes(tmp_path_factory):
     i32, i64, ptr = ctypes.c_int, ctypes.c_int64, ctypes.c_size_t
     lib.folds.argtypes = [i32, i32, ptr, ptr, i64]
     lib.few_fits.argtypes = [i64, i64]
+    lib.xdt.argtypes = [i64, i64, i64, i64, ctypes.POINTER(ctypes.c_uint)]
     return lib
 
 
@@ -47,3 +50,19 @@ def test_few_row_product_leaves_what_32_bits_do_not_count_to_others(routes):
         assert not routes.few_fits(1, K), K
     assert routes.few_fits(1 << 26, 768) and (((1 << 27) - 16) // 16) * 512 < 1 << 32
     assert routes.few_fits((1 << 27) - 16, 768) and not routes.few_fits(1 << 27, 768) and not routes.few_fits(1 << 31, 8)
+
+
+def test_wide_blocks_of_few_rows_keep_the_two_projections_apart(routes):
+    """x_proj and dt_proj in one kernel: from 768 rows up to 1536 channels, from 2700 beyond; only the sizes it is built for."""
+    g = ctypes.c_uint()
+    rows = lambda M, d_inner=1536, dt_rank=48, N=16: routes.xdt(M, d_inner, dt_rank, N, g)
+    for d_inner, dt_rank in ((64, 32), (512, 32), (1024, 32), (1536, 48), (1536, 64)):
+        assert rows(767, d_inner, dt_rank) == 0 and rows(768, d_inner, dt_rank) == 16 and g.value == 3
+    for d_inner, dt_rank in ((1600, 48), (2048, 64), (3072, 48), (4096, 64), (5120, 64), (1 << 20, 64)):
+        for M in (768, 1100, 2000, 2699):
+            assert rows(M, d_inner, dt_rank) == 0, (M, d_inner)
+        assert rows(2700, d_inner, dt_rank) == 16 and g.value == 1
+    assert rows(1361) == 16 and g.value == 2 and rows(4096) == 16 and rows(4097) == 32 and rows(8193) == 64
+    assert rows(8192, 64, 32) == 32 and rows(8193, dt_rank=64) != 64
+    for kw in (dict(N=8), dict(N=32), dict(dt_rank=40), dict(dt_rank=96), dict(d_inner=1568), dict(d_inner=32), dict(d_inner=1 << 21)):
+        assert rows(8000, **kw) == 0
