@@ -908,9 +908,11 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
         // the way into a block at a draft position: norm and conv come together, the next projection only with them
         if (!linear_few_fits(N, a.K) || !a.conv_w || !a.conv_src || !a.conv_dst || a.conv_k < 2 || (a.xproj_w && (!a.xproj_part || a.width[0] % 16)))
             return hipErrorInvalidValue;
-        if (tiles(16, 16) <= kTilesResident) MAMBA_FEW_K(1, true, 32);
-        else if (tiles(32, 16) <= kTilesResident) MAMBA_FEW_K(2, true, 32);
-        else MAMBA_FEW_K(4, true, 32);
+        switch (linear_few_row_tiles(a.M, N)) {
+        case 1: MAMBA_FEW_K(1, true, 32); break;
+        case 2: MAMBA_FEW_K(2, true, 32); break;
+        default: MAMBA_FEW_K(4, true, 32); break;
+        }
         return hipGetLastError();
     }
     // Few output tiles: latency decides, and the tiles are kept so small that they just fill the CUs once (a second
@@ -938,7 +940,14 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     }
     // what is left of the few rows, except for very wide outputs (the LM head), where the tiled kernel's shared x tile
     // reads less
-    if (few && a.M <= 64 && N < 8192) { MAMBA_FEW_K(4, false, 32); return hipGetLastError(); }
+    if (few && a.M <= 64 && N < 8192) {
+        switch (linear_few_row_tiles(a.M, N)) {
+        case 1: MAMBA_FEW(1); break;
+        case 2: MAMBA_FEW(2); break;
+        default: MAMBA_FEW_K(4, false, 32); break;
+        }
+        return hipGetLastError();
+    }
 #undef MAMBA_FEW
 #undef MAMBA_FEW_K
     if (vec && N % 128 == 0 && a.M >= 128 && a.K % (2 * kWideBK) == 0) {

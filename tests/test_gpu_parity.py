@@ -1396,6 +1396,14 @@ def test_block_step_more_branches(m, n, dm, D, N, K, R):
     assert_close(values(to_host(g_conv)), r_conv, tol, "block step conv")
 
 
+@pytest.mark.parametrize("n,dm,D,N,K,R", [(5, 64, 2112, 16, 4, 48), (20, 64, 2112, 16, 4, 48), (40, 64, 2112, 16, 4, 48),
+                                          (3, 2560, 5120, 16, 4, 160), (2, 64, 8208, 16, 2, 192), (17, 40, 4112, 4, 3, 8)])
+def test_block_step_of_wide_models(m, n, dm, D, N, K, R):
+    """More column blocks of in_proj than CUs, with every number of row tiles, and more partial sums of the x projection
+    than the step has in flight at a time (up to 513 parts), in numbers that do not divide evenly."""
+    test_block_step_more_branches(m, n, dm, D, N, K, R)
+
+
 def test_block_step_bad_parent_poisons_only_that_branch(m):
     """A parent index outside the source cache cannot be honoured: that branch's states and hidden row
     come back NaN (never an out-of-bounds read), the other branches are untouched by it."""

@@ -12,6 +12,7 @@ SHIM = """
 extern "C" int folds(int n_seg1, int before, uintptr_t h0, uintptr_t h_final, int64_t bytes)
 { return mamba::ssd_folds(n_seg1, before, (const void *)h0, (const void *)h_final, bytes); }
 extern "C" int few_fits(int64_t N, int64_t K) { return mamba::linear_few_fits(N, K); }
+extern "C" int row_tiles(int64_t M, int64_t N) { return mamba::linear_few_row_tiles(M, N); }
 extern "C" int xdt(int64_t M, int64_t d_inner, int64_t dt_rank, int64_t N, unsigned *groups)
 { return mamba::xdt_plan(M, d_inner, dt_rank, N, groups); }
 """
@@ -27,6 +28,7 @@ def routes(tmp_path_factory):
     i32, i64, ptr = ctypes.c_int, ctypes.c_int64, ctypes.c_size_t
     lib.folds.argtypes = [i32, i32, ptr, ptr, i64]
     lib.few_fits.argtypes = [i64, i64]
+    lib.row_tiles.argtypes = [i64, i64]
     lib.xdt.argtypes = [i64, i64, i64, i64, ctypes.POINTER(ctypes.c_uint)]
     return lib
 
@@ -66,3 +68,13 @@ def test_wide_blocks_of_few_rows_keep_the_two_projections_apart(routes):
     assert rows(8192, 64, 32) == 32 and rows(8193, dt_rank=64) != 64
     for kw in (dict(N=8), dict(N=32), dict(dt_rank=40), dict(dt_rank=96), dict(d_inner=1568), dict(d_inner=32), dict(d_inner=1 << 21)):
         assert rows(8000, **kw) == 0
+
+
+def test_few_row_product_forms_no_more_row_tiles_than_there_are_rows(routes):
+    """One round of workgroups where that is possible, and never twice the row tiles of 16 that the rows need."""
+    assert [routes.row_tiles(M, 3072) for M in (1, 16, 17, 32, 33, 48, 64)] == [1, 1, 2, 2, 4, 4, 4]
+    assert [routes.row_tiles(M, 1024) for M in (16, 17, 64)] == [1, 1, 1] and routes.row_tiles(64, 2048) == 2
+    for N in (16, 3072, 4096, 4112, 6144, 8184, 10240, 1 << 20):
+        for M in range(1, 65):
+            tiles = routes.row_tiles(M, N)
+            assert tiles in (1, 2, 4) and (tiles == 1 or 16 * tiles < 2 * 16 * -(-M // 16)), (M, N)
