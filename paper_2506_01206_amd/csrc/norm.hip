@@ -3,8 +3,10 @@
 // One wavefront per token row, the row and its weights kept in registers between the reduction and the scaling so that
 // everything is read once and in one trip to memory.  A lane takes four adjacent features at a time: its weights are then
 // 16 bytes next to its neighbour's 16.  (With eight features, 16 bytes of the row, the weights come in 16-byte pieces 32
-// bytes apart, and the address path takes a cycle per lane for those, three times what the row itself takes.)  8000 x 768
-// 7.7 -> 6.5 us, 333 x 768 3.2 -> 2.9 us.
+// bytes apart, and the address path takes a cycle per lane for those, three times what the row itself takes.)  Launches one
+// after the other: 8000 x 768 7.2 -> 6.2 us, 333 x 768 3.6 -> 3.4 us.  The kernel is instantiated for the row's own length:
+// registers for a longer one keep wavefronts off the CU (8000 x 2560 with room for 4096 features 17.3 us, its own 15.6,
+// 2000 x 2560 5.97 and 5.71; 8000 x 1280 with room for 2048 9.4 and 8.7).
 #include "device_math.h"
 #include "launch.h"
 
@@ -13,6 +15,7 @@ namespace {
 
 constexpr int kWave = 64;
 constexpr int kRowsPerBlock = 4;
+
 __device__ __forceinline__ float wave_sum(float v)
 {
 #pragma unroll
@@ -63,20 +66,22 @@ rmsnorm_kernel(const bf16_t *__restrict__ x, const float *__restrict__ w, bf16_t
     }
 }
 
+// the instantiation that holds just the row: NV = ceil(C / 256), 1 to 16
+template <int NV> void launch_norm(const NormArgs &a, unsigned blocks, hipStream_t stream)
+{
+    if constexpr (NV < 16) {
+        if (a.C > 4 * kWave * NV) return launch_norm<NV + 1>(a, blocks, stream);
+    }
+    rmsnorm_kernel<NV><<<blocks, kWave * kRowsPerBlock, 0, stream>>>(static_cast<const bf16_t *>(a.x), a.w, static_cast<bf16_t *>(a.y),
+                                                                     a.M, (int)a.C, a.eps);
+}
+
 }  // namespace
 
 hipError_t launch_rmsnorm(const NormArgs &a, hipStream_t stream)
 {
     const unsigned blocks = (unsigned)((a.M + kRowsPerBlock - 1) / kRowsPerBlock);
-    const int64_t need = (a.C + 4 * kWave - 1) / (4 * kWave);    // C <= 4096: at most 16
-#define MAMBA_LAUNCH_NORM(NV) rmsnorm_kernel<NV><<<blocks, kWave * kRowsPerBlock, 0, stream>>>(static_cast<const bf16_t *>(a.x), a.w, static_cast<bf16_t *>(a.y), a.M, (int)a.C, a.eps)
-    if (need <= 1) MAMBA_LAUNCH_NORM(1);
-    else if (need <= 2) MAMBA_LAUNCH_NORM(2);
-    else if (need <= 3) MAMBA_LAUNCH_NORM(3);
-    else if (need <= 4) MAMBA_LAUNCH_NORM(4);
-    else if (need <= 8) MAMBA_LAUNCH_NORM(8);
-    else MAMBA_LAUNCH_NORM(16);
-#undef MAMBA_LAUNCH_NORM
+    launch_norm<1>(a, blocks, stream);                           // C <= 4096
     return hipGetLastError();
 }
 

@@ -1220,7 +1220,9 @@ def test_linear_wide_tiles_are_deterministic(m):
             assert torch.equal(out, first)
 
 
-@pytest.mark.parametrize("M,C", [(1, 8), (7, 768), (1000, 768), (33, 2048), (5, 4096), (3, 40)])
+@pytest.mark.parametrize("M,C", [(1, 8), (7, 768), (1000, 768), (33, 2048), (5, 4096), (3, 40),
+                                 # both sides of every row length that an instantiation holds
+                                 *[(6, c) for n in range(1, 16) for c in (256 * n, 256 * n + 8)], (9, 4088)])
 def test_rmsnorm_against_oracle(m, M, C):
     rng = np.random.default_rng(M + C)
     x = synth.to_io((rng.standard_normal((M, C)) * rng.uniform(0.01, 30, (M, 1))).astype(np.float32), synth.BF16)
