@@ -10,8 +10,9 @@
 // input element is read once (plus K-1 halo rows per tile) and every wavefront access is a
 // contiguous run.  Loads of the next group of rows are issued before the current group is used.  Groups are short:
 // what is in flight is bounded by wavefronts, and those by registers.  Against tiles of 8 to 32 rows per single wavefront
-// with taps of its own: 64 x 1536 4.3 -> 3.4 us, 2048 x 1536 6.7 -> 5.8, 8000 x 1536 14.9 -> 12.0, 32768 x 1536 46.7 ->
-// 42 us (201 MB, 4.8 TB/s), 15 x 5525 x 544 60 -> 50 us.
+// with taps of its own (bf16, operands from memory): 64 x 1536 4.3 -> 3.4 us, 2048 x 1536 6.7 -> 5.8, 8000 x 1536 14.9 -> 12.0,
+// 32768 x 1536 46.7 -> 42 us (201 MB, 4.8 TB/s), 15 x 5525 x 544 60 -> 50 us.  What gains nothing from it keeps the single
+// wavefronts (launch_conv_k).
 // In tree drafting (Sec. 4.1) a branch starts from the window of its parent: the carried rows can be
 // read through a parent index, which replaces a separate copy of the window.
 #include "device_math.h"
@@ -24,6 +25,7 @@ constexpr int kWave = 64;
 constexpr int kTilesPerBlock = 4;   // wavefronts of a workgroup: consecutive time tiles of the same channels
 constexpr int kBlock = kWave * kTilesPerBlock;
 constexpr int kRows = 2;       // rows loaded together, one group ahead
+constexpr int kRowsWave = 8;   // the same of a wavefront on its own
 
 // orders LDS only: the rows requested ahead of it stay in flight
 __device__ __forceinline__ void lds_barrier_c()
@@ -83,6 +85,87 @@ template <int COUNT> __device__ __forceinline__ void st_block(bf16_t *p, const f
     for (int v = 0; v < COUNT / 8; ++v) pack_row(f + 8 * v, q[v]);
 }
 
+// What a lane keeps while it walks the tokens of its VEC adjacent channels: taps, bias and the K - 1 rows before the next one.
+template <typename T, int VEC, int K, bool SILU> struct ConvLane {
+    typedef typename RowVec<T, VEC>::type row_t;
+    static constexpr int H = K - 1;
+    float wr[VEC][K], br[VEC];
+    float win[H > 0 ? H : 1][VEC];                                  // win[H - 1] is the newest
+    float carried[VEC * (H > 0 ? H : 1)];
+
+    // rows before token 0 come from the carried state, whose (VEC, H) block of this lane is one contiguous run
+    __device__ __forceinline__ void load_carried(const T *state_in, const int32_t *parent, int64_t b, int64_t n_in, int64_t D, int64_t d0)
+    {
+        // a draft branch continues from its parent's window (the copy is fused into this load)
+        const int64_t pb = parent ? (int64_t)parent[b] : b;
+        const bool p_ok = !parent || (pb >= 0 && pb < n_in);
+        if (!state_in) {
+#pragma unroll
+            for (int i = 0; i < VEC * H; ++i) carried[i] = 0.0f;
+        } else if (!p_ok) {
+#pragma unroll
+            for (int i = 0; i < VEC * H; ++i) carried[i] = __int_as_float(0x7fc00000);
+        } else if constexpr (VEC > 1) {
+            ld_block<VEC * H>(state_in + (pb * D + d0) * H, carried);
+        } else {
+#pragma unroll
+            for (int k = 0; k < H; ++k) carried[k] = ld_io(state_in, (pb * D + d0) * H + k);
+        }
+    }
+    // window row i is token t: its row, or for a negative t the carried one
+    __device__ __forceinline__ void set_window(int i, int64_t t, row_t row)
+    {
+        if (t >= 0) {
+            unpack_row(row, win[i]);
+        } else {
+#pragma unroll
+            for (int c = 0; c < VEC; ++c) {
+                float v = 0.0f;
+#pragma unroll
+                for (int k = 0; k < H; ++k)
+                    if (k == H + t) v = carried[c * H + k];
+                win[i][c] = v;
+            }
+        }
+    }
+    __device__ __forceinline__ row_t emit(row_t raw)
+    {
+        float cur[VEC], o[VEC];
+        unpack_row(raw, cur);
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) {
+            float acc = br[c];
+#pragma unroll
+            for (int k = 0; k < H; ++k) acc = fmaf(wr[c][k], win[k][c], acc);
+            acc = fmaf(wr[c][K - 1], cur[c], acc);
+            o[c] = SILU ? silu_f32(acc) : acc;
+        }
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) {
+#pragma unroll
+            for (int k = 0; k + 1 < H; ++k) win[k][c] = win[k + 1][c];
+            if (H > 0) win[H - 1][c] = cur[c];
+        }
+        row_t packed;
+        pack_row(o, packed);
+        return packed;
+    }
+    __device__ __forceinline__ void store_window(T *state_out, int64_t b, int64_t D, int64_t d0) const
+    {
+        float last[VEC * (H > 0 ? H : 1)];
+#pragma unroll
+        for (int c = 0; c < VEC; ++c)
+#pragma unroll
+            for (int k = 0; k < H; ++k) last[c * H + k] = win[k][c];
+        if constexpr (VEC > 1) {
+            st_block<VEC * H>(state_out + (b * D + d0) * H, last);
+        } else {
+#pragma unroll
+            for (int k = 0; k < H; ++k) st_io(state_out, (b * D + d0) * H + k, last[k]);
+        }
+    }
+};
+
 // grid: (channel-vector groups, groups of four time tiles, batch), blocks of 64 x 4 threads (a grid has fewer than 2^32 threads
 // along x, so the wavefronts of a workgroup count along y)
 template <typename T, int VEC, int K, bool SILU>
@@ -104,56 +187,29 @@ conv1d_kernel(const T *__restrict__ x, const float *__restrict__ w, const float 
     // Taps and bias of the 64 VEC channels, fetched once for the workgroup with adjacent lanes on adjacent 16 bytes.  (A
     // lane's own VEC K taps are one run of memory, but read by that lane every 16-byte piece lies 128 bytes from its
     // neighbour's, and the address path takes a cycle per lane: three times what the token rows themselves take.)
-    constexpr int kSlots = VEC > 1 ? VEC * K / 4 : 1;               // float4 of taps per lane
-    constexpr int kTapIters = (kWave * kSlots + kBlock - 1) / kBlock, kBiasIters = VEC > 1 ? (kWave * VEC + kBlock - 1) / kBlock : 1;
-    __shared__ __attribute__((aligned(16))) float4 lds_w[VEC > 1 ? kSlots : 1][kWave + 1];   // + 1: eight slots of a lane fall on eight bank groups
-    __shared__ __attribute__((aligned(16))) float lds_b[VEC > 1 ? kWave * VEC : 1];
+    constexpr int kSlots = VEC * K / 4;                             // float4 of taps per lane
+    constexpr int kTapIters = (kWave * kSlots + kBlock - 1) / kBlock, kBiasIters = (kWave * VEC + kBlock - 1) / kBlock;
+    __shared__ __attribute__((aligned(16))) float4 lds_w[kSlots][kWave + 1];   // + 1: eight slots of a lane fall on eight bank groups
+    __shared__ __attribute__((aligned(16))) float lds_b[kWave * VEC];
     float4 tap[kTapIters];
     float bias_in[kBiasIters];
-    float wr[VEC][K], br[VEC];
-    if constexpr (VEC > 1) {
-        const int64_t n_taps = (D - d_block) * K / 4;               // D % VEC == 0: whole float4
+    const int64_t n_taps = (D - d_block) * K / 4;                   // D % VEC == 0: whole float4
 #pragma unroll
-        for (int i = 0; i < kTapIters; ++i) {
-            const int q = tid + i * kBlock;
-            tap[i] = reinterpret_cast<const float4 *>(w + d_block * K)[q < n_taps ? q : 0];
-        }
+    for (int i = 0; i < kTapIters; ++i) {
+        const int q = tid + i * kBlock;
+        tap[i] = reinterpret_cast<const float4 *>(w + d_block * K)[q < n_taps ? q : 0];
+    }
 #pragma unroll
-        for (int i = 0; i < kBiasIters; ++i) {
-            const int64_t d = d_block + tid + i * kBlock;
-            bias_in[i] = bias ? bias[d < D ? d : D - 1] : 0.0f;
-        }
-    } else if (live) {
-#pragma unroll
-        for (int k = 0; k < K; ++k) wr[0][k] = w[d0 * K + k];
-        br[0] = bias ? bias[d0] : 0.0f;
+    for (int i = 0; i < kBiasIters; ++i) {
+        const int64_t d = d_block + tid + i * kBlock;
+        bias_in[i] = bias ? bias[d < D ? d : D - 1] : 0.0f;
     }
 
     const T *xb = x + b * L * D + d0;
     T *yb = y + b * L * D + d0;
     auto ld_row = [&](int64_t t) { return *reinterpret_cast<const row_t *>(xb + t * D); };
-
-    // window: the H rows before t0 in padded time; win[H-1] is the newest.  Rows before token 0
-    // come from the carried state, whose (VEC, H) block of this lane is one contiguous run.
-    float win[H > 0 ? H : 1][VEC];
-    float carried[VEC * (H > 0 ? H : 1)];
-    if (live && t0 < H && t0 < t1 + (L == 0)) {
-        // a draft branch continues from its parent's window (the copy is fused into this load)
-        const int64_t pb = parent ? (int64_t)parent[b] : b;
-        const bool p_ok = !parent || (pb >= 0 && pb < n_in);
-        if (!state_in) {
-#pragma unroll
-            for (int i = 0; i < VEC * H; ++i) carried[i] = 0.0f;
-        } else if (!p_ok) {
-#pragma unroll
-            for (int i = 0; i < VEC * H; ++i) carried[i] = __int_as_float(0x7fc00000);
-        } else if constexpr (VEC > 1) {
-            ld_block<VEC * H>(state_in + (pb * D + d0) * H, carried);
-        } else {
-#pragma unroll
-            for (int k = 0; k < H; ++k) carried[k] = ld_io(state_in, (pb * D + d0) * H + k);
-        }
-    }
+    ConvLane<T, VEC, K, SILU> c;
+    if (live && t0 < H && t0 < t1 + (L == 0)) c.load_carried(state_in, parent, b, n_in, D, d0);
     // (the rows before the tile and its first group of rows are on their way before anything is waited for)
     row_t before[H > 0 ? H : 1];
     row_t cur[kRows];
@@ -167,61 +223,24 @@ conv1d_kernel(const T *__restrict__ x, const float *__restrict__ w, const float 
         for (int i = 0; i < H; ++i) before[i] = ld_row(t0 - H + i < 0 ? 0 : t0 - H + i);
         ld_group(cur, t0);
     }
-    if constexpr (VEC > 1) {
 #pragma unroll
-        for (int i = 0; i < kTapIters; ++i) {
-            const int q = tid + i * kBlock;
-            if (q < kWave * kSlots) lds_w[q % kSlots][q / kSlots] = tap[i];
-        }
-#pragma unroll
-        for (int i = 0; i < kBiasIters; ++i)
-            if (tid + i * kBlock < kWave * VEC) lds_b[tid + i * kBlock] = bias_in[i];
-        lds_barrier_c();
-#pragma unroll
-        for (int i = 0; i < kSlots; ++i) unpack_row(lds_w[i][lane], &wr[0][0] + 4 * i);
-#pragma unroll
-        for (int i = 0; i < VEC / 4; ++i) unpack_row(*reinterpret_cast<const float4 *>(&lds_b[lane * VEC + 4 * i]), br + 4 * i);
+    for (int i = 0; i < kTapIters; ++i) {
+        const int q = tid + i * kBlock;
+        if (q < kWave * kSlots) lds_w[q % kSlots][q / kSlots] = tap[i];
     }
+#pragma unroll
+    for (int i = 0; i < kBiasIters; ++i)
+        if (tid + i * kBlock < kWave * VEC) lds_b[tid + i * kBlock] = bias_in[i];
+    lds_barrier_c();
+#pragma unroll
+    for (int i = 0; i < kSlots; ++i) unpack_row(lds_w[i][lane], &c.wr[0][0] + 4 * i);
+#pragma unroll
+    for (int i = 0; i < VEC / 4; ++i) unpack_row(*reinterpret_cast<const float4 *>(&lds_b[lane * VEC + 4 * i]), c.br + 4 * i);
     if (!live || t0 >= t1 + (t0 == 0 && L == 0)) return;        // (no token at all: one tile passes the carried state on)
 #pragma unroll
-    for (int i = 0; i < H; ++i) {
-        const int64_t t = t0 - H + i;  // token index of this window row, negative => carried state
-        if (t >= 0) {
-            unpack_row(before[i], win[i]);
-        } else {
-#pragma unroll
-            for (int c = 0; c < VEC; ++c) {
-                float v = 0.0f;
-#pragma unroll
-                for (int k = 0; k < H; ++k)
-                    if (k == H + t) v = carried[c * H + k];
-                win[i][c] = v;
-            }
-        }
-    }
+    for (int i = 0; i < H; ++i) c.set_window(i, t0 - H + i, before[i]);
 
-    auto emit = [&](int64_t t, row_t raw) {
-        float cur[VEC], o[VEC];
-        unpack_row(raw, cur);
-#pragma unroll
-        for (int c = 0; c < VEC; ++c) {
-            float acc = br[c];
-#pragma unroll
-            for (int k = 0; k < H; ++k) acc = fmaf(wr[c][k], win[k][c], acc);
-            acc = fmaf(wr[c][K - 1], cur[c], acc);
-            o[c] = SILU ? silu_f32(acc) : acc;
-        }
-#pragma unroll
-        for (int c = 0; c < VEC; ++c) {
-#pragma unroll
-            for (int k = 0; k + 1 < H; ++k) win[k][c] = win[k + 1][c];
-            if (H > 0) win[H - 1][c] = cur[c];
-        }
-        row_t packed;
-        pack_row(o, packed);
-        *reinterpret_cast<row_t *>(yb + t * D) = packed;
-    };
-
+    auto emit = [&](int64_t t, row_t raw) { *reinterpret_cast<row_t *>(yb + t * D) = c.emit(raw); };
     for (int64_t t = t0; t < t1; t += kRows) {
         row_t nxt[kRows];
         const bool more = t + kRows < t1;
@@ -239,49 +258,117 @@ conv1d_kernel(const T *__restrict__ x, const float *__restrict__ w, const float 
             for (int i = 0; i < kRows; ++i) cur[i] = nxt[i];
         }
     }
+    if (state_out && t1 == L) c.store_window(state_out, b, D, d0);
+}
 
-    if (state_out && t1 == L) {
-        float last[VEC * (H > 0 ? H : 1)];
+// The same with one wavefront to a workgroup, taps of its own and longer groups of rows: for what the kernel above has no use of
+// its four wavefronts for, or of 16-byte pieces (launch_conv_k).
+// grid: (channel-vector groups, time tiles, batch)
+template <typename T, int VEC, int K, bool SILU>
+__global__ void __launch_bounds__(kWave)
+conv1d_wave_kernel(const T *__restrict__ x, const float *__restrict__ w, const float *__restrict__ bias,
+                   const T *state_in, T *__restrict__ y, T *state_out, int64_t L, int64_t D,
+                   int64_t tile_len, const int32_t *__restrict__ parent, int64_t n_in)
+{
+    typedef typename RowVec<T, VEC>::type row_t;
+    constexpr int H = K - 1;
+    const int64_t b = blockIdx.z;
+    const int64_t d0 = ((int64_t)blockIdx.x * kWave + threadIdx.x) * VEC;
+    if (d0 >= D) return;                                            // no cross-lane work below
+    const int64_t t0 = (int64_t)blockIdx.y * tile_len;
+    const int64_t t1 = (t0 + tile_len < L) ? t0 + tile_len : L;
+    ConvLane<T, VEC, K, SILU> c;
+    if constexpr (VEC > 1) {
+        ld_block<VEC * K>(w + d0 * K, &c.wr[0][0]);
+    } else {
 #pragma unroll
-        for (int c = 0; c < VEC; ++c)
+        for (int k = 0; k < K; ++k) c.wr[0][k] = w[d0 * K + k];
+    }
 #pragma unroll
-            for (int k = 0; k < H; ++k) last[c * H + k] = win[k][c];
-        if constexpr (VEC > 1) {
-            st_block<VEC * H>(state_out + (b * D + d0) * H, last);
-        } else {
+    for (int i = 0; i < VEC; ++i) c.br[i] = bias ? bias[d0 + i] : 0.0f;
+
+    const T *xb = x + b * L * D + d0;
+    T *yb = y + b * L * D + d0;
+    auto ld_row = [&](int64_t t) { return *reinterpret_cast<const row_t *>(xb + t * D); };
+    if (t0 < H) c.load_carried(state_in, parent, b, n_in, D, d0);
 #pragma unroll
-            for (int k = 0; k < H; ++k) st_io(state_out, (b * D + d0) * H + k, last[k]);
+    for (int i = 0; i < H; ++i) {
+        const int64_t t = t0 - H + i;
+        row_t row{};
+        if (t >= 0) row = ld_row(t);
+        c.set_window(i, t, row);
+    }
+    auto emit = [&](int64_t t, row_t raw) { *reinterpret_cast<row_t *>(yb + t * D) = c.emit(raw); };
+    int64_t t = t0;
+    row_t cur[kRowsWave];
+    if (t + kRowsWave <= t1) {
+#pragma unroll
+        for (int i = 0; i < kRowsWave; ++i) cur[i] = ld_row(t + i);
+    }
+    for (; t + kRowsWave <= t1; t += kRowsWave) {
+        row_t nxt[kRowsWave];
+        const bool more = t + 2 * kRowsWave <= t1;
+        if (more) {
+#pragma unroll
+            for (int i = 0; i < kRowsWave; ++i) nxt[i] = ld_row(t + kRowsWave + i);
+        }
+#pragma unroll
+        for (int i = 0; i < kRowsWave; ++i) emit(t + i, cur[i]);
+        if (more) {
+#pragma unroll
+            for (int i = 0; i < kRowsWave; ++i) cur[i] = nxt[i];
         }
     }
+    for (; t < t1; ++t) emit(t, ld_row(t));
+    if (state_out && t1 == L) c.store_window(state_out, b, D, d0);
 }
 
 template <typename T, int VEC, int K> hipError_t launch_conv_k(const ConvArgs &a, hipStream_t stream)
 {
     const int64_t vecs = (a.D + VEC - 1) / VEC;
     const unsigned gx = (unsigned)((vecs + kWave - 1) / kWave);
-    // channel vectors per wavefront: an even split, not a remainder for the last one, in whole 128-byte lines
-    const int even = (int)((vecs + gx - 1) / gx);
-    const int lanes = VEC > 1 ? (even + 7) / 8 * 8 : even;
+    // Whose kernel: time tiles side by side in a workgroup, or single wavefronts.  The first needs several tiles and 16-byte
+    // pieces; us on tiles / single wavefronts:
+    //   a state updated in place, which is one tile: 2048 x 1536 bf16 622 / 437, f32 378 / 260; 64 x 8 x 1536 5.8 / 4.7
+    //   one or two tokens: 64 x 1 x 1536 bf16 4.0 / 3.4, f32 3.8 / 3.4, 128 x 2 x 768 4.2 / 3.8 (64 x 4 x 1536 4.2 / 4.4)
+    //   one channel to a lane: 4000 x 777 bf16 8.0 / 6.8, f32 8.1 / 7.3; 32768 x 777 34.9 / 32.8, 50.0 / 46.9
+    //   few float32 lanes on many rows: 16384 x 64 5.4 / 5.1, 32768 x 64 7.7 / 7.2 (12000 x 64 4.6 / 5.1, 16384 x 256 6.7 / 7.5)
+    // Everywhere else the tiles are as fast or faster (8000 x 1536 bf16 11.4 / 14.7, f32 16.8 / 17.6).
+    const bool in_place = a.state_out && a.state_in == a.state_out;
+    const bool waves = VEC == 1 || in_place || a.L <= 2 || (sizeof(T) == 4 && vecs <= 32 && a.batch * a.L >= 16384);
+    const int rows = waves ? kRowsWave : kRows;
     // Time tiles: enough workgroups to fill the chip, long enough to amortize the K-1 halo rows.
     // An in-place state update keeps one tile so that a thread reads the state before it writes it.
     // Short inputs get shorter tiles (down to one group of rows) until there are about two wavefronts per SIMD: a row
     // takes a wavefront some 500 cycles of arithmetic, so on a short input the rows in turn are most of the time.
-    int64_t tile_len = 16;
-    while (tile_len > kRows && (int64_t)gx * ((a.L + tile_len - 1) / tile_len) * a.batch < 2048) tile_len /= 2;
-    if (a.state_out && a.state_in == a.state_out) tile_len = a.L;
+    int64_t tile_len = waves ? 32 : 16;
+    while (tile_len > rows && (int64_t)gx * ((a.L + tile_len - 1) / tile_len) * a.batch < 2048) tile_len /= 2;
+    if (in_place) tile_len = a.L;
     if ((a.L + tile_len - 1) / tile_len > 65535) tile_len = (a.L + 65534) / 65535;
     if (tile_len < 1) tile_len = 1;
     int64_t tiles = (a.L + tile_len - 1) / tile_len;
     if (tiles < 1) tiles = 1;  // L == 0: one tile that only passes the carried state on
-    const dim3 grid(gx, (unsigned)((tiles + kTilesPerBlock - 1) / kTilesPerBlock), (unsigned)a.batch), block(kWave, kTilesPerBlock);
     const T *x = static_cast<const T *>(a.x);
     const T *si = static_cast<const T *>(a.state_in);
     T *y = static_cast<T *>(a.y);
     T *so = static_cast<T *>(a.state_out);
-    if (a.apply_silu)
-        conv1d_kernel<T, VEC, K, true><<<grid, block, 0, stream>>>(x, a.w, a.bias, si, y, so, a.L, a.D, tile_len, lanes, a.parent, a.n_in);
-    else
-        conv1d_kernel<T, VEC, K, false><<<grid, block, 0, stream>>>(x, a.w, a.bias, si, y, so, a.L, a.D, tile_len, lanes, a.parent, a.n_in);
+    if (waves) {
+        const dim3 grid(gx, (unsigned)tiles, (unsigned)a.batch);
+        if (a.apply_silu)
+            conv1d_wave_kernel<T, VEC, K, true><<<grid, kWave, 0, stream>>>(x, a.w, a.bias, si, y, so, a.L, a.D, tile_len, a.parent, a.n_in);
+        else
+            conv1d_wave_kernel<T, VEC, K, false><<<grid, kWave, 0, stream>>>(x, a.w, a.bias, si, y, so, a.L, a.D, tile_len, a.parent, a.n_in);
+        return hipGetLastError();
+    }
+    if constexpr (VEC > 1) {
+        // channel vectors per wavefront: an even split, not a remainder for the last one, in whole 128-byte lines
+        const int lanes = (int)((vecs + gx - 1) / gx + 7) / 8 * 8;
+        const dim3 grid(gx, (unsigned)((tiles + kTilesPerBlock - 1) / kTilesPerBlock), (unsigned)a.batch), block(kWave, kTilesPerBlock);
+        if (a.apply_silu)
+            conv1d_kernel<T, VEC, K, true><<<grid, block, 0, stream>>>(x, a.w, a.bias, si, y, so, a.L, a.D, tile_len, lanes, a.parent, a.n_in);
+        else
+            conv1d_kernel<T, VEC, K, false><<<grid, block, 0, stream>>>(x, a.w, a.bias, si, y, so, a.L, a.D, tile_len, lanes, a.parent, a.n_in);
+    }
     return hipGetLastError();
 }
 

@@ -270,6 +270,29 @@ def test_scan_strided_layouts(m, io, B, L, D, N):
 
 
 @pytest.mark.parametrize("io", [synth.F32, synth.BF16])
+@pytest.mark.parametrize("B,L,D", [(2, 1, 64), (3, 2, 1536), (2, 3, 64), (1, 7, 777), (2, 9, 40), (1, 100, 1536), (1, 37, 8)])
+def test_conv_state_updated_in_place_equals_its_own_buffer(m, io, B, L, D):
+    """Single wavefronts on one tile (in place) and time tiles side by side do the same operations: bit for bit the same."""
+    c = synth.prefill_case(B, L, D, 16, 4, io, seed=L + D)
+    rng = np.random.default_rng(L * D)
+    g = {k: to_dev(c[k]) for k in ("x", "conv_w", "conv_bias")}
+    state = to_dev(synth.to_io(rng.standard_normal((B, D, 3)).astype(np.float32), io))
+    y, st = m.mamba_conv1d_fwd(g["x"], g["conv_w"], g["conv_bias"], conv_state_in=state)
+    y2, st2 = m.mamba_conv1d_fwd(g["x"], g["conv_w"], g["conv_bias"], conv_state_in=state, conv_state_out=state)
+    assert torch.equal(y, y2) and torch.equal(st, state)
+    empty, passed = m.mamba_conv1d_fwd(g["x"][:, :0].contiguous(), g["conv_w"], g["conv_bias"], conv_state_in=state)   # no token
+    assert empty.numel() == 0 and torch.equal(passed, state)
+
+
+@pytest.mark.parametrize("B,L,D,io", [(1, 9001, 512, synth.F32), (1, 4110, 1024, synth.F32), (2, 4501, 2048, synth.BF16),   # 18-row tiles
+                                      (1, 16384, 128, synth.F32), (4, 4097, 12, synth.F32), (1, 16383, 132, synth.F32)])    # few lanes, many rows
+def test_conv_time_tiles_of_long_contexts(m, B, L, D, io):
+    """Both sides of the rules for the tile length and for single wavefronts, on contexts that leave a ragged last tile."""
+    say(B=B, L=L, D=D, io=io)
+    check_conv(m, synth.prefill_case(B, L, D, 16, 4, io, seed=L + D))
+
+
+@pytest.mark.parametrize("io", [synth.F32, synth.BF16])
 @pytest.mark.parametrize("K", [2, 4])
 @pytest.mark.parametrize("B,L,D", [(2, 150, 100), (1, 2, 9), (3, 300, 64), (1, 1, 1)])
 def test_conv_strided_layouts(m, io, K, B, L, D):
