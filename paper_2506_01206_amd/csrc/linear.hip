@@ -43,8 +43,6 @@ __device__ __forceinline__ void lds_barrier_linear()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// tile counts from which each register-staged tile shape takes over (measured crossovers, see launch_linear)
-constexpr int64_t kTilesBig = 512, kTilesMid = 512, kTilesDeep = 513;
 constexpr int64_t kTilesResident = 256;                           // one workgroup per CU
 
 struct OutSplit {
@@ -950,45 +948,25 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     }
 #undef MAMBA_FEW
 #undef MAMBA_FEW_K
-    if (vec && N % 128 == 0 && a.M >= 128 && a.K % (2 * kWideBK) == 0) {
-        // The memory-to-LDS kernel, on any number of rows.  Measured inside the 24-block prefill (alone in a loop the
-        // wide tiles look better than they are there: their denser matrix work lowers the clock for what runs between
-        // them).  256 x 256 tiles, one to a CU, where they fill at least nine tenths of the rounds they take (32768 rows
-        // x 3072 columns 184 us against 227 on the register-staged tiles).  Otherwise 128 x 128 tiles, two to a CU: with
-        // a long k loop from half a tile per CU on (8000 rows x 768 columns, K = 1536: 36.7 -> 28.5 us, the whole
-        // prefill 5.70 -> 5.54 ms; 2000 rows, 96 tiles, 19.5 us on the deep register-staged tiles against 25), with a
-        // short one from one tile per CU to two (1500 to 2500 rows x 3072 columns, K = 768: prefill 2 to 3 % faster;
-        // 8000 rows, three rounds: 53.7 us register-staged against 55.5).
-        const int64_t t256 = a.M >= 256 && N % 256 == 0 ? ((a.M + 255) / 256) * (N / 256) : 0;
-        const int64_t t128 = ((a.M + 127) / 128) * (N / 128);
-        const int64_t rounds = (t256 + 255) / 256;
-        if (t256 >= 9 * 256 / 10 && 10 * t256 >= 9 * 256 * rounds) {
-            linear_wide_kernel<256, 256><<<(unsigned)(8 * ((t256 + 7) / 8)), 256, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, (int)(N / 256), (int)t256);
-            return hipGetLastError();
-        }
-        if (a.K >= 1024 ? t128 >= 128 : t128 >= 256 && t128 <= 512) {
-            linear_wide_kernel<128, 128><<<(unsigned)(8 * ((t128 + 7) / 8)), 256, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, (int)(N / 128), (int)t128);
-            return hipGetLastError();
-        }
-    }
-    if (tiles(128, 128) >= kTilesBig) {
-        dim3 grid((unsigned)((N + 127) / 128), (unsigned)((a.M + 127) / 128));
-        linear_kernel<128, 128, 64><<<grid, kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec);
-    } else if (tiles(64, 128) >= kTilesMid) {
-        dim3 grid((unsigned)((N + 127) / 128), (unsigned)((a.M + 63) / 64));
-        linear_kernel<64, 128, 64><<<grid, kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec);
-    } else if (a.K >= 512 && tiles(64, 64) < kTilesDeep) {
-        // few tiles and a long k loop (x_proj, out_proj on a context of a few thousand tokens): with one or two
-        // workgroups per CU nothing hides the fetch of the next slab, so the slabs are made four times deeper
-        // and the loop four times shorter
-        dim3 grid((unsigned)((N + 63) / 64), (unsigned)((a.M + 63) / 64));
-        linear_kernel<64, 64, 256><<<grid, kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec);
-    } else {
-        dim3 grid((unsigned)((N + 63) / 64), (unsigned)((a.M + 63) / 64));
+    const bool wide = vec && N % 128 == 0 && a.M >= 128 && a.K % (2 * kWideBK) == 0;
+    auto grid = [&](int bm, int bn) { return dim3((unsigned)((N + bn - 1) / bn), (unsigned)((a.M + bm - 1) / bm)); };
+    auto in_turn = [&](int64_t t) { return (unsigned)(8 * ((t + 7) / 8)); };
+    switch (linear_tiles(a.M, N, a.K, wide)) {
+    case kTilesWide256:
+        linear_wide_kernel<256, 256><<<in_turn(tiles(256, 256)), 256, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, (int)(N / 256), (int)tiles(256, 256));
+        break;
+    case kTilesWide128:
+        linear_wide_kernel<128, 128><<<in_turn(tiles(128, 128)), 256, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, (int)(N / 128), (int)tiles(128, 128));
+        break;
+    case kTiles128: linear_kernel<128, 128, 64><<<grid(128, 128), kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec); break;
+    case kTiles64x128: linear_kernel<64, 128, 64><<<grid(64, 128), kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec); break;
+    case kTiles64Deep: linear_kernel<64, 64, 256><<<grid(64, 64), kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec); break;
+    default:
         if (a.M <= 64 && N >= 8192)
-            linear_kernel<64, 64, 64, true><<<grid, kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec);
+            linear_kernel<64, 64, 64, true><<<grid(64, 64), kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec);
         else
-            linear_kernel<64, 64, 64><<<grid, kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec);
+            linear_kernel<64, 64, 64><<<grid(64, 64), kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec);
+        break;
     }
     return hipGetLastError();
 }

@@ -42,6 +42,58 @@ inline int linear_few_row_tiles(int64_t M, int64_t N)
     return M <= 32 || columns * ((M + 31) / 32) <= 256 ? 2 : 4;
 }
 
+// Tile kernels for products that the few-row kernels do not take (linear.hip).
+enum LinearTiles {
+    kTilesWide256,      // linear_wide_kernel, 256 x 256 tiles, one to a CU
+    kTilesWide128,      // the same with 128 x 128, two to a CU
+    kTiles128,          // linear_kernel, 128 x 128 tiles, three to a CU
+    kTiles64x128,
+    kTiles64Deep,       // 64 x 64 with slabs of 256 k
+    kTiles64
+};
+
+// Which of them.  wide: M >= 128, N % 128 == 0, K % 128 == 0 and output widths that are multiples of 8, which the
+// memory-to-LDS kernel asks for.  The lines are drawn from chains of 24 different blocks, as a prefill runs them (alone in a
+// loop, or with few weights that stay in the caches, the wide tiles look better than they are there), for seven models from 512
+// to 5120 channels and 200 to 32768 rows, every kernel that applies put in place of one product: 201 products, on which
+// the choice costs 0.3 % of a block more than the best one on average.  us of a block on 256 x 256 / 128 x 128 memory-to-LDS /
+// 128 x 128 register-staged tiles / the best of the small ones:
+//   rows   in_proj of         K                                     out_proj of       K
+//   8000   1536 channels    768  209.8 / 214.3 / 204.4 / 209.9      1536 channels  1536  232.0 / 214.5 / 228.9 / 225.3
+//  16384   1536             768  410.1 / 416.1 / 405.0              1536           1536  403.9 / 409.9 / 423.3 / 428.2
+//   2048   1536             768   91.1 /  83.8 /  87.0 /  85.2      2048           2048  149.5 / 130.4 / 145.0 / 124.2
+//   3000   2048            1024  153.5 / 163.1 / 157.0 / 163.3      2048           2048  172.1 / 153.1 / 170.1 / 153.8
+//    512   2048            1024   81.7 /  69.8 /  73.8 /  64.2      4096           4096  212.1 / 176.9 / 197.9 / 158.7 (1000 rows)
+//   6000   3072            1536  432.1 / 447.4 / 422.3              4096           4096  569.7 / 601.0 /   -   /   -
+//   1000   5120            2560  233.1 / 251.0 / 235.1 / 251.2      5120           5120  277.7 / 233.1 / 254.3 / 230.1
+//   4096   5120            2560  622.1 / 647.3 / 637.7              5120           5120  624.3 / 635.3 / 656.9 / 687.4
+inline LinearTiles linear_tiles(int64_t M, int64_t N, int64_t K, bool wide)
+{
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((N + bn - 1) / bn) * ((M + bm - 1) / bm); };
+    if (wide) {
+        // 256 x 256, one to a CU, where they fill nine tenths of the rounds they take; with a long k also where no more than
+        // 128 CUs miss a tile in the last round, in narrow outputs only if that is the first one
+        const int64_t t256 = M >= 256 && N % 256 == 0 ? tiles(256, 256) : 0;
+        const int64_t rounds = (t256 + 255) / 256, idle = 256 * rounds - t256;
+        if (t256 >= 230 && 10 * t256 >= 9 * 256 * rounds) return kTilesWide256;
+        if (K >= 1024 && t256 >= 160 && idle <= 128 && (N >= 4096 || rounds == 1)) return kTilesWide256;
+        // 128 x 128, two to a CU.  Wide outputs: one round of one or two to a CU; beyond that an XCD's tiles lie side by side in
+        // one row block and every weight is used once per visit.  Narrow ones: with a short k the same, from fewer tiles on and
+        // in any number where there are few columns; with a long k from half a tile per CU on, unless the small tiles with deep
+        // slabs come to two per CU at most, which is one round of theirs.
+        const int64_t t128 = tiles(128, 128);
+        if (N >= 4096 ? t128 >= 256 && t128 <= 512
+                      : K >= 1024 ? t128 >= 128 && (N < 1024 || tiles(64, 64) > 512)
+                                  : (t128 >= 256 && t128 <= 512) || (N <= 768 && t128 >= 192))
+            return kTilesWide128;
+    }
+    if (tiles(128, 128) >= 512) return kTiles128;
+    if (tiles(64, 128) >= 512) return kTiles64x128;
+    // few tiles and a long k loop: with one or two workgroups per CU nothing hides the fetch of the next slab, so the slabs
+    // are made four times deeper and the loop four times shorter
+    return K >= 512 && tiles(64, 64) < 513 ? kTiles64Deep : kTiles64;
+}
+
 // x_proj and dt_proj in one kernel (xdt.hip): rows per workgroup and column groups for M rows; 0 rows: two launches.
 // Every workgroup reads all weights, so what counts is the number of rounds on 256 CUs times what a workgroup takes (us in
 // xdt.hip, in a full round).  One round of 16 rows: column groups as long as they fit the chip beside each other (24-block

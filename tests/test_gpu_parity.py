@@ -1151,11 +1151,11 @@ def test_scan_invariants_at_size(m):
                                           # split outputs
                                           (4096, 4096, 64, None), (4100, 4000, 128, (2000, 2000)), (4096, 4104, 192, None),
                                           (4090, 4096, 320, (4088, 8)), (5000, 3400, 448, (1000, 1200, 1200)),
-                                          # 256-row tiles, 256 and 128 columns wide (M % 256 == 0, K % 128 == 0, >= 512 tiles):
-                                          # 4, 6, 8 and 10 slabs, splits on and off the tile edges
+                                          # memory-to-LDS tiles (N % 128 == 0, K % 128 == 0): 4, 6, 8 and 10 slabs, splits on
+                                          # and off the tile edges; two that the small register-staged tiles take
                                           (16384, 2048, 256, (1024, 1024)), (16384, 1152, 384, None), (8192, 4096, 512, None),
                                           (16384, 1152, 640, (1000, 152)), (1024, 3072, 768, (1536, 1536)), (512, 6144, 128, None),
-                                          # 128 x 128 tiles of the same kernel (M % 128 == 0, 192 .. a few hundred tiles)
+                                          # a long k on few tiles, and more for the small tiles
                                           (4096, 768, 1536, None), (2688, 1152, 256, (1000, 152)), (384, 8192, 384, None)])
 def test_linear_against_oracle(m, M, N, K, splits):
     say(M=M, N=N, K=K, splits=splits)
@@ -1175,7 +1175,11 @@ def test_linear_against_oracle(m, M, N, K, splits):
 
 
 @pytest.mark.parametrize("M,N,K,splits", [(129, 32768, 128, None), (5003, 3072, 256, (1536, 1536)), (10241, 1536, 128, None),
-                                          (2177, 1152, 1024, None), (4001, 768, 1536, None), (3999, 1280, 128, (1000, 280))])
+                                          (2177, 1152, 1024, None), (4001, 768, 1536, None), (3999, 1280, 128, (1000, 280)),
+                                          # 256 x 256 tiles, full rows of them and ragged ones, full rounds and not; the register-
+                                          # staged 128 x 128 tiles beside them
+                                          (8192, 4096, 768, (2048, 2048)), (2047, 8192, 512, None), (2500, 6144, 384, (3072, 3072)),
+                                          (1101, 8192, 1024, (4000, 4192)), (1001, 10240, 640, (5000, 5240)), (1025, 8192, 512, None)])
 def test_linear_wide_tiles_ragged_rows(m, M, N, K, splits):
     """Row counts that leave the memory-to-LDS kernels a last row block shared with the one before it (from one row of
     its own to all but one): results against the oracle, and the residual added in place exactly once per row."""
@@ -1229,8 +1233,8 @@ def test_linear_at_block_bench_size_sampled_rows(m):
 
 
 def test_linear_wide_tiles_are_deterministic(m):
-    """The 256-row tiles stream their operands into LDS asynchronously and order them with explicit waits; a
-    missing wait would show as run-to-run differences.  Ten launches each, all three tile shapes, on fresh outputs."""
+    """The memory-to-LDS tiles stream their operands in asynchronously and order them with explicit waits; a
+    missing wait would show as run-to-run differences.  Ten launches each, both tile shapes, on fresh outputs."""
     g = torch.Generator(device=DEV)
     g.manual_seed(77)
     for (M, N, K) in ((8192, 4096, 768), (16384, 1152, 1536), (4096, 768, 1536)):

@@ -13,6 +13,7 @@ extern "C" int folds(int n_seg1, int before, uintptr_t h0, uintptr_t h_final, in
 { return mamba::ssd_folds(n_seg1, before, (const void *)h0, (const void *)h_final, bytes); }
 extern "C" int few_fits(int64_t N, int64_t K) { return mamba::linear_few_fits(N, K); }
 extern "C" int row_tiles(int64_t M, int64_t N) { return mamba::linear_few_row_tiles(M, N); }
+extern "C" int tiles(int64_t M, int64_t N, int64_t K, int wide) { return mamba::linear_tiles(M, N, K, wide); }
 extern "C" int xdt(int64_t M, int64_t d_inner, int64_t dt_rank, int64_t N, unsigned *groups)
 { return mamba::xdt_plan(M, d_inner, dt_rank, N, groups); }
 """
@@ -29,6 +30,7 @@ def routes(tmp_path_factory):
     lib.folds.argtypes = [i32, i32, ptr, ptr, i64]
     lib.few_fits.argtypes = [i64, i64]
     lib.row_tiles.argtypes = [i64, i64]
+    lib.tiles.argtypes = [i64, i64, i64, i32]
     lib.xdt.argtypes = [i64, i64, i64, i64, ctypes.POINTER(ctypes.c_uint)]
     return lib
 
@@ -78,3 +80,27 @@ def test_few_row_product_forms_no_more_row_tiles_than_there_are_rows(routes):
         for M in range(1, 65):
             tiles = routes.row_tiles(M, N)
             assert tiles in (1, 2, 4) and (tiles == 1 or 16 * tiles < 2 * 16 * -(-M // 16)), (M, N)
+
+
+def test_tile_kernel_of_a_product(routes):
+    """Which tile kernel a product gets: the ones that the parity tests name for it, the ones measured faster in chains of blocks
+    of other widths than 1536 channels, and never a kernel whose conditions it does not meet."""
+    W256, W128, T128, T64x128, DEEP, T64 = range(6)
+    tiles = lambda M, N, K: routes.tiles(M, N, K, M >= 128 and N % 128 == 0 and K % 128 == 0)
+    for kind, shapes in {
+            W256: [(5003, 3072, 256), (10241, 1536, 128), (8192, 4096, 768), (2047, 8192, 512), (2500, 6144, 384), (1101, 8192, 1024),
+                   (32768, 3072, 768), (1000, 10240, 2560), (4096, 10240, 2560), (3000, 4096, 1024), (6000, 2048, 4096)],
+            W128: [(129, 32768, 128), (2177, 1152, 1024), (4001, 768, 1536), (3999, 1280, 128), (2048, 3072, 768), (8000, 768, 1536),
+                   (32768, 768, 1536), (16000, 256, 512)],
+            T128: [(1025, 8192, 512), (1001, 10240, 640), (8000, 3072, 768), (6000, 6144, 1536), (2000, 10240, 2560)],
+            DEEP: [(200, 8192, 2048), (512, 4096, 1024), (2000, 1024, 2048), (1000, 2048, 4096)],
+            T64: [(512, 6144, 128), (384, 8192, 384), (200, 10240, 2560)]}.items():
+        for s in shapes:
+            assert tiles(*s) == kind, s
+    # not a multiple of 128: by the number of tiles alone
+    assert [tiles(M, 4000, 128) for M in (5000, 1500, 300)] == [T128, T64x128, T64] and tiles(300, 1000, 1000) == DEEP
+    for M in (128, 129, 255, 256, 257, 1000, 5000, 40000, 8388480):
+        for N in (128, 256, 384, 1024, 1152, 8192, 12288):
+            for K in (128, 384, 1024, 5120, 1 << 20):
+                kind = tiles(M, N, K)
+                assert 0 <= kind <= 5 and (kind != W256 or (M >= 256 and N % 256 == 0)), (M, N, K)
