@@ -389,7 +389,10 @@ state_step_conv_kernel(float *h_out, const float *h_in, const int32_t *__restric
 // 256 float4s apart, so every wavefront load or store is still one contiguous 1 KiB run; all
 // loads of the U pieces are issued before the first one is used, which keeps several KiB per
 // wavefront in flight (the step is a single pass over the state and lives on memory latency).
-template <typename T, int N, int U, bool HAS_Z, bool SOFTPLUS>
+// MORE: ranges of more than kParts partial sums (see there); the others do without that loop (+0.2 us for every launch).
+constexpr int kParts = 8;
+__host__ __device__ inline int xproj_sides(int xn, int n_parts) { return kBlock / (xn / 4) < n_parts ? kBlock / (xn / 4) : n_parts; }
+template <typename T, int N, int U, bool HAS_Z, bool SOFTPLUS, bool MORE>
 __global__ void __launch_bounds__(kBlock)
 state_step_xproj_kernel(float *h_out, const float *h_in, const int32_t *__restrict__ parent,
                   const T *__restrict__ x, const T *__restrict__ dt, const float *__restrict__ A,
@@ -419,9 +422,8 @@ state_step_xproj_kernel(float *h_out, const float *h_in, const int32_t *__restri
     // for first, so the first eight of a range are requested ahead of everything else (behind the state row they would
     // wait for the parent index): 12 x 1536 channels 4.6 -> 4.2 us, 3 x 1536 4.3 -> 3.8 us.  Longer ranges (wide models) go on
     // by eight: 1 x 5120 channels, 320 parts of 192 sums, 12.8 us against 21.3 one after the other, 32 x 5120 32.5 against 51.3.
-    constexpr int kParts = 8;
     const int xn = (int)dt_rank + 2 * N, xn4 = xn / 4;
-    const int sides = min(kBlock / xn4, n_parts);
+    const int sides = xproj_sides(xn, n_parts);
     const int side = (int)threadIdx.x / xn4, k4 = (int)threadIdx.x - side * xn4;
     const int per = (n_parts + sides - 1) / sides, first = side * per, last = min(first + per, n_parts);
     const bool adds = side < sides && first < last;
@@ -467,12 +469,14 @@ state_step_xproj_kernel(float *h_out, const float *h_in, const int32_t *__restri
 #pragma unroll
                 for (int u = 0; u < kParts; ++u)
                     if (first + u < last) add(pv[u]);
-                for (int c = first + kParts; c < last; c += kParts) {   // more of them (wide models): as many in flight again
+                if constexpr (MORE) {
+                    for (int c = first + kParts; c < last; c += kParts) {   // as many in flight again
 #pragma unroll
-                    for (int u = 0; u < kParts; ++u) pv[u] = pr[(int64_t)min(c + u, last - 1) * xn4];
+                        for (int u = 0; u < kParts; ++u) pv[u] = pr[(int64_t)min(c + u, last - 1) * xn4];
 #pragma unroll
-                    for (int u = 0; u < kParts; ++u)
-                        if (c + u < last) add(pv[u]);
+                        for (int u = 0; u < kParts; ++u)
+                            if (c + u < last) add(pv[u]);
+                    }
                 }
             }
             *reinterpret_cast<float4 *>(&xs_side[side * xn + 4 * k4]) = sum;
@@ -575,8 +579,9 @@ template <typename T, int N, int U> hipError_t launch_step_u(const StepArgs &a, 
         static_cast<const T *>(a.Bm), static_cast<const T *>(a.Cm), a.Dskip,                      \
         static_cast<const T *>(a.z), a.dt_bias, static_cast<T *>(a.out), a.n_in, a.D,                \
         static_cast<const bf16_t *>(a.dt_w), a.dt_rank)
-#define MAMBA_STEP_X(HZ, SP)                                                                      \
-    state_step_xproj_kernel<T, N, U, HZ, SP><<<grid, kBlock, 0, stream>>>(                        \
+#define MAMBA_STEP_X(HZ, SP) (more ? MAMBA_STEP_XM(HZ, SP, true) : MAMBA_STEP_XM(HZ, SP, false))
+#define MAMBA_STEP_XM(HZ, SP, MR)                                                                 \
+    state_step_xproj_kernel<T, N, U, HZ, SP, MR><<<grid, kBlock, 0, stream>>>(                    \
         a.h_out, a.h_in, a.parent, static_cast<const T *>(a.x), static_cast<const T *>(a.dt), a.A, \
         static_cast<const T *>(a.Bm), static_cast<const T *>(a.Cm), a.Dskip,                      \
         static_cast<const T *>(a.z), a.dt_bias, static_cast<T *>(a.out), a.n_in, a.D,                \
@@ -604,6 +609,8 @@ template <typename T, int N, int U> hipError_t launch_step_u(const StepArgs &a, 
         }
     }
     if (a.xpart && a.dt_w) {
+        const int sides = xproj_sides((int)a.dt_rank + 2 * N, a.n_parts);
+        const bool more = (a.n_parts + sides - 1) / sides > kParts;
         if (a.z) {
             if (a.dt_softplus) MAMBA_STEP_X(true, true);
             else MAMBA_STEP_X(true, false);
@@ -622,6 +629,7 @@ template <typename T, int N, int U> hipError_t launch_step_u(const StepArgs &a, 
     }
 #undef MAMBA_STEP
 #undef MAMBA_STEP_X
+#undef MAMBA_STEP_XM
     return hipGetLastError();
     } else {
         return hipErrorInvalidValue;   // eight float4s per lane exist for the plain step only
