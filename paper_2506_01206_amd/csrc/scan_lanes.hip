@@ -249,7 +249,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
     // With 2-byte elements everything a super-step needs is requested during the one before; with float32 (twice
     // the registers) only x and dt are, and z, B_t, C_t are fetched where they are used.
     constexpr bool kAhead = sizeof(T) == 2;
-    Row6<T> x_nxt, dt_nxt, z_nxt, x_cur, z_cur;
+    Row6<T> x_cur, z_cur;                                            // the super-step's own: kept for the gate
     constexpr int kChunkGroups = BcChunk<T>::kGroups;
     constexpr int kChunksPerRow = kParts / kChunkGroups;             // 2 (bf16) or 4 (float32)
     constexpr int kChunks = 2 * kT * kChunksPerRow;                  // B and C of a super-step
@@ -257,6 +257,11 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
     constexpr int kBcHeld = 3;                                       // chunks a thread holds at a time
     BcChunk<T> bc_nxt[kBcHeld];
 
+    // Addresses are a base of the super-step, which is uniform (scalar registers), and 32 bits of the thread's own (512 rows
+    // of the widest layer that takes this kernel, some 4600 channels, are far below that): with 64 bits of its own for
+    // every tensor the walk had to spill, and a kernel with scratch memory takes 0.4 us longer to start.
+    // The last token of a super-step, counted from its start; tokens past it re-read its row and are zeroed at use.
+    auto last_of = [&](int64_t t_base) { return (int)(L - 1 - t_base < kT - 1 ? L - 1 - t_base : kT - 1); };
     // chunk q of a super-step: (array, token, position in the row); `first`: 0, or 3 for the second half of float32
     auto fetch_bc = [&](int64_t t_base, int first) {
 #pragma unroll
@@ -264,9 +269,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
             const int q = tid + (first + it) * kThreadsL;
             if (kChunks % kThreadsL == 0 || q < kChunks) {
                 const int arr = q / (kT * kChunksPerRow), r = q % (kT * kChunksPerRow);
-                int64_t t = t_base + r / kChunksPerRow;
-                t = t < L ? t : L - 1;
-                bc_nxt[it].load((arr ? Cm : Bm) + (row0 + t) * kN + (r % kChunksPerRow) * (kN / kChunksPerRow));
+                bc_nxt[it].load((arr ? Cm : Bm) + (row0 + t_base) * kN + (uint32_t)(min(r / kChunksPerRow, last_of(t_base)) * kN + (r % kChunksPerRow) * (kN / kChunksPerRow)));
             }
         }
     };
@@ -285,19 +288,18 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
             }
         }
     };
-    auto fetch = [&](int64_t t_base) {
-        int64_t t = t_base + kTau * ti + tj;
-        t = t < L ? t : L - 1;                       // tokens past the end re-read the last one and are zeroed at use
-        const int64_t o = (row0 + t) * D + c0;
-        x_nxt.load(x + o);
-        dt_nxt.load(dt + o);
-        if constexpr (kAhead && HAS_Z) z_nxt.load(z + o);
+    auto fetch = [&](int64_t t_base, Row6<T> &xr, Row6<T> &dtr, Row6<T> &zr) {
+        const int64_t base = (row0 + t_base) * D + c0;
+        const uint32_t o = (uint32_t)min(kTau * ti + tj, last_of(t_base)) * (uint32_t)D;
+        xr.load(x + base + o);
+        dtr.load(dt + base + o);
+        if constexpr (kAhead && HAS_Z) zr.load(z + base + o);
     };
-    auto publish = [&](int64_t t_base) {
-        const bool valid = t_base + kTau * ti + tj < L;
+    auto publish = [&](int64_t t_base, const Row6<T> &xr, const Row6<T> &dtr) {
+        const bool valid = kTau * ti + tj <= last_of(t_base);
         float xv[kG], dv[kG];
-        x_nxt.unpack(xv);
-        dt_nxt.unpack(dv);
+        xr.unpack(xv);
+        dtr.unpack(dv);
 #pragma unroll
         for (int c = 0; c < kG; ++c) {
             const float v = dv[c] + lds_par[0][c];
@@ -306,15 +308,12 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
             reinterpret_cast<float *>(&lds_d[c][tj >> 2][ti])[tj & 3] = d;
             reinterpret_cast<float *>(&lds_u[c][tj >> 2][ti])[tj & 3] = d * xv[c];
         }
-        x_cur = x_nxt;
-        if constexpr (HAS_Z && kAhead) z_cur = z_nxt;
     };
     auto gate = [&](int64_t t_base, Out6<T> &o6) {   // the outputs of the super-step
         float xv[kG], zv[kG], ov[kG];
         x_cur.unpack(xv);
         if constexpr (HAS_Z && !kAhead) {
-            const int64_t t = t_base + kTau * ti + tj;
-            z_cur.load(z + (row0 + (t < L ? t : L - 1)) * D + c0);
+            z_cur.load(z + (row0 + t_base) * D + c0 + (uint32_t)min(kTau * ti + tj, last_of(t_base)) * (uint32_t)D);
         }
         if constexpr (HAS_Z) z_cur.unpack(zv);
 #pragma unroll
@@ -328,9 +327,8 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
         o6.pack(ov);
     };
     auto store = [&](int64_t t_base, const Out6<T> &o6) {
-        const int64_t t = t_base + kTau * ti + tj;
-        if (t >= L) return;
-        T *p = out + (row0 + t) * D + c0;
+        if (kTau * ti + tj > last_of(t_base)) return;
+        T *p = out + (row0 + t_base) * D + c0 + (uint32_t)(kTau * ti + tj) * (uint32_t)D;
         if (dead == 0) {
             o6.store(p);
         } else {
@@ -341,11 +339,14 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
     };
 
     const int64_t n_super = (L + kT - 1) / kT;
-    if (token_thread) fetch(0);
+    // (the first rows land where they stay: passed on through the registers of the next ones, the copy would wait for them here,
+    // before B and C are requested)
+    Row6<T> dt_first;
+    if (token_thread) fetch(0, x_cur, dt_first, z_cur);
     fetch_bc(0, 0);
     if (tid < 2 * kG) (&lds_par[0][0])[tid] = par;
     lds_barrier_l();   // the channel parameters are in LDS
-    if (token_thread) publish(0);
+    if (token_thread) publish(0, x_cur, dt_first);
     publish_bc(0);
     if constexpr (kBcIters > kBcHeld) {
         fetch_bc(0, kBcHeld);
@@ -353,10 +354,11 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
     }
     lds_barrier_l();
 
-    for (int64_t k = 0; k < n_super; ++k) {
+    for (int64_t k = 0; k < n_super; ++k) {                       // L >= 1: at least one
         const int64_t t_base = k * kT;
         const bool more = k + 1 < n_super;
-        if (token_thread && more) fetch(t_base + kT);
+        Row6<T> x_nxt, dt_nxt, z_nxt;
+        if (token_thread && more) fetch(t_base + kT, x_nxt, dt_nxt, z_nxt);
 
         // ---- 1. the lane's 8 tokens from zero (lane 0: from the state entering the super-step), decays kept
         // (delta and delta * x are taken from LDS four tokens at a time: fewer registers held at once)
@@ -415,6 +417,14 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
                 hp[r >> 2][r & 3] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(Hs[r]), 63));
             }
         }
+        // the final state leaves as soon as it is known, not behind the last outputs (a wavefront's own, as its part of h0 was)
+        if (!more && h_final && lane == 0 && ca >= dead) {
+#pragma unroll
+            for (int ch = 0; ch < 2; ++ch)
+#pragma unroll
+                for (int n = 0; n < 4; ++n)
+                    h_final[b * D * kN + (c0 + ca + ch) * kN + 4 * part + n] = hp[ch][n];
+        }
         // The next super-step's rows are requested here rather than at the top: their registers would otherwise be
         // held through the first walk, where the decays pile up; the second walk, the barrier and the gating of
         // this super-step's outputs are what their latency hides behind.
@@ -460,7 +470,11 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
         if (token_thread) {
             gate(t_base, o6);
             if constexpr (!kAhead) store(t_base, o6);   // (float32 has no registers to hold them in)
-            if (more) publish(t_base + kT);
+            if (more) {
+                publish(t_base + kT, x_nxt, dt_nxt);
+                x_cur = x_nxt;
+                if constexpr (HAS_Z && kAhead) z_cur = z_nxt;
+            }
         }
         if (more) {
             publish_bc(0);
@@ -473,14 +487,6 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
             if (token_thread) store(t_base, o6);
         }
         lds_barrier_l();   // the next super-step is in LDS
-    }
-
-    if (h_final && lane == 0 && ca >= dead) {
-#pragma unroll
-        for (int ch = 0; ch < 2; ++ch)
-#pragma unroll
-            for (int n = 0; n < 4; ++n)
-                h_final[b * D * kN + (c0 + ca + ch) * kN + 4 * part + n] = hp[ch][n];
     }
 }
 
