@@ -494,12 +494,15 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
 
 // Shapes the lane-scan kernel serves: 16 states, token rows that can be read in 4-byte pieces from any even
 // channel, at least one full workgroup; and among those the ones it is expected to finish before the two-pass
-// kernels of scan.hip.  Its time is rounds x (about 6 us + 11.6 ns per token), a round being 256 workgroups of 6
-// channels (every workgroup walks the whole sequence); the two-pass kernels take about 24 us + 9.8 ns per token
-// and 1536 channels.  Measured in one run, lanes against two-pass, 1536 channels: 9000 tokens 113 against 121 us; two sequences of 3000 tokens 72 against 79; 768
-// channels x 2000 tokens 25 against 30, x 600 tokens 15 against 21.  Before either had its waits for stores taken out: 32768
-// tokens 461 against 353, two sequences of 4096 102 against 101, 768 channels x 4096 tokens 48 against 44, 2048 channels (342
-// workgroups, two rounds) x 4096 tokens 105 against 76.
+// kernels of scan.hip.  Its time is a number of rounds of 256 workgroups of 6 channels, every one walking the whole sequence;
+// that of the two-pass kernels goes with all tokens.  Measured over 358 shapes: a round of the lanes takes 7.3 us + 10.0 ns a
+// token in bf16, 6.9 us + 13.1 ns in float32, the two passes 19.3 us + 10.2 ns a token and 1536 channels, 18.4 us + 9.8 ns.
+// The line (6 us + 11.6 ns against 24 us + 9.8 ns) lies between the two types, since the choice, and with it the size of
+// the workspace, is not told the type.  us, lanes / two-pass, bf16 | float32; * what the line takes:
+//   1 x  600 x  768  16.4*/ 22.2 | 16.8*/ 21.3       1 x 2048 x 1536  28.6*/ 41.1 | 34.0*/ 39.1       1 x   64 x 4096  22.7*/ 19.8 |  22.9*/ 19.1
+//   1 x 2048 x  768  26.8*/ 31.8 | 31.7*/ 31.0       1 x 6000 x 1536  69.3*/ 79.8 | 86.4*/ 75.0       1 x 8192 x 1536  90.0*/ 99.4 | 113.4*/ 92.9
+//   1 x 3000 x  768  37.2 / 41.0*| 44.6 / 37.2*      2 x 3000 x 1536  73.1*/ 79.2 | 88.2*/ 74.7       1 x 10240 x 1536 110.7 / 119.0*| 141.9 / 111.7*
+//   1 x 4096 x 2048 104.9 / 74.9*| 111.3 / 69.4*     2 x 4096 x 1536  93.6 / 99.0*| 115.0 / 92.4*     1 x 16384 x 1536 172.9 / 178.6*| 249.1 / 167.1*
 bool scan_lanes_applies(int64_t batch, int64_t L, int64_t D, int64_t N)
 {
     if (N != kN || D % 2 != 0 || D < kG || L < 64 || batch > 65535) return false;
