@@ -425,8 +425,8 @@ def test_block_validation_and_workspace(b):
     need_prefill = ws_bytes(ctypes.byref(p), 1, 2048)
     need_step = ws_bytes(ctypes.byref(p), 12, 1)
     assert need_prefill >= 4 * 2048 * 1536 * 2 and need_step >= 4 * 12 * 1536 * 2
-    # one token on a few rows also holds the partial sums of the x projection: (d_inner / 32, rows, dt_rank + 2 N) floats
-    assert need_step >= 4 * 12 * 1536 * 2 + (1536 // 32) * 12 * 80 * 4
+    # one token on a few rows also holds the partial sums of the x projection: (rows, d_inner / 16, dt_rank + 2 N) floats
+    assert need_step >= 4 * 12 * 1536 * 2 + (1536 // 16) * 12 * 80 * 4
     assert ws_bytes(ctypes.byref(p), 12, 1) < ws_bytes(ctypes.byref(p), 24, 1)
     assert ws_bytes(ctypes.byref(p), 0, 1) == 0 and ws_bytes(ctypes.byref(p), 1, 0) == 0
     assert ws_bytes(ctypes.byref(_block_params(b, N=5)), 1, 64) == 0 and ws_bytes(ctypes.byref(_block_params(b, dm=772)), 1, 64) == 0
