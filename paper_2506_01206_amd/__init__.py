@@ -1,6 +1,6 @@
 """MI355X-native selective-SSM layer core of a Mamba drafter (gfx950 HIP kernels behind a C ABI).
 
-``paper_2506_01206_amd.binding`` holds the ctypes binding of the C-ABI library
+``paper_2506_01206_amd.binding`` holds the Python binding of the C-ABI library
 (mamba_conv1d_fwd, mamba_scan_fwd, mamba_state_step, mamba_state_fork);
 ``paper_2506_01206_amd.synth`` the seeded input generators.  The binding is
 imported on first attribute access so that the generators stay usable where
