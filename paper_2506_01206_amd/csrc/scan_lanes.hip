@@ -30,7 +30,8 @@
 // thread (j, i) of the first 8 wavefronts owns token 8 i + j of the super-step, all 6 channels (B_t and C_t are
 // fetched by all threads in consecutive 16-byte pieces);
 // operands go to LDS as float32 in layouts in which consecutive lanes touch consecutive 16-byte slots.
-// The next super-step's rows are requested before the second walk of the current one and used after it.
+// The next super-step's rows are requested at the start of the current one, its B_t and C_t before the second walk (float32: where
+// they are used); both are used after that.
 #include "device_math.h"
 #include "launch.h"
 
@@ -425,9 +426,9 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
                 for (int n = 0; n < 4; ++n)
                     h_final[b * D * kN + (c0 + ca + ch) * kN + 4 * part + n] = hp[ch][n];
         }
-        // The next super-step's rows are requested here rather than at the top: their registers would otherwise be
-        // held through the first walk, where the decays pile up; the second walk, the barrier and the gating of
-        // this super-step's outputs are what their latency hides behind.
+        // The next super-step's B and C are requested here rather than with its rows at the top: their registers would
+        // otherwise be held through the first walk, where the decays pile up; the second walk, the barrier and the gating
+        // of this super-step's outputs are what their latency hides behind.
         if (more) {
             if constexpr (kAhead) fetch_bc(t_base + kT, 0);
         }
