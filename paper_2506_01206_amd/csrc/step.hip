@@ -238,147 +238,133 @@ state_step_shared_kernel(float *h_out, const float *h_in, const int32_t *__restr
     }
 }
 
+// H carried inputs of a channel (or K taps), one run of memory: moved as widely as its alignment allows.
+template <typename T, int COUNT> struct Run { T v[COUNT]; };
+template <typename T, int COUNT> __device__ __forceinline__ Run<T, COUNT> ld_run(const T *p)
+{
+    Run<T, COUNT> r;
+    __builtin_memcpy(&r, p, sizeof(r));
+    return r;
+}
+__device__ __forceinline__ float as_f32(float v) { return v; }
+__device__ __forceinline__ float as_f32(bf16_t v) { return bf16_to_f32(v); }
+__device__ __forceinline__ float from_lane(float v, unsigned byte_of_lane) { return __int_as_float(__builtin_amdgcn_ds_bpermute((int)byte_of_lane, __float_as_int(v))); }
+
 // Fork, conv step and state update of one layer in a single launch (Sec. 4.1: a child continues from its parent's
 // states; the draft loop of a tree is this, once per layer and position).  x is the input *before* the conv:
 //   win = conv_src[p, d, :];  a = conv_bias[d] + sum_k w[d,k] win[k] + w[d,K-1] x[j,d];  x_c = silu(a)
 //   conv_dst[j, d, :] = (win[1..], x[j,d]);  then the step above on x_c rounded to the I/O type
 // in the arithmetic order of the conv kernel and of the step kernel, so that the result is bit for bit what
 // mamba_conv1d_fwd (L = 1, on the window gathered by parent) followed by mamba_state_step gives.
-// The workgroup's channels (256 U / (N/4) of them) are convolved first, one channel per thread: window, taps,
-// bias and input are loaded once per channel, not once per lane (with the conv evaluated by every lane of a channel
-// the wide step was bound by the issue of its many small loads: 17.7 us against 13.1 us for two launches); x_c goes
-// through LDS to the lanes that own the channel's states, whose state rows are already on their way by then.
-// (Forming the step's token-side values per channel in the same loop, as state_step_shared_kernel does, helped one
-// shape and cost three -- 64 x 4096: 9.4 -> 8.7 us, 32 x 1536: 3.7 -> 4.0, 128 x 4096: 17.9 -> 19.8 -- and is not done.)
-// grid: (ceil(D * N / 4 / (256 * U)), n_out)
-template <typename T, int N, int U, bool HAS_Z, bool SOFTPLUS>
-__global__ void __launch_bounds__(kBlock)
-state_step_conv_kernel(float *h_out, const float *h_in, const int32_t *__restrict__ parent,
-                       const T *__restrict__ x, const T *__restrict__ dt, const float *__restrict__ A,
-                       const T *__restrict__ Bm, const T *__restrict__ Cm,
-                       const float *__restrict__ Dskip, const T *__restrict__ z,
-                       const float *__restrict__ dt_bias, T *__restrict__ out, int64_t n_in, int64_t D,
-                       const float *__restrict__ conv_w, const float *__restrict__ conv_bias, const T *conv_src,
-                       T *conv_dst, T *__restrict__ xc_out, int conv_k, int conv_silu)
+// A wavefront owns 64 P / Q adjacent channels of a branch (Q = N / 4) in two layouts.  Channel layout (a lane per channel):
+// everything that there is once per channel, i.e. window, taps, input, dt, z and the parameters, the conv, softplus, the gate
+// and the stores of window and output.  State layout: piece i of P is the float4s 64 i .. 64 i + 63 of the channels' states,
+// one contiguous KiB; lane l of it works on channel (64 i + l) / Q.  delta * log2(e) and delta * x go from the first to the
+// second by one lane permutation each per piece, the sums come back by one: no LDS memory, no barrier.
+// What bounds a launch of a few branches is a wavefront's own chain, parent index -> state row -> arithmetic -> store, and the
+// instructions in it: with every lane of a channel doing the channel's work (five small loads, softplus and gate four
+// times) and the conv in one wavefront of a workgroup behind a barrier 32 x 1536 took 3.71 us in a replayed graph and 64 x
+// 4096 9.39; now 3.33 and 8.74, where a bare copy of the same state rows takes 2.4 and 7.6 and an empty launch 1.6.
+// grid: (ceil(D / (64 P / Q)), n_out)
+template <typename T, int N, int K, int P, bool HAS_Z, bool SOFTPLUS>
+__global__ void __launch_bounds__(64)
+state_step_conv_kernel(const int32_t *__restrict__ parent, const float *h_in, const T *conv_src, const T *__restrict__ x,
+                       const float *__restrict__ A, const T *__restrict__ dt, const T *__restrict__ z,
+                       const T *__restrict__ Bm, const T *__restrict__ Cm, const float *__restrict__ conv_w,
+                       const float *__restrict__ conv_bias, const float *__restrict__ dt_bias, const float *__restrict__ Dskip,
+                       float *h_out, T *conv_dst, T *__restrict__ out, T *__restrict__ xc_out, int64_t n_in, uint32_t D, int conv_silu)
 {
-    constexpr int Q = N / 4;
-    constexpr int kChannels = kBlock * U / Q;                     // channels whose states this workgroup owns
-    __shared__ float xs[kChannels];
-    const int H = conv_k - 1;                                     // 1 .. 3 carried inputs per channel
-    const int64_t j = blockIdx.y;
-    const int64_t row4 = D * Q;  // float4s per branch
-    const int64_t d_lo = (int64_t)blockIdx.x * kChannels;
-    const float4 *a4 = reinterpret_cast<const float4 *>(A);
+    constexpr int Q = N / 4, H = K - 1;
+    constexpr unsigned kPer = 64 / Q, kCh = kPer * P;             // channels of a piece and of the wavefront
+    const unsigned lane = threadIdx.x, j = blockIdx.y, d0 = blockIdx.x * kCh;
+    const int32_t parent_in = (parent ? parent : reinterpret_cast<const int32_t *>(A))[parent ? j : 0];
+    const unsigned nd = min(D - d0, kCh);
+    const unsigned c = min(lane % kCh, nd - 1);                   // (offsets of a lane are 32 bits from a scalar base)
+    const bool live = lane < nd;
+    const int64_t row = (int64_t)((uint64_t)j * D + d0);
 
-    int64_t f[U], d[U];
-    bool live[U];
-    float4 h[U], a[U], bv[U], cv[U];
-    float dv[U], zv[U], bias[U], dsk[U];
+    // what does not depend on the parent index
+    const T xr = (x + row)[c], dtr = (dt + row)[c];
+    T zr{};
+    if constexpr (HAS_Z) zr = (z + row)[c];
+    const Run<float, K> taps = ld_run<float, K>(conv_w + (uint64_t)d0 * K + c * K);
+    const float cb_in = ((conv_bias ? conv_bias : A) + d0)[c], bias_in = ((dt_bias ? dt_bias : A) + d0)[c], dsk_in = ((Dskip ? Dskip : A) + d0)[c];
+    const unsigned q = lane % Q;                                  // 64 i is a multiple of Q: the same for all pieces
+    const Run<T, 4> br = ld_run<T, 4>(static_cast<const T *>(__builtin_assume_aligned(Bm + j * N + 4 * q, 4 * sizeof(T))));
+    const Run<T, 4> cr = ld_run<T, 4>(static_cast<const T *>(__builtin_assume_aligned(Cm + j * N + 4 * q, 4 * sizeof(T))));
+    unsigned f[P];
+    float4 h[P], a[P];
+    const float4 *a4 = reinterpret_cast<const float4 *>(A) + (uint64_t)d0 * Q;
 #pragma unroll
-    for (int i = 0; i < U; ++i) {
-        const int64_t f_raw = ((int64_t)blockIdx.x * U + i) * kBlock + threadIdx.x;
-        live[i] = f_raw < row4;
-        f[i] = live[i] ? f_raw : row4 - 1;
-        d[i] = f[i] / Q;
-        const int q = (int)(f[i] - d[i] * Q);
+    for (unsigned i = 0; i < P; ++i) {
+        f[i] = min(64 * i + lane, nd * Q - 1);
         a[i] = a4[f[i]];
-        bv[i] = ld4_io<N>(Bm + j * N + 4 * q);
-        cv[i] = ld4_io<N>(Cm + j * N + 4 * q);
-        dv[i] = ld_io(dt, j * D + d[i]);
-        zv[i] = HAS_Z ? ld_io(z, j * D + d[i]) : 0.0f;
-        bias[i] = dt_bias ? dt_bias[d[i]] : 0.0f;
-        dsk[i] = Dskip ? Dskip[d[i]] : 0.0f;
     }
-    // the state row and the window are the loads that have to wait for the parent index
-    const int64_t p = parent ? (int64_t)parent[j] : j;
+    // the window and the state rows
+    const int64_t p = parent ? (int64_t)parent_in : (int64_t)j;
     const bool p_ok = p >= 0 && p < n_in;
-    const float4 *hin4 = reinterpret_cast<const float4 *>(h_in) + (p_ok ? p : 0) * row4;
+    const uint64_t pd = (uint64_t)(p_ok ? (uint32_t)p : 0u) * D + d0;
+    const Run<T, H> win = ld_run<T, H>(conv_src + pd * H + c * H);
+    const float4 *hin4 = reinterpret_cast<const float4 *>(h_in) + pd * Q;
 #pragma unroll
-    for (int i = 0; i < U; ++i) h[i] = ld_stream(hin4 + f[i]);
+    for (int i = 0; i < P; ++i) h[i] = ld_stream(hin4 + f[i]);
+    __builtin_amdgcn_sched_barrier(0);                            // all of it in flight before any of it is used
 
-    // conv step, one channel per thread, same order of operations as the conv kernel: bias, taps oldest to newest,
-    // then the new input
+    // conv step, same order of operations as the conv kernel: bias, taps oldest to newest, the new input last
     const float nan = __int_as_float(0x7fc00000);
-    for (int c = threadIdx.x; c < kChannels; c += kBlock) {
-        const int64_t dc = d_lo + c;
-        if (dc >= D) break;
-        // With one float4 per lane (few branches: the launch lives on latency) every fetch is unconditional, a tap
-        // the window does not have re-reads its last one and is dropped afterwards: a load under a condition is
-        // waited for inside its branch, one memory latency after the other.  With several float4s per lane (many
-        // branches: the launch lives on bandwidth) the conditional form measured faster (64 x 4096: 9.4 against
-        // 10.7 us), so it stays there.
-        float wk[4], carried[3];
-        const T *win = conv_src + ((p_ok ? p : 0) * D + dc) * H;
-        if constexpr (U == 1) {
+    const float xpre = as_f32(xr);
+    float acc = conv_bias ? cb_in : 0.0f;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const float v = conv_w[dc * conv_k + (k <= H ? k : H)];
-                wk[k] = k <= H ? v : 0.0f;
-            }
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const float v = ld_io(win, k < H ? k : H - 1);
-                carried[k] = k < H ? v : 0.0f;
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) wk[k] = k <= H ? conv_w[dc * conv_k + k] : 0.0f;
-#pragma unroll
-            for (int k = 0; k < 3; ++k) carried[k] = k < H ? ld_io(win, k) : 0.0f;
-        }
-        const float xpre = ld_io(x, j * D + dc);
-        float acc = conv_bias ? conv_bias[dc] : 0.0f;
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-            if (k < H) acc = fmaf(wk[k], carried[k], acc);
-        float wlast = wk[0];
-#pragma unroll
-        for (int k = 1; k < 4; ++k)
-            if (k == H) wlast = wk[k];
-        acc = fmaf(wlast, xpre, acc);
-        const float xc = conv_silu ? silu_f32(acc) : acc;
-        // the stored tensor the step would read
-        xs[c] = sizeof(T) == 2 ? bf16_to_f32(f32_to_bf16(xc)) : xc;
+    for (int k = 0; k < H; ++k) acc = fmaf(taps.v[k], as_f32(win.v[k]), acc);
+    acc = fmaf(taps.v[H], xpre, acc);
+    const float xc = conv_silu ? silu_f32(acc) : acc;
+    const float xv = sizeof(T) == 2 ? bf16_to_f32(f32_to_bf16(xc)) : xc;    // the stored tensor the step would read
+    if (live) {
         // new window: the carried inputs move up, the new input comes last (NaN in front where the parent was bad)
-        T *nwin = conv_dst + (j * D + dc) * H;
+        Run<T, H> nwin;
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
-            if (k + 1 < H) st_io(nwin, k, p_ok ? carried[k + 1] : nan);
-        st_io(nwin, H - 1, xpre);
-        if (xc_out) st_io(xc_out, j * D + dc, p_ok ? xc : nan);
+        for (int k = 0; k + 1 < H; ++k) {
+            nwin.v[k] = win.v[k + 1];
+            if (!p_ok) st_io(nwin.v, k, nan);
+        }
+        nwin.v[H - 1] = xr;
+        __builtin_memcpy(conv_dst + row * H + c * H, &nwin, sizeof(nwin));
+        if (xc_out) st_io(xc_out + row, c, p_ok ? xc : nan);
     }
-    __syncthreads();
 
+    const float v = as_f32(dtr) + (dt_bias ? bias_in : 0.0f);
+    const float delta = SOFTPLUS ? softplus_f32(v) : v;
+    // (a bad parent's states and output become NaN through the input term; x + -0 is x, its sign included)
+    const float u = delta * xv + (p_ok ? -0.0f : nan);
+    const float dl = delta * kLog2e;
+    float bv[4], cv[4], y = 0.0f;
 #pragma unroll
-    for (int i = 0; i < U; ++i) {
-        const float xv = xs[d[i] - d_lo];
-        const float v = dv[i] + bias[i];
-        const float delta = SOFTPLUS ? softplus_f32(v) : v;
-        const float u = delta * xv;
-        const float dl = delta * kLog2e;
-        float4 hh = h[i];
-        hh.x = fmaf(exp2_hw(dl * a[i].x), hh.x, u * bv[i].x);
-        hh.y = fmaf(exp2_hw(dl * a[i].y), hh.y, u * bv[i].y);
-        hh.z = fmaf(exp2_hw(dl * a[i].z), hh.z, u * bv[i].z);
-        hh.w = fmaf(exp2_hw(dl * a[i].w), hh.w, u * bv[i].w);
-        float y = hh.x * cv[i].x;
-        y = fmaf(hh.y, cv[i].y, y);
-        y = fmaf(hh.z, cv[i].z, y);
-        y = fmaf(hh.w, cv[i].w, y);
-        y = channel_sum<Q>(y);
-        if (!p_ok) {
-            hh = make_float4(nan, nan, nan, nan);
-            y = nan;
-        }
-        if (live[i]) {
-            st_stream(reinterpret_cast<float4 *>(h_out) + j * row4 + f[i], hh);
-            if (f[i] - d[i] * Q == 0) {
-                y = fmaf(dsk[i], xv, y);
-                if constexpr (HAS_Z) y *= silu_f32(zv[i]);
-                st_io(out, j * D + d[i], y);
-            }
-        }
+    for (int k = 0; k < 4; ++k) {
+        bv[k] = as_f32(br.v[k]);
+        cv[k] = as_f32(cr.v[k]);
     }
+    float4 *hout4 = reinterpret_cast<float4 *>(h_out) + row * Q;
+#pragma unroll
+    for (unsigned i = 0; i < P; ++i) {
+        const unsigned from = (lane / Q + i * kPer) * 4;
+        const float dli = Q == 1 ? dl : from_lane(dl, from), ui = Q == 1 ? u : from_lane(u, from);
+        float4 hh = h[i];
+        hh.x = fmaf(exp2_hw(dli * a[i].x), hh.x, ui * bv[0]);
+        hh.y = fmaf(exp2_hw(dli * a[i].y), hh.y, ui * bv[1]);
+        hh.z = fmaf(exp2_hw(dli * a[i].z), hh.z, ui * bv[2]);
+        hh.w = fmaf(exp2_hw(dli * a[i].w), hh.w, ui * bv[3]);
+        float yi = hh.x * cv[0];
+        yi = fmaf(hh.y, cv[1], yi);
+        yi = fmaf(hh.z, cv[2], yi);
+        yi = fmaf(hh.w, cv[3], yi);
+        yi = channel_sum<Q>(yi);
+        y = q == i ? yi : y;                                      // all Q lanes of a channel have it: lane q keeps piece q's
+        if (64 * i + lane < nd * Q) st_stream(hout4 + f[i], hh);
+    }
+    y = Q == 1 ? y : from_lane(y, (lane % kPer * Q + lane / kPer) * 4);
+    y = fmaf(Dskip ? dsk_in : 0.0f, xv, y);
+    if constexpr (HAS_Z) y *= silu_f32(as_f32(zr));
+    if (live) st_io(out + row, c, y);
 }
 
 // The same step for a draft position of the whole block, where the x projection arrives as partial sums (see
@@ -556,7 +542,7 @@ template <typename T, int N, int U> hipError_t launch_step_u(const StepArgs &a, 
     const int64_t row4 = a.D * (N / 4);
     const int64_t per_block = (int64_t)kBlock * U;
     dim3 grid((unsigned)((row4 + per_block - 1) / per_block), (unsigned)a.n_out);
-    if (U > 1 && !a.dt_w && !a.conv_w) {
+    if (U > 1 && !a.dt_w) {
 #define MAMBA_STEP_S(HZ, SP)                                                                      \
     state_step_shared_kernel<T, N, U, HZ, SP><<<grid, kBlock, 0, stream>>>(                       \
         a.h_out, a.h_in, a.parent, static_cast<const T *>(a.x), static_cast<const T *>(a.dt), a.A, \
@@ -586,28 +572,6 @@ template <typename T, int N, int U> hipError_t launch_step_u(const StepArgs &a, 
         static_cast<const T *>(a.Bm), static_cast<const T *>(a.Cm), a.Dskip,                      \
         static_cast<const T *>(a.z), a.dt_bias, static_cast<T *>(a.out), a.n_in, a.D,                \
         static_cast<const bf16_t *>(a.dt_w), a.dt_rank, a.xpart, a.n_parts)
-    if (a.conv_w) {
-        if constexpr (U == 2) {
-            return hipErrorInvalidValue;                          // the conv variant is built for U = 1 and 4 only (see launch_step_n)
-        } else {
-#define MAMBA_STEP_C(HZ, SP)                                                                      \
-    state_step_conv_kernel<T, N, U, HZ, SP><<<grid, kBlock, 0, stream>>>(                         \
-        a.h_out, a.h_in, a.parent, static_cast<const T *>(a.x), static_cast<const T *>(a.dt), a.A, \
-        static_cast<const T *>(a.Bm), static_cast<const T *>(a.Cm), a.Dskip,                      \
-        static_cast<const T *>(a.z), a.dt_bias, static_cast<T *>(a.out), a.n_in, a.D, a.conv_w,   \
-        a.conv_bias, static_cast<const T *>(a.conv_src), static_cast<T *>(a.conv_dst),             \
-        static_cast<T *>(a.xc_out), a.conv_k, a.conv_silu)
-            if (a.z) {
-                if (a.dt_softplus) MAMBA_STEP_C(true, true);
-                else MAMBA_STEP_C(true, false);
-            } else {
-                if (a.dt_softplus) MAMBA_STEP_C(false, true);
-                else MAMBA_STEP_C(false, false);
-            }
-#undef MAMBA_STEP_C
-            return hipGetLastError();
-        }
-    }
     if (a.xpart && a.dt_w) {
         const int sides = xproj_sides((int)a.dt_rank + 2 * N, a.n_parts);
         const bool more = (a.n_parts + sides - 1) / sides > kParts;
@@ -636,16 +600,51 @@ template <typename T, int N, int U> hipError_t launch_step_u(const StepArgs &a, 
     }
 }
 
+template <typename T, int N, int K, int P> hipError_t launch_step_conv(const StepArgs &a, hipStream_t stream)
+{
+    constexpr int kCh = 64 / (N / 4) * P;
+    const dim3 grid((unsigned)((a.D + kCh - 1) / kCh), (unsigned)a.n_out);
+#define MAMBA_STEP_C(HZ, SP)                                                                      \
+    state_step_conv_kernel<T, N, K, P, HZ, SP><<<grid, 64, 0, stream>>>(                             \
+        a.parent, a.h_in, static_cast<const T *>(a.conv_src), static_cast<const T *>(a.x), a.A,   \
+        static_cast<const T *>(a.dt), static_cast<const T *>(a.z), static_cast<const T *>(a.Bm),  \
+        static_cast<const T *>(a.Cm), a.conv_w, a.conv_bias, a.dt_bias, a.Dskip, a.h_out,         \
+        static_cast<T *>(a.conv_dst), static_cast<T *>(a.out), static_cast<T *>(a.xc_out), a.n_in, (uint32_t)a.D, a.conv_silu)
+    if (a.z) {
+        if (a.dt_softplus) MAMBA_STEP_C(true, true);
+        else MAMBA_STEP_C(true, false);
+    } else {
+        if (a.dt_softplus) MAMBA_STEP_C(false, true);
+        else MAMBA_STEP_C(false, false);
+    }
+#undef MAMBA_STEP_C
+    return hipGetLastError();
+}
+
 template <typename T, int N> hipError_t launch_step_n(const StepArgs &a, hipStream_t stream)
 {
+    if (a.conv_w) {
+        // Four pieces per wavefront, two while those come to no more than one wavefront per SIMD.  us a launch in a
+        // replayed graph on 4 / 2 pieces: 4 x 768 2.43 / 2.23, 32 x 768 3.16 / 2.99, 32 x 1536 3.33 / 3.38, 64 x 1536 4.73 /
+        // 5.00, 64 x 4096 8.74 / 9.18, 128 x 4096 14.90 / 16.18
+        constexpr int Q = N / 4, kFew = Q < 2 ? Q : 2, kMany = Q < 4 ? Q : 4;
+        if (a.D > UINT32_MAX) return hipErrorInvalidValue;
+        const bool few = a.n_out * ((a.D + 64 / Q * kFew - 1) / (64 / Q * kFew)) <= 1024;
+        switch (a.conv_k) {
+        case 2: return few ? launch_step_conv<T, N, 2, kFew>(a, stream) : launch_step_conv<T, N, 2, kMany>(a, stream);
+        case 3: return few ? launch_step_conv<T, N, 3, kFew>(a, stream) : launch_step_conv<T, N, 3, kMany>(a, stream);
+        case 4: return few ? launch_step_conv<T, N, 4, kFew>(a, stream) : launch_step_conv<T, N, 4, kMany>(a, stream);
+        default: return hipErrorInvalidValue;
+        }
+    }
     // several float4s per lane as long as that still leaves about three workgroups per CU
     const int64_t row4 = a.D * (N / 4);
     auto blocks = [&](int u) { return a.n_out * ((row4 + kBlock * u - 1) / (kBlock * u)); };
     // the plain step with eight per lane while that gives between 1.5 and 4 workgroups per CU: 64 branches x 4096
     // channels 8.7 -> 7.6 us, the time of a bare copy of the same state rows; 128 branches are better off with four
-    if (!a.conv_w && !a.dt_w && blocks(8) >= 384 && blocks(8) < 1024) return launch_step_u<T, N, 8>(a, stream);
+    if (!a.dt_w && blocks(8) >= 384 && blocks(8) < 1024) return launch_step_u<T, N, 8>(a, stream);
     if (blocks(kStepUnroll) >= 768) return launch_step_u<T, N, kStepUnroll>(a, stream);
-    if (kStepUnroll > 2 && blocks(2) >= 768 && !a.conv_w) return launch_step_u<T, N, 2>(a, stream);
+    if (kStepUnroll > 2 && blocks(2) >= 768) return launch_step_u<T, N, 2>(a, stream);
     return launch_step_u<T, N, 1>(a, stream);
 }
 

@@ -534,6 +534,28 @@ def test_conv_state_step_equals_conv_then_step(m, io, N, D, K):
     assert torch.equal(h, ho) and torch.equal(c, cst) and torch.equal(o, o2)
 
 
+@pytest.mark.parametrize("N", [4, 8, 16, 32])
+@pytest.mark.parametrize("n_out,D", [(1, 1), (3, 7), (2, 17), (5, 64), (4, 65), (1, 127), (520, 33), (350, 129), (1030, 16)])
+def test_conv_state_step_edges_of_a_wavefront(m, N, n_out, D):
+    """Channel counts around what a wavefront owns (8 to 64), on both sides of the line between two and four pieces of
+    states per wavefront (1024 wavefronts with two), bit for bit against conv step and state step."""
+    K, n_in = 4, 3
+    for io in (synth.F32, synth.BF16):
+        say(N=N, n_out=n_out, D=D, io=io)
+        rng = np.random.default_rng(N + 100 * D + n_out)
+        P = {k: to_dev(v) for k, v in synth.layer_params(rng, D, N, K, random_A=True).items()}
+        g = {k: to_dev(v) for k, v in synth.token_inputs(rng, (n_out,), D, N, io).items()}
+        h_in = to_dev(rng.standard_normal((n_in, D, N)).astype(np.float32))
+        c_in = to_dev(synth.to_io(rng.standard_normal((n_in, D, K - 1)).astype(np.float32), io))
+        par = to_dev(rng.integers(0, n_in, n_out).astype(np.int32))
+        forked, _ = m.mamba_state_fork(c_in.unsqueeze(0), None, par)
+        xc, cst = m.mamba_conv1d_fwd(g["x"].unsqueeze(1), P["conv_w"], P["conv_bias"], conv_state_in=forked[0])
+        ho, o = m.mamba_state_step(h_in, xc.squeeze(1), g["dt"], P["A"], g["Bm"], g["Cm"], P["Dskip"], g["z"], P["dt_bias"], parent_idx=par)
+        ho2, cst2, o2, xc2 = m.mamba_conv_state_step(h_in, c_in, g["x"], P["conv_w"], P["conv_bias"], g["dt"], P["A"], g["Bm"], g["Cm"],
+                                                     P["Dskip"], g["z"], P["dt_bias"], parent_idx=par, want_xc=True)
+        assert torch.equal(ho, ho2) and torch.equal(o, o2) and torch.equal(cst, cst2) and torch.equal(xc.squeeze(1), xc2)
+
+
 def test_step_rejects_out_of_range_parent_without_reading(m):
     D, N = 64, 16
     rng = np.random.default_rng(0)
