@@ -13,7 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmamba_hip.so")
 MARSHAL = os.path.join(HERE, "_marshal.so")
-SOURCES = ["api.cpp", "sd_tree_search.cpp", "conv1d.hip", "scan.hip", "scan_direct.hip", "scan_lanes.hip", "strided.hip", "step.hip", "fork.hip", "linear.hip", "xdt.hip", "norm.hip", "vocab.hip", "ssd.hip"]
+SOURCES = ["api.cpp", "sd_tree_search.cpp", "conv1d.hip", "scan.hip", "scan_direct.hip", "scan_lanes.hip", "strided.hip", "step.hip", "fork.hip", "linear.hip", "draft_in.hip", "xdt.hip", "norm.hip", "vocab.hip", "ssd.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-fp32 VALU instructions are switched off for every device function.  The first 14 dwords of a kernel's arguments come in
 # registers instead of through a scalar load (a trip to the cache that every address waits for): 0.13 us of each of the launches

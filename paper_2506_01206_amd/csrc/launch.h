@@ -180,6 +180,7 @@ struct LinearArgs {
     int xproj_n = 0;
 };
 hipError_t launch_linear(const LinearArgs &a, hipStream_t stream);
+hipError_t launch_draft_in(const LinearArgs &a, hipStream_t stream);   // what launch_linear does with norm_w
 
 // x_proj and dt_proj of a context as one kernel: [dtl | bm | cm] = xc wx^T, dt = dtl wdt^T, all bf16.
 // xc, dt: (M, d_inner); wx: (dt_rank + 2 N, d_inner); wdt: (d_inner, dt_rank); dtl: (M, dt_rank); bm, cm: (M, N).

@@ -50,24 +50,6 @@ struct OutSplit {
     int64_t width[3];
 };
 
-// one step of the depthwise causal conv + SiLU applied to the first output tensor on its way out
-struct ConvTail {
-    const float *w, *bias;      // (channels, k), (channels) or nullptr; w == nullptr: no conv
-    const bf16_t *src;          // (rows_in, channels, k - 1) carried windows
-    bf16_t *dst;                // (M, channels, k - 1)
-    const int32_t *parent;      // row m continues from src[parent[m]]; nullptr: src[m]
-    int64_t n_in;
-    int k;
-};
-
-// the next projection applied to the first output tensor on its way out, as partial sums per column block
-struct XprojTail {
-    const bf16_t *w;            // (n, ldw) bf16; nullptr: off
-    float *part;                // (M, n, column blocks of the first output tensor)
-    int n;
-    int64_t ldw;                // row length of w = width of the first output tensor
-};
-
 // column n of the virtual (M, N) output -> tensor and column inside it
 __device__ __forceinline__ int locate(const OutSplit &o, int64_t n, int64_t *col)
 {
@@ -600,59 +582,34 @@ linear_split_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, 
 }
 
 // ---------------------------------------------------------------------------------------------------
-// A draft position (M <= 64 rows, Sec. 4.1): w is read once, nothing is big, and what counts is the number of trips to
-// memory and of barriers between the launch and the last store.  One workgroup per 16 output columns (192 of them for
-// in_proj, twice what 32 columns give) and 16 MT rows, its eight wavefronts share the k range in contiguous pieces of steps.
+// A draft position (M <= 64 rows, Sec. 4.1; the way into a block is draft_in.hip): w is read once, nothing is big, and what counts
+// is the number of trips to memory and of barriers between the launch and the last store.  One workgroup per 16 output columns and
+// 16 MT rows, its eight wavefronts share the k range in contiguous pieces of steps.
 // A fragment of v_mfma_f32_16x16x32_bf16 wants row l % 16 in lane l; loaded like that, no two lanes of a quad share a
 // 64-byte piece of a line and the address path takes a cycle per lane (60 for the 1 KiB, measured over 192 loads a CU).
 // With a row's 64 bytes on the four lanes of a quad it takes 34, with 128 on eight lanes about half of that, so that is
 // how rows are loaded; a patch of LDS private to the wavefront turns them into fragments.  KW: the k of a step, 64 (whole
 // lines) from K = 1024 on, where every wavefront has two steps or more: out_proj of 12 rows 3.9 -> 3.6 us, x_proj of 333
 // rows 3.9 -> 3.7, 128 rows x 768 5.2 -> 4.4.  On a shorter k steps of 64 leave wavefronts with one step or none and asking
-// for rows that do not exist (64 x 1024, K = 512: 2.9 us against 3.4; in_proj of a draft position 5.0 against 6.0), and a
-// branch around those requests costs more than it saves (3.6 -> 3.9 us).
-// The partial tiles of the wavefronts meet in LDS, one output per thread; what else an output needs (bias, residual, the
-// carried conv window behind the parent index) has been on its way since before the main loop.
-// IN (in_proj of a draft position): norm, conv and next projection ride along.
-//   NORM: RMSNorm on the way in.  The weight goes on the x fragments; the sum of squares of a row is reduced over the
-//     lanes that share it by lane swaps and over the wavefronts by whoever applies the row factor (eight LDS words).
-//   CONV: the columns of the first output tensor go through one step of the causal conv + SiLU.
-//   xp.w: the finished 16 columns of the first output tensor (as stored) are multiplied into the next projection right
-//     here, one 16x16x16 MFMA per 16 of its outputs and 16 rows, and leave as partial sums (row, column block, output):
-//     runs of `n` floats per row, so that both sides move whole lines.
-// Measured on the drafter's shapes (12 rows, weights rotating through 24 layers, per launch in a replayed graph), against
-// 32-column tiles that went through LDS patches: in_proj with everything 9.0 -> 5.0 us, out_proj 5.8 -> 3.9 us; with 64
-// rows 18.2 -> 9.9 and 10.3 -> 4.0 us.  (Fragments straight from memory: 5.7, 4.8, 11.0 and 5.1 us.  16 wavefronts, or
-// six k steps in flight instead of three, measured the same.)
-typedef short bf16x4_bits __attribute__((ext_vector_type(4)));
+// for rows that do not exist (64 x 1024, K = 512: 2.9 us against 3.4), and a branch around those requests costs more than it
+// saves (3.6 -> 3.9 us).
+// The partial tiles of the wavefronts meet in LDS, one output per thread; what else an output needs (bias, residual) has been on
+// its way since before the main loop.
+// (16 wavefronts, or six k steps in flight instead of three, measured the same.)
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
-// the sum over the four lanes of a quad, in all of them
-__device__ __forceinline__ float sum_over_quad(float v)
-{
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xb1, 0xf, 0xf, false));   // quad_perm [1,0,3,2]
-    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4e, 0xf, 0xf, false));   // quad_perm [2,3,0,1]
-}
-
-template <int MT, bool IN, int KW>
+template <int MT, int KW>
 __global__ void __launch_bounds__(512)
 linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, const float *__restrict__ bias,
-                  const bf16_t *residual, OutSplit out, int M, int N, int K, const float *__restrict__ norm_w, float eps,
-                  ConvTail conv, XprojTail xp)
+                  const bf16_t *residual, OutSplit out, int M, int N, int K)
 {
     constexpr int NW = 8, kThr = NW * 64, G = 3;                   // G: k steps in flight per wavefront
     constexpr int C = KW / 8;                                      // 16-byte chunks of a row in a step of KW
     constexpr int LT = C / 4, RL = 16 / LT;                        // loads per 16-row tile, rows per load
     constexpr int PB = KW == 32 ? G : 2;                           // patches in turn
     constexpr int OPT = (MT * 256 + kThr - 1) / kThr;              // outputs per thread
-    constexpr bool NORM = IN, CONV = IN;
-    static_assert(KW == 32 || (KW == 64 && !IN), "the sum of squares is reduced over quads");
-    constexpr int kXcRow = 24;                                     // elements between rows of the finished columns in LDS (48 bytes: 8-byte aligned, spread over the banks)
     __shared__ __attribute__((aligned(16))) uint4 patch[NW][PB][1 + MT][64 * LT];
     __shared__ __attribute__((aligned(16))) float part[NW][MT][4][64];
-    __shared__ __attribute__((aligned(16))) float4 norm_lds[NORM ? NW : 1][G * 2 * C];
-    __shared__ __attribute__((aligned(16))) float ssq[MT * 16][NW];
-    __shared__ __attribute__((aligned(16))) uint16_t xc[CONV ? MT * 16 * kXcRow : 8];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, lg = lane >> 4;                      // fragment view: row, 16-byte chunk of a k32 half
@@ -665,13 +622,9 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
     const int n0 = blockIdx.x * 16, m0 = blockIdx.y * (16 * MT);
     const int w0 = (int)out.width[0], w1 = (int)out.width[1];
 
-    // ---- what the outputs of this thread need besides their sums, first part (nothing is used where it is fetched)
-    struct Tail {
-        float bias, cb, wk[4];
-        uint16_t res, carried[3];
-        int32_t parent;
-    };
-    Tail tail[OPT];
+    // ---- what the outputs of this thread need besides their sums (nothing is used where it is fetched)
+    float tail_bias[OPT];
+    uint16_t tail_res[OPT];
     int om[OPT], on[OPT];
     bool live[OPT];
 #pragma unroll
@@ -680,13 +633,11 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
         om[j] = m0 + (o >> 8) * 16 + 4 * (l >> 4) + (r >> 6);
         on[j] = n0 + (l & 15);
         live[j] = o < MT * 256 && om[j] < M && on[j] < N;
-        tail[j].bias = tail[j].cb = 0.0f;
-        tail[j].res = 0;
-        tail[j].parent = om[j];
+        tail_bias[j] = 0.0f;
+        tail_res[j] = 0;
         if (!live[j]) continue;
-        if (bias) tail[j].bias = bias[on[j]];
-        if (residual) tail[j].res = residual[(int64_t)om[j] * N + on[j]];          // single output tensor
-        if (CONV && conv.parent && on[j] < w0) tail[j].parent = conv.parent[om[j]];
+        if (bias) tail_bias[j] = bias[on[j]];
+        if (residual) tail_res[j] = residual[(int64_t)om[j] * N + on[j]];          // single output tensor
     }
 
     // ---- the wavefront's share of k: steps [s_first, s_end) of KW
@@ -705,25 +656,10 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
         xrow[t] = reinterpret_cast<const uint4 *>(x + (int64_t)(m < M ? m : M - 1) * K);   // rows past M repeat the last one, never stored
     }
     f32x4v acc[MT];
-    float ss[MT];
 #pragma unroll
-    for (int t = 0; t < MT; ++t) {
-        acc[t] = f32x4v(0.0f);
-        ss[t] = 0.0f;
-    }
-    const bool xp_on = CONV && xp.w && n0 < w0;                    // uniform: a column block lies in one output tensor (w0 % 16 == 0)
-    const int xp_tiles = xp_on ? (xp.n + 15) >> 4 : 0, xp_tasks = xp_tiles * MT;
-    uint2 xw[3] = {};
-    bool windows_pending = CONV;
-    for (int s0 = s_first; s0 < s_end || windows_pending; s0 += G) {
+    for (int t = 0; t < MT; ++t) acc[t] = f32x4v(0.0f);
+    for (int s0 = s_first; s0 < s_end; s0 += G) {
         uint4 wf[LT][G], xf[LT * MT][G];
-        // the norm weights of the wavefront's KW G k values: one 16-byte piece per lane, handed out by LDS (fetched by every lane
-        // that needs them they would be 32 bytes apart, loads at a cycle of the address path per lane)
-        float4 nw;
-        if constexpr (NORM) {
-            const int f = 2 * C * s0 + lane;
-            nw = reinterpret_cast<const float4 *>(norm_w)[lane < 2 * C * G && f < 2 * kchunks ? f : 0];
-        }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const int c = C * (s0 + g) + lch;
@@ -733,51 +669,13 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
 #pragma unroll
             for (int t = 0; t < LT * MT; ++t) xf[t][g] = xrow[t][cc];
         }
-        if (CONV && windows_pending) {
-            // the windows behind the parent index, once the main loop's first requests are on their way
-            windows_pending = false;
-            const int H = conv.k - 1;
-#pragma unroll
-            for (int j = 0; j < OPT; ++j) {
-                if (!live[j] || on[j] >= w0) continue;
-                const bool p_ok = tail[j].parent >= 0 && (int64_t)tail[j].parent < conv.n_in;
-                const int64_t win = ((int64_t)(p_ok ? tail[j].parent : 0) * w0 + on[j]) * H;
-                if (conv.bias) tail[j].cb = conv.bias[on[j]];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) tail[j].wk[k] = conv.w[(int64_t)on[j] * conv.k + (k <= H ? k : H)];
-#pragma unroll
-                for (int k = 0; k < 3; ++k) tail[j].carried[k] = conv.src[win + (k < H ? k : H - 1)];
-            }
-            // and this wavefront's fragments of the next projection: rows of xp.w are its outputs, 16 of its k are n0 ..
-#pragma unroll
-            for (int r = 0; r < 3; ++r) {
-                const int task = r * NW + wave;
-                const int row = task % (xp_tiles ? xp_tiles : 1) * 16 + li;
-                if (xp_on && task < xp_tasks) xw[r] = *reinterpret_cast<const uint2 *>(xp.w + (int64_t)(row < xp.n ? row : xp.n - 1) * xp.ldw + n0 + 4 * lg);
-            }
-        }
         __builtin_amdgcn_sched_barrier(0);                         // all of it in flight before any of it is used
-        if constexpr (NORM) {
-            if (lane < 2 * C * G) norm_lds[wave][lane] = nw;
-            wave_sync();
-        }
         auto fill = [&](int g) __attribute__((always_inline)) {
             const bool ok = s0 + g < s_end && C * (s0 + g) + lch < kchunks;   // else zeros: adds nothing
 #pragma unroll
             for (int t = 0; t < LT; ++t) patch[wave][g % PB][0][64 * t + put] = ok ? wf[t][g] : make_uint4(0, 0, 0, 0);
 #pragma unroll
-            for (int t = 0; t < LT * MT; ++t) {
-                uint4 q = ok ? xf[t][g] : make_uint4(0, 0, 0, 0);
-                if constexpr (NORM) {
-                    const float4 g0 = norm_lds[wave][2 * C * g + 2 * lch], g1 = norm_lds[wave][2 * C * g + 2 * lch + 1];
-                    const float v0 = bf16_lo(q.x), v1 = bf16_hi(q.x), v2 = bf16_lo(q.y), v3 = bf16_hi(q.y);
-                    const float v4 = bf16_lo(q.z), v5 = bf16_hi(q.z), v6 = bf16_lo(q.w), v7 = bf16_hi(q.w);
-                    ss[t / LT] += v0 * v0 + v1 * v1 + v2 * v2 + v3 * v3 + v4 * v4 + v5 * v5 + v6 * v6 + v7 * v7;
-                    q = make_uint4(f32x2_to_bf16x2(v0 * g0.x, v1 * g0.y), f32x2_to_bf16x2(v2 * g0.z, v3 * g0.w),
-                                   f32x2_to_bf16x2(v4 * g1.x, v5 * g1.y), f32x2_to_bf16x2(v6 * g1.z, v7 * g1.w));
-                }
-                patch[wave][g % PB][1 + t / LT][64 * (t % LT) + put] = q;
-            }
+            for (int t = 0; t < LT * MT; ++t) patch[wave][g % PB][1 + t / LT][64 * (t % LT) + put] = ok ? xf[t][g] : make_uint4(0, 0, 0, 0);
         };
 #pragma unroll
         for (int g = 0; g < (PB < G ? 1 : G); ++g) fill(g);
@@ -800,13 +698,6 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
     for (int t = 0; t < MT; ++t)
 #pragma unroll
         for (int i = 0; i < 4; ++i) part[wave][t][i][lane] = acc[t][i];
-    if constexpr (NORM) {
-#pragma unroll
-        for (int t = 0; t < MT; ++t) {
-            float v = sum_over_quad(ss[t]);
-            if (lch == 0) ssq[16 * t + lrow][wave] = v;
-        }
-    }
     lds_barrier_linear();
 
 #pragma unroll
@@ -815,71 +706,16 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
         float v = 0.0f;
 #pragma unroll
         for (int q = 0; q < NW; ++q) v += part[q][t][i][l];
-        if constexpr (NORM) {
-            float sq = 0.0f;
-#pragma unroll
-            for (int q = 0; q < NW; ++q) sq += ssq[16 * t + 4 * (l >> 4) + i][q];
-            v *= __builtin_amdgcn_rsqf(sq / (float)K + eps);
-        }
         if (!live[j]) continue;
-        v = bf16_to_f32(f32_to_bf16(v + tail[j].bias));            // same two roundings as the tiled kernel
+        v = bf16_to_f32(f32_to_bf16(v + tail_bias[j]));            // same two roundings as the tiled kernel
         int col = on[j], width = w0, sp = 0;
         if (col >= w0) {
             col -= w0; width = w1; sp = 1;
             if (col >= w1) { col -= w1; width = (int)out.width[2]; sp = 2; }
         }
         bf16_t *optr = sp == 0 ? out.ptr[0] : sp == 1 ? out.ptr[1] : out.ptr[2];
-        const int64_t off = (int64_t)om[j] * width + col;
-        if (residual) v += bf16_to_f32(tail[j].res);
-        if (CONV && sp == 0) {
-            // the window of this (row, channel): K - 1 carried values, then v; same order of operations as the stand-alone
-            // conv kernel.  A bad parent index leaves NaN in the carried places.
-            const int H = conv.k - 1;
-            const bool p_ok = tail[j].parent >= 0 && (int64_t)tail[j].parent < conv.n_in;
-            uint16_t carried[3];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) carried[k] = p_ok ? tail[j].carried[k] : (uint16_t)0x7fc0;
-            bf16_t *nwin = conv.dst + off * H;
-            float a = tail[j].cb;
-#pragma unroll
-            for (int k = 0; k < 3; ++k)
-                if (k < H) a = fmaf(tail[j].wk[k], bf16_to_f32(carried[k]), a);
-            float wlast = tail[j].wk[0];
-#pragma unroll
-            for (int k = 1; k < 4; ++k)
-                if (k == H) wlast = tail[j].wk[k];
-            a = fmaf(wlast, v, a);
-#pragma unroll
-            for (int k = 0; k < 2; ++k)
-                if (k + 1 < H) nwin[k] = carried[k + 1];
-            if (H > 0) nwin[H - 1] = (bf16_t)f32_to_bf16(v);
-            v = silu_f32(a);
-        }
-        const uint32_t stored = f32_to_bf16(v);
-        optr[off] = (bf16_t)stored;
-        if (CONV && xp_on) xc[(om[j] - m0) * kXcRow + (l & 15)] = (uint16_t)stored;
-    }
-    if constexpr (CONV) {
-        if (!xp_on) return;
-        // (rows past M hold whatever was in LDS: they only reach outputs that are not stored)
-        lds_barrier_linear();
-        for (int r = 0; r * NW + wave < xp_tasks; ++r) {
-            const int task = r * NW + wave, jt = task % xp_tiles, t = task / xp_tiles;
-            uint2 b2 = r == 0 ? xw[0] : r == 1 ? xw[1] : xw[2];
-            if (r > 2) {
-                const int row = jt * 16 + li;
-                b2 = *reinterpret_cast<const uint2 *>(xp.w + (int64_t)(row < xp.n ? row : xp.n - 1) * xp.ldw + n0 + 4 * lg);
-            }
-            const uint2 a2 = *reinterpret_cast<const uint2 *>(&xc[(16 * t + li) * kXcRow + 4 * lg]);
-            const f32x4v y = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4_bits, a2), __builtin_bit_cast(bf16x4_bits, b2),
-                                                                       f32x4v(0.0f), 0, 0, 0);
-            const int jn = jt * 16 + li;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int m = m0 + 16 * t + 4 * lg + i;
-                if (m < M && jn < xp.n) xp.part[((int64_t)m * (w0 >> 4) + blockIdx.x) * xp.n + jn] = y[i];
-            }
-        }
+        if (residual) v += bf16_to_f32(tail_res[j]);
+        optr[(int64_t)om[j] * width + col] = (bf16_t)f32_to_bf16(v);
     }
 }
 
@@ -897,22 +733,9 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     const bf16_t *x = static_cast<const bf16_t *>(a.x), *w = static_cast<const bf16_t *>(a.w);
     const bf16_t *res = static_cast<const bf16_t *>(a.residual);
     auto tiles = [&](int64_t bm, int64_t bn) { return ((N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
-    const ConvTail ct{a.conv_w, a.conv_b, static_cast<const bf16_t *>(a.conv_src), static_cast<bf16_t *>(a.conv_dst),
-                      a.conv_parent, a.conv_n_in, a.conv_k};
-    const XprojTail xt{static_cast<const bf16_t *>(a.xproj_w), a.xproj_part, a.xproj_n, a.width[0]};
-#define MAMBA_FEW_K(MT, IN, KW) linear_few_kernel<MT, IN, KW><<<dim3((unsigned)((N + 15) / 16), (unsigned)((a.M + 16 * MT - 1) / (16 * MT))), 512, 0, stream>>>(x, w, a.bias, res, o, (int)a.M, (int)N, (int)a.K, a.norm_w, a.eps, ct, xt)
-#define MAMBA_FEW(MT) do { if (a.K >= 1024) MAMBA_FEW_K(MT, false, 64); else MAMBA_FEW_K(MT, false, 32); } while (0)
-    if (a.norm_w) {
-        // the way into a block at a draft position: norm and conv come together, the next projection only with them
-        if (!linear_few_fits(N, a.K) || !a.conv_w || !a.conv_src || !a.conv_dst || a.conv_k < 2 || (a.xproj_w && (!a.xproj_part || a.width[0] % 16)))
-            return hipErrorInvalidValue;
-        switch (linear_few_row_tiles(a.M, N)) {
-        case 1: MAMBA_FEW_K(1, true, 32); break;
-        case 2: MAMBA_FEW_K(2, true, 32); break;
-        default: MAMBA_FEW_K(4, true, 32); break;
-        }
-        return hipGetLastError();
-    }
+#define MAMBA_FEW_K(MT, KW) linear_few_kernel<MT, KW><<<dim3((unsigned)((N + 15) / 16), (unsigned)((a.M + 16 * MT - 1) / (16 * MT))), 512, 0, stream>>>(x, w, a.bias, res, o, (int)a.M, (int)N, (int)a.K)
+#define MAMBA_FEW(MT) do { if (a.K >= 1024) MAMBA_FEW_K(MT, 64); else MAMBA_FEW_K(MT, 32); } while (0)
+    if (a.norm_w) return launch_draft_in(a, stream);
     // Few output tiles: latency decides, and the tiles are kept so small that they just fill the CUs once (a second
     // round of workgroups costs nearly as much again: 256 rows x 768 columns, K = 1536, on 32 x 32 tiles 5.9 us, 264 rows
     // 9.4 us; a fifth of a round does not).  Tiles 16 columns wide while 16 or 32 rows each are enough, or 64 on a short k;
@@ -925,7 +748,7 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     const bool few = linear_few_fits(N, a.K);
     if (few && tiles(16, 16) <= kTilesResident * 5 / 4) { MAMBA_FEW(1); return hipGetLastError(); }
     if (few && tiles(32, 16) <= kTilesResident) { MAMBA_FEW(2); return hipGetLastError(); }
-    if (a.K <= 768 && tiles(64, 16) <= kTilesResident) { MAMBA_FEW_K(4, false, 32); return hipGetLastError(); }
+    if (a.K <= 768 && tiles(64, 16) <= kTilesResident) { MAMBA_FEW_K(4, 32); return hipGetLastError(); }
     if (a.K >= 512 && tiles(32, 32) <= kTilesResident) {
         const dim3 grid((unsigned)((N + 31) / 32), (unsigned)((a.M + 31) / 32));
         linear_split_kernel<1><<<grid, 512, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K);
@@ -942,7 +765,7 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
         switch (linear_few_row_tiles(a.M, N)) {
         case 1: MAMBA_FEW(1); break;
         case 2: MAMBA_FEW(2); break;
-        default: MAMBA_FEW_K(4, false, 32); break;
+        default: MAMBA_FEW_K(4, 32); break;
         }
         return hipGetLastError();
     }

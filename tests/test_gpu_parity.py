@@ -1455,6 +1455,29 @@ def test_block_step_of_wide_models(m, n, dm, D, N, K, R):
     test_block_step_more_branches(m, n, dm, D, N, K, R)
 
 
+@pytest.mark.parametrize("dm", [8, 72, 256, 512, 576, 768, 1024, 1536, 2048, 2056])
+@pytest.mark.parametrize("n,K", [(2, 4), (17, 4), (64, 4), (15, 3), (49, 2)])
+def test_block_step_every_split_of_k(m, n, dm, K):
+    """Every way the wavefronts of the kernel in front share k (one trip, several, remainders of a step), with one, two and four
+    row tiles.  Bounds against the unrounded block: five tensors on the way (u, x_c, z, y, out) are rounded to bf16, at most
+    2^-9 of a value each, so their errors add up to less than 2^-9 sqrt(5) < 2^-7 of the result's 2-norm, and the largest of up
+    to 131072 elements lies within six of that."""
+    D, N, R = (1552 if n > 16 else 80), 16, 8
+    say(n=n, dm=dm, D=D, K=K)
+    rng = np.random.default_rng(n + dm + D)
+    w, w64, blk = make_block(m, rng, dm, D, N, K, R)
+    conv = synth.to_io(rng.standard_normal((5, D, K - 1)).astype(np.float32), synth.BF16)
+    ssm = rng.standard_normal((5, D, N)).astype(np.float32)
+    hid = synth.to_io(rng.standard_normal((n, dm)).astype(np.float32), synth.BF16)
+    par = rng.integers(0, 5, n).astype(np.int32)
+    out, g_conv, g_ssm = m.mamba_block_step(blk, to_dev(hid), to_dev(conv), to_dev(ssm), parent_idx=to_dev(par))
+    ro, r_conv, r_ssm = oracle.block_fwd(w64, W(hid)[:, None, :], conv_state_in=W(conv)[par], h0=ssm.astype(np.float64)[par])
+    for got, ref, what in ((values(to_host(out)), ro[:, 0], "out"), (to_host(g_ssm), r_ssm, "ssm"), (values(to_host(g_conv)), r_conv, "conv")):
+        got = np.asarray(got, dtype=np.float64)
+        assert np.linalg.norm(got - ref) <= 2.0 ** -7 * np.linalg.norm(ref), what
+        assert_close(got, ref, 6 * 2.0 ** -7, what)
+
+
 def test_block_step_bad_parent_poisons_only_that_branch(m):
     """A parent index outside the source cache cannot be honoured: that branch's states and hidden row
     come back NaN (never an out-of-bounds read), the other branches are untouched by it."""
