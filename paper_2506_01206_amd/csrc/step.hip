@@ -18,6 +18,14 @@ namespace {
 
 constexpr int kBlock = 256;
 
+// barrier that orders LDS only: requests in flight stay in flight
+__device__ __forceinline__ void lds_barrier_s()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 template <int CTRL> __device__ __forceinline__ float dpp_add(float v)
 {
     const int o = __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false);
@@ -367,172 +375,157 @@ state_step_conv_kernel(const int32_t *__restrict__ parent, const float *h_in, co
     if (live) st_io(out + row, c, y);
 }
 
-// The same step for a draft position of the whole block, where the x projection arrives as partial sums (see
-// StepArgs::xpart): what does not depend on it (the state row above all) is requested first, then the parts are
-// added up, and dt (through the fused dt projection), B and C come out of LDS.  Kept apart from the plain kernel,
-// which stays as lean as it was.
-// grid: (ceil(D * N / 4 / (256 * U)), n_out).  A lane owns U float4s of the branch's (D, N) state,
-// 256 float4s apart, so every wavefront load or store is still one contiguous 1 KiB run; all
-// loads of the U pieces are issued before the first one is used, which keeps several KiB per
-// wavefront in flight (the step is a single pass over the state and lives on memory latency).
-// MORE: ranges of more than kParts partial sums (see there); the others do without that loop (+0.2 us for every launch).
+// The same step for a draft position of the whole block (bf16, softplus, gate), where the x projection arrives as partial sums (see
+// StepArgs::xpart).  The branch's row of it (dt low rank | B | C) is n_parts runs of xn = dt_rank + 2 N floats: they are added up
+// in order and rounded to bf16, as the stored tensors they replace would have been.  The workgroup reads `sides` contiguous ranges
+// of `per` parts side by side, as many as it has threads for, 16 bytes each, and adds those few sums up from LDS; then dt (through
+// the fused dt projection), B and C come out of LDS.  The parts are what the step waits for first, so the first eight of a range are
+// requested ahead of everything else; the state row, behind the parent index, last.  Longer ranges (MORE: wide models) go on by eight.
+// Nothing but the parts' trip to memory is long here: what counts is the instructions between the launch and the last store.
+// Offsets of a lane are 32 bits from scalar bases, the split of the parts is worked out on the host, and the shapes that occur have
+// no conditions left (EXACT: eight parts to every range; NC: pieces of four dt weights per lane, 0: any number).  us a launch in a
+// replayed graph, 1 / 12 / 48 rows (before: divisions by the run's length, 64-bit offsets, loops of unknown length): 1024 channels 2.70 /
+// 2.82 / 4.17 (3.24 / 3.37 / 4.52), 1536 2.39 / 3.00 / 5.52 (3.28 / 3.84 / 6.12), 4096 5.4 / 9.2 / 18.7 (7.1 / 9.6 / 19.5), 5120 7.0 / 13.4 /
+// 35.4 (9.0 / 13.5 / 37.7).
+// grid: (ceil(D * N / 4 / (256 * U)), n_out)
 constexpr int kParts = 8;
-__host__ __device__ inline int xproj_sides(int xn, int n_parts) { return kBlock / (xn / 4) < n_parts ? kBlock / (xn / 4) : n_parts; }
-template <typename T, int N, int U, bool HAS_Z, bool SOFTPLUS, bool MORE>
-__global__ void __launch_bounds__(kBlock)
-state_step_xproj_kernel(float *h_out, const float *h_in, const int32_t *__restrict__ parent,
-                  const T *__restrict__ x, const T *__restrict__ dt, const float *__restrict__ A,
-                  const T *__restrict__ Bm, const T *__restrict__ Cm,
-                  const float *__restrict__ Dskip, const T *__restrict__ z,
-                  const float *__restrict__ dt_bias, T *__restrict__ out, int64_t n_in, int64_t D,
-                  const bf16_t *__restrict__ dt_w, int64_t dt_rank, const float *__restrict__ xpart, int n_parts)
+template <typename V> __device__ __forceinline__ V ld_at(const void *base, unsigned byte) { return *reinterpret_cast<const V *>(static_cast<const char *>(base) + byte); }
+struct XprojSplit {
+    int sides, per, magic;                                        // thread t reads range t * magic >> 16
+};
+__host__ __device__ inline XprojSplit xproj_split(int xn, int n_parts)
 {
-    constexpr int Q = N / 4;
-    constexpr int CW = 4;                                         // dt_w pieces a lane can hold ahead of the x projection sums
-    const int64_t j = blockIdx.y;
-    const int64_t row4 = D * Q;  // float4s per branch
-    const float4 *a4 = reinterpret_cast<const float4 *>(A);
-    __shared__ __attribute__((aligned(16))) float xs[256], xs_side[kBlock * 4];
-    const bool hold_w = dt_rank / 4 <= CW * Q;
+    const int xn4 = xn / 4, sides = kBlock / xn4 < n_parts ? kBlock / xn4 : n_parts;
+    return {sides, (n_parts + sides - 1) / sides, (65536 + xn4 - 1) / xn4};   // t < 256 and xn4 <= 64: t / xn4 exactly
+}
 
-    int64_t f[U], d[U];
-    int q[U];
-    bool live[U];
-    float4 h[U], a[U], bv[U], cv[U];
-    float xv[U], dv[U], zv[U], bias[U], dsk[U];
-    uint2 wq[U][CW];
-    // The branch's row of the x projection (dt low rank | B | C) arrives as n_parts partial sums: they are added
-    // up in order and rounded to bf16, as the stored tensors they replace would have been.  A part is one run of
-    // dt_rank + 2 N floats (a multiple of four); the workgroup reads as many parts side by side as it has threads for, 16
-    // bytes each and a contiguous range of parts, and adds those few sums up from LDS.  The parts are what the step waits
-    // for first, so the first eight of a range are requested ahead of everything else (behind the state row they would
-    // wait for the parent index): 12 x 1536 channels 4.6 -> 4.2 us, 3 x 1536 4.3 -> 3.8 us.  Longer ranges (wide models) go on
-    // by eight: 1 x 5120 channels, 320 parts of 192 sums, 12.8 us against 21.3 one after the other, 32 x 5120 32.5 against 51.3.
-    const int xn = (int)dt_rank + 2 * N, xn4 = xn / 4;
-    const int sides = xproj_sides(xn, n_parts);
-    const int side = (int)threadIdx.x / xn4, k4 = (int)threadIdx.x - side * xn4;
-    const int per = (n_parts + sides - 1) / sides, first = side * per, last = min(first + per, n_parts);
-    const bool adds = side < sides && first < last;
-    const float4 *pr = reinterpret_cast<const float4 *>(xpart) + j * n_parts * xn4 + k4;
+template <int N, int U, int NC, bool EXACT, bool MORE>
+__global__ void __launch_bounds__(kBlock)
+state_step_xproj_kernel(const float *__restrict__ xpart, int n_parts, int sides_in, int per, int magic, int D, int dt_rank_in, const int32_t *__restrict__ parent,
+                        const float *h_in, const bf16_t *__restrict__ dt_w, const bf16_t *__restrict__ x, const bf16_t *__restrict__ z,
+                        const float *__restrict__ A, const float *__restrict__ dt_bias, const float *__restrict__ Dskip, float *h_out,
+                        bf16_t *__restrict__ out, int64_t n_in)
+{
+    constexpr int Q = N / 4, CW = NC ? NC : 4;                    // CW: dt_w pieces a lane can hold ahead of the x projection sums
+    __shared__ __attribute__((aligned(16))) float xs[256], xs_side[kBlock * 4 + 4];   // + 4: where threads past the last range write
+    const unsigned tid = threadIdx.x, j = blockIdx.y;
+    const int dt_rank = NC ? 4 * NC * Q : dt_rank_in, xn = dt_rank + 2 * N;
+    const int sides = NC && EXACT ? kBlock / (xn >> 2) : sides_in;   // (eight parts to a range: there are more parts than ranges)
+    const unsigned xn4 = (unsigned)xn >> 2, row4 = (unsigned)D * Q;
+
+    // ---- the partial sums
+    const unsigned side = NC ? tid / xn4 : tid * (unsigned)magic >> 16, k4 = tid - side * xn4;
+    const unsigned sd = min(side, (unsigned)sides - 1), first = sd * (unsigned)per;
+    const unsigned count = EXACT ? kParts : first < (unsigned)n_parts ? min((unsigned)per, (unsigned)n_parts - first) : 0u;   // parts of this range
+    const float4 *pr = reinterpret_cast<const float4 *>(xpart) + (uint64_t)j * (unsigned)n_parts * xn4;
+    const unsigned at = ((EXACT || first < (unsigned)n_parts ? first : 0u) * xn4 + k4) * 16, part_bytes = xn4 * 16;
     float4 pv[kParts];
-    if (adds) {
 #pragma unroll
-        for (int u = 0; u < kParts; ++u) pv[u] = pr[(int64_t)min(first + u, last - 1) * xn4];
-    }
-    // then everything else that does not depend on the x projection
+    for (unsigned u = 0; u < kParts; ++u) pv[u] = ld_at<float4>(pr, at + (EXACT ? u : min(u, count ? count - 1 : 0u)) * part_bytes);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- everything else that does not depend on the x projection
+    const int32_t parent_in = (parent ? parent : reinterpret_cast<const int32_t *>(dt_w))[parent ? j : 0];
+    unsigned f[U], d[U];
+    const unsigned q = tid % Q;                                   // 256 i is a multiple of Q: the same for all pieces
+    float4 h[U], a[U];
+    bf16_t xr[U], zr[U];
+    float bias_in[U], dsk_in[U];
+    uint2 wq[U][CW];
+    const unsigned pieces = NC ? NC * Q : (unsigned)dt_rank >> 2;
+    const bool hold_w = NC || pieces <= CW * Q;
 #pragma unroll
-    for (int i = 0; i < U; ++i) {
-        const int64_t f_raw = ((int64_t)blockIdx.x * U + i) * kBlock + threadIdx.x;
-        live[i] = f_raw < row4;
-        f[i] = live[i] ? f_raw : row4 - 1;
+    for (unsigned i = 0; i < U; ++i) {
+        f[i] = min((blockIdx.x * U + i) * kBlock + tid, row4 - 1);
         d[i] = f[i] / Q;
-        q[i] = (int)(f[i] - d[i] * Q);
-        a[i] = a4[f[i]];
-        xv[i] = ld_io(x, j * D + d[i]);
-        zv[i] = HAS_Z ? ld_io(z, j * D + d[i]) : 0.0f;
-        bias[i] = dt_bias ? dt_bias[d[i]] : 0.0f;
-        dsk[i] = Dskip ? Dskip[d[i]] : 0.0f;
 #pragma unroll
-        for (int c = 0; c < CW; ++c) wq[i][c] = make_uint2(0, 0);
-        if (hold_w) {
-            const uint2 *wrow = reinterpret_cast<const uint2 *>(dt_w + d[i] * dt_rank);
-#pragma unroll
-            for (int c = 0; c < CW; ++c)
-                if (q[i] + c * Q < dt_rank / 4) wq[i][c] = wrow[q[i] + c * Q];
+        for (unsigned c = 0; c < CW; ++c) {
+            const unsigned cc = q + c * Q;
+            wq[i][c] = make_uint2(0, 0);
+            if constexpr (NC) wq[i][c] = ld_at<uint2>(dt_w, (d[i] * (NC * Q) + q) * 8 + c * Q * 8);
+            else if (hold_w && cc < pieces) wq[i][c] = reinterpret_cast<const uint2 *>(dt_w)[(uint64_t)d[i] * pieces + cc];
         }
+        a[i] = ld_at<float4>(A, 16 * f[i]);
+        xr[i] = ld_at<bf16_t>(x + (uint64_t)j * (unsigned)D, 2 * d[i]);
+        zr[i] = ld_at<bf16_t>(z + (uint64_t)j * (unsigned)D, 2 * d[i]);
+        bias_in[i] = ld_at<float>(dt_bias ? dt_bias : A, 4 * d[i]);
+        dsk_in[i] = ld_at<float>(Dskip ? Dskip : A, 4 * d[i]);
     }
-    // the state row is the only load that has to wait for the parent index
-    const int64_t p = parent ? (int64_t)parent[j] : j;
+    const int64_t p = parent ? (int64_t)parent_in : (int64_t)j;
     const bool p_ok = p >= 0 && p < n_in;
-    const float4 *hin4 = reinterpret_cast<const float4 *>(h_in) + (p_ok ? p : 0) * row4;
+    const float4 *hin4 = reinterpret_cast<const float4 *>(h_in) + (uint64_t)(p_ok ? (uint32_t)p : 0u) * row4;
 #pragma unroll
-    for (int i = 0; i < U; ++i) h[i] = ld_stream(hin4 + f[i]);
+    for (int i = 0; i < U; ++i) h[i] = ld_stream(reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(hin4) + 16 * f[i]));
+    __builtin_amdgcn_sched_barrier(0);                            // all of it in flight before any of it is used
+
     {
-        if (side < sides) {
-            float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            auto add = [&](float4 v) { sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w; };
-            if (adds) {
+        float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        auto add = [&](float4 v, bool use) __attribute__((always_inline)) {
+            sum.x += use ? v.x : 0.0f; sum.y += use ? v.y : 0.0f; sum.z += use ? v.z : 0.0f; sum.w += use ? v.w : 0.0f;
+        };
 #pragma unroll
-                for (int u = 0; u < kParts; ++u)
-                    if (first + u < last) add(pv[u]);
-                if constexpr (MORE) {
-                    for (int c = first + kParts; c < last; c += kParts) {   // as many in flight again
+        for (unsigned u = 0; u < kParts; ++u) add(pv[u], EXACT || u < count);
+        if constexpr (MORE) {
+            for (unsigned c = kParts; c < count; c += kParts) {   // as many in flight again
 #pragma unroll
-                        for (int u = 0; u < kParts; ++u) pv[u] = pr[(int64_t)min(c + u, last - 1) * xn4];
+                for (unsigned u = 0; u < kParts; ++u) pv[u] = ld_at<float4>(pr, at + min(c + u, count - 1) * part_bytes);
 #pragma unroll
-                        for (int u = 0; u < kParts; ++u)
-                            if (c + u < last) add(pv[u]);
-                    }
-                }
+                for (unsigned u = 0; u < kParts; ++u) add(pv[u], c + u < count);
             }
-            *reinterpret_cast<float4 *>(&xs_side[side * xn + 4 * k4]) = sum;
         }
-        __syncthreads();
-        if ((int)threadIdx.x < xn) {
-            float sum = 0.0f;
-            for (int u = 0; u < sides; ++u) sum += xs_side[u * xn + threadIdx.x];
-            xs[threadIdx.x] = bf16_to_f32(f32_to_bf16(sum));
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < U; ++i) {
-            bv[i] = *reinterpret_cast<const float4 *>(&xs[dt_rank + 4 * q[i]]);
-            cv[i] = *reinterpret_cast<const float4 *>(&xs[dt_rank + N + 4 * q[i]]);
-            float acc = 0.0f;
-            if (hold_w) {
-#pragma unroll
-                for (int c = 0; c < CW; ++c) {
-                    const int cc = q[i] + c * Q;
-                    if (cc < dt_rank / 4) {
-                        const float4 b4 = *reinterpret_cast<const float4 *>(&xs[4 * cc]);
-                        acc = fmaf(bf16_lo(wq[i][c].x), b4.x, acc);
-                        acc = fmaf(bf16_hi(wq[i][c].x), b4.y, acc);
-                        acc = fmaf(bf16_lo(wq[i][c].y), b4.z, acc);
-                        acc = fmaf(bf16_hi(wq[i][c].y), b4.w, acc);
-                    }
-                }
-            } else {
-                const uint2 *wrow = reinterpret_cast<const uint2 *>(dt_w + d[i] * dt_rank);
-                for (int64_t c = q[i]; c < dt_rank / 4; c += Q) {
-                    const uint2 a2 = wrow[c];
-                    const float4 b4 = *reinterpret_cast<const float4 *>(&xs[4 * c]);
-                    acc = fmaf(bf16_lo(a2.x), b4.x, acc);
-                    acc = fmaf(bf16_hi(a2.x), b4.y, acc);
-                    acc = fmaf(bf16_lo(a2.y), b4.z, acc);
-                    acc = fmaf(bf16_hi(a2.y), b4.w, acc);
-                }
-            }
-            dv[i] = bf16_to_f32(f32_to_bf16(channel_sum<Q>(acc)));
-        }
+        // (unconditional: under a condition the compiler would move the requests in there too)
+        *reinterpret_cast<float4 *>(&xs_side[side < (unsigned)sides ? side * xn + 4 * k4 : kBlock * 4]) = sum;
     }
+    lds_barrier_s();
+    if (tid < (unsigned)xn) {
+        float sum = 0.0f;
+        constexpr int kTurn = NC && EXACT ? kBlock / (NC * Q + N / 2) : 12;
+        for (int u0 = 0; u0 < sides; u0 += kTurn) {
+            float v[kTurn];
+#pragma unroll
+            for (int u = 0; u < kTurn; ++u) v[u] = xs_side[(NC && EXACT ? u : min(u0 + u, sides - 1)) * xn + tid];
+#pragma unroll
+            for (int u = 0; u < kTurn; ++u) sum += (NC && EXACT) || u0 + u < sides ? v[u] : 0.0f;
+        }
+        xs[tid] = bf16_to_f32(f32_to_bf16(sum));
+    }
+    lds_barrier_s();
+
+    const float4 bv = *reinterpret_cast<const float4 *>(&xs[dt_rank + 4 * q]), cv = *reinterpret_cast<const float4 *>(&xs[dt_rank + N + 4 * q]);
 #pragma unroll
     for (int i = 0; i < U; ++i) {
-        const float v = dv[i] + bias[i];
-        const float delta = SOFTPLUS ? softplus_f32(v) : v;
-        const float u = delta * xv[i];
+        float acc = 0.0f;
+        auto dot = [&](uint2 w, unsigned cc) __attribute__((always_inline)) {
+            const float4 b4 = *reinterpret_cast<const float4 *>(&xs[4 * cc]);
+            acc = fmaf(bf16_lo(w.x), b4.x, acc);
+            acc = fmaf(bf16_hi(w.x), b4.y, acc);
+            acc = fmaf(bf16_lo(w.y), b4.z, acc);
+            acc = fmaf(bf16_hi(w.y), b4.w, acc);
+        };
+        if (hold_w) {
+#pragma unroll
+            for (unsigned c = 0; c < CW; ++c) dot(wq[i][c], NC || q + c * Q < pieces ? q + c * Q : 0u);
+        } else {
+            const uint2 *wrow = reinterpret_cast<const uint2 *>(dt_w) + (uint64_t)d[i] * pieces;
+            for (unsigned c = q; c < pieces; c += Q) dot(wrow[c], c);
+        }
+        const float xv = bf16_to_f32(xr[i]);
+        const float delta = softplus_f32(bf16_to_f32(f32_to_bf16(channel_sum<Q>(acc))) + (dt_bias ? bias_in[i] : 0.0f));
+        const float u = delta * xv + (p_ok ? -0.0f : __int_as_float(0x7fc00000));   // (x + -0 is x; a bad parent poisons states and output)
         const float dl = delta * kLog2e;
         float4 hh = h[i];
-        hh.x = fmaf(exp2_hw(dl * a[i].x), hh.x, u * bv[i].x);
-        hh.y = fmaf(exp2_hw(dl * a[i].y), hh.y, u * bv[i].y);
-        hh.z = fmaf(exp2_hw(dl * a[i].z), hh.z, u * bv[i].z);
-        hh.w = fmaf(exp2_hw(dl * a[i].w), hh.w, u * bv[i].w);
-        float y = hh.x * cv[i].x;
-        y = fmaf(hh.y, cv[i].y, y);
-        y = fmaf(hh.z, cv[i].z, y);
-        y = fmaf(hh.w, cv[i].w, y);
+        hh.x = fmaf(exp2_hw(dl * a[i].x), hh.x, u * bv.x);
+        hh.y = fmaf(exp2_hw(dl * a[i].y), hh.y, u * bv.y);
+        hh.z = fmaf(exp2_hw(dl * a[i].z), hh.z, u * bv.z);
+        hh.w = fmaf(exp2_hw(dl * a[i].w), hh.w, u * bv.w);
+        float y = hh.x * cv.x;
+        y = fmaf(hh.y, cv.y, y);
+        y = fmaf(hh.z, cv.z, y);
+        y = fmaf(hh.w, cv.w, y);
         y = channel_sum<Q>(y);
-        if (!p_ok) {
-            const float nan = __int_as_float(0x7fc00000);
-            hh = make_float4(nan, nan, nan, nan);
-            y = nan;
-        }
-        if (live[i]) {
-            st_stream(reinterpret_cast<float4 *>(h_out) + j * row4 + f[i], hh);
-            if (q[i] == 0) {
-                y = fmaf(dsk[i], xv[i], y);
-                if constexpr (HAS_Z) y *= silu_f32(zv[i]);
-                st_io(out, j * D + d[i], y);
-            }
+        if ((blockIdx.x * U + i) * kBlock + tid < row4) {
+            st_stream(reinterpret_cast<float4 *>(h_out) + (uint64_t)j * row4 + f[i], hh);
+            if (q == 0) st_io(out + (uint64_t)j * (unsigned)D, d[i], fmaf(Dskip ? dsk_in[i] : 0.0f, xv, y) * silu_f32(bf16_to_f32(zr[i])));
         }
     }
 }
@@ -565,25 +558,6 @@ template <typename T, int N, int U> hipError_t launch_step_u(const StepArgs &a, 
         static_cast<const T *>(a.Bm), static_cast<const T *>(a.Cm), a.Dskip,                      \
         static_cast<const T *>(a.z), a.dt_bias, static_cast<T *>(a.out), a.n_in, a.D,                \
         static_cast<const bf16_t *>(a.dt_w), a.dt_rank)
-#define MAMBA_STEP_X(HZ, SP) (more ? MAMBA_STEP_XM(HZ, SP, true) : MAMBA_STEP_XM(HZ, SP, false))
-#define MAMBA_STEP_XM(HZ, SP, MR)                                                                 \
-    state_step_xproj_kernel<T, N, U, HZ, SP, MR><<<grid, kBlock, 0, stream>>>(                    \
-        a.h_out, a.h_in, a.parent, static_cast<const T *>(a.x), static_cast<const T *>(a.dt), a.A, \
-        static_cast<const T *>(a.Bm), static_cast<const T *>(a.Cm), a.Dskip,                      \
-        static_cast<const T *>(a.z), a.dt_bias, static_cast<T *>(a.out), a.n_in, a.D,                \
-        static_cast<const bf16_t *>(a.dt_w), a.dt_rank, a.xpart, a.n_parts)
-    if (a.xpart && a.dt_w) {
-        const int sides = xproj_sides((int)a.dt_rank + 2 * N, a.n_parts);
-        const bool more = (a.n_parts + sides - 1) / sides > kParts;
-        if (a.z) {
-            if (a.dt_softplus) MAMBA_STEP_X(true, true);
-            else MAMBA_STEP_X(true, false);
-        } else {
-            if (a.dt_softplus) MAMBA_STEP_X(false, true);
-            else MAMBA_STEP_X(false, false);
-        }
-        return hipGetLastError();
-    }
     if (a.z) {
         if (a.dt_softplus) MAMBA_STEP(true, true);
         else MAMBA_STEP(true, false);
@@ -592,8 +566,6 @@ template <typename T, int N, int U> hipError_t launch_step_u(const StepArgs &a, 
         else MAMBA_STEP(false, false);
     }
 #undef MAMBA_STEP
-#undef MAMBA_STEP_X
-#undef MAMBA_STEP_XM
     return hipGetLastError();
     } else {
         return hipErrorInvalidValue;   // eight float4s per lane exist for the plain step only
@@ -621,6 +593,27 @@ template <typename T, int N, int K, int P> hipError_t launch_step_conv(const Ste
     return hipGetLastError();
 }
 
+template <int N, int U> hipError_t launch_step_xproj(const StepArgs &a, hipStream_t stream)
+{
+    const int64_t per_block = (int64_t)kBlock * U, row4 = a.D * (N / 4);
+    const dim3 grid((unsigned)((row4 + per_block - 1) / per_block), (unsigned)a.n_out);
+    const XprojSplit sp = xproj_split((int)a.dt_rank + 2 * N, a.n_parts);
+    const bool exact = sp.per == kParts && sp.sides * kParts == a.n_parts, more = sp.per > kParts;
+#define MAMBA_STEP_X(NC, EX, MR)                                                                  \
+    state_step_xproj_kernel<N, U, NC, EX, MR><<<grid, kBlock, 0, stream>>>(                       \
+        a.xpart, a.n_parts, sp.sides, sp.per, sp.magic, (int)a.D, (int)a.dt_rank, a.parent, a.h_in,                       \
+        static_cast<const bf16_t *>(a.dt_w), static_cast<const bf16_t *>(a.x), static_cast<const bf16_t *>(a.z), a.A, \
+        a.dt_bias, a.Dskip, a.h_out, static_cast<bf16_t *>(a.out), a.n_in)
+#define MAMBA_STEP_XC(NC) do { if (exact) MAMBA_STEP_X(NC, true, false); else if (more) MAMBA_STEP_X(NC, false, true); else MAMBA_STEP_X(NC, false, false); } while (0)
+    if (N == 16 && a.dt_rank == 32) MAMBA_STEP_XC(2);
+    else if (N == 16 && a.dt_rank == 48) MAMBA_STEP_XC(3);
+    else if (N == 16 && a.dt_rank == 64) MAMBA_STEP_XC(4);
+    else MAMBA_STEP_XC(0);
+#undef MAMBA_STEP_XC
+#undef MAMBA_STEP_X
+    return hipGetLastError();
+}
+
 template <typename T, int N> hipError_t launch_step_n(const StepArgs &a, hipStream_t stream)
 {
     if (a.conv_w) {
@@ -643,6 +636,13 @@ template <typename T, int N> hipError_t launch_step_n(const StepArgs &a, hipStre
     // the plain step with eight per lane while that gives between 1.5 and 4 workgroups per CU: 64 branches x 4096
     // channels 8.7 -> 7.6 us, the time of a bare copy of the same state rows; 128 branches are better off with four
     if (!a.dt_w && blocks(8) >= 384 && blocks(8) < 1024) return launch_step_u<T, N, 8>(a, stream);
+    if constexpr (sizeof(T) == 2) {
+        if (a.xpart) {
+            if (!a.dt_w || !a.z || !a.dt_softplus || a.dt_rank + 2 * N > kBlock || a.dt_rank % 4 || a.n_parts < 1 || a.D >= (int64_t)1 << 26) return hipErrorInvalidValue;
+            if (blocks(4) >= 768) return launch_step_xproj<N, 4>(a, stream);
+            return blocks(2) >= 768 ? launch_step_xproj<N, 2>(a, stream) : launch_step_xproj<N, 1>(a, stream);
+        }
+    }
     if (blocks(kStepUnroll) >= 768) return launch_step_u<T, N, kStepUnroll>(a, stream);
     if (kStepUnroll > 2 && blocks(2) >= 768) return launch_step_u<T, N, 2>(a, stream);
     return launch_step_u<T, N, 1>(a, stream);

@@ -1455,15 +1455,11 @@ def test_block_step_of_wide_models(m, n, dm, D, N, K, R):
     test_block_step_more_branches(m, n, dm, D, N, K, R)
 
 
-@pytest.mark.parametrize("dm", [8, 72, 256, 512, 576, 768, 1024, 1536, 2048, 2056])
-@pytest.mark.parametrize("n,K", [(2, 4), (17, 4), (64, 4), (15, 3), (49, 2)])
-def test_block_step_every_split_of_k(m, n, dm, K):
-    """Every way the wavefronts of the kernel in front share k (one trip, several, remainders of a step), with one, two and four
-    row tiles.  Bounds against the unrounded block: five tensors on the way (u, x_c, z, y, out) are rounded to bf16, at most
-    2^-9 of a value each, so their errors add up to less than 2^-9 sqrt(5) < 2^-7 of the result's 2-norm, and the largest of up
-    to 131072 elements lies within six of that."""
-    D, N, R = (1552 if n > 16 else 80), 16, 8
-    say(n=n, dm=dm, D=D, K=K)
+def block_step_within_roundings(m, n, dm, D, N, K, R):
+    """Bounds against the unrounded block: five tensors on the way (u, x_c, z, y, out) are rounded to bf16, at most 2^-9 of a
+    value each, so their errors add up to less than 2^-9 sqrt(5) < 2^-7 of the result's 2-norm, and the largest of up to 131072
+    elements lies within six of that."""
+    say(n=n, dm=dm, D=D, N=N, K=K, R=R)
     rng = np.random.default_rng(n + dm + D)
     w, w64, blk = make_block(m, rng, dm, D, N, K, R)
     conv = synth.to_io(rng.standard_normal((5, D, K - 1)).astype(np.float32), synth.BF16)
@@ -1476,6 +1472,22 @@ def test_block_step_every_split_of_k(m, n, dm, K):
         got = np.asarray(got, dtype=np.float64)
         assert np.linalg.norm(got - ref) <= 2.0 ** -7 * np.linalg.norm(ref), what
         assert_close(got, ref, 6 * 2.0 ** -7, what)
+
+
+@pytest.mark.parametrize("dm", [8, 72, 256, 512, 576, 768, 1024, 1536, 2048, 2056])
+@pytest.mark.parametrize("n,K", [(2, 4), (17, 4), (64, 4), (15, 3), (49, 2)])
+def test_block_step_every_split_of_k(m, n, dm, K):
+    """Every way the wavefronts of the kernel in front share k (one trip, several, remainders of a step), with one, two and four
+    row tiles."""
+    block_step_within_roundings(m, n, dm, 1552 if n > 16 else 80, 16, K, 8)
+
+
+@pytest.mark.parametrize("n,D,N,R", [(2, 16, 16, 48), (3, 48, 16, 32), (2, 1280, 16, 64), (9, 1536, 16, 48), (64, 1536, 16, 48), (3, 2048, 16, 32),
+                                     (64, 3072, 16, 48), (5, 1552, 16, 64), (4, 96, 4, 8), (7, 528, 8, 40), (2, 640, 32, 128)])
+def test_block_step_every_split_of_the_partial_sums(m, n, D, N, R):
+    """Partial sums of the x projection in ranges of eight (exactly), fewer and more, with one, two and four float4s per lane
+    and every way a lane holds its weights of the dt projection."""
+    block_step_within_roundings(m, n, 64, D, N, 4, R)
 
 
 def test_block_step_bad_parent_poisons_only_that_branch(m):
