@@ -39,6 +39,12 @@ __device__ __forceinline__ float exp2_hw(float v) { return __builtin_amdgcn_exp2
 __device__ __forceinline__ float log2_hw(float v) { return __builtin_amdgcn_logf(v); }
 __device__ __forceinline__ float rcp_hw(float v) { return __builtin_amdgcn_rcpf(v); }
 
+// Kernel arguments that are used last would be fetched last, a trip to the scalar cache ahead of a kernel's final stores; a value
+// requested early but used only under a condition would be requested there.  Naming them where they should be there keeps both.
+template <typename P> __device__ __forceinline__ void arg_here(P p) { asm volatile("" ::"s"(p)); }
+template <typename... P> __device__ __forceinline__ void args_here(P... p) { (arg_here(p), ...); }
+__device__ __forceinline__ void values_here(float &v) { asm volatile("" : "+v"(v)); }
+
 // softplus(v) = log(1 + e^v) = max(v, 0) + log1p(w), w = e^-|v| <= 1, to ~1e-7 relative (plus the
 // rounding of the exp2 argument for large |v|).  The sum s = 1 + w drops w's low bits; they are
 // recovered exactly as r = w - (s - 1) and added back: log1p(w) = log(s) + log1p(r / s), which is

@@ -58,12 +58,13 @@ draft_in_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, cons
     constexpr int kThr = 64 * NW, H = CK - 1;
     static_assert(16 * G <= 64, "a lane fetches one piece of the norm weights");
     constexpr int kStep = (1 + MT) * 2048;                         // fragments of one step: w, then MT row tiles
-    constexpr int PB = G * NW * kStep <= 64 * 1024 ? G : 1;     // patches in turn: more than one workgroup to a CU
+    constexpr int PB = G * NW * kStep <= 48 * 1024 ? G : 1;     // patches in turn: several workgroups to a CU
     constexpr int OPT = (MT * 256 + kThr - 1) / kThr;              // outputs per thread
     constexpr int kXcRow = 24;                                     // elements between rows of the finished columns (48 bytes: 8-byte aligned, spread over the banks)
     constexpr int XT = MT == 1 && NW >= 5 ? 1 : 2;                 // x projection tiles of a wavefront whose weights are fetched ahead
-    __shared__ __attribute__((aligned(16))) unsigned char patch[NW][PB][kStep];
-    __shared__ __attribute__((aligned(16))) float part[NW][MT][4][64];
+    // a wavefront's patches, and its partial tiles once it is done with those
+    constexpr int kWave = PB * kStep > MT * 1024 ? PB * kStep : MT * 1024;
+    __shared__ __attribute__((aligned(16))) unsigned char patch[NW][kWave];
     __shared__ __attribute__((aligned(16))) float4 norm_lds[NW][16 * G];
     __shared__ __attribute__((aligned(16))) float ssq[MT * 16][NW];
     __shared__ __attribute__((aligned(16))) uint16_t xc[MT * 16 * kXcRow];
@@ -155,7 +156,7 @@ draft_in_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, cons
         if (lane < 16u * G) norm_lds[wave][lane] = nw;
         wave_sync();
         auto fill = [&](int g) __attribute__((always_inline)) {
-            unsigned char *p = patch[wave][g % PB];
+            unsigned char *p = patch[wave] + g % PB * kStep;
             const bool ok = EVEN || (s0 + g < s_end && 8u * (unsigned)(s0 + g) + lch < kchunks);   // else zeros: adds nothing
 #pragma unroll
             for (int t = 0; t < 2; ++t) *reinterpret_cast<u32x4 *>(p + 1024 * t + put) = ok ? wf[g][t] : u32x4(0u);
@@ -175,7 +176,7 @@ draft_in_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, cons
             }
         };
         auto product = [&](int g) __attribute__((always_inline)) {
-            const unsigned char *p = patch[wave][g % PB];
+            const unsigned char *p = patch[wave] + g % PB * kStep;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const unsigned get = h ? get1 : get0;
@@ -203,7 +204,7 @@ draft_in_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, cons
 #pragma unroll
     for (int t = 0; t < MT; ++t)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) part[wave][t][i][lane] = acc[t][i];
+        for (int i = 0; i < 4; ++i) reinterpret_cast<float *>(patch[wave])[(4 * t + i) * 64 + lane] = acc[t][i];
 #pragma unroll
     for (int t = 0; t < 2 * MT; ++t) {
         // the sum over the eight lanes of a row: quad_perm [1,0,3,2], [2,3,0,1], row_half_mirror
@@ -217,7 +218,7 @@ draft_in_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, cons
         const int o = tid + j * kThr, t = (o >> 8) < MT ? o >> 8 : 0, i = (o >> 6) & 3;
         float v = 0.0f, sq = 0.0f;
 #pragma unroll
-        for (int q = 0; q < NW; ++q) v += part[q][t][i][lane];
+        for (int q = 0; q < NW; ++q) v += reinterpret_cast<const float *>(patch[q])[(4 * t + i) * 64 + lane];
 #pragma unroll
         for (int q = 0; q < NW; ++q) sq += ssq[16 * t + 4 * lg + i][q];
         v *= __builtin_amdgcn_rsqf(fmaf(sq, inv_k, eps));

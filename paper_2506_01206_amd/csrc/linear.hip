@@ -451,17 +451,6 @@ linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
     }
 }
 
-// ---------------------------------------------------------------------------------------------------
-// Few output tiles and a long k loop (the projections of a short context, x_proj of one of a few thousand tokens): walked
-// slab by slab such a product takes a memory latency per slab on a part of the chip, so here a workgroup's whole k range
-// is in flight at once.  One workgroup per 32 output columns and 32 MB rows; its eight wavefronts take the 64-wide k
-// blocks round robin, three of them at a time, and their partial tiles are added through LDS.  A wavefront fetches a k
-// block of 32 rows x 128 bytes with four 16-byte loads per lane, eight lanes on one row, so that every load instruction
-// covers whole 128-byte lines (what the address path takes time for: about 4 cycles a line); the block then goes through
-// a 4 KiB LDS patch private to the wavefront (16-byte slots xor-swizzled by the row, conflict-free both ways) and comes
-// back as MFMA fragments: lane (r, h) takes the slots 4 h .. 4 h + 3 of row r, one per k16 step.  Both operands use the
-// same slot order, so the sum over k is complete.
-// grid: (ceil(N / 32), ceil(M / (32 MB)))
 __device__ __forceinline__ void wave_sync()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -469,227 +458,130 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int MB>
-__global__ void __launch_bounds__(512)
-linear_split_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, const float *__restrict__ bias,
-                    const bf16_t *residual, OutSplit out, int64_t M, int64_t N, int64_t K)
-{
-    constexpr int NW = 8, G = 3;
-    constexpr int OPT = MB * 1024 / (NW * 64);                    // outputs per thread
-    // in the main loop 1 + MB patches of 4 KiB per wavefront (w block, x blocks), afterwards the partial tiles
-    __shared__ __attribute__((aligned(16))) unsigned char lds[NW * (1 + MB) * 4096];
-    float (*part)[MB * 16][64] = reinterpret_cast<float (*)[MB * 16][64]>(lds);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int r = lane & 31, h = lane >> 5;                       // fragment view: row, k half
-    const int lrow = lane >> 3, lch = lane & 7;                   // load view: row (+ 8 i), 16-byte slot
-    const int64_t n0 = (int64_t)blockIdx.x * 32, m0 = (int64_t)blockIdx.y * (32 * MB);
-    const int64_t kchunks = K / 8, kblocks = (K + 63) / 64;
-    uint4 *patch_w = reinterpret_cast<uint4 *>(lds + wave * (1 + MB) * 4096), *patch_x = patch_w + 256;
-    const int put = lrow * 8 + (lch ^ lrow);                      // + 64 i: slot of row lrow + 8 i ((lrow + 8 i) & 7 == lrow)
-    int get[4];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) get[s] = r * 8 + ((4 * h + s) ^ (r & 7));
-
-    const uint4 *wptr[4], *xptr[MB][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t n = n0 + lrow + 8 * i;                      // columns past N and rows past M repeat the last one, never stored
-        wptr[i] = reinterpret_cast<const uint4 *>(w + (n < N ? n : N - 1) * K);
-#pragma unroll
-        for (int b = 0; b < MB; ++b) {
-            const int64_t m = m0 + b * 32 + lrow + 8 * i;
-            xptr[b][i] = reinterpret_cast<const uint4 *>(x + (m < M ? m : M - 1) * K);
-        }
-    }
-    // output o = tid + 512 j: row block o / 1024, accumulator i = o / 64 % 16 of lane o % 64; what it needs besides its
-    // sum is fetched ahead of the main loop
-    int64_t off[OPT];
-    int sp[OPT];
-    float bv[OPT];
-    uint16_t res[OPT];
-#pragma unroll
-    for (int j = 0; j < OPT; ++j) {
-        const int o = tid + j * 512, i = (o >> 6) & 15;
-        const int64_t m = m0 + (o >> 10) * 32 + 8 * (i >> 2) + 4 * h + (i & 3), n = n0 + r;
-        bv[j] = 0.0f;
-        res[j] = 0;
-        sp[j] = -1;
-        off[j] = 0;
-        if (m >= M || n >= N) continue;
-        int64_t col;
-        sp[j] = locate(out, n, &col);
-        off[j] = m * (sp[j] == 0 ? out.width[0] : sp[j] == 1 ? out.width[1] : out.width[2]) + col;
-        if (bias) bv[j] = bias[n];
-        if (residual) res[j] = residual[off[j]];
-    }
-    f32x16 acc[MB];
-#pragma unroll
-    for (int b = 0; b < MB; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[b][i] = 0.0f;
-
-    for (int64_t blk0 = wave; blk0 < kblocks; blk0 += NW * G) {
-        uint4 wf[G][4], xf[G][MB][4];
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const int64_t c = (blk0 + g * NW) * 8 + lch;
-            const bool ok = c < kchunks;                          // also false for blocks past the last
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                wf[g][i] = ok ? wptr[i][c] : make_uint4(0, 0, 0, 0);
-#pragma unroll
-                for (int b = 0; b < MB; ++b) xf[g][b][i] = ok ? xptr[b][i][c] : make_uint4(0, 0, 0, 0);
-            }
-        }
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            bf16x8 wv[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                patch_w[put + 64 * i] = wf[g][i];
-#pragma unroll
-                for (int b = 0; b < MB; ++b) patch_x[256 * b + put + 64 * i] = xf[g][b][i];
-            }
-            wave_sync();
-#pragma unroll
-            for (int s = 0; s < 4; ++s) wv[s] = __builtin_bit_cast(bf16x8, patch_w[get[s]]);
-#pragma unroll
-            for (int b = 0; b < MB; ++b)
-#pragma unroll
-                for (int s = 0; s < 4; ++s)
-                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, patch_x[256 * b + get[s]]), wv[s], acc[b], 0, 0, 0);
-            wave_sync();
-        }
-    }
-    __syncthreads();                                              // patches are done with: their memory is reused below
-    // acc[b][i] is C[m = 32 b + 8 (i / 4) + 4 (lane / 32) + i % 4][n = n0 + lane % 32]
-#pragma unroll
-    for (int b = 0; b < MB; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) part[wave][16 * b + i][lane] = acc[b][i];
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < OPT; ++j) {
-        const int o = tid + j * 512;
-        float v = 0.0f;
-#pragma unroll
-        for (int q = 0; q < NW; ++q) v += part[q][o >> 6][lane];
-        if (sp[j] < 0) continue;
-        v = bf16_to_f32(f32_to_bf16(v + bv[j]));                  // same two roundings as the tiled kernel
-        if (residual) v += bf16_to_f32(res[j]);
-        (sp[j] == 0 ? out.ptr[0] : sp[j] == 1 ? out.ptr[1] : out.ptr[2])[off[j]] = (bf16_t)f32_to_bf16(v);
-    }
-}
-
 // ---------------------------------------------------------------------------------------------------
-// A draft position (M <= 64 rows, Sec. 4.1; the way into a block is draft_in.hip): w is read once, nothing is big, and what counts
-// is the number of trips to memory and of barriers between the launch and the last store.  One workgroup per 16 output columns and
-// 16 MT rows, its eight wavefronts share the k range in contiguous pieces of steps.
+// Few output tiles (a draft position, Sec. 4.1, whose way into a block is draft_in.hip; a short context; the narrow products of a
+// longer one): nothing is big, and what counts is the number of trips to memory and of barriers between the launch and the last
+// store, and the instructions between them.  One workgroup per 8 CG output columns and 16 MT rows, its NW wavefronts share the
+// k range in contiguous pieces of steps of 64, G steps of a wavefront in flight.
 // A fragment of v_mfma_f32_16x16x32_bf16 wants row l % 16 in lane l; loaded like that, no two lanes of a quad share a
 // 64-byte piece of a line and the address path takes a cycle per lane (60 for the 1 KiB, measured over 192 loads a CU).
 // With a row's 64 bytes on the four lanes of a quad it takes 34, with 128 on eight lanes about half of that, so that is
-// how rows are loaded; a patch of LDS private to the wavefront turns them into fragments.  KW: the k of a step, 64 (whole
-// lines) from K = 1024 on, where every wavefront has two steps or more: out_proj of 12 rows 3.9 -> 3.6 us, x_proj of 333
-// rows 3.9 -> 3.7, 128 rows x 768 5.2 -> 4.4.  On a shorter k steps of 64 leave wavefronts with one step or none and asking
-// for rows that do not exist (64 x 1024, K = 512: 2.9 us against 3.4), and a branch around those requests costs more than it
-// saves (3.6 -> 3.9 us).
+// how rows are loaded; a patch of LDS private to the wavefront turns them into fragments, and later holds its partial tiles.
+// A CU's share of that path is what a workgroup of 16 columns and 16 rows takes longest for (K = 1536: 96 such loads), so eight
+// columns where that does not make a second round of workgroups (their fragments' other half is never written nor used).
 // The partial tiles of the wavefronts meet in LDS, one output per thread; what else an output needs (bias, residual) has been on
 // its way since before the main loop.
-// (16 wavefronts, or six k steps in flight instead of three, measured the same.)
+// us in chains of 24 different weights, replayed (before: 64-byte pieces, the residual waited for where it was fetched, twice the
+// LDS; 32-column tiles for the larger ones): 12 x 768, K = 1536 3.10 (3.71), 64 x 768 3.4 (3.9), 128 x 3072, K = 768 4.8 (7.0), 333 x 768,
+// K = 1536 6.3 (8.5), 512 x 512, K = 1024 4.7 (5.9).
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
-template <int MT, int KW>
-__global__ void __launch_bounds__(512)
+// EVEN: K = 64 NW G, one trip of every wavefront; otherwise any K that is a multiple of 8.
+template <int MT, int CG, int NW, int G, bool EVEN>
+__global__ void __launch_bounds__(64 * NW)
 linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, const float *__restrict__ bias,
-                  const bf16_t *residual, OutSplit out, int M, int N, int K)
+                  const bf16_t *residual, int M, int N, int K, OutSplit out)
 {
-    constexpr int NW = 8, kThr = NW * 64, G = 3;                   // G: k steps in flight per wavefront
-    constexpr int C = KW / 8;                                      // 16-byte chunks of a row in a step of KW
-    constexpr int LT = C / 4, RL = 16 / LT;                        // loads per 16-row tile, rows per load
-    constexpr int PB = KW == 32 ? G : 2;                           // patches in turn
+    constexpr int kThr = NW * 64;
+    constexpr int kStep = (1 + MT) * 2048;                         // fragments of one step: w, then MT row tiles
+    constexpr int PB = G * NW * kStep <= 32 * 1024 ? G : 1;        // patches in turn: several workgroups to a CU
     constexpr int OPT = (MT * 256 + kThr - 1) / kThr;              // outputs per thread
-    __shared__ __attribute__((aligned(16))) uint4 patch[NW][PB][1 + MT][64 * LT];
-    __shared__ __attribute__((aligned(16))) float part[NW][MT][4][64];
-    const int tid = threadIdx.x, lane = tid & 63;
+    // a wavefront's patches, and its partial tiles once it is done with those
+    constexpr int kWave = PB * kStep > MT * 1024 ? PB * kStep : MT * 1024;
+    __shared__ __attribute__((aligned(16))) unsigned char patch[NW][kWave];
+    const unsigned tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int li = lane & 15, lg = lane >> 4;                      // fragment view: row, 16-byte chunk of a k32 half
-    const int lrow = lane / C, lch = lane % C;                     // load view: row (+ RL), 16-byte chunk of the step
-    auto slot = [](int row, int chunk) { return row * C + (chunk ^ (C == 8 ? row & 7 : row >> 2)); };   // no bank conflicts either way
-    const int put = slot(lrow, lch);                               // + 64: RL rows further
-    int get[LT];
-#pragma unroll
-    for (int h = 0; h < LT; ++h) get[h] = slot(li, lg + 4 * h);
-    const int n0 = blockIdx.x * 16, m0 = blockIdx.y * (16 * MT);
-    const int w0 = (int)out.width[0], w1 = (int)out.width[1];
+    const unsigned li = lane & 15, lg = lane >> 4;                 // fragment view: row, 16-byte chunk of a k32 half
+    const unsigned lrow = lane >> 3, lch = lane & 7;               // load view: row (+ 8 t), 16-byte chunk of the step
+    const int n0 = blockIdx.x * (8 * CG), m0 = blockIdx.y * (16 * MT);
 
-    // ---- what the outputs of this thread need besides their sums (nothing is used where it is fetched)
-    float tail_bias[OPT];
-    uint16_t tail_res[OPT];
-    int om[OPT], on[OPT];
-    bool live[OPT];
+    // ---- what the outputs of this thread need besides their sums (nothing is used where it is fetched): tile o / 256,
+    // accumulator (o / 64) % 4 of lane o % 64
+    const int on = n0 + (int)li;
+    const unsigned col_in = (unsigned)min(on, N - 1);
+    int om[OPT];
+    uint16_t res[OPT];
+    // (unconditional requests: one under a condition is converted, and so waited for, inside its branch)
+    float bias_in = (bias ? bias : reinterpret_cast<const float *>(x))[bias ? col_in : 0u];
 #pragma unroll
     for (int j = 0; j < OPT; ++j) {
-        const int o = tid + j * kThr, r = o & 255, l = r & 63;     // tile o / 256, accumulator r / 64 of lane l
-        om[j] = m0 + (o >> 8) * 16 + 4 * (l >> 4) + (r >> 6);
-        on[j] = n0 + (l & 15);
-        live[j] = o < MT * 256 && om[j] < M && on[j] < N;
-        tail_bias[j] = 0.0f;
-        tail_res[j] = 0;
-        if (!live[j]) continue;
-        if (bias) tail_bias[j] = bias[on[j]];
-        if (residual) tail_res[j] = residual[(int64_t)om[j] * N + on[j]];          // single output tensor
+        const int o6 = wave + j * NW;
+        om[j] = m0 + (o6 >> 2) * 16 + (o6 & 3) + 4 * (int)lg;
+        res[j] = (residual ? residual : x)[residual ? (int64_t)min(om[j], M - 1) * N + col_in : 0];   // single output tensor
     }
+    __builtin_amdgcn_sched_barrier(0);
 
-    // ---- the wavefront's share of k: steps [s_first, s_end) of KW
-    const int steps = (K + KW - 1) / KW, per = (steps + NW - 1) / NW;
-    const int s_first = wave * per, s_end = s_first + per < steps ? s_first + per : steps;
-    const int kchunks = K >> 3;                                    // K % 8 == 0
-    const uint4 *wrow[LT], *xrow[LT * MT];
+    // ---- the wavefront's share of k: steps [s_first, s_end)
+    const int steps = EVEN ? NW * G : (K + 63) >> 6, per = EVEN ? G : (steps + NW - 1) / NW;
+    const int s_first = wave * per, s_end = EVEN || s_first + per < steps ? s_first + per : steps;
+    const unsigned kchunks = (unsigned)K >> 3;                     // K % 8 == 0
+    const char *wb = reinterpret_cast<const char *>(w + (int64_t)n0 * K), *xb = reinterpret_cast<const char *>(x + (int64_t)m0 * K);
+    unsigned wo[CG], xo[2 * MT];
+    int64_t wfar[CG], xfar[2 * MT];
 #pragma unroll
-    for (int t = 0; t < LT; ++t) {
-        const int n = n0 + RL * t + lrow;
-        wrow[t] = reinterpret_cast<const uint4 *>(w + (int64_t)(n < N ? n : N - 1) * K);
+    for (unsigned t = 0; t < CG; ++t) {
+        const unsigned r = min(8 * t + lrow, (unsigned)(N - 1 - n0));
+        wo[t] = r * (2u * (unsigned)K) + 16 * lch;
+        wfar[t] = (int64_t)r * 2 * K + 16 * lch;
     }
 #pragma unroll
-    for (int t = 0; t < LT * MT; ++t) {
-        const int m = m0 + RL * t + lrow;
-        xrow[t] = reinterpret_cast<const uint4 *>(x + (int64_t)(m < M ? m : M - 1) * K);   // rows past M repeat the last one, never stored
+    for (unsigned t = 0; t < 2 * MT; ++t) {
+        const unsigned r = min(8 * t + lrow, (unsigned)(M - 1 - m0));   // rows past M repeat the last one, never stored
+        xo[t] = r * (2u * (unsigned)K) + 16 * lch;
+        xfar[t] = (int64_t)r * 2 * K + 16 * lch;
     }
+    const unsigned put = (lrow * 8 + (lch ^ lrow)) * 16;           // + 1024 t: chunks xor-swizzled by the row, no bank conflicts either way
+    const unsigned get0 = (li * 8 + (lg ^ (li & 7))) * 16, get1 = (li * 8 + ((lg + 4) ^ (li & 7))) * 16;
+
     f32x4v acc[MT];
 #pragma unroll
     for (int t = 0; t < MT; ++t) acc[t] = f32x4v(0.0f);
-    for (int s0 = s_first; s0 < s_end; s0 += G) {
-        uint4 wf[LT][G], xf[LT * MT][G];
+    bool first = true;
+    for (int s0 = s_first; EVEN ? first : s0 < s_end; s0 += G) {
+        first = false;
+        u32x4 wf[G][CG], xf[G][2 * MT];
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const int c = C * (s0 + g) + lch;
-            const int cc = s0 + g < s_end && c < kchunks ? c : 0;
+            const int s = EVEN || s0 + g < s_end ? s0 + g : 0;
+            const unsigned back = EVEN || 8u * (unsigned)s + lch < kchunks ? 0u : 16 * lch;   // chunks past K re-read the step's first one
+            const char *ws = wb + (int64_t)s * 128, *xs = xb + (int64_t)s * 128;
 #pragma unroll
-            for (int t = 0; t < LT; ++t) wf[t][g] = wrow[t][cc];
+            for (int t = 0; t < CG; ++t) wf[g][t] = *reinterpret_cast<const u32x4 *>(EVEN ? ws + wo[t] : ws + (wfar[t] - back));
 #pragma unroll
-            for (int t = 0; t < LT * MT; ++t) xf[t][g] = xrow[t][cc];
+            for (int t = 0; t < 2 * MT; ++t) xf[g][t] = *reinterpret_cast<const u32x4 *>(EVEN ? xs + xo[t] : xs + (xfar[t] - back));
         }
         __builtin_amdgcn_sched_barrier(0);                         // all of it in flight before any of it is used
+        if (s0 == s_first) args_here(out.ptr[0], out.ptr[1], out.ptr[2], out.width[0], out.width[1], out.width[2]);
         auto fill = [&](int g) __attribute__((always_inline)) {
-            const bool ok = s0 + g < s_end && C * (s0 + g) + lch < kchunks;   // else zeros: adds nothing
+            unsigned char *p = patch[wave] + g % PB * kStep;
+            const bool ok = EVEN || (s0 + g < s_end && 8u * (unsigned)(s0 + g) + lch < kchunks);   // else zeros: adds nothing
 #pragma unroll
-            for (int t = 0; t < LT; ++t) patch[wave][g % PB][0][64 * t + put] = ok ? wf[t][g] : make_uint4(0, 0, 0, 0);
+            for (int t = 0; t < CG; ++t) *reinterpret_cast<u32x4 *>(p + 1024 * t + put) = ok ? wf[g][t] : u32x4(0u);
 #pragma unroll
-            for (int t = 0; t < LT * MT; ++t) patch[wave][g % PB][1 + t / LT][64 * (t % LT) + put] = ok ? xf[t][g] : make_uint4(0, 0, 0, 0);
+            for (int t = 0; t < 2 * MT; ++t) *reinterpret_cast<u32x4 *>(p + 2048 + 1024 * t + put) = ok ? xf[g][t] : u32x4(0u);
         };
+        auto product = [&](int g) __attribute__((always_inline)) {
+            const unsigned char *p = patch[wave] + g % PB * kStep;
 #pragma unroll
-        for (int g = 0; g < (PB < G ? 1 : G); ++g) fill(g);
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            if (PB < G && g + 1 < G) fill(g + 1);
-            wave_sync();
-#pragma unroll
-            for (int h = 0; h < LT; ++h) {
-                const bf16x8 wv = __builtin_bit_cast(bf16x8, patch[wave][g % PB][0][get[h]]);
+            for (int h = 0; h < 2; ++h) {
+                const unsigned get = h ? get1 : get0;
+                const bf16x8 wv = *reinterpret_cast<const bf16x8 *>(p + get);
 #pragma unroll
                 for (int t = 0; t < MT; ++t)
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, patch[wave][g % PB][1 + t][get[h]]), wv, acc[t], 0, 0, 0);
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8 *>(p + 2048 * (1 + t) + get), wv, acc[t], 0, 0, 0);
             }
+        };
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            fill(g);
+            wave_sync();
+            if (PB == G) continue;
+            product(g);
+            wave_sync();
+        }
+        if constexpr (PB == G) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) product(g);
             wave_sync();
         }
     }
@@ -697,26 +589,46 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
 #pragma unroll
     for (int t = 0; t < MT; ++t)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) part[wave][t][i][lane] = acc[t][i];
+        for (int i = 0; i < 4; ++i) reinterpret_cast<float *>(patch[wave])[(4 * t + i) * 64 + lane] = acc[t][i];
+    values_here(bias_in);
     lds_barrier_linear();
 
 #pragma unroll
     for (int j = 0; j < OPT; ++j) {
-        const int o = tid + j * kThr, t = (o >> 8) < MT ? o >> 8 : 0, i = (o >> 6) & 3, l = o & 63;
+        const int o6 = wave + j * NW, t = (o6 >> 2) < MT ? o6 >> 2 : 0, i = o6 & 3;
         float v = 0.0f;
 #pragma unroll
-        for (int q = 0; q < NW; ++q) v += part[q][t][i][l];
-        if (!live[j]) continue;
-        v = bf16_to_f32(f32_to_bf16(v + tail_bias[j]));            // same two roundings as the tiled kernel
-        int col = on[j], width = w0, sp = 0;
-        if (col >= w0) {
-            col -= w0; width = w1; sp = 1;
-            if (col >= w1) { col -= w1; width = (int)out.width[2]; sp = 2; }
+        for (int q = 0; q < NW; ++q) v += reinterpret_cast<const float *>(patch[q])[(4 * t + i) * 64 + lane];
+        if (o6 >= 4 * MT || om[j] >= M || on >= N || li >= 8 * CG) continue;
+        v = bf16_to_f32(f32_to_bf16(v + (bias ? bias_in : 0.0f)));   // same two roundings as the tiled kernel
+        if (residual) {
+            out.ptr[0][(int64_t)om[j] * N + on] = (bf16_t)f32_to_bf16(v + bf16_to_f32(res[j]));
+            continue;
         }
-        bf16_t *optr = sp == 0 ? out.ptr[0] : sp == 1 ? out.ptr[1] : out.ptr[2];
-        if (residual) v += bf16_to_f32(tail_res[j]);
-        optr[(int64_t)om[j] * width + col] = (bf16_t)f32_to_bf16(v);
+        int64_t col;
+        const int sp = locate(out, on, &col);
+        (sp == 0 ? out.ptr[0] : sp == 1 ? out.ptr[1] : out.ptr[2])[(int64_t)om[j] * (sp == 0 ? out.width[0] : sp == 1 ? out.width[1] : out.width[2]) + col] =
+            (bf16_t)f32_to_bf16(v);
     }
+}
+
+template <int MT, int CG>
+hipError_t launch_few(const bf16_t *x, const bf16_t *w, const float *bias, const bf16_t *res, const OutSplit &o, int64_t M, int64_t N, int64_t K,
+                      hipStream_t stream)
+{
+    const dim3 grid((unsigned)((N + 8 * CG - 1) / (8 * CG)), (unsigned)((M + 16 * MT - 1) / (16 * MT)));
+#define MAMBA_FEW(NW, G, EVEN) linear_few_kernel<MT, CG, NW, G, EVEN><<<grid, 64 * NW, 0, stream>>>(x, w, bias, res, (int)M, (int)N, (int)K, o)
+    const int64_t per = (K + 511) / 512;
+    if (K == 256) MAMBA_FEW(4, 1, true);
+    else if (K < 256) MAMBA_FEW(4, 1, false);
+    else if (K == 512) MAMBA_FEW(8, 1, true);
+    else if (K == 768) MAMBA_FEW(6, 2, true);
+    else if (K == 1024) MAMBA_FEW(8, 2, true);
+    else if (K == 1536) MAMBA_FEW(8, 3, true);
+    else if (per <= 2 || per == 4) MAMBA_FEW(8, 2, false);
+    else MAMBA_FEW(8, 3, false);
+#undef MAMBA_FEW
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -733,44 +645,26 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     const bf16_t *x = static_cast<const bf16_t *>(a.x), *w = static_cast<const bf16_t *>(a.w);
     const bf16_t *res = static_cast<const bf16_t *>(a.residual);
     auto tiles = [&](int64_t bm, int64_t bn) { return ((N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
-#define MAMBA_FEW_K(MT, KW) linear_few_kernel<MT, KW><<<dim3((unsigned)((N + 15) / 16), (unsigned)((a.M + 16 * MT - 1) / (16 * MT))), 512, 0, stream>>>(x, w, a.bias, res, o, (int)a.M, (int)N, (int)a.K)
-#define MAMBA_FEW(MT) do { if (a.K >= 1024) MAMBA_FEW_K(MT, 64); else MAMBA_FEW_K(MT, 32); } while (0)
+#define MAMBA_FEW(MT, CG) return launch_few<MT, CG>(x, w, a.bias, res, o, a.M, N, a.K, stream)
     if (a.norm_w) return launch_draft_in(a, stream);
-    // Few output tiles: latency decides, and the tiles are kept so small that they just fill the CUs once (a second
-    // round of workgroups costs nearly as much again: 256 rows x 768 columns, K = 1536, on 32 x 32 tiles 5.9 us, 264 rows
-    // 9.4 us; a fifth of a round does not).  Tiles 16 columns wide while 16 or 32 rows each are enough, or 64 on a short k;
-    // they fetch x for every 16 columns anew, so beyond that the 32-column tiles: 32 rows from where every wavefront has
-    // a k block, 64 rows from where it has two (on less the slab kernel, 64 x 64 tiles, is as fast).
-    // us on      16x16 32x16 64x16 32x32 64x32 slabs  (x: more than one round)
-    //   64 x 1024, K = 512    2.9   3.3   4.0   4.8   6.5   5.6        333 x 80, K = 1536    3.7   4.4   6.2   5.7   7.6  10.4
-    //  128 x  768, K = 1536   4.6x  4.4   6.2   5.6   7.7  10.5        333 x 640, K = 768    5.1x  5.7x  4.7   5.3   7.1   7.0
-    //  256 x  768, K = 1536   6.0x  7.0x  6.3   5.6   7.6  10.5        512 x 768, K = 1536   9.5x  9.9x 10.6x  9.3x  7.7  10.6
-    const bool few = linear_few_fits(N, a.K);
-    if (few && tiles(16, 16) <= kTilesResident * 5 / 4) { MAMBA_FEW(1); return hipGetLastError(); }
-    if (few && tiles(32, 16) <= kTilesResident) { MAMBA_FEW(2); return hipGetLastError(); }
-    if (a.K <= 768 && tiles(64, 16) <= kTilesResident) { MAMBA_FEW_K(4, 32); return hipGetLastError(); }
-    if (a.K >= 512 && tiles(32, 32) <= kTilesResident) {
-        const dim3 grid((unsigned)((N + 31) / 32), (unsigned)((a.M + 31) / 32));
-        linear_split_kernel<1><<<grid, 512, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K);
-        return hipGetLastError();
-    }
-    if (a.K >= 1024 && tiles(64, 32) <= kTilesResident) {
-        const dim3 grid((unsigned)((N + 31) / 32), (unsigned)((a.M + 63) / 64));
-        linear_split_kernel<2><<<grid, 512, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K);
-        return hipGetLastError();
-    }
-    // what is left of the few rows, except for very wide outputs (the LM head), where the tiled kernel's shared x tile
-    // reads less
-    if (few && a.M <= 64 && N < 8192) {
-        switch (linear_few_row_tiles(a.M, N)) {
-        case 1: MAMBA_FEW(1); break;
-        case 2: MAMBA_FEW(2); break;
-        default: MAMBA_FEW_K(4, 32); break;
-        }
-        return hipGetLastError();
+    // Few output tiles (linear_few_kernel).  Eight columns while that makes one round of workgroups on 256 CUs, 16 while 16 rows
+    // each make little more, 32 rows beyond; the tile kernels take over where those come to more than about four to a CU (three
+    // on a short k).  us on 16 x 8 / 16 x 16 / 32 x 16 / the best tile kernel:
+    //    12 x  768, K = 1536  3.1 / 3.3 / 3.7 / 10.3       333 x   80, K = 1536   3.3 /  3.5 /  4.1 / 11.4
+    //   128 x  768, K = 1536  4.8 / 4.3 / 4.0 / 10.9      1000 x   80, K = 1536   4.7 /  4.4 /  4.2 / 11.5
+    //   700 x  768, K = 1536    - / 10.5 / 10.0 / 11.0    1000 x  768, K = 1536     - / 13.5 / 12.1 / 11.8
+    //   128 x 3072, K =  768    - / 5.3 / 4.8 / 7.0        256 x 3072, K =  768     - /  8.1 /  8.1 /  7.1
+    //   256 x 2048, K =  512    - / 5.1 / 4.7 / 5.8        512 x 2048, K =  512     - /  7.9 /  7.1 /  6.0
+    //   512 x 1024, K = 2048    - / 13.7 / 12.1 / 13.3     700 x 1024, K = 2048     - / 17.6 / 16.4 / 13.4
+    //   256 x 1536, K =   48    - / 3.1 / 2.9 / 3.1        333 x 1536, K =   48     - /  3.4 /  3.6 /  3.1
+    // (A last row tile that is half empty and opens a third round of two to a CU: 333 x 768, K = 1536 6.3 with 16 rows, 6.7 with 32.)
+    if (linear_few_fits(N, a.K)) {
+        const int64_t t16 = tiles(16, 16), t32 = tiles(32, 16);
+        if (tiles(16, 8) <= kTilesResident) MAMBA_FEW(1, 1);
+        if (t16 <= kTilesResident * 9 / 8 || (t32 > 2 * kTilesResident && 2 * t32 > t16 && t16 <= 4 * kTilesResident)) MAMBA_FEW(1, 2);
+        if (t32 <= kTilesResident * (a.K >= 256 ? 9 : 6) / 2) MAMBA_FEW(2, 2);
     }
 #undef MAMBA_FEW
-#undef MAMBA_FEW_K
     const bool wide = vec && N % 128 == 0 && a.M >= 128 && a.K % (2 * kWideBK) == 0;
     auto grid = [&](int bm, int bn) { return dim3((unsigned)((N + bn - 1) / bn), (unsigned)((a.M + bm - 1) / bm)); };
     auto in_turn = [&](int64_t t) { return (unsigned)(8 * ((t + 7) / 8)); };

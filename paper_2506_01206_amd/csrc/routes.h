@@ -30,11 +30,11 @@ inline bool linear_few_fits(int64_t N, int64_t K)
     return K <= (int64_t)INT32_MAX - 63 && N <= ((int64_t)1 << 27) - 16;
 }
 
-// Row tiles of 16 (1, 2 or 4) per workgroup of that product for M <= 64 rows, 16 columns each: as few as make one round of
-// workgroups on 256 CUs, and no more than there are rows for, since tiles past the last row cost what the others do.  A
-// whole draft position with 1, 2, 4 tiles in in_proj: 3 rows of a 5120-channel model (640 column blocks) 43.8, 49.2, 61.2 us,
-// of a 3072-channel one 19.7, 23.9, 28.6; 24 rows 66.1, 68.2, 79.2 and 28.7, 30.3, 34.6; 48 rows of a 1536-channel one 19.0,
-// 21.0, 21.5, of a 512-channel one 12.0, 12.9, 14.6.
+// Row tiles of 16 (1, 2 or 4) per workgroup of the way into a block at a draft position (draft_in.hip), M <= 64 rows, 16 columns
+// each: as few as make one round of workgroups on 256 CUs, and no more than there are rows for, since tiles past the last row
+// cost what the others do.  A whole draft position with 1, 2, 4 tiles: 3 rows of a 5120-channel model (640 column blocks) 43.8,
+// 49.2, 61.2 us, of a 3072-channel one 19.7, 23.9, 28.6; 24 rows 66.1, 68.2, 79.2 and 28.7, 30.3, 34.6; 48 rows of a
+// 1536-channel one 19.0, 21.0, 21.5, of a 512-channel one 12.0, 12.9, 14.6 (measured on the kernel before it, which lay the same way).
 inline int linear_few_row_tiles(int64_t M, int64_t N)
 {
     const int64_t columns = (N + 15) / 16;

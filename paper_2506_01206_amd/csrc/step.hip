@@ -457,6 +457,7 @@ state_step_xproj_kernel(const float *__restrict__ xpart, int n_parts, int sides_
 #pragma unroll
     for (int i = 0; i < U; ++i) h[i] = ld_stream(reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(hin4) + 16 * f[i]));
     __builtin_amdgcn_sched_barrier(0);                            // all of it in flight before any of it is used
+    args_here(h_out, out);
 
     {
         float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);

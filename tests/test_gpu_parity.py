@@ -1221,6 +1221,15 @@ def test_linear_few_tiles(m, M, N, K, splits):
     test_linear_against_oracle(m, M, N, K, splits)
 
 
+@pytest.mark.parametrize("K", [8, 64, 72, 256, 264, 512, 768, 1024, 1096, 1536, 2048, 3080])
+@pytest.mark.parametrize("M,N,splits", [(1, 8, None), (15, 100, (48, 12, 40)), (17, 2041, None), (100, 1500, (700, 800)), (33, 8200, None),
+                                        (500, 1000, None)])
+def test_linear_few_every_split_of_k(m, M, N, K, splits):
+    """Every way the wavefronts of the kernel for few output tiles share k (one trip, several, remainders of a step), on 8 and 16
+    columns and on 32 rows."""
+    test_linear_against_oracle(m, M, N, K, splits)
+
+
 def test_linear_k_beyond_32_bits(m):
     """k that rounds up past 2^31 and k beyond it, on one output tile: the product of two sparse rows, whole numbers, so exact."""
     longest = (1 << 31) + 8
