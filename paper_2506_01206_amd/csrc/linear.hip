@@ -477,7 +477,9 @@ __device__ __forceinline__ void wave_sync()
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
 // EVEN: K = 64 NW G, one trip of every wavefront; otherwise any K that is a multiple of 8.
-template <int MT, int CG, int NW, int G, bool EVEN>
+// STREAM: w is read once and is large (the LM head on a draft position): its loads are streaming, so that they do not push the
+// blocks' weights, which the next position reads again, out of the last-level cache.
+template <int MT, int CG, int NW, int G, bool EVEN, bool STREAM>
 __global__ void __launch_bounds__(64 * NW)
 linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, const float *__restrict__ bias,
                   const bf16_t *residual, int M, int N, int K, OutSplit out)
@@ -546,7 +548,10 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
             const unsigned back = EVEN || 8u * (unsigned)s + lch < kchunks ? 0u : 16 * lch;   // chunks past K re-read the step's first one
             const char *ws = wb + (int64_t)s * 128, *xs = xb + (int64_t)s * 128;
 #pragma unroll
-            for (int t = 0; t < CG; ++t) wf[g][t] = *reinterpret_cast<const u32x4 *>(EVEN ? ws + wo[t] : ws + (wfar[t] - back));
+            for (int t = 0; t < CG; ++t) {
+                const u32x4 *p = reinterpret_cast<const u32x4 *>(EVEN ? ws + wo[t] : ws + (wfar[t] - back));
+                wf[g][t] = STREAM ? __builtin_nontemporal_load(p) : *p;
+            }
 #pragma unroll
             for (int t = 0; t < 2 * MT; ++t) xf[g][t] = *reinterpret_cast<const u32x4 *>(EVEN ? xs + xo[t] : xs + (xfar[t] - back));
         }
@@ -612,12 +617,12 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
     }
 }
 
-template <int MT, int CG>
+template <int MT, int CG, bool STREAM = false>
 hipError_t launch_few(const bf16_t *x, const bf16_t *w, const float *bias, const bf16_t *res, const OutSplit &o, int64_t M, int64_t N, int64_t K,
                       hipStream_t stream)
 {
     const dim3 grid((unsigned)((N + 8 * CG - 1) / (8 * CG)), (unsigned)((M + 16 * MT - 1) / (16 * MT)));
-#define MAMBA_FEW(NW, G, EVEN) linear_few_kernel<MT, CG, NW, G, EVEN><<<grid, 64 * NW, 0, stream>>>(x, w, bias, res, (int)M, (int)N, (int)K, o)
+#define MAMBA_FEW(NW, G, EVEN) linear_few_kernel<MT, CG, NW, G, EVEN, STREAM><<<grid, 64 * NW, 0, stream>>>(x, w, bias, res, (int)M, (int)N, (int)K, o)
     const int64_t per = (K + 511) / 512;
     if (K == 256) MAMBA_FEW(4, 1, true);
     else if (K < 256) MAMBA_FEW(4, 1, false);
@@ -645,7 +650,7 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     const bf16_t *x = static_cast<const bf16_t *>(a.x), *w = static_cast<const bf16_t *>(a.w);
     const bf16_t *res = static_cast<const bf16_t *>(a.residual);
     auto tiles = [&](int64_t bm, int64_t bn) { return ((N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
-#define MAMBA_FEW(MT, CG) return launch_few<MT, CG>(x, w, a.bias, res, o, a.M, N, a.K, stream)
+#define MAMBA_FEW(...) return launch_few<__VA_ARGS__>(x, w, a.bias, res, o, a.M, N, a.K, stream)
     if (a.norm_w) return launch_draft_in(a, stream);
     // Few output tiles (linear_few_kernel).  Eight columns while that makes one round of workgroups on 256 CUs, 16 while 16 rows
     // each make little more, 32 rows beyond; the tile kernels take over where those come to more than about four to a CU (three
@@ -657,9 +662,13 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     //   256 x 2048, K =  512    - / 5.1 / 4.7 / 5.8        512 x 2048, K =  512     - /  7.9 /  7.1 /  6.0
     //   512 x 1024, K = 2048    - / 13.7 / 12.1 / 13.3     700 x 1024, K = 2048     - / 17.6 / 16.4 / 13.4
     //   256 x 1536, K =   48    - / 3.1 / 2.9 / 3.1        333 x 1536, K =   48     - /  3.4 /  3.6 /  3.1
+    // Up to 16 rows against very many columns (the LM head on a draft position): 16 columns each, any number of rounds, up to a k of
+    // four trips; us on that / 64 x 64 tiles: 1 x 50280, K = 768 13.3 / 15.7, 12 x 50280 15.1 / 17.0, 12 x 16384 6.7 / 10.0, 12 x 32768,
+    // K = 2048 25.0 / 30.4 (12 x 50280, K = 2560 54.3 / 51.5; 32 x 50280, K = 768 on 32 rows 22.6 / 18.3).
     // (A last row tile that is half empty and opens a third round of two to a CU: 333 x 768, K = 1536 6.3 with 16 rows, 6.7 with 32.)
     if (linear_few_fits(N, a.K)) {
         const int64_t t16 = tiles(16, 16), t32 = tiles(32, 16);
+        if (a.M <= 16 && N >= 8192 && a.K <= 2048) MAMBA_FEW(1, 2, true);
         if (tiles(16, 8) <= kTilesResident) MAMBA_FEW(1, 1);
         if (t16 <= kTilesResident * 9 / 8 || (t32 > 2 * kTilesResident && 2 * t32 > t16 && t16 <= 4 * kTilesResident)) MAMBA_FEW(1, 2);
         if (t32 <= kTilesResident * (a.K >= 256 ? 9 : 6) / 2) MAMBA_FEW(2, 2);
