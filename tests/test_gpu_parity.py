@@ -1537,6 +1537,23 @@ def test_topk_is_exact(m, M, V, k):
         assert to_host(i2)[0, 0] == 2 and 1 not in to_host(i2)[0]
 
 
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 8])
+@pytest.mark.parametrize("V", [1, 7, 9, 8193, 65535, 65544, 73737])
+def test_topk_with_nans_of_both_signs(m, V, k):
+    """Rows that start at every alignment, of one turn of vectors and a little more, with NaNs (quiet and signalling, both
+    signs) among few distinct values: NaN ranks as -inf, ties go to the lower index."""
+    M = 3
+    rng = np.random.default_rng(V + k)
+    bits = synth.to_io(rng.integers(-3, 3, (M, V)).astype(np.float32), synth.BF16)
+    for j, nan in enumerate((0x7fc0, 0xffc0, 0x7f81, 0xff81, 0xff80, 0x7f80)):
+        bits[rng.integers(0, M, V // 20 + (j < 2)), rng.integers(0, V, V // 20 + (j < 2))] = nan
+    vals = values(bits).astype(np.float64)
+    ri, rv = oracle.topk(np.where(np.isnan(vals), -np.inf, vals), k)
+    idx, val = m.mamba_topk_fwd(to_dev(bits), k)
+    assert np.array_equal(to_host(idx), ri)
+    assert np.array_equal(to_host(val).astype(np.float64), rv)
+
+
 def test_embedding_is_a_gather(m):
     rng = np.random.default_rng(3)
     V, dm = 1000, 768
