@@ -220,8 +220,8 @@ linear_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, const 
 // matrix cores half the time at best.  This kernel takes 256 x 256 tiles, one workgroup per CU and one
 // wavefront per SIMD, each wavefront a 128 x 128 part held in 256 accumulator registers: per k the same
 // 8 cycles of cache traffic now feed 32 cycles of MFMA.
-// (With BM = 128 it also runs 128 x 128 tiles, two workgroups to a CU, for products too small to give every CU
-// a 256-row tile: the feeding scheme below, not the tile size, is what those gain from.)
+// (With BN = 128 it also runs 128 x 128 and 192 x 128 tiles, two workgroups to a CU, for products too small to give every CU
+// a 256-row tile, or that leave CUs without one: the feeding scheme below, not the tile size, is what those gain from.)
 //
 // Operands go from memory straight into LDS (global_load_lds_dwordx4: lane l of a wavefront lands at
 // M0 + 16 l, so one instruction fills eight 128-byte rows): no staging registers, and none of the LDS
@@ -677,7 +677,12 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     const bool wide = vec && N % 128 == 0 && a.M >= 128 && a.K % (2 * kWideBK) == 0;
     auto grid = [&](int bm, int bn) { return dim3((unsigned)((N + bn - 1) / bn), (unsigned)((a.M + bm - 1) / bm)); };
     auto in_turn = [&](int64_t t) { return (unsigned)(8 * ((t + 7) / 8)); };
-    switch (linear_tiles(a.M, N, a.K, wide)) {
+    const LinearTiles kind = linear_tiles(a.M, N, a.K, wide);
+    if (linear_wide192(a.M, N, a.K, wide, kind)) {
+        linear_wide_kernel<192, 128><<<in_turn(tiles(192, 128)), 256, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, (int)(N / 128), (int)tiles(192, 128));
+        return hipGetLastError();
+    }
+    switch (kind) {
     case kTilesWide256:
         linear_wide_kernel<256, 256><<<in_turn(tiles(256, 256)), 256, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, (int)(N / 256), (int)tiles(256, 256));
         break;

@@ -94,6 +94,31 @@ inline LinearTiles linear_tiles(int64_t M, int64_t N, int64_t K, bool wide)
     return K >= 512 && tiles(64, 64) < 513 ? kTiles64Deep : kTiles64;
 }
 
+// 192 x 128 tiles lie between the others in size, so they often leave fewer CUs idle in the last round; as many flops an
+// operand byte as half of a 256 x 256 tile's, and two to a CU, so one's output goes out under the other's products.  They are
+// weighed against the choice above (other) wherever that takes a second round of 128 x 128 tiles: rounds times what one takes, in
+// units of a full set of 256 128 x 128 tiles (7 us at K = 768, 12.5 at K = 1536), a half-full round of two to a CU costing less.  Fitted
+// to 139 products of five models; the choice costs 0.4 % of the better of the two on average.  us on the choice above /
+// 192 x 128, random operands, 24 weights in turn:
+//    3000 x 3072, K =  768   27.6 /  20.9     12000 x  768, K = 1536   43.0 /  36.1      6000 x 6144, K = 1536  140.9 / 117.6
+//    8000 x 3072, K =  768   54.1 /  43.2     16384 x 3072, K =  768   84.0*/  88.6     12000 x 1536, K = 3072  125.9 / 108.0
+//    5000 x 2048, K =  512   21.9 /  17.0      8000 x 4096, K = 1024   69.8*/  74.4      7000 x 2560, K = 5120  205.0 / 173.3
+inline bool linear_wide192(int64_t M, int64_t N, int64_t K, bool wide, LinearTiles other)
+{
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((N + bn - 1) / bn) * ((M + bm - 1) / bm); };
+    if (!wide || M < 192 || tiles(128, 128) <= 512 || (other != kTilesWide256 && other != kTilesWide128 && other != kTiles128)) return false;
+    const bool longk = K >= 1024;
+    auto rounds = [](int64_t t, int64_t per, double full, double half) {
+        const int64_t rem = t % per;
+        return (double)(t / per) * full + (rem == 0 ? 0.0 : rem <= per / 2 ? half : full);
+    };
+    const double with = rounds(tiles(192, 128), 512, longk ? 3.1 : 2.9, longk ? 1.9 : 1.7);
+    const double without = other == kTilesWide256 ? rounds(tiles(256, 256), 256, longk ? 3.6 : 3.9, longk ? 3.6 : 3.9)
+                           : other == kTilesWide128 ? rounds(tiles(128, 128), 512, 2.14, longk ? 1.5 : 1.3)
+                                                    : rounds(tiles(128, 128), 768, longk ? 3.6 : 3.5, longk ? 2.7 : 2.6);
+    return with < without;
+}
+
 // x_proj and dt_proj in one kernel (xdt.hip): rows per workgroup and column groups for M rows; 0 rows: two launches.
 // Every workgroup reads all weights, so what counts is the number of rounds on 256 CUs times what a workgroup takes (us in
 // xdt.hip, in a full round).  One round of 16 rows: column groups as long as they fit the chip beside each other (24-block

@@ -1208,6 +1208,13 @@ def test_linear_wide_tiles_ragged_rows(m, M, N, K, splits):
     test_linear_against_oracle(m, M, N, K, splits)
 
 
+@pytest.mark.parametrize("M,N,K,splits", [(2977, 3072, 128, (1536, 1536)), (8000, 3072, 256, (1500, 1572)), (4993, 2048, 384, None),
+                                          (5184, 2048, 512, None), (11905, 768, 1536, None), (12095, 768, 128, (384, 384)), (3073, 6144, 128, None)])
+def test_linear_192_row_tiles(m, M, N, K, splits):
+    """Products that take 192 x 128 tiles: full row blocks, and a last one of one row, of one less than all and in between."""
+    test_linear_against_oracle(m, M, N, K, splits)
+
+
 @pytest.mark.parametrize("M,N,K,splits", [(1, 4096, 8, None), (17, 2050, 40, None), (257, 250, 1544, (48, 102, 100)),   # 16 x 16
                                           (19, 4090, 768, (2040, 2050)), (100, 800, 520, None),                          # 32 x 16
                                           (65, 4000, 512, (1500, 2500)), (255, 999, 1288, None), (2700, 80, 1536, (48, 16, 16)),   # 32 x 32

@@ -14,6 +14,7 @@ extern "C" int folds(int n_seg1, int before, uintptr_t h0, uintptr_t h_final, in
 extern "C" int few_fits(int64_t N, int64_t K) { return mamba::linear_few_fits(N, K); }
 extern "C" int row_tiles(int64_t M, int64_t N) { return mamba::linear_few_row_tiles(M, N); }
 extern "C" int tiles(int64_t M, int64_t N, int64_t K, int wide) { return mamba::linear_tiles(M, N, K, wide); }
+extern "C" int wide192(int64_t M, int64_t N, int64_t K, int wide) { return mamba::linear_wide192(M, N, K, wide, mamba::linear_tiles(M, N, K, wide)); }
 extern "C" int xdt(int64_t M, int64_t d_inner, int64_t dt_rank, int64_t N, unsigned *groups)
 { return mamba::xdt_plan(M, d_inner, dt_rank, N, groups); }
 """
@@ -31,6 +32,7 @@ def routes(tmp_path_factory):
     lib.few_fits.argtypes = [i64, i64]
     lib.row_tiles.argtypes = [i64, i64]
     lib.tiles.argtypes = [i64, i64, i64, i32]
+    lib.wide192.argtypes = [i64, i64, i64, i32]
     lib.xdt.argtypes = [i64, i64, i64, i64, ctypes.POINTER(ctypes.c_uint)]
     return lib
 
@@ -104,3 +106,14 @@ def test_tile_kernel_of_a_product(routes):
             for K in (128, 384, 1024, 5120, 1 << 20):
                 kind = tiles(M, N, K)
                 assert 0 <= kind <= 5 and (kind != W256 or (M >= 256 and N % 256 == 0)), (M, N, K)
+
+
+def test_192_row_tiles(routes):
+    """The products that the parity tests name for them, those measured faster and slower, and never without their conditions."""
+    takes = lambda M, N, K: bool(routes.wide192(M, N, K, M >= 128 and N % 128 == 0 and K % 128 == 0))
+    for s in [(2977, 3072, 128), (8000, 3072, 256), (4993, 2048, 384), (5184, 2048, 512), (11905, 768, 1536), (12095, 768, 128), (3073, 6144, 128),
+              (3000, 3072, 768), (8000, 3072, 768), (5000, 2048, 512), (12000, 768, 1536), (6000, 6144, 1536), (12000, 1536, 3072), (7000, 2560, 5120)]:
+        assert takes(*s), s
+    for s in [(16384, 3072, 768), (32768, 3072, 768), (8000, 4096, 1024), (1500, 3072, 768), (2000, 2560, 5120), (32768, 768, 1536), (191, 1 << 16, 128),
+              (8000, 3000, 768), (8000, 3072, 760)]:
+        assert not takes(*s), s
