@@ -468,12 +468,13 @@ __device__ __forceinline__ void wave_sync()
 // With a row's 64 bytes on the four lanes of a quad it takes 34, with 128 on eight lanes about half of that, so that is
 // how rows are loaded; a patch of LDS private to the wavefront turns them into fragments, and later holds its partial tiles.
 // A CU's share of that path is what a workgroup of 16 columns and 16 rows takes longest for (K = 1536: 96 such loads), so eight
-// columns where that does not make a second round of workgroups (their fragments' other half is never written nor used).
+// columns where that does not make a second round of workgroups (their fragments' other half is never written nor used), and
+// tiles of up to 32 columns and 64 rows, which ask for fewer bytes an output, where there are many.
 // The partial tiles of the wavefronts meet in LDS, one output per thread; what else an output needs (bias, residual) has been on
 // its way since before the main loop.
 // us in chains of 24 different weights, replayed (before: 64-byte pieces, the residual waited for where it was fetched, twice the
-// LDS; 32-column tiles for the larger ones): 12 x 768, K = 1536 3.10 (3.71), 64 x 768 3.4 (3.9), 128 x 3072, K = 768 4.8 (7.0), 333 x 768,
-// K = 1536 6.3 (8.5), 512 x 512, K = 1024 4.7 (5.9).
+// LDS; a kernel of its own for 32-column tiles): 12 x 768, K = 1536 3.10 (3.71), 64 x 768 3.4 (3.9), 128 x 3072, K = 768 5.0 (7.0), 333 x
+// 768, K = 1536 6.2 (8.5), 1000 x 768 9.0 (11.8), 512 x 512, K = 1024 3.9 (5.9).
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
 // EVEN: K = 64 NW G, one trip of every wavefront; otherwise any K that is a multiple of 8.
@@ -485,11 +486,12 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
                   const bf16_t *residual, int M, int N, int K, OutSplit out)
 {
     constexpr int kThr = NW * 64;
-    constexpr int kStep = (1 + MT) * 2048;                         // fragments of one step: w, then MT row tiles
+    constexpr int NT = (CG + 1) / 2;                               // column tiles of 16
+    constexpr int kStep = (NT + MT) * 2048;                        // fragments of one step: NT column tiles of w, then MT row tiles
     constexpr int PB = G * NW * kStep <= 32 * 1024 ? G : 1;        // patches in turn: several workgroups to a CU
-    constexpr int OPT = (MT * 256 + kThr - 1) / kThr;              // outputs per thread
+    constexpr int OPT = (MT * NT * 256 + kThr - 1) / kThr;         // outputs per thread
     // a wavefront's patches, and its partial tiles once it is done with those
-    constexpr int kWave = PB * kStep > MT * 1024 ? PB * kStep : MT * 1024;
+    constexpr int kWave = PB * kStep > MT * NT * 1024 ? PB * kStep : MT * NT * 1024;
     __shared__ __attribute__((aligned(16))) unsigned char patch[NW][kWave];
     const unsigned tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -497,19 +499,20 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
     const unsigned lrow = lane >> 3, lch = lane & 7;               // load view: row (+ 8 t), 16-byte chunk of the step
     const int n0 = blockIdx.x * (8 * CG), m0 = blockIdx.y * (16 * MT);
 
-    // ---- what the outputs of this thread need besides their sums (nothing is used where it is fetched): tile o / 256,
-    // accumulator (o / 64) % 4 of lane o % 64
-    const int on = n0 + (int)li;
-    const unsigned col_in = (unsigned)min(on, N - 1);
-    int om[OPT];
+    // ---- what the outputs of this thread need besides their sums (nothing is used where it is fetched): tile o / 256 (row tile
+    // by row tile), accumulator (o / 64) % 4 of lane o % 64
+    int om[OPT], on[OPT];
     uint16_t res[OPT];
-    // (unconditional requests: one under a condition is converted, and so waited for, inside its branch)
-    float bias_in = (bias ? bias : reinterpret_cast<const float *>(x))[bias ? col_in : 0u];
+    float bias_in[OPT];
 #pragma unroll
     for (int j = 0; j < OPT; ++j) {
-        const int o6 = wave + j * NW;
-        om[j] = m0 + (o6 >> 2) * 16 + (o6 & 3) + 4 * (int)lg;
-        res[j] = (residual ? residual : x)[residual ? (int64_t)min(om[j], M - 1) * N + col_in : 0];   // single output tensor
+        const int o6 = wave + j * NW, tile = o6 >> 2;
+        om[j] = m0 + tile / NT * 16 + (o6 & 3) + 4 * (int)lg;
+        on[j] = n0 + tile % NT * 16 + (int)li;
+        const unsigned col = (unsigned)min(on[j], N - 1);
+        // (unconditional requests: one under a condition is converted, and so waited for, inside its branch)
+        bias_in[j] = (bias ? bias : reinterpret_cast<const float *>(x))[bias ? col : 0u];
+        res[j] = (residual ? residual : x)[residual ? (int64_t)min(om[j], M - 1) * N + col : 0];   // single output tensor
     }
     __builtin_amdgcn_sched_barrier(0);
 
@@ -535,9 +538,11 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
     const unsigned put = (lrow * 8 + (lch ^ lrow)) * 16;           // + 1024 t: chunks xor-swizzled by the row, no bank conflicts either way
     const unsigned get0 = (li * 8 + (lg ^ (li & 7))) * 16, get1 = (li * 8 + ((lg + 4) ^ (li & 7))) * 16;
 
-    f32x4v acc[MT];
+    f32x4v acc[MT][NT];
 #pragma unroll
-    for (int t = 0; t < MT; ++t) acc[t] = f32x4v(0.0f);
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) acc[t][n] = f32x4v(0.0f);
     bool first = true;
     for (int s0 = s_first; EVEN ? first : s0 < s_end; s0 += G) {
         first = false;
@@ -563,17 +568,22 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
 #pragma unroll
             for (int t = 0; t < CG; ++t) *reinterpret_cast<u32x4 *>(p + 1024 * t + put) = ok ? wf[g][t] : u32x4(0u);
 #pragma unroll
-            for (int t = 0; t < 2 * MT; ++t) *reinterpret_cast<u32x4 *>(p + 2048 + 1024 * t + put) = ok ? xf[g][t] : u32x4(0u);
+            for (int t = 0; t < 2 * MT; ++t) *reinterpret_cast<u32x4 *>(p + 2048 * NT + 1024 * t + put) = ok ? xf[g][t] : u32x4(0u);
         };
         auto product = [&](int g) __attribute__((always_inline)) {
             const unsigned char *p = patch[wave] + g % PB * kStep;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const unsigned get = h ? get1 : get0;
-                const bf16x8 wv = *reinterpret_cast<const bf16x8 *>(p + get);
+                bf16x8 wv[NT];
 #pragma unroll
-                for (int t = 0; t < MT; ++t)
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8 *>(p + 2048 * (1 + t) + get), wv, acc[t], 0, 0, 0);
+                for (int n = 0; n < NT; ++n) wv[n] = *reinterpret_cast<const bf16x8 *>(p + 2048 * n + get);
+#pragma unroll
+                for (int t = 0; t < MT; ++t) {
+                    const bf16x8 xv = *reinterpret_cast<const bf16x8 *>(p + 2048 * (NT + t) + get);
+#pragma unroll
+                    for (int n = 0; n < NT; ++n) acc[t][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv, wv[n], acc[t][n], 0, 0, 0);
+                }
             }
         };
 #pragma unroll
@@ -590,28 +600,31 @@ linear_few_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, co
             wave_sync();
         }
     }
-    // acc[t][i] is C[m = 16 t + 4 (lane / 16) + i][n = lane % 16]
+    // acc[t][n][i] is C[m = 16 t + 4 (lane / 16) + i][16 n + lane % 16]
 #pragma unroll
     for (int t = 0; t < MT; ++t)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) reinterpret_cast<float *>(patch[wave])[(4 * t + i) * 64 + lane] = acc[t][i];
-    values_here(bias_in);
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) reinterpret_cast<float *>(patch[wave])[(4 * (t * NT + n) + i) * 64 + lane] = acc[t][n][i];
+#pragma unroll
+    for (int j = 0; j < OPT; ++j) values_here(bias_in[j]);
     lds_barrier_linear();
 
 #pragma unroll
     for (int j = 0; j < OPT; ++j) {
-        const int o6 = wave + j * NW, t = (o6 >> 2) < MT ? o6 >> 2 : 0, i = o6 & 3;
+        const int o6 = wave + j * NW, at = (o6 < 4 * MT * NT ? o6 : 0) * 64 + (int)lane;
         float v = 0.0f;
 #pragma unroll
-        for (int q = 0; q < NW; ++q) v += reinterpret_cast<const float *>(patch[q])[(4 * t + i) * 64 + lane];
-        if (o6 >= 4 * MT || om[j] >= M || on >= N || li >= 8 * CG) continue;
-        v = bf16_to_f32(f32_to_bf16(v + (bias ? bias_in : 0.0f)));   // same two roundings as the tiled kernel
+        for (int q = 0; q < NW; ++q) v += reinterpret_cast<const float *>(patch[q])[at];
+        if (o6 >= 4 * MT * NT || om[j] >= M || on[j] >= N || li >= 8 * CG) continue;
+        v = bf16_to_f32(f32_to_bf16(v + (bias ? bias_in[j] : 0.0f)));   // same two roundings as the tiled kernel
         if (residual) {
-            out.ptr[0][(int64_t)om[j] * N + on] = (bf16_t)f32_to_bf16(v + bf16_to_f32(res[j]));
+            out.ptr[0][(int64_t)om[j] * N + on[j]] = (bf16_t)f32_to_bf16(v + bf16_to_f32(res[j]));
             continue;
         }
         int64_t col;
-        const int sp = locate(out, on, &col);
+        const int sp = locate(out, on[j], &col);
         (sp == 0 ? out.ptr[0] : sp == 1 ? out.ptr[1] : out.ptr[2])[(int64_t)om[j] * (sp == 0 ? out.width[0] : sp == 1 ? out.width[1] : out.width[2]) + col] =
             (bf16_t)f32_to_bf16(v);
     }
@@ -632,7 +645,6 @@ hipError_t launch_few(const bf16_t *x, const bf16_t *w, const float *bias, const
     else if (K == 1536) MAMBA_FEW(8, 3, true);
     else if (per <= 2 || per == 4) MAMBA_FEW(8, 2, false);
     else MAMBA_FEW(8, 3, false);
-#undef MAMBA_FEW
     return hipGetLastError();
 }
 
@@ -652,26 +664,28 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     auto tiles = [&](int64_t bm, int64_t bn) { return ((N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
 #define MAMBA_FEW(...) return launch_few<__VA_ARGS__>(x, w, a.bias, res, o, a.M, N, a.K, stream)
     if (a.norm_w) return launch_draft_in(a, stream);
-    // Few output tiles (linear_few_kernel).  Eight columns while that makes one round of workgroups on 256 CUs, 16 while 16 rows
-    // each make little more, 32 rows beyond; the tile kernels take over where those come to more than about four to a CU (three
-    // on a short k).  us on 16 x 8 / 16 x 16 / 32 x 16 / the best tile kernel:
-    //    12 x  768, K = 1536  3.1 / 3.3 / 3.7 / 10.3       333 x   80, K = 1536   3.3 /  3.5 /  4.1 / 11.4
-    //   128 x  768, K = 1536  4.8 / 4.3 / 4.0 / 10.9      1000 x   80, K = 1536   4.7 /  4.4 /  4.2 / 11.5
-    //   700 x  768, K = 1536    - / 10.5 / 10.0 / 11.0    1000 x  768, K = 1536     - / 13.5 / 12.1 / 11.8
-    //   128 x 3072, K =  768    - / 5.3 / 4.8 / 7.0        256 x 3072, K =  768     - /  8.1 /  8.1 /  7.1
-    //   256 x 2048, K =  512    - / 5.1 / 4.7 / 5.8        512 x 2048, K =  512     - /  7.9 /  7.1 /  6.0
-    //   512 x 1024, K = 2048    - / 13.7 / 12.1 / 13.3     700 x 1024, K = 2048     - / 17.6 / 16.4 / 13.4
-    //   256 x 1536, K =   48    - / 3.1 / 2.9 / 3.1        333 x 1536, K =   48     - /  3.4 /  3.6 /  3.1
+    // Few output tiles (linear_few_kernel): the tile that makes one round of workgroups on 256 CUs, from 16 rows x 8 columns up; the
+    // tile kernels take over where 32 x 32 comes to more than two or three to a CU.  us on 16 x 8 / 16 x 16 / 32 x 16 / 32 x 32 / 64 x 32 /
+    // the best tile kernel:
+    //    12 x  768, K = 1536  3.1 / 3.3 / 3.7 /   -  /   -  / 10.3      333 x   80, K = 1536  3.3 / 3.6 /  4.1 /  4.9 /   -  / 11.4
+    //   128 x  768, K = 1536  4.8 / 4.3 / 4.1 /  4.6 /  6.4 / 10.9      333 x  768, K = 1536   -  / 6.3 /  6.8 /  6.2 /  6.5 / 10.9
+    //   700 x  768, K = 1536   -  / 10.6/ 10.1/  8.4 / 11.5 / 11.0     1000 x  768, K = 1536   -  / 13.7/ 12.1 /  9.0 / 12.0 / 11.8
+    //   128 x 3072, K =  768   -  / 5.3 / 5.0 /  5.1 /  5.6 /  7.0      256 x 3072, K =  768   -  / 8.2 /  8.2 /  7.7 /  9.5 /  7.1
+    //   256 x 2048, K =  512   -  / 5.1 / 4.6 /  4.2 /  4.4 /  5.8      512 x 2048, K =  512   -  / 8.0 /  7.1 /  6.5 /  7.3 /  6.0
+    //   512 x  512, K = 1024   -  / 5.2 / 4.7 /  3.9 /  5.1 /  8.4      700 x 1024, K = 2048   -  / 18.3/ 16.5 / 12.1 / 15.0 / 13.3
+    //   256 x 1536, K = 3072   -  / 15.3/ 12.7/ 12.9 / 10.3 / 18.1      256 x 2048, K = 4096   -  / 29.2/ 24.2 / 21.4 / 18.0 / 28.3
+    //   200 x 2560, K = 5120   -  / 40.9/ 37.3/ 37.4 / 36.4 / 34.9      256 x 1536, K =   48   -  / 3.1 /  2.9 /   -  /   -  /  3.1
     // Up to 16 rows against very many columns (the LM head on a draft position): 16 columns each, any number of rounds, up to a k of
     // four trips; us on that / 64 x 64 tiles: 1 x 50280, K = 768 13.3 / 15.7, 12 x 50280 15.1 / 17.0, 12 x 16384 6.7 / 10.0, 12 x 32768,
     // K = 2048 25.0 / 30.4 (12 x 50280, K = 2560 54.3 / 51.5; 32 x 50280, K = 768 on 32 rows 22.6 / 18.3).
-    // (A last row tile that is half empty and opens a third round of two to a CU: 333 x 768, K = 1536 6.3 with 16 rows, 6.7 with 32.)
     if (linear_few_fits(N, a.K)) {
-        const int64_t t16 = tiles(16, 16), t32 = tiles(32, 16);
+        const int64_t round = kTilesResident, t32 = tiles(32, 32), most = a.K > 3072 ? 512 : a.K > 512 && a.K < 1024 ? 608 : 768;
         if (a.M <= 16 && N >= 8192 && a.K <= 2048) MAMBA_FEW(1, 2, true);
-        if (tiles(16, 8) <= kTilesResident) MAMBA_FEW(1, 1);
-        if (t16 <= kTilesResident * 9 / 8 || (t32 > 2 * kTilesResident && 2 * t32 > t16 && t16 <= 4 * kTilesResident)) MAMBA_FEW(1, 2);
-        if (t32 <= kTilesResident * (a.K >= 256 ? 9 : 6) / 2) MAMBA_FEW(2, 2);
+        if (tiles(16, 8) <= round) MAMBA_FEW(1, 1);
+        if (tiles(16, 16) <= round * 9 / 8 || (a.M <= 16 && N < 8192)) MAMBA_FEW(1, 2);
+        if (tiles(32, 16) <= (a.K < 256 ? 3 * round : round)) MAMBA_FEW(2, 2);
+        if (a.K >= 2048 && a.M > 64 && t32 > round && tiles(64, 32) <= round) MAMBA_FEW(4, 4);
+        if (a.K >= 256 && t32 <= most) MAMBA_FEW(2, 4);
     }
 #undef MAMBA_FEW
     const bool wide = vec && N % 128 == 0 && a.M >= 128 && a.K % (2 * kWideBK) == 0;

@@ -1230,10 +1230,10 @@ def test_linear_few_tiles(m, M, N, K, splits):
 
 @pytest.mark.parametrize("K", [8, 64, 72, 256, 264, 512, 768, 1024, 1096, 1536, 2048, 3080])
 @pytest.mark.parametrize("M,N,splits", [(1, 8, None), (15, 100, (48, 12, 40)), (17, 2041, None), (100, 1500, (700, 800)), (33, 8200, None),
-                                        (500, 1000, None)])
+                                        (500, 1000, None), (129, 1999, (999, 1000))])
 def test_linear_few_every_split_of_k(m, M, N, K, splits):
     """Every way the wavefronts of the kernel for few output tiles share k (one trip, several, remainders of a step), on 8 and 16
-    columns and on 32 rows."""
+    columns and on 32 rows, on 32 x 32 tiles and, with a k of 2048 and more, on 64 x 32."""
     test_linear_against_oracle(m, M, N, K, splits)
 
 
