@@ -13,9 +13,11 @@
 // tokens this beats the two-pass kernels' launches and hand-overs, on long sequences their full-line accesses
 // win; scan_lanes_applies draws the line.)
 //
-// A workgroup owns 6 adjacent channels (256 workgroups for 1536 channels) and walks the sequence in
-// super-steps of 512 tokens.  Its 12 wavefronts are (channel pair, group of 4 states); the 64 lanes of a
-// wavefront are 64 consecutive blocks of 8 tokens.  Per super-step a lane
+// A workgroup owns 6 adjacent channels (256 workgroups for 1536 channels; 4 or 2 of a narrower layer, so that it still has as
+// many: 1 x 1000 x 768 15.2 -> 12.4 us, 1 x 1000 x 512 15.7 -> 10.4) and walks the sequence in
+// super-steps of 512 tokens.  Its 12 (8, 4) wavefronts are (channel pair, group of 4 states); the 64 lanes of a
+// wavefront are 64 consecutive blocks of 8 tokens (4 where the whole sequence is 256 tokens or shorter, 256 x 1536 9.3 -> 7.4 us, and
+// with 2 channels, which 8 tokens would leave without a thread for each).  Per super-step a lane
 //   1. integrates its 8 tokens from a zero state (lane 0 from the true state that enters the super-step),
 //      keeping the 8 x 8 decay factors a = exp(delta A) in registers: mul, exp2, mul, fma per update;
 //   2. forms the decay over its whole block, P = exp(A * sum of its deltas);
@@ -38,14 +40,8 @@
 namespace mamba {
 namespace {
 
-constexpr int kG = 6;                    // channels per workgroup
 constexpr int kN = 16;                   // states per channel
 constexpr int kParts = 4;                // groups of 4 states
-constexpr int kWaves = (kG / 2) * kParts;
-constexpr int kThreadsL = 64 * kWaves;   // 768
-constexpr int kTau = 8;                  // tokens per lane and super-step
-constexpr int kT = 64 * kTau;            // tokens per super-step
-constexpr int kTokenThreads = kT;        // one token row per thread of the first 8 wavefronts
 constexpr int kBcPart = 66, kBcTau = kParts * kBcPart + 1;   // slots per state group and per token j of lds_B / lds_C
 
 __device__ __forceinline__ void lds_barrier_l()
@@ -102,58 +98,64 @@ __device__ __forceinline__ float wave_rotate1(float v)
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x13C, 0xf, 0xf, false));
 }
 
-// six adjacent channels of one token row, as they lie in memory
-template <typename T> struct Row6;
-template <> struct Row6<bf16_t> {
-    uint32_t v[3];
+// G adjacent channels of one token row, as they lie in memory
+template <typename T, int G> struct RowG;
+template <int G> struct RowG<bf16_t, G> {
+    uint32_t v[G / 2];
     __device__ __forceinline__ void load(const bf16_t *p)
     {
-        const uint32_t *q = reinterpret_cast<const uint32_t *>(p);
-        v[0] = q[0]; v[1] = q[1]; v[2] = q[2];
+#pragma unroll
+        for (int c = 0; c < G / 2; ++c) v[c] = reinterpret_cast<const uint32_t *>(p)[c];
     }
     __device__ __forceinline__ void unpack(float *f) const
     {
-        f[0] = bf16_lo(v[0]); f[1] = bf16_hi(v[0]); f[2] = bf16_lo(v[1]); f[3] = bf16_hi(v[1]);
-        f[4] = bf16_lo(v[2]); f[5] = bf16_hi(v[2]);
+#pragma unroll
+        for (int c = 0; c < G / 2; ++c) f[2 * c] = bf16_lo(v[c]), f[2 * c + 1] = bf16_hi(v[c]);
     }
 };
-template <> struct Row6<float> {
-    float2 v[3];
+template <int G> struct RowG<float, G> {
+    float2 v[G / 2];
     __device__ __forceinline__ void load(const float *p)
     {
-        const float2 *q = reinterpret_cast<const float2 *>(p);
-        v[0] = q[0]; v[1] = q[1]; v[2] = q[2];
+#pragma unroll
+        for (int c = 0; c < G / 2; ++c) v[c] = reinterpret_cast<const float2 *>(p)[c];
     }
     __device__ __forceinline__ void unpack(float *f) const
     {
-        f[0] = v[0].x; f[1] = v[0].y; f[2] = v[1].x; f[3] = v[1].y; f[4] = v[2].x; f[5] = v[2].y;
+#pragma unroll
+        for (int c = 0; c < G / 2; ++c) f[2 * c] = v[c].x, f[2 * c + 1] = v[c].y;
     }
 };
-// six adjacent channels of one output row, rounded to the type they are stored as
-template <typename T> struct Out6;
-template <> struct Out6<bf16_t> {
-    typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
-    typedef u32x3 u32x3_at4 __attribute__((aligned(4)));
-    uint32_t v[3];
+// G adjacent channels of one output row, rounded to the type they are stored as
+template <typename T, int G> struct OutG;
+template <int G> struct OutG<bf16_t, G> {
+    typedef uint32_t words __attribute__((ext_vector_type(G / 2)));
+    typedef words words_at4 __attribute__((aligned(4)));
+    uint32_t v[G / 2];
     __device__ __forceinline__ void pack(const float *f)
     {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) v[c] = f32x2_to_bf16x2(f[2 * c], f[2 * c + 1]);
+        for (int c = 0; c < G / 2; ++c) v[c] = f32x2_to_bf16x2(f[2 * c], f[2 * c + 1]);
     }
-    __device__ __forceinline__ void store(bf16_t *p) const { *reinterpret_cast<u32x3_at4 *>(p) = u32x3{v[0], v[1], v[2]}; }
+    __device__ __forceinline__ void store(bf16_t *p) const
+    {
+        if constexpr (G == 6) *reinterpret_cast<words_at4 *>(p) = words{v[0], v[1], v[2]};
+        else if constexpr (G == 4) *reinterpret_cast<words_at4 *>(p) = words{v[0], v[1]};
+        else *reinterpret_cast<uint32_t *>(p) = v[0];
+    }
     __device__ __forceinline__ void store_pair(bf16_t *p, int c) const { reinterpret_cast<uint32_t *>(p)[c] = v[c]; }
 };
-template <> struct Out6<float> {
-    float2 v[3];
+template <int G> struct OutG<float, G> {
+    float2 v[G / 2];
     __device__ __forceinline__ void pack(const float *f)
     {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) v[c] = make_float2(f[2 * c], f[2 * c + 1]);
+        for (int c = 0; c < G / 2; ++c) v[c] = make_float2(f[2 * c], f[2 * c + 1]);
     }
     __device__ __forceinline__ void store(float *p) const
     {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) reinterpret_cast<float2 *>(p)[c] = v[c];
+        for (int c = 0; c < G / 2; ++c) reinterpret_cast<float2 *>(p)[c] = v[c];
     }
     __device__ __forceinline__ void store_pair(float *p, int c) const { reinterpret_cast<float2 *>(p)[c] = v[c]; }
 };
@@ -178,13 +180,18 @@ template <> struct BcChunk<float> {      // 4 values: one group
     __device__ __forceinline__ float4 group(int) const { return v; }
 };
 
-// grid: (ceil(D / 6) rounded up to a multiple of 8, batch); block: 768.  N = 16, D even and >= 6.
-template <typename T, bool HAS_Z, bool SOFTPLUS>
-__global__ void __launch_bounds__(kThreadsL)
+// kG: channels per workgroup (2, 4 or 6); kTau: tokens per lane and super-step (4 or 8), 64 kTau tokens no more than threads.
+// grid: (ceil(D / kG) rounded up to a multiple of 8, batch); block: 128 kG.  N = 16, D even and >= kG.
+template <typename T, bool HAS_Z, bool SOFTPLUS, int kG, int kTau>
+__global__ void __launch_bounds__(64 * kParts * (kG / 2))
 scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T *Bm, const T *Cm,
                   const float *__restrict__ Dskip, const T *z, const float *__restrict__ dt_bias,
                   const float *h0 /* may alias h_final */, T *out, float *h_final, int64_t L, int64_t D)
 {
+    constexpr int kThreadsL = 64 * kParts * (kG / 2);
+    constexpr int kT = 64 * kTau;            // tokens per super-step
+    constexpr int kTokenThreads = kT;        // one token row per thread of the first wavefronts
+    static_assert(kTokenThreads <= kThreadsL, "a token row per thread");
     // [token j of the lane's block][state group][lane][4 states]: the lanes of a wavefront read consecutive slots.
     // The threads that fill them write, eight lanes at a time, four consecutive tokens (j) x two state groups two
     // apart: with rows of 66 slots and 265 slots per j those eight 16-byte slots fall on eight different quarters
@@ -223,7 +230,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
     // tj of the block of lane ti.  (A wavefront's 4-byte accesses to the [..][lane][4 tokens] arrays then cover all
     // banks: 8 lanes x 4 positions.)
     const bool token_thread = tid < kTokenThreads;
-    const int tj = tid & (kTau - 1), ti = (tid >> 3) & 63;
+    const int tj = tid & (kTau - 1), ti = (tid / kTau) & 63;
     // dt_bias and D of the workgroup's channels: one load per thread, requested here and put into LDS only after the
     // first rows have been requested as well (written where it is fetched, wavefront 0 would sit through two
     // memory round trips before it asks for anything else, and the whole workgroup waits for it at the barrier)
@@ -250,12 +257,12 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
     // With 2-byte elements everything a super-step needs is requested during the one before; with float32 (twice
     // the registers) only x and dt are, and z, B_t, C_t are fetched where they are used.
     constexpr bool kAhead = sizeof(T) == 2;
-    Row6<T> x_cur, z_cur;                                            // the super-step's own: kept for the gate
+    RowG<T, kG> x_cur, z_cur;                                            // the super-step's own: kept for the gate
     constexpr int kChunkGroups = BcChunk<T>::kGroups;
     constexpr int kChunksPerRow = kParts / kChunkGroups;             // 2 (bf16) or 4 (float32)
     constexpr int kChunks = 2 * kT * kChunksPerRow;                  // B and C of a super-step
-    constexpr int kBcIters = (kChunks + kThreadsL - 1) / kThreadsL;  // 3 or 6
-    constexpr int kBcHeld = 3;                                       // chunks a thread holds at a time
+    constexpr int kBcIters = (kChunks + kThreadsL - 1) / kThreadsL;  // 2 to 8
+    constexpr int kBcHeld = kAhead ? kBcIters : (kBcIters + 1) / 2;  // chunks a thread holds at a time
     BcChunk<T> bc_nxt[kBcHeld];
 
     // Addresses are a base of the super-step, which is uniform (scalar registers), and 32 bits of the thread's own (512 rows
@@ -263,7 +270,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
     // every tensor the walk had to spill, and a kernel with scratch memory takes 0.4 us longer to start.
     // The last token of a super-step, counted from its start; tokens past it re-read its row and are zeroed at use.
     auto last_of = [&](int64_t t_base) { return (int)(L - 1 - t_base < kT - 1 ? L - 1 - t_base : kT - 1); };
-    // chunk q of a super-step: (array, token, position in the row); `first`: 0, or 3 for the second half of float32
+    // chunk q of a super-step: (array, token, position in the row); `first`: 0, or kBcHeld for the second half of float32
     auto fetch_bc = [&](int64_t t_base, int first) {
 #pragma unroll
         for (int it = 0; it < kBcHeld; ++it) {
@@ -289,14 +296,14 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
             }
         }
     };
-    auto fetch = [&](int64_t t_base, Row6<T> &xr, Row6<T> &dtr, Row6<T> &zr) {
+    auto fetch = [&](int64_t t_base, RowG<T, kG> &xr, RowG<T, kG> &dtr, RowG<T, kG> &zr) {
         const int64_t base = (row0 + t_base) * D + c0;
         const uint32_t o = (uint32_t)min(kTau * ti + tj, last_of(t_base)) * (uint32_t)D;
         xr.load(x + base + o);
         dtr.load(dt + base + o);
         if constexpr (kAhead && HAS_Z) zr.load(z + base + o);
     };
-    auto publish = [&](int64_t t_base, const Row6<T> &xr, const Row6<T> &dtr) {
+    auto publish = [&](int64_t t_base, const RowG<T, kG> &xr, const RowG<T, kG> &dtr) {
         const bool valid = kTau * ti + tj <= last_of(t_base);
         float xv[kG], dv[kG];
         xr.unpack(xv);
@@ -310,7 +317,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
             reinterpret_cast<float *>(&lds_u[c][tj >> 2][ti])[tj & 3] = d * xv[c];
         }
     };
-    auto gate = [&](int64_t t_base, Out6<T> &o6) {   // the outputs of the super-step
+    auto gate = [&](int64_t t_base, OutG<T, kG> &o6) {   // the outputs of the super-step
         float xv[kG], zv[kG], ov[kG];
         x_cur.unpack(xv);
         if constexpr (HAS_Z && !kAhead) {
@@ -327,7 +334,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
         }
         o6.pack(ov);
     };
-    auto store = [&](int64_t t_base, const Out6<T> &o6) {
+    auto store = [&](int64_t t_base, const OutG<T, kG> &o6) {
         if (kTau * ti + tj > last_of(t_base)) return;
         T *p = out + (row0 + t_base) * D + c0 + (uint32_t)(kTau * ti + tj) * (uint32_t)D;
         if (dead == 0) {
@@ -342,7 +349,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
     const int64_t n_super = (L + kT - 1) / kT;
     // (the first rows land where they stay: passed on through the registers of the next ones, the copy would wait for them here,
     // before B and C are requested)
-    Row6<T> dt_first;
+    RowG<T, kG> dt_first;
     if (token_thread) fetch(0, x_cur, dt_first, z_cur);
     fetch_bc(0, 0);
     if (tid < 2 * kG) (&lds_par[0][0])[tid] = par;
@@ -358,7 +365,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
     for (int64_t k = 0; k < n_super; ++k) {                       // L >= 1: at least one
         const int64_t t_base = k * kT;
         const bool more = k + 1 < n_super;
-        Row6<T> x_nxt, dt_nxt, z_nxt;
+        RowG<T, kG> x_nxt, dt_nxt, z_nxt;
         if (token_thread && more) fetch(t_base + kT, x_nxt, dt_nxt, z_nxt);
 
         // ---- 1. the lane's 8 tokens from zero (lane 0: from the state entering the super-step), decays kept
@@ -465,7 +472,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
         if constexpr (!kAhead) {
             if (more) fetch_bc(t_base + kT, 0);
         }
-        Out6<T> o6;
+        OutG<T, kG> o6;
         // The outputs are stored last: loads and stores are waited for by one counter, so a wait for the next rows that came
         // after the stores would also wait for the stores, with everyone else at the barrier.
         if (token_thread) {
@@ -493,51 +500,90 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
 
 }  // namespace
 
+namespace {
+
+// Channels per workgroup: what takes the fewest rounds of 256 workgroups times what one takes (a workgroup of fewer channels has
+// fewer wavefronts to a SIMD and is faster, but not in proportion).  us with 2 / 4 / 6 channels, bf16 | float32:
+//   1 x 1000 x  512  10.4*/ 11.6 / 15.7 | 12.2*/ 12.2 / 20.6      1 x  512 x 256   6.3*/  7.2 /  9.1 |  6.6*/  7.0 /  9.5
+//   1 x 1000 x  768  14.6 / 12.4*/ 15.2 | 15.9 / 13.5*/ 18.1      1 x 2000 x 1000 25.9 / 21.1*/ 26.0 | 28.5 / 23.7*/ 30.2
+//   1 x 2048 x 1536  36.1 / 39.6 / 26.7*| 37.1 / 44.9 / 32.4*     1 x 1000 x 2048   -  / 24.0*/ 32.3 |   -  / 24.8*/ 33.4
+int lanes_channels(int64_t batch, int64_t L, int64_t D)
+{
+    auto cost = [&](int64_t g, double round) { return (double)((batch * ((D + g - 1) / g) + 255) / 256) * round; };
+    const double six = cost(6, 1.0), four = cost(4, 0.8), two = cost(2, L <= 256 ? 0.68 : 0.7);
+    return two <= four && two <= six ? 2 : four <= six ? 4 : 6;
+}
+
+}  // namespace
+
 // Shapes the lane-scan kernel serves: 16 states, token rows that can be read in 4-byte pieces from any even
 // channel, at least one full workgroup; and among those the ones it is expected to finish before the two-pass
-// kernels of scan.hip.  Its time is a number of rounds of 256 workgroups of 6 channels, every one walking the whole sequence;
-// that of the two-pass kernels goes with all tokens.  Measured over 358 shapes: a round of the lanes takes 7.3 us + 10.0 ns a
-// token in bf16, 6.9 us + 13.1 ns in float32, the two passes 19.3 us + 10.2 ns a token and 1536 channels, 18.4 us + 9.8 ns.
-// The line (6 us + 11.6 ns against 24 us + 9.8 ns) lies between the two types, since the choice, and with it the size of
-// the workspace, is not told the type.  us, lanes / two-pass, bf16 | float32; * what the line takes:
-//   1 x  600 x  768  16.4*/ 22.2 | 16.8*/ 21.3       1 x 2048 x 1536  28.6*/ 41.1 | 34.0*/ 39.1       1 x   64 x 4096  22.7*/ 19.8 |  22.9*/ 19.1
-//   1 x 2048 x  768  26.8*/ 31.8 | 31.7*/ 31.0       1 x 6000 x 1536  69.3*/ 79.8 | 86.4*/ 75.0       1 x 8192 x 1536  90.0*/ 99.4 | 113.4*/ 92.9
-//   1 x 3000 x  768  37.2 / 41.0*| 44.6 / 37.2*      2 x 3000 x 1536  73.1*/ 79.2 | 88.2*/ 74.7       1 x 10240 x 1536 110.7 / 119.0*| 141.9 / 111.7*
-//   1 x 4096 x 2048 104.9 / 74.9*| 111.3 / 69.4*     2 x 4096 x 1536  93.6 / 99.0*| 115.0 / 92.4*     1 x 16384 x 1536 172.9 / 178.6*| 249.1 / 167.1*
+// kernels of scan.hip.  Its time is a number of rounds of 256 workgroups, every one walking the whole sequence;
+// that of the two-pass kernels goes with all tokens.  Measured over 358 shapes: a round of six channels takes 7.3 us + 10.0 ns a
+// token in bf16, 6.9 us + 13.1 ns in float32, the two passes 19.3 us + 10.2 ns a token and 1536 channels, 18.4 us + 9.8 ns.  A
+// round of four takes 5 us + 8 | 10 ns, of two 3 us + 7 | 10.4 ns.
+// The line lies between the two types, since the choice, and with it the size of the workspace, is not told the type; with two and
+// four channels close to where float32 comes out even.  us, lanes / two-pass, bf16 | float32; * what the line takes:
+//   1 x  600 x  768   9.3*/ 22.2 |  9.6*/ 21.3       1 x 2048 x 1536  28.6*/ 41.1 | 34.0*/ 39.1       1 x   64 x 4096  15.5*/ 19.8 |  15.8*/ 19.1
+//   1 x 2000 x  768  20.6*/ 31.5 | 23.4*/ 30.8       1 x 6000 x 1536  69.3*/ 79.8 | 86.4*/ 75.0       1 x 8192 x 1536  90.0*/ 99.4 | 113.4*/ 92.9
+//   1 x 4000 x  768  36.6 / 39.2*| 42.4 / 40.3*      1 x 4000 x 1024  36.9*/ 48.2 | 43.7*/ 46.6       1 x 10240 x 1536 110.7 / 119.0*| 141.9 / 111.7*
+//   1 x 2000 x  256  16.6 / 22.7*| 21.7 / 20.9*      1 x 2000 x 2048  40.2*/ 47.6 | 44.6*/ 45.7       1 x 4000 x 512   33.6 / 31.6*| 42.6 / 31.5*
+//   1 x 4096 x 2048  74.9 / 75.8*| 95.0 / 69.9*      2 x 4096 x 1536  93.6 / 99.0*| 115.0 / 92.4*     1 x 16384 x 1536 172.9 / 178.6*| 249.1 / 167.1*
 bool scan_lanes_applies(int64_t batch, int64_t L, int64_t D, int64_t N)
 {
-    if (N != kN || D % 2 != 0 || D < kG || L < 64 || batch > 65535) return false;
-    const double groups = (double)batch * (double)((D + kG - 1) / kG);
-    const double rounds = (double)(int64_t)((groups + 255.0) / 256.0);
-    const double lanes_ns = rounds * (6000.0 + 11.6 * (double)L);
+    if (N != kN || D % 2 != 0 || D < 6 || L < 64 || batch > 65535) return false;
+    const int64_t g = lanes_channels(batch, L, D), groups = batch * ((D + g - 1) / g);
+    const double rounds = (double)((groups + 255) / 256);
+    const double first = g == 6 ? 6000.0 : g == 4 ? 5000.0 : 2500.0, token = g == 6 ? 11.6 : g == 4 ? 9.7 : 12.5;
+    const double lanes_ns = rounds * (first + token * (double)L);
     const double two_pass_ns = 24000.0 + 9.8 * (double)L * ((double)batch * (double)D / 1536.0);
     return lanes_ns < two_pass_ns;
 }
 
-hipError_t launch_scan_lanes(const ScanArgs &a, hipStream_t stream)
+namespace {
+
+template <typename T, int G, int TAU> hipError_t launch_lanes(const ScanArgs &a, hipStream_t stream)
 {
-    const int64_t n_groups = (a.D + kG - 1) / kG;
+    const int64_t n_groups = (a.D + G - 1) / G;
     const dim3 grid((unsigned)(8 * ((n_groups + 7) / 8)), (unsigned)a.batch);   // padded for the XCD-aware numbering
-#define MAMBA_LAUNCH_LANES(T, HZ, SP)                                                                       \
-    scan_lanes_kernel<T, HZ, SP><<<grid, kThreadsL, 0, stream>>>(                                           \
+#define MAMBA_LAUNCH_LANES(HZ, SP)                                                                          \
+    scan_lanes_kernel<T, HZ, SP, G, TAU><<<grid, 64 * kParts * (G / 2), 0, stream>>>(                       \
         static_cast<const T *>(a.x), static_cast<const T *>(a.dt), a.A, static_cast<const T *>(a.Bm),       \
         static_cast<const T *>(a.Cm), a.Dskip, static_cast<const T *>(a.z), a.dt_bias, a.h0,                \
         static_cast<T *>(a.out), a.h_final, a.L, a.D)
-#define MAMBA_LAUNCH_LANES_T(T)                                  \
-    do {                                                         \
-        if (a.z) {                                               \
-            if (a.dt_softplus) MAMBA_LAUNCH_LANES(T, true, true);  \
-            else MAMBA_LAUNCH_LANES(T, true, false);             \
-        } else {                                                 \
-            if (a.dt_softplus) MAMBA_LAUNCH_LANES(T, false, true); \
-            else MAMBA_LAUNCH_LANES(T, false, false);            \
-        }                                                        \
-    } while (0)
-    if (a.io == kIoBf16) MAMBA_LAUNCH_LANES_T(bf16_t);
-    else MAMBA_LAUNCH_LANES_T(float);
-#undef MAMBA_LAUNCH_LANES_T
+    if (a.z) {
+        if (a.dt_softplus) MAMBA_LAUNCH_LANES(true, true);
+        else MAMBA_LAUNCH_LANES(true, false);
+    } else {
+        if (a.dt_softplus) MAMBA_LAUNCH_LANES(false, true);
+        else MAMBA_LAUNCH_LANES(false, false);
+    }
 #undef MAMBA_LAUNCH_LANES
     return hipGetLastError();
+}
+
+template <typename T> hipError_t launch_lanes_io(const ScanArgs &a, hipStream_t stream)
+{
+    // (a super-step of 512 tokens is half empty on 256: 256 x 768 with 4 channels 7.2 -> 5.6 us, float32 256 x 256 with 2 8.5 -> 4.4)
+    if (a.L <= 256) {
+        switch (lanes_channels(a.batch, a.L, a.D)) {
+        case 2: return launch_lanes<T, 2, 4>(a, stream);
+        case 4: return launch_lanes<T, 4, 4>(a, stream);
+        default: return launch_lanes<T, 6, 4>(a, stream);
+        }
+    }
+    switch (lanes_channels(a.batch, a.L, a.D)) {
+    case 2: return launch_lanes<T, 2, 4>(a, stream);
+    case 4: return launch_lanes<T, 4, 8>(a, stream);
+    default: return launch_lanes<T, 6, 8>(a, stream);
+    }
+}
+
+}  // namespace
+
+hipError_t launch_scan_lanes(const ScanArgs &a, hipStream_t stream)
+{
+    return a.io == kIoBf16 ? launch_lanes_io<bf16_t>(a, stream) : launch_lanes_io<float>(a, stream);
 }
 
 }  // namespace mamba

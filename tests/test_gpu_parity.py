@@ -183,6 +183,21 @@ def test_scan_single_pass_shapes(m, io, N, B, L, D):
 
 
 @pytest.mark.parametrize("io", [synth.F32, synth.BF16])
+@pytest.mark.parametrize("B,L,D", [(1, 64, 6), (1, 255, 512), (2, 257, 254), (1, 1025, 510),          # two channels to a workgroup
+                                   (1, 256, 1022), (1, 65, 2046), (3, 700, 330), (1, 1300, 1022),         # four
+                                   (1, 200, 1534), (1, 256, 3072), (1, 300, 1532)])                       # six
+def test_scan_time_across_lanes_every_width(m, io, B, L, D):
+    """Every number of channels to a workgroup and of tokens to a lane, with channel counts that leave the last workgroup
+    fewer of its own, one super-step, exactly one and several, with and without gate and carried state."""
+    say(io=io, B=B, L=L, D=D)
+    assert m.mamba_scan_kernel(B, L, D, 16) == "lanes"
+    c = synth.prefill_case(B, L, D, 16, 4, io, seed=60000 + L + D, random_A=True)
+    h0 = np.random.default_rng(L + D).standard_normal((B, D, 16)).astype(np.float32)
+    check_scan(m, c, h0=h0, what="lanes")
+    check_scan(m, c, what="lanes, zero state, no gate", z=None)
+
+
+@pytest.mark.parametrize("io", [synth.F32, synth.BF16])
 @pytest.mark.parametrize("B,L,D", [(1, 64, 576), (1, 513, 576), (2, 1000, 290), (1, 1030, 580), (3, 700, 198),
                                    (1, 1537, 1536), (16, 100, 36)])
 def test_scan_time_across_lanes_shapes(m, io, B, L, D):
