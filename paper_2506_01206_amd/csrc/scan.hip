@@ -9,7 +9,11 @@
 // C_t are the same for all channels of a batch row: they are staged through LDS as float32 and
 // read back with wave-uniform (broadcast) loads.  The recurrence is elementwise: 4 VALU
 // operations and one hardware exp2 per state update, no matrix product anywhere, and it is this
-// instruction stream (the exp2 issues at half the FMA rate), not HBM, that bounds it.
+// instruction stream (the exp2 takes the issue cycles of three multiplies), not HBM, that bounds it.
+// Exponentials are issued in runs that the other wavefronts of the SIMD do not cut into, those of the tokens' own
+// softplus and SiLU a tile at a time (transcendental_run): bf16 32768 x 1536 pass 1 136 -> 119 us, pass 2 171 -> 147.
+// (u B_t as a 4 x 4 x 1 matrix product of sixteen blocks, every lane its own column and B out of one register for
+// all, takes a multiply off every update, but costs 9 cycles for four and nothing of it overlaps: 146 and 189 us.)
 //
 // Time chunking.  A batch row offers only D / (64 CPL) wavefronts, far fewer than the 1024
 // SIMDs of the chip, so long sequences are cut into n_chunks time chunks that run in parallel:
@@ -33,7 +37,11 @@ namespace mamba {
 namespace {
 
 constexpr int kWave = 64;
-constexpr int kTile = 4;  // time steps whose token loads are issued together, one tile ahead
+// Time steps whose token loads are issued together, one tile ahead.  (The output pass of float32 holds three arrays of two registers
+// a step and channel pair: with four steps it needs 200 registers at 16 states and runs two wavefronts to a SIMD.  32768 x 1536:
+// four steps 206 us, two 185.  With 8 states there are registers enough: 20000 x 1536 four 136, two 140.)
+constexpr int kTile = 4;
+template <typename T, int N> constexpr int kOutTile = sizeof(T) == 4 && N > 8 ? 2 : kTile;
 
 template <typename T, int CPL> struct RawT;
 template <> struct RawT<float, 1> { typedef float type; };
@@ -68,10 +76,8 @@ template <int CPL> __device__ __forceinline__ void st_pack(bf16_t *p, const floa
 // every step then reads its N values with wave-uniform (broadcast) 16-byte LDS reads into
 // VGPRs.  Compared with scalar loads this keeps SGPR operands (which issue slower) and the
 // bf16 unpacking out of the inner loop.  NARR = 1 stages B only, 2 stages B and C.
-// sched_barrier mask: scalar, memory and LDS instructions may still be moved across; vector ALU ones stay put
-constexpr int kSchedMemoryOnly = 0x4 | 0x10 | 0x20 | 0x40 | 0x80 | 0x100 | 0x200;
 constexpr int kBcTile = 16;
-static_assert(kBcTile % kTile == 0, "B/C tiles must start on a token-tile boundary");
+static_assert(kBcTile % kTile == 0 && kTile % 2 == 0, "B/C tiles must start on a token-tile boundary");
 
 // The values of a lane are adjacent (one load per array) and stay as they were loaded until they go to LDS: converted where
 // they are requested, they would make the wavefront wait there, for them and for the token rows requested before them.
@@ -201,8 +207,9 @@ __device__ __forceinline__ void store_state(const float (&h)[CPL][N], float *p)
 // ---------------------------------------------------------------------------------------
 // pass 2 (and the only pass when n_chunks == 1): full recurrence with outputs
 // grid: (channel groups, n_chunks, batch), block: one wavefront
+// (float32: the two wavefronts to a SIMD that the compiler would settle for cost more than the registers save, see kOutTile)
 template <typename T, int N, int CPL, bool HAS_Z, bool SOFTPLUS>
-__global__ void __launch_bounds__(kWave)
+__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && N == 16 ? 3 : 1)))
 scan_chunk_out(const T *__restrict__ x, const T *__restrict__ dt, const float *__restrict__ A,
                const T *__restrict__ Bm, const T *__restrict__ Cm, const float *__restrict__ Dskip,
                const T *__restrict__ z, const float *__restrict__ dt_bias,
@@ -211,6 +218,7 @@ scan_chunk_out(const T *__restrict__ x, const T *__restrict__ dt, const float *_
                int64_t chunk_len, int n_chunks)
 {
     typedef typename RawT<T, CPL>::type raw_t;
+    constexpr int kTile = kOutTile<T, N>;
     const int lane = threadIdx.x;
     const int64_t b = blockIdx.z;
     const int chunk = blockIdx.y;
@@ -251,39 +259,43 @@ scan_chunk_out(const T *__restrict__ x, const T *__restrict__ dt, const float *_
             if (t + kBcTile < t1) bc.issue(t + kBcTile);
         }
     };
-    auto step = [&](int64_t t, raw_t xr, raw_t dr, raw_t zr) {
+    // deltas and gates of a tile's tokens, their exponentials, logarithms and reciprocals in runs
+    auto token_work = [&](auto &dl, auto &gt, const raw_t *dr, const raw_t *zr) {
+        constexpr int kSteps = sizeof(dl) / sizeof(float) / CPL;
+#pragma unroll
+        for (int i = 0; i < kSteps; ++i) {
+            unpack(dr[i], dl + i * CPL);
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) dl[i * CPL + c] += s.bias[c];
+            if constexpr (HAS_Z) unpack(zr[i], gt + i * CPL);
+        }
+        if constexpr (SOFTPLUS) softplus_run(dl);
+        if constexpr (HAS_Z) silu_run(gt);
+    };
+    auto step = [&](int64_t t, raw_t xr, const float *delta_t, const float *gate_t) {
         const int rel = (int)(t - t0);
         const int buf = (rel / kBcTile) & 1, sidx = rel & (kBcTile - 1);
         float bf[N], cf[N];
         bc.read(buf, 0, sidx, bf);
         bc.read(buf, 1, sidx, cf);
-        float xv[CPL], dv[CPL], zv[CPL], ov[CPL];
+        float xv[CPL], ov[CPL];
         unpack(xr, xv);
-        unpack(dr, dv);
-        if constexpr (HAS_Z) unpack(zr, zv);
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
-            const float v = dv[c] + s.bias[c];
-            const float delta = SOFTPLUS ? softplus_f32(v) : v;
+            const float delta = delta_t[c];
             const float u = delta * xv[c];
             float y = s.dskip[c] * xv[c];
-            // The exponentials of a channel's states are issued as one run, the plain instructions around them
-            // as runs of their own: exp2 next to exp2 issues at its own rate, exp2 scattered among multiplies
-            // costs every neighbour extra (a bare loop of this update: 22 cycles per update in runs of 16, 25 to
-            // 28 interleaved, which is what the compiler's scheduler produces when left alone).
+            // the exponentials of a channel's states are issued as one run
             float a[N];
 #pragma unroll
             for (int n = 0; n < N; ++n) a[n] = delta * s.a2[c][n];
-            __builtin_amdgcn_sched_barrier(kSchedMemoryOnly);
-#pragma unroll
-            for (int n = 0; n < N; ++n) a[n] = exp2_hw(a[n]);
-            __builtin_amdgcn_sched_barrier(kSchedMemoryOnly);
+            exp2_run(a);
 #pragma unroll
             for (int n = 0; n < N; ++n) {
                 s.h[c][n] = fmaf(a[n], s.h[c][n], u * bf[n]);
                 y = fmaf(s.h[c][n], cf[n], y);
             }
-            ov[c] = HAS_Z ? y * silu_f32(zv[c]) : y;
+            ov[c] = HAS_Z ? y * gate_t[c] : y;
         }
         // (dead lanes store too, what the lane they shadow stores: a branch here would leave the number of stores in flight
         // open, and the wait for the next rows would then be a wait for the stores as well)
@@ -308,8 +320,10 @@ scan_chunk_out(const T *__restrict__ x, const T *__restrict__ dt, const float *_
         const bool more = t + 2 * kTile <= t1;
         if (more) load_tile(t + kTile, xn, dn, zn);
         bc_advance(t);
+        float dl[kTile * CPL], gt[kTile * CPL];
+        token_work(dl, gt, dc, zc);
 #pragma unroll
-        for (int i = 0; i < kTile; ++i) step(t + i, xc[i], dc[i], zc[i]);
+        for (int i = 0; i < kTile; ++i) step(t + i, xc[i], dl + i * CPL, gt + i * CPL);
         if (more) {
 #pragma unroll
             for (int i = 0; i < kTile; ++i) {
@@ -322,10 +336,13 @@ scan_chunk_out(const T *__restrict__ x, const T *__restrict__ dt, const float *_
 #pragma nounroll
     for (; t < t1; ++t) {
         const int64_t o = (row0 + t) * D + d0;
+        const raw_t xr = ld_raw<T, CPL>(x + o), dr = ld_raw<T, CPL>(dt + o);
         raw_t zr = raw_t();
         if constexpr (HAS_Z) zr = ld_raw<T, CPL>(z + o);
         bc_advance(t);
-        step(t, ld_raw<T, CPL>(x + o), ld_raw<T, CPL>(dt + o), zr);
+        float dl[CPL], gt[CPL];
+        token_work(dl, gt, &dr, &zr);
+        step(t, xr, dl, gt);
     }
 
     if (h_final && chunk == n_chunks - 1 && live) store_state<N, CPL>(s.h, h_final + (b * D + d0) * N);
@@ -377,29 +394,37 @@ scan_chunk_state(const T *__restrict__ x, const T *__restrict__ dt, const float 
             if (t + kBcTile < t1) bc.issue(t + kBcTile);
         }
     };
-    auto step = [&](int64_t t, raw_t xr, raw_t dr) {
+    auto token_work = [&](auto &dl, const raw_t *dr) {
+        constexpr int kSteps = sizeof(dl) / sizeof(float) / CPL;
+#pragma unroll
+        for (int i = 0; i < kSteps; ++i) {
+            unpack(dr[i], dl + i * CPL);
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) dl[i * CPL + c] += s.bias[c];
+        }
+        if constexpr (SOFTPLUS) softplus_run(dl);
+    };
+    auto step = [&](int64_t t, raw_t xr, const float *delta_t) {
         const int rel = (int)(t - t0);
         float bf[N];
         bc.read((rel / kBcTile) & 1, 0, rel & (kBcTile - 1), bf);
-        float xv[CPL], dv[CPL];
+        float xv[CPL];
         unpack(xr, xv);
-        unpack(dr, dv);
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
-            const float v = dv[c] + s.bias[c];
-            const float delta = SOFTPLUS ? softplus_f32(v) : v;
+            const float delta = delta_t[c];
             const float u = delta * xv[c];
             sum[c] += delta;
-            // exponentials as one run per channel (see pass 2)
             float a[N];
 #pragma unroll
             for (int n = 0; n < N; ++n) a[n] = delta * s.a2[c][n];
-            __builtin_amdgcn_sched_barrier(kSchedMemoryOnly);
-#pragma unroll
-            for (int n = 0; n < N; ++n) a[n] = exp2_hw(a[n]);
-            __builtin_amdgcn_sched_barrier(kSchedMemoryOnly);
+            exp2_run(a);
 #pragma unroll
             for (int n = 0; n < N; ++n) s.h[c][n] = fmaf(a[n], s.h[c][n], u * bf[n]);
+            // nothing of a step needs its states at once: left alone, the compiler moves the updates behind the exponentials of
+            // the steps that follow and holds those (float32 32768 x 1536, 216 registers against 168: 165 -> 137 us)
+#pragma unroll
+            for (int n = 0; n < N; ++n) values_here(s.h[c][n]);
         }
     };
 
@@ -420,8 +445,10 @@ scan_chunk_state(const T *__restrict__ x, const T *__restrict__ dt, const float 
         const bool more = t + 2 * kTile <= t1;
         if (more) load_tile(t + kTile, xn, dn);
         bc_advance(t);
+        float dl[kTile * CPL];
+        token_work(dl, dc);
 #pragma unroll
-        for (int i = 0; i < kTile; ++i) step(t + i, xc[i], dc[i]);
+        for (int i = 0; i < kTile; ++i) step(t + i, xc[i], dl + i * CPL);
         if (more) {
 #pragma unroll
             for (int i = 0; i < kTile; ++i) {
@@ -433,8 +460,11 @@ scan_chunk_state(const T *__restrict__ x, const T *__restrict__ dt, const float 
 #pragma nounroll
     for (; t < t1; ++t) {
         const int64_t o = (row0 + t) * D + d0;
+        const raw_t dr = ld_raw<T, CPL>(dt + o);
         bc_advance(t);
-        step(t, ld_raw<T, CPL>(x + o), ld_raw<T, CPL>(dt + o));
+        float dl[CPL];
+        token_work(dl, &dr);
+        step(t, ld_raw<T, CPL>(x + o), dl);
     }
 
     if (live) {

@@ -25,8 +25,6 @@
 namespace mamba {
 namespace {
 
-// sched_barrier mask: scalar, memory and LDS instructions may still be moved across; vector ALU ones stay put
-constexpr int kSchedMemoryOnly = 0x4 | 0x10 | 0x20 | 0x40 | 0x80 | 0x100 | 0x200;
 constexpr int kThreads = 256;
 constexpr int kChannels = 64;   // channels per workgroup
 constexpr int kTile = 64;       // steps per tile (a multiple of 32)
@@ -122,7 +120,7 @@ __device__ __forceinline__ float quad_sum_scatter(const float (&p)[4], int q)
 // grid: (ceil(D / 64), batch); block: 256.  D % 8 == 0, N % 4 == 0.
 // (The tiles in LDS allow two workgroups to a compute unit, two wavefronts to a SIMD; stating that, and unrolling
 // the tile loop fully, lets the compiler's scheduler keep more LDS operands in flight: 8192 tokens x 8 x 4096
-// channels 1.25 -> 1.18 ms.  With 32 states the same two hints make it spill, so that variant keeps the defaults.)
+// channels 1.25 -> 1.18 ms; what it takes since its exponentials are in runs of their own, 1.05 -> 0.94.  With 32 states the same two hints make it spill, so that variant keeps the defaults.)
 template <typename T, int N, bool HAS_Z, bool SOFTPLUS>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N > 16 ? 1 : 2, N > 16 ? 8 : 2)))
 scan_direct_kernel(const T *x, const T *dt, const float *__restrict__ A, const T *Bm, const T *Cm,
@@ -214,12 +212,14 @@ scan_direct_kernel(const T *x, const T *dt, const float *__restrict__ A, const T
             // write eight different groups of four banks at a time (unrotated, four of them share a group)
             float4 *dst = reinterpret_cast<float4 *>(&lds_du[lr + 32 * i][8 * lcg]);
 #pragma unroll
+            for (int e = 0; e < 8; ++e) dv[e] += bias8[e];
+            if constexpr (SOFTPLUS) softplus_run(dv);
+#pragma unroll
             for (int e = 0; e < 8; e += 2) {
                 float d[2];
 #pragma unroll
                 for (int k = 0; k < 2; ++k) {
-                    const float v = dv[e + k] + bias8[e + k];
-                    d[k] = SOFTPLUS ? softplus_f32(v) : v;
+                    d[k] = dv[e + k];
                     if (tail) d[k] = valid ? d[k] : 0.0f;    // steps past the end leave the state as it is
                 }
                 dst[(e / 2 + (lcg >> 1)) & 3] = make_float4(d[0], d[0] * xv[e], d[1], d[1] * xv[e + 1]);
@@ -247,11 +247,14 @@ scan_direct_kernel(const T *x, const T *dt, const float *__restrict__ A, const T
             const float4 y0 = *reinterpret_cast<const float4 *>(&lds_y[lr + 32 * i][8 * lcg]);
             const float4 y1 = *reinterpret_cast<const float4 *>(&lds_y[lr + 32 * i][8 * lcg + 4]);
             yv[0] = y0.x; yv[1] = y0.y; yv[2] = y0.z; yv[3] = y0.w; yv[4] = y1.x; yv[5] = y1.y; yv[6] = y1.z; yv[7] = y1.w;
-            if constexpr (HAS_Z) z_cur[i].unpack(zv);
+            if constexpr (HAS_Z) {
+                z_cur[i].unpack(zv);
+                silu_run(zv);
+            }
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const float y = fmaf(dsk8[e], xv[e], yv[e]);
-                ov[e] = HAS_Z ? y * silu_f32(zv[e]) : y;
+                ov[e] = HAS_Z ? y * zv[e] : y;
             }
             o8[i].pack(ov);
         }
@@ -309,25 +312,19 @@ scan_direct_kernel(const T *x, const T *dt, const float *__restrict__ A, const T
         for (int s4 = 0; s4 < kTile; s4 += 4) {
             Group ahead;
             read_group(ahead, (s4 + 4) & (kTile - 1));       // the last group re-reads the first, unused
-            // the exponentials of the four steps as one run (exp2 next to exp2 issues at its own rate, scattered
-            // among multiplies it slows its neighbours), then the updates
-            float a[4][SPL], yp[4];
+            // the exponentials of the four steps as one run, then the updates
+            float a[4 * SPL], yp[4];
 #pragma unroll
             for (int j4 = 0; j4 < 4; ++j4)
 #pragma unroll
-                for (int j = 0; j < SPL; ++j) a[j4][j] = cur.du[j4].x * a2[j];
-            __builtin_amdgcn_sched_barrier(kSchedMemoryOnly);
-#pragma unroll
-            for (int j4 = 0; j4 < 4; ++j4)
-#pragma unroll
-                for (int j = 0; j < SPL; ++j) a[j4][j] = exp2_hw(a[j4][j]);
-            __builtin_amdgcn_sched_barrier(kSchedMemoryOnly);
+                for (int j = 0; j < SPL; ++j) a[j4 * SPL + j] = cur.du[j4].x * a2[j];
+            exp2_run(a);
 #pragma unroll
             for (int j4 = 0; j4 < 4; ++j4) {
                 yp[j4] = 0.0f;
 #pragma unroll
                 for (int j = 0; j < SPL; ++j) {
-                    h[j] = fmaf(a[j4][j], h[j], cur.du[j4].y * cur.bv[j4][j]);
+                    h[j] = fmaf(a[j4 * SPL + j], h[j], cur.du[j4].y * cur.bv[j4][j]);
                     yp[j4] = fmaf(h[j], cur.cv[j4][j], yp[j4]);
                 }
             }

@@ -133,6 +133,23 @@ def test_scan_shapes(m, io, L, D):
 
 @pytest.mark.parametrize("io", [synth.F32, synth.BF16])
 @pytest.mark.parametrize("N", [4, 8, 16, 32])
+def test_scan_remainders_of_a_tile(m, io, N):
+    """Chunks of whole tiles of two and of four steps, of tiles and a remainder, and of a remainder alone, the last chunk
+    shorter still, with and without gate and softplus."""
+    say(io=io, N=N)
+    c = synth.prefill_case(1, 41, 70, N, 4, io, seed=70000 + N)
+    h0 = np.random.default_rng(N).standard_normal((1, 70, N)).astype(np.float32)
+    for chunk_len in (1, 3, 4, 6, 7, 20):
+        check_scan(m, c, h0=h0, chunk_len=chunk_len, what="chunk_len=%d" % chunk_len)
+        check_scan(m, c, chunk_len=chunk_len, what="no gate, chunk_len=%d" % chunk_len, z=None)
+    c3 = dict(c)
+    c3["dt"] = (np.abs(values(c["dt"])) * 0.1).astype(np.float32) if io == synth.F32 else c["dt"]
+    if io == synth.F32:
+        check_scan(m, c3, h0=h0, dt_softplus=False, chunk_len=7, what="delta given directly")
+
+
+@pytest.mark.parametrize("io", [synth.F32, synth.BF16])
+@pytest.mark.parametrize("N", [4, 8, 16, 32])
 def test_scan_state_sizes_and_random_A(m, io, N):
     say(io=io, N=N)
     c = synth.prefill_case(2, 300, 96, N, 4, io, seed=500 + N, random_A=True)
