@@ -142,10 +142,9 @@ def test_scan_remainders_of_a_tile(m, io, N):
     for chunk_len in (1, 3, 4, 6, 7, 20):
         check_scan(m, c, h0=h0, chunk_len=chunk_len, what="chunk_len=%d" % chunk_len)
         check_scan(m, c, chunk_len=chunk_len, what="no gate, chunk_len=%d" % chunk_len, z=None)
-    c3 = dict(c)
-    c3["dt"] = (np.abs(values(c["dt"])) * 0.1).astype(np.float32) if io == synth.F32 else c["dt"]
-    if io == synth.F32:
-        check_scan(m, c3, h0=h0, dt_softplus=False, chunk_len=7, what="delta given directly")
+    c3 = dict(c)                     # (deltas above zero, and no bias that could take one below: exp(delta A) then never exceeds 1)
+    c3["dt"] = synth.to_io(np.abs(synth.io_values(c["dt"], io)) + 0.01, io)
+    check_scan(m, c3, h0=h0, dt_softplus=False, dt_bias=None, chunk_len=7, what="delta given directly")
 
 
 @pytest.mark.parametrize("io", [synth.F32, synth.BF16])
