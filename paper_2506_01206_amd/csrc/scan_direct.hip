@@ -387,8 +387,8 @@ template <typename T> hipError_t launch_direct_io(const ScanArgs &a, hipStream_t
 // The single-pass kernel serves a shape when its token rows can be read in 16-byte pieces and there are enough
 // 64-channel blocks to give nearly every compute unit a workgroup: then walking every token once beats cutting
 // time, which walks every token twice.  A lone workgroup takes the same time per step whatever the grid, so the
-// crossover is where the two-pass kernels stop fitting their work into that time (measured on 2048 tokens:
-// 192 blocks 185 us against 174 us in two passes, 256 blocks 194 against 234, 512 blocks 25 % ahead).
+// crossover is where the two-pass kernels stop fitting their work into that time (bf16, us, here / in two passes: 160 blocks of
+// 2000 tokens 169 / 149, 192 blocks of 3000 246 / 210, 224 blocks of 1000 87 / 111, 256 blocks of 8192 666 / 690, 512 blocks 25 % ahead).
 bool scan_direct_applies(int64_t batch, int64_t L, int64_t D, int64_t N)
 {
     if (L < 1 || D % 8 != 0 || N % 4 != 0 || batch > 65535) return false;

@@ -190,6 +190,11 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
 {
     constexpr int kThreadsL = 64 * kParts * (kG / 2);
     constexpr int kT = 64 * kTau;            // tokens per super-step
+    // Exponentials in runs of eight (a token's), logarithms with them.  Runs of 16 spill, and runs of the gate's do in float32.  The
+    // one wavefront to a SIMD that two channels make has no others to keep out, only the order to lose: 256 x 256 float32 4.42 us,
+    // 4.58 in runs.  With more, us: 2048 x 1536 bf16 28.2 -> 26.8, float32 32.4 -> 31.5; 333 x 1536 9.6 -> 9.3; 8000 x 1536
+    // 99.1 -> 97.7; 2000 x 1000 21.2 -> 20.4; 4 x 3000 x 768 74.6 -> 72.0.
+    constexpr bool kRuns = kG > 2;
     constexpr int kTokenThreads = kT;        // one token row per thread of the first wavefronts
     static_assert(kTokenThreads <= kThreadsL, "a token row per thread");
     // [token j of the lane's block][state group][lane][4 states]: the lanes of a wavefront read consecutive slots.
@@ -309,10 +314,16 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
         xr.unpack(xv);
         dtr.unpack(dv);
 #pragma unroll
+        for (int c = 0; c < kG; ++c) dv[c] += lds_par[0][c];
+        if constexpr (SOFTPLUS) {
+            if constexpr (kRuns) softplus_run(dv);
+            else
+#pragma unroll
+                for (int c = 0; c < kG; ++c) dv[c] = softplus_f32(dv[c]);
+        }
+#pragma unroll
         for (int c = 0; c < kG; ++c) {
-            const float v = dv[c] + lds_par[0][c];
-            float d = SOFTPLUS ? softplus_f32(v) : v;
-            d = valid ? d : 0.0f;                    // a token past the end leaves the state as it is
+            const float d = valid ? dv[c] : 0.0f;    // a token past the end leaves the state as it is
             reinterpret_cast<float *>(&lds_d[c][tj >> 2][ti])[tj & 3] = d;
             reinterpret_cast<float *>(&lds_u[c][tj >> 2][ti])[tj & 3] = d * xv[c];
         }
@@ -388,6 +399,15 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
                 const int j = 4 * jh + jj;
                 const float4 b4 = lds_B[j * kBcTau + part * kBcPart + lane];
                 const float bv[4] = {b4.x, b4.y, b4.z, b4.w};
+                float e[8];
+#pragma unroll
+                for (int ch = 0; ch < 2; ++ch)
+#pragma unroll
+                    for (int n = 0; n < 4; ++n) e[4 * ch + n] = (jj == 0 ? d4[ch].x : jj == 1 ? d4[ch].y : jj == 2 ? d4[ch].z : d4[ch].w) * a2[ch][n];
+                if constexpr (kRuns) exp2_run(e);
+                else
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) e[i] = exp2_hw(e[i]);
 #pragma unroll
                 for (int ch = 0; ch < 2; ++ch) {
                     const float d = jj == 0 ? d4[ch].x : jj == 1 ? d4[ch].y : jj == 2 ? d4[ch].z : d4[ch].w;
@@ -395,7 +415,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
                     dsum[ch] += d;
 #pragma unroll
                     for (int n = 0; n < 4; ++n) {
-                        a[j][ch][n] = exp2_hw(d * a2[ch][n]);
+                        a[j][ch][n] = e[4 * ch + n];
                         h[ch][n] = fmaf(a[j][ch][n], h[ch][n], u * bv[n]);
                     }
                 }
@@ -519,16 +539,16 @@ int lanes_channels(int64_t batch, int64_t L, int64_t D)
 // Shapes the lane-scan kernel serves: 16 states, token rows that can be read in 4-byte pieces from any even
 // channel, at least one full workgroup; and among those the ones it is expected to finish before the two-pass
 // kernels of scan.hip.  Its time is a number of rounds of 256 workgroups, every one walking the whole sequence;
-// that of the two-pass kernels goes with all tokens.  Measured over 358 shapes: a round of six channels takes 7.3 us + 10.0 ns a
-// token in bf16, 6.9 us + 13.1 ns in float32, the two passes 19.3 us + 10.2 ns a token and 1536 channels, 18.4 us + 9.8 ns.  A
-// round of four takes 5 us + 8 | 10 ns, of two 3 us + 7 | 10.4 ns.
-// The line lies between the two types, since the choice, and with it the size of the workspace, is not told the type; with two and
-// four channels close to where float32 comes out even.  us, lanes / two-pass, bf16 | float32; * what the line takes:
-//   1 x  600 x  768   9.3*/ 22.2 |  9.6*/ 21.3       1 x 2048 x 1536  28.6*/ 41.1 | 34.0*/ 39.1       1 x   64 x 4096  15.5*/ 19.8 |  15.8*/ 19.1
-//   1 x 2000 x  768  20.6*/ 31.5 | 23.4*/ 30.8       1 x 6000 x 1536  69.3*/ 79.8 | 86.4*/ 75.0       1 x 8192 x 1536  90.0*/ 99.4 | 113.4*/ 92.9
-//   1 x 4000 x  768  36.6 / 39.2*| 42.4 / 40.3*      1 x 4000 x 1024  36.9*/ 48.2 | 43.7*/ 46.6       1 x 10240 x 1536 110.7 / 119.0*| 141.9 / 111.7*
-//   1 x 2000 x  256  16.6 / 22.7*| 21.7 / 20.9*      1 x 2000 x 2048  40.2*/ 47.6 | 44.6*/ 45.7       1 x 4000 x 512   33.6 / 31.6*| 42.6 / 31.5*
-//   1 x 4096 x 2048  74.9 / 75.8*| 95.0 / 69.9*      2 x 4096 x 1536  93.6 / 99.0*| 115.0 / 92.4*     1 x 16384 x 1536 172.9 / 178.6*| 249.1 / 167.1*
+// that of the two-pass kernels goes with all tokens.  The line lies between the two types, since the choice, and with it the size of
+// the workspace, is not told the type, and it lies where the two met before the two-pass kernels' exponentials went into runs: those
+// have gained more by it (1.15x) than this one (1.03x), so that they now win from about 7000 tokens of 1536 bf16 channels on, but a
+// call that this kernel took needs no workspace, and one made without would be refused if the line moved down.
+// us, lanes / two-pass, bf16 | float32; * what the line takes:
+//   1 x  600 x  768  11.2*/ 21.6 | 11.9*/ 20.5       1 x 2048 x 1536  25.8*/ 36.1 | 31.2*/ 35.9       1 x   64 x 4096  15.5*/ 18.2 |  15.6*/ 18.4
+//   1 x 2000 x  768  19.4*/ 26.8 | 22.5*/ 25.9       1 x 6000 x 1536  70.8*/ 74.2 | 93.7*/ 73.0       1 x 8192 x 1536  97.5*/ 92.7 | 123.2*/ 89.2
+//   1 x 4000 x  768  34.0 / 36.7*| 40.8 / 36.8*      1 x 4000 x 1024  34.5*/ 44.5 | 41.9*/ 42.8       1 x 10240 x 1536 123.0 / 110.9*| 152.6 / 104.8*
+//   1 x 2000 x  256  16.9 / 22.5*| 21.5 / 21.3*      1 x 2000 x 2048  37.6*/ 43.4 | 43.6*/ 41.9       1 x 4000 x 512   33.6 / 30.9*| 41.9 / 29.7*
+//   4 x 1000 x  768  28.6*/ 35.3 | 34.2*/ 35.4       2 x 1000 x 1536  28.8*/ 34.9 | 34.1*/ 35.5       2 x 3000 x 1536  73.7*/ 73.6 | 97.5*/ 69.4
 bool scan_lanes_applies(int64_t batch, int64_t L, int64_t D, int64_t N)
 {
     if (N != kN || D % 2 != 0 || D < 6 || L < 64 || batch > 65535) return false;
