@@ -77,9 +77,10 @@ hipError_t launch_scan(const ScanArgs &a, hipStream_t stream);
 hipError_t scan_static_scratch(float **ptr);
 // Carry over chunk states, in place: slot 0 <- h0 (or 0); slot c <- exp(A * sumdt[c-1]) * slot[c-1] + slot[c].
 // ws_state: (batch, n_slots, D, N) fp32, slot c holding the local end state of chunk c - 1 on entry;
-// ws_sumdt: (batch, n_slots, D) fp32, entry c the sum of deltas of chunk c; A: (D, N).
+// ws_sumdt: (batch, n_slots, D) fp32, entry c the sum of deltas of chunk c; A: (D, N).  The first `walk` slots are walked; those that
+// are not a multiple of slot_step need not be written back.
 hipError_t launch_chunk_carry(const float *A, const float *h0, float *ws_state, const float *ws_sumdt, int64_t batch,
-                              int64_t D, int N, int n_slots, hipStream_t stream);
+                              int64_t D, int N, int n_slots, int walk, int slot_step, hipStream_t stream);
 hipError_t launch_copy_state(const float *src /* nullptr: zeros */, float *dst, int64_t n, hipStream_t stream);
 
 // Scalar-decay (Mamba-2 style) layer core.  x, z, out: (batch, L, H, P); dt: (batch, L, H); Bm, Cm: (batch, L, N);

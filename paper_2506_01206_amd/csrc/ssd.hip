@@ -644,10 +644,11 @@ hipError_t launch_ssd(const SsdArgs &a, hipStream_t stream)
     // 8000 255 -> 228; 2048 tokens (fourteen) takes 3 us more that way).  Not where the final state lies over h0, all or
     // part of it: other workgroups still read that.  (Instantiations of their own: as a run-time switch it changed the register allocation of
     // the other way, 2048 tokens 37 -> 41 us.)
-    const bool fold = ssd_folds(p.n_seg1, (p.n_seg2 - 1) * slot_step, a.h0, a.h_final, a.batch * D * a.N * (int64_t)sizeof(float));
+    const int before = (p.n_seg2 - 1) * slot_step;                // segments of pass 1 that the last one of pass 2 starts behind
+    const bool fold = ssd_folds(p.n_seg1, before, a.h0, a.h_final, a.batch * D * a.N * (int64_t)sizeof(float));
 #define MAMBA_SSD(NN, P2, HZ) (fold ? MAMBA_SSD_F(NN, P2, HZ, true) : MAMBA_SSD_F(NN, P2, HZ, false))
 #define MAMBA_SSD_F(NN, P2, HZ, FD)                                                                                       \
-    ssd_segment<NN, P2, HZ, FD><<<dim3((unsigned)((P2) ? p.n_seg2 : FD ? (p.n_seg2 - 1) * slot_step : p.n_seg1), (unsigned)a.H, (unsigned)a.batch),        \
+    ssd_segment<NN, P2, HZ, FD><<<dim3((unsigned)((P2) ? p.n_seg2 : before), (unsigned)a.H, (unsigned)a.batch),        \
                               (P2) ? 2 * kThreads : kThreads, 0, stream>>>(                                         \
         x, dt, a.A, Bm, Cm, a.Dskip, z, a.dt_bias, ws_state, ws_sumdt, a_rows, out, a.h0, a.h_final, a.L, a.H,       \
         (P2) ? p.chunks2 : p.chunks1, (P2) ? p.n_seg2 : p.n_seg1, n_slots, slot_step, nc, a.dt_softplus)
@@ -655,7 +656,7 @@ hipError_t launch_ssd(const SsdArgs &a, hipStream_t stream)
         if (a.N == 64) MAMBA_SSD(64, false, false);
         else MAMBA_SSD(128, false, false);
         if (!fold)
-            if (hipError_t e = launch_chunk_carry(a_rows, a.h0, ws_state, ws_sumdt, a.batch, D, a.N, n_slots, stream)) return e;
+            if (hipError_t e = launch_chunk_carry(a_rows, a.h0, ws_state, ws_sumdt, a.batch, D, a.N, n_slots, before + 1, slot_step, stream)) return e;
     } else {
         // a single segment starts from h0 itself: slot 0 <- h0 (or zeros)
         for (int64_t b = 0; b < a.batch; ++b)

@@ -169,6 +169,18 @@ def test_scan_carry_variants(m, N, L, chunk_len):
     check_scan(m, c, h0=h0, chunk_len=chunk_len, what="carry over %d slots" % ((L + chunk_len - 1) // chunk_len))
 
 
+@pytest.mark.parametrize("D", [66, 4100])
+@pytest.mark.parametrize("slots", [2, 8, 9, 16, 17, 32, 33])
+def test_scan_carry_of_few_slots(m, slots, D):
+    """One lane walks up to 32 slots: every number of registers it holds them in, one state to a lane (66 channels) and four
+    (4100, the last wavefront not full), and the first count it leaves to the segmented kernels."""
+    say(slots=slots, D=D)
+    L = 3 * slots - 1
+    c = synth.prefill_case(1, L, D, 16, 4, synth.F32, seed=7100 + slots, random_A=True)
+    h0 = np.random.default_rng(slots).standard_normal((1, D, 16)).astype(np.float32)
+    check_scan(m, c, h0=h0, chunk_len=3, what="carry over %d slots" % slots)
+
+
 @pytest.mark.parametrize("io", [synth.F32, synth.BF16])
 @pytest.mark.parametrize("N", [4, 8, 16, 32])
 @pytest.mark.parametrize("B,L,D", [(56, 1, 256), (56, 31, 256), (28, 65, 512), (56, 100, 200), (224, 129, 64), (230, 7, 8)])
@@ -1734,6 +1746,24 @@ def test_ssd_scan_final_state_shifted_over_the_initial_state(m, B, L, H, N):
             h0.copy_(g["h0"])
             out2, _ = call(h0, h_final=state)
             assert torch.equal(out, out2) and torch.equal(hf, state), (shift, at)
+
+
+@pytest.mark.parametrize("B,L,H,N", [(1, 2048, 24, 128), (2, 1500, 10, 64), (1, 6401, 4, 64), (1, 19199, 1, 64)])
+def test_ssd_scan_carry_of_every_other_slot(m, B, L, H, N):
+    """Pass 1 cuts the sequence twice as fine as pass 2 and leaves out what no segment starts behind: 15 slots of which the carry
+    writes back eight, 23, 99 (segmented carry) and 299 (the looped one)."""
+    from oracle import ssd
+    say(B=B, L=L, H=H, N=N)
+    c = ssd_case(np.random.default_rng(L), B, L, H, 64, N, synth.BF16)
+    g = {k: to_dev(v) for k, v in c.items()}
+    out, hf = m.mamba2_ssd_fwd(g["x"], g["dt"], g["A"], g["Bm"], g["Cm"], g["Dskip"], g["z"], g["dt_bias"], g["h0"])
+    out, hf = values(to_host(out)), to_host(hf)
+    w = {k: W(v) for k, v in c.items()}
+    for h in {0, H - 1}:
+        ro, rh = ssd.ssd_scan(w["x"][:, :, h:h + 1], w["dt"][:, :, h:h + 1], w["A"][h:h + 1], w["Bm"], w["Cm"], w["Dskip"][h:h + 1],
+                              w["z"][:, :, h:h + 1], w["dt_bias"][h:h + 1], w["h0"][:, h:h + 1])
+        assert_close(out[:, :, h:h + 1], ro, TOL[synth.BF16], "ssd out, head %d" % h)
+        assert_close(hf[:, h:h + 1], rh, TOL[synth.BF16], "ssd final state, head %d" % h)
 
 
 def test_ssd_scan_at_bench_size_sampled_heads(m):
