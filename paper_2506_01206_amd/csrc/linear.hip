@@ -635,16 +635,16 @@ hipError_t launch_few(const bf16_t *x, const bf16_t *w, const float *bias, const
                       hipStream_t stream)
 {
     const dim3 grid((unsigned)((N + 8 * CG - 1) / (8 * CG)), (unsigned)((M + 16 * MT - 1) / (16 * MT)));
-#define MAMBA_FEW(NW, G, EVEN) linear_few_kernel<MT, CG, NW, G, EVEN, STREAM><<<grid, 64 * NW, 0, stream>>>(x, w, bias, res, (int)M, (int)N, (int)K, o)
+#define MAMBA_FEW_K(NW, G, EVEN) linear_few_kernel<MT, CG, NW, G, EVEN, STREAM><<<grid, 64 * NW, 0, stream>>>(x, w, bias, res, (int)M, (int)N, (int)K, o)
     const int64_t per = (K + 511) / 512;
-    if (K == 256) MAMBA_FEW(4, 1, true);
-    else if (K < 256) MAMBA_FEW(4, 1, false);
-    else if (K == 512) MAMBA_FEW(8, 1, true);
-    else if (K == 768) MAMBA_FEW(6, 2, true);
-    else if (K == 1024) MAMBA_FEW(8, 2, true);
-    else if (K == 1536) MAMBA_FEW(8, 3, true);
-    else if (per <= 2 || per == 4) MAMBA_FEW(8, 2, false);
-    else MAMBA_FEW(8, 3, false);
+    if (K == 256) MAMBA_FEW_K(4, 1, true);
+    else if (K < 256) MAMBA_FEW_K(4, 1, false);
+    else if (K == 512) MAMBA_FEW_K(8, 1, true);
+    else if (K == 768) MAMBA_FEW_K(6, 2, true);
+    else if (K == 1024) MAMBA_FEW_K(8, 2, true);
+    else if (K == 1536) MAMBA_FEW_K(8, 3, true);
+    else if (per <= 2 || per == 4) MAMBA_FEW_K(8, 2, false);
+    else MAMBA_FEW_K(8, 3, false);
     return hipGetLastError();
 }
 
