@@ -392,14 +392,26 @@ ssd_segment(const bf16_t *x, const bf16_t *dt, const float *__restrict__ A, cons
                     }
                     // gacc[4 g + q] = C_t . B_s, t = 32 tt + lane % 32, s = 32 half + 8 g + 4 (lane / 32) + q
                     // M = G * exp(s_t - s_s) * delta_s for s <= t (steps past L have delta = 0), + D on the diagonal
+                    // (exponentials in runs of eight that the SIMD's other wavefronts stay out of, transcendental_run: 24 heads, 128 states, 32768
+                    // tokens 217 -> 207 us, 4 x 8000 232 -> 218, 2048 35.9 -> 34.9; runs of four 0.4 % behind, all sixteen ahead, under the
+                    // products, spill, and runs for the gate gain nothing)
+                    float e8[8];
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
                         const int s0 = half * 32 + 8 * g + 4 * up;
-                        const float c4[4] = {cs[g].x, cs[g].y, cs[g].z, cs[g].w}, d4[4] = {ds[g].x, ds[g].y, ds[g].z, ds[g].w};
+                        const float d4[4] = {ds[g].x, ds[g].y, ds[g].z, ds[g].w};
+                        if (g % 2 == 0) {
+#pragma unroll
+                            for (int w = 0; w < 2; ++w) {
+                                e8[4 * w] = (ct - cs[g + w].x) * kLog2e, e8[4 * w + 1] = (ct - cs[g + w].y) * kLog2e;
+                                e8[4 * w + 2] = (ct - cs[g + w].z) * kLog2e, e8[4 * w + 3] = (ct - cs[g + w].w) * kLog2e;
+                            }
+                            exp2_run(e8);
+                        }
                         float v[4];
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
-                            v[q] = (s0 + q <= t) ? gacc[4 * g + q] * exp2_hw((ct - c4[q]) * kLog2e) * d4[q] : 0.0f;
+                            v[q] = (s0 + q <= t) ? gacc[4 * g + q] * e8[4 * (g % 2) + q] * d4[q] : 0.0f;
                             if (s0 + q == t) v[q] += dsk;
                         }
                         split4(v, reinterpret_cast<uint2 *>(&mm_hi[t * kRowS + s0]), reinterpret_cast<uint2 *>(&mm_lo[t * kRowS + s0]));
