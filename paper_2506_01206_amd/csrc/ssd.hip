@@ -351,6 +351,9 @@ ssd_segment(const bf16_t *x, const bf16_t *dt, const float *__restrict__ A, cons
                     *reinterpret_cast<uint2 *>(orow + 8 * g) = make_uint2(f32x2_to_bf16x2(y[0], y[1]), f32x2_to_bf16x2(y[2], y[3]));
                 }
             };
+            // The chain between the barriers is this role's (products, M, products), so its wavefronts issue ahead of the state role's on
+            // their SIMD: 32768 tokens 207.4 -> 205.2 us, 4 x 8000 218.3 -> 216.1 (the other way round 228 and 260).
+            __builtin_amdgcn_s_setprio(1);
             for (int chunk = c_first; chunk < c_last; ++chunk) {
                 const int buf = (chunk - c_first) & 1;
                 epilogue();
@@ -392,9 +395,9 @@ ssd_segment(const bf16_t *x, const bf16_t *dt, const float *__restrict__ A, cons
                     }
                     // gacc[4 g + q] = C_t . B_s, t = 32 tt + lane % 32, s = 32 half + 8 g + 4 (lane / 32) + q
                     // M = G * exp(s_t - s_s) * delta_s for s <= t (steps past L have delta = 0), + D on the diagonal
-                    // (exponentials in runs of eight that the SIMD's other wavefronts stay out of, transcendental_run: 24 heads, 128 states, 32768
-                    // tokens 217 -> 207 us, 4 x 8000 232 -> 218, 2048 35.9 -> 34.9; runs of four 0.4 % behind, all sixteen ahead, under the
-                    // products, spill, and runs for the gate gain nothing)
+                    // (exponentials in runs of eight, see transcendental_run; the role's priority keeps the state role out of them: 24 heads, 128 states,
+                    // 32768 tokens 217 -> 207 us, 4 x 8000 232 -> 218, 2048 35.9 -> 34.9; runs of four 0.4 % behind, all sixteen ahead,
+                    // under the products, spill, and runs for the gate gain nothing)
                     float e8[8];
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
@@ -406,7 +409,10 @@ ssd_segment(const bf16_t *x, const bf16_t *dt, const float *__restrict__ A, cons
                                 e8[4 * w] = (ct - cs[g + w].x) * kLog2e, e8[4 * w + 1] = (ct - cs[g + w].y) * kLog2e;
                                 e8[4 * w + 2] = (ct - cs[g + w].z) * kLog2e, e8[4 * w + 3] = (ct - cs[g + w].w) * kLog2e;
                             }
-                            exp2_run(e8);
+                            __builtin_amdgcn_sched_barrier(kSchedMemoryOnly);
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) e8[i] = exp2_hw(e8[i]);
+                            __builtin_amdgcn_sched_barrier(kSchedMemoryOnly);
                         }
                         float v[4];
 #pragma unroll
