@@ -655,7 +655,7 @@ int mamba_block_step(const mamba_block_params_t *p, const void *hidden, void *hi
         // The x projection rides along as well: every in_proj workgroup multiplies its 16 finished x_c columns into it
         // and the state step adds the partial sums up, which takes the launch of a product with few output tiles out of
         // the chain.
-        const bool fuse_xproj = Di % 16 == 0 && R + 2 * N <= 256;
+        const bool fuse_xproj = Di % 16 == 0 && R + 2 * N <= 256 && step_xproj_fits(Di, N, R);
         if (fuse_xproj) {
             in.xproj_w = p->x_proj_w;
             in.xproj_part = reinterpret_cast<float *>(bb.xpart);

@@ -30,6 +30,16 @@ inline bool linear_few_fits(int64_t N, int64_t K)
     return K <= (int64_t)INT32_MAX - 63 && N <= ((int64_t)1 << 27) - 16;
 }
 
+// The state step of a draft position that adds up the x projection's partial sums (state_step_xproj_kernel) forms a lane's
+// places in A, a row of states, the dt weights and a row of partial sums (one run of dt_rank + 2 N floats per 16 channels) as
+// bytes in 32 bits, so each of them has to stay below 4 GiB.  A wider block keeps the x projection in a launch of its own, and
+// the state step that counts in 64 bits.
+inline bool step_xproj_fits(int64_t D, int64_t N, int64_t dt_rank)
+{
+    const int64_t most = (int64_t)1 << 32;
+    return D <= most / (4 * N) && D <= most / (2 * dt_rank) && D / 16 <= most / (4 * (dt_rank + 2 * N));
+}
+
 // Row tiles of 16 (1, 2 or 4) per workgroup of the way into a block at a draft position (draft_in.hip), M <= 64 rows, 16 columns
 // each: as few as make one round of workgroups on 256 CUs, and no more than there are rows for, since tiles past the last row
 // cost what the others do.  A whole draft position with 1, 2, 4 tiles: 3 rows of a 5120-channel model (640 column blocks) 43.8,

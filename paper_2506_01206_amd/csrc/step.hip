@@ -12,6 +12,7 @@
 // index the gather is fused into the load of h_in, which makes a separate state copy unnecessary.
 #include "device_math.h"
 #include "launch.h"
+#include "routes.h"
 
 namespace mamba {
 namespace {
@@ -382,7 +383,7 @@ state_step_conv_kernel(const int32_t *__restrict__ parent, const float *h_in, co
 // the fused dt projection), B and C come out of LDS.  The parts are what the step waits for first, so the first eight of a range are
 // requested ahead of everything else; the state row, behind the parent index, last.  Longer ranges (MORE: wide models) go on by eight.
 // Nothing but the parts' trip to memory is long here: what counts is the instructions between the launch and the last store.
-// Offsets of a lane are 32 bits from scalar bases, the split of the parts is worked out on the host, and the shapes that occur have
+// Offsets of a lane are 32 bits from scalar bases (step_xproj_fits), the split of the parts is worked out on the host, and the shapes that occur have
 // no conditions left (EXACT: eight parts to every range; NC: pieces of four dt weights per lane, 0: any number).  us a launch in a
 // replayed graph, 1 / 12 / 48 rows (before: divisions by the run's length, 64-bit offsets, loops of unknown length): 1024 channels 2.70 /
 // 2.82 / 4.17 (3.24 / 3.37 / 4.52), 1536 2.39 / 3.00 / 5.52 (3.28 / 3.84 / 6.12), 4096 5.4 / 9.2 / 18.7 (7.1 / 9.6 / 19.5), 5120 7.0 / 13.4 /
@@ -639,7 +640,7 @@ template <typename T, int N> hipError_t launch_step_n(const StepArgs &a, hipStre
     if (!a.dt_w && blocks(8) >= 384 && blocks(8) < 1024) return launch_step_u<T, N, 8>(a, stream);
     if constexpr (sizeof(T) == 2) {
         if (a.xpart) {
-            if (!a.dt_w || !a.z || !a.dt_softplus || a.dt_rank + 2 * N > kBlock || a.dt_rank % 4 || a.n_parts < 1 || a.D >= (int64_t)1 << 26) return hipErrorInvalidValue;
+            if (!a.dt_w || !a.z || !a.dt_softplus || a.dt_rank + 2 * N > kBlock || a.dt_rank % 4 || a.n_parts < 1 || !step_xproj_fits(a.D, N, a.dt_rank)) return hipErrorInvalidValue;
             if (blocks(4) >= 768) return launch_step_xproj<N, 4>(a, stream);
             return blocks(2) >= 768 ? launch_step_xproj<N, 2>(a, stream) : launch_step_xproj<N, 1>(a, stream);
         }

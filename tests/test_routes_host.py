@@ -12,6 +12,7 @@ SHIM = """
 extern "C" int folds(int n_seg1, int before, uintptr_t h0, uintptr_t h_final, int64_t bytes)
 { return mamba::ssd_folds(n_seg1, before, (const void *)h0, (const void *)h_final, bytes); }
 extern "C" int few_fits(int64_t N, int64_t K) { return mamba::linear_few_fits(N, K); }
+extern "C" int xproj_fits(int64_t D, int64_t N, int64_t dt_rank) { return mamba::step_xproj_fits(D, N, dt_rank); }
 extern "C" int row_tiles(int64_t M, int64_t N) { return mamba::linear_few_row_tiles(M, N); }
 extern "C" int tiles(int64_t M, int64_t N, int64_t K, int wide) { return mamba::linear_tiles(M, N, K, wide); }
 extern "C" int wide192(int64_t M, int64_t N, int64_t K, int wide) { return mamba::linear_wide192(M, N, K, wide, mamba::linear_tiles(M, N, K, wide)); }
@@ -30,6 +31,7 @@ def routes(tmp_path_factory):
     i32, i64, ptr = ctypes.c_int, ctypes.c_int64, ctypes.c_size_t
     lib.folds.argtypes = [i32, i32, ptr, ptr, i64]
     lib.few_fits.argtypes = [i64, i64]
+    lib.xproj_fits.argtypes = [i64, i64, i64]
     lib.row_tiles.argtypes = [i64, i64]
     lib.tiles.argtypes = [i64, i64, i64, i32]
     lib.wide192.argtypes = [i64, i64, i64, i32]
@@ -56,6 +58,20 @@ def test_few_row_product_leaves_what_32_bits_do_not_count_to_others(routes):
         assert not routes.few_fits(1, K), K
     assert routes.few_fits(1 << 26, 768) and (((1 << 27) - 16) // 16) * 512 < 1 << 32
     assert routes.few_fits((1 << 27) - 16, 768) and not routes.few_fits(1 << 27, 768) and not routes.few_fits(1 << 31, 8)
+
+
+@pytest.mark.parametrize("N", [4, 8, 16, 32])
+@pytest.mark.parametrize("dt_rank", [8, 32, 48, 64, 128])
+def test_draft_position_state_step_leaves_what_32_bit_offsets_do_not_reach_to_others(routes, N, dt_rank):
+    """The kernel that adds up the x projection's partial sums counts a lane's bytes in 32 bits: every last place that it forms
+    has to fit, and every block of which they all fit is still taken, up to the widest that the product ahead of it takes."""
+    D_most = (1 << 26) - 16
+    assert routes.few_fits(2 * D_most, 768)
+    for D in (16, 1536, 5120, 1 << 24, (1 << 25) - 16, 1 << 25, (1 << 25) + 16, 44739232, 44739248, D_most):
+        last = [16 * (D * N // 4 - 1), 2 * dt_rank * D - 8, 16 * (D // 16 * ((dt_rank + 2 * N) // 4) - 1), 4 * (D - 1)]
+        assert bool(routes.xproj_fits(D, N, dt_rank)) == all(v < 1 << 32 for v in last), D
+    assert bool(routes.xproj_fits((1 << 25) + 16, N, dt_rank)) == (N <= 16 and dt_rank <= 48)
+    assert routes.xproj_fits(1 << 24, 32, 128) and not routes.xproj_fits((1 << 24) + 16, 32, 136)
 
 
 def test_wide_blocks_of_few_rows_keep_the_two_projections_apart(routes):
