@@ -382,6 +382,15 @@ int mamba_conv_state_step(float *h_out, const float *h_in, void *conv_state_out,
     }
     StepArgs a{h_out, h_in, parent_idx, x, dt, Bm, Cm, z, A, Dskip, dt_bias, out,
                n_out, n_in, D, (int)N, (int)io, dt_softplus};
+    if (!conv_step_fits(D, N)) {
+        // x_c goes through the output where nobody asked for it: the step reads a channel's before it writes there
+        ConvArgs cv{x, conv_w, conv_bias, conv_state_in, xc_out ? xc_out : out, conv_state_out, n_out, 1, D, K, apply_silu ? 1 : 0, (int)io};
+        cv.parent = parent_idx;
+        cv.n_in = n_in;
+        if (hipError_t e = launch_conv1d(cv, static_cast<hipStream_t>(hip_stream))) return (int)e;
+        a.x = cv.y;
+        return (int)launch_step(a, static_cast<hipStream_t>(hip_stream));
+    }
     a.conv_w = conv_w;
     a.conv_bias = conv_bias;
     a.conv_src = conv_state_in;

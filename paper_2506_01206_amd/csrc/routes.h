@@ -30,6 +30,14 @@ inline bool linear_few_fits(int64_t N, int64_t K)
     return K <= (int64_t)INT32_MAX - 63 && N <= ((int64_t)1 << 27) - 16;
 }
 
+// The fused layer step (state_step_conv_kernel) counts channels in 32 bits and launches a wavefront per 64 of them (32 with 32
+// states), whose threads along x have to stay below 2^32.  A wider layer takes the conv and the state step one after the other,
+// which count in 64 bits.
+inline bool conv_step_fits(int64_t D, int64_t N)
+{
+    return D <= (N > 16 ? ((int64_t)1 << 31) - 32 : ((int64_t)1 << 32) - 64);
+}
+
 // The state step of a draft position that adds up the x projection's partial sums (state_step_xproj_kernel) forms a lane's
 // places in A, a row of states, the dt weights and a row of partial sums (one run of dt_rank + 2 N floats per 16 channels) as
 // bytes in 32 bits, so each of them has to stay below 4 GiB.  A wider block keeps the x projection in a launch of its own, and

@@ -623,7 +623,7 @@ template <typename T, int N> hipError_t launch_step_n(const StepArgs &a, hipStre
         // replayed graph on 4 / 2 pieces: 4 x 768 2.43 / 2.23, 32 x 768 3.16 / 2.99, 32 x 1536 3.33 / 3.38, 64 x 1536 4.73 /
         // 5.00, 64 x 4096 8.74 / 9.18, 128 x 4096 14.90 / 16.18
         constexpr int Q = N / 4, kFew = Q < 2 ? Q : 2, kMany = Q < 4 ? Q : 4;
-        if (a.D > UINT32_MAX) return hipErrorInvalidValue;
+        if (!conv_step_fits(a.D, N)) return hipErrorInvalidValue;
         const bool few = a.n_out * ((a.D + 64 / Q * kFew - 1) / (64 / Q * kFew)) <= 1024;
         switch (a.conv_k) {
         case 2: return few ? launch_step_conv<T, N, 2, kFew>(a, stream) : launch_step_conv<T, N, 2, kMany>(a, stream);

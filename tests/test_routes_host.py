@@ -12,6 +12,7 @@ SHIM = """
 extern "C" int folds(int n_seg1, int before, uintptr_t h0, uintptr_t h_final, int64_t bytes)
 { return mamba::ssd_folds(n_seg1, before, (const void *)h0, (const void *)h_final, bytes); }
 extern "C" int few_fits(int64_t N, int64_t K) { return mamba::linear_few_fits(N, K); }
+extern "C" int conv_step_fits(int64_t D, int64_t N) { return mamba::conv_step_fits(D, N); }
 extern "C" int xproj_fits(int64_t D, int64_t N, int64_t dt_rank) { return mamba::step_xproj_fits(D, N, dt_rank); }
 extern "C" int row_tiles(int64_t M, int64_t N) { return mamba::linear_few_row_tiles(M, N); }
 extern "C" int tiles(int64_t M, int64_t N, int64_t K, int wide) { return mamba::linear_tiles(M, N, K, wide); }
@@ -31,6 +32,7 @@ def routes(tmp_path_factory):
     i32, i64, ptr = ctypes.c_int, ctypes.c_int64, ctypes.c_size_t
     lib.folds.argtypes = [i32, i32, ptr, ptr, i64]
     lib.few_fits.argtypes = [i64, i64]
+    lib.conv_step_fits.argtypes = [i64, i64]
     lib.xproj_fits.argtypes = [i64, i64, i64]
     lib.row_tiles.argtypes = [i64, i64]
     lib.tiles.argtypes = [i64, i64, i64, i32]
@@ -58,6 +60,16 @@ def test_few_row_product_leaves_what_32_bits_do_not_count_to_others(routes):
         assert not routes.few_fits(1, K), K
     assert routes.few_fits(1 << 26, 768) and (((1 << 27) - 16) // 16) * 512 < 1 << 32
     assert routes.few_fits((1 << 27) - 16, 768) and not routes.few_fits(1 << 27, 768) and not routes.few_fits(1 << 31, 8)
+
+
+@pytest.mark.parametrize("N", [4, 8, 16, 32])
+def test_fused_layer_step_leaves_what_32_bits_do_not_count_to_others(routes, N):
+    """Channels in 32 bits and a grid of fewer than 2^32 threads along x, one wavefront per 64 / (N / 4) channels times the
+    pieces of a branch with many of them."""
+    channels = 64 // (N // 4) * min(N // 4, 4)
+    for D in (1, 1536, 1 << 30, (1 << 31) - 32, (1 << 31) - 24, 1 << 31, (1 << 32) - 64, (1 << 32) - 56, 1 << 32, 6 << 30):
+        threads = -(-D // channels) * 64
+        assert bool(routes.conv_step_fits(D, N)) == (D < 1 << 32 and threads < 1 << 32), D
 
 
 @pytest.mark.parametrize("N", [4, 8, 16, 32])
