@@ -15,10 +15,12 @@ LIB = os.path.join(HERE, "libmamba_hip.so")
 MARSHAL = os.path.join(HERE, "_marshal.so")
 SOURCES = ["api.cpp", "sd_tree_search.cpp", "conv1d.hip", "scan.hip", "scan_direct.hip", "scan_lanes.hip", "strided.hip", "step.hip", "fork.hip", "linear.hip", "draft_in.hip", "xdt.hip", "norm.hip", "vocab.hip", "ssd.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-# packed-fp32 VALU instructions are switched off for every device function.  The first 14 dwords of a kernel's arguments come in
-# registers instead of through a scalar load (a trip to the cache that every address waits for): 0.13 us of each of the launches
-# of a draft position (24-block draft of the tree (3,2,2,1,1) 1754 -> 1706 us, prefill of 333 tokens 1111 -> 1101).  So the
-# pointers that a kernel needs first are its first arguments.
+# packed-fp32 VALU instructions are switched off for every device function.  The first 14 dwords of a kernel's arguments, up to
+# the first aggregate, come in registers instead of through a scalar load (a trip to the cache that every address waits for).
+# us of a launch in a chain, without / with: 12 x 768 product of k = 1536 3.32 / 3.10, fused layer step 32 x 1536 3.92 / 3.47, RMSNorm of 8000
+# rows 7.65 / 7.24, scalar-decay scan of 1000 tokens 30.5 / 30.0.  Three kernels that do little but wait for memory lose
+# by it (scalar-decay step of 4 branches 3.52 / 3.91, state step 1 x 768 1.95 / 2.04, embedding of 12 tokens 1.81 / 1.95): their
+# first argument is an aggregate.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-mllvm", "-amdgpu-kernarg-preload-count=16", "-Wall", "-Wno-unused-function"]

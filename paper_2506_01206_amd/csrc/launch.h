@@ -109,6 +109,13 @@ struct SsdStepArgs {
 };
 hipError_t launch_ssd_step(const SsdStepArgs &a, hipStream_t stream);
 
+// The states of a step as one kernel argument: the compiler brings arguments in registers only up to the first aggregate, so that
+// a kernel whose first argument this is fetches them all as it goes (who gains by that is in build.py).
+struct StepStates {
+    float *out;
+    const float *in;
+};
+
 struct StepArgs {
     float *h_out;
     const float *h_in;

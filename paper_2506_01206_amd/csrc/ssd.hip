@@ -551,10 +551,12 @@ ssd_segment(const bf16_t *x, const bf16_t *dt, const float *__restrict__ A, cons
 // ---------------------------------------------------------------------------------------------------
 // one step for every live draft branch (the counterpart of the selective state update): a lane owns a
 // float4 of the branch's (H, P, N) state, the N / 4 lanes of a channel add their partial C.h.
+// (Arguments fetched by the kernel, not brought in registers: 24 heads of 64 x 128, 4 branches 3.91 -> 3.51 us, 16 8.41 -> 8.29, 64
+// 24.08 -> 24.03, 128 44.81 -> 44.50.)
 // grid: (ceil(H * P * N / 4 / 256), n_out)
 template <typename T, int N>
 __global__ void __launch_bounds__(kThreads)
-ssd_step_kernel(float *h_out, const float *h_in, const int32_t *__restrict__ parent, const T *__restrict__ x,
+ssd_step_kernel(StepStates h, const int32_t *__restrict__ parent, const T *__restrict__ x,
                 const T *__restrict__ dt, const float *__restrict__ A, const T *__restrict__ Bm, const T *__restrict__ Cm,
                 const float *__restrict__ Dskip, const T *__restrict__ z, const float *__restrict__ dt_bias,
                 T *__restrict__ out, int64_t n_in, int64_t H, int P, int softplus)
@@ -581,7 +583,7 @@ ssd_step_kernel(float *h_out, const float *h_in, const int32_t *__restrict__ par
     const bool p_ok = p >= 0 && p < n_in;
     // the state is touched once per step: streaming accesses, as in the selective step
     typedef float f32x4 __attribute__((ext_vector_type(4)));
-    const f32x4 hraw = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(h_in) + (p_ok ? p : 0) * row4 + f);
+    const f32x4 hraw = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(h.in) + (p_ok ? p : 0) * row4 + f);
     float4 hv = make_float4(hraw.x, hraw.y, hraw.z, hraw.w);
     hv.x = fmaf(a, hv.x, u * bq[0]);
     hv.y = fmaf(a, hv.y, u * bq[1]);
@@ -601,7 +603,7 @@ ssd_step_kernel(float *h_out, const float *h_in, const int32_t *__restrict__ par
     if (!live) return;
     f32x4 hst;
     hst.x = hv.x; hst.y = hv.y; hst.z = hv.z; hst.w = hv.w;
-    __builtin_nontemporal_store(hst, reinterpret_cast<f32x4 *>(h_out) + j * row4 + f);
+    __builtin_nontemporal_store(hst, reinterpret_cast<f32x4 *>(h.out) + j * row4 + f);
     if (q == 0) {
         y = fmaf(Dskip ? Dskip[hh] : 0.0f, xv, y);
         if (z) y *= silu_f32(ld_io(z, j * H * P + d));
@@ -698,7 +700,7 @@ hipError_t launch_ssd_step(const SsdStepArgs &a, hipStream_t stream)
     const int64_t row4 = a.H * a.P * (a.N / 4);
     dim3 grid((unsigned)((row4 + kThreads - 1) / kThreads), (unsigned)a.n_out);
 #define MAMBA_SSD_STEP(T, NN)                                                                                     \
-    ssd_step_kernel<T, NN><<<grid, kThreads, 0, stream>>>(a.h_out, a.h_in, a.parent, static_cast<const T *>(a.x),  \
+    ssd_step_kernel<T, NN><<<grid, kThreads, 0, stream>>>(StepStates{a.h_out, a.h_in}, a.parent, static_cast<const T *>(a.x), \
         static_cast<const T *>(a.dt), a.A, static_cast<const T *>(a.Bm), static_cast<const T *>(a.Cm), a.Dskip,   \
         static_cast<const T *>(a.z), a.dt_bias, static_cast<T *>(a.out), a.n_in, a.H, a.P, a.dt_softplus)
     if (a.io == kIoBf16) {

@@ -12,10 +12,15 @@ constexpr int kBlock = 256;
 
 // out[m, :] = table[tokens[m], :]; rows of dm bf16 moved as 16-byte vectors (dm % 8 == 0).
 // A token outside [0, V) yields a row of NaN instead of an out-of-bounds read.
+// (The sizes are one aggregate and come first, so that the kernel fetches its arguments and nobody brings them in registers: 1 token
+// 1.80 -> 1.69 us, 12 1.95 -> 1.80, 333 2.03 -> 1.92; 8000 5.43 -> 5.75.)
+struct EmbeddingSizes {
+    int64_t V, vecs;
+};
 __global__ void __launch_bounds__(kBlock)
-embedding_kernel(const int32_t *__restrict__ tokens, const uint4 *__restrict__ table, uint4 *__restrict__ out,
-                 int64_t V, int64_t vecs)
+embedding_kernel(EmbeddingSizes sizes, const int32_t *__restrict__ tokens, const uint4 *__restrict__ table, uint4 *__restrict__ out)
 {
+    const int64_t V = sizes.V, vecs = sizes.vecs;
     const int64_t m = blockIdx.x;
     const int64_t t = tokens[m];
     const bool ok = t >= 0 && t < V;
@@ -164,8 +169,8 @@ topk_kernel(const bf16_t *__restrict__ logits, int32_t *__restrict__ idx, float 
 hipError_t launch_embedding(const int32_t *tokens, const void *table, void *out, int64_t M, int64_t V, int64_t dm,
                             hipStream_t stream)
 {
-    embedding_kernel<<<(unsigned)M, kBlock, 0, stream>>>(tokens, static_cast<const uint4 *>(table),
-                                                       static_cast<uint4 *>(out), V, dm / 8);
+    embedding_kernel<<<(unsigned)M, kBlock, 0, stream>>>(EmbeddingSizes{V, dm / 8}, tokens, static_cast<const uint4 *>(table),
+                                                       static_cast<uint4 *>(out));
     return hipGetLastError();
 }
 
