@@ -306,7 +306,8 @@ template <int MT> hipError_t launch_m(const LinearArgs &a, hipStream_t stream)
         if (a.K == 768) return launch_k<MT, MT < 2 ? 4 : 6, MT < 2 ? 3 : 2, true>(a, stream);
         if (a.K == 1024) return launch_k<MT, MT < 2 ? 4 : 8, MT < 2 ? 4 : 2, true>(a, stream);
         if (a.K == 1536) return launch_k<MT, 8, 3, true>(a, stream);
-        if (a.K == 2048 && MT < 4) return launch_k<MT, 8, MT < 4 ? 4 : 3, true>(a, stream);
+        if constexpr (MT < 4)
+            if (a.K == 2048) return launch_k<MT, 8, 4, true>(a, stream);
     }
     // any other k: as many steps at once as leave the fewest empty ones in the last trip
     const int64_t per = (a.K + 511) / 512;

@@ -609,10 +609,15 @@ template <int N, int U> hipError_t launch_step_xproj(const StepArgs &a, hipStrea
         static_cast<const bf16_t *>(a.dt_w), static_cast<const bf16_t *>(a.x), static_cast<const bf16_t *>(a.z), a.A, \
         a.dt_bias, a.Dskip, a.h_out, static_cast<bf16_t *>(a.out), a.n_in)
 #define MAMBA_STEP_XC(NC) do { if (exact) MAMBA_STEP_X(NC, true, false); else if (more) MAMBA_STEP_X(NC, false, true); else MAMBA_STEP_X(NC, false, false); } while (0)
-    if (N == 16 && a.dt_rank == 32) MAMBA_STEP_XC(2);
-    else if (N == 16 && a.dt_rank == 48) MAMBA_STEP_XC(3);
-    else if (N == 16 && a.dt_rank == 64) MAMBA_STEP_XC(4);
-    else MAMBA_STEP_XC(0);
+    if constexpr (N == 16) {
+        switch (a.dt_rank) {
+        case 32: MAMBA_STEP_XC(2); return hipGetLastError();
+        case 48: MAMBA_STEP_XC(3); return hipGetLastError();
+        case 64: MAMBA_STEP_XC(4); return hipGetLastError();
+        default: break;
+        }
+    }
+    MAMBA_STEP_XC(0);
 #undef MAMBA_STEP_XC
 #undef MAMBA_STEP_X
     return hipGetLastError();
