@@ -1204,12 +1204,13 @@ def test_scan_invariants_at_size(m):
 @pytest.mark.parametrize("M,N,K,splits", [(1, 1, 8, None), (5, 80, 48, (48, 16, 16)), (130, 200, 72, None),
                                           (257, 3072, 768, (1536, 1536)), (1000, 80, 1536, (48, 16, 16)),
                                           (384, 768, 1536, None), (64, 1536, 48, None), (129, 129, 1032, (1, 128)),
-                                          # few rows (draft positions): the split-k kernel, one or two row blocks
+                                          # few output tiles (draft positions, narrow products): 16 x 8, two of them on 32 x 16
                                           (18, 3072, 768, (1536, 1536)), (12, 80, 1536, (48, 16, 16)), (32, 768, 1536, None),
                                           (33, 100, 520, (3, 90, 7)), (64, 50, 1544, None), (3, 1000, 72, None),
                                           (65, 96, 512, None),
-                                          # few rows, very wide (the LM head): tiled kernel with streaming weight loads
-                                          (12, 8200, 136, None), (64, 9000, 64, (8192, 808)),
+                                          # few rows, very wide (the LM head): 16 x 16 with streaming weight loads up to 16 rows, the
+                                          # vocabulary and width of a 130M-shaped drafter among them; 64 x 64 tiles for more rows
+                                          (12, 8200, 136, None), (1, 50280, 768, None), (16, 50280, 768, None), (64, 9000, 64, (8192, 808)),
                                           # more than a thousand 128 x 128 tiles (ragged edges, short and odd slab counts)
                                           (8190, 4100, 136, (2052, 2048)), (8192, 4096, 40, None), (8300, 4000, 32, (8, 3992)),
                                           # whole slabs only (K a multiple of 64): 1, 2, 3, 5 and 7 of them, ragged edges,
@@ -1261,9 +1262,10 @@ def test_linear_192_row_tiles(m, M, N, K, splits):
 @pytest.mark.parametrize("M,N,K,splits", [(1, 4096, 8, None), (17, 2050, 40, None), (257, 250, 1544, (48, 102, 100)),   # 16 x 16
                                           (19, 4090, 768, (2040, 2050)), (100, 800, 520, None),                          # 32 x 16
                                           (65, 4000, 512, (1500, 2500)), (255, 999, 1288, None), (2700, 80, 1536, (48, 16, 16)),   # 32 x 32
-                                          (330, 761, 1096, (3, 700, 58)), (641, 700, 1024, None), (129, 2600, 4104, None),         # 64 x 32
-                                          (50, 5000, 264, (4000, 1000)), (64, 4500, 776, None),                          # 64 x 16
-                                          # steps of 64 k: 16 x 16, 32 x 16
+                                          (330, 761, 1096, (3, 700, 58)), (641, 700, 1024, None),                        # 32 x 32
+                                          (50, 5000, 264, (4000, 1000)), (64, 4500, 776, None),                          # 32 x 32
+                                          (129, 2600, 4104, None),                                                       # 64 x 32
+                                          # 16 x 8, with one row block and with twenty-one; 32 x 16
                                           (13, 80, 1024, None), (333, 80, 2056, (48, 16, 16)), (100, 790, 1032, (300, 490))])
 def test_linear_few_tiles(m, M, N, K, splits):
     """Products with few output tiles, at both sides of the lines between the tile shapes they get and with ragged rows,
@@ -1272,11 +1274,13 @@ def test_linear_few_tiles(m, M, N, K, splits):
 
 
 @pytest.mark.parametrize("K", [8, 64, 72, 256, 264, 512, 768, 1024, 1096, 1536, 2048, 3080])
-@pytest.mark.parametrize("M,N,splits", [(1, 8, None), (15, 100, (48, 12, 40)), (17, 2041, None), (100, 1500, (700, 800)), (33, 8200, None),
-                                        (500, 1000, None), (129, 1999, (999, 1000))])
+@pytest.mark.parametrize("M,N,splits", [(1, 8, None), (15, 100, (48, 12, 40)), (17, 2041, None), (31, 3900, (1900, 2000)),
+                                        (100, 1500, (700, 800)), (33, 8200, None), (500, 1000, None), (129, 1999, (999, 1000)),
+                                        (1, 8192, None), (12, 8201, (8000, 201))])
 def test_linear_few_every_split_of_k(m, M, N, K, splits):
-    """Every way the wavefronts of the kernel for few output tiles share k (one trip, several, remainders of a step), on 8 and 16
-    columns and on 32 rows, on 32 x 32 tiles and, with a k of 2048 and more, on 64 x 32."""
+    """Every way the wavefronts of the kernel for few output tiles share k (one trip, several, remainders of a step), on tiles of
+    16 x 8, 16 x 16 and 32 x 16, on 32 x 32 from a k of 256 on, on 64 x 32 with 2048 and more, and on 16 x 16 with streaming weight
+    loads (the LM head: up to 16 rows, 8192 columns and more) up to 2048."""
     test_linear_against_oracle(m, M, N, K, splits)
 
 
