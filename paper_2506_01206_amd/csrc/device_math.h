@@ -64,12 +64,13 @@ __device__ __forceinline__ float silu_f32(float v)
     return v * rcp_hw(1.0f + exp2_hw(-v * kLog2e));
 }
 
-// Transcendental instructions in runs.  A SIMD issues one after the other at 8 cycles each and plain instructions at 2.7, but loses
-// cycles at every change between the two kinds, those of different wavefronts included.  So a run keeps what is next to it in the
+// Transcendental instructions in runs.  ns an instruction takes of a SIMD with 4 wavefronts, each kind alone: mul 1.2, fma 1.5, exp2
+// 3.6 to 4.0.  At every change between the two kinds time is lost, those of different wavefronts included.  So a run keeps what is next to it in the
 // program out of it (the fences: scalar, memory and LDS instructions may cross, vector ones not) and keeps the other wavefronts of
 // the SIMD from cutting in (the priority of a wave, raised for the length of the run; the others issue what is not vector
-// work, and have their turn after it).  A bare loop of state updates (mul, exp2, mul, fma, fma), cycles per update at 2, 3 and 4
-// wavefronts per SIMD: 23.5, 22.7 and 22.1 in runs, 19.9, 19.3 and 18.9 with the priority; the sum of the parts is 19.
+// work, and have their turn after it).  A bare loop of state updates (mul, exp2, mul, fma, fma; sixteen exponentials a run), ns of
+// a SIMD per update at 2, 3 and 4 wavefronts: 11.9, 11.6 and 11.5 in the compiler's order, 11.2, 11.0 and 10.7 in runs, 8.3, 9.2 and 8.1
+// with the priority, less than the parts alone add up to (9.0 to 9.4).
 constexpr int kSchedMemoryOnly = 0x4 | 0x10 | 0x20 | 0x40 | 0x80 | 0x100 | 0x200;
 template <typename F> __device__ __forceinline__ void transcendental_run(F issue)
 {

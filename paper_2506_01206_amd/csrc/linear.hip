@@ -675,6 +675,11 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     //   512 x  512, K = 1024   -  / 5.2 / 4.7 /  3.9 /  5.1 /  8.4      700 x 1024, K = 2048   -  / 18.3/ 16.5 / 12.1 / 15.0 / 13.3
     //   256 x 1536, K = 3072   -  / 15.3/ 12.7/ 12.9 / 10.3 / 18.1      256 x 2048, K = 4096   -  / 29.2/ 24.2 / 21.4 / 18.0 / 28.3
     //   200 x 2560, K = 5120   -  / 40.9/ 37.3/ 37.4 / 36.4 / 34.9      256 x 1536, K =   48   -  / 3.1 /  2.9 /   -  /   -  /  3.1
+    // How many 32 x 32 (`most`), between k of 512 and 1024; us on 32 x 32 / the tile kernels for k = 576, 640, 768, 896, 960:
+    //   608 tiles (256 x 2432)  7.2 / 7.6    7.2 / 7.6    7.4 / 7.9    7.6 / 9.1    7.7 / 9.2
+    //   672 tiles (224 x 3072)  7.1 / 7.1    7.2 / 7.1    7.5 / 7.1    7.7 / 8.3    7.8 / 8.3
+    //   768 tiles (768 x 1024)  7.1 / 7.1    7.2 / 7.2    7.7 / 7.2    7.7 / 8.4    7.9 / 8.4
+    // So 608 is where the two meet for a k of 768; for k between that and 1024 32 x 32 stays ahead up to 768 tiles, by 4 to 8 %.
     // Up to 16 rows against very many columns (the LM head on a draft position): 16 columns each, any number of rounds, up to a k of
     // four trips; us on that / 64 x 64 tiles: 1 x 50280, K = 768 13.3 / 15.7, 12 x 50280 15.1 / 17.0, 12 x 16384 6.7 / 10.0, 12 x 32768,
     // K = 2048 25.0 / 30.4 (12 x 50280, K = 2560 54.3 / 51.5; 32 x 50280, K = 768 on 32 rows 22.6 / 18.3).

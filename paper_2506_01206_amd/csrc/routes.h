@@ -50,9 +50,12 @@ inline bool step_xproj_fits(int64_t D, int64_t N, int64_t dt_rank)
 
 // Row tiles of 16 (1, 2 or 4) per workgroup of the way into a block at a draft position (draft_in.hip), M <= 64 rows, 16 columns
 // each: as few as make one round of workgroups on 256 CUs, and no more than there are rows for, since tiles past the last row
-// cost what the others do.  A whole draft position with 1, 2, 4 tiles: 3 rows of a 5120-channel model (640 column blocks) 43.8,
-// 49.2, 61.2 us, of a 3072-channel one 19.7, 23.9, 28.6; 24 rows 66.1, 68.2, 79.2 and 28.7, 30.3, 34.6; 48 rows of a
-// 1536-channel one 19.0, 21.0, 21.5, of a 512-channel one 12.0, 12.9, 14.6 (measured on the kernel before it, which lay the same way).
+// cost what the others do.  us of a whole block with 1 / 2 / 4 tiles, 24 blocks in turn, replayed (* what this takes):
+//    3 rows of 5120 channels 34.1*/ 41.2 / 53.8, of 3072 18.5*/ 19.4 / 26.7, of 1536 9.3*/ 10.0 / 11.8    12 rows of 1536 10.2*/ 10.9 / 12.7
+//   24 rows of 5120 channels 57.5 / 62.7*/ 68.8, of 3072 26.9 / 26.7*/ 33.4, of 1536 12.3 / 12.7*/ 14.4   32 rows of 1536 12.9 / 13.3*/ 15.0
+//   48 rows of 5120 channels 92.8 /102.6 /101.6*, of 1536 15.7 / 16.6 / 17.6*, of 512 8.9*/ 9.6 / 10.7    64 rows of 1536 17.0 / 18.1 / 19.1*
+// The rounds come from the kernel before draft_in.hip; on that one a single tile is ahead also where it makes further rounds, by up
+// to 12 % of a block.
 inline int linear_few_row_tiles(int64_t M, int64_t N)
 {
     const int64_t columns = (N + 15) / 16;

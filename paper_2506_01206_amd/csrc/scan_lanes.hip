@@ -523,10 +523,10 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
 namespace {
 
 // Channels per workgroup: what takes the fewest rounds of 256 workgroups times what one takes (a workgroup of fewer channels has
-// fewer wavefronts to a SIMD and is faster, but not in proportion).  us with 2 / 4 / 6 channels, bf16 | float32:
-//   1 x 1000 x  512  10.4*/ 11.6 / 15.7 | 12.2*/ 12.2 / 20.6      1 x  512 x 256   6.3*/  7.2 /  9.1 |  6.6*/  7.0 /  9.5
-//   1 x 1000 x  768  14.6 / 12.4*/ 15.2 | 15.9 / 13.5*/ 18.1      1 x 2000 x 1000 25.9 / 21.1*/ 26.0 | 28.5 / 23.7*/ 30.2
-//   1 x 2048 x 1536  36.1 / 39.6 / 26.7*| 37.1 / 44.9 / 32.4*     1 x 1000 x 2048   -  / 24.0*/ 32.3 |   -  / 24.8*/ 33.4
+// fewer wavefronts to a SIMD and is faster, but not in proportion).  us with 2 / 4 / 6 channels, bf16 | float32 (one session):
+//   1 x 1000 x  512  10.5*/ 10.6 / 13.8 | 12.3*/ 11.9 / 19.9      1 x  512 x 256   6.3*/  6.9 /  8.9 |  6.6*/  6.7 /  9.1
+//   1 x 1000 x  768  14.5 / 11.7*/ 14.2 | 16.0 / 13.2*/ 17.6      1 x 2000 x 1000 26.1 / 19.9*/ 24.0 | 28.5 / 23.0*/ 29.0
+//   1 x 2048 x 1536  36.3 / 37.6 / 25.0*| 37.0 / 43.2 / 31.3*     1 x 1000 x 2048 25.3 / 23.0*/ 30.7 | 28.8 / 24.0*/ 32.2
 int lanes_channels(int64_t batch, int64_t L, int64_t D)
 {
     auto cost = [&](int64_t g, double round) { return (double)((batch * ((D + g - 1) / g) + 255) / 256) * round; };
@@ -541,14 +541,17 @@ int lanes_channels(int64_t batch, int64_t L, int64_t D)
 // kernels of scan.hip.  Its time is a number of rounds of 256 workgroups, every one walking the whole sequence;
 // that of the two-pass kernels goes with all tokens.  The line lies between the two types, since the choice, and with it the size of
 // the workspace, is not told the type, and it lies where the two met before the two-pass kernels' exponentials went into runs: those
-// have gained more by it (1.15x) than this one (1.03x), so that they now win from about 7000 tokens of 1536 bf16 channels on, but a
-// call that this kernel took needs no workspace, and one made without would be refused if the line moved down.
-// us, lanes / two-pass, bf16 | float32; * what the line takes:
-//   1 x  600 x  768  11.2*/ 21.6 | 11.9*/ 20.5       1 x 2048 x 1536  25.8*/ 36.1 | 31.2*/ 35.9       1 x   64 x 4096  15.5*/ 18.2 |  15.6*/ 18.4
-//   1 x 2000 x  768  19.4*/ 26.8 | 22.5*/ 25.9       1 x 6000 x 1536  70.8*/ 74.2 | 93.7*/ 73.0       1 x 8192 x 1536  97.5*/ 92.7 | 123.2*/ 89.2
-//   1 x 4000 x  768  34.0 / 36.7*| 40.8 / 36.8*      1 x 4000 x 1024  34.5*/ 44.5 | 41.9*/ 42.8       1 x 10240 x 1536 123.0 / 110.9*| 152.6 / 104.8*
-//   1 x 2000 x  256  16.9 / 22.5*| 21.5 / 21.3*      1 x 2000 x 2048  37.6*/ 43.4 | 43.6*/ 41.9       1 x 4000 x 512   33.6 / 30.9*| 41.9 / 29.7*
-//   4 x 1000 x  768  28.6*/ 35.3 | 34.2*/ 35.4       2 x 1000 x 1536  28.8*/ 34.9 | 34.1*/ 35.5       2 x 3000 x 1536  73.7*/ 73.6 | 97.5*/ 69.4
+// have gained more by it than this one, so that between about 7000 tokens of 1536 channels (float32: 2700) and the line they are
+// ahead by up to 9 % (float32: 31 %).  But a call that this kernel took needs no workspace, and one made without would be
+// refused if the line moved down; a whole block, which brings its workspace and is bf16, could be told apart, and is not.
+// us, lanes / two-pass, bf16 | float32, one session, four sets of operands in turn (on one set, which stays in the last-level
+// cache, 1 x 8192 x 1536 takes 81 | 110 here); * what the line takes:
+//   1 x  600 x  768  11.1*/ 20.8 | 12.0*/ 20.9       1 x 2048 x 1536  25.8*/ 35.5 | 31.4*/ 35.9       1 x   64 x 4096  15.4*/ 17.3 |  15.6*/ 17.0
+//   1 x 2000 x  768  19.6*/ 30.1 | 22.7*/ 26.5       1 x 6000 x 1536  68.7*/ 73.5 | 93.5*/ 68.5       1 x 8192 x 1536  97.0*/ 92.6 | 123.8*/ 87.0
+//   1 x 4000 x  768  34.0 / 37.4*| 41.0 / 37.2*      1 x 7000 x 1536  84.0*/ 83.1 |108.0*/ 79.3       1 x 10240 x 1536 125.7 / 110.7*| 152.0 / 104.2*
+//   1 x 2000 x  256  17.0 / 21.8*| 21.8 / 22.0*      1 x 4000 x 1024  34.5*/ 44.3 | 41.7*/ 42.6       1 x 4000 x 512   33.8 / 32.9*| 42.1 / 29.6*
+//   1 x 3000 x 1536  34.4*/ 45.5 | 48.4*/ 43.8       1 x 4000 x 1536  43.9*/ 53.9 | 65.3*/ 52.9       1 x 9900 x 1536 120.2*/110.6 | 151.8*/ 104.3
+//   4 x 1000 x  768  28.3*/ 35.7 | 34.2*/ 35.5       1 x 2000 x 2048  37.6*/ 43.5 | 43.0*/ 41.6       2 x 3000 x 1536  75.2*/ 73.2 | 98.0*/ 68.4
 bool scan_lanes_applies(int64_t batch, int64_t L, int64_t D, int64_t N)
 {
     if (N != kN || D % 2 != 0 || D < 6 || L < 64 || batch > 65535) return false;
