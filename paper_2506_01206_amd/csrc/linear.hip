@@ -20,6 +20,7 @@
 // Epilogue: the accumulators (+ bias) are rounded to bf16 into LDS, then leave as 16-byte row
 // chunks (+ residual), so that stores are coalesced; output splits that are not multiples of 8
 // columns take an element-wise path.
+#include <algorithm>
 #include <type_traits>
 
 #include "device_math.h"
@@ -459,6 +460,212 @@ __device__ __forceinline__ void wave_sync()
 }
 
 // ---------------------------------------------------------------------------------------------------
+// One round of tiles (the projections of a context of some hundred to a few thousand tokens): no CU has a second tile to work
+// on while it waits, so what counts is how many slabs are under way.  A slab of 64 k takes about 1 us to come from the last-level
+// cache and 0.1 to 0.4 to be multiplied, so a ring of LDS stages holds as many slabs as fit (64 x 128 tiles: six of 24 KB, 128 x
+// 128: four of 32 KB, both eight wavefronts and one workgroup to a CU; 64 x 64: four of 16 KB, four wavefronts and two), all but
+// one of them requested.  Loads, swizzle and fragments are those of linear_wide_kernel, and so are the sums, to the bit.  Before the
+// last quarter of slab s a wavefront waits for its part of slab s + 1 (loads arrive in order, so it leaves as many under way as
+// the younger slabs have), the barrier publishes that and frees the stage of slab s, and slab s + STAGES is requested into it, a
+// quarter of its loads under every quarter of products.  The epilogue goes through 2 KB of LDS private to a wavefront, a 32 x 32
+// block at a time, without a barrier; the residual is requested three slabs before the end.
+// Of the 12.0 us of 2048 x 768, K = 1536 (64 x 128 tiles), the loads alone take 8.2 and the fragment reads with the products 8.4 (LDS: a
+// slab is written once and read 2.7 times, 700 cycles against 256 of matrix work), the outputs 2.  us in chains of 24 weights,
+// replayed, before (register-staged tiles, memory-to-LDS tiles of two stages) / now: 512 x 3072, K = 768 8.9 / 8.1; 1000 x 3072
+// 12.3 / 10.1; 2048 x 768, K = 1536 17.1 / 12.0; 4000 x 768 19.3 / 16.1; 1500 x 1024, K = 2048 20.7 / 14.6; 2048 x 1536, K = 3072
+// 41.7 / 30.8.  As one persistent workgroup per CU on 256 x 128 tiles the same scheme does not beat the tiles above on long contexts
+// (32768 x 3072 175 to 182 us against 165 to 175): matrix cores on random data are held back by power there (the MFMAs alone take
+// 75 us on constant operands and 97 to 106 on random ones).
+// Requires M >= BM, N % BN == 0, K % 64 == 0 and output widths that are multiples of 8; the last row block moves back as above.
+// grid: 8 * ceil(tiles / 8) workgroups, each XCD a contiguous range of tiles in groups of group_n columns: a walk over all
+// columns would bring all of w into every XCD's L2.
+template <int BM, int BN, int WM, int WN, int STAGES, int PER_CU>
+__global__ void __launch_bounds__(64 * WM * WN, WM * WN * PER_CU / 4)
+linear_ring_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ bias, const bf16_t *residual,
+                   int64_t M, int64_t K, int tiles_m, int tiles_n, int group_n, OutSplit out)
+{
+    constexpr int NW = WM * WN;
+    constexpr int MT = BM / WM / 32, NT = BN / WN / 32;           // 32 x 32 MFMA tiles per wavefront along m and n
+    constexpr int kStage = (BM + BN) * kWideRow;
+    constexpr int NLX = BM / 8 / NW, NLW = BN / 8 / NW, NL = NLX + NLW;   // loads per wavefront and slab
+    static_assert(NLX * 8 * NW == BM && NLW * 8 * NW == BN && MT * WM * 32 == BM && NT * WN * 32 == BN, "whole loads and tiles");
+    constexpr int kPatch = 32 * 64;                               // a 32 x 32 block of outputs
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[STAGES * kStage + NW * kPatch];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+
+    const int n_tiles = tiles_m * tiles_n, per_xcd = (n_tiles + 7) / 8;
+    const int tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per_xcd || tile >= n_tiles) return;
+    const int group = tile / (group_n * tiles_m), in_group = tile - group * group_n * tiles_m;
+    const int width = min(group_n, tiles_n - group * group_n), row_block = in_group / width;
+    const int64_t m_first = (int64_t)row_block * BM, n0 = (int64_t)(group * group_n + in_group - row_block * width) * BN;
+    const int64_t m0 = m_first + BM <= M ? m_first : M - BM;
+    const int dead = (int)(m_first - m0);                         // leading rows that belong to the row block before
+
+    const uint32_t lane_off = (uint32_t)((lane >> 3) * K * 2 + (((lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7)) << 4));
+    const char *xrow = reinterpret_cast<const char *>(x + (m0 + 8 * wave) * K);   // of the next slab to be requested
+    const char *wrow = reinterpret_cast<const char *>(w + (n0 + 8 * wave) * K);
+    const int64_t rows_nw = 16 * NW * K;                          // bytes between a wavefront's groups of 8 rows
+    const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)lds;
+    const int S = (int)(K / kWideBK);
+    int to_request = S, stage_at = 0;
+    auto request = [&](auto first, auto last) __attribute__((always_inline)) {   // loads [first, last) of that slab
+        if (to_request <= 0) return;
+#pragma unroll
+        for (int i = decltype(first)::value; i < decltype(last)::value; ++i)
+            load_to_lds16(i < NLX ? xrow + i * rows_nw : wrow + (i - NLX) * rows_nw, lane_off,
+                          lds0 + stage_at + (i < NLX ? 0 : BM * kWideRow) + wave * 1024 + (i < NLX ? i : i - NLX) * (1024 * NW));
+    };
+    auto requested = [&]() __attribute__((always_inline)) {
+        stage_at = stage_at + kStage == STAGES * kStage ? 0 : stage_at + kStage;
+        xrow += kWideRow;
+        wrow += kWideRow;
+        --to_request;
+    };
+    typedef std::integral_constant<int, 0> L0;
+    typedef std::integral_constant<int, (NL + 3) / 4> L1;
+    typedef std::integral_constant<int, (2 * NL + 3) / 4> L2;
+    typedef std::integral_constant<int, (3 * NL + 3) / 4> L3;
+    typedef std::integral_constant<int, NL> L4;
+    // waits until no more than the loads of min(younger, STAGES - 2) slabs are under way (vmcnt is split over bits 3:0 and 15:14)
+    auto wait_for = [&](int younger) __attribute__((always_inline)) {
+#define MAMBA_RING_WAIT(SLABS) __builtin_amdgcn_s_waitcnt(0x0F70 | (((SLABS) * NL) & 15) | ((((SLABS) * NL) >> 4) << 14))
+        static_assert(STAGES >= 3 && STAGES <= 6 && (STAGES - 2) * NL < 64, "a case for every number of slabs under way");
+        if (younger >= STAGES - 2) MAMBA_RING_WAIT(STAGES - 2);
+        else if (STAGES > 5 && younger == 3) MAMBA_RING_WAIT(3);
+        else if (STAGES > 4 && younger == 2) MAMBA_RING_WAIT(2);
+        else if (STAGES > 3 && younger == 1) MAMBA_RING_WAIT(1);
+        else MAMBA_RING_WAIT(0);
+#undef MAMBA_RING_WAIT
+    };
+
+    f32x16 acc[MT][NT];
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int b = 0; b < NT; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.0f;
+    int frag_x[4], frag_w[4];                                     // as in linear_wide_kernel
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        const int slot = ((2 * ks + (lane >> 5)) ^ ((lane >> 1) & 7)) << 4;
+        frag_x[ks] = (wm * (BM / WM) + (lane & 31)) * kWideRow + slot;
+        frag_w[ks] = (BM + wn * (BN / WN) + (lane & 31)) * kWideRow + slot;
+    }
+    struct Frags { bf16x8 xf[MT], wf[NT]; };
+    auto load_frags = [&](const unsigned char *stage, int ks, Frags &f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t) f.xf[t] = *reinterpret_cast<const bf16x8 *>(stage + frag_x[ks] + t * 32 * kWideRow);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) f.wf[t] = *reinterpret_cast<const bf16x8 *>(stage + frag_w[ks] + t * 32 * kWideRow);
+    };
+    auto multiply = [&](const Frags &f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int a = 0; a < MT; ++a)
+#pragma unroll
+            for (int b = 0; b < NT; ++b)
+                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.wf[b], f.xf[a], acc[a][b], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // the 16-byte chunks of the outputs that this thread stores: row 16 i + lane / 4 of block (a, b), chunk lane % 4 of its row
+    auto out_row = [&](int a, int i) __attribute__((always_inline)) { return wm * (BM / WM) + a * 32 + 16 * i + (lane >> 2); };
+    auto out_at = [&](int row, int b, int *sp) __attribute__((always_inline)) {
+        int64_t col;
+        *sp = locate(out, n0 + wn * (BN / WN) + b * 32 + (lane & 3) * 8, &col);
+        return (m0 + row) * out.width[*sp] + col;
+    };
+    u32x4 res[MT][NT][2];
+
+#pragma unroll
+    for (int i = 0; i < STAGES - 1; ++i) {
+        request(L0(), L4());
+        requested();
+    }
+    int younger = S - 1;                                          // slabs behind the one that is waited for
+    wait_for(younger);
+    lds_barrier_linear();
+    Frags f0, f1;
+    const unsigned char *cur = lds;
+    load_frags(cur, 0, f0);
+    request(L0(), L1());
+    const int fetch_res = residual ? (S > 3 ? S - 3 : 0) : -1;
+#pragma unroll 1
+    for (int s = 0; s < S; ++s) {
+        if (s == fetch_res) {
+#pragma unroll
+            for (int a = 0; a < MT; ++a)
+#pragma unroll
+                for (int b = 0; b < NT; ++b)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        int sp;                                   // (a dead row is not read: its owner may be writing it)
+                        const int64_t at = out_at(max(out_row(a, i), dead), b, &sp);
+                        res[a][b][i] = *reinterpret_cast<const u32x4 *>(residual + at);
+                    }
+        }
+        load_frags(cur, 1, f1);
+        request(L1(), L2());
+        multiply(f0);
+        load_frags(cur, 2, f0);
+        request(L2(), L3());
+        multiply(f1);
+        load_frags(cur, 3, f1);
+        request(L3(), L4());
+        requested();
+        multiply(f0);
+        // every read of this stage has been issued, and the last ones are waited for (the products below want them): the stage is
+        // free behind the barrier
+        __builtin_amdgcn_s_waitcnt(0xC07F);                       // lgkmcnt(0)
+        wait_for(--younger);
+        lds_barrier_linear();
+        cur = cur + kStage == lds + STAGES * kStage ? lds : cur + kStage;
+        if (s + 1 < S) load_frags(cur, 0, f0);
+        request(L0(), L1());
+        multiply(f1);
+    }
+
+    // acc[a][b][4 g + j] is C[m = 32 a + lane % 32][n = 32 b + 8 g + 4 (lane / 32) + j] of the wavefront's part.  Rows of a block lie
+    // 64 bytes apart, their four 16-byte slots swizzled by the row pair.
+    unsigned char *patch = lds + STAGES * kStage + wave * kPatch;
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int b = 0; b < NT; ++b) {
+            const int r = lane & 31;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                float4 bv = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                if (bias) bv = *reinterpret_cast<const float4 *>(bias + n0 + wn * (BN / WN) + b * 32 + 8 * g + 4 * (lane >> 5));
+                uint2 v;
+                v.x = f32x2_to_bf16x2(acc[a][b][4 * g + 0] + bv.x, acc[a][b][4 * g + 1] + bv.y);
+                v.y = f32x2_to_bf16x2(acc[a][b][4 * g + 2] + bv.z, acc[a][b][4 * g + 3] + bv.w);
+                *reinterpret_cast<uint2 *>(patch + r * 64 + ((g ^ ((r >> 1) & 3)) << 4) + 8 * (lane >> 5)) = v;
+            }
+            wave_sync();
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int pr = 16 * i + (lane >> 2), row = out_row(a, i);
+                uint4 v = *reinterpret_cast<const uint4 *>(patch + pr * 64 + (((lane & 3) ^ ((pr >> 1) & 3)) << 4));
+                if (residual) {
+                    const u32x4 q = res[a][b][i];
+                    v.x = f32x2_to_bf16x2(bf16_lo(v.x) + bf16_lo(q.x), bf16_hi(v.x) + bf16_hi(q.x));
+                    v.y = f32x2_to_bf16x2(bf16_lo(v.y) + bf16_lo(q.y), bf16_hi(v.y) + bf16_hi(q.y));
+                    v.z = f32x2_to_bf16x2(bf16_lo(v.z) + bf16_lo(q.z), bf16_hi(v.z) + bf16_hi(q.z));
+                    v.w = f32x2_to_bf16x2(bf16_lo(v.w) + bf16_lo(q.w), bf16_hi(v.w) + bf16_hi(q.w));
+                }
+                int sp;
+                const int64_t at = out_at(row, b, &sp);
+                if (row >= dead) *reinterpret_cast<uint4 *>(out.ptr[sp] + at) = v;
+            }
+            wave_sync();
+        }
+}
+
+// ---------------------------------------------------------------------------------------------------
 // Few output tiles (a draft position, Sec. 4.1, whose way into a block is draft_in.hip; a short context; the narrow products of a
 // longer one): nothing is big, and what counts is the number of trips to memory and of barriers between the launch and the last
 // store, and the instructions between them.  One workgroup per 8 CG output columns and 16 MT rows, its NW wavefronts share the
@@ -648,6 +855,20 @@ hipError_t launch_few(const bf16_t *x, const bf16_t *w, const float *bias, const
     return hipGetLastError();
 }
 
+template <int BM, int BN, int WM, int WN, int STAGES, int PER_CU>
+hipError_t launch_ring(const bf16_t *x, const bf16_t *w, const float *bias, const bf16_t *res, const OutSplit &o, int64_t M, int64_t N, int64_t K,
+                       hipStream_t stream)
+{
+    const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)(N / BN);
+    // columns of a group: as many as bring about 2 MB of w, half of an XCD's L2, in groups of equal width
+    const int64_t most = std::max<int64_t>(1, ((int64_t)9 << 18) / (BN * 2 * K));
+    const int64_t groups = (tiles_n + most - 1) / most;
+    const unsigned per_xcd = (unsigned)((tiles_m * tiles_n + 7) / 8);
+    linear_ring_kernel<BM, BN, WM, WN, STAGES, PER_CU><<<8 * per_xcd, 64 * WM * WN, 0, stream>>>(
+        x, w, bias, res, M, K, tiles_m, tiles_n, (int)((tiles_n + groups - 1) / groups), o);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
@@ -693,7 +914,13 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
         if (a.K >= 256 && t32 <= most) MAMBA_FEW(2, 4);
     }
 #undef MAMBA_FEW
-    const bool wide = vec && N % 128 == 0 && a.M >= 128 && a.K % (2 * kWideBK) == 0;
+    switch (linear_ring(a.M, N, a.K, vec != 0)) {
+    case kRing64: return launch_ring<64, 64, 2, 2, 4, 2>(x, w, a.bias, res, o, a.M, N, a.K, stream);
+    case kRing64x128: return launch_ring<64, 128, 2, 4, 6, 1>(x, w, a.bias, res, o, a.M, N, a.K, stream);
+    case kRing128: return launch_ring<128, 128, 2, 4, 4, 1>(x, w, a.bias, res, o, a.M, N, a.K, stream);
+    default: break;
+    }
+    const bool wide = vec && N % 128 == 0 && a.M >= 128 && a.K % (2 * kWideBK) == 0 && a.K <= kToLdsLongestK;
     auto grid = [&](int bm, int bn) { return dim3((unsigned)((N + bn - 1) / bn), (unsigned)((a.M + bm - 1) / bm)); };
     auto in_turn = [&](int64_t t) { return (unsigned)(8 * ((t + 7) / 8)); };
     const LinearTiles kind = linear_tiles(a.M, N, a.K, wide);

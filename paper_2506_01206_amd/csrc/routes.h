@@ -63,6 +63,30 @@ inline int linear_few_row_tiles(int64_t M, int64_t N)
     return M <= 32 || columns * ((M + 31) / 32) <= 256 ? 2 : 4;
 }
 
+// linear_wide_kernel and linear_ring_kernel place a lane's 16 bytes within eight rows of k in 32 bits.
+constexpr int64_t kToLdsLongestK = (int64_t)1 << 28;
+
+// Products whose tiles come in one round of workgroups take linear_ring_kernel, the smallest tile that does it; the few-row kernels
+// have been asked before.  64 x 64 tiles run two to a CU, but a second set of them costs what half as many 64 x 128 do.  us on
+// the kernel before (the tile kernels below) / 64 x 64 / 64 x 128 / 128 x 128, 24 weights in turn:
+//    200 x 3072, K =  768   7.1 / 6.6*/ 8.0 / 9.7       512 x 3072, K =  768   8.9 / 8.5 / 8.1*/10.0      1000 x 3072, K =  768  12.3 / 12.5 / 13.6 / 10.1*
+//    200 x 5120, K = 1280  12.9 /12.1*/13.5 /17.1       333 x 5120, K = 1280  13.7 /14.9 /13.3*/17.0       700 x 5120, K = 1280  21.0 / 23.6 / 20.8 / 17.1*
+//   1000 x 1024, K = 2048  16.4 /12.1*/13.8 /17.7      2048 x  768, K = 1536  17.1 /12.3 /11.8*/15.0      4000 x  768, K = 1536  19.3 / 20.0 / 20.9 / 16.1*
+//   2048 x  512, K = 1024  11.1 / 8.0*/ 9.4 /11.6      3000 x  512, K = 1024  15.0 / 9.8 / 9.5*/11.9      3000 x 1280, K = 2560  37.4 / 36.2 / 31.9 / 28.6*
+// Beyond one round the tile kernels are ahead: 1500 x 3072 13.7 / 18.4 / 19.5 / 18.9, 2048 x 3072 15.7 / 22.1 / 20.6 / 19.3.  With a short
+// k there is little to have under way: K = 256, 1024 x 1024 4.8 / 4.5* 64 x 64, but 1024 x 2048 5.8* / 5.9 64 x 128, 1500 x 1536 6.2* / 6.5
+// 128 x 128; K = 384, 1000 x 1536 7.0 / 6.7* 64 x 128.
+enum LinearRing { kRingNone, kRing64, kRing64x128, kRing128 };
+inline LinearRing linear_ring(int64_t M, int64_t N, int64_t K, bool vector_out)
+{
+    if (!vector_out || K % 64 != 0 || K < 256 || K > kToLdsLongestK || M < 64 || N % 64 != 0) return kRingNone;
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((N + bn - 1) / bn) * ((M + bm - 1) / bm); };
+    if (tiles(64, 64) <= 320) return kRing64;
+    if (N % 128 != 0 || K < 384) return kRingNone;
+    if (tiles(64, 128) <= 256) return kRing64x128;
+    return M >= 128 && tiles(128, 128) <= 256 ? kRing128 : kRingNone;
+}
+
 // Tile kernels for products that the few-row kernels do not take (linear.hip).
 enum LinearTiles {
     kTilesWide256,      // linear_wide_kernel, 256 x 256 tiles, one to a CU

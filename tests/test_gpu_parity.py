@@ -1259,6 +1259,24 @@ def test_linear_192_row_tiles(m, M, N, K, splits):
     test_linear_against_oracle(m, M, N, K, splits)
 
 
+@pytest.mark.parametrize("M,N,K,splits", [(641, 1280, 256, (640, 640)), (449, 2560, 1024, None), (704, 1856, 320, (600, 1256)),     # 64 x 64
+                                          (1025, 1536, 384, (768, 768)), (1087, 1536, 448, None), (512, 3072, 768, (1536, 1536)),   # 64 x 128
+                                          (2049, 1152, 384, None), (2175, 1152, 1536, (1144, 8)), (4096, 768, 832, None)])          # 128 x 128
+def test_linear_one_round_of_tiles(m, M, N, K, splits):
+    """Products whose tiles come in one round: full row blocks, a last one of one row and of all but one, as few slabs of k as the
+    ring of stages may meet and more; and ten launches that have to agree, since a missing wait would show as differences."""
+    test_linear_against_oracle(m, M, N, K, splits)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(78)
+    x = torch.randn(M, K, device=DEV, generator=g).bfloat16()
+    w = (torch.randn(N, K, device=DEV, generator=g) / K ** 0.5).bfloat16()
+    (first,) = m.mamba_linear_fwd(x, w)
+    for _ in range(9):
+        out = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=DEV)
+        m.mamba_linear_fwd(x, w, outs=[out])
+        assert torch.equal(out, first)
+
+
 @pytest.mark.parametrize("M,N,K,splits", [(1, 4096, 8, None), (17, 2050, 40, None), (257, 250, 1544, (48, 102, 100)),   # 16 x 16
                                           (19, 4090, 768, (2040, 2050)), (100, 800, 520, None),                          # 32 x 16
                                           (65, 4000, 512, (1500, 2500)), (255, 999, 1288, None), (2700, 80, 1536, (48, 16, 16)),   # 32 x 32

@@ -16,6 +16,7 @@ extern "C" int conv_step_fits(int64_t D, int64_t N) { return mamba::conv_step_fi
 extern "C" int xproj_fits(int64_t D, int64_t N, int64_t dt_rank) { return mamba::step_xproj_fits(D, N, dt_rank); }
 extern "C" int row_tiles(int64_t M, int64_t N) { return mamba::linear_few_row_tiles(M, N); }
 extern "C" int tiles(int64_t M, int64_t N, int64_t K, int wide) { return mamba::linear_tiles(M, N, K, wide); }
+extern "C" int ring(int64_t M, int64_t N, int64_t K, int vec) { return mamba::linear_ring(M, N, K, vec != 0); }
 extern "C" int wide192(int64_t M, int64_t N, int64_t K, int wide) { return mamba::linear_wide192(M, N, K, wide, mamba::linear_tiles(M, N, K, wide)); }
 extern "C" int xdt(int64_t M, int64_t d_inner, int64_t dt_rank, int64_t N, unsigned *groups)
 { return mamba::xdt_plan(M, d_inner, dt_rank, N, groups); }
@@ -37,6 +38,7 @@ def routes(tmp_path_factory):
     lib.row_tiles.argtypes = [i64, i64]
     lib.tiles.argtypes = [i64, i64, i64, i32]
     lib.wide192.argtypes = [i64, i64, i64, i32]
+    lib.ring.argtypes = [i64, i64, i64, i32]
     lib.xdt.argtypes = [i64, i64, i64, i64, ctypes.POINTER(ctypes.c_uint)]
     return lib
 
@@ -145,3 +147,16 @@ def test_192_row_tiles(routes):
     for s in [(16384, 3072, 768), (32768, 3072, 768), (8000, 4096, 1024), (1500, 3072, 768), (2000, 2560, 5120), (32768, 768, 1536), (191, 1 << 16, 128),
               (8000, 3000, 768), (8000, 3072, 760)]:
         assert not takes(*s), s
+
+
+def test_one_round_of_tiles(routes):
+    """The products that the parity test names for each tile, more than a round left alone, and never without the conditions."""
+    none, t64, t64x128, t128 = range(4)
+    for want, cases in ((t64, [(641, 1280, 256), (449, 2560, 1024), (704, 1856, 320), (64, 64, 1 << 28)]),
+                        (t64x128, [(1025, 1536, 384), (1087, 1536, 448), (512, 3072, 768)]),
+                        (t128, [(2049, 1152, 384), (2175, 1152, 1536), (4096, 768, 832)]),
+                        (none, [(2048, 3072, 768), (1500, 3072, 768), (2048, 2048, 256), (63, 64, 256), (641, 1288, 256), (1025, 1600, 384),
+                                (64, 64, 248), (64, 64, 264), (64, 64, (1 << 28) + 64), (1 << 20, 64, 256)])):
+        for s in cases:
+            assert routes.ring(*s, 1) == want, s
+            assert routes.ring(*s, 0) == none, s
