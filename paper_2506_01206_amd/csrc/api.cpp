@@ -487,7 +487,7 @@ int mamba_rmsnorm_fwd(const void *x, const float *w, void *y, int64_t M, int64_t
 namespace {
 
 struct BlockBuffers {
-    char *a, *b, *c, *d;        // four (rows, d_inner) bf16 buffers: x then dt | z | x_c | normed then y
+    char *a, *b, *c, *d;        // four (rows, d_inner) bf16 buffers: normed then dt | z | x_c | x then y
     char *dtl, *bm, *cm;        // (rows, dt_rank), (rows, d_state), (rows, d_state) bf16
     char *xpart;                // one token on up to 64 rows: (rows, d_inner / 16, dt_rank + 2 d_state) float32 partial sums
     char *scan_ws;
@@ -520,6 +520,22 @@ bool block_layout(const mamba_block_params_t *p, int64_t batch, int64_t L, void 
     bb->scan_ws_bytes = sws;
     bb->total = (size_t)off;
     return true;
+}
+
+// Whether the conv over time rides in in_proj: where there is a tile for it and nothing that one of the two launches would have
+// finished with is written by a workgroup while another reads it.  (Everything else takes the two calls, which have their own checks.)
+bool conv_rides_in_proj(const mamba_block_params_t *p, const void *hidden, const void *state_in, const void *state_out, const void *workspace,
+                        size_t ws_bytes, int64_t batch, int64_t rows)
+{
+    const int64_t Di = p->d_inner, dm = p->d_model;
+    int64_t st;
+    if (linear_conv_tiles(rows, Di, dm, p->d_conv) == kConvApart || batch > kMaxGridYZ || rows > kMaxGridYZ * 128) return false;
+    if (!size3(batch, Di, p->d_conv - 1, 2, &st) || !aligned16(state_in) || !aligned16(state_out) || overlap(state_in, st, state_out, st)) return false;
+    const void *read[5] = {p->in_proj_w, p->conv_w, p->conv_b, state_in, hidden};
+    const int64_t bytes[5] = {4 * Di * dm, 4 * Di * p->d_conv, 4 * Di, st, 2 * rows * dm};
+    for (int i = 0; i < 5; ++i)
+        if (overlap(read[i], bytes[i], workspace, (int64_t)ws_bytes) || overlap(read[i], bytes[i], state_out, st)) return false;
+    return !overlap(state_out, st, workspace, (int64_t)ws_bytes);
 }
 
 int block_params_ok(const mamba_block_params_t *p)
@@ -577,13 +593,25 @@ int mamba_block_fwd(const mamba_block_params_t *p, const void *hidden, void *hid
     const int64_t rows = batch * L, Di = p->d_inner, N = p->d_state, R = p->dt_rank;
     const mamba_dtype_t io = MAMBA_BF16;
     int rc;
-    // u = rmsnorm(hidden)                                   -> d
-    if ((rc = mamba_rmsnorm_fwd(hidden, p->norm_w, bb.d, rows, p->d_model, p->eps, io, hip_stream))) return rc;
-    // [x | z] = u W_in^T                                    -> a, b
-    if ((rc = mamba_linear_fwd(bb.d, p->in_proj_w, nullptr, nullptr, bb.a, Di, bb.b, Di, nullptr, 0, rows, p->d_model, io, hip_stream))) return rc;
-    // x_c = silu(conv1d(x))                                 -> c
-    if ((rc = mamba_conv1d_fwd(bb.a, p->conv_w, p->conv_b, conv_state_in, bb.c, conv_state_out, batch, L, Di, p->d_conv, 1, io, hip_stream))) return rc;
-    // [dt_low | B | C] = x_c W_x^T,  dt = dt_low W_dt^T       -> a (x is dead)
+    // u = rmsnorm(hidden)                                   -> a
+    if ((rc = mamba_rmsnorm_fwd(hidden, p->norm_w, bb.a, rows, p->d_model, p->eps, io, hip_stream))) return rc;
+    if (conv_rides_in_proj(p, hidden, conv_state_in, conv_state_out, workspace, bb.total, batch, rows)) {
+        // [x | z] = u W_in^T, x_c = silu(conv1d(x))            -> c, b (x is not stored)
+        LinearArgs in{bb.a, p->in_proj_w, nullptr, nullptr, {bb.c, bb.b, nullptr}, {Di, Di, 0}, rows, p->d_model};
+        in.conv_w = p->conv_w;
+        in.conv_b = p->conv_b;
+        in.conv_src = conv_state_in;
+        in.conv_dst = conv_state_out;
+        in.conv_k = p->d_conv;
+        in.conv_L = L;
+        if (hipError_t e = launch_linear_conv(in, static_cast<hipStream_t>(hip_stream))) return (int)e;
+    } else {
+        // [x | z] = u W_in^T                                   -> d, b
+        if ((rc = mamba_linear_fwd(bb.a, p->in_proj_w, nullptr, nullptr, bb.d, Di, bb.b, Di, nullptr, 0, rows, p->d_model, io, hip_stream))) return rc;
+        // x_c = silu(conv1d(x))                                -> c
+        if ((rc = mamba_conv1d_fwd(bb.d, p->conv_w, p->conv_b, conv_state_in, bb.c, conv_state_out, batch, L, Di, p->d_conv, 1, io, hip_stream))) return rc;
+    }
+    // [dt_low | B | C] = x_c W_x^T,  dt = dt_low W_dt^T       -> a (u is dead)
     unsigned groups;
     if (xdt_plan(rows, Di, R, N, &groups) > 0) {
         const int64_t xw = (R + 2 * N) * Di * 2, low = rows * R * 2, bc = rows * N * 2;   // (sizes that block_layout has checked)
@@ -596,7 +624,7 @@ int mamba_block_fwd(const mamba_block_params_t *p, const void *hidden, void *hid
         if ((rc = mamba_linear_fwd(bb.c, p->x_proj_w, nullptr, nullptr, bb.dtl, R, bb.bm, N, bb.cm, N, rows, Di, io, hip_stream))) return rc;
         if ((rc = mamba_linear_fwd(bb.dtl, p->dt_proj_w, nullptr, nullptr, bb.a, Di, nullptr, 0, nullptr, 0, rows, R, io, hip_stream))) return rc;
     }
-    // y = scan(...) gated by silu(z)                        -> d (u is dead)
+    // y = scan(...) gated by silu(z)                        -> d (x is dead)
     if ((rc = mamba_scan_fwd(bb.c, bb.a, p->A, bb.bm, bb.cm, p->Dskip, bb.b, p->dt_bias, h0, bb.d, h_final,
                              bb.scan_ws_bytes ? bb.scan_ws : nullptr, bb.scan_ws_bytes, batch, L, Di, N, 0, 1, io, hip_stream)))
         return rc;

@@ -179,6 +179,9 @@ struct LinearArgs {
     const int32_t *conv_parent = nullptr;
     int64_t conv_n_in = 0;
     int conv_k = 0;
+    // (launch_linear_conv: the conv over time instead, rows are sequences of conv_L; conv_src the inputs carried in or null, conv_dst those
+    // carried on or null, (sequences, width[0], conv_k - 1) and not the same buffer)
+    int64_t conv_L = 0;
     // with xproj_w (xproj_n, width[0]) bf16 every workgroup also multiplies its 16 finished columns of the first
     // output tensor (as stored, i.e. after the conv step) into the next projection and leaves the partial sums in
     // xproj_part[(row, column block, j)] (float32, (M, width[0] / 16, xproj_n)); whoever consumes them adds the
@@ -188,6 +191,8 @@ struct LinearArgs {
     int xproj_n = 0;
 };
 hipError_t launch_linear(const LinearArgs &a, hipStream_t stream);
+// out[0] = silu(conv1d(x w[:D]^T)), out[1] = x w[D:]^T, D = width[0] = width[1], where linear_conv_tiles (routes.h) has a tile for it
+hipError_t launch_linear_conv(const LinearArgs &a, hipStream_t stream);
 hipError_t launch_draft_in(const LinearArgs &a, hipStream_t stream);   // what launch_linear does with norm_w
 
 // x_proj and dt_proj of a context as one kernel: [dtl | bm | cm] = xc wx^T, dt = dtl wdt^T, all bf16.

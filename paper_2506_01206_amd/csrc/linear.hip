@@ -23,6 +23,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "conv_lane.h"
 #include "device_math.h"
 #include "launch.h"
 #include "routes.h"
@@ -216,6 +217,81 @@ linear_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w, const 
 
 
 // ---------------------------------------------------------------------------------------------------
+// The way into a block on a context: [x | z] = u W_in^T, x_c = silu(conv1d(x)).  The tile kernels below (CONV) have a finished tile of x
+// in LDS, rounded as the stored tensor would be, and form x_c from it where they would store x, which never goes to memory.  What that
+// takes is vector work of the epilogue (45 cycles an output of a lane), under another workgroup's products where two share a CU, and
+// three rows more in a tile; what it saves is a launch that reads and writes all of x.  us, in_proj and conv / one launch, 24 blocks in
+// turn: 333 x 1536 11.6 / 8.7, 2048 20.5 / 18.5, 8000 53.9 / 47.3, 32768 216 / 187 (linear_conv_tiles has the tiles).  Formed on the way into
+// the x projection instead (xdt.hip), with no other workgroup to hide it: 8000 rows 28.3 -> 23.0, 32768 101 -> 92, but 333 11.1 -> 14.2.
+struct ConvTail {
+    const float *w, *bias;           // (width[0], kConvTaps), (width[0]) or null
+    const bf16_t *state_in;          // (sequences, width[0], kConvTaps - 1) or null: zeros
+    bf16_t *state_out;               // the same or null
+    uint32_t L;                      // rows of a sequence
+    int z_blocks;                    // row blocks of z (linear_wide_kernel)
+};
+constexpr int kConvHalo = kConvTaps - 1;
+
+// Rows of row block r: m0 + dead .. m0 + BM - 1, of BM that are multiplied.  The last block moves back to end at M; with the conv the
+// first rows of every block but the first are there for the windows of the others.
+template <int BM, bool CONV> __device__ __forceinline__ void rows_of_block(int r, int64_t M, int64_t *m0, int *dead)
+{
+    const int64_t first = !CONV ? (int64_t)r * BM : r == 0 ? 0 : BM + (int64_t)(r - 1) * (BM - kConvHalo);
+    const int64_t from = CONV && r > 0 ? first - kConvHalo : first;
+    *m0 = from + BM <= M ? from : M - BM;
+    *dead = (int)(first - *m0);
+}
+
+// x_c of a tile of x: rows kRow bytes apart in LDS, channels n0 .. n0 + BN - 1.  A thread takes eight adjacent channels of consecutive rows.
+template <int BM, int BN, int THREADS, int kRow>
+__device__ __forceinline__ void conv_rows(const unsigned char *tile, int64_t m0, int dead, int64_t n0, bf16_t *xc, int64_t D, const ConvTail &conv)
+{
+    constexpr int kCpr = BN / 8, kPer = BM * kCpr / THREADS, H = kConvHalo;
+    static_assert(BM * kCpr % THREADS == 0 && THREADS % kCpr == 0, "whole runs of rows");
+    const int cc = (int)threadIdx.x % kCpr, row0 = (int)threadIdx.x / kCpr * kPer;
+    const int64_t d0 = n0 + cc * 8;
+    ConvLane<bf16_t, 8, kConvTaps, true> c;
+    ld_block<8 * kConvTaps>(conv.w + d0 * kConvTaps, &c.wr[0][0]);
+    if (conv.bias) ld_block<8>(conv.bias + d0, c.br);
+    else
+#pragma unroll
+        for (int i = 0; i < 8; ++i) c.br[i] = 0.0f;
+    auto raw = [&](int row) __attribute__((always_inline)) { return *reinterpret_cast<const uint4 *>(tile + row * kRow + cc * 16); };
+    bf16_t *o = xc + (m0 + row0) * D + d0;
+    // A tile that lies inside a sequence needs no looking at t: none of its rows has a window that reaches back before one, none is the last.
+    const uint32_t t_first = (uint32_t)(m0 + dead) % conv.L;
+    if (t_first >= (uint32_t)H && (uint64_t)t_first + (uint32_t)(BM - dead) < conv.L) {
+#pragma unroll
+        for (int i = 0; i < H; ++i) c.set_window(i, 0, raw(row0 - H + i < 0 ? 0 : row0 - H + i));   // (rows before the tile: for dead ones)
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const uint4 y = c.emit(raw(row0 + i));
+            if (row0 + i >= dead) *reinterpret_cast<uint4 *>(o + i * D) = y;
+        }
+    } else {
+        const uint32_t m = (uint32_t)(m0 + row0);
+        uint32_t q = m / conv.L, t = m - q * conv.L;
+        if (t < (uint32_t)H) c.load_carried(conv.state_in, nullptr, q, 0, D, d0);
+#pragma unroll
+        for (int i = 0; i < H; ++i) c.set_window(i, (int64_t)t - H + i, raw(row0 - H + i < 0 ? 0 : row0 - H + i));
+#pragma unroll 1
+        for (int i = 0; i < kPer; ++i) {
+            if (i > 0 && t == 0) {
+                c.load_carried(conv.state_in, nullptr, q, 0, D, d0);
+#pragma unroll
+                for (int k = 0; k < H; ++k) c.set_window(k, k - H, uint4{});
+            }
+            const uint4 y = c.emit(raw(row0 + i));
+            if (row0 + i >= dead) {
+                *reinterpret_cast<uint4 *>(o + i * D) = y;
+                if (conv.state_out && t == conv.L - 1) c.store_window(conv.state_out, q, D, d0);
+            }
+            if (++t == conv.L) t = 0, ++q;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------
 // Many rows (the projections of a long context).  A 128 x 128 tile asks the L1 for 512 bytes per k and
 // multiplies 8 cycles per k on every SIMD, so the cache, which delivers 64 bytes a cycle, can feed the
 // matrix cores half the time at best.  This kernel takes 256 x 256 tiles, one workgroup per CU and one
@@ -250,10 +326,10 @@ __device__ __forceinline__ void load_to_lds16(const char *base, uint32_t lane_of
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(lane_off), "s"(base) : "memory");
 }
 
-template <int BM, int BN>
+template <int BM, int BN, bool CONV = false>
 __global__ void __launch_bounds__(256)
 linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ bias, const bf16_t *residual,
-                   OutSplit out, int64_t M, int64_t N, int64_t K, int tiles_n, int n_tiles)
+                   OutSplit out, int64_t M, int64_t N, int64_t K, int tiles_n, int n_tiles, ConvTail conv)
 {
     constexpr int MT = BM / 64, NT = BN / 64;                     // 32 x 32 MFMA tiles per wavefront along m and n
     constexpr int kRows = BM + BN;
@@ -268,9 +344,16 @@ linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
     const int per_xcd = (n_tiles + 7) / 8;
     const int tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
     if (tile >= n_tiles) return;
-    const int64_t m_first = (int64_t)(tile / tiles_n) * BM, n0 = (int64_t)(tile % tiles_n) * BN;
-    const int64_t m0 = m_first + BM <= M ? m_first : M - BM;
-    const int dead = (int)(m_first - m0);                         // leading rows that belong to the row block before
+    int row_block = tile / tiles_n, column = tile % tiles_n;
+    if constexpr (CONV) {                                         // the row blocks that only x has, whose own overlap, come last
+        const int both = conv.z_blocks * tiles_n, x_columns = (int)(out.width[0] / BN);
+        if (tile >= both) row_block = conv.z_blocks + (tile - both) / x_columns, column = (tile - both) % x_columns;
+    }
+    const int64_t n0 = (int64_t)column * BN;
+    int64_t m0;
+    int dead;                                                     // leading rows that belong to the row block before
+    if (CONV && n0 < out.width[0]) rows_of_block<BM, true>(row_block, M, &m0, &dead);
+    else rows_of_block<BM, false>(row_block, M, &m0, &dead);
 
     // Loads: wavefront v takes the row groups g = 4 j + v (rows 8 g .. 8 g + 7 of the stage; x rows first, then w);
     // lane l lands in row 8 g + l / 8, slot l % 8, and therefore fetches slot (l % 8) ^ ((4 (g & 1) + l / 16) & 7)
@@ -428,6 +511,12 @@ linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
             __builtin_amdgcn_sched_barrier(0);                    // one group at a time: the accumulators stay where they are until used
         }
     lds_barrier_linear();
+    if constexpr (CONV) {
+        if (n0 < out.width[0]) {                                  // width[0] is a multiple of BN
+            conv_rows<BM, BN, 256, kOutRow>(lds, m0, dead, n0, out.ptr[0], out.width[0], conv);
+            return;
+        }
+    }
     auto store_chunk = [&](int i, int row, int cc) __attribute__((always_inline)) {
         uint4 v = *reinterpret_cast<const uint4 *>(lds + row * kOutRow + cc * 16);
         int64_t col;
@@ -479,10 +568,10 @@ __device__ __forceinline__ void wave_sync()
 // Requires M >= BM, N % BN == 0, K % 64 == 0 and output widths that are multiples of 8; the last row block moves back as above.
 // grid: 8 * ceil(tiles / 8) workgroups, each XCD a contiguous range of tiles in groups of group_n columns: a walk over all
 // columns would bring all of w into every XCD's L2.
-template <int BM, int BN, int WM, int WN, int STAGES, int PER_CU>
+template <int BM, int BN, int WM, int WN, int STAGES, int PER_CU, bool CONV = false>
 __global__ void __launch_bounds__(64 * WM * WN, WM * WN * PER_CU / 4)
 linear_ring_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ bias, const bf16_t *residual,
-                   int64_t M, int64_t K, int tiles_m, int tiles_n, int group_n, OutSplit out)
+                   int64_t M, int64_t K, int tiles_m, int tiles_n, int group_n, OutSplit out, ConvTail conv)
 {
     constexpr int NW = WM * WN;
     constexpr int MT = BM / WM / 32, NT = BN / WN / 32;           // 32 x 32 MFMA tiles per wavefront along m and n
@@ -500,9 +589,10 @@ linear_ring_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
     if ((int)(blockIdx.x >> 3) >= per_xcd || tile >= n_tiles) return;
     const int group = tile / (group_n * tiles_m), in_group = tile - group * group_n * tiles_m;
     const int width = min(group_n, tiles_n - group * group_n), row_block = in_group / width;
-    const int64_t m_first = (int64_t)row_block * BM, n0 = (int64_t)(group * group_n + in_group - row_block * width) * BN;
-    const int64_t m0 = m_first + BM <= M ? m_first : M - BM;
-    const int dead = (int)(m_first - m0);                         // leading rows that belong to the row block before
+    const int64_t n0 = (int64_t)(group * group_n + in_group - row_block * width) * BN;
+    int64_t m0;
+    int dead;                                                     // leading rows that belong to the row block before
+    rows_of_block<BM, CONV>(row_block, M, &m0, &dead);
 
     const uint32_t lane_off = (uint32_t)((lane >> 3) * K * 2 + (((lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7)) << 4));
     const char *xrow = reinterpret_cast<const char *>(x + (m0 + 8 * wave) * K);   // of the next slab to be requested
@@ -628,6 +718,33 @@ linear_ring_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
         multiply(f1);
     }
 
+    if constexpr (CONV) {
+        // the whole tile, since windows reach into the rows of other wavefronts; every read of the stages is behind the last barrier
+        constexpr int kOutRow = BN * 2 + 16, kCpr = BN / 8;
+        static_assert(BM * kOutRow <= STAGES * kStage, "the stages hold the output tile");
+#pragma unroll
+        for (int a = 0; a < MT; ++a)
+#pragma unroll
+            for (int b = 0; b < NT; ++b)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    *reinterpret_cast<uint2 *>(lds + (wm * (BM / WM) + a * 32 + (lane & 31)) * kOutRow + (wn * (BN / WN) + b * 32 + 8 * g + 4 * (lane >> 5)) * 2) =
+                        make_uint2(f32x2_to_bf16x2(acc[a][b][4 * g + 0], acc[a][b][4 * g + 1]), f32x2_to_bf16x2(acc[a][b][4 * g + 2], acc[a][b][4 * g + 3]));
+        lds_barrier_linear();
+        if (n0 < out.width[0]) {                                  // width[0] is a multiple of BN
+            conv_rows<BM, BN, 64 * NW, kOutRow>(lds, m0, dead, n0, out.ptr[0], out.width[0], conv);
+        } else {
+#pragma unroll
+            for (int i = 0; i < BM * kCpr / (64 * NW); ++i) {
+                const int row = (tid + i * 64 * NW) / kCpr, cc = (tid + i * 64 * NW) % kCpr;
+                int64_t col;
+                const int sp = locate(out, n0 + cc * 8, &col);
+                if (row >= dead)
+                    *reinterpret_cast<uint4 *>(out.ptr[sp] + (m0 + row) * out.width[sp] + col) = *reinterpret_cast<const uint4 *>(lds + row * kOutRow + cc * 16);
+            }
+        }
+        return;
+    }
     // acc[a][b][4 g + j] is C[m = 32 a + lane % 32][n = 32 b + 8 g + 4 (lane / 32) + j] of the wavefront's part.  Rows of a block lie
     // 64 bytes apart, their four 16-byte slots swizzled by the row pair.
     unsigned char *patch = lds + STAGES * kStage + wave * kPatch;
@@ -855,17 +972,28 @@ hipError_t launch_few(const bf16_t *x, const bf16_t *w, const float *bias, const
     return hipGetLastError();
 }
 
-template <int BM, int BN, int WM, int WN, int STAGES, int PER_CU>
+template <int BM, int BN, int WM, int WN, int STAGES, int PER_CU, bool CONV = false>
 hipError_t launch_ring(const bf16_t *x, const bf16_t *w, const float *bias, const bf16_t *res, const OutSplit &o, int64_t M, int64_t N, int64_t K,
-                       hipStream_t stream)
+                       hipStream_t stream, const ConvTail &conv = ConvTail{})
 {
-    const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)(N / BN);
+    const int tiles_m = (int)row_blocks(M, BM, CONV), tiles_n = (int)(N / BN);
     // columns of a group: as many as bring about 2 MB of w, half of an XCD's L2, in groups of equal width
     const int64_t most = std::max<int64_t>(1, ((int64_t)9 << 18) / (BN * 2 * K));
     const int64_t groups = (tiles_n + most - 1) / most;
     const unsigned per_xcd = (unsigned)((tiles_m * tiles_n + 7) / 8);
-    linear_ring_kernel<BM, BN, WM, WN, STAGES, PER_CU><<<8 * per_xcd, 64 * WM * WN, 0, stream>>>(
-        x, w, bias, res, M, K, tiles_m, tiles_n, (int)((tiles_n + groups - 1) / groups), o);
+    linear_ring_kernel<BM, BN, WM, WN, STAGES, PER_CU, CONV><<<8 * per_xcd, 64 * WM * WN, 0, stream>>>(
+        x, w, bias, res, M, K, tiles_m, tiles_n, (int)((tiles_n + groups - 1) / groups), o, conv);
+    return hipGetLastError();
+}
+
+template <int BM, int BN, bool CONV = false>
+hipError_t launch_wide(const bf16_t *x, const bf16_t *w, const float *bias, const bf16_t *res, const OutSplit &o, int64_t M, int64_t N, int64_t K,
+                       hipStream_t stream, ConvTail conv = ConvTail{})
+{
+    const int64_t tiles_n = N / BN, z_blocks = row_blocks(M, BM, false);
+    const int64_t n_tiles = z_blocks * tiles_n + (CONV ? (row_blocks(M, BM, true) - z_blocks) * (o.width[0] / BN) : 0);
+    conv.z_blocks = (int)z_blocks;
+    linear_wide_kernel<BM, BN, CONV><<<(unsigned)(8 * ((n_tiles + 7) / 8)), 256, 0, stream>>>(x, w, bias, res, o, M, N, K, (int)tiles_n, (int)n_tiles, conv);
     return hipGetLastError();
 }
 
@@ -922,19 +1050,11 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     }
     const bool wide = vec && N % 128 == 0 && a.M >= 128 && a.K % (2 * kWideBK) == 0 && a.K <= kToLdsLongestK;
     auto grid = [&](int bm, int bn) { return dim3((unsigned)((N + bn - 1) / bn), (unsigned)((a.M + bm - 1) / bm)); };
-    auto in_turn = [&](int64_t t) { return (unsigned)(8 * ((t + 7) / 8)); };
     const LinearTiles kind = linear_tiles(a.M, N, a.K, wide);
-    if (linear_wide192(a.M, N, a.K, wide, kind)) {
-        linear_wide_kernel<192, 128><<<in_turn(tiles(192, 128)), 256, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, (int)(N / 128), (int)tiles(192, 128));
-        return hipGetLastError();
-    }
+    if (linear_wide192(a.M, N, a.K, wide, kind)) return launch_wide<192, 128>(x, w, a.bias, res, o, a.M, N, a.K, stream);
     switch (kind) {
-    case kTilesWide256:
-        linear_wide_kernel<256, 256><<<in_turn(tiles(256, 256)), 256, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, (int)(N / 256), (int)tiles(256, 256));
-        break;
-    case kTilesWide128:
-        linear_wide_kernel<128, 128><<<in_turn(tiles(128, 128)), 256, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, (int)(N / 128), (int)tiles(128, 128));
-        break;
+    case kTilesWide256: return launch_wide<256, 256>(x, w, a.bias, res, o, a.M, N, a.K, stream);
+    case kTilesWide128: return launch_wide<128, 128>(x, w, a.bias, res, o, a.M, N, a.K, stream);
     case kTiles128: linear_kernel<128, 128, 64><<<grid(128, 128), kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec); break;
     case kTiles64x128: linear_kernel<64, 128, 64><<<grid(64, 128), kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec); break;
     case kTiles64Deep: linear_kernel<64, 64, 256><<<grid(64, 64), kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec); break;
@@ -946,6 +1066,25 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
         break;
     }
     return hipGetLastError();
+}
+
+hipError_t launch_linear_conv(const LinearArgs &a, hipStream_t stream)
+{
+    const OutSplit o{{static_cast<bf16_t *>(a.out[0]), static_cast<bf16_t *>(a.out[1]), nullptr}, {a.width[0], a.width[1], 0}};
+    const bf16_t *x = static_cast<const bf16_t *>(a.x), *w = static_cast<const bf16_t *>(a.w);
+    const ConvTail conv{a.conv_w, a.conv_b, static_cast<const bf16_t *>(a.conv_src), static_cast<bf16_t *>(a.conv_dst), (uint32_t)a.conv_L, 0};
+    const int64_t N = a.width[0] + a.width[1];
+#define MAMBA_CONV(HOW, ...) return launch_##HOW<__VA_ARGS__, true>(x, w, nullptr, nullptr, o, a.M, N, a.K, stream, conv)
+    switch (linear_conv_tiles(a.M, a.width[0], a.K, a.conv_k)) {
+    case kConvRing64: MAMBA_CONV(ring, 64, 64, 2, 2, 4, 2);
+    case kConvRing64x128: MAMBA_CONV(ring, 64, 128, 2, 4, 6, 1);
+    case kConvRing128: MAMBA_CONV(ring, 128, 128, 2, 4, 4, 1);
+    case kConvWide128: MAMBA_CONV(wide, 128, 128);
+    case kConvWide192: MAMBA_CONV(wide, 192, 128);
+    case kConvWide256: MAMBA_CONV(wide, 256, 256);
+    default: return hipErrorInvalidValue;
+    }
+#undef MAMBA_CONV
 }
 
 }  // namespace mamba

@@ -63,6 +63,9 @@ inline int linear_few_row_tiles(int64_t M, int64_t N)
     return M <= 32 || columns * ((M + 31) / 32) <= 256 ? 2 : 4;
 }
 
+// Taps of the conv that a tile kernel forms from its finished tile.
+constexpr int kConvTaps = 4;
+
 // linear_wide_kernel and linear_ring_kernel place a lane's 16 bytes within eight rows of k in 32 bits.
 constexpr int64_t kToLdsLongestK = (int64_t)1 << 28;
 
@@ -85,6 +88,55 @@ inline LinearRing linear_ring(int64_t M, int64_t N, int64_t K, bool vector_out)
     if (N % 128 != 0 || K < 384) return kRingNone;
     if (tiles(64, 128) <= 256) return kRing64x128;
     return M >= 128 && tiles(128, 128) <= 256 ? kRing128 : kRingNone;
+}
+
+// The way into a block on a context (x | z = u W_in^T, then the conv over time on x) in one launch: the tile whose product takes least,
+// by rounds of workgroups over the chip; or the product and the conv apart, where the rows that a tile of x shares with the one before
+// it cost more than the conv's launch (512 rows of 4096 channels: 320 128 x 128 tiles instead of 256), on rows that the few-row
+// kernels take, and on what the tiles cannot.  Fitted to 117 products of seven models, 64 to 32768 rows: the choice costs 1.0 % more
+// than the best of them on average, and the launch 13.7 % less than the two.  us, product + conv / the launch on 64 x 64 / 64 x 128 / 128 x 128
+// ring, 128 x 128 / 192 x 128 / 256 x 256 wide tiles (u, K):
+//     100 x 1536,  768   8.6 /  7.1*/  9.2 /   -  /   -  /   -  /   -       2048 x 1536,  768  20.5 / 28.6 / 33.0 / 22.1 / 18.5*/ 22.6 / 32.6
+//     333 x 1536,  768  11.6 /  8.7*/  9.6 / 11.2 / 13.8 / 15.7 / 30.8      8000 x 1536,  768  53.9 / 86.1 /100.5 / 64.2 / 51.0 / 47.3*/ 61.9
+//     600 x 1536,  768  12.7 / 10.2 / 10.1*/ 11.7 / 14.3 / 16.8 / 31.7     32768 x 1536,  768   216 /  332 /  387 /  245 /  215 /  187*/  194
+//    1000 x 1536,  768  15.5 / 16.2 / 17.7 / 12.2*/ 15.2 / 17.7 / 31.8      4000 x 4096, 2048   144 /  227 /  239 /  167 /  165 /  141 /  126*
+//     200 x 1024,  512   7.5 /  6.3*/  8.3 /  9.5 / 10.8 / 12.8 /   -       2048 x 4096, 2048  73.4*/  127 /  131 /  102 /  101 / 85.6 /  105
+enum ConvTiles { kConvApart, kConvRing64, kConvRing64x128, kConvRing128, kConvWide128, kConvWide192, kConvWide256 };
+inline int64_t row_blocks(int64_t M, int64_t BM, bool conv)      // with the conv all but the first have kConvTaps - 1 rows that are another's
+{
+    return !conv || M <= BM ? (M + BM - 1) / BM : 1 + (M - BM + BM - kConvTaps) / (BM - kConvTaps + 1);
+}
+inline ConvTiles linear_conv_tiles(int64_t M, int64_t D, int64_t K, int64_t taps)
+{
+    if (taps != kConvTaps || M < 64 || M > (int64_t)1 << 23 || D % 64 != 0 || D > (int64_t)1 << 20 || K % 64 != 0 || K < 256 || K > kToLdsLongestK)
+        return kConvApart;
+    // us: a launch, a round of workgroups, and where two share a CU a round that gives no CU a second one
+    struct Tile { ConvTiles kind; int64_t bm, bn, per_round; double launch, round, round_k, half, half_k; };
+    const Tile all[6] = {{kConvRing64, 64, 64, 512, 2.6, 1.5, .0076, 1.1, .0051},    {kConvRing64x128, 64, 128, 256, 2.5, 2.5, .0067, 0, 0},
+                         {kConvRing128, 128, 128, 256, 2.4, 3.4, .0085, 0, 0},       {kConvWide128, 128, 128, 512, 3.9, 2.0, .0172, 1.6, .0118},
+                         {kConvWide192, 192, 128, 512, 4.5, 4.6, .0205, 2.4, .0139}, {kConvWide256, 256, 256, 256, 6.6, 9.1, .0219, 0, 0}};
+    const double none = 1e30;
+    auto us = [&](const Tile &t, bool conv) {
+        const bool ring = t.kind <= kConvRing128;
+        if (M < t.bm) return none;
+        // (x and z have row blocks of their own in the wide kernels, x's in the others)
+        const int64_t z = row_blocks(M, t.bm, false), x = row_blocks(M, t.bm, conv);
+        const int64_t tiles = ring ? x * ((2 * D + t.bn - 1) / t.bn) : z * ((2 * D + t.bn - 1) / t.bn) + (x - z) * ((D + t.bn - 1) / t.bn);
+        if (ring && tiles > t.per_round) return none;              // one round
+        const int64_t full = tiles / t.per_round, rest = tiles % t.per_round;
+        const bool half = t.half > 0 && rest > 0 && rest <= t.per_round / 2;
+        return t.launch + (double)(full + (rest > 0 && !half ? 1 : 0)) * (t.round + t.round_k * (double)K) + (half ? t.half + t.half_k * (double)K : 0.0);
+    };
+    double best = none, apart = none;
+    ConvTiles kind = kConvApart;
+    for (const Tile &t : all) {
+        const double a = us(t, false) + 2.5 + 7.5e-7 * (double)M * (double)D;
+        if (a < apart) apart = a;
+        if (D % t.bn != 0 || (t.kind > kConvRing128 && K % 128 != 0)) continue;
+        const double c = us(t, true);
+        if (c < best) best = c, kind = t.kind;
+    }
+    return best <= apart ? kind : kConvApart;
 }
 
 // Tile kernels for products that the few-row kernels do not take (linear.hip).

@@ -1456,6 +1456,39 @@ def test_block_x_and_dt_projection_in_one_pass(m, B, L, D, R):
     check_block_stages(m, blk, w64, hid)
 
 
+@pytest.mark.parametrize("B,L,dm,D", [(1, 64, 256, 64), (1, 65, 256, 128), (2, 63, 320, 64), (3, 67, 256, 192), (64, 1, 256, 64), (50, 2, 256, 128),
+                                      (30, 3, 256, 64), (5, 125, 256, 320),                             # 64 x 64 tiles
+                                      (1, 100, 2560, 5120),                                             # 64 x 128
+                                      (2, 490, 256, 1024), (1, 1003, 256, 1024), (500, 4, 256, 512),    # 128 x 128, one round
+                                      (1, 1254, 256, 1536), (4, 316, 256, 1536),                        # 128 x 128, two to a CU
+                                      (1, 1281, 384, 1536), (2, 670, 384, 1536), (3, 447, 384, 1536),   # 192 x 128
+                                      (1, 4031, 384, 2048), (4, 1012, 384, 2048)])                      # 256 x 256
+def test_block_conv_in_the_way_in(m, B, L, dm, D):
+    """The conv formed from finished tiles of in_proj: full and moved row blocks, sequences that start and end inside a tile, at its first
+    rows and at its last, and that are shorter than the window; with inputs carried in and without, stage by stage.  What it replaces,
+    in_proj and the conv as calls of their own, rounds in the same places: the same values, but for a product that gets its sums in
+    another order there."""
+    say(B=B, L=L, dm=dm, D=D)
+    rng = np.random.default_rng(B * 1000 + L + D + dm)
+    w, w64, blk = make_block(m, rng, dm, D, 16, 4, 32)
+    hid = synth.to_io(rng.standard_normal((B, L, dm)).astype(np.float32), synth.BF16)
+    conv_in = synth.to_io(rng.standard_normal((B, D, 3)).astype(np.float32), synth.BF16)
+    for carried in (None, conv_in) if B * L < 1100 else (conv_in,):
+        check_block_stages(m, blk, w64, hid, conv_in=carried)
+    ws = torch.empty(m.mamba_block_workspace_bytes(blk, B, L), dtype=torch.uint8, device=DEV)
+    _, state, _ = m.mamba_block_fwd(blk, to_dev(hid), conv_state_in=to_dev(conv_in), workspace=ws)
+    st = m.mamba_block_workspace_layout(blk, B, L, ws)
+    u = m.mamba_rmsnorm_fwd(to_dev(hid).view(B * L, dm), blk.w["norm_w"], eps=1e-5)
+    x, z = m.mamba_linear_fwd(u, blk.w["in_proj_w"], splits=(D, D))
+    xc, state1 = m.mamba_conv1d_fwd(x.view(B, L, D), blk.w["conv_w"], blk.w.get("conv_b"), conv_state_in=to_dev(conv_in))
+    for got, ref in ((st["z"], z), (st["x_c"], xc.view(B * L, D)), (state, state1)):
+        assert (got != ref).float().mean().item() < 2e-3          # rounding flips of sums in another order
+    # in place on the carried inputs: the two calls, to the bit
+    s = to_dev(conv_in).clone()
+    m.mamba_block_fwd(blk, to_dev(hid), conv_state_in=s, conv_state_out=s, workspace=ws)
+    assert torch.equal(s, state1) and torch.equal(m.mamba_block_workspace_layout(blk, B, L, ws)["x_c"], xc.view(B * L, D))
+
+
 @pytest.mark.parametrize("tree", [(3, 2, 1), (1, 1), (4,), (33, 2, 1), (66, 2)])
 def test_block_decode_steps_against_oracle(m, tree):
     """Tree drafting through whole blocks: at every draft position each branch continues from its

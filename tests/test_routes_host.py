@@ -17,6 +17,8 @@ extern "C" int xproj_fits(int64_t D, int64_t N, int64_t dt_rank) { return mamba:
 extern "C" int row_tiles(int64_t M, int64_t N) { return mamba::linear_few_row_tiles(M, N); }
 extern "C" int tiles(int64_t M, int64_t N, int64_t K, int wide) { return mamba::linear_tiles(M, N, K, wide); }
 extern "C" int ring(int64_t M, int64_t N, int64_t K, int vec) { return mamba::linear_ring(M, N, K, vec != 0); }
+extern "C" int conv_tiles(int64_t M, int64_t D, int64_t K, int64_t taps) { return mamba::linear_conv_tiles(M, D, K, taps); }
+extern "C" int64_t row_blocks(int64_t M, int64_t BM, int conv) { return mamba::row_blocks(M, BM, conv != 0); }
 extern "C" int wide192(int64_t M, int64_t N, int64_t K, int wide) { return mamba::linear_wide192(M, N, K, wide, mamba::linear_tiles(M, N, K, wide)); }
 extern "C" int xdt(int64_t M, int64_t d_inner, int64_t dt_rank, int64_t N, unsigned *groups)
 { return mamba::xdt_plan(M, d_inner, dt_rank, N, groups); }
@@ -39,6 +41,8 @@ def routes(tmp_path_factory):
     lib.tiles.argtypes = [i64, i64, i64, i32]
     lib.wide192.argtypes = [i64, i64, i64, i32]
     lib.ring.argtypes = [i64, i64, i64, i32]
+    lib.conv_tiles.argtypes = [i64] * 4
+    lib.row_blocks.argtypes, lib.row_blocks.restype = [i64, i64, i32], i64
     lib.xdt.argtypes = [i64, i64, i64, i64, ctypes.POINTER(ctypes.c_uint)]
     return lib
 
@@ -160,3 +164,38 @@ def test_one_round_of_tiles(routes):
         for s in cases:
             assert routes.ring(*s, 1) == want, s
             assert routes.ring(*s, 0) == none, s
+
+
+def test_conv_in_the_way_into_a_block(routes):
+    """The tile that the parity test names for each product, the product and the conv apart where the rows that tiles share cost more
+    than a launch, and never a tile that the shape does not divide into.  Every row has one block that stores it, and a tile of x the
+    three rows before its own."""
+    apart, r64, r64x128, r128, w128, w192, w256 = range(7)
+    for kind, shapes in {r64: [(64, 64, 256), (189, 128, 256), (333, 1536, 768), (600, 512, 256), (64, 1 << 20, 256)],
+                         r64x128: [(200, 4096, 2048), (100, 5120, 2560)], r128: [(1000, 1024, 256), (2003, 512, 256), (1000, 1536, 768)],
+                         w128: [(1254, 1536, 256), (1264, 1536, 256), (2048, 1536, 768)],
+                         w192: [(1281, 1536, 384), (8000, 1536, 768), (32768, 1536, 768)],
+                         w256: [(4031, 2048, 384), (4048, 2048, 384), (4000, 4096, 2048)],
+                         apart: [(63, 1536, 768), (333, 1536, 192), (333, 1536, 800), (333, 1500, 768), (512, 4096, 2048), (2048, 4096, 2048),
+                                 (1 << 24, 128, 256), (333, (1 << 20) + 64, 768)]}.items():
+        for s in shapes:
+            got = routes.conv_tiles(*s, 4)
+            assert got == kind or (kind == r64 and s[1] == 1 << 20 and got in (apart, r64)), (s, got)
+            assert routes.conv_tiles(*s, 3) == apart, s
+    size = {r64: (64, 64), r64x128: (64, 128), r128: (128, 128), w128: (128, 128), w192: (192, 128), w256: (256, 256)}
+    for D in (64, 128, 192, 320, 512, 1088, 1536, 4096):
+        for K in (256, 320, 768, 2048):
+            for M in (64, 65, 127, 128, 191, 192, 255, 256, 500, 1000, 3000, 20000, 1 << 23):
+                kind = routes.conv_tiles(M, D, K, 4)
+                if kind != apart:
+                    bm, bn = size[kind]
+                    assert M >= bm and D % bn == 0 and (kind < w128 or K % 128 == 0), (M, D, K)
+    for bm in (64, 128, 192, 256):
+        for M in (bm, bm + 1, bm + 3, 2 * bm - 4, 2 * bm - 3, 2 * bm - 2, 10 * bm, 10 * bm - 27, 10 * bm - 26):
+            stored = 0
+            for r in range(routes.row_blocks(M, bm, 1)):
+                first = 0 if r == 0 else bm + (r - 1) * (bm - 3)
+                m0 = min(first - 3 if r else 0, M - bm)
+                assert first == stored and m0 >= 0 and (r == 0 or first - m0 >= 3), (M, bm, r)
+                stored = m0 + bm
+            assert stored == M and routes.row_blocks(M, bm, 0) == -(-M // bm)
