@@ -35,6 +35,11 @@ struct ScanArgs {
     int N, io, dt_softplus;
     int64_t chunk_len, n_chunks;
     int single_pass = 0;  // kScanDirect / kScanLanes: one of the single-pass kernels (n_chunks == 1, no workspace)
+    // with dt_w (D, dt_rank) bf16 the kernel also does the dt projection: ``dt`` is then the low-rank (batch, L, dt_rank) tensor and
+    // dt_out (batch, L, D) receives the projected one (bf16, gated, dt_softplus, where scan_lanes_takes_low_dt)
+    const void *dt_w = nullptr;
+    void *dt_out = nullptr;
+    int64_t dt_rank = 0;
 };
 constexpr int kScanChunked = 0, kScanDirect = 1, kScanLanes = 2;
 // The library's own choice (chunk_len = 0) of kernel for a shape: channels across lanes (scan_direct.hip) when
@@ -44,6 +49,8 @@ int scan_kernel_choice(int64_t batch, int64_t L, int64_t D, int64_t N);
 bool scan_direct_applies(int64_t batch, int64_t L, int64_t D, int64_t N);
 bool scan_lanes_applies(int64_t batch, int64_t L, int64_t D, int64_t N);
 hipError_t launch_scan_direct(const ScanArgs &a, hipStream_t stream);
+// whether launch_scan_lanes takes a whole block's scan together with its dt projection: contexts of one super-step
+bool scan_lanes_takes_low_dt(int64_t batch, int64_t L, int64_t D, int64_t N, int64_t dt_rank);
 hipError_t launch_scan_lanes(const ScanArgs &a, hipStream_t stream);
 // Token tensors with element strides {batch, token, channel} (strided.hip): plain kernels, one lane per channel.
 struct ConvStridedArgs {

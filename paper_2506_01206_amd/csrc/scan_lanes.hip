@@ -42,6 +42,7 @@ namespace {
 
 constexpr int kN = 16;                   // states per channel
 constexpr int kParts = 4;                // groups of 4 states
+constexpr int kLowRank = 64;             // most dt columns that a scan takes the projection of
 constexpr int kBcPart = 66, kBcTau = kParts * kBcPart + 1;   // slots per state group and per token j of lds_B / lds_C
 
 __device__ __forceinline__ void lds_barrier_l()
@@ -180,13 +181,25 @@ template <> struct BcChunk<float> {      // 4 values: one group
     __device__ __forceinline__ float4 group(int) const { return v; }
 };
 
+// A context of one super-step in a whole block (LOW): the dt projection in here, from its low-rank input.  A workgroup's six channels of
+// 512 tokens are 16 small products of a wavefront each on the idle matrix cores, and what it fetches for them is contiguous where
+// dt is 12 bytes of every row; as a launch of its own the projection is a trip to memory and back and little else.  us of the scan, and
+// of both: 100 x 1536 7.1 -> 7.7, 10.2 -> 7.7; 333 x 1536 10.9 -> 11.4, 14.6 -> 11.4; 24-block prefill of 333 tokens 874 -> 808.  Longer contexts, whose
+// next rows are on their way while one super-step is walked, have no registers for it, and their two narrow products share a kernel
+// (xdt.hip).
+struct LowDt {
+    const bf16_t *w;                 // (D, rank)
+    bf16_t *out;                     // (batch, L, D): what the projection as a launch of its own would have stored
+    int rank;                        // a multiple of 8, at most kLowRank
+};
+
 // kG: channels per workgroup (2, 4 or 6); kTau: tokens per lane and super-step (4 or 8), 64 kTau tokens no more than threads.
 // grid: (ceil(D / kG) rounded up to a multiple of 8, batch); block: 128 kG.  N = 16, D even and >= kG.
-template <typename T, bool HAS_Z, bool SOFTPLUS, int kG, int kTau>
+template <typename T, bool HAS_Z, bool SOFTPLUS, int kG, int kTau, bool LOW = false>
 __global__ void __launch_bounds__(64 * kParts * (kG / 2))
 scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T *Bm, const T *Cm,
                   const float *__restrict__ Dskip, const T *z, const float *__restrict__ dt_bias,
-                  const float *h0 /* may alias h_final */, T *out, float *h_final, int64_t L, int64_t D)
+                  const float *h0 /* may alias h_final */, T *out, float *h_final, int64_t L, int64_t D, LowDt low)
 {
     constexpr int kThreadsL = 64 * kParts * (kG / 2);
     constexpr int kT = 64 * kTau;            // tokens per super-step
@@ -305,7 +318,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
         const int64_t base = (row0 + t_base) * D + c0;
         const uint32_t o = (uint32_t)min(kTau * ti + tj, last_of(t_base)) * (uint32_t)D;
         xr.load(x + base + o);
-        dtr.load(dt + base + o);
+        if constexpr (!LOW) dtr.load(dt + base + o);
         if constexpr (kAhead && HAS_Z) zr.load(z + base + o);
     };
     auto publish = [&](int64_t t_base, const RowG<T, kG> &xr, const RowG<T, kG> &dtr) {
@@ -345,9 +358,9 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
         }
         o6.pack(ov);
     };
-    auto store = [&](int64_t t_base, const OutG<T, kG> &o6) {
+    auto store = [&](T *rows, int64_t t_base, const OutG<T, kG> &o6) {
         if (kTau * ti + tj > last_of(t_base)) return;
-        T *p = out + (row0 + t_base) * D + c0 + (uint32_t)(kTau * ti + tj) * (uint32_t)D;
+        T *p = rows + (row0 + t_base) * D + c0 + (uint32_t)(kTau * ti + tj) * (uint32_t)D;
         if (dead == 0) {
             o6.store(p);
         } else {
@@ -357,12 +370,60 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
         }
     };
 
-    const int64_t n_super = (L + kT - 1) / kT;
+    const int64_t n_super = LOW ? 1 : (L + kT - 1) / kT;
     // (the first rows land where they stay: passed on through the registers of the next ones, the copy would wait for them here,
     // before B and C are requested)
     RowG<T, kG> dt_first;
     if (token_thread) fetch(0, x_cur, dt_first, z_cur);
-    fetch_bc(0, 0);
+    if constexpr (LOW) {
+        // dt = dt_low W_dt^T on the matrix cores: a wavefront's 64 tokens as two blocks of 32 columns, the workgroup's channels as the
+        // first rows, 16 k at a time; rounded as the stored tensor is.  y[q][j] is token 32 q + lane % 32, channel 4 (lane / 32) + j.
+        typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+        typedef float f32x16 __attribute__((ext_vector_type(16)));
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        if (token_thread) {
+            u32x4 wf[kLowRank / 16], xf[2][kLowRank / 16];
+            const int up = lane >> 5, ch = (lane & 31) < kG ? lane & 31 : kG - 1;
+#pragma unroll
+            for (int ks = 0; ks < kLowRank / 16; ++ks) {
+                const int k = min(16 * ks + 8 * up, low.rank - 8);
+                wf[ks] = *reinterpret_cast<const u32x4 *>(low.w + (c0 + ch) * low.rank + k);
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    xf[q][ks] = *reinterpret_cast<const u32x4 *>(dt + (row0 + min((tid & ~63) + 32 * q + (lane & 31), last_of(0))) * low.rank + k);
+            }
+            fetch_bc(0, 0);
+            f32x16 y[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) y[q][i] = 0.0f;
+#pragma unroll
+                for (int ks = 0; ks < kLowRank / 16; ++ks) {
+                    const bool in = 16 * ks + 8 * up < low.rank;   // (both operands: what stands in for the missing k may be infinite)
+                    const u32x4 wv = in ? wf[ks] : u32x4(0u), xv = in ? xf[q][ks] : u32x4(0u);
+                    y[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wv), __builtin_bit_cast(bf16x8, xv), y[q], 0, 0, 0);
+                }
+            }
+            // a lane has the first four channels of one token and the others of another: what is not its own goes to the lane 32 away
+            float dv[8];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float other = __shfl_xor(up ? y[0][j] : y[1][j], 32);
+                dv[j] = up ? other : y[0][j];
+                dv[4 + j] = up ? y[1][j] : other;
+            }
+            OutG<T, kG> stored;
+            stored.pack(dv);
+#pragma unroll
+            for (int c = 0; c < kG / 2; ++c) dt_first.v[c] = stored.v[c];
+            store(low.out, 0, stored);
+        } else {
+            fetch_bc(0, 0);
+        }
+    } else {
+        fetch_bc(0, 0);
+    }
     if (tid < 2 * kG) (&lds_par[0][0])[tid] = par;
     lds_barrier_l();   // the channel parameters are in LDS
     if (token_thread) publish(0, x_cur, dt_first);
@@ -375,7 +436,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
 
     for (int64_t k = 0; k < n_super; ++k) {                       // L >= 1: at least one
         const int64_t t_base = k * kT;
-        const bool more = k + 1 < n_super;
+        const bool more = !LOW && k + 1 < n_super;
         RowG<T, kG> x_nxt, dt_nxt, z_nxt;
         if (token_thread && more) fetch(t_base + kT, x_nxt, dt_nxt, z_nxt);
 
@@ -497,7 +558,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
         // after the stores would also wait for the stores, with everyone else at the barrier.
         if (token_thread) {
             gate(t_base, o6);
-            if constexpr (!kAhead) store(t_base, o6);   // (float32 has no registers to hold them in)
+            if constexpr (!kAhead) store(out, t_base, o6);   // (float32 has no registers to hold them in)
             if (more) {
                 publish(t_base + kT, x_nxt, dt_nxt);
                 x_cur = x_nxt;
@@ -512,7 +573,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
             }
         }
         if constexpr (kAhead) {
-            if (token_thread) store(t_base, o6);
+            if (token_thread) store(out, t_base, o6);
         }
         lds_barrier_l();   // the next super-step is in LDS
     }
@@ -569,40 +630,49 @@ template <typename T, int G, int TAU> hipError_t launch_lanes(const ScanArgs &a,
 {
     const int64_t n_groups = (a.D + G - 1) / G;
     const dim3 grid((unsigned)(8 * ((n_groups + 7) / 8)), (unsigned)a.batch);   // padded for the XCD-aware numbering
-#define MAMBA_LAUNCH_LANES(HZ, SP)                                                                          \
-    scan_lanes_kernel<T, HZ, SP, G, TAU><<<grid, 64 * kParts * (G / 2), 0, stream>>>(                       \
+#define MAMBA_LAUNCH_LANES(HZ, SP, LOW, LOWDT)                                                              \
+    scan_lanes_kernel<T, HZ, SP, G, TAU, LOW><<<grid, 64 * kParts * (G / 2), 0, stream>>>(                  \
         static_cast<const T *>(a.x), static_cast<const T *>(a.dt), a.A, static_cast<const T *>(a.Bm),       \
         static_cast<const T *>(a.Cm), a.Dskip, static_cast<const T *>(a.z), a.dt_bias, a.h0,                \
-        static_cast<T *>(a.out), a.h_final, a.L, a.D)
+        static_cast<T *>(a.out), a.h_final, a.L, a.D, LOWDT)
+    if constexpr (sizeof(T) == 2) {
+        if (a.dt_w) {
+            const LowDt low{static_cast<const bf16_t *>(a.dt_w), static_cast<bf16_t *>(a.dt_out), (int)a.dt_rank};
+            MAMBA_LAUNCH_LANES(true, true, true, low);
+            return hipGetLastError();
+        }
+    }
     if (a.z) {
-        if (a.dt_softplus) MAMBA_LAUNCH_LANES(true, true);
-        else MAMBA_LAUNCH_LANES(true, false);
+        if (a.dt_softplus) MAMBA_LAUNCH_LANES(true, true, false, LowDt{});
+        else MAMBA_LAUNCH_LANES(true, false, false, LowDt{});
     } else {
-        if (a.dt_softplus) MAMBA_LAUNCH_LANES(false, true);
-        else MAMBA_LAUNCH_LANES(false, false);
+        if (a.dt_softplus) MAMBA_LAUNCH_LANES(false, true, false, LowDt{});
+        else MAMBA_LAUNCH_LANES(false, false, false, LowDt{});
     }
 #undef MAMBA_LAUNCH_LANES
     return hipGetLastError();
 }
 
+// tokens of a super-step (a super-step of 512 tokens is half empty on 256: 256 x 768 with 4 channels 7.2 -> 5.6 us, float32 256 x 256 with 2
+// 8.5 -> 4.4)
+int lanes_super_step(int64_t batch, int64_t L, int64_t D) { return L <= 256 || lanes_channels(batch, L, D) == 2 ? 256 : 512; }
+
 template <typename T> hipError_t launch_lanes_io(const ScanArgs &a, hipStream_t stream)
 {
-    // (a super-step of 512 tokens is half empty on 256: 256 x 768 with 4 channels 7.2 -> 5.6 us, float32 256 x 256 with 2 8.5 -> 4.4)
-    if (a.L <= 256) {
-        switch (lanes_channels(a.batch, a.L, a.D)) {
-        case 2: return launch_lanes<T, 2, 4>(a, stream);
-        case 4: return launch_lanes<T, 4, 4>(a, stream);
-        default: return launch_lanes<T, 6, 4>(a, stream);
-        }
-    }
+    const bool longer = lanes_super_step(a.batch, a.L, a.D) == 512;
     switch (lanes_channels(a.batch, a.L, a.D)) {
     case 2: return launch_lanes<T, 2, 4>(a, stream);
-    case 4: return launch_lanes<T, 4, 8>(a, stream);
-    default: return launch_lanes<T, 6, 8>(a, stream);
+    case 4: return longer ? launch_lanes<T, 4, 8>(a, stream) : launch_lanes<T, 4, 4>(a, stream);
+    default: return longer ? launch_lanes<T, 6, 8>(a, stream) : launch_lanes<T, 6, 4>(a, stream);
     }
 }
 
 }  // namespace
+
+bool scan_lanes_takes_low_dt(int64_t batch, int64_t L, int64_t D, int64_t N, int64_t dt_rank)
+{
+    return scan_kernel_choice(batch, L, D, N) == kScanLanes && L <= lanes_super_step(batch, L, D) && dt_rank % 8 == 0 && dt_rank <= kLowRank;
+}
 
 hipError_t launch_scan_lanes(const ScanArgs &a, hipStream_t stream)
 {

@@ -1489,6 +1489,25 @@ def test_block_conv_in_the_way_in(m, B, L, dm, D):
     assert torch.equal(s, state1) and torch.equal(m.mamba_block_workspace_layout(blk, B, L, ws)["x_c"], xc.view(B * L, D))
 
 
+@pytest.mark.parametrize("B,L,dm,D,R", [(1, 64, 64, 64, 8), (3, 65, 64, 96, 16), (1, 256, 64, 512, 24), (1, 256, 128, 1000, 40),      # 2 or 4 channels
+                                        (1, 255, 64, 1536, 48), (1, 257, 64, 1536, 64), (1, 511, 64, 1000, 56), (1, 512, 64, 1528, 48),  # 4 or 6
+                                        (1, 513, 64, 1536, 48), (1, 300, 64, 1536, 72)])                                                # not taken
+def test_block_dt_projection_in_the_scan(m, B, L, dm, D, R):
+    """The dt projection inside the scan of a context of one super-step: full and ragged super-steps, the last workgroup moved back, ranks
+    that end inside a block of 16 k; one token and one rank more than it takes, stage by stage."""
+    say(B=B, L=L, dm=dm, D=D, R=R)
+    rng = np.random.default_rng(B * 1000 + L + D + R)
+    w, w64, blk = make_block(m, rng, dm, D, 16, 4, R)
+    hid = synth.to_io(rng.standard_normal((B, L, dm)).astype(np.float32), synth.BF16)
+    h0 = rng.standard_normal((B, D, 16)).astype(np.float32)
+    check_block_stages(m, blk, w64, hid, h0=h0)
+    # final states over the initial ones
+    h = to_dev(h0).clone()
+    a, _, b = m.mamba_block_fwd(blk, to_dev(hid), h0=to_dev(h0))
+    c, _, d = m.mamba_block_fwd(blk, to_dev(hid), h0=h, h_final=h)
+    assert torch.equal(a, c) and torch.equal(b, d) and torch.equal(h, b)
+
+
 @pytest.mark.parametrize("tree", [(3, 2, 1), (1, 1), (4,), (33, 2, 1), (66, 2)])
 def test_block_decode_steps_against_oracle(m, tree):
     """Tree drafting through whole blocks: at every draft position each branch continues from its
