@@ -15,9 +15,8 @@
 //
 // A workgroup owns 6 adjacent channels (256 workgroups for 1536 channels; 4 or 2 of a narrower layer, so that it still has as
 // many: 1 x 1000 x 768 15.2 -> 12.4 us, 1 x 1000 x 512 15.7 -> 10.4) and walks the sequence in
-// super-steps of 512 tokens.  Its 12 (8, 4) wavefronts are (channel pair, group of 4 states); the 64 lanes of a
-// wavefront are 64 consecutive blocks of 8 tokens (4 where the whole sequence is 256 tokens or shorter, 256 x 1536 9.3 -> 7.4 us, and
-// with 2 channels, which 8 tokens would leave without a thread for each).  Per super-step a lane
+// super-steps of 512 (384, 256) tokens.  Its 12 (8, 4) wavefronts are (channel pair, group of 4 states); the 64 lanes of a
+// wavefront are 64 consecutive blocks of 8 tokens (or 6 or 4, lanes_tau).  Per super-step a lane
 //   1. integrates its 8 tokens from a zero state (lane 0 from the true state that enters the super-step),
 //      keeping the 8 x 8 decay factors a = exp(delta A) in registers: mul, exp2, mul, fma per update;
 //   2. forms the decay over its whole block, P = exp(A * sum of its deltas);
@@ -193,7 +192,7 @@ struct LowDt {
     int rank;                        // a multiple of 8, at most kLowRank
 };
 
-// kG: channels per workgroup (2, 4 or 6); kTau: tokens per lane and super-step (4 or 8), 64 kTau tokens no more than threads.
+// kG: channels per workgroup (2, 4 or 6); kTau: tokens per lane and super-step (4, 6 or 8), 64 kTau tokens no more than threads.
 // grid: (ceil(D / kG) rounded up to a multiple of 8, batch); block: 128 kG.  N = 16, D even and >= kG.
 template <typename T, bool HAS_Z, bool SOFTPLUS, int kG, int kTau, bool LOW = false>
 __global__ void __launch_bounds__(64 * kParts * (kG / 2))
@@ -216,10 +215,13 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
     // of the banks (j * 265 + 2 * 66 * pos = j + 4 * pos mod 8).
     __shared__ __attribute__((aligned(16))) float4 lds_B[kTau * kBcTau];
     __shared__ __attribute__((aligned(16))) float4 lds_C[kTau * kBcTau];
-    // [channel][half of the block][lane][4 tokens]
-    __shared__ __attribute__((aligned(16))) float4 lds_d[kG][kTau / 4][64];   // delta
-    __shared__ __attribute__((aligned(16))) float4 lds_u[kG][kTau / 4][64];   // delta * x
-    __shared__ __attribute__((aligned(16))) float4 lds_y[kParts][kG][kTau / 4][64];   // C . h per token, same layout: one part per state group
+    // [channel][part of the block][lane][kQ tokens]; rows of two tokens are padded so that the three parts a token row of threads
+    // writes fall on different banks
+    constexpr int kQ = kTau % 4 == 0 ? 4 : 2, kRow = kQ == 4 ? 64 : 64 + 11;
+    typedef float quad __attribute__((ext_vector_type(kQ)));
+    __shared__ __attribute__((aligned(16))) quad lds_d[kG][kTau / kQ][kRow];   // delta
+    __shared__ __attribute__((aligned(16))) quad lds_u[kG][kTau / kQ][kRow];   // delta * x
+    __shared__ __attribute__((aligned(16))) quad lds_y[kParts][kG][kTau / kQ][kRow];   // C . h per token, same layout: one part per state group
     __shared__ float lds_par[2][kG];                                           // dt_bias, D of the workgroup's channels
 
     const int tid = threadIdx.x;
@@ -248,7 +250,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
     // tj of the block of lane ti.  (A wavefront's 4-byte accesses to the [..][lane][4 tokens] arrays then cover all
     // banks: 8 lanes x 4 positions.)
     const bool token_thread = tid < kTokenThreads;
-    const int tj = tid & (kTau - 1), ti = (tid / kTau) & 63;
+    const int tj = tid % kTau, ti = (tid / kTau) & 63;
     // dt_bias and D of the workgroup's channels: one load per thread, requested here and put into LDS only after the
     // first rows have been requested as well (written where it is fetched, wavefront 0 would sit through two
     // memory round trips before it asks for anything else, and the whole workgroup waits for it at the barrier)
@@ -310,7 +312,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
                 float4 *dst = arr ? lds_C : lds_B;
 #pragma unroll
                 for (int g = 0; g < kChunkGroups; ++g)
-                    dst[(tok & (kTau - 1)) * kBcTau + (pos * kChunkGroups + g) * kBcPart + tok / kTau] = bc_nxt[it].group(g);
+                    dst[(tok % kTau) * kBcTau + (pos * kChunkGroups + g) * kBcPart + tok / kTau] = bc_nxt[it].group(g);
             }
         }
     };
@@ -337,8 +339,8 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
 #pragma unroll
         for (int c = 0; c < kG; ++c) {
             const float d = valid ? dv[c] : 0.0f;    // a token past the end leaves the state as it is
-            reinterpret_cast<float *>(&lds_d[c][tj >> 2][ti])[tj & 3] = d;
-            reinterpret_cast<float *>(&lds_u[c][tj >> 2][ti])[tj & 3] = d * xv[c];
+            reinterpret_cast<float *>(&lds_d[c][tj / kQ][ti])[tj % kQ] = d;
+            reinterpret_cast<float *>(&lds_u[c][tj / kQ][ti])[tj % kQ] = d * xv[c];
         }
     };
     auto gate = [&](int64_t t_base, OutG<T, kG> &o6) {   // the outputs of the super-step
@@ -351,7 +353,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
 #pragma unroll
         for (int c = 0; c < kG; ++c) {
             // the four state groups in a fixed order: the result does not depend on which wavefront was first
-            auto part_y = [&](int p) { return reinterpret_cast<const float *>(&lds_y[p][c][tj >> 2][ti])[tj & 3]; };
+            auto part_y = [&](int p) { return reinterpret_cast<const float *>(&lds_y[p][c][tj / kQ][ti])[tj % kQ]; };
             const float ch = (part_y(0) + part_y(1)) + (part_y(2) + part_y(3));
             const float y = fmaf(lds_par[1][c], xv[c], ch);
             ov[c] = HAS_Z ? y * silu_f32(zv[c]) : y;
@@ -448,31 +450,31 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
 #pragma unroll
             for (int n = 0; n < 4; ++n) h[ch][n] = lane == 0 ? hp[ch][n] : 0.0f;
 #pragma unroll
-        for (int jh = 0; jh < kTau / 4; ++jh) {
-            float4 d4[2], u4[2];
+        for (int jh = 0; jh < kTau / kQ; ++jh) {
+            quad d4[2], u4[2];
 #pragma unroll
             for (int ch = 0; ch < 2; ++ch) {
                 d4[ch] = lds_d[ca + ch][jh][lane];
                 u4[ch] = lds_u[ca + ch][jh][lane];
             }
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                const int j = 4 * jh + jj;
+            for (int jj = 0; jj < kQ; ++jj) {
+                const int j = kQ * jh + jj;
                 const float4 b4 = lds_B[j * kBcTau + part * kBcPart + lane];
                 const float bv[4] = {b4.x, b4.y, b4.z, b4.w};
                 float e[8];
 #pragma unroll
                 for (int ch = 0; ch < 2; ++ch)
 #pragma unroll
-                    for (int n = 0; n < 4; ++n) e[4 * ch + n] = (jj == 0 ? d4[ch].x : jj == 1 ? d4[ch].y : jj == 2 ? d4[ch].z : d4[ch].w) * a2[ch][n];
+                    for (int n = 0; n < 4; ++n) e[4 * ch + n] = d4[ch][jj] * a2[ch][n];
                 if constexpr (kRuns) exp2_run(e);
                 else
 #pragma unroll
                     for (int i = 0; i < 8; ++i) e[i] = exp2_hw(e[i]);
 #pragma unroll
                 for (int ch = 0; ch < 2; ++ch) {
-                    const float d = jj == 0 ? d4[ch].x : jj == 1 ? d4[ch].y : jj == 2 ? d4[ch].z : d4[ch].w;
-                    const float u = jj == 0 ? u4[ch].x : jj == 1 ? u4[ch].y : jj == 2 ? u4[ch].z : u4[ch].w;
+                    const float d = d4[ch][jj];
+                    const float u = u4[ch][jj];
                     dsum[ch] += d;
 #pragma unroll
                     for (int n = 0; n < 4; ++n) {
@@ -522,20 +524,20 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
         }
         // ---- 4. the 8 tokens again from the true state, with outputs (delta * x is read again rather than kept)
 #pragma unroll
-        for (int jh = 0; jh < kTau / 4; ++jh) {
+        for (int jh = 0; jh < kTau / kQ; ++jh) {
             __builtin_amdgcn_sched_barrier(0);
-            float4 u4[2];
-            float yq[2][4];
+            quad u4[2];
+            quad yq[2];
 #pragma unroll
             for (int ch = 0; ch < 2; ++ch) u4[ch] = lds_u[ca + ch][jh][lane];
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                const int j = 4 * jh + jj;
+            for (int jj = 0; jj < kQ; ++jj) {
+                const int j = kQ * jh + jj;
                 const float4 b4 = lds_B[j * kBcTau + part * kBcPart + lane], c4 = lds_C[j * kBcTau + part * kBcPart + lane];
                 const float bv[4] = {b4.x, b4.y, b4.z, b4.w}, cv[4] = {c4.x, c4.y, c4.z, c4.w};
 #pragma unroll
                 for (int ch = 0; ch < 2; ++ch) {
-                    const float u = jj == 0 ? u4[ch].x : jj == 1 ? u4[ch].y : jj == 2 ? u4[ch].z : u4[ch].w;
+                    const float u = u4[ch][jj];
                     float yp = 0.0f;
 #pragma unroll
                     for (int n = 0; n < 4; ++n) {
@@ -546,7 +548,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
                 }
             }
 #pragma unroll
-            for (int ch = 0; ch < 2; ++ch) lds_y[part][ca + ch][jh][lane] = make_float4(yq[ch][0], yq[ch][1], yq[ch][2], yq[ch][3]);
+            for (int ch = 0; ch < 2; ++ch) lds_y[part][ca + ch][jh][lane] = yq[ch];
         }
         lds_barrier_l();   // y of the super-step is complete; its operands are used up
 
@@ -653,17 +655,28 @@ template <typename T, int G, int TAU> hipError_t launch_lanes(const ScanArgs &a,
     return hipGetLastError();
 }
 
-// tokens of a super-step (a super-step of 512 tokens is half empty on 256: 256 x 768 with 4 channels 7.2 -> 5.6 us, float32 256 x 256 with 2
-// 8.5 -> 4.4)
-int lanes_super_step(int64_t batch, int64_t L, int64_t D) { return L <= 256 || lanes_channels(batch, L, D) == 2 ? 256 : 512; }
+// Tokens of a lane, 64 times that to a super-step: what takes the fewest super-steps times what one takes, which is 5.3 us with 8 tokens,
+// 4.1 with 6 and 3.2 with 4 (1536 channels; a last one that is not full takes somewhat less).  Two channels to a workgroup leave no
+// threads for more than 4.  us with 4 / 6 / 8 tokens:
+//    200 x 1536  7.25*/ 8.37 / 9.05     400 x 1536 10.45 / 12.56 / 9.84*    1000 x 1536 17.06 / 16.92 / 15.49*     700 x 1000 10.68 / 10.33*/ 11.66
+//    300 x 1536 10.42 / 8.79*/ 9.48     600 x 1536 13.49 / 12.69*/14.70     1100 x 1536 19.82 / 17.06*/ 19.72      350 x 1536 float32 11.43 / 9.75*/ 10.70
+//    384 x 1536 10.51 / 9.19*/ 9.83     768 x 1536 13.73 / 13.01*/14.92     1900 x 1536 29.56 / 26.07 / 25.83*     700 x 1536 float32 16.88 / 16.21*/ 18.23
+int lanes_tau(int64_t batch, int64_t L, int64_t D)
+{
+    if (L <= 256 || lanes_channels(batch, L, D) == 2) return 4;
+    return 4.1 * (double)((L + 383) / 384) < 0.95 * 5.3 * (double)((L + 511) / 512) ? 6 : 8;
+}
 
 template <typename T> hipError_t launch_lanes_io(const ScanArgs &a, hipStream_t stream)
 {
-    const bool longer = lanes_super_step(a.batch, a.L, a.D) == 512;
-    switch (lanes_channels(a.batch, a.L, a.D)) {
-    case 2: return launch_lanes<T, 2, 4>(a, stream);
-    case 4: return longer ? launch_lanes<T, 4, 8>(a, stream) : launch_lanes<T, 4, 4>(a, stream);
-    default: return longer ? launch_lanes<T, 6, 8>(a, stream) : launch_lanes<T, 6, 4>(a, stream);
+    switch (10 * lanes_channels(a.batch, a.L, a.D) + lanes_tau(a.batch, a.L, a.D)) {
+    case 24: return launch_lanes<T, 2, 4>(a, stream);
+    case 44: return launch_lanes<T, 4, 4>(a, stream);
+    case 46: return launch_lanes<T, 4, 6>(a, stream);
+    case 48: return launch_lanes<T, 4, 8>(a, stream);
+    case 64: return launch_lanes<T, 6, 4>(a, stream);
+    case 66: return launch_lanes<T, 6, 6>(a, stream);
+    default: return launch_lanes<T, 6, 8>(a, stream);
     }
 }
 
@@ -671,7 +684,7 @@ template <typename T> hipError_t launch_lanes_io(const ScanArgs &a, hipStream_t 
 
 bool scan_lanes_takes_low_dt(int64_t batch, int64_t L, int64_t D, int64_t N, int64_t dt_rank)
 {
-    return scan_kernel_choice(batch, L, D, N) == kScanLanes && L <= lanes_super_step(batch, L, D) && dt_rank % 8 == 0 && dt_rank <= kLowRank;
+    return scan_kernel_choice(batch, L, D, N) == kScanLanes && L <= 64 * lanes_tau(batch, L, D) && dt_rank % 8 == 0 && dt_rank <= kLowRank;
 }
 
 hipError_t launch_scan_lanes(const ScanArgs &a, hipStream_t stream)

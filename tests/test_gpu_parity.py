@@ -213,7 +213,9 @@ def test_scan_single_pass_shapes(m, io, N, B, L, D):
 @pytest.mark.parametrize("io", [synth.F32, synth.BF16])
 @pytest.mark.parametrize("B,L,D", [(1, 64, 6), (1, 255, 512), (2, 257, 254), (1, 1025, 510),          # two channels to a workgroup
                                    (1, 256, 1022), (1, 65, 2046), (3, 700, 330), (1, 1300, 1022),         # four
-                                   (1, 200, 1534), (1, 256, 3072), (1, 300, 1532)])                       # six
+                                   (1, 200, 1534), (1, 256, 3072), (1, 300, 1532),                        # six
+                                   (1, 257, 1020), (1, 384, 1022), (1, 385, 1022), (2, 513, 510), (1, 768, 1000), (1, 769, 1000),   # 6 and 8 tokens to a
+                                   (1, 384, 1534), (1, 385, 1534), (1, 767, 1532), (1, 1025, 1536), (1, 1152, 1530)])               # lane, four and six
 def test_scan_time_across_lanes_every_width(m, io, B, L, D):
     """Every number of channels to a workgroup and of tokens to a lane, with channel counts that leave the last workgroup
     fewer of its own, one super-step, exactly one and several, with and without gate and carried state."""
