@@ -538,18 +538,22 @@ bool conv_rides_in_proj(const mamba_block_params_t *p, const void *hidden, const
     return !overlap(state_out, st, workspace, (int64_t)ws_bytes);
 }
 
-// Whether the scan takes the dt projection along: contexts of one super-step of the lanes kernel, too few rows for xdt.hip, and nothing
-// that the scan writes shared with what it then reads.  (Everything else takes the calls, which have their own checks.)
-bool dt_rides_in_scan(const mamba_block_params_t *p, const float *h0, const float *h_final, const void *workspace, size_t ws_bytes, int64_t batch,
-                      int64_t L)
+// Whether a block's scan is launched on the lanes kernel here, and with low_dt, whether that takes the dt projection along (contexts of one
+// super-step, too few rows for xdt.hip): nothing that the scan writes is shared with what it then reads.  (Everything else takes the
+// calls, which have their own checks.)
+bool block_scan_on_lanes(const mamba_block_params_t *p, const float *h0, const float *h_final, const void *workspace, size_t ws_bytes, int64_t batch,
+                         int64_t L, bool *low_dt)
 {
     const int64_t Di = p->d_inner, N = p->d_state, R = p->dt_rank, w = 2 * Di * R;
     unsigned groups;
     int64_t st;
-    if (batch > kMaxGridYZ || !scan_lanes_takes_low_dt(batch, L, Di, N, R) || xdt_plan(batch * L, Di, R, N, &groups) > 0) return false;
+    *low_dt = false;
+    if (batch > kMaxGridYZ || !scan_lanes_in_block(batch, L, Di, N)) return false;
     if (!size3(batch, Di, N, 4, &st) || !aligned16(h0) || !aligned16(h_final) || (h_final != h0 && overlap(h_final, st, h0, st))) return false;
-    return !overlap(p->dt_proj_w, w, workspace, (int64_t)ws_bytes) && !overlap(h_final, st, p->dt_proj_w, w) &&
-           !overlap(h0, st, workspace, (int64_t)ws_bytes) && !overlap(h_final, st, workspace, (int64_t)ws_bytes);
+    if (overlap(h0, st, workspace, (int64_t)ws_bytes) || overlap(h_final, st, workspace, (int64_t)ws_bytes)) return false;
+    *low_dt = scan_lanes_takes_low_dt(batch, L, Di, N, R) && xdt_plan(batch * L, Di, R, N, &groups) == 0 &&
+              !overlap(p->dt_proj_w, w, workspace, (int64_t)ws_bytes) && !overlap(h_final, st, p->dt_proj_w, w);
+    return true;
 }
 
 int block_params_ok(const mamba_block_params_t *p)
@@ -627,7 +631,8 @@ int mamba_block_fwd(const mamba_block_params_t *p, const void *hidden, void *hid
     }
     // [dt_low | B | C] = x_c W_x^T,  dt = dt_low W_dt^T       -> a (u is dead)
     unsigned groups;
-    const bool dt_in_scan = dt_rides_in_scan(p, h0, h_final, workspace, bb.total, batch, L);
+    bool dt_in_scan;
+    const bool lanes = block_scan_on_lanes(p, h0, h_final, workspace, bb.total, batch, L, &dt_in_scan);
     if (xdt_plan(rows, Di, R, N, &groups) > 0) {
         const int64_t xw = (R + 2 * N) * Di * 2, low = rows * R * 2, bc = rows * N * 2;   // (sizes that block_layout has checked)
         if (overlap(bb.dtl, low, p->x_proj_w, xw) || overlap(bb.bm, bc, p->x_proj_w, xw) || overlap(bb.cm, bc, p->x_proj_w, xw) ||
@@ -642,15 +647,17 @@ int mamba_block_fwd(const mamba_block_params_t *p, const void *hidden, void *hid
             return rc;
     }
     // y = scan(...) gated by silu(z)                        -> d (x is dead)
-    if (dt_in_scan) {
-        ScanArgs sa{bb.c, bb.dtl, bb.bm, bb.cm, bb.b, p->A, p->Dskip, p->dt_bias, h0, bb.d, h_final, nullptr, batch, L, Di, (int)N, kIoBf16, 1, L, 1};
+    if (lanes) {
+        ScanArgs sa{bb.c, bb.a, bb.bm, bb.cm, bb.b, p->A, p->Dskip, p->dt_bias, h0, bb.d, h_final, nullptr, batch, L, Di, (int)N, kIoBf16, 1, L, 1};
         sa.single_pass = kScanLanes;
-        sa.dt_w = p->dt_proj_w;
-        sa.dt_out = bb.a;
-        sa.dt_rank = R;
+        if (dt_in_scan) {
+            sa.dt = bb.dtl;
+            sa.dt_w = p->dt_proj_w;
+            sa.dt_out = bb.a;
+            sa.dt_rank = R;
+        }
         if (hipError_t e = launch_scan(sa, static_cast<hipStream_t>(hip_stream))) return (int)e;
-    } else
-    if ((rc = mamba_scan_fwd(bb.c, bb.a, p->A, bb.bm, bb.cm, p->Dskip, bb.b, p->dt_bias, h0, bb.d, h_final,
+    } else if ((rc = mamba_scan_fwd(bb.c, bb.a, p->A, bb.bm, bb.cm, p->Dskip, bb.b, p->dt_bias, h0, bb.d, h_final,
                              bb.scan_ws_bytes ? bb.scan_ws : nullptr, bb.scan_ws_bytes, batch, L, Di, N, 0, 1, io, hip_stream)))
         return rc;
     // hidden_out = hidden + y W_out^T

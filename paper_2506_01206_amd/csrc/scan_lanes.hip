@@ -597,6 +597,14 @@ int lanes_channels(int64_t batch, int64_t L, int64_t D)
     return two <= four && two <= six ? 2 : four <= six ? 4 : 6;
 }
 
+// ns: rounds of workgroups times what one takes, to which a token adds `six`, `four` or `two` by its channels
+double lanes_ns(int64_t batch, int64_t L, int64_t D, double six, double four, double two)
+{
+    const int64_t g = lanes_channels(batch, L, D), groups = batch * ((D + g - 1) / g);
+    const double first = g == 6 ? 6000.0 : g == 4 ? 5000.0 : 2500.0, token = g == 6 ? six : g == 4 ? four : two;
+    return (double)((groups + 255) / 256) * (first + token * (double)L);
+}
+
 }  // namespace
 
 // Shapes the lane-scan kernel serves: 16 states, token rows that can be read in 4-byte pieces from any even
@@ -618,12 +626,23 @@ int lanes_channels(int64_t batch, int64_t L, int64_t D)
 bool scan_lanes_applies(int64_t batch, int64_t L, int64_t D, int64_t N)
 {
     if (N != kN || D % 2 != 0 || D < 6 || L < 64 || batch > 65535) return false;
-    const int64_t g = lanes_channels(batch, L, D), groups = batch * ((D + g - 1) / g);
-    const double rounds = (double)((groups + 255) / 256);
-    const double first = g == 6 ? 6000.0 : g == 4 ? 5000.0 : 2500.0, token = g == 6 ? 11.6 : g == 4 ? 9.7 : 12.5;
-    const double lanes_ns = rounds * (first + token * (double)L);
     const double two_pass_ns = 24000.0 + 9.8 * (double)L * ((double)batch * (double)D / 1536.0);
-    return lanes_ns < two_pass_ns;
+    return lanes_ns(batch, L, D, 11.6, 9.7, 12.5) < two_pass_ns;
+}
+
+// The same in a whole block, whose scan finds its operands in the last-level cache as long as the block's four tensors of (rows, D) bf16 fit
+// its 256 MB: the small pieces of the token rows that this kernel reads come sooner from there, the two passes gain nothing by it.
+// us of a block, two passes / lanes, three sets of operands in turn (* what this takes; a line within 2 us is left to the two passes):
+//   1 x 10500 x 1536 260 / 243*      2 x 4000 x 1536 205 / 196*      3 x 3000 x 1536 241 / 219*      1 x  8000 x 1024 140 / 133*      1 x 6000 x 4096 545* / 554
+//   1 x 16000 x 1536 368 / 346*      2 x 8000 x 1536 367 / 350*      4 x 1000 x 1536 127*/ 125       1 x 10000 x  768 134*/ 143       1 x 3000 x 2048 133 / 127*
+//   1 x 20000 x 1536 458 / 437*      4 x 8000 x 1536 634*/ 724       8 x  500 x 1536 125*/ 139       1 x  9000 x 3072 537 / 518*      2 x 1500 x 2048 133* / 139
+//   1 x 32768 x 1536 634*/ 744       4 x 4000 x 1536 370*/ 362       8 x 2000 x 1536 369*/ 377       1 x  6000 x  512  88*/ 81
+bool scan_lanes_in_block(int64_t batch, int64_t L, int64_t D, int64_t N)
+{
+    if (scan_kernel_choice(batch, L, D, N) != kScanChunked) return scan_kernel_choice(batch, L, D, N) == kScanLanes;
+    if (N != kN || D % 2 != 0 || D < 6 || L < 64 || batch > 65535 || (double)batch * (double)L * (double)D > 32e6) return false;
+    const double two_pass_ns = 24000.0 + 10.0 * (double)L * ((double)batch * (double)D / 1536.0);
+    return lanes_ns(batch, L, D, 9.9, 8.3, 10.7) < two_pass_ns - 2000.0;
 }
 
 namespace {

@@ -1417,6 +1417,8 @@ def check_block_stages(m, blk, w64, hid, conv_in=None, h0=None, what="block"):
                                            (3, 33, 256, 512, 8, 3, 16),
                                            # long enough for the 256-row projection tiles (in_proj and out_proj)
                                            (1, 4096, 768, 1536, 16, 4, 48),
+                                           # scans that a block takes on the lanes kernel and a call of its own does not (the pieces' others)
+                                           (2, 4000, 64, 1536, 16, 4, 48), (3, 1000, 64, 1024, 16, 4, 32),
                                            # 32 states, the fastest of them decaying by exp(-16 delta) a step
                                            (2, 100, 216, 1144, 32, 3, 24)])
 def test_block_prefill_against_oracle(m, B, L, dm, D, N, K, R):
