@@ -294,10 +294,12 @@ __device__ __forceinline__ void conv_rows(const unsigned char *tile, int64_t m0,
 // ---------------------------------------------------------------------------------------------------
 // Many rows (the projections of a long context).  A 128 x 128 tile asks the L1 for 512 bytes per k and
 // multiplies 8 cycles per k on every SIMD, so the cache, which delivers 64 bytes a cycle, can feed the
-// matrix cores half the time at best.  This kernel takes 256 x 256 tiles, one workgroup per CU and one
-// wavefront per SIMD, each wavefront a 128 x 128 part held in 256 accumulator registers: per k the same
-// 8 cycles of cache traffic now feed 32 cycles of MFMA.
-// (With BN = 128 it also runs 128 x 128 and 192 x 128 tiles, two workgroups to a CU, for products too small to give every CU
+// matrix cores half the time at best.  This kernel takes 256 x 256 tiles, one workgroup per CU and two
+// wavefronts per SIMD, each with a 128 x 64 part in 128 accumulator registers: per k the same
+// 8 cycles of cache traffic now feed 32 cycles of MFMA.  (As four wavefronts of 128 x 128, which read a third less LDS, a SIMD has nothing
+// to multiply while its one wavefront waits at the slab's barrier or for fragments: us of four / eight wavefronts, 24 weights in turn, 4096 x
+// 3072, K = 768 24.9 / 21.9, 16384 x 3072 83.8 / 77.4, 32768 x 3072 179 / 170, 8000 x 768, K = 1536 39.8 / 33.4, 8000 x 4096, K = 1024 68.3 / 64.9.)
+// (With four wavefronts it also runs 128 x 128 and 192 x 128 tiles, two workgroups to a CU, for products too small to give every CU
 // a 256-row tile, or that leave CUs without one: the feeding scheme below, not the tile size, is what those gain from.)
 //
 // Operands go from memory straight into LDS (global_load_lds_dwordx4: lane l of a wavefront lands at
@@ -326,12 +328,13 @@ __device__ __forceinline__ void load_to_lds16(const char *base, uint32_t lane_of
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(lane_off), "s"(base) : "memory");
 }
 
-template <int BM, int BN, bool CONV = false>
-__global__ void __launch_bounds__(256)
+template <int BM, int BN, bool CONV = false, int WM = 2, int WN = 2>
+__global__ void __launch_bounds__(64 * WM * WN)
 linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ bias, const bf16_t *residual,
                    OutSplit out, int64_t M, int64_t N, int64_t K, int tiles_n, int n_tiles, ConvTail conv)
 {
-    constexpr int MT = BM / 64, NT = BN / 64;                     // 32 x 32 MFMA tiles per wavefront along m and n
+    constexpr int NW = WM * WN, kThr = 64 * NW;
+    constexpr int MT = BM / WM / 32, NT = BN / WN / 32;           // 32 x 32 MFMA tiles per wavefront along m and n
     constexpr int kRows = BM + BN;
     constexpr int kStage = kRows * kWideRow;
     constexpr int kOutRow = BN * 2 + 16;
@@ -339,7 +342,7 @@ linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
     __shared__ __attribute__((aligned(1024))) unsigned char lds[kLds];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wm = wave / WN, wn = wave % WN;
 
     const int per_xcd = (n_tiles + 7) / 8;
     const int tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
@@ -355,21 +358,21 @@ linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
     if (CONV && n0 < out.width[0]) rows_of_block<BM, true>(row_block, M, &m0, &dead);
     else rows_of_block<BM, false>(row_block, M, &m0, &dead);
 
-    // Loads: wavefront v takes the row groups g = 4 j + v (rows 8 g .. 8 g + 7 of the stage; x rows first, then w);
+    // Loads: wavefront v takes the row groups g = NW j + v (rows 8 g .. 8 g + 7 of the stage; x rows first, then w);
     // lane l lands in row 8 g + l / 8, slot l % 8, and therefore fetches slot (l % 8) ^ ((4 (g & 1) + l / 16) & 7)
     // of that row (g & 1 == v & 1).
-    constexpr int NLX = BM / 32, NLW = BN / 32;              // loads per wavefront and slab
+    constexpr int NLX = BM / 8 / NW, NLW = BN / 8 / NW;      // loads per wavefront and slab
     const uint32_t lane_off = (uint32_t)((lane >> 3) * K * 2 + (((lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7)) << 4));
     const char *xrow = reinterpret_cast<const char *>(x + (m0 + 8 * wave) * K);
     const char *wrow = reinterpret_cast<const char *>(w + (n0 + 8 * wave) * K);
-    const int64_t rows32 = 64 * K;                                 // bytes between rows 32 apart
+    const int64_t rows_nw = 16 * NW * K;                           // bytes between a wavefront's groups of 8 rows
     const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)lds;
     // loads [first, last) of the slab at k0 into the stage at byte `stage`
     auto request = [&](int64_t k0, int stage, auto first, auto last) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = decltype(first)::value; i < decltype(last)::value; ++i) {
-            const char *base = i < NLX ? xrow + (i * rows32 + 2 * k0) : wrow + ((i - NLX) * rows32 + 2 * k0);
-            load_to_lds16(base, lane_off, lds0 + stage + (i < NLX ? 0 : BM * kWideRow) + wave * 1024 + (i < NLX ? i : i - NLX) * 4096);
+            const char *base = i < NLX ? xrow + (i * rows_nw + 2 * k0) : wrow + ((i - NLX) * rows_nw + 2 * k0);
+            load_to_lds16(base, lane_off, lds0 + stage + (i < NLX ? 0 : BM * kWideRow) + wave * 1024 + (i < NLX ? i : i - NLX) * (1024 * NW));
         }
     };
     typedef std::integral_constant<int, 0> L0;
@@ -391,8 +394,8 @@ linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
         const int slot = ((2 * ks + (lane >> 5)) ^ ((lane >> 1) & 7)) << 4;
-        frag_x[ks] = (wm * (BM / 2) + (lane & 31)) * kWideRow + slot;
-        frag_w[ks] = (BM + wn * (BN / 2) + (lane & 31)) * kWideRow + slot;
+        frag_x[ks] = (wm * (BM / WM) + (lane & 31)) * kWideRow + slot;
+        frag_w[ks] = (BM + wn * (BN / WN) + (lane & 31)) * kWideRow + slot;
     }
     struct Frags { bf16x8 xf[MT], wf[NT]; };
     auto load_x = [&](const unsigned char *stage, int ks, Frags &f, int t) __attribute__((always_inline)) {
@@ -478,12 +481,12 @@ linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
     // Epilogue.  The residual chunks this thread will add are requested first, all at once: with one workgroup per
     // CU nothing else would hide their latency, and fetched four at a time inside the store loop they cost a third
     // of the tile's time.
-    constexpr int kCpr = BN / 8, kChunks = BM * kCpr / 256;
+    constexpr int kCpr = BN / 8, kChunks = BM * kCpr / kThr;
     u32x4 res[kChunks];
     if (residual) {
 #pragma unroll
         for (int i = 0; i < kChunks; ++i) {
-            const int c = tid + i * 256, row = c / kCpr, cc = c % kCpr;
+            const int c = tid + i * kThr, row = c / kCpr, cc = c % kCpr;
             int64_t col;
             const int sp = locate(out, n0 + cc * 8, &col);
             // (a dead row is not read: where the residual is the output itself its owner may be writing it)
@@ -497,12 +500,12 @@ linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
     for (int b = 0; b < NT; ++b)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            const int nl = wn * (BN / 2) + b * 32 + 8 * g + 4 * (lane >> 5);
+            const int nl = wn * (BN / WN) + b * 32 + 8 * g + 4 * (lane >> 5);
             float4 bv = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             if (bias) bv = *reinterpret_cast<const float4 *>(bias + n0 + nl);
 #pragma unroll
             for (int a = 0; a < MT; ++a) {
-                const int ml = wm * (BM / 2) + a * 32 + (lane & 31);
+                const int ml = wm * (BM / WM) + a * 32 + (lane & 31);
                 uint2 v;
                 v.x = f32x2_to_bf16x2(acc[a][b][4 * g + 0] + bv.x, acc[a][b][4 * g + 1] + bv.y);
                 v.y = f32x2_to_bf16x2(acc[a][b][4 * g + 2] + bv.z, acc[a][b][4 * g + 3] + bv.w);
@@ -513,7 +516,7 @@ linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
     lds_barrier_linear();
     if constexpr (CONV) {
         if (n0 < out.width[0]) {                                  // width[0] is a multiple of BN
-            conv_rows<BM, BN, 256, kOutRow>(lds, m0, dead, n0, out.ptr[0], out.width[0], conv);
+            conv_rows<BM, BN, kThr, kOutRow>(lds, m0, dead, n0, out.ptr[0], out.width[0], conv);
             return;
         }
     }
@@ -533,11 +536,11 @@ linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
     };
     if (dead == 0) {
 #pragma unroll
-        for (int i = 0; i < kChunks; ++i) store_chunk(i, (tid + i * 256) / kCpr, (tid + i * 256) % kCpr);
+        for (int i = 0; i < kChunks; ++i) store_chunk(i, (tid + i * kThr) / kCpr, (tid + i * kThr) % kCpr);
     } else {
 #pragma unroll
         for (int i = 0; i < kChunks; ++i)
-            if ((tid + i * 256) / kCpr >= dead) store_chunk(i, (tid + i * 256) / kCpr, (tid + i * 256) % kCpr);
+            if ((tid + i * kThr) / kCpr >= dead) store_chunk(i, (tid + i * kThr) / kCpr, (tid + i * kThr) % kCpr);
     }
 }
 
@@ -986,14 +989,14 @@ hipError_t launch_ring(const bf16_t *x, const bf16_t *w, const float *bias, cons
     return hipGetLastError();
 }
 
-template <int BM, int BN, bool CONV = false>
+template <int BM, int BN, bool CONV = false, int WM = 2, int WN = 2>
 hipError_t launch_wide(const bf16_t *x, const bf16_t *w, const float *bias, const bf16_t *res, const OutSplit &o, int64_t M, int64_t N, int64_t K,
                        hipStream_t stream, ConvTail conv = ConvTail{})
 {
     const int64_t tiles_n = N / BN, z_blocks = row_blocks(M, BM, false);
     const int64_t n_tiles = z_blocks * tiles_n + (CONV ? (row_blocks(M, BM, true) - z_blocks) * (o.width[0] / BN) : 0);
     conv.z_blocks = (int)z_blocks;
-    linear_wide_kernel<BM, BN, CONV><<<(unsigned)(8 * ((n_tiles + 7) / 8)), 256, 0, stream>>>(x, w, bias, res, o, M, N, K, (int)tiles_n, (int)n_tiles, conv);
+    linear_wide_kernel<BM, BN, CONV, WM, WN><<<(unsigned)(8 * ((n_tiles + 7) / 8)), 64 * WM * WN, 0, stream>>>(x, w, bias, res, o, M, N, K, (int)tiles_n, (int)n_tiles, conv);
     return hipGetLastError();
 }
 
@@ -1051,9 +1054,10 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     const bool wide = vec && N % 128 == 0 && a.M >= 128 && a.K % (2 * kWideBK) == 0 && a.K <= kToLdsLongestK;
     auto grid = [&](int bm, int bn) { return dim3((unsigned)((N + bn - 1) / bn), (unsigned)((a.M + bm - 1) / bm)); };
     const LinearTiles kind = linear_tiles(a.M, N, a.K, wide);
+    if (linear_wide256(a.M, N, a.K, wide)) return launch_wide<256, 256, false, 2, 4>(x, w, a.bias, res, o, a.M, N, a.K, stream);
     if (linear_wide192(a.M, N, a.K, wide, kind)) return launch_wide<192, 128>(x, w, a.bias, res, o, a.M, N, a.K, stream);
     switch (kind) {
-    case kTilesWide256: return launch_wide<256, 256>(x, w, a.bias, res, o, a.M, N, a.K, stream);
+    case kTilesWide256: return launch_wide<256, 256, false, 2, 4>(x, w, a.bias, res, o, a.M, N, a.K, stream);
     case kTilesWide128: return launch_wide<128, 128>(x, w, a.bias, res, o, a.M, N, a.K, stream);
     case kTiles128: linear_kernel<128, 128, 64><<<grid(128, 128), kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec); break;
     case kTiles64x128: linear_kernel<64, 128, 64><<<grid(64, 128), kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec); break;
@@ -1075,13 +1079,14 @@ hipError_t launch_linear_conv(const LinearArgs &a, hipStream_t stream)
     const ConvTail conv{a.conv_w, a.conv_b, static_cast<const bf16_t *>(a.conv_src), static_cast<bf16_t *>(a.conv_dst), (uint32_t)a.conv_L, 0};
     const int64_t N = a.width[0] + a.width[1];
 #define MAMBA_CONV(HOW, ...) return launch_##HOW<__VA_ARGS__, true>(x, w, nullptr, nullptr, o, a.M, N, a.K, stream, conv)
+    if (linear_conv_tiles(a.M, a.width[0], a.K, a.conv_k) == kConvWide256)
+        return launch_wide<256, 256, true, 2, 4>(x, w, nullptr, nullptr, o, a.M, N, a.K, stream, conv);
     switch (linear_conv_tiles(a.M, a.width[0], a.K, a.conv_k)) {
     case kConvRing64: MAMBA_CONV(ring, 64, 64, 2, 2, 4, 2);
     case kConvRing64x128: MAMBA_CONV(ring, 64, 128, 2, 4, 6, 1);
     case kConvRing128: MAMBA_CONV(ring, 128, 128, 2, 4, 4, 1);
     case kConvWide128: MAMBA_CONV(wide, 128, 128);
     case kConvWide192: MAMBA_CONV(wide, 192, 128);
-    case kConvWide256: MAMBA_CONV(wide, 256, 256);
     default: return hipErrorInvalidValue;
     }
 #undef MAMBA_CONV

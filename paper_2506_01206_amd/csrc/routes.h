@@ -93,14 +93,14 @@ inline LinearRing linear_ring(int64_t M, int64_t N, int64_t K, bool vector_out)
 // The way into a block on a context (x | z = u W_in^T, then the conv over time on x) in one launch: the tile whose product takes least,
 // by rounds of workgroups over the chip; or the product and the conv apart, where the rows that a tile of x shares with the one before
 // it cost more than the conv's launch (512 rows of 4096 channels: 320 128 x 128 tiles instead of 256), on rows that the few-row
-// kernels take, and on what the tiles cannot.  Fitted to 117 products of seven models, 64 to 32768 rows: the choice costs 1.0 % more
-// than the best of them on average, and the launch 13.7 % less than the two.  us, product + conv / the launch on 64 x 64 / 64 x 128 / 128 x 128
-// ring, 128 x 128 / 192 x 128 / 256 x 256 wide tiles (u, K):
-//     100 x 1536,  768   8.6 /  7.1*/  9.2 /   -  /   -  /   -  /   -       2048 x 1536,  768  20.5 / 28.6 / 33.0 / 22.1 / 18.5*/ 22.6 / 32.6
-//     333 x 1536,  768  11.6 /  8.7*/  9.6 / 11.2 / 13.8 / 15.7 / 30.8      8000 x 1536,  768  53.9 / 86.1 /100.5 / 64.2 / 51.0 / 47.3*/ 61.9
-//     600 x 1536,  768  12.7 / 10.2 / 10.1*/ 11.7 / 14.3 / 16.8 / 31.7     32768 x 1536,  768   216 /  332 /  387 /  245 /  215 /  187*/  194
-//    1000 x 1536,  768  15.5 / 16.2 / 17.7 / 12.2*/ 15.2 / 17.7 / 31.8      4000 x 4096, 2048   144 /  227 /  239 /  167 /  165 /  141 /  126*
-//     200 x 1024,  512   7.5 /  6.3*/  8.3 /  9.5 / 10.8 / 12.8 /   -       2048 x 4096, 2048  73.4*/  127 /  131 /  102 /  101 / 85.6 /  105
+// kernels take, and on what the tiles cannot.  Fitted to 179 products of seven models, 64 to 32768 rows: the choice costs 0.9 % more
+// than the best of them on average, and the launch 15 % less than the two.  us, product + conv / the launch on 64 x 64 / 64 x 128 / 128 x 128
+// ring, 128 x 128 / 192 x 128 / 256 x 256 wide tiles (D, K):
+//     100 x 1536,  768   8.3 /  6.9*/  9.1 /   -  /   -  /   -  /   -       2048 x 1536,  768  19.8 / 28.2 / 32.6 / 21.3 / 17.8*/ 22.1 / 27.0
+//     333 x 1536,  768  11.8 /  8.8*/  9.7 / 11.4 / 13.9 / 15.6 / 25.5      8000 x 1536,  768  52.4 / 85.4 / 99.1 / 60.7 / 50.1 / 46.0*/ 53.0
+//     600 x 1536,  768  12.7 / 10.2*/ 10.2 / 11.7 / 14.3 / 16.8 /   -      32768 x 1536,  768   216 /  331 /  387 /  241 /  219 /  189 /  175*
+//    1000 x 1536,  768  15.7 / 16.3 / 17.8 / 12.4*/ 15.2 / 17.7 / 26.3     16384 x 3072, 1536   329 /  541 /  562 /  403 /  388 /  323 /  301*
+//     200 x 1024,  512   7.5 /  6.3*/  8.3 /  9.5 / 10.8 / 12.8 /   -       2048 x 4096, 2048  72.8*/  127 /  131 /  102 /  101 / 85.6 /  105
 enum ConvTiles { kConvApart, kConvRing64, kConvRing64x128, kConvRing128, kConvWide128, kConvWide192, kConvWide256 };
 inline int64_t row_blocks(int64_t M, int64_t BM, bool conv)      // with the conv all but the first have kConvTaps - 1 rows that are another's
 {
@@ -114,7 +114,7 @@ inline ConvTiles linear_conv_tiles(int64_t M, int64_t D, int64_t K, int64_t taps
     struct Tile { ConvTiles kind; int64_t bm, bn, per_round; double launch, round, round_k, half, half_k; };
     const Tile all[6] = {{kConvRing64, 64, 64, 512, 2.6, 1.5, .0076, 1.1, .0051},    {kConvRing64x128, 64, 128, 256, 2.5, 2.5, .0067, 0, 0},
                          {kConvRing128, 128, 128, 256, 2.4, 3.4, .0085, 0, 0},       {kConvWide128, 128, 128, 512, 3.9, 2.0, .0172, 1.6, .0118},
-                         {kConvWide192, 192, 128, 512, 4.5, 4.6, .0205, 2.4, .0139}, {kConvWide256, 256, 256, 256, 6.6, 9.1, .0219, 0, 0}};
+                         {kConvWide192, 192, 128, 512, 4.5, 4.6, .0205, 2.4, .0139}, {kConvWide256, 256, 256, 256, 5.0, 6.8, .0220, 0, 0}};
     const double none = 1e30;
     auto us = [&](const Tile &t, bool conv) {
         const bool ring = t.kind <= kConvRing128;
@@ -136,7 +136,7 @@ inline ConvTiles linear_conv_tiles(int64_t M, int64_t D, int64_t K, int64_t taps
         const double c = us(t, true);
         if (c < best) best = c, kind = t.kind;
     }
-    return best <= apart ? kind : kConvApart;
+    return best <= 1.05 * apart ? kind : kConvApart;               // (the conv of a tile is cheaper than the model has it)
 }
 
 // Tile kernels for products that the few-row kernels do not take (linear.hip).
@@ -214,6 +214,26 @@ inline bool linear_wide192(int64_t M, int64_t N, int64_t K, bool wide, LinearTil
                            : other == kTilesWide128 ? rounds(tiles(128, 128), 512, 2.14, longk ? 1.5 : 1.3)
                                                     : rounds(tiles(128, 128), 768, longk ? 3.6 : 3.5, longk ? 2.7 : 2.6);
     return with < without;
+}
+
+// 256 x 256 tiles of eight wavefronts multiply faster than the others once every CU has one, which leaves the number of rounds: a launch's
+// microseconds and a round's, two workgroups to a CU taking six tenths of one where no CU has a second.  Fitted to 153 products of
+// seven models, 1000 to 32768 rows; taken where that is 4 % less than the 128- and 192-row tiles are thought to take, which in none of them
+// was slower than what linear_tiles and linear_wide192 choose.  us on that / on 256 x 256:
+//   16384 x  768, K = 1536   47.6 /  40.6      10000 x 3072, K =  768   54.0 /  49.4      16384 x 3072, K =  768   84.3 /  77.7
+//    5000 x 3072, K =  768   28.8 /  25.9       5000 x 6144, K = 1536   92.9 /  87.3      10000 x 2560, K = 5120  296.5 / 263.4
+//    8000 x  768, K = 1536   25.6*/  34.5      12000 x 3072, K =  768   61.4*/  70.4       8000 x 3072, K =  768   43.6*/  45.3
+inline bool linear_wide256(int64_t M, int64_t N, int64_t K, bool wide)
+{
+    if (!wide || M < 1000 || N % 256 != 0) return false;
+    auto us = [&](int64_t bm, int64_t bn, int64_t per, double launch, double round, double round_k) {
+        const int64_t t = ((M + bm - 1) / bm) * ((N + bn - 1) / bn), rest = t % per;
+        const double part = (double)rest / (double)per;
+        const double rounds = (double)(t / per) + (rest == 0 ? 0.0 : per == 512 && part <= 0.5 ? 0.62 : 0.7 + 0.3 * part);
+        return launch + rounds * (round + round_k * (double)K);
+    };
+    const double w128 = us(128, 128, 512, 1.9, 3.0, .0159), w192 = us(192, 128, 512, 1.1, 5.0, .0203);
+    return us(256, 256, 256, 0.4, 7.5, .0244) < 0.96 * (w128 < w192 ? w128 : w192);
 }
 
 // x_proj and dt_proj in one kernel (xdt.hip): rows per workgroup and column groups for M rows; 0 rows: two launches.

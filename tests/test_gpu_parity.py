@@ -1261,6 +1261,24 @@ def test_linear_192_row_tiles(m, M, N, K, splits):
     test_linear_against_oracle(m, M, N, K, splits)
 
 
+@pytest.mark.parametrize("M,N,K,splits", [(4097, 3072, 128, (1536, 1536)), (16385, 768, 256, None), (7936, 2048, 512, (600, 1448)), (5003, 3072, 384, None),
+                                          (2047, 8192, 128, None)])
+def test_linear_256_tiles(m, M, N, K, splits):
+    """256 x 256 tiles of eight wavefronts: full row blocks and moved ones, as few slabs of k as there may be, split outputs; and ten launches
+    that have to agree."""
+    test_linear_against_oracle(m, M, N, K, splits)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(79)
+    x = torch.randn(M, K, device=DEV, generator=g).bfloat16()
+    w = (torch.randn(N, K, device=DEV, generator=g) / K ** 0.5).bfloat16()
+    res = torch.randn(M, N, device=DEV, generator=g).bfloat16()
+    (first,) = m.mamba_linear_fwd(x, w, residual=res)
+    for _ in range(9):
+        out = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=DEV)
+        m.mamba_linear_fwd(x, w, residual=res, outs=[out])
+        assert torch.equal(out, first)
+
+
 @pytest.mark.parametrize("M,N,K,splits", [(641, 1280, 256, (640, 640)), (449, 2560, 1024, None), (704, 1856, 320, (600, 1256)),     # 64 x 64
                                           (1025, 1536, 384, (768, 768)), (1087, 1536, 448, None), (512, 3072, 768, (1536, 1536)),   # 64 x 128
                                           (2049, 1152, 384, None), (2175, 1152, 1536, (1144, 8)), (4096, 768, 832, None)])          # 128 x 128

@@ -18,6 +18,7 @@ extern "C" int row_tiles(int64_t M, int64_t N) { return mamba::linear_few_row_ti
 extern "C" int tiles(int64_t M, int64_t N, int64_t K, int wide) { return mamba::linear_tiles(M, N, K, wide); }
 extern "C" int ring(int64_t M, int64_t N, int64_t K, int vec) { return mamba::linear_ring(M, N, K, vec != 0); }
 extern "C" int conv_tiles(int64_t M, int64_t D, int64_t K, int64_t taps) { return mamba::linear_conv_tiles(M, D, K, taps); }
+extern "C" int wide256(int64_t M, int64_t N, int64_t K, int wide) { return mamba::linear_wide256(M, N, K, wide != 0); }
 extern "C" int64_t row_blocks(int64_t M, int64_t BM, int conv) { return mamba::row_blocks(M, BM, conv != 0); }
 extern "C" int wide192(int64_t M, int64_t N, int64_t K, int wide) { return mamba::linear_wide192(M, N, K, wide, mamba::linear_tiles(M, N, K, wide)); }
 extern "C" int xdt(int64_t M, int64_t d_inner, int64_t dt_rank, int64_t N, unsigned *groups)
@@ -41,6 +42,7 @@ def routes(tmp_path_factory):
     lib.tiles.argtypes = [i64, i64, i64, i32]
     lib.wide192.argtypes = [i64, i64, i64, i32]
     lib.ring.argtypes = [i64, i64, i64, i32]
+    lib.wide256.argtypes = [i64, i64, i64, i32]
     lib.conv_tiles.argtypes = [i64] * 4
     lib.row_blocks.argtypes, lib.row_blocks.restype = [i64, i64, i32], i64
     lib.xdt.argtypes = [i64, i64, i64, i64, ctypes.POINTER(ctypes.c_uint)]
@@ -174,8 +176,8 @@ def test_conv_in_the_way_into_a_block(routes):
     for kind, shapes in {r64: [(64, 64, 256), (189, 128, 256), (333, 1536, 768), (600, 512, 256), (64, 1 << 20, 256)],
                          r64x128: [(200, 4096, 2048), (100, 5120, 2560)], r128: [(1000, 1024, 256), (2003, 512, 256), (1000, 1536, 768)],
                          w128: [(1254, 1536, 256), (1264, 1536, 256), (2048, 1536, 768)],
-                         w192: [(1281, 1536, 384), (8000, 1536, 768), (32768, 1536, 768)],
-                         w256: [(4031, 2048, 384), (4048, 2048, 384), (4000, 4096, 2048)],
+                         w192: [(1281, 1536, 384), (8000, 1536, 768)],
+                         w256: [(4031, 2048, 384), (4048, 2048, 384), (4000, 4096, 2048), (10000, 1536, 768), (16384, 3072, 1536), (32768, 1536, 768)],
                          apart: [(63, 1536, 768), (333, 1536, 192), (333, 1536, 800), (333, 1500, 768), (512, 4096, 2048), (2048, 4096, 2048),
                                  (1 << 24, 128, 256), (333, (1 << 20) + 64, 768)]}.items():
         for s in shapes:
@@ -199,3 +201,15 @@ def test_conv_in_the_way_into_a_block(routes):
                 assert first == stored and m0 >= 0 and (r == 0 or first - m0 >= 3), (M, bm, r)
                 stored = m0 + bm
             assert stored == M and routes.row_blocks(M, bm, 0) == -(-M // bm)
+
+
+def test_256_tiles_by_rounds(routes):
+    """Products measured faster and slower on 256 x 256 tiles, those that the parity tests name for other tiles, and never without the
+    conditions."""
+    takes = lambda M, N, K: bool(routes.wide256(M, N, K, M >= 128 and N % 128 == 0 and K % 128 == 0))
+    for s in [(16384, 768, 1536), (10000, 3072, 768), (16384, 3072, 768), (32768, 3072, 768), (5000, 3072, 768), (5000, 6144, 1536), (10000, 2560, 5120)]:
+        assert takes(*s), s
+    for s in [(8000, 768, 1536), (12000, 3072, 768), (8000, 3072, 768), (8000, 512, 1024), (999, 10240, 2560), (16384, 896, 1536), (16384, 768, 1600),
+              (2977, 3072, 128), (4993, 2048, 384), (11905, 768, 1536), (12095, 768, 128), (3073, 6144, 128), (1025, 8192, 512), (1001, 10240, 640),
+              (2177, 1152, 1024), (4001, 768, 1536), (129, 32768, 128)]:
+        assert not takes(*s), s
