@@ -1058,7 +1058,11 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     if (linear_wide192(a.M, N, a.K, wide, kind)) return launch_wide<192, 128>(x, w, a.bias, res, o, a.M, N, a.K, stream);
     switch (kind) {
     case kTilesWide256: return launch_wide<256, 256, false, 2, 4>(x, w, a.bias, res, o, a.M, N, a.K, stream);
-    case kTilesWide128: return launch_wide<128, 128>(x, w, a.bias, res, o, a.M, N, a.K, stream);
+    case kTilesWide128:
+        // a long k where half of the CUs or more have one tile only: eight wavefronts there too.  us of four / eight: 6000 x 768, K = 1536 21.7 /
+        // 20.5, 8000 x 768 23.7 / 22.8, 4000 x 1024, K = 2048 26.7 / 24.8; 16384 x 512, K = 1024 (two to every CU) 22.8* / 23.3, 8000 x 3072, K = 768 45.9* / 47.9
+        if (a.K >= 1024 && tiles(128, 128) <= 384) return launch_wide<128, 128, false, 2, 4>(x, w, a.bias, res, o, a.M, N, a.K, stream);
+        return launch_wide<128, 128>(x, w, a.bias, res, o, a.M, N, a.K, stream);
     case kTiles128: linear_kernel<128, 128, 64><<<grid(128, 128), kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec); break;
     case kTiles64x128: linear_kernel<64, 128, 64><<<grid(64, 128), kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec); break;
     case kTiles64Deep: linear_kernel<64, 64, 256><<<grid(64, 64), kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec); break;
