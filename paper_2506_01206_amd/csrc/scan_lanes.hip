@@ -615,6 +615,8 @@ double lanes_ns(int64_t batch, int64_t L, int64_t D, double six, double four, do
 // have gained more by it than this one, so that between about 7000 tokens of 1536 channels (float32: 2700) and the line they are
 // ahead by up to 9 % (float32: 31 %).  But a call that this kernel took needs no workspace, and one made without would be
 // refused if the line moved down; a whole block, which brings its workspace and is bf16, could be told apart, and is not.
+// Down to 33 tokens (a call of fewer keeps the kernel that mamba_scan_kernel has always named for it; a block takes them too): one super-step
+// against three launches, 1 x 40 x 1536 6.1 / 16.0, 1 x 40 x 256 3.9 / 15.8, 2 x 40 x 1536 10.8 / 16.4, 1 x 40 x 4096 15.4 / 16.3.
 // us, lanes / two-pass, bf16 | float32, one session, four sets of operands in turn (on one set, which stays in the last-level
 // cache, 1 x 8192 x 1536 takes 81 | 110 here); * what the line takes:
 //   1 x  600 x  768  11.1*/ 20.8 | 12.0*/ 20.9       1 x 2048 x 1536  25.8*/ 35.5 | 31.4*/ 35.9       1 x   64 x 4096  15.4*/ 17.3 |  15.6*/ 17.0
@@ -625,7 +627,7 @@ double lanes_ns(int64_t batch, int64_t L, int64_t D, double six, double four, do
 //   4 x 1000 x  768  28.3*/ 35.7 | 34.2*/ 35.5       1 x 2000 x 2048  37.6*/ 43.5 | 43.0*/ 41.6       2 x 3000 x 1536  75.2*/ 73.2 | 98.0*/ 68.4
 bool scan_lanes_applies(int64_t batch, int64_t L, int64_t D, int64_t N)
 {
-    if (N != kN || D % 2 != 0 || D < 6 || L < 64 || batch > 65535) return false;
+    if (N != kN || D % 2 != 0 || D < 6 || L <= 32 || batch > 65535) return false;
     const double two_pass_ns = 24000.0 + 9.8 * (double)L * ((double)batch * (double)D / 1536.0);
     return lanes_ns(batch, L, D, 11.6, 9.7, 12.5) < two_pass_ns;
 }
@@ -636,11 +638,12 @@ bool scan_lanes_applies(int64_t batch, int64_t L, int64_t D, int64_t N)
 //   1 x 10500 x 1536 260 / 243*      2 x 4000 x 1536 205 / 196*      3 x 3000 x 1536 241 / 219*      1 x  8000 x 1024 140 / 133*      1 x 6000 x 4096 545* / 554
 //   1 x 16000 x 1536 368 / 346*      2 x 8000 x 1536 367 / 350*      4 x 1000 x 1536 127*/ 125       1 x 10000 x  768 134*/ 143       1 x 3000 x 2048 133 / 127*
 //   1 x 20000 x 1536 458 / 437*      4 x 8000 x 1536 634*/ 724       8 x  500 x 1536 125*/ 139       1 x  9000 x 3072 537 / 518*      2 x 1500 x 2048 133* / 139
+//   1 x    16 x 1536  25 /  21*      1 x   40 x 1536  36 /  22*      2 x   40 x 1536  37 /  28*      4 x   40 x 1536  40*/  39       1 x    2 x 1536  20*/ 20
 //   1 x 32768 x 1536 634*/ 744       4 x 4000 x 1536 370*/ 362       8 x 2000 x 1536 369*/ 377       1 x  6000 x  512  88*/ 81
 bool scan_lanes_in_block(int64_t batch, int64_t L, int64_t D, int64_t N)
 {
     if (scan_kernel_choice(batch, L, D, N) != kScanChunked) return scan_kernel_choice(batch, L, D, N) == kScanLanes;
-    if (N != kN || D % 2 != 0 || D < 6 || L < 64 || batch > 65535 || (double)batch * (double)L * (double)D > 32e6) return false;
+    if (N != kN || D % 2 != 0 || D < 6 || L < 4 || batch > 65535 || (double)batch * (double)L * (double)D > 32e6) return false;
     const double two_pass_ns = 24000.0 + 10.0 * (double)L * ((double)batch * (double)D / 1536.0);
     return lanes_ns(batch, L, D, 9.9, 8.3, 10.7) < two_pass_ns - 2000.0;
 }
@@ -703,7 +706,7 @@ template <typename T> hipError_t launch_lanes_io(const ScanArgs &a, hipStream_t 
 
 bool scan_lanes_takes_low_dt(int64_t batch, int64_t L, int64_t D, int64_t N, int64_t dt_rank)
 {
-    return scan_kernel_choice(batch, L, D, N) == kScanLanes && L <= 64 * lanes_tau(batch, L, D) && dt_rank % 8 == 0 && dt_rank <= kLowRank;
+    return scan_lanes_in_block(batch, L, D, N) && L <= 64 * lanes_tau(batch, L, D) && dt_rank % 8 == 0 && dt_rank <= kLowRank;
 }
 
 hipError_t launch_scan_lanes(const ScanArgs &a, hipStream_t stream)

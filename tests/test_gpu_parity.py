@@ -211,7 +211,7 @@ def test_scan_single_pass_shapes(m, io, N, B, L, D):
 
 
 @pytest.mark.parametrize("io", [synth.F32, synth.BF16])
-@pytest.mark.parametrize("B,L,D", [(1, 64, 6), (1, 255, 512), (2, 257, 254), (1, 1025, 510),          # two channels to a workgroup
+@pytest.mark.parametrize("B,L,D", [(1, 33, 256), (1, 47, 1000), (2, 63, 1536), (1, 64, 6), (1, 255, 512), (2, 257, 254), (1, 1025, 510),          # two channels to a workgroup
                                    (1, 256, 1022), (1, 65, 2046), (3, 700, 330), (1, 1300, 1022),         # four
                                    (1, 200, 1534), (1, 256, 3072), (1, 300, 1532),                        # six
                                    (1, 257, 1020), (1, 384, 1022), (1, 385, 1022), (2, 513, 510), (1, 768, 1000), (1, 769, 1000),   # 6 and 8 tokens to a
@@ -1511,7 +1511,8 @@ def test_block_conv_in_the_way_in(m, B, L, dm, D):
     assert torch.equal(s, state1) and torch.equal(m.mamba_block_workspace_layout(blk, B, L, ws)["x_c"], xc.view(B * L, D))
 
 
-@pytest.mark.parametrize("B,L,dm,D,R", [(1, 64, 64, 64, 8), (3, 65, 64, 96, 16), (1, 256, 64, 512, 24), (1, 256, 128, 1000, 40),      # 2 or 4 channels
+@pytest.mark.parametrize("B,L,dm,D,R", [(1, 4, 64, 256, 16), (1, 17, 64, 1536, 48), (2, 33, 64, 768, 24), (1, 3, 64, 256, 16),   # shorter than a call's own
+                                        (1, 64, 64, 64, 8), (3, 65, 64, 96, 16), (1, 256, 64, 512, 24), (1, 256, 128, 1000, 40),      # 2 or 4 channels
                                         (1, 255, 64, 1536, 48), (1, 257, 64, 1536, 64), (1, 511, 64, 1000, 56), (1, 512, 64, 1528, 48),  # 4 or 6
                                         (1, 513, 64, 1536, 48), (1, 300, 64, 1536, 72)])                                                # not taken
 def test_block_dt_projection_in_the_scan(m, B, L, dm, D, R):
