@@ -683,15 +683,18 @@ template <typename T, int G, int TAU> hipError_t launch_lanes(const ScanArgs &a,
 //    200 x 1536  7.25*/ 8.37 / 9.05     400 x 1536 10.45 / 12.56 / 9.84*    1000 x 1536 17.06 / 16.92 / 15.49*     700 x 1000 10.68 / 10.33*/ 11.66
 //    300 x 1536 10.42 / 8.79*/ 9.48     600 x 1536 13.49 / 12.69*/14.70     1100 x 1536 19.82 / 17.06*/ 19.72      350 x 1536 float32 11.43 / 9.75*/ 10.70
 //    384 x 1536 10.51 / 9.19*/ 9.83     768 x 1536 13.73 / 13.01*/14.92     1900 x 1536 29.56 / 26.07 / 25.83*     700 x 1536 float32 16.88 / 16.21*/ 18.23
-int lanes_tau(int64_t batch, int64_t L, int64_t D)
+// In float32, where a super-step's B and C are not requested ahead, one super-step more costs more; us with 6 / 8, bf16 | float32:
+//   2251 x  488, batch 6  82.6*/ 82.8 | 108.6 / 107.2*     2107 x 1392, batch 2  55.7*/ 57.4 | 77.4 / 76.2*     2101 x 504, batch 2  25.1*/ 25.6 | 28.5 / 27.9*
+//   2682 x  456, batch 3  34.1*/ 36.3 |  42.7 / 42.4*      1124 x 2304           32.1*/ 36.6 | 38.6*/ 42.5
+int lanes_tau(int64_t batch, int64_t L, int64_t D, int io)
 {
     if (L <= 256 || lanes_channels(batch, L, D) == 2) return 4;
-    return 4.1 * (double)((L + 383) / 384) < 0.95 * 5.3 * (double)((L + 511) / 512) ? 6 : 8;
+    return 4.1 * (double)((L + 383) / 384) < (io == kIoBf16 ? 0.95 : 0.9) * 5.3 * (double)((L + 511) / 512) ? 6 : 8;
 }
 
 template <typename T> hipError_t launch_lanes_io(const ScanArgs &a, hipStream_t stream)
 {
-    switch (10 * lanes_channels(a.batch, a.L, a.D) + lanes_tau(a.batch, a.L, a.D)) {
+    switch (10 * lanes_channels(a.batch, a.L, a.D) + lanes_tau(a.batch, a.L, a.D, a.io)) {
     case 24: return launch_lanes<T, 2, 4>(a, stream);
     case 44: return launch_lanes<T, 4, 4>(a, stream);
     case 46: return launch_lanes<T, 4, 6>(a, stream);
@@ -706,7 +709,7 @@ template <typename T> hipError_t launch_lanes_io(const ScanArgs &a, hipStream_t 
 
 bool scan_lanes_takes_low_dt(int64_t batch, int64_t L, int64_t D, int64_t N, int64_t dt_rank)
 {
-    return scan_lanes_in_block(batch, L, D, N) && L <= 64 * lanes_tau(batch, L, D) && dt_rank % 8 == 0 && dt_rank <= kLowRank;
+    return scan_lanes_in_block(batch, L, D, N) && L <= 64 * lanes_tau(batch, L, D, kIoBf16) && dt_rank % 8 == 0 && dt_rank <= kLowRank;
 }
 
 hipError_t launch_scan_lanes(const ScanArgs &a, hipStream_t stream)
