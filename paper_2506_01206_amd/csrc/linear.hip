@@ -301,6 +301,10 @@ __device__ __forceinline__ void conv_rows(const unsigned char *tile, int64_t m0,
 // 3072, K = 768 24.9 / 21.9, 16384 x 3072 83.8 / 77.4, 32768 x 3072 179 / 170, 8000 x 768, K = 1536 39.8 / 33.4, 8000 x 4096, K = 1024 68.3 / 64.9.)
 // (With four wavefronts it also runs 128 x 128 and 192 x 128 tiles, two workgroups to a CU, for products too small to give every CU
 // a 256-row tile, or that leave CUs without one: the feeding scheme below, not the tile size, is what those gain from.)
+// (And 256 x 192 tiles, eight wavefronts of 64 x 96, where those leave fewer CUs idle in the last round: 32768 x 768, K = 1536 is two whole rounds
+// instead of one and a half of 256 x 256, 79.6 -> 75.1 us; a round of them takes six sevenths of one of 256 x 256 for three quarters of the
+// products.  With the conv, whose epilogue leaves a quarter of the threads idle there, they are slower than the others throughout: one block of
+// 8000 x 1536 188 -> 200 us, of 32768 645 -> 674 with both products on them.)
 //
 // Operands go from memory straight into LDS (global_load_lds_dwordx4: lane l of a wavefront lands at
 // M0 + 16 l, so one instruction fills eight 128-byte rows): no staging registers, and none of the LDS
@@ -1054,6 +1058,7 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     const bool wide = vec && N % 128 == 0 && a.M >= 128 && a.K % (2 * kWideBK) == 0 && a.K <= kToLdsLongestK;
     auto grid = [&](int bm, int bn) { return dim3((unsigned)((N + bn - 1) / bn), (unsigned)((a.M + bm - 1) / bm)); };
     const LinearTiles kind = linear_tiles(a.M, N, a.K, wide);
+    if (linear_wide256x192(a.M, N, a.K, vec != 0)) return launch_wide<256, 192, false, 4, 2>(x, w, a.bias, res, o, a.M, N, a.K, stream);
     if (linear_wide256(a.M, N, a.K, wide)) return launch_wide<256, 256, false, 2, 4>(x, w, a.bias, res, o, a.M, N, a.K, stream);
     if (linear_wide192(a.M, N, a.K, wide, kind)) return launch_wide<192, 128>(x, w, a.bias, res, o, a.M, N, a.K, stream);
     switch (kind) {
@@ -1083,9 +1088,8 @@ hipError_t launch_linear_conv(const LinearArgs &a, hipStream_t stream)
     const ConvTail conv{a.conv_w, a.conv_b, static_cast<const bf16_t *>(a.conv_src), static_cast<bf16_t *>(a.conv_dst), (uint32_t)a.conv_L, 0};
     const int64_t N = a.width[0] + a.width[1];
 #define MAMBA_CONV(HOW, ...) return launch_##HOW<__VA_ARGS__, true>(x, w, nullptr, nullptr, o, a.M, N, a.K, stream, conv)
-    if (linear_conv_tiles(a.M, a.width[0], a.K, a.conv_k) == kConvWide256)
-        return launch_wide<256, 256, true, 2, 4>(x, w, nullptr, nullptr, o, a.M, N, a.K, stream, conv);
     switch (linear_conv_tiles(a.M, a.width[0], a.K, a.conv_k)) {
+    case kConvWide256: return launch_wide<256, 256, true, 2, 4>(x, w, nullptr, nullptr, o, a.M, N, a.K, stream, conv);
     case kConvRing64: MAMBA_CONV(ring, 64, 64, 2, 2, 4, 2);
     case kConvRing64x128: MAMBA_CONV(ring, 64, 128, 2, 4, 6, 1);
     case kConvRing128: MAMBA_CONV(ring, 128, 128, 2, 4, 4, 1);

@@ -223,17 +223,35 @@ inline bool linear_wide192(int64_t M, int64_t N, int64_t K, bool wide, LinearTil
 //   16384 x  768, K = 1536   47.6 /  40.6      10000 x 3072, K =  768   54.0 /  49.4      16384 x 3072, K =  768   84.3 /  77.7
 //    5000 x 3072, K =  768   28.8 /  25.9       5000 x 6144, K = 1536   92.9 /  87.3      10000 x 2560, K = 5120  296.5 / 263.4
 //    8000 x  768, K = 1536   25.6*/  34.5      12000 x 3072, K =  768   61.4*/  70.4       8000 x 3072, K =  768   43.6*/  45.3
+inline double wide_tiles_us(int64_t M, int64_t N, int64_t K, int64_t bm, int64_t bn, int64_t per, double launch, double round, double round_k, double first)
+{
+    const int64_t t = ((M + bm - 1) / bm) * ((N + bn - 1) / bn), rest = t % per;
+    const double part = (double)rest / (double)per;
+    const double rounds = (double)(t / per) + (rest == 0 ? 0.0 : per == 512 && part <= 0.5 ? 0.62 : first + (1.0 - first) * part);
+    return launch + rounds * (round + round_k * (double)K);
+}
+inline double wide128_us(int64_t M, int64_t N, int64_t K) { return wide_tiles_us(M, N, K, 128, 128, 512, 1.9, 3.0, .0159, .7); }
+inline double wide192_us(int64_t M, int64_t N, int64_t K) { return wide_tiles_us(M, N, K, 192, 128, 512, 1.1, 5.0, .0203, .7); }
+inline double wide256_us(int64_t M, int64_t N, int64_t K) { return wide_tiles_us(M, N, K, 256, 256, 256, 0.4, 7.5, .0244, .7); }
 inline bool linear_wide256(int64_t M, int64_t N, int64_t K, bool wide)
 {
     if (!wide || M < 1000 || N % 256 != 0) return false;
-    auto us = [&](int64_t bm, int64_t bn, int64_t per, double launch, double round, double round_k) {
-        const int64_t t = ((M + bm - 1) / bm) * ((N + bn - 1) / bn), rest = t % per;
-        const double part = (double)rest / (double)per;
-        const double rounds = (double)(t / per) + (rest == 0 ? 0.0 : per == 512 && part <= 0.5 ? 0.62 : 0.7 + 0.3 * part);
-        return launch + rounds * (round + round_k * (double)K);
-    };
-    const double w128 = us(128, 128, 512, 1.9, 3.0, .0159), w192 = us(192, 128, 512, 1.1, 5.0, .0203);
-    return us(256, 256, 256, 0.4, 7.5, .0244) < 0.96 * (w128 < w192 ? w128 : w192);
+    const double w128 = wide128_us(M, N, K), w192 = wide192_us(M, N, K);
+    return wide256_us(M, N, K) < 0.96 * (w128 < w192 ? w128 : w192);
+}
+
+// 256 x 192 tiles of eight wavefronts, one to a CU, by the same count of rounds, where that is less than for all the others; asked before
+// them.  Of 83 products, 1000 to 32768 rows, these get them; us on the others / on them (24000 x 768, K = 768 and 6000 x 768, for which they
+// are thought slower: 32.7 / 38.3, 14.8 / 18.6):
+//   16384 x 1536, K =  768   58.8 /  44.6     32768 x 1152, K = 2304  170.5 / 153.6     16384 x 768, K =  768   25.1 /  23.8     8000 x 1536, K = 3072   70.4 /  66.3
+//    4096 x 3072, K =  768   25.3 /  23.9     16384 x 1536, K = 3072  144.8 / 135.2     16384 x 768, K = 1536   40.0 /  38.0     2500 x 3840, K = 1920   44.7 /  44.1
+//    8000 x 1152, K = 2304   48.4 /  44.1     16384 x 1152, K = 2304   91.1 /  87.0     32768 x 768, K =  768   45.4 /  44.6     6000 x 1536, K = 3072   62.5 /  57.1
+//    4096 x 6144, K = 1536   81.4 /  81.9     24000 x 1536, K = 3072  201.3 / 196.2     32768 x 768, K = 1536   79.6 /  75.1
+inline bool linear_wide256x192(int64_t M, int64_t N, int64_t K, bool vector_out)
+{
+    if (!vector_out || M < 1000 || N % 192 != 0 || K % 128 != 0 || K > kToLdsLongestK) return false;
+    const double own = wide_tiles_us(M, N, K, 256, 192, 256, 0.5, 7.5, .0195, .66);
+    return own < .99 * wide128_us(M, N, K) && own < wide192_us(M, N, K) && (N % 256 != 0 || own < .99 * wide256_us(M, N, K));
 }
 
 // x_proj and dt_proj in one kernel (xdt.hip): rows per workgroup and column groups for M rows; 0 rows: two launches.

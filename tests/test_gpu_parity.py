@@ -1279,6 +1279,14 @@ def test_linear_256_tiles(m, M, N, K, splits):
         assert torch.equal(out, first)
 
 
+@pytest.mark.parametrize("M,N,K,splits", [(3713, 3264, 128, None), (3840, 3264, 256, (1000, 2264)), (5761, 2112, 384, None), (1921, 6144, 384, (3072, 3072)),
+                                          (7000, 1728, 128, (1720, 8))])
+def test_linear_256_x_192_tiles(m, M, N, K, splits):
+    """256 x 192 tiles: a last row block of one row, a full one and in between, two slabs of k and more, outputs split inside a tile; and the launches
+    that have to agree."""
+    test_linear_256_tiles(m, M, N, K, splits)
+
+
 @pytest.mark.parametrize("M,N,K,splits", [(641, 1280, 256, (640, 640)), (449, 2560, 1024, None), (704, 1856, 320, (600, 1256)),     # 64 x 64
                                           (1025, 1536, 384, (768, 768)), (1087, 1536, 448, None), (512, 3072, 768, (1536, 1536)),   # 64 x 128
                                           (2049, 1152, 384, None), (2175, 1152, 1536, (1144, 8)), (4096, 768, 832, None)])          # 128 x 128

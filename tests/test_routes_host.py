@@ -19,6 +19,7 @@ extern "C" int tiles(int64_t M, int64_t N, int64_t K, int wide) { return mamba::
 extern "C" int ring(int64_t M, int64_t N, int64_t K, int vec) { return mamba::linear_ring(M, N, K, vec != 0); }
 extern "C" int conv_tiles(int64_t M, int64_t D, int64_t K, int64_t taps) { return mamba::linear_conv_tiles(M, D, K, taps); }
 extern "C" int wide256(int64_t M, int64_t N, int64_t K, int wide) { return mamba::linear_wide256(M, N, K, wide != 0); }
+extern "C" int wide256x192(int64_t M, int64_t N, int64_t K, int vec) { return mamba::linear_wide256x192(M, N, K, vec != 0); }
 extern "C" int64_t row_blocks(int64_t M, int64_t BM, int conv) { return mamba::row_blocks(M, BM, conv != 0); }
 extern "C" int wide192(int64_t M, int64_t N, int64_t K, int wide) { return mamba::linear_wide192(M, N, K, wide, mamba::linear_tiles(M, N, K, wide)); }
 extern "C" int xdt(int64_t M, int64_t d_inner, int64_t dt_rank, int64_t N, unsigned *groups)
@@ -43,6 +44,7 @@ def routes(tmp_path_factory):
     lib.wide192.argtypes = [i64, i64, i64, i32]
     lib.ring.argtypes = [i64, i64, i64, i32]
     lib.wide256.argtypes = [i64, i64, i64, i32]
+    lib.wide256x192.argtypes = [i64, i64, i64, i32]
     lib.conv_tiles.argtypes = [i64] * 4
     lib.row_blocks.argtypes, lib.row_blocks.restype = [i64, i64, i32], i64
     lib.xdt.argtypes = [i64, i64, i64, i64, ctypes.POINTER(ctypes.c_uint)]
@@ -201,6 +203,16 @@ def test_conv_in_the_way_into_a_block(routes):
                 assert first == stored and m0 >= 0 and (r == 0 or first - m0 >= 3), (M, bm, r)
                 stored = m0 + bm
             assert stored == M and routes.row_blocks(M, bm, 0) == -(-M // bm)
+
+
+def test_256_x_192_tiles_by_rounds(routes):
+    """Products measured faster and slower on 256 x 192 tiles, those that the parity tests name for other tiles, and never without the conditions."""
+    for s in [(16384, 1536, 768), (32768, 768, 1536), (16384, 768, 1536), (4096, 3072, 768), (2500, 3840, 1920), (8000, 1152, 2304), (24000, 1536, 3072)]:
+        assert routes.wide256x192(*s, 1) and not routes.wide256x192(*s, 0), s
+    for s in [(8000, 768, 1536), (6000, 768, 768), (24000, 768, 768), (8000, 3072, 768), (32768, 3072, 768), (32768, 6144, 1536), (10000, 1536, 3072),
+              (999, 768, 768), (16384, 1600, 768), (16384, 1536, 832), (16384, 1536, (1 << 28) + 128),
+              (8000, 3072, 256), (11905, 768, 1536), (12095, 768, 128), (4097, 3072, 128), (16385, 768, 256), (2977, 3072, 128), (5003, 3072, 384)]:
+        assert not routes.wide256x192(*s, 1), s
 
 
 def test_256_tiles_by_rounds(routes):
