@@ -241,17 +241,18 @@ inline bool linear_wide256(int64_t M, int64_t N, int64_t K, bool wide)
 }
 
 // 256 x 192 tiles of eight wavefronts, one to a CU, by the same count of rounds, where that is less than for all the others; asked before
-// them.  Of 83 products, 1000 to 32768 rows, these get them; us on the others / on them (24000 x 768, K = 768 and 6000 x 768, for which they
-// are thought slower: 32.7 / 38.3, 14.8 / 18.6):
-//   16384 x 1536, K =  768   58.8 /  44.6     32768 x 1152, K = 2304  170.5 / 153.6     16384 x 768, K =  768   25.1 /  23.8     8000 x 1536, K = 3072   70.4 /  66.3
-//    4096 x 3072, K =  768   25.3 /  23.9     16384 x 1536, K = 3072  144.8 / 135.2     16384 x 768, K = 1536   40.0 /  38.0     2500 x 3840, K = 1920   44.7 /  44.1
-//    8000 x 1152, K = 2304   48.4 /  44.1     16384 x 1152, K = 2304   91.1 /  87.0     32768 x 768, K =  768   45.4 /  44.6     6000 x 1536, K = 3072   62.5 /  57.1
-//    4096 x 6144, K = 1536   81.4 /  81.9     24000 x 1536, K = 3072  201.3 / 196.2     32768 x 768, K = 1536   79.6 /  75.1
+// them.  us on the others / on them, products in a row and a block whose out_proj it is:
+//   16384 x 1536, K =  768   58.8 /  44.6     32768 x 1152, K = 2304  170.5 / 153.6     16384 x 768, K =  768   25.1 /  23.8      4096 x 3072, K =  768   25.3 /  23.9
+//   32768 x  768, K = 1536   79.6 /  75.1, block 610 / 602              16384 x 768, K = 1536   40.0 /  38.0, block 330 / 327
+//    4096 x 6144, K = 1536   81.4 /  81.9     16384 x 1536, K = 3072  144.8 / 135.2, block 796 / 788          6000 x  768, K =  768   14.8*/  18.6
+// Three hundredths short of 192 x 128 tiles, of which two to a CU hide each other's residual: 6000 x 1536, K = 3072 (1.9 short) is 62.5 / 57.1 in
+// a row, but 335 / 339 in a block, 16384 x 1152, K = 2304 91.1 / 87.0 and 556* / 559.  Widths that those cannot take have slower tiles to
+// compare with: 16384 x 576, K = 1152 block 284 / 267, 20000 x 576 360 / 330.
 inline bool linear_wide256x192(int64_t M, int64_t N, int64_t K, bool vector_out)
 {
     if (!vector_out || M < 1000 || N % 192 != 0 || K % 128 != 0 || K > kToLdsLongestK) return false;
     const double own = wide_tiles_us(M, N, K, 256, 192, 256, 0.5, 7.5, .0195, .66);
-    return own < .99 * wide128_us(M, N, K) && own < wide192_us(M, N, K) && (N % 256 != 0 || own < .99 * wide256_us(M, N, K));
+    return own < .99 * wide128_us(M, N, K) && own < (N % 128 == 0 ? .97 : 1.0) * wide192_us(M, N, K) && (N % 256 != 0 || own < .99 * wide256_us(M, N, K));
 }
 
 // x_proj and dt_proj in one kernel (xdt.hip): rows per workgroup and column groups for M rows; 0 rows: two launches.
