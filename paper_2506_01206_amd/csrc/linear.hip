@@ -313,7 +313,7 @@ __device__ __forceinline__ void conv_rows(const unsigned char *tile, int64_t m0,
 // on the memory side of the load, which makes the fragment reads (32 rows, one slot each) conflict-free.
 // The instruction is issued from inline assembly so that the compiler's wait-count pass does not see an LDS
 // write it cannot place (it would wait for every load in flight before each LDS read); the waits are explicit:
-// vmcnt(0) before the one barrier per slab.  Slabs of 64 k alternate between two stages.  The barrier of
+// vmcnt(0) and lgkmcnt(0) before the one barrier per slab.  Slabs of 64 k alternate between two stages.  The barrier of
 // slab s comes when its last fragments have been read, a quarter before its end; slab s + 2 is requested
 // right after it into the stage just freed and has a whole slab of multiplications to arrive.
 // The product is formed transposed (w fragments as the row operand), so that a lane's four accumulators
@@ -425,8 +425,9 @@ linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
     };
     // Slab s, read from stage s % 2, whose first fragments are already in f0.  Four quarters of MT NT MFMAs; the
     // fragments of a quarter are read during the one before it (the instruction groups keep the scheduler from
-    // moving the reads next to their use).  After the third quarter every read of this stage has been issued: the
-    // slab s + 1 must have landed by then (requested a slab ago), the barrier publishes it, the stage of slab s is
+    // moving the reads next to their use).  After the third quarter every read of this stage has been issued, and is waited
+    // for: behind the barrier other wavefronts' loads overwrite the stage, which keep no order with a read that is still
+    // under way.  The slab s + 1 must have landed by then (requested a slab ago), the barrier publishes it, the stage of slab s is
     // free, and the last quarter requests slab s + 2 into it (REQUEST) and reads the first fragments of slab s + 1
     // (NEXT) between its multiplications.
     Frags f0, f1;
@@ -450,7 +451,8 @@ linear_wide_kernel(const bf16_t *x, const bf16_t *w, const float *__restrict__ b
         MAMBA_WIDE_QUARTER(3, f0, f1)
 #undef MAMBA_WIDE_QUARTER
 #undef MAMBA_WIDE_SPREAD
-        __builtin_amdgcn_s_waitcnt(0x0F70);                       // vmcnt(0): this wavefront's part of slab s + 1 is in LDS
+        // vmcnt(0) lgkmcnt(0): this wavefront's part of slab s + 1 is in LDS, its fragments of slab s are in registers
+        __builtin_amdgcn_s_waitcnt(0x0070);
         lds_barrier_linear();
 #define MAMBA_WIDE_LAST(A, FROM, TO)                                                                                  \
         if constexpr (REQUEST) request(k_next, P * kStage, FROM(), TO());                                             \
