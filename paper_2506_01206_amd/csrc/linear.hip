@@ -45,8 +45,6 @@ __device__ __forceinline__ void lds_barrier_linear()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-constexpr int64_t kTilesResident = 256;                           // one workgroup per CU
-
 struct OutSplit {
     bf16_t *ptr[3];
     int64_t width[3];
@@ -1016,71 +1014,40 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
         o.width[s] = a.width[s];
     }
     const int64_t N = a.width[0] + a.width[1] + a.width[2];
-    const int vec = (a.width[0] % 8 == 0 && a.width[1] % 8 == 0 && a.width[2] % 8 == 0) ? 1 : 0;
+    const int vec = linear_vector_out(a.width) ? 1 : 0;
     const bf16_t *x = static_cast<const bf16_t *>(a.x), *w = static_cast<const bf16_t *>(a.w);
     const bf16_t *res = static_cast<const bf16_t *>(a.residual);
-    auto tiles = [&](int64_t bm, int64_t bn) { return ((N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
-#define MAMBA_FEW(...) return launch_few<__VA_ARGS__>(x, w, a.bias, res, o, a.M, N, a.K, stream)
     if (a.norm_w) return launch_draft_in(a, stream);
-    // Few output tiles (linear_few_kernel): the tile that makes one round of workgroups on 256 CUs, from 16 rows x 8 columns up; the
-    // tile kernels take over where 32 x 32 comes to more than two or three to a CU.  us on 16 x 8 / 16 x 16 / 32 x 16 / 32 x 32 / 64 x 32 /
-    // the best tile kernel:
-    //    12 x  768, K = 1536  3.1 / 3.3 / 3.7 /   -  /   -  / 10.3      333 x   80, K = 1536  3.3 / 3.6 /  4.1 /  4.9 /   -  / 11.4
-    //   128 x  768, K = 1536  4.8 / 4.3 / 4.1 /  4.6 /  6.4 / 10.9      333 x  768, K = 1536   -  / 6.3 /  6.8 /  6.2 /  6.5 / 10.9
-    //   700 x  768, K = 1536   -  / 10.6/ 10.1/  8.4 / 11.5 / 11.0     1000 x  768, K = 1536   -  / 13.7/ 12.1 /  9.0 / 12.0 / 11.8
-    //   128 x 3072, K =  768   -  / 5.3 / 5.0 /  5.1 /  5.6 /  7.0      256 x 3072, K =  768   -  / 8.2 /  8.2 /  7.7 /  9.5 /  7.1
-    //   256 x 2048, K =  512   -  / 5.1 / 4.6 /  4.2 /  4.4 /  5.8      512 x 2048, K =  512   -  / 8.0 /  7.1 /  6.5 /  7.3 /  6.0
-    //   512 x  512, K = 1024   -  / 5.2 / 4.7 /  3.9 /  5.1 /  8.4      700 x 1024, K = 2048   -  / 18.3/ 16.5 / 12.1 / 15.0 / 13.3
-    //   256 x 1536, K = 3072   -  / 15.3/ 12.7/ 12.9 / 10.3 / 18.1      256 x 2048, K = 4096   -  / 29.2/ 24.2 / 21.4 / 18.0 / 28.3
-    //   200 x 2560, K = 5120   -  / 40.9/ 37.3/ 37.4 / 36.4 / 34.9      256 x 1536, K =   48   -  / 3.1 /  2.9 /   -  /   -  /  3.1
-    // How many 32 x 32 (`most`), between k of 512 and 1024; us on 32 x 32 / the tile kernels for k = 576, 640, 768, 896, 960:
-    //   608 tiles (256 x 2432)  7.2 / 7.6    7.2 / 7.6    7.4 / 7.9    7.6 / 9.1    7.7 / 9.2
-    //   672 tiles (224 x 3072)  7.1 / 7.1    7.2 / 7.1    7.5 / 7.1    7.7 / 8.3    7.8 / 8.3
-    //   768 tiles (768 x 1024)  7.1 / 7.1    7.2 / 7.2    7.7 / 7.2    7.7 / 8.4    7.9 / 8.4
-    // So 608 is where the two meet for a k of 768; for k between that and 1024 32 x 32 stays ahead up to 768 tiles, by 4 to 8 %.
-    // Up to 16 rows against very many columns (the LM head on a draft position): 16 columns each, any number of rounds, up to a k of
-    // four trips; us on that / 64 x 64 tiles: 1 x 50280, K = 768 13.3 / 15.7, 12 x 50280 15.1 / 17.0, 12 x 16384 6.7 / 10.0, 12 x 32768,
-    // K = 2048 25.0 / 30.4 (12 x 50280, K = 2560 54.3 / 51.5; 32 x 50280, K = 768 on 32 rows 22.6 / 18.3).
-    if (linear_few_fits(N, a.K)) {
-        const int64_t round = kTilesResident, t32 = tiles(32, 32), most = a.K > 3072 ? 512 : a.K > 512 && a.K < 1024 ? 608 : 768;
-        if (a.M <= 16 && N >= 8192 && a.K <= 2048) MAMBA_FEW(1, 2, true);
-        if (tiles(16, 8) <= round) MAMBA_FEW(1, 1);
-        if (tiles(16, 16) <= round * 9 / 8 || (a.M <= 16 && N < 8192)) MAMBA_FEW(1, 2);
-        if (tiles(32, 16) <= (a.K < 256 ? 3 * round : round)) MAMBA_FEW(2, 2);
-        if (a.K >= 2048 && a.M > 64 && t32 > round && tiles(64, 32) <= round) MAMBA_FEW(4, 4);
-        if (a.K >= 256 && t32 <= most) MAMBA_FEW(2, 4);
+#define MAMBA_LINEAR(HOW, ...) return launch_##HOW<__VA_ARGS__>(x, w, a.bias, res, o, a.M, N, a.K, stream)
+#define MAMBA_TILES(BM, BN, ...)                                                                                                      \
+    linear_kernel<BM, BN, __VA_ARGS__><<<dim3((unsigned)((N + BN - 1) / BN), (unsigned)((a.M + BM - 1) / BM)), kThreads, 0, stream>>>( \
+        x, w, a.bias, res, o, a.M, N, a.K, vec);                                                                                      \
+    return hipGetLastError()
+    switch (linear_route(a.M, a.width, a.K)) {
+    case kFew16x16Stream: MAMBA_LINEAR(few, 1, 2, true);
+    case kFew16x8: MAMBA_LINEAR(few, 1, 1);
+    case kFew16x16: MAMBA_LINEAR(few, 1, 2);
+    case kFew32x16: MAMBA_LINEAR(few, 2, 2);
+    case kFew64x32: MAMBA_LINEAR(few, 4, 4);
+    case kFew32x32: MAMBA_LINEAR(few, 2, 4);
+    case kRing64: MAMBA_LINEAR(ring, 64, 64, 2, 2, 4, 2);
+    case kRing64x128: MAMBA_LINEAR(ring, 64, 128, 2, 4, 6, 1);
+    case kRing128: MAMBA_LINEAR(ring, 128, 128, 2, 4, 4, 1);
+    case kWide256x192: MAMBA_LINEAR(wide, 256, 192, false, 4, 2);
+    case kWide256: MAMBA_LINEAR(wide, 256, 256, false, 2, 4);
+    case kWide192: MAMBA_LINEAR(wide, 192, 128);
+    case kWide128Eight: MAMBA_LINEAR(wide, 128, 128, false, 2, 4);
+    case kWide128: MAMBA_LINEAR(wide, 128, 128);
+    case kTiles128: MAMBA_TILES(128, 128, 64);
+    case kTiles64x128: MAMBA_TILES(64, 128, 64);
+    case kTiles64Deep: MAMBA_TILES(64, 64, 256);
+    case kTiles64Stream: MAMBA_TILES(64, 64, 64, true);
+    case kTiles64: MAMBA_TILES(64, 64, 64);
+    case kNoKernel: break;
     }
-#undef MAMBA_FEW
-    switch (linear_ring(a.M, N, a.K, vec != 0)) {
-    case kRing64: return launch_ring<64, 64, 2, 2, 4, 2>(x, w, a.bias, res, o, a.M, N, a.K, stream);
-    case kRing64x128: return launch_ring<64, 128, 2, 4, 6, 1>(x, w, a.bias, res, o, a.M, N, a.K, stream);
-    case kRing128: return launch_ring<128, 128, 2, 4, 4, 1>(x, w, a.bias, res, o, a.M, N, a.K, stream);
-    default: break;
-    }
-    const bool wide = vec && N % 128 == 0 && a.M >= 128 && a.K % (2 * kWideBK) == 0 && a.K <= kToLdsLongestK;
-    auto grid = [&](int bm, int bn) { return dim3((unsigned)((N + bn - 1) / bn), (unsigned)((a.M + bm - 1) / bm)); };
-    const LinearTiles kind = linear_tiles(a.M, N, a.K, wide);
-    if (linear_wide256x192(a.M, N, a.K, vec != 0)) return launch_wide<256, 192, false, 4, 2>(x, w, a.bias, res, o, a.M, N, a.K, stream);
-    if (linear_wide256(a.M, N, a.K, wide)) return launch_wide<256, 256, false, 2, 4>(x, w, a.bias, res, o, a.M, N, a.K, stream);
-    if (linear_wide192(a.M, N, a.K, wide, kind)) return launch_wide<192, 128>(x, w, a.bias, res, o, a.M, N, a.K, stream);
-    switch (kind) {
-    case kTilesWide256: return launch_wide<256, 256, false, 2, 4>(x, w, a.bias, res, o, a.M, N, a.K, stream);
-    case kTilesWide128:
-        // a long k where half of the CUs or more have one tile only: eight wavefronts there too.  us of four / eight: 6000 x 768, K = 1536 21.7 /
-        // 20.5, 8000 x 768 23.7 / 22.8, 4000 x 1024, K = 2048 26.7 / 24.8; 16384 x 512, K = 1024 (two to every CU) 22.8* / 23.3, 8000 x 3072, K = 768 45.9* / 47.9
-        if (a.K >= 1024 && tiles(128, 128) <= 384) return launch_wide<128, 128, false, 2, 4>(x, w, a.bias, res, o, a.M, N, a.K, stream);
-        return launch_wide<128, 128>(x, w, a.bias, res, o, a.M, N, a.K, stream);
-    case kTiles128: linear_kernel<128, 128, 64><<<grid(128, 128), kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec); break;
-    case kTiles64x128: linear_kernel<64, 128, 64><<<grid(64, 128), kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec); break;
-    case kTiles64Deep: linear_kernel<64, 64, 256><<<grid(64, 64), kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec); break;
-    default:
-        if (a.M <= 64 && N >= 8192)
-            linear_kernel<64, 64, 64, true><<<grid(64, 64), kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec);
-        else
-            linear_kernel<64, 64, 64><<<grid(64, 64), kThreads, 0, stream>>>(x, w, a.bias, res, o, a.M, N, a.K, vec);
-        break;
-    }
-    return hipGetLastError();
+    return hipErrorInvalidValue;
+#undef MAMBA_TILES
+#undef MAMBA_LINEAR
 }
 
 hipError_t launch_linear_conv(const LinearArgs &a, hipStream_t stream)

@@ -69,6 +69,48 @@ constexpr int kConvTaps = 4;
 // linear_wide_kernel and linear_ring_kernel place a lane's 16 bytes within eight rows of k in 32 bits.
 constexpr int64_t kToLdsLongestK = (int64_t)1 << 28;
 
+// The kernels of a product (linear.hip): what linear_route chooses from.
+enum LinearKernel {
+    kNoKernel,
+    kFew16x8, kFew16x16, kFew16x16Stream, kFew32x16, kFew32x32, kFew64x32,   // linear_few_kernel, rows x columns; w read past the caches
+    kRing64, kRing64x128, kRing128,                                          // linear_ring_kernel
+    kWide256x192, kWide256, kWide192, kWide128Eight, kWide128,               // linear_wide_kernel: 256 rows on eight wavefronts, 192 x 128 on
+                                                                             // four, 128 x 128 on either
+    kTiles128, kTiles64x128, kTiles64Deep, kTiles64, kTiles64Stream          // linear_kernel; slabs of 256 k; w read past the caches
+};
+
+// Few output tiles (linear_few_kernel): the tile that makes one round of workgroups on 256 CUs, from 16 rows x 8 columns up; the
+// tile kernels take over where 32 x 32 comes to more than two or three to a CU.  us on 16 x 8 / 16 x 16 / 32 x 16 / 32 x 32 / 64 x 32 /
+// the best tile kernel:
+//    12 x  768, K = 1536  3.1 / 3.3 / 3.7 /   -  /   -  / 10.3      333 x   80, K = 1536  3.3 / 3.6 /  4.1 /  4.9 /   -  / 11.4
+//   128 x  768, K = 1536  4.8 / 4.3 / 4.1 /  4.6 /  6.4 / 10.9      333 x  768, K = 1536   -  / 6.3 /  6.8 /  6.2 /  6.5 / 10.9
+//   700 x  768, K = 1536   -  / 10.6/ 10.1/  8.4 / 11.5 / 11.0     1000 x  768, K = 1536   -  / 13.7/ 12.1 /  9.0 / 12.0 / 11.8
+//   128 x 3072, K =  768   -  / 5.3 / 5.0 /  5.1 /  5.6 /  7.0      256 x 3072, K =  768   -  / 8.2 /  8.2 /  7.7 /  9.5 /  7.1
+//   256 x 2048, K =  512   -  / 5.1 / 4.6 /  4.2 /  4.4 /  5.8      512 x 2048, K =  512   -  / 8.0 /  7.1 /  6.5 /  7.3 /  6.0
+//   512 x  512, K = 1024   -  / 5.2 / 4.7 /  3.9 /  5.1 /  8.4      700 x 1024, K = 2048   -  / 18.3/ 16.5 / 12.1 / 15.0 / 13.3
+//   256 x 1536, K = 3072   -  / 15.3/ 12.7/ 12.9 / 10.3 / 18.1      256 x 2048, K = 4096   -  / 29.2/ 24.2 / 21.4 / 18.0 / 28.3
+//   200 x 2560, K = 5120   -  / 40.9/ 37.3/ 37.4 / 36.4 / 34.9      256 x 1536, K =   48   -  / 3.1 /  2.9 /   -  /   -  /  3.1
+// How many 32 x 32 (`most`), between k of 512 and 1024; us on 32 x 32 / the tile kernels for k = 576, 640, 768, 896, 960:
+//   608 tiles (256 x 2432)  7.2 / 7.6    7.2 / 7.6    7.4 / 7.9    7.6 / 9.1    7.7 / 9.2
+//   672 tiles (224 x 3072)  7.1 / 7.1    7.2 / 7.1    7.5 / 7.1    7.7 / 8.3    7.8 / 8.3
+//   768 tiles (768 x 1024)  7.1 / 7.1    7.2 / 7.2    7.7 / 7.2    7.7 / 8.4    7.9 / 8.4
+// So 608 is where the two meet for a k of 768; for k between that and 1024 32 x 32 stays ahead up to 768 tiles, by 4 to 8 %.
+// Up to 16 rows against very many columns (the LM head on a draft position): 16 columns each, any number of rounds, up to a k of
+// four trips; us on that / 64 x 64 tiles: 1 x 50280, K = 768 13.3 / 15.7, 12 x 50280 15.1 / 17.0, 12 x 16384 6.7 / 10.0, 12 x 32768,
+// K = 2048 25.0 / 30.4 (12 x 50280, K = 2560 54.3 / 51.5; 32 x 50280, K = 768 on 32 rows 22.6 / 18.3).
+inline LinearKernel linear_few(int64_t M, int64_t N, int64_t K)
+{
+    if (!linear_few_fits(N, K)) return kNoKernel;
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((N + bn - 1) / bn) * ((M + bm - 1) / bm); };
+    const int64_t round = 256, t32 = tiles(32, 32), most = K > 3072 ? 512 : K > 512 && K < 1024 ? 608 : 768;
+    if (M <= 16 && N >= 8192 && K <= 2048) return kFew16x16Stream;
+    if (tiles(16, 8) <= round) return kFew16x8;
+    if (tiles(16, 16) <= round * 9 / 8 || (M <= 16 && N < 8192)) return kFew16x16;
+    if (tiles(32, 16) <= (K < 256 ? 3 * round : round)) return kFew32x16;
+    if (K >= 2048 && M > 64 && t32 > round && tiles(64, 32) <= round) return kFew64x32;
+    return K >= 256 && t32 <= most ? kFew32x32 : kNoKernel;
+}
+
 // Products whose tiles come in one round of workgroups take linear_ring_kernel, the smallest tile that does it; the few-row kernels
 // have been asked before.  64 x 64 tiles run two to a CU, but a second set of them costs what half as many 64 x 128 do.  us on
 // the kernel before (the tile kernels below) / 64 x 64 / 64 x 128 / 128 x 128, 24 weights in turn:
@@ -79,15 +121,14 @@ constexpr int64_t kToLdsLongestK = (int64_t)1 << 28;
 // Beyond one round the tile kernels are ahead: 1500 x 3072 13.7 / 18.4 / 19.5 / 18.9, 2048 x 3072 15.7 / 22.1 / 20.6 / 19.3.  With a short
 // k there is little to have under way: K = 256, 1024 x 1024 4.8 / 4.5* 64 x 64, but 1024 x 2048 5.8* / 5.9 64 x 128, 1500 x 1536 6.2* / 6.5
 // 128 x 128; K = 384, 1000 x 1536 7.0 / 6.7* 64 x 128.
-enum LinearRing { kRingNone, kRing64, kRing64x128, kRing128 };
-inline LinearRing linear_ring(int64_t M, int64_t N, int64_t K, bool vector_out)
+inline LinearKernel linear_ring(int64_t M, int64_t N, int64_t K, bool vector_out)
 {
-    if (!vector_out || K % 64 != 0 || K < 256 || K > kToLdsLongestK || M < 64 || N % 64 != 0) return kRingNone;
+    if (!vector_out || K % 64 != 0 || K < 256 || K > kToLdsLongestK || M < 64 || N % 64 != 0) return kNoKernel;
     auto tiles = [&](int64_t bm, int64_t bn) { return ((N + bn - 1) / bn) * ((M + bm - 1) / bm); };
     if (tiles(64, 64) <= 320) return kRing64;
-    if (N % 128 != 0 || K < 384) return kRingNone;
+    if (N % 128 != 0 || K < 384) return kNoKernel;
     if (tiles(64, 128) <= 256) return kRing64x128;
-    return M >= 128 && tiles(128, 128) <= 256 ? kRing128 : kRingNone;
+    return M >= 128 && tiles(128, 128) <= 256 ? kRing128 : kNoKernel;
 }
 
 // The way into a block on a context (x | z = u W_in^T, then the conv over time on x) in one launch: the tile whose product takes least,
@@ -139,18 +180,8 @@ inline ConvTiles linear_conv_tiles(int64_t M, int64_t D, int64_t K, int64_t taps
     return best <= 1.05 * apart ? kind : kConvApart;               // (the conv of a tile is cheaper than the model has it)
 }
 
-// Tile kernels for products that the few-row kernels do not take (linear.hip).
-enum LinearTiles {
-    kTilesWide256,      // linear_wide_kernel, 256 x 256 tiles, one to a CU
-    kTilesWide128,      // the same with 128 x 128, two to a CU
-    kTiles128,          // linear_kernel, 128 x 128 tiles, three to a CU
-    kTiles64x128,
-    kTiles64Deep,       // 64 x 64 with slabs of 256 k
-    kTiles64
-};
-
-// Which of them.  wide: M >= 128, N % 128 == 0, K % 128 == 0 and output widths that are multiples of 8, which the
-// memory-to-LDS kernel asks for.  The lines are drawn from chains of 24 different blocks, as a prefill runs them (alone in a
+// Tile kernels for products that the few-row and ring kernels do not take.  wide: M >= 128, N % 128 == 0, K % 128 == 0 and output widths
+// that are multiples of 8, which the memory-to-LDS kernel asks for.  The lines are drawn from chains of 24 different blocks, as a prefill runs them (alone in a
 // loop, or with few weights that stay in the caches, the wide tiles look better than they are there), for seven models from 512
 // to 5120 channels and 200 to 32768 rows, every kernel that applies put in place of one product: 201 products, on which
 // the choice costs 0.3 % of a block more than the best one on average.  us of a block on 256 x 256 / 128 x 128 memory-to-LDS /
@@ -164,7 +195,7 @@ enum LinearTiles {
 //   6000   3072            1536  432.1 / 447.4 / 422.3              4096           4096  569.7 / 601.0 /   -   /   -
 //   1000   5120            2560  233.1 / 251.0 / 235.1 / 251.2      5120           5120  277.7 / 233.1 / 254.3 / 230.1
 //   4096   5120            2560  622.1 / 647.3 / 637.7              5120           5120  624.3 / 635.3 / 656.9 / 687.4
-inline LinearTiles linear_tiles(int64_t M, int64_t N, int64_t K, bool wide)
+inline LinearKernel linear_tiles(int64_t M, int64_t N, int64_t K, bool wide)
 {
     auto tiles = [&](int64_t bm, int64_t bn) { return ((N + bn - 1) / bn) * ((M + bm - 1) / bm); };
     if (wide) {
@@ -172,8 +203,8 @@ inline LinearTiles linear_tiles(int64_t M, int64_t N, int64_t K, bool wide)
         // 128 CUs miss a tile in the last round, in narrow outputs only if that is the first one
         const int64_t t256 = M >= 256 && N % 256 == 0 ? tiles(256, 256) : 0;
         const int64_t rounds = (t256 + 255) / 256, idle = 256 * rounds - t256;
-        if (t256 >= 230 && 10 * t256 >= 9 * 256 * rounds) return kTilesWide256;
-        if (K >= 1024 && t256 >= 160 && idle <= 128 && (N >= 4096 || rounds == 1)) return kTilesWide256;
+        if (t256 >= 230 && 10 * t256 >= 9 * 256 * rounds) return kWide256;
+        if (K >= 1024 && t256 >= 160 && idle <= 128 && (N >= 4096 || rounds == 1)) return kWide256;
         // 128 x 128, two to a CU.  Wide outputs: one round of one or two to a CU; beyond that an XCD's tiles lie side by side in
         // one row block and every weight is used once per visit.  Narrow ones: with a short k the same, from fewer tiles on and
         // in any number where there are few columns; with a long k from half a tile per CU on, unless the small tiles with deep
@@ -182,7 +213,7 @@ inline LinearTiles linear_tiles(int64_t M, int64_t N, int64_t K, bool wide)
         if (N >= 4096 ? t128 >= 256 && t128 <= 512
                       : K >= 1024 ? t128 >= 128 && (N < 1024 || tiles(64, 64) > 512)
                                   : (t128 >= 256 && t128 <= 512) || (N <= 768 && t128 >= 192))
-            return kTilesWide128;
+            return kWide128;
     }
     if (tiles(128, 128) >= 512) return kTiles128;
     if (tiles(64, 128) >= 512) return kTiles64x128;
@@ -200,18 +231,18 @@ inline LinearTiles linear_tiles(int64_t M, int64_t N, int64_t K, bool wide)
 //    3000 x 3072, K =  768   27.6 /  20.9     12000 x  768, K = 1536   43.0 /  36.1      6000 x 6144, K = 1536  140.9 / 117.6
 //    8000 x 3072, K =  768   54.1 /  43.2     16384 x 3072, K =  768   84.0*/  88.6     12000 x 1536, K = 3072  125.9 / 108.0
 //    5000 x 2048, K =  512   21.9 /  17.0      8000 x 4096, K = 1024   69.8*/  74.4      7000 x 2560, K = 5120  205.0 / 173.3
-inline bool linear_wide192(int64_t M, int64_t N, int64_t K, bool wide, LinearTiles other)
+inline bool linear_wide192(int64_t M, int64_t N, int64_t K, bool wide, LinearKernel other)
 {
     auto tiles = [&](int64_t bm, int64_t bn) { return ((N + bn - 1) / bn) * ((M + bm - 1) / bm); };
-    if (!wide || M < 192 || tiles(128, 128) <= 512 || (other != kTilesWide256 && other != kTilesWide128 && other != kTiles128)) return false;
+    if (!wide || M < 192 || tiles(128, 128) <= 512 || (other != kWide256 && other != kWide128 && other != kTiles128)) return false;
     const bool longk = K >= 1024;
     auto rounds = [](int64_t t, int64_t per, double full, double half) {
         const int64_t rem = t % per;
         return (double)(t / per) * full + (rem == 0 ? 0.0 : rem <= per / 2 ? half : full);
     };
     const double with = rounds(tiles(192, 128), 512, longk ? 3.1 : 2.9, longk ? 1.9 : 1.7);
-    const double without = other == kTilesWide256 ? rounds(tiles(256, 256), 256, longk ? 3.6 : 3.9, longk ? 3.6 : 3.9)
-                           : other == kTilesWide128 ? rounds(tiles(128, 128), 512, 2.14, longk ? 1.5 : 1.3)
+    const double without = other == kWide256 ? rounds(tiles(256, 256), 256, longk ? 3.6 : 3.9, longk ? 3.6 : 3.9)
+                           : other == kWide128 ? rounds(tiles(128, 128), 512, 2.14, longk ? 1.5 : 1.3)
                                                     : rounds(tiles(128, 128), 768, longk ? 3.6 : 3.5, longk ? 2.7 : 2.6);
     return with < without;
 }
@@ -253,6 +284,32 @@ inline bool linear_wide256x192(int64_t M, int64_t N, int64_t K, bool vector_out)
     if (!vector_out || M < 1000 || N % 192 != 0 || K % 128 != 0 || K > kToLdsLongestK) return false;
     const double own = wide_tiles_us(M, N, K, 256, 192, 256, 0.5, 7.5, .0195, .66);
     return own < .99 * wide128_us(M, N, K) && own < (N % 128 == 0 ? .97 : 1.0) * wide192_us(M, N, K) && (N % 256 != 0 || own < .99 * wide256_us(M, N, K));
+}
+
+// Eight wavefronts for 128 x 128 tiles of a long k as well where half of the CUs or more have one tile only.  us of four / eight:
+// 6000 x 768, K = 1536 21.7 / 20.5, 8000 x 768 23.7 / 22.8, 4000 x 1024, K = 2048 26.7 / 24.8; 16384 x 512, K = 1024 (two to every CU) 22.8* /
+// 23.3, 8000 x 3072, K = 768 45.9* / 47.9
+inline bool linear_wide128_eight(int64_t M, int64_t N, int64_t K)
+{
+    return K >= 1024 && ((M + 127) / 128) * ((N + 127) / 128) <= 384;
+}
+
+// The kernel of a product x (M, K) w (N, K)^T whose outputs are width[0], width[1] and width[2] columns wide: the rules above, in the
+// order in which they are asked.
+inline bool linear_vector_out(const int64_t width[3]) { return width[0] % 8 == 0 && width[1] % 8 == 0 && width[2] % 8 == 0; }
+inline LinearKernel linear_route(int64_t M, const int64_t width[3], int64_t K)
+{
+    const int64_t N = width[0] + width[1] + width[2];
+    const bool vec = linear_vector_out(width), wide = vec && N % 128 == 0 && M >= 128 && K % 128 == 0 && K <= kToLdsLongestK;
+    if (const LinearKernel few = linear_few(M, N, K)) return few;
+    if (const LinearKernel ring = linear_ring(M, N, K, vec)) return ring;
+    const LinearKernel tiles = linear_tiles(M, N, K, wide);
+    if (linear_wide256x192(M, N, K, vec)) return kWide256x192;
+    if (linear_wide256(M, N, K, wide)) return kWide256;
+    if (linear_wide192(M, N, K, wide, tiles)) return kWide192;
+    if (tiles == kWide128 && linear_wide128_eight(M, N, K)) return kWide128Eight;
+    if (tiles == kTiles64 && M <= 64 && N >= 8192) return kTiles64Stream;
+    return tiles;
 }
 
 // x_proj and dt_proj in one kernel (xdt.hip): rows per workgroup and column groups for M rows; 0 rows: two launches.

@@ -1219,11 +1219,11 @@ def test_scan_invariants_at_size(m):
                                           # split outputs
                                           (4096, 4096, 64, None), (4100, 4000, 128, (2000, 2000)), (4096, 4104, 192, None),
                                           (4090, 4096, 320, (4088, 8)), (5000, 3400, 448, (1000, 1200, 1200)),
-                                          # memory-to-LDS tiles (N % 128 == 0, K % 128 == 0): 4, 6, 8 and 10 slabs, splits on
-                                          # and off the tile edges; two that the small register-staged tiles take
+                                          # memory-to-LDS tiles (N % 128 == 0, K % 128 == 0): 4, 6, 8, 10 and 12 slabs, splits on
+                                          # and off the tile edges; one that the small register-staged tiles take
                                           (16384, 2048, 256, (1024, 1024)), (16384, 1152, 384, None), (8192, 4096, 512, None),
                                           (16384, 1152, 640, (1000, 152)), (1024, 3072, 768, (1536, 1536)), (512, 6144, 128, None),
-                                          # a long k on few tiles, and more for the small tiles
+                                          # a long k and a short one on one round of 128 x 128 tiles, and one more for the small tiles
                                           (4096, 768, 1536, None), (2688, 1152, 256, (1000, 152)), (384, 8192, 384, None)])
 def test_linear_against_oracle(m, M, N, K, splits):
     say(M=M, N=N, K=K, splits=splits)
@@ -1244,8 +1244,8 @@ def test_linear_against_oracle(m, M, N, K, splits):
 
 @pytest.mark.parametrize("M,N,K,splits", [(129, 32768, 128, None), (5003, 3072, 256, (1536, 1536)), (10241, 1536, 128, None),
                                           (2177, 1152, 1024, None), (4001, 768, 1536, None), (3999, 1280, 128, (1000, 280)),
-                                          # 256 x 256 tiles, full rows of them and ragged ones, full rounds and not; the register-
-                                          # staged 128 x 128 tiles beside them
+                                          # 256 x 256 tiles, full rows of them and ragged ones, full rounds and not; 192 x 128 tiles
+                                          # beside them
                                           (8192, 4096, 768, (2048, 2048)), (2047, 8192, 512, None), (2500, 6144, 384, (3072, 3072)),
                                           (1101, 8192, 1024, (4000, 4192)), (1001, 10240, 640, (5000, 5240)), (1025, 8192, 512, None)])
 def test_linear_wide_tiles_ragged_rows(m, M, N, K, splits):
@@ -1255,9 +1255,26 @@ def test_linear_wide_tiles_ragged_rows(m, M, N, K, splits):
 
 
 @pytest.mark.parametrize("M,N,K,splits", [(2977, 3072, 128, (1536, 1536)), (8000, 3072, 256, (1500, 1572)), (4993, 2048, 384, None),
-                                          (5184, 2048, 512, None), (11905, 768, 1536, None), (12095, 768, 128, (384, 384)), (3073, 6144, 128, None)])
+                                          (5184, 2048, 512, None), (11905, 768, 1536, None), (12095, 768, 128, (384, 384)), (3073, 6144, 128, None),
+                                          (8000, 3072, 256, (1504, 1568))])
 def test_linear_192_row_tiles(m, M, N, K, splits):
-    """Products that take 192 x 128 tiles: full row blocks, and a last one of one row, of one less than all and in between."""
+    """Products that take 192 x 128 tiles: full row blocks, and a last one of one row, of one less than all and in between.  (Outputs
+    that are not multiples of 8 columns wide get register-staged tiles.)"""
+    test_linear_against_oracle(m, M, N, K, splits)
+
+
+@pytest.mark.parametrize("M,N,K,splits", [(8000, 768, 1536, None), (5505, 768, 1536, None), (5888, 768, 1024, None), (2177, 2304, 1024, (1144, 1160)),  # eight wavefronts
+                                          (3968, 1280, 384, None), (4097, 1280, 384, None), (4223, 1280, 512, None), (3969, 1280, 640, (640, 640))])     # four
+def test_linear_128_row_tiles(m, M, N, K, splits):
+    """128 x 128 memory-to-LDS tiles on eight wavefronts and on four: full row blocks, a last one of one row, of all but one and in between,
+    slabs beyond the first two; and the launches that have to agree."""
+    test_linear_256_tiles(m, M, N, K, splits)
+
+
+@pytest.mark.parametrize("M,N,K,splits", [(1472, 4000, 320, None), (1500, 4000, 128, None), (1501, 4001, 200, (2000, 2001)),     # 64 x 128
+                                          (704, 1000, 1000, None), (641, 1000, 1000, None), (1030, 1200, 520, (600, 600)), (450, 3000, 1288, (1499, 1501))])
+def test_linear_small_register_staged_tiles(m, M, N, K, splits):
+    """64 x 128 tiles, and 64 x 64 with slabs of 256 k: whole slabs and a part of one, full tiles and ragged ones."""
     test_linear_against_oracle(m, M, N, K, splits)
 
 
@@ -1365,7 +1382,7 @@ def test_linear_at_block_bench_size_sampled_rows(m):
 
 def test_linear_wide_tiles_are_deterministic(m):
     """The memory-to-LDS tiles stream their operands in asynchronously and order them with explicit waits; a
-    missing wait would show as run-to-run differences.  Ten launches each, both tile shapes, on fresh outputs."""
+    missing wait would show as run-to-run differences.  Ten launches each, 256 x 256 and 128 x 128 tiles and a ring of them, on fresh outputs."""
     g = torch.Generator(device=DEV)
     g.manual_seed(77)
     for (M, N, K) in ((8192, 4096, 768), (16384, 1152, 1536), (4096, 768, 1536)):
@@ -1441,7 +1458,7 @@ def check_block_stages(m, blk, w64, hid, conv_in=None, h0=None, what="block"):
 
 @pytest.mark.parametrize("B,L,dm,D,N,K,R", [(2, 96, 64, 128, 16, 4, 8), (1, 700, 768, 1536, 16, 4, 48),
                                            (3, 33, 256, 512, 8, 3, 16),
-                                           # long enough for the 256-row projection tiles (in_proj and out_proj)
+                                           # long enough for one round of 128 x 128 tiles in out_proj
                                            (1, 4096, 768, 1536, 16, 4, 48),
                                            # scans that a block takes on the lanes kernel and a call of its own does not (the pieces' others)
                                            (2, 4000, 64, 1536, 16, 4, 48), (3, 1000, 64, 1024, 16, 4, 32),

@@ -2,6 +2,7 @@
 plain host functions; a small shim of them is compiled with the system's C++ compiler, no GPU and no large tensor involved."""
 import ctypes
 import os
+import re
 import subprocess
 
 import pytest
@@ -22,9 +23,14 @@ extern "C" int wide256(int64_t M, int64_t N, int64_t K, int wide) { return mamba
 extern "C" int wide256x192(int64_t M, int64_t N, int64_t K, int vec) { return mamba::linear_wide256x192(M, N, K, vec != 0); }
 extern "C" int64_t row_blocks(int64_t M, int64_t BM, int conv) { return mamba::row_blocks(M, BM, conv != 0); }
 extern "C" int wide192(int64_t M, int64_t N, int64_t K, int wide) { return mamba::linear_wide192(M, N, K, wide, mamba::linear_tiles(M, N, K, wide)); }
+extern "C" int route(int64_t M, int64_t n0, int64_t n1, int64_t n2, int64_t K)
+{ const int64_t width[3] = {n0, n1, n2}; return mamba::linear_route(M, width, K); }
 extern "C" int xdt(int64_t M, int64_t d_inner, int64_t dt_rank, int64_t N, unsigned *groups)
 { return mamba::xdt_plan(M, d_inner, dt_rank, N, groups); }
 """
+
+with open(os.path.join(ROOT, "paper_2506_01206_amd", "csrc", "routes.h")) as f:
+    KERNELS = re.findall(r"\bk\w+", re.sub(r"//.*", "", re.search(r"enum LinearKernel \{(.*?)\};", f.read(), re.S).group(1)))
 
 
 @pytest.fixture(scope="module")
@@ -47,6 +53,7 @@ def routes(tmp_path_factory):
     lib.wide256x192.argtypes = [i64, i64, i64, i32]
     lib.conv_tiles.argtypes = [i64] * 4
     lib.row_blocks.argtypes, lib.row_blocks.restype = [i64, i64, i32], i64
+    lib.route.argtypes = [i64] * 5
     lib.xdt.argtypes = [i64, i64, i64, i64, ctypes.POINTER(ctypes.c_uint)]
     return lib
 
@@ -123,9 +130,9 @@ def test_few_row_product_forms_no_more_row_tiles_than_there_are_rows(routes):
 
 
 def test_tile_kernel_of_a_product(routes):
-    """Which tile kernel a product gets: the ones that the parity tests name for it, the ones measured faster in chains of blocks
+    """Which tile kernel a product gets where the rules asked before leave it: the ones measured faster in chains of blocks
     of other widths than 1536 channels, and never a kernel whose conditions it does not meet."""
-    W256, W128, T128, T64x128, DEEP, T64 = range(6)
+    W256, W128, T128, T64x128, DEEP, T64 = (KERNELS.index(k) for k in ("kWide256", "kWide128", "kTiles128", "kTiles64x128", "kTiles64Deep", "kTiles64"))
     tiles = lambda M, N, K: routes.tiles(M, N, K, M >= 128 and N % 128 == 0 and K % 128 == 0)
     for kind, shapes in {
             W256: [(5003, 3072, 256), (10241, 1536, 128), (8192, 4096, 768), (2047, 8192, 512), (2500, 6144, 384), (1101, 8192, 1024),
@@ -143,7 +150,7 @@ def test_tile_kernel_of_a_product(routes):
         for N in (128, 256, 384, 1024, 1152, 8192, 12288):
             for K in (128, 384, 1024, 5120, 1 << 20):
                 kind = tiles(M, N, K)
-                assert 0 <= kind <= 5 and (kind != W256 or (M >= 256 and N % 256 == 0)), (M, N, K)
+                assert kind in (W256, W128, T128, T64x128, DEEP, T64) and (kind != W256 or (M >= 256 and N % 256 == 0)), (M, N, K)
 
 
 def test_192_row_tiles(routes):
@@ -159,7 +166,7 @@ def test_192_row_tiles(routes):
 
 def test_one_round_of_tiles(routes):
     """The products that the parity test names for each tile, more than a round left alone, and never without the conditions."""
-    none, t64, t64x128, t128 = range(4)
+    none, t64, t64x128, t128 = (KERNELS.index(k) for k in ("kNoKernel", "kRing64", "kRing64x128", "kRing128"))
     for want, cases in ((t64, [(641, 1280, 256), (449, 2560, 1024), (704, 1856, 320), (64, 64, 1 << 28)]),
                         (t64x128, [(1025, 1536, 384), (1087, 1536, 448), (512, 3072, 768)]),
                         (t128, [(2049, 1152, 384), (2175, 1152, 1536), (4096, 768, 832)]),
@@ -225,3 +232,64 @@ def test_256_tiles_by_rounds(routes):
               (2977, 3072, 128), (4993, 2048, 384), (11905, 768, 1536), (12095, 768, 128), (3073, 6144, 128), (1025, 8192, 512), (1001, 10240, 640),
               (2177, 1152, 1024), (4001, 768, 1536), (129, 32768, 128)]:
         assert not takes(*s), s
+
+
+# The kernel that each product of the GPU parity tests is there for: rows, columns, k.  (Those of test_linear_few_every_split_of_k, every k
+# on ten shapes, are left to the rules that its docstring names.)
+PARITY = {
+    "kFew16x8": [(1, 1, 8), (5, 80, 48), (130, 200, 72), (129, 129, 1032), (12, 80, 1536), (32, 768, 1536), (33, 100, 520), (64, 50, 1544),
+                 (3, 1000, 72), (65, 96, 512), (13, 80, 1024), (333, 80, 2056)],
+    "kFew16x16": [(1, 4096, 8), (17, 2050, 40), (257, 250, 1544)],
+    "kFew16x16Stream": [(12, 8200, 136), (1, 50280, 768), (16, 50280, 768)],
+    "kFew32x16": [(1000, 80, 1536), (64, 1536, 48), (18, 3072, 768), (19, 4090, 768), (100, 800, 520), (100, 790, 1032)],
+    "kFew32x32": [(384, 768, 1536), (65, 4000, 512), (255, 999, 1288), (2700, 80, 1536), (330, 761, 1096), (641, 700, 1024), (50, 5000, 264),
+                  (64, 4500, 776)],
+    "kFew64x32": [(129, 2600, 4104)],
+    "kRing64": [(257, 3072, 768), (641, 1280, 256), (449, 2560, 1024), (704, 1856, 320)],
+    "kRing64x128": [(1025, 1536, 384), (1087, 1536, 448), (512, 3072, 768)],
+    "kRing128": [(1024, 3072, 768), (4096, 768, 1536), (384, 8192, 384), (2049, 1152, 384), (2175, 1152, 1536), (4096, 768, 832),
+                 (2177, 1152, 1024), (4001, 768, 1536)],
+    "kWide256x192": [(3713, 3264, 128), (3840, 3264, 256), (5761, 2112, 384), (1921, 6144, 384), (7000, 1728, 128)],
+    "kWide256": [(4097, 3072, 128), (16385, 768, 256), (7936, 2048, 512), (5003, 3072, 384), (2047, 8192, 128), (16384, 2048, 256),
+                 (8192, 4096, 512), (5003, 3072, 256), (10241, 1536, 128), (8192, 4096, 768), (2047, 8192, 512), (2500, 6144, 384)],
+    "kWide192": [(2977, 3072, 128), (4993, 2048, 384), (5184, 2048, 512), (11905, 768, 1536), (12095, 768, 128), (3073, 6144, 128),
+                 (8000, 3072, 256, 1504), (16384, 1152, 384), (16384, 1152, 640), (1101, 8192, 1024), (1001, 10240, 640), (1025, 8192, 512)],
+    "kWide128Eight": [(8000, 768, 1536), (5505, 768, 1536), (5888, 768, 1024), (2177, 2304, 1024)],
+    "kWide128": [(3968, 1280, 384), (4097, 1280, 384), (4223, 1280, 512), (3969, 1280, 640), (129, 32768, 128), (3999, 1280, 128)],
+    "kTiles128": [(8000, 3072, 256, 1500), (8190, 4100, 136), (8192, 4096, 40), (8300, 4000, 32), (4096, 4096, 64), (4100, 4000, 128),
+                  (4096, 4104, 192), (4090, 4096, 320), (5000, 3400, 448)],
+    "kTiles64x128": [(1472, 4000, 320), (1500, 4000, 128), (1501, 4001, 200)],
+    "kTiles64Deep": [(704, 1000, 1000), (641, 1000, 1000), (1030, 1200, 520), (450, 3000, 1288)],
+    "kTiles64": [(512, 6144, 128), (2688, 1152, 256)],
+    "kTiles64Stream": [(64, 9000, 64)],
+}
+
+
+def test_every_product_of_the_parity_tests_reaches_the_kernel_it_is_there_for(routes):
+    """The whole choice, in the order in which its rules are asked: no kernel without a parity test, no product that slips to another one,
+    and for the tiles that move their last row block back one that is full, one that is not, outputs split and a residual in place, and
+    more slabs than are requested before the first product."""
+    import test_gpu_parity as gpu
+    widths = lambda N, splits: (list(splits or (N,)) + [0, 0])[:3]
+    kernel = lambda M, N, K, splits=None: KERNELS[routes.route(M, *widths(N, splits), K)]
+    cases = {}                                                     # shape (and first output, where one shape comes twice) -> its splits
+    for name in dir(gpu):
+        marks = [k.args for k in getattr(getattr(gpu, name), "pytestmark", ()) if k.name == "parametrize"]
+        if name.startswith("test_linear_") and len(marks) == 1 and marks[0][0] == "M,N,K,splits":
+            for M, N, K, splits in marks[0][1]:
+                listed = [(M, N, K, splits[0])] if splits and any((M, N, K, splits[0]) in l for l in PARITY.values()) else [(M, N, K)]
+                cases.setdefault(listed[0], []).append(splits)
+    assert sorted(cases) == sorted(shape for shapes in PARITY.values() for shape in shapes)
+    assert set(PARITY) | {"kNoKernel"} == set(KERNELS)
+    rows = dict(kRing64=64, kRing64x128=64, kRing128=128, kWide256x192=256, kWide256=256, kWide192=192, kWide128Eight=128, kWide128=128)
+    for want, shapes in PARITY.items():
+        for shape in shapes:
+            for splits in cases[shape]:
+                assert kernel(*shape[:3], splits) == want, (shape, splits)
+        if want in rows:
+            assert {shape[0] % rows[want] == 0 for shape in shapes} == {True, False}, want
+            assert {splits is None for shape in shapes for splits in cases[shape]} == {True, False}, want
+            assert any(K >= 384 and M % rows[want] and None in cases[(M, N, K)] for M, N, K in (s for s in shapes if len(s) == 3)), want
+    # the launches that have to agree, and the sampled rows
+    assert [kernel(*s) for s in ((8192, 4096, 768), (16384, 1152, 1536), (4096, 768, 1536))] == ["kWide256", "kWide128", "kRing128"]
+    assert kernel(32768, 3072, 768, (1536, 1536)) == "kWide256" and kernel(32768, 768, 1536) == "kWide256x192"
