@@ -546,12 +546,14 @@ bool block_scan_on_lanes(const mamba_block_params_t *p, const float *h0, const f
 {
     const int64_t Di = p->d_inner, N = p->d_state, R = p->dt_rank, w = 2 * Di * R;
     unsigned groups;
-    int64_t st;
+    int64_t st, cl, nc;
     *low_dt = false;
-    if (batch > kMaxGridYZ || !scan_lanes_in_block(batch, L, Di, N)) return false;
+    const int choice = scan_kernel_choice(batch, L, Di, N);       // what a call of its own takes
+    scan_plan(batch, L, Di, N, 0, &cl, &nc);
+    if (batch > kMaxGridYZ || choice == kScanDirect || (choice == kScanChunked && !scan_lanes_in_block(batch, L, Di, N, R, nc))) return false;
     if (!size3(batch, Di, N, 4, &st) || !aligned16(h0) || !aligned16(h_final) || (h_final != h0 && overlap(h_final, st, h0, st))) return false;
     if (overlap(h0, st, workspace, (int64_t)ws_bytes) || overlap(h_final, st, workspace, (int64_t)ws_bytes)) return false;
-    *low_dt = scan_lanes_takes_low_dt(batch, L, Di, N, R) && xdt_plan(batch * L, Di, R, N, &groups) == 0 &&
+    *low_dt = scan_lanes_takes_low_dt(batch, L, Di, R) && xdt_plan(batch * L, Di, R, N, &groups) == 0 &&
               !overlap(p->dt_proj_w, w, workspace, (int64_t)ws_bytes) && !overlap(h_final, st, p->dt_proj_w, w);
     return true;
 }

@@ -47,11 +47,7 @@ constexpr int kScanChunked = 0, kScanDirect = 1, kScanLanes = 2;
 // narrow layer, else time chunks across workgroups (scan.hip).
 int scan_kernel_choice(int64_t batch, int64_t L, int64_t D, int64_t N);
 bool scan_direct_applies(int64_t batch, int64_t L, int64_t D, int64_t N);
-bool scan_lanes_applies(int64_t batch, int64_t L, int64_t D, int64_t N);
-bool scan_lanes_in_block(int64_t batch, int64_t L, int64_t D, int64_t N);   // the choice for the scan of a whole block
 hipError_t launch_scan_direct(const ScanArgs &a, hipStream_t stream);
-// whether launch_scan_lanes takes a whole block's scan together with its dt projection: contexts of one super-step
-bool scan_lanes_takes_low_dt(int64_t batch, int64_t L, int64_t D, int64_t N, int64_t dt_rank);
 hipError_t launch_scan_lanes(const ScanArgs &a, hipStream_t stream);
 // Token tensors with element strides {batch, token, channel} (strided.hip): plain kernels, one lane per channel.
 struct ConvStridedArgs {

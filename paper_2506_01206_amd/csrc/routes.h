@@ -30,6 +30,107 @@ inline bool linear_few_fits(int64_t N, int64_t K)
     return K <= (int64_t)INT32_MAX - 63 && N <= ((int64_t)1 << 27) - 16;
 }
 
+// The lanes scan (scan_lanes.hip): its states per channel, and the most dt columns that it takes the projection of.
+constexpr int kLanesStates = 16, kLanesLowRank = 64;
+
+// Channels per workgroup: what takes the fewest rounds of 256 workgroups times what one takes (a workgroup of fewer channels has
+// fewer wavefronts to a SIMD and is faster, but not in proportion).  us with 2 / 4 / 6 channels, bf16 | float32 (one session):
+//   1 x 1000 x  512  10.5*/ 10.6 / 13.8 | 12.3*/ 11.9 / 19.9      1 x  512 x 256   6.3*/  6.9 /  8.9 |  6.6*/  6.7 /  9.1
+//   1 x 1000 x  768  14.5 / 11.7*/ 14.2 | 16.0 / 13.2*/ 17.6      1 x 2000 x 1000 26.1 / 19.9*/ 24.0 | 28.5 / 23.0*/ 29.0
+//   1 x 2048 x 1536  36.3 / 37.6 / 25.0*| 37.0 / 43.2 / 31.3*     1 x 1000 x 2048 25.3 / 23.0*/ 30.7 | 28.8 / 24.0*/ 32.2
+inline int lanes_channels(int64_t batch, int64_t L, int64_t D)
+{
+    auto cost = [&](int64_t g, double round) { return (double)((batch * ((D + g - 1) / g) + 255) / 256) * round; };
+    const double six = cost(6, 1.0), four = cost(4, 0.8), two = cost(2, L <= 256 ? 0.68 : 0.7);
+    return two <= four && two <= six ? 2 : four <= six ? 4 : 6;
+}
+
+// ns: rounds of workgroups times what one takes, to which a token adds `six`, `four` or `two` by its channels.  by_xcd: with the workgroups
+// that fill the last group of 8, one to an XCD, as the kernel's grid has them
+inline double lanes_ns(int64_t batch, int64_t L, int64_t D, double six, double four, double two, bool by_xcd = false)
+{
+    const int64_t g = lanes_channels(batch, L, D), row = (D + g - 1) / g, groups = batch * (by_xcd ? (row + 7) / 8 * 8 : row);
+    const double first = g == 6 ? 6000.0 : g == 4 ? 5000.0 : 2500.0, token = g == 6 ? six : g == 4 ? four : two;
+    return (double)((groups + 255) / 256) * (first + token * (double)L);
+}
+
+// Shapes the lane-scan kernel serves: 16 states, token rows that can be read in 4-byte pieces from any even
+// channel, at least one full workgroup; and among those the ones it is expected to finish before the two-pass
+// kernels of scan.hip.  Its time is a number of rounds of 256 workgroups, every one walking the whole sequence;
+// that of the two-pass kernels goes with all tokens.  The line lies between the two types, since the choice, and with it the size of
+// the workspace, is not told the type, and it lies where the two met before the two-pass kernels' exponentials went into runs: those
+// have gained more by it than this one, so that between about 7000 tokens of 1536 channels (float32: 2700) and the line they are
+// ahead by up to 9 % (float32: 31 %).  But a call that this kernel took needs no workspace, and one made without would be
+// refused if the line moved down.  (A whole block brings its workspace and is bf16: scan_lanes_in_block.)
+// Down to 33 tokens (a call of fewer keeps the kernel that mamba_scan_kernel has always named for it; a block takes them too): one super-step
+// against three launches, 1 x 40 x 1536 6.1 / 16.0, 1 x 40 x 256 3.9 / 15.8, 2 x 40 x 1536 10.8 / 16.4, 1 x 40 x 4096 15.4 / 16.3.
+// us, lanes / two-pass, bf16 | float32, one session, four sets of operands in turn (on one set, which stays in the last-level
+// cache, 1 x 8192 x 1536 takes 81 | 110 here); * what the line takes:
+//   1 x  600 x  768  11.1*/ 20.8 | 12.0*/ 20.9       1 x 2048 x 1536  25.8*/ 35.5 | 31.4*/ 35.9       1 x   64 x 4096  15.4*/ 17.3 |  15.6*/ 17.0
+//   1 x 2000 x  768  19.6*/ 30.1 | 22.7*/ 26.5       1 x 6000 x 1536  68.7*/ 73.5 | 93.5*/ 68.5       1 x 8192 x 1536  97.0*/ 92.6 | 123.8*/ 87.0
+//   1 x 4000 x  768  34.0 / 37.4*| 41.0 / 37.2*      1 x 7000 x 1536  84.0*/ 83.1 |108.0*/ 79.3       1 x 10240 x 1536 125.7 / 110.7*| 152.0 / 104.2*
+//   1 x 2000 x  256  17.0 / 21.8*| 21.8 / 22.0*      1 x 4000 x 1024  34.5*/ 44.3 | 41.7*/ 42.6       1 x 4000 x 512   33.8 / 32.9*| 42.1 / 29.6*
+//   1 x 3000 x 1536  34.4*/ 45.5 | 48.4*/ 43.8       1 x 4000 x 1536  43.9*/ 53.9 | 65.3*/ 52.9       1 x 9900 x 1536 120.2*/110.6 | 151.8*/ 104.3
+//   4 x 1000 x  768  28.3*/ 35.7 | 34.2*/ 35.5       1 x 2000 x 2048  37.6*/ 43.5 | 43.0*/ 41.6       2 x 3000 x 1536  75.2*/ 73.2 | 98.0*/ 68.4
+inline bool scan_lanes_applies(int64_t batch, int64_t L, int64_t D, int64_t N)
+{
+    if (N != kLanesStates || D % 2 != 0 || D < 6 || L <= 32 || batch > 65535) return false;
+    const double two_pass_ns = 24000.0 + 9.8 * (double)L * ((double)batch * (double)D / 1536.0);
+    return lanes_ns(batch, L, D, 11.6, 9.7, 12.5) < two_pass_ns;
+}
+
+// The same in a whole block, whose scan finds its operands in the last-level cache as long as the block's four tensors of (rows, D) bf16 fit
+// its 256 MB: the small pieces of the token rows that this kernel reads come sooner from there, the two passes gain nothing by it.
+// us of a block, two passes / lanes, three sets of operands in turn (* what this takes; a line within 2 us is left to the two passes):
+//   1 x 10500 x 1536 260 / 243*      2 x 4000 x 1536 205 / 196*      3 x 3000 x 1536 241 / 219*      1 x  8000 x 1024 140 / 133*      1 x 6000 x 4096 545* / 554
+//   1 x 16000 x 1536 368 / 346*      2 x 8000 x 1536 367 / 350*      4 x 1000 x 1536 127*/ 125       1 x 10000 x  768 134*/ 143       1 x 3000 x 2048 133 / 127*
+//   1 x 20000 x 1536 458 / 437*      4 x 8000 x 1536 634*/ 724       8 x  500 x 1536 125*/ 139       1 x  9000 x 3072 537 / 518*      2 x 1500 x 2048 133* / 139
+//   1 x    16 x 1536  25 /  21*      1 x   40 x 1536  36 /  22*      2 x   40 x 1536  37 /  28*      4 x   40 x 1536  40*/  39       1 x    2 x 1536  20*/ 20
+//   1 x 32768 x 1536 634*/ 744       4 x 4000 x 1536 370*/ 362       8 x 2000 x 1536 369*/ 377       1 x  6000 x  512  88*/ 81
+// Contexts that the two passes take as one chunk (up to 16 tokens) are one launch there as well, of about 0.4 us a token, and dt has one
+// of its own: the lanes kernel is ahead where its workgroups come in one round (dealt to the XCDs in whole groups of 8), and on more
+// tokens the more rounds they come in.  400 blocks of 64 to 5120 channels, 4 to 16 tokens: 4.1 % ahead of the two passes, 4.25 the better
+// of the two each time.  us of a block, two passes / lanes:
+//   1 x  4 x  256  17.7 / 16.9*      1 x  4 x 1536  21.8*/ 22.3      3 x  4 x 1536  21.5*/ 31.7      6 x  8 x  768  22.6*/ 30.5      12 x  8 x 256  20.1*/ 22.8
+//   1 x 16 x  256  22.5 / 16.8*      1 x 16 x 1536  26.2 / 21.9*     3 x 16 x 1536  28.1*/ 33.1      2 x 15 x 1024  25.1 / 21.4*     12 x 16 x 256  23.9 / 23.4*
+//   1 x  8 x 4096  35.4*/ 44.9       1 x 16 x 2048  28.2 / 24.9*     2 x 16 x 1536  27.0*/ 27.5      4 x 13 x  256  22.4 / 18.1*      1 x  6 x 2048  24.6*/ 24.5
+// and with 96 dt columns, whose projection stays apart: 1 x 4 x 768 20.1*/ 21.3, 1 x 15 x 1024 24.8 / 21.1*.
+// chunks: what scan_plan cuts such a call into, for which the line above has declined.
+inline bool scan_lanes_in_block(int64_t batch, int64_t L, int64_t D, int64_t N, int64_t dt_rank, int64_t chunks)
+{
+    if (N != kLanesStates || D % 2 != 0 || D < 6 || L < 4 || batch > 65535 || (double)batch * (double)L * (double)D > 32e6) return false;
+    if (chunks == 1) {
+        const int64_t g = lanes_channels(batch, L, D);
+        const double own = lanes_ns(batch, L, D, 9.9, 8.3, 10.7, true);
+        const double dt_apart = dt_rank <= kLanesLowRank ? 0.0 : g == 6 ? 2200.0 : 4250.0;
+        // (a single chunk of more tokens has channels for the whole chip)
+        return L <= 16 && own < (g == 6 ? 3000.0 + 500.0 * (double)L : 2200.0 + 950.0 * (double)L) - dt_apart;
+    }
+    const double two_pass_ns = 24000.0 + 10.0 * (double)L * ((double)batch * (double)D / 1536.0);
+    return lanes_ns(batch, L, D, 9.9, 8.3, 10.7) < two_pass_ns - 2000.0;
+}
+
+// Tokens of a lane, 64 times that to a super-step: what takes the fewest super-steps times what one takes, which is 5.3 us with 8 tokens,
+// 4.1 with 6 and 3.2 with 4 (1536 channels; a last one that is not full takes somewhat less).  Two channels to a workgroup leave no
+// threads for more than 4.  us with 4 / 6 / 8 tokens:
+//    200 x 1536  7.25*/ 8.37 / 9.05     400 x 1536 10.45 / 12.56 / 9.84*    1000 x 1536 17.06 / 16.92 / 15.49*     700 x 1000 10.68 / 10.33*/ 11.66
+//    300 x 1536 10.42 / 8.79*/ 9.48     600 x 1536 13.49 / 12.69*/14.70     1100 x 1536 19.82 / 17.06*/ 19.72      350 x 1536 float32 11.43 / 9.75*/ 10.70
+//    384 x 1536 10.51 / 9.19*/ 9.83     768 x 1536 13.73 / 13.01*/14.92     1900 x 1536 29.56 / 26.07 / 25.83*     700 x 1536 float32 16.88 / 16.21*/ 18.23
+// In float32, where a super-step's B and C are not requested ahead, one super-step more costs more; us with 6 / 8, bf16 | float32:
+//   2251 x  488, batch 6  82.6*/ 82.8 | 108.6 / 107.2*     2107 x 1392, batch 2  55.7*/ 57.4 | 77.4 / 76.2*     2101 x 504, batch 2  25.1*/ 25.6 | 28.5 / 27.9*
+//   2682 x  456, batch 3  34.1*/ 36.3 |  42.7 / 42.4*      1124 x 2304           32.1*/ 36.6 | 38.6*/ 42.5
+inline int lanes_tau(int64_t batch, int64_t L, int64_t D, bool bf16)
+{
+    if (L <= 256 || lanes_channels(batch, L, D) == 2) return 4;
+    return 4.1 * (double)((L + 383) / 384) < (bf16 ? 0.95 : 0.9) * 5.3 * (double)((L + 511) / 512) ? 6 : 8;
+}
+
+// Whether the lanes kernel takes a whole block's scan, which it has been given, together with its dt projection: contexts of one super-step.
+inline bool scan_lanes_takes_low_dt(int64_t batch, int64_t L, int64_t D, int64_t dt_rank)
+{
+    return L <= 64 * lanes_tau(batch, L, D, true) && dt_rank % 8 == 0 && dt_rank <= kLanesLowRank;
+}
+
 // The fused layer step (state_step_conv_kernel) counts channels in 32 bits and launches a wavefront per 64 of them (32 with 32
 // states), whose threads along x have to stay below 2^32.  A wider layer takes the conv and the state step one after the other,
 // which count in 64 bits.

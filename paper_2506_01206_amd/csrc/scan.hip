@@ -28,6 +28,7 @@
 #include "../../include/mamba_hip.h"
 #include "device_math.h"
 #include "launch.h"
+#include "routes.h"
 
 // Chunk states of the allocation-free entry point (mamba_scan_fwd_static): device memory that comes with the code
 // object, one copy per GPU at its own address, held until the process ends.

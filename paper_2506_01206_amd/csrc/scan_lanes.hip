@@ -35,13 +35,13 @@
 // they are used); both are used after that.
 #include "device_math.h"
 #include "launch.h"
+#include "routes.h"
 
 namespace mamba {
 namespace {
 
-constexpr int kN = 16;                   // states per channel
+constexpr int kN = kLanesStates;         // states per channel
 constexpr int kParts = 4;                // groups of 4 states
-constexpr int kLowRank = 64;             // most dt columns that a scan takes the projection of
 constexpr int kBcPart = 66, kBcTau = kParts * kBcPart + 1;   // slots per state group and per token j of lds_B / lds_C
 
 __device__ __forceinline__ void lds_barrier_l()
@@ -189,7 +189,7 @@ template <> struct BcChunk<float> {      // 4 values: one group
 struct LowDt {
     const bf16_t *w;                 // (D, rank)
     bf16_t *out;                     // (batch, L, D): what the projection as a launch of its own would have stored
-    int rank;                        // a multiple of 8, at most kLowRank
+    int rank;                        // a multiple of 8, at most kLanesLowRank
 };
 
 // kG: channels per workgroup (2, 4 or 6); kTau: tokens per lane and super-step (4, 6 or 8), 64 kTau tokens no more than threads.
@@ -286,7 +286,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
     BcChunk<T> bc_nxt[kBcHeld];
 
     // Addresses are a base of the super-step, which is uniform (scalar registers), and 32 bits of the thread's own (512 rows
-    // of the widest layer that takes this kernel, some 4600 channels, are far below that): with 64 bits of its own for
+    // of the widest layer that takes this kernel, some 6200 channels, are far below that): with 64 bits of its own for
     // every tensor the walk had to spill, and a kernel with scratch memory takes 0.4 us longer to start.
     // The last token of a super-step, counted from its start; tokens past it re-read its row and are zeroed at use.
     auto last_of = [&](int64_t t_base) { return (int)(L - 1 - t_base < kT - 1 ? L - 1 - t_base : kT - 1); };
@@ -384,10 +384,10 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
         typedef float f32x16 __attribute__((ext_vector_type(16)));
         typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
         if (token_thread) {
-            u32x4 wf[kLowRank / 16], xf[2][kLowRank / 16];
+            u32x4 wf[kLanesLowRank / 16], xf[2][kLanesLowRank / 16];
             const int up = lane >> 5, ch = (lane & 31) < kG ? lane & 31 : kG - 1;
 #pragma unroll
-            for (int ks = 0; ks < kLowRank / 16; ++ks) {
+            for (int ks = 0; ks < kLanesLowRank / 16; ++ks) {
                 const int k = min(16 * ks + 8 * up, low.rank - 8);
                 wf[ks] = *reinterpret_cast<const u32x4 *>(low.w + (c0 + ch) * low.rank + k);
 #pragma unroll
@@ -401,7 +401,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
 #pragma unroll
                 for (int i = 0; i < 16; ++i) y[q][i] = 0.0f;
 #pragma unroll
-                for (int ks = 0; ks < kLowRank / 16; ++ks) {
+                for (int ks = 0; ks < kLanesLowRank / 16; ++ks) {
                     const bool in = 16 * ks + 8 * up < low.rank;   // (both operands: what stands in for the missing k may be infinite)
                     const u32x4 wv = in ? wf[ks] : u32x4(0u), xv = in ? xf[q][ks] : u32x4(0u);
                     y[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wv), __builtin_bit_cast(bf16x8, xv), y[q], 0, 0, 0);
@@ -585,71 +585,6 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
 
 namespace {
 
-// Channels per workgroup: what takes the fewest rounds of 256 workgroups times what one takes (a workgroup of fewer channels has
-// fewer wavefronts to a SIMD and is faster, but not in proportion).  us with 2 / 4 / 6 channels, bf16 | float32 (one session):
-//   1 x 1000 x  512  10.5*/ 10.6 / 13.8 | 12.3*/ 11.9 / 19.9      1 x  512 x 256   6.3*/  6.9 /  8.9 |  6.6*/  6.7 /  9.1
-//   1 x 1000 x  768  14.5 / 11.7*/ 14.2 | 16.0 / 13.2*/ 17.6      1 x 2000 x 1000 26.1 / 19.9*/ 24.0 | 28.5 / 23.0*/ 29.0
-//   1 x 2048 x 1536  36.3 / 37.6 / 25.0*| 37.0 / 43.2 / 31.3*     1 x 1000 x 2048 25.3 / 23.0*/ 30.7 | 28.8 / 24.0*/ 32.2
-int lanes_channels(int64_t batch, int64_t L, int64_t D)
-{
-    auto cost = [&](int64_t g, double round) { return (double)((batch * ((D + g - 1) / g) + 255) / 256) * round; };
-    const double six = cost(6, 1.0), four = cost(4, 0.8), two = cost(2, L <= 256 ? 0.68 : 0.7);
-    return two <= four && two <= six ? 2 : four <= six ? 4 : 6;
-}
-
-// ns: rounds of workgroups times what one takes, to which a token adds `six`, `four` or `two` by its channels
-double lanes_ns(int64_t batch, int64_t L, int64_t D, double six, double four, double two)
-{
-    const int64_t g = lanes_channels(batch, L, D), groups = batch * ((D + g - 1) / g);
-    const double first = g == 6 ? 6000.0 : g == 4 ? 5000.0 : 2500.0, token = g == 6 ? six : g == 4 ? four : two;
-    return (double)((groups + 255) / 256) * (first + token * (double)L);
-}
-
-}  // namespace
-
-// Shapes the lane-scan kernel serves: 16 states, token rows that can be read in 4-byte pieces from any even
-// channel, at least one full workgroup; and among those the ones it is expected to finish before the two-pass
-// kernels of scan.hip.  Its time is a number of rounds of 256 workgroups, every one walking the whole sequence;
-// that of the two-pass kernels goes with all tokens.  The line lies between the two types, since the choice, and with it the size of
-// the workspace, is not told the type, and it lies where the two met before the two-pass kernels' exponentials went into runs: those
-// have gained more by it than this one, so that between about 7000 tokens of 1536 channels (float32: 2700) and the line they are
-// ahead by up to 9 % (float32: 31 %).  But a call that this kernel took needs no workspace, and one made without would be
-// refused if the line moved down; a whole block, which brings its workspace and is bf16, could be told apart, and is not.
-// Down to 33 tokens (a call of fewer keeps the kernel that mamba_scan_kernel has always named for it; a block takes them too): one super-step
-// against three launches, 1 x 40 x 1536 6.1 / 16.0, 1 x 40 x 256 3.9 / 15.8, 2 x 40 x 1536 10.8 / 16.4, 1 x 40 x 4096 15.4 / 16.3.
-// us, lanes / two-pass, bf16 | float32, one session, four sets of operands in turn (on one set, which stays in the last-level
-// cache, 1 x 8192 x 1536 takes 81 | 110 here); * what the line takes:
-//   1 x  600 x  768  11.1*/ 20.8 | 12.0*/ 20.9       1 x 2048 x 1536  25.8*/ 35.5 | 31.4*/ 35.9       1 x   64 x 4096  15.4*/ 17.3 |  15.6*/ 17.0
-//   1 x 2000 x  768  19.6*/ 30.1 | 22.7*/ 26.5       1 x 6000 x 1536  68.7*/ 73.5 | 93.5*/ 68.5       1 x 8192 x 1536  97.0*/ 92.6 | 123.8*/ 87.0
-//   1 x 4000 x  768  34.0 / 37.4*| 41.0 / 37.2*      1 x 7000 x 1536  84.0*/ 83.1 |108.0*/ 79.3       1 x 10240 x 1536 125.7 / 110.7*| 152.0 / 104.2*
-//   1 x 2000 x  256  17.0 / 21.8*| 21.8 / 22.0*      1 x 4000 x 1024  34.5*/ 44.3 | 41.7*/ 42.6       1 x 4000 x 512   33.8 / 32.9*| 42.1 / 29.6*
-//   1 x 3000 x 1536  34.4*/ 45.5 | 48.4*/ 43.8       1 x 4000 x 1536  43.9*/ 53.9 | 65.3*/ 52.9       1 x 9900 x 1536 120.2*/110.6 | 151.8*/ 104.3
-//   4 x 1000 x  768  28.3*/ 35.7 | 34.2*/ 35.5       1 x 2000 x 2048  37.6*/ 43.5 | 43.0*/ 41.6       2 x 3000 x 1536  75.2*/ 73.2 | 98.0*/ 68.4
-bool scan_lanes_applies(int64_t batch, int64_t L, int64_t D, int64_t N)
-{
-    if (N != kN || D % 2 != 0 || D < 6 || L <= 32 || batch > 65535) return false;
-    const double two_pass_ns = 24000.0 + 9.8 * (double)L * ((double)batch * (double)D / 1536.0);
-    return lanes_ns(batch, L, D, 11.6, 9.7, 12.5) < two_pass_ns;
-}
-
-// The same in a whole block, whose scan finds its operands in the last-level cache as long as the block's four tensors of (rows, D) bf16 fit
-// its 256 MB: the small pieces of the token rows that this kernel reads come sooner from there, the two passes gain nothing by it.
-// us of a block, two passes / lanes, three sets of operands in turn (* what this takes; a line within 2 us is left to the two passes):
-//   1 x 10500 x 1536 260 / 243*      2 x 4000 x 1536 205 / 196*      3 x 3000 x 1536 241 / 219*      1 x  8000 x 1024 140 / 133*      1 x 6000 x 4096 545* / 554
-//   1 x 16000 x 1536 368 / 346*      2 x 8000 x 1536 367 / 350*      4 x 1000 x 1536 127*/ 125       1 x 10000 x  768 134*/ 143       1 x 3000 x 2048 133 / 127*
-//   1 x 20000 x 1536 458 / 437*      4 x 8000 x 1536 634*/ 724       8 x  500 x 1536 125*/ 139       1 x  9000 x 3072 537 / 518*      2 x 1500 x 2048 133* / 139
-//   1 x    16 x 1536  25 /  21*      1 x   40 x 1536  36 /  22*      2 x   40 x 1536  37 /  28*      4 x   40 x 1536  40*/  39       1 x    2 x 1536  20*/ 20
-//   1 x 32768 x 1536 634*/ 744       4 x 4000 x 1536 370*/ 362       8 x 2000 x 1536 369*/ 377       1 x  6000 x  512  88*/ 81
-bool scan_lanes_in_block(int64_t batch, int64_t L, int64_t D, int64_t N)
-{
-    if (scan_kernel_choice(batch, L, D, N) != kScanChunked) return scan_kernel_choice(batch, L, D, N) == kScanLanes;
-    if (N != kN || D % 2 != 0 || D < 6 || L < 4 || batch > 65535 || (double)batch * (double)L * (double)D > 32e6) return false;
-    const double two_pass_ns = 24000.0 + 10.0 * (double)L * ((double)batch * (double)D / 1536.0);
-    return lanes_ns(batch, L, D, 9.9, 8.3, 10.7) < two_pass_ns - 2000.0;
-}
-
-namespace {
-
 template <typename T, int G, int TAU> hipError_t launch_lanes(const ScanArgs &a, hipStream_t stream)
 {
     const int64_t n_groups = (a.D + G - 1) / G;
@@ -677,24 +612,9 @@ template <typename T, int G, int TAU> hipError_t launch_lanes(const ScanArgs &a,
     return hipGetLastError();
 }
 
-// Tokens of a lane, 64 times that to a super-step: what takes the fewest super-steps times what one takes, which is 5.3 us with 8 tokens,
-// 4.1 with 6 and 3.2 with 4 (1536 channels; a last one that is not full takes somewhat less).  Two channels to a workgroup leave no
-// threads for more than 4.  us with 4 / 6 / 8 tokens:
-//    200 x 1536  7.25*/ 8.37 / 9.05     400 x 1536 10.45 / 12.56 / 9.84*    1000 x 1536 17.06 / 16.92 / 15.49*     700 x 1000 10.68 / 10.33*/ 11.66
-//    300 x 1536 10.42 / 8.79*/ 9.48     600 x 1536 13.49 / 12.69*/14.70     1100 x 1536 19.82 / 17.06*/ 19.72      350 x 1536 float32 11.43 / 9.75*/ 10.70
-//    384 x 1536 10.51 / 9.19*/ 9.83     768 x 1536 13.73 / 13.01*/14.92     1900 x 1536 29.56 / 26.07 / 25.83*     700 x 1536 float32 16.88 / 16.21*/ 18.23
-// In float32, where a super-step's B and C are not requested ahead, one super-step more costs more; us with 6 / 8, bf16 | float32:
-//   2251 x  488, batch 6  82.6*/ 82.8 | 108.6 / 107.2*     2107 x 1392, batch 2  55.7*/ 57.4 | 77.4 / 76.2*     2101 x 504, batch 2  25.1*/ 25.6 | 28.5 / 27.9*
-//   2682 x  456, batch 3  34.1*/ 36.3 |  42.7 / 42.4*      1124 x 2304           32.1*/ 36.6 | 38.6*/ 42.5
-int lanes_tau(int64_t batch, int64_t L, int64_t D, int io)
-{
-    if (L <= 256 || lanes_channels(batch, L, D) == 2) return 4;
-    return 4.1 * (double)((L + 383) / 384) < (io == kIoBf16 ? 0.95 : 0.9) * 5.3 * (double)((L + 511) / 512) ? 6 : 8;
-}
-
 template <typename T> hipError_t launch_lanes_io(const ScanArgs &a, hipStream_t stream)
 {
-    switch (10 * lanes_channels(a.batch, a.L, a.D) + lanes_tau(a.batch, a.L, a.D, a.io)) {
+    switch (10 * lanes_channels(a.batch, a.L, a.D) + lanes_tau(a.batch, a.L, a.D, a.io == kIoBf16)) {
     case 24: return launch_lanes<T, 2, 4>(a, stream);
     case 44: return launch_lanes<T, 4, 4>(a, stream);
     case 46: return launch_lanes<T, 4, 6>(a, stream);
@@ -706,11 +626,6 @@ template <typename T> hipError_t launch_lanes_io(const ScanArgs &a, hipStream_t 
 }
 
 }  // namespace
-
-bool scan_lanes_takes_low_dt(int64_t batch, int64_t L, int64_t D, int64_t N, int64_t dt_rank)
-{
-    return scan_lanes_in_block(batch, L, D, N) && L <= 64 * lanes_tau(batch, L, D, kIoBf16) && dt_rank % 8 == 0 && dt_rank <= kLowRank;
-}
 
 hipError_t launch_scan_lanes(const ScanArgs &a, hipStream_t stream)
 {

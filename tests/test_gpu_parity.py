@@ -1537,6 +1537,7 @@ def test_block_conv_in_the_way_in(m, B, L, dm, D):
 
 
 @pytest.mark.parametrize("B,L,dm,D,R", [(1, 4, 64, 256, 16), (1, 17, 64, 1536, 48), (2, 33, 64, 768, 24), (1, 3, 64, 256, 16),   # shorter than a call's own
+                                        (1, 16, 64, 1536, 48), (3, 16, 64, 1536, 48), (1, 15, 64, 1024, 96),   # one chunk, taken and not; dt apart
                                         (1, 64, 64, 64, 8), (3, 65, 64, 96, 16), (1, 256, 64, 512, 24), (1, 256, 128, 1000, 40),      # 2 or 4 channels
                                         (1, 255, 64, 1536, 48), (1, 257, 64, 1536, 64), (1, 511, 64, 1000, 56), (1, 512, 64, 1528, 48),  # 4 or 6
                                         (1, 513, 64, 1536, 48), (1, 300, 64, 1536, 72)])                                                # not taken

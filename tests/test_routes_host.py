@@ -25,6 +25,11 @@ extern "C" int64_t row_blocks(int64_t M, int64_t BM, int conv) { return mamba::r
 extern "C" int wide192(int64_t M, int64_t N, int64_t K, int wide) { return mamba::linear_wide192(M, N, K, wide, mamba::linear_tiles(M, N, K, wide)); }
 extern "C" int route(int64_t M, int64_t n0, int64_t n1, int64_t n2, int64_t K)
 { const int64_t width[3] = {n0, n1, n2}; return mamba::linear_route(M, width, K); }
+extern "C" int lanes_call(int64_t batch, int64_t L, int64_t D, int64_t N) { return mamba::scan_lanes_applies(batch, L, D, N); }
+extern "C" int lanes_block(int64_t batch, int64_t L, int64_t D, int64_t N, int64_t dt_rank, int64_t chunks)
+{ return mamba::scan_lanes_in_block(batch, L, D, N, dt_rank, chunks); }
+extern "C" int lanes_low_dt(int64_t batch, int64_t L, int64_t D, int64_t dt_rank) { return mamba::scan_lanes_takes_low_dt(batch, L, D, dt_rank); }
+extern "C" int lanes_tokens(int64_t batch, int64_t L, int64_t D, int bf16) { return mamba::lanes_tau(batch, L, D, bf16 != 0); }
 extern "C" int xdt(int64_t M, int64_t d_inner, int64_t dt_rank, int64_t N, unsigned *groups)
 { return mamba::xdt_plan(M, d_inner, dt_rank, N, groups); }
 """
@@ -53,6 +58,10 @@ def routes(tmp_path_factory):
     lib.wide256x192.argtypes = [i64, i64, i64, i32]
     lib.conv_tiles.argtypes = [i64] * 4
     lib.row_blocks.argtypes, lib.row_blocks.restype = [i64, i64, i32], i64
+    lib.lanes_call.argtypes = [i64] * 4
+    lib.lanes_block.argtypes = [i64] * 6
+    lib.lanes_low_dt.argtypes = [i64] * 4
+    lib.lanes_tokens.argtypes = [i64] * 3 + [i32]
     lib.route.argtypes = [i64] * 5
     lib.xdt.argtypes = [i64, i64, i64, i64, ctypes.POINTER(ctypes.c_uint)]
     return lib
@@ -293,3 +302,34 @@ def test_every_product_of_the_parity_tests_reaches_the_kernel_it_is_there_for(ro
     # the launches that have to agree, and the sampled rows
     assert [kernel(*s) for s in ((8192, 4096, 768), (16384, 1152, 1536), (4096, 768, 1536))] == ["kWide256", "kWide128", "kRing128"]
     assert kernel(32768, 3072, 768, (1536, 1536)) == "kWide256" and kernel(32768, 768, 1536) == "kWide256x192"
+
+
+def test_short_contexts_of_a_block_keep_the_single_launch_where_the_lanes_scan_takes_several_rounds(routes):
+    """Up to 16 tokens the two passes are one launch: blocks measured faster and slower on the lanes kernel than on that one."""
+    takes = lambda b, L, D, R=48, chunks=1: bool(routes.lanes_block(b, L, D, 16, R, chunks))
+    for s in [(1, 4, 256), (2, 4, 256), (1, 6, 768), (1, 16, 256), (1, 16, 1536), (1, 8, 1536), (2, 15, 1024), (12, 16, 256), (4, 13, 256), (1, 16, 2048),
+              (2, 12, 256), (1, 15, 1024, 96)]:
+        assert takes(*s), s
+    for s in [(1, 4, 1536), (3, 4, 1536), (3, 16, 1536), (6, 8, 768), (12, 8, 256), (12, 4, 256), (1, 8, 4096), (1, 16, 4096), (2, 16, 1536), (3, 9, 768),
+              (2, 5, 2048), (3, 5, 1024), (1, 5, 2560), (1, 7, 3072), (14, 9, 256, 64), (6, 16, 768), (1, 16, 2560, 80), (9, 10, 256), (17, 8, 64),
+              (1, 6, 2048), (1, 4, 768, 96), (1, 3, 64), (8, 6, 1536), (1, 9, 5120)]:
+        assert not takes(*s), s
+    # more tokens are three launches: the other line
+    for s in [(1, 17, 1536), (1, 40, 1536), (2, 17, 1024), (3, 20, 1536), (1, 24, 2048)]:
+        assert takes(*s, 48, 2), s
+    assert not takes(3, 25, 2560, 48, 2) and not takes(1, 40, 1537, 48, 3) and not routes.lanes_block(1, 40, 1536, 8, 48, 3)
+    assert routes.lanes_low_dt(1, 512, 1536, 64) and not routes.lanes_low_dt(1, 513, 1536, 64) and not routes.lanes_low_dt(1, 40, 1536, 72)
+
+
+def test_lanes_scan_counts_its_places_in_32_bits(routes):
+    """The kernel addresses the rows of a super-step, up to 512, by 32-bit element offsets, of layers as wide as its lines let through."""
+    widest = 0
+    for D in [2 * i for i in range(3, 5000)] + [1 << k for k in range(14, 31)]:
+        for L in (4, 16, 17, 33, 64, 300, 512, 1000, 4000, 5050, 32000000 // D, 1 << 20):
+            for chunks in (1, 3):
+                if routes.lanes_call(1, L, D, 16) or routes.lanes_block(1, L, D, 16, 48, chunks):
+                    widest = max(widest, D)
+    assert 6144 <= widest <= 6200 and 512 * widest < 1 << 32
+    # tokens to a lane: what a call's super-steps come to
+    assert [routes.lanes_tokens(1, L, 1536, 1) for L in (256, 257, 384, 385, 512, 700, 1100)] == [4, 6, 6, 8, 8, 6, 6]
+    assert routes.lanes_tokens(1, 1100, 512, 1) == 4 and routes.lanes_tokens(1, 700, 1536, 0) == 6 and routes.lanes_tokens(6, 2251, 488, 0) == 8
