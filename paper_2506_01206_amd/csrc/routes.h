@@ -45,11 +45,17 @@ inline int lanes_channels(int64_t batch, int64_t L, int64_t D)
     return two <= four && two <= six ? 2 : four <= six ? 4 : 6;
 }
 
-// ns: rounds of workgroups times what one takes, to which a token adds `six`, `four` or `two` by its channels.  by_xcd: with the workgroups
-// that fill the last group of 8, one to an XCD, as the kernel's grid has them
+// Workgroups of a launch.  by_xcd: with those that fill the last group of 8 of a row, one to an XCD, as the grid has them
+inline int64_t lanes_groups(int64_t batch, int64_t L, int64_t D, bool by_xcd)
+{
+    const int64_t g = lanes_channels(batch, L, D), row = (D + g - 1) / g;
+    return batch * (by_xcd ? (row + 7) / 8 * 8 : row);
+}
+
+// ns: rounds of workgroups times what one takes, to which a token adds `six`, `four` or `two` by its channels
 inline double lanes_ns(int64_t batch, int64_t L, int64_t D, double six, double four, double two, bool by_xcd = false)
 {
-    const int64_t g = lanes_channels(batch, L, D), row = (D + g - 1) / g, groups = batch * (by_xcd ? (row + 7) / 8 * 8 : row);
+    const int64_t g = lanes_channels(batch, L, D), groups = lanes_groups(batch, L, D, by_xcd);
     const double first = g == 6 ? 6000.0 : g == 4 ? 5000.0 : 2500.0, token = g == 6 ? six : g == 4 ? four : two;
     return (double)((groups + 255) / 256) * (first + token * (double)L);
 }
@@ -81,12 +87,18 @@ inline bool scan_lanes_applies(int64_t batch, int64_t L, int64_t D, int64_t N)
 
 // The same in a whole block, whose scan finds its operands in the last-level cache as long as the block's four tensors of (rows, D) bf16 fit
 // its 256 MB: the small pieces of the token rows that this kernel reads come sooner from there, the two passes gain nothing by it.
-// us of a block, two passes / lanes, three sets of operands in turn (* what this takes; a line within 2 us is left to the two passes):
+// What is predicted less than 15 % ahead (8 % where workgroups of fewer channels come in one round) is taken only where the workgroups, dealt
+// to the XCDs in whole groups of 8, fill the last round: CUs that stand idle in it, and rows cut to other than whole lines, had cost up to
+// 16 % of a block (lanes are thought 4 % ahead on 2 x 9084 x 640, whose 240 workgroups leave one CU in sixteen idle).  1100 blocks of 256 to 6144
+// channels, 17 to 22000 tokens, near the line: 5.0 % ahead of the two passes on average, one of 320 taken slower by more than 1.5 % (without that
+// 4.7 %, 68 of 430 slower).
+// us of a block, two passes / lanes, three sets of operands in turn (* what this takes; a line within 3 us is left to the two passes):
 //   1 x 10500 x 1536 260 / 243*      2 x 4000 x 1536 205 / 196*      3 x 3000 x 1536 241 / 219*      1 x  8000 x 1024 140 / 133*      1 x 6000 x 4096 545* / 554
 //   1 x 16000 x 1536 368 / 346*      2 x 8000 x 1536 367 / 350*      4 x 1000 x 1536 127*/ 125       1 x 10000 x  768 134*/ 143       1 x 3000 x 2048 133 / 127*
 //   1 x 20000 x 1536 458 / 437*      4 x 8000 x 1536 634*/ 724       8 x  500 x 1536 125*/ 139       1 x  9000 x 3072 537 / 518*      2 x 1500 x 2048 133* / 139
-//   1 x    16 x 1536  25 /  21*      1 x   40 x 1536  36 /  22*      2 x   40 x 1536  37 /  28*      4 x   40 x 1536  40*/  39       1 x    2 x 1536  20*/ 20
 //   1 x 32768 x 1536 634*/ 744       4 x 4000 x 1536 370*/ 362       8 x 2000 x 1536 369*/ 377       1 x  6000 x  512  88*/ 81
+//   2 x  9084 x  640 162*/ 192       1 x 6653 x 1280 125*/ 140       2 x 1164 x 2048  99*/ 109       1 x 14920 x 1408 332*/ 361       3 x 6795 x 448 157*/ 169
+//   1 x    40 x 1536  36 /  22*      2 x   40 x 1536  37 /  28*      4 x   40 x 1536  40*/  39       1 x   493 x 3456  65*/  58       1 x 2041 x 256  43*/  38
 // Contexts that the two passes take as one chunk (up to 16 tokens) are one launch there as well, of about 0.4 us a token, and dt has one
 // of its own: the lanes kernel is ahead where its workgroups come in one round (dealt to the XCDs in whole groups of 8), and on more
 // tokens the more rounds they come in.  400 blocks of 64 to 5120 channels, 4 to 16 tokens: 4.1 % ahead of the two passes, 4.25 the better
@@ -99,15 +111,18 @@ inline bool scan_lanes_applies(int64_t batch, int64_t L, int64_t D, int64_t N)
 inline bool scan_lanes_in_block(int64_t batch, int64_t L, int64_t D, int64_t N, int64_t dt_rank, int64_t chunks)
 {
     if (N != kLanesStates || D % 2 != 0 || D < 6 || L < 4 || batch > 65535 || (double)batch * (double)L * (double)D > 32e6) return false;
+    const double own = lanes_ns(batch, L, D, 9.9, 8.3, 10.7, true);
     if (chunks == 1) {
-        const int64_t g = lanes_channels(batch, L, D);
-        const double own = lanes_ns(batch, L, D, 9.9, 8.3, 10.7, true);
-        const double dt_apart = dt_rank <= kLanesLowRank ? 0.0 : g == 6 ? 2200.0 : 4250.0;
+        const bool six = lanes_channels(batch, L, D) == 6;
+        const double dt_apart = dt_rank <= kLanesLowRank ? 0.0 : six ? 2200.0 : 4250.0;
         // (a single chunk of more tokens has channels for the whole chip)
-        return L <= 16 && own < (g == 6 ? 3000.0 + 500.0 * (double)L : 2200.0 + 950.0 * (double)L) - dt_apart;
+        return L <= 16 && own < (six ? 3000.0 + 500.0 * (double)L : 2200.0 + 950.0 * (double)L) - dt_apart;
     }
     const double two_pass_ns = 24000.0 + 10.0 * (double)L * ((double)batch * (double)D / 1536.0);
-    return lanes_ns(batch, L, D, 9.9, 8.3, 10.7) < two_pass_ns - 2000.0;
+    const int64_t groups = lanes_groups(batch, L, D, true);
+    const bool filled = (double)groups >= 0.95 * (double)((groups + 255) / 256 * 256);
+    const double ahead = groups <= 256 && lanes_channels(batch, L, D) < 6 ? 0.92 : 0.85;
+    return own < ahead * two_pass_ns || (filled && own < two_pass_ns - 3000.0);
 }
 
 // Tokens of a lane, 64 times that to a super-step: what takes the fewest super-steps times what one takes, which is 5.3 us with 8 tokens,

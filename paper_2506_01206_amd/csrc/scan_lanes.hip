@@ -286,7 +286,7 @@ scan_lanes_kernel(const T *x, const T *dt, const float *__restrict__ A, const T 
     BcChunk<T> bc_nxt[kBcHeld];
 
     // Addresses are a base of the super-step, which is uniform (scalar registers), and 32 bits of the thread's own (512 rows
-    // of the widest layer that takes this kernel, some 6200 channels, are far below that): with 64 bits of its own for
+    // of the widest layer that takes this kernel, 4608 channels, are far below that): with 64 bits of its own for
     // every tensor the walk had to spill, and a kernel with scratch memory takes 0.4 us longer to start.
     // The last token of a super-step, counted from its start; tokens past it re-read its row and are zeroed at use.
     auto last_of = [&](int64_t t_base) { return (int)(L - 1 - t_base < kT - 1 ? L - 1 - t_base : kT - 1); };

@@ -329,7 +329,19 @@ def test_lanes_scan_counts_its_places_in_32_bits(routes):
             for chunks in (1, 3):
                 if routes.lanes_call(1, L, D, 16) or routes.lanes_block(1, L, D, 16, 48, chunks):
                     widest = max(widest, D)
-    assert 6144 <= widest <= 6200 and 512 * widest < 1 << 32
+    assert 4600 <= widest <= 4608 and 512 * widest < 1 << 32
     # tokens to a lane: what a call's super-steps come to
     assert [routes.lanes_tokens(1, L, 1536, 1) for L in (256, 257, 384, 385, 512, 700, 1100)] == [4, 6, 6, 8, 8, 6, 6]
     assert routes.lanes_tokens(1, 1100, 512, 1) == 4 and routes.lanes_tokens(1, 700, 1536, 0) == 6 and routes.lanes_tokens(6, 2251, 488, 0) == 8
+
+
+def test_blocks_take_the_lanes_scan_where_its_last_round_is_full(routes):
+    """Blocks near the line between the lanes scan and the two passes, measured faster and slower."""
+    takes = lambda b, L, D: bool(routes.lanes_block(b, L, D, 16, 48, 5))
+    for s in [(1, 10500, 1536), (1, 16000, 1536), (1, 20000, 1536), (2, 4000, 1536), (2, 8000, 1536), (3, 3000, 1536), (1, 8000, 1024), (1, 9000, 3072),
+              (1, 3000, 2048), (1, 40, 1536), (2, 40, 1536), (3, 1000, 1024), (1, 2041, 256), (1, 4065, 768), (2, 4101, 384), (1, 17, 4096)]:
+        assert takes(*s), s
+    for s in [(2, 9084, 640), (4, 8311, 320), (1, 6653, 1280), (2, 521, 1792), (3, 10189, 448), (2, 1164, 2048), (1, 1577, 2368), (1, 14920, 1408),
+              (2, 8701, 704), (1, 6769, 2816), (2, 14536, 704), (1, 32768, 1536), (4, 8000, 1536), (1, 10000, 768), (8, 500, 1536), (1, 6000, 4096),
+              (4, 40, 1536), (2, 1500, 2048), (8, 2000, 1536), (1, 6000, 512)]:
+        assert not takes(*s), s
