@@ -249,8 +249,10 @@ inline LinearKernel linear_ring(int64_t M, int64_t N, int64_t K, bool vector_out
 
 // The way into a block on a context (x | z = u W_in^T, then the conv over time on x) in one launch: the tile whose product takes least,
 // by rounds of workgroups over the chip; or the product and the conv apart, where the rows that a tile of x shares with the one before
-// it cost more than the conv's launch (512 rows of 4096 channels: 320 128 x 128 tiles instead of 256), on rows that the few-row
-// kernels take, and on what the tiles cannot.  Fitted to 179 products of seven models, 64 to 32768 rows: the choice costs 0.9 % more
+// it cost more than the conv's launch (512 rows of 4096 channels: 320 128 x 128 tiles instead of 256), on fewer than 64 rows, on a product
+// that the few-row kernels take and share the k of, where that is long for so few tiles, and on what the tiles cannot.  (Those on 500 blocks of 64
+// to 700 rows, us of a block apart / together (rows, D, K): 70, 256, 2496 24.1*/ 27.6, 133, 128, 2112 24.0*/ 26.1, 116, 512, 2048 24.7*/ 26.0, but 64,
+// 1536, 768 together; the line keeps 94 % of what the better of the two would save.)  Fitted to 179 products of seven models, 64 to 32768 rows: the choice costs 0.9 % more
 // than the best of them on average, and the launch 15 % less than the two.  us, product + conv / the launch on 64 x 64 / 64 x 128 / 128 x 128
 // ring, 128 x 128 / 192 x 128 / 256 x 256 wide tiles (D, K):
 //     100 x 1536,  768   8.3 /  6.9*/  9.1 /   -  /   -  /   -  /   -       2048 x 1536,  768  19.8 / 28.2 / 32.6 / 21.3 / 17.8*/ 22.1 / 27.0
@@ -267,6 +269,7 @@ inline ConvTiles linear_conv_tiles(int64_t M, int64_t D, int64_t K, int64_t taps
 {
     if (taps != kConvTaps || M < 64 || M > (int64_t)1 << 23 || D % 64 != 0 || D > (int64_t)1 << 20 || K % 64 != 0 || K < 256 || K > kToLdsLongestK)
         return kConvApart;
+    if (linear_few(M, 2 * D, K) != kNoKernel && K > 700 + 16 * ((M + 63) / 64 * (D / 32))) return kConvApart;
     // us: a launch, a round of workgroups, and where two share a CU a round that gives no CU a second one
     struct Tile { ConvTiles kind; int64_t bm, bn, per_round; double launch, round, round_k, half, half_k; };
     const Tile all[6] = {{kConvRing64, 64, 64, 512, 2.6, 1.5, .0076, 1.1, .0051},    {kConvRing64x128, 64, 128, 256, 2.5, 2.5, .0067, 0, 0},

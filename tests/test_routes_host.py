@@ -191,12 +191,14 @@ def test_conv_in_the_way_into_a_block(routes):
     than a launch, and never a tile that the shape does not divide into.  Every row has one block that stores it, and a tile of x the
     three rows before its own."""
     apart, r64, r64x128, r128, w128, w192, w256 = range(7)
-    for kind, shapes in {r64: [(64, 64, 256), (189, 128, 256), (333, 1536, 768), (600, 512, 256), (64, 1 << 20, 256)],
+    for kind, shapes in {r64: [(64, 1536, 768), (100, 1536, 768), (64, 64, 256), (189, 128, 256), (333, 1536, 768), (600, 512, 256), (64, 1 << 20, 256)],
                          r64x128: [(200, 4096, 2048), (100, 5120, 2560)], r128: [(1000, 1024, 256), (2003, 512, 256), (1000, 1536, 768)],
                          w128: [(1254, 1536, 256), (1264, 1536, 256), (2048, 1536, 768)],
                          w192: [(1281, 1536, 384), (8000, 1536, 768)],
                          w256: [(4031, 2048, 384), (4048, 2048, 384), (4000, 4096, 2048), (10000, 1536, 768), (16384, 3072, 1536), (32768, 1536, 768)],
-                         apart: [(63, 1536, 768), (333, 1536, 192), (333, 1536, 800), (333, 1500, 768), (512, 4096, 2048), (2048, 4096, 2048),
+                         # a long k that the few-row kernels share among wavefronts
+                         apart: [(70, 256, 2496), (65, 128, 2112), (133, 128, 2112), (86, 128, 2112), (67, 192, 1600), (116, 512, 2048), (258, 128, 1664),
+                                 (182, 64, 2432), (66, 448, 1536), (112, 128, 1536), (63, 1536, 768), (333, 1536, 192), (333, 1536, 800), (333, 1500, 768), (512, 4096, 2048), (2048, 4096, 2048),
                                  (1 << 24, 128, 256), (333, (1 << 20) + 64, 768)]}.items():
         for s in shapes:
             got = routes.conv_tiles(*s, 4)
