@@ -397,10 +397,16 @@ inline bool linear_wide256(int64_t M, int64_t N, int64_t K, bool wide)
 //    4096 x 6144, K = 1536   81.4 /  81.9     16384 x 1536, K = 3072  144.8 / 135.2, block 796 / 788          6000 x  768, K =  768   14.8*/  18.6
 // Three hundredths short of 192 x 128 tiles, of which two to a CU hide each other's residual: 6000 x 1536, K = 3072 (1.9 short) is 62.5 / 57.1 in
 // a row, but 335 / 339 in a block, 16384 x 1152, K = 2304 91.1 / 87.0 and 556* / 559.  Widths that those cannot take have slower tiles to
-// compare with: 16384 x 576, K = 1152 block 284 / 267, 20000 x 576 360 / 330.
+// compare with: 16384 x 576, K = 1152 block 284 / 267, 20000 x 576 360 / 330.  At widths that 128 divides, only
+// where they fill the last round: in one that they do not, 192 x 128 tiles, two to a CU, lose less than the count says, the more the longer
+// the k (5578 x 1536, K = 6400 111* / 123, 2221 x 4224, K = 6016 114* / 126, 1166 x 6912, K = 2944 60* / 68; of 40 such products 35 are slower here,
+// 5 % on average; of 147 that fill it 9, by 5 % at most, and 7 % faster on average), while at the others all of 263 are faster, by a half.
+// So whole rounds and little else: of out_proj's row counts from 1000 to 32768 at 768 x K = 1536 those from 16321 to 16384 and from 32641 to 32768.
 inline bool linear_wide256x192(int64_t M, int64_t N, int64_t K, bool vector_out)
 {
     if (!vector_out || M < 1000 || N % 192 != 0 || K % 128 != 0 || K > kToLdsLongestK) return false;
+    const int64_t tiles = ((M + 255) / 256) * (N / 192);
+    if (N % 128 == 0 && (double)tiles < 0.95 * (double)((tiles + 255) / 256 * 256)) return false;
     const double own = wide_tiles_us(M, N, K, 256, 192, 256, 0.5, 7.5, .0195, .66);
     return own < .99 * wide128_us(M, N, K) && own < (N % 128 == 0 ? .97 : 1.0) * wide192_us(M, N, K) && (N % 256 != 0 || own < .99 * wide256_us(M, N, K));
 }

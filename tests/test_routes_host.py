@@ -227,7 +227,12 @@ def test_256_x_192_tiles_by_rounds(routes):
     """Products measured faster and slower on 256 x 192 tiles, those that the parity tests name for other tiles, and never without the conditions."""
     for s in [(16384, 1536, 768), (32768, 768, 1536), (16384, 768, 1536), (4096, 3072, 768), (32768, 1152, 2304), (16384, 1536, 3072), (16384, 576, 1152)]:
         assert routes.wide256x192(*s, 1) and not routes.wide256x192(*s, 0), s
-    for s in [(8000, 768, 1536), (6000, 768, 768), (24000, 768, 768), (8000, 3072, 768), (32768, 3072, 768), (32768, 6144, 1536), (10000, 1536, 3072), (6000, 1536, 3072), (16384, 1152, 2304),
+    # widths that 128 does not divide: any number of rounds; others: whole ones
+    for s in [(1856, 4800, 6016), (2429, 4800, 7552), (3615, 2880, 4352), (4993, 7296, 4096), (1240, 9600, 5888), (21699, 1152, 2048)]:
+        assert routes.wide256x192(*s, 1), s
+    for s in [(5578, 1536, 6400), (2221, 4224, 6016), (7419, 1152, 6528), (25274, 768, 7040), (2787, 3072, 3456), (1790, 5376, 4224),
+              (1730, 5376, 2560), (1166, 6912, 2944), (1277, 7296, 2944), (1016, 8832, 1920), (1765, 6144, 3072),
+              (8000, 768, 1536), (6000, 768, 768), (24000, 768, 768), (8000, 3072, 768), (32768, 3072, 768), (32768, 6144, 1536), (10000, 1536, 3072), (6000, 1536, 3072), (16384, 1152, 2304),
               (999, 768, 768), (16384, 1600, 768), (16384, 1536, 832), (16384, 1536, (1 << 28) + 128),
               (8000, 3072, 256), (11905, 768, 1536), (12095, 768, 128), (4097, 3072, 128), (16385, 768, 256), (2977, 3072, 128), (5003, 3072, 384)]:
         assert not routes.wide256x192(*s, 1), s
