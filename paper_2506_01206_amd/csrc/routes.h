@@ -236,12 +236,17 @@ inline LinearKernel linear_few(int64_t M, int64_t N, int64_t K)
 //   2048 x  512, K = 1024  11.1 / 8.0*/ 9.4 /11.6      3000 x  512, K = 1024  15.0 / 9.8 / 9.5*/11.9      3000 x 1280, K = 2560  37.4 / 36.2 / 31.9 / 28.6*
 // Beyond one round the tile kernels are ahead: 1500 x 3072 13.7 / 18.4 / 19.5 / 18.9, 2048 x 3072 15.7 / 22.1 / 20.6 / 19.3.  With a short
 // k there is little to have under way: K = 256, 1024 x 1024 4.8 / 4.5* 64 x 64, but 1024 x 2048 5.8* / 5.9 64 x 128, 1500 x 1536 6.2* / 6.5
-// 128 x 128; K = 384, 1000 x 1536 7.0 / 6.7* 64 x 128.
+// 128 x 128; K = 384, 1000 x 1536 7.0 / 6.7* 64 x 128 (64 x 64 tiles of K = 256 8.8 % ahead on 65 products, 64 x 128 of K = 384 2.7 % on 37, a third
+// of them slower, by 7 % at most).
+// More 64 x 64 tiles than CUs, of a long k, and rows for three of them or fewer: nearly all of what a tile loads is w, from memory, and the CUs
+// that have two are as long as twice one.  335 products of 256 to 320 tiles: with the line for those at 270 7 are slower than on the kernel
+// before, by 7 % at most, and 19.5 % ahead on average; at 320 throughout 30, by up to 23 %, and 19.2 %.  us on the kernel before / 64 x 64 / 64 x 128:
+//    109 x 10240, K = 8064  59.8 / 78.1 / 63.7*      87 x 10240, K = 3584  28.9 / 35.8 / 30.4*     102 x 9856, K = 4224  34.7 / 35.1 / 29.4*
 inline LinearKernel linear_ring(int64_t M, int64_t N, int64_t K, bool vector_out)
 {
     if (!vector_out || K % 64 != 0 || K < 256 || K > kToLdsLongestK || M < 64 || N % 64 != 0) return kNoKernel;
     auto tiles = [&](int64_t bm, int64_t bn) { return ((N + bn - 1) / bn) * ((M + bm - 1) / bm); };
-    if (tiles(64, 64) <= 320) return kRing64;
+    if (tiles(64, 64) <= (K >= 2048 && M <= 192 ? 270 : 320)) return kRing64;
     if (N % 128 != 0 || K < 384) return kNoKernel;
     if (tiles(64, 128) <= 256) return kRing64x128;
     return M >= 128 && tiles(128, 128) <= 256 ? kRing128 : kNoKernel;

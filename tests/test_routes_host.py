@@ -176,6 +176,12 @@ def test_192_row_tiles(routes):
 def test_one_round_of_tiles(routes):
     """The products that the parity test names for each tile, more than a round left alone, and never without the conditions."""
     none, t64, t64x128, t128 = (KERNELS.index(k) for k in ("kNoKernel", "kRing64", "kRing64x128", "kRing128"))
+    # more 64 x 64 tiles than CUs: not with a long k and few rows
+    for s in [(109, 10240, 8064), (87, 10240, 3584), (84, 9600, 7296), (166, 6656, 5632), (126, 9728, 5120), (85, 10240, 2816)]:
+        assert routes.ring(*s, 1) == t64x128, s
+    for s in [(126, 8192, 5120), (86, 8640, 2048), (85, 10240, 1984), (193, 5120, 5120), (593, 2048, 2688)]:
+        assert routes.ring(*s, 1) == t64, s
+    assert routes.ring(101, 8768, 8000, 1) == none
     for want, cases in ((t64, [(641, 1280, 256), (449, 2560, 1024), (704, 1856, 320), (64, 64, 1 << 28)]),
                         (t64x128, [(1025, 1536, 384), (1087, 1536, 448), (512, 3072, 768)]),
                         (t128, [(2049, 1152, 384), (2175, 1152, 1536), (4096, 768, 832)]),
