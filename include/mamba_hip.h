@@ -271,7 +271,9 @@ int mamba_rmsnorm_fwd(const void *x, const float *w, void *y, int64_t M, int64_t
  *
  * mamba_block_fwd encodes L tokens of `batch` sequences (prefill): hidden, hidden_out (batch,L,d_model);
  * conv_state_in / h0 (nullable) carry a previous piece of the sequence, conv_state_out / h_final
- * (nullable) receive the states after the last token.  hidden_out may be hidden itself.
+ * (nullable) receive the states after the last token.  hidden_out may be hidden itself.  conv_state_out may be conv_state_in; on
+ * contexts of few rows, whose conv is then formed in a launch of its own behind a product that sums k in another order, results can differ
+ * from those of a call with separate buffers by a rounding to bf16 of x and z.
  * mamba_block_step advances n_out draft branches by one token (decode): branch j continues from
  * the states of branch parent_idx[j] of the source caches (n_in rows); with parent_idx NULL the
  * step is in place (sources == destinations, n_in == n_out).  hidden, hidden_out: (n_out, d_model).

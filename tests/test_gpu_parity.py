@@ -1503,6 +1503,11 @@ def test_block_x_and_dt_projection_in_one_pass(m, B, L, D, R):
     check_block_stages(m, blk, w64, hid)
 
 
+def few_outputs(rows, D):
+    """Of the products below: whether in_proj as a call of its own is taken by the kernels whose wavefronts share k."""
+    return rows * D <= 200000
+
+
 @pytest.mark.parametrize("B,L,dm,D", [(1, 64, 256, 64), (1, 65, 256, 128), (2, 63, 320, 64), (3, 67, 256, 192), (64, 1, 256, 64), (50, 2, 256, 128),
                                       (30, 3, 256, 64), (5, 125, 256, 320),                             # 64 x 64 tiles
                                       (1, 100, 2560, 5120),                                             # 64 x 128
@@ -1513,8 +1518,8 @@ def test_block_x_and_dt_projection_in_one_pass(m, B, L, D, R):
 def test_block_conv_in_the_way_in(m, B, L, dm, D):
     """The conv formed from finished tiles of in_proj: full and moved row blocks, sequences that start and end inside a tile, at its first
     rows and at its last, and that are shorter than the window; with inputs carried in and without, stage by stage.  What it replaces,
-    in_proj and the conv as calls of their own, rounds in the same places: the same values, but for a product that gets its sums in
-    another order there."""
+    in_proj and the conv as calls of their own, rounds in the same places: the same bits, but for the products of few tiles, whose
+    k the wavefronts share there and which so get their sums in another order."""
     say(B=B, L=L, dm=dm, D=D)
     rng = np.random.default_rng(B * 1000 + L + D + dm)
     w, w64, blk = make_block(m, rng, dm, D, 16, 4, 32)
@@ -1529,7 +1534,10 @@ def test_block_conv_in_the_way_in(m, B, L, dm, D):
     x, z = m.mamba_linear_fwd(u, blk.w["in_proj_w"], splits=(D, D))
     xc, state1 = m.mamba_conv1d_fwd(x.view(B, L, D), blk.w["conv_w"], blk.w.get("conv_b"), conv_state_in=to_dev(conv_in))
     for got, ref in ((st["z"], z), (st["x_c"], xc.view(B * L, D)), (state, state1)):
-        assert (got != ref).float().mean().item() < 2e-3          # rounding flips of sums in another order
+        if few_outputs(B * L, D):
+            assert (got != ref).float().mean().item() < 2e-3      # rounding flips of sums in another order
+        else:
+            assert torch.equal(got, ref)
     # in place on the carried inputs: the two calls, to the bit
     s = to_dev(conv_in).clone()
     m.mamba_block_fwd(blk, to_dev(hid), conv_state_in=s, conv_state_out=s, workspace=ws)
@@ -1539,6 +1547,7 @@ def test_block_conv_in_the_way_in(m, B, L, dm, D):
 @pytest.mark.parametrize("B,L,dm,D,R", [(1, 4, 64, 256, 16), (1, 17, 64, 1536, 48), (2, 33, 64, 768, 24), (1, 3, 64, 256, 16),   # shorter than a call's own
                                         (1, 16, 64, 1536, 48), (3, 16, 64, 1536, 48), (1, 15, 64, 1024, 96),   # one chunk, taken and not; dt apart
                                         (1, 64, 64, 64, 8), (3, 65, 64, 96, 16), (1, 256, 64, 512, 24), (1, 256, 128, 1000, 40),      # 2 or 4 channels
+                                        (1, 300, 64, 768, 48), (1, 384, 64, 1000, 40),                                  # 4 channels, 6 tokens to a lane
                                         (1, 255, 64, 1536, 48), (1, 257, 64, 1536, 64), (1, 511, 64, 1000, 56), (1, 512, 64, 1528, 48),  # 4 or 6
                                         (1, 513, 64, 1536, 48), (1, 300, 64, 1536, 72)])                                                # not taken
 def test_block_dt_projection_in_the_scan(m, B, L, dm, D, R):

@@ -29,6 +29,7 @@ extern "C" int lanes_call(int64_t batch, int64_t L, int64_t D, int64_t N) { retu
 extern "C" int lanes_block(int64_t batch, int64_t L, int64_t D, int64_t N, int64_t dt_rank, int64_t chunks)
 { return mamba::scan_lanes_in_block(batch, L, D, N, dt_rank, chunks); }
 extern "C" int lanes_low_dt(int64_t batch, int64_t L, int64_t D, int64_t dt_rank) { return mamba::scan_lanes_takes_low_dt(batch, L, D, dt_rank); }
+extern "C" int lanes_channels(int64_t batch, int64_t L, int64_t D) { return mamba::lanes_channels(batch, L, D); }
 extern "C" int lanes_tokens(int64_t batch, int64_t L, int64_t D, int bf16) { return mamba::lanes_tau(batch, L, D, bf16 != 0); }
 extern "C" int xdt(int64_t M, int64_t d_inner, int64_t dt_rank, int64_t N, unsigned *groups)
 { return mamba::xdt_plan(M, d_inner, dt_rank, N, groups); }
@@ -61,6 +62,7 @@ def routes(tmp_path_factory):
     lib.lanes_call.argtypes = [i64] * 4
     lib.lanes_block.argtypes = [i64] * 6
     lib.lanes_low_dt.argtypes = [i64] * 4
+    lib.lanes_channels.argtypes = [i64] * 3
     lib.lanes_tokens.argtypes = [i64] * 3 + [i32]
     lib.route.argtypes = [i64] * 5
     lib.xdt.argtypes = [i64, i64, i64, i64, ctypes.POINTER(ctypes.c_uint)]
@@ -358,3 +360,24 @@ def test_blocks_take_the_lanes_scan_where_its_last_round_is_full(routes):
               (2, 8701, 704), (1, 6769, 2816), (2, 14536, 704), (1, 32768, 1536), (4, 8000, 1536), (1, 10000, 768), (8, 500, 1536), (1, 6000, 4096),
               (4, 40, 1536), (2, 1500, 2048), (8, 2000, 1536), (1, 6000, 512)]:
         assert not takes(*s), s
+
+
+def test_blocks_of_the_parity_tests_reach_the_kernels_they_are_there_for(routes):
+    """Every tile that forms the conv, on products whose launch apart sums in the same order and in another; every number of channels and
+    tokens of a scan that takes the dt projection along, and blocks on both sides of its lines."""
+    import test_gpu_parity as gpu
+    cases = lambda f: next(k.args[1] for k in f.pytestmark if k.name == "parametrize")
+    tiles = set()
+    for B, L, dm, D in cases(gpu.test_block_conv_in_the_way_in):
+        tiles.add(routes.conv_tiles(B * L, D, dm, 4))
+        few = KERNELS[routes.route(B * L, D, D, 0, dm)].startswith("kFew")
+        assert few == gpu.few_outputs(B * L, D), (B, L, dm, D)
+    assert tiles == set(range(1, 7))                               # never apart
+    low, apart = set(), 0
+    for B, L, dm, D, R in cases(gpu.test_block_dt_projection_in_the_scan):
+        lanes = routes.lanes_call(B, L, D, 16) or routes.lanes_block(B, L, D, 16, R, 1 if L <= 16 else 2)
+        if lanes and routes.lanes_low_dt(B, L, D, R):
+            low.add((routes.lanes_channels(B, L, D), routes.lanes_tokens(B, L, D, 1)))
+        else:
+            apart += 1
+    assert low == {(2, 4), (4, 4), (4, 6), (4, 8), (6, 4), (6, 6), (6, 8)} and apart >= 4
