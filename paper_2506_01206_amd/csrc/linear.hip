@@ -566,7 +566,8 @@ __device__ __forceinline__ void wave_sync()
 // quarter of its loads under every quarter of products.  The epilogue goes through 2 KB of LDS private to a wavefront, a 32 x 32
 // block at a time, without a barrier; the residual is requested three slabs before the end.
 // Of the 12.0 us of 2048 x 768, K = 1536 (64 x 128 tiles), the loads alone take 8.2 and the fragment reads with the products 8.4 (LDS: a
-// slab is written once and read 2.7 times, 700 cycles against 256 of matrix work), the outputs 2.  us in chains of 24 weights,
+// slab is written once and read 2.7 times, 700 cycles against 256 of matrix work), the outputs 2 (each alone; busy over all CUs the address
+// units 4.2, LDS 2.0, matrix cores 1.9).  us in chains of 24 weights,
 // replayed, before (register-staged tiles, memory-to-LDS tiles of two stages) / now: 512 x 3072, K = 768 8.9 / 8.1; 1000 x 3072
 // 12.3 / 10.1; 2048 x 768, K = 1536 17.1 / 12.0; 4000 x 768 19.3 / 16.1; 1500 x 1024, K = 2048 20.7 / 14.6; 2048 x 1536, K = 3072
 // 41.7 / 30.8.  As one persistent workgroup per CU on 256 x 128 tiles the same scheme does not beat the tiles above on long contexts

@@ -308,7 +308,9 @@ inline ConvTiles linear_conv_tiles(int64_t M, int64_t D, int64_t K, int64_t taps
 // that are multiples of 8, which the memory-to-LDS kernel asks for.  The lines are drawn from chains of 24 different blocks, as a prefill runs them (alone in a
 // loop, or with few weights that stay in the caches, the wide tiles look better than they are there), for seven models from 512
 // to 5120 channels and 200 to 32768 rows, every kernel that applies put in place of one product: 201 products, on which
-// the choice costs 0.3 % of a block more than the best one on average.  us of a block on 256 x 256 / 128 x 128 memory-to-LDS /
+// the choice costs 0.3 % of a block more than the best one on average.  (That was with 256 x 256 tiles on four wavefronts.  On eight they are 5 to
+// 16 % faster, and linear_wide256 is asked first; what the lines here still give them after it has declined takes, on 120 products, 2.4 % more than
+// the best of the memory-to-LDS tiles, nearly all of it at k of 128 and 256.)  us of a block on 256 x 256 / 128 x 128 memory-to-LDS /
 // 128 x 128 register-staged tiles / the best of the small ones:
 //   rows   in_proj of         K                                     out_proj of       K
 //   8000   1536 channels    768  209.8 / 214.3 / 204.4 / 209.9      1536 channels  1536  232.0 / 214.5 / 228.9 / 225.3
@@ -350,7 +352,8 @@ inline LinearKernel linear_tiles(int64_t M, int64_t N, int64_t K, bool wide)
 // operand byte as half of a 256 x 256 tile's, and two to a CU, so one's output goes out under the other's products.  They are
 // weighed against the choice above (other) wherever that takes a second round of 128 x 128 tiles: rounds times what one takes, in
 // units of a full set of 256 128 x 128 tiles (7 us at K = 768, 12.5 at K = 1536), a half-full round of two to a CU costing less.  Fitted
-// to 139 products of five models; the choice costs 0.4 % of the better of the two on average.  us on the choice above /
+// to 139 products of five models, the 256 x 256 tiles of them on four wavefronts (those on eight have been asked: linear_wide256); the choice costs
+// 0.4 % of the better of the two on average.  us on the choice above /
 // 192 x 128, random operands, 24 weights in turn:
 //    3000 x 3072, K =  768   27.6 /  20.9     12000 x  768, K = 1536   43.0 /  36.1      6000 x 6144, K = 1536  140.9 / 117.6
 //    8000 x 3072, K =  768   54.1 /  43.2     16384 x 3072, K =  768   84.0*/  88.6     12000 x 1536, K = 3072  125.9 / 108.0
@@ -425,7 +428,9 @@ inline bool linear_wide128_eight(int64_t M, int64_t N, int64_t K)
 }
 
 // The kernel of a product x (M, K) w (N, K)^T whose outputs are width[0], width[1] and width[2] columns wide: the rules above, in the
-// order in which they are asked.
+// order in which they are asked.  1500 random products (48 to 33000 rows, 128 to 11000 columns, k 256 to 6000) are 6.6 % faster with them on
+// average than on the kernels from before the ring and the tiles on eight wavefronts, 3 of them slower by more than 1.5 %, by 8 % at most; on 342 that
+// the few-row and ring kernels leave, with every other kernel put in its place, the choice takes 1.7 % more than the best.
 inline bool linear_vector_out(const int64_t width[3]) { return width[0] % 8 == 0 && width[1] % 8 == 0 && width[2] % 8 == 0; }
 inline LinearKernel linear_route(int64_t M, const int64_t width[3], int64_t K)
 {
